@@ -261,11 +261,11 @@ int omni_sparse_prefill(const omni_layer_desc* desc, const void* Q, const void* 
  *   before the call returns.
  * Outputs have the padded batch's shapes ([batch, n_q_heads, n_tokens] for scores,
  * q_idx and key_scores, as omni_sparse_attn_fwd / _bwd take them); rows and list
- * entries beyond a sequence's length / counts are unspecified.  The kernels of a
- * sequence are sized to that sequence and are launched sequence after sequence on
- * the caller's stream.  Padding rows of Q and K are never read.
- * Workspace: OMNI_CALL_PREFILL_SELECT with param = probe_block (as for the padded
- * length; one sequence uses it at a time).
+ * entries beyond a sequence's length / counts are unspecified.  Sequences go through
+ * the selection's launches together, as many at a time as the workspace holds (32 at
+ * most).  Padding rows of Q and K are never read.
+ * Workspace: OMNI_CALL_PREFILL_SELECT with param = probe_block for desc; the one of a
+ * descriptor with batch 1 suffices (one sequence at a time then).
  */
 int omni_prefill_select_varlen(const omni_layer_desc* desc, const void* Q, const void* K,
                                const int32_t* seq_tokens, const int32_t* seq_vis_begin,

@@ -1,5 +1,6 @@
 // C-ABI entry points: argument validation, workspace carving, dispatch.
 // Everything here runs on the host; no entry point allocates device memory.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -129,9 +130,24 @@ void prof_end(int id, hipStream_t st) {
 
 static bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
+// The partial sums of the probe keys are used up before the probe's scratch is first written: they share the space.
 static size_t prefill_select_ws(const Layer& L, int dtype, int pb) {
-  return align_up(score_queries_ws(L), 256) + align_up(probe_ws(L, dtype, pb), 256) +
-         align_up(budget_stats_ws(L), 256) + select_ws(L);
+  return std::max(score_queries_ws(L), align_up(probe_ws(L, dtype, pb), 256) + select_lists_ws(L));
+}
+
+// The selection of a prefill step (scores, probe, both lists) on a workspace of prefill_select_ws bytes.
+static int run_prefill_select(const Layer& L, int dtype, const Ragged& rg, const void* Q, const void* K, int q_mode,
+                              float q_param, float recall_p, int pb, int budget_mode, float* probe_keys, float* scores,
+                              int* q_idx, int* q_cnt, float* key_scores, double* kurtosis, int* flattest, int* budget,
+                              float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st, SelectSource* sel) {
+  char* ws_lists = static_cast<char*>(ws) + align_up(probe_ws(L, dtype, pb), 256);
+  int rc = run_probe_keys(L, dtype, K, probe_keys, ws, st, rg);
+  if (rc != OMNI_OK) return rc;
+  // one pass over Q: lazy/active scores and pooled queries; then the two probe passes over K
+  rc = run_probe(L, dtype, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
+  if (rc != OMNI_OK) return rc;
+  return run_select_lists(L, rg, scores, q_mode, q_param, q_idx, q_cnt, key_scores, recall_p, budget_mode, kurtosis,
+                          flattest, budget, recall, kv_idx, b_cap, ws_lists, st, sel);
 }
 
 static size_t kv_budget_ws(const Layer& L, int dtype, int pb) {
@@ -438,17 +454,9 @@ int omni_prefill_select(const omni_layer_desc* desc, const void* Q, const void* 
   L.bph = budget_mode == 2;
   CHECK(check_ws(ws, ws_bytes, prefill_select_ws(L, desc->dtype, probe_block)));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws_score = static_cast<char*>(ws);
-  char* ws_probe = ws_score + align_up(score_queries_ws(L), 256);
-  char* ws_stats = ws_probe + align_up(probe_ws(L, desc->dtype, probe_block), 256);
-  char* ws_sel = ws_stats + align_up(budget_stats_ws(L), 256);
-  CHECK(run_probe_keys(L, desc->dtype, K, probe_keys, ws_score, st));
-  // one pass over Q: lazy/active scores and pooled queries; then the two probe passes over K
-  CHECK(run_probe(L, desc->dtype, Q, K, probe_block, key_scores, ws_probe, st, probe_keys, scores));
-  CHECK(run_select_queries(L, scores, q_mode, q_param, q_idx, q_cnt, ws_sel, st));
-  // the recall pass already finds each head's cut for its budget: the key lists are compacted from it
-  CHECK(run_budget_stats(L, key_scores, recall_p, budget_mode, kurtosis, flattest, budget, recall, ws_stats, st, b_cap));
-  return run_select_kv_from_stats(L, key_scores, ws_stats, b_cap, kv_idx, ws_sel, st);
+  return run_prefill_select(L, desc->dtype, Ragged{}, Q, K, q_mode, q_param, recall_p, probe_block, budget_mode, probe_keys,
+                            scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st,
+                            nullptr);
 }
 
 size_t omni_sparse_prefill_workspace_bytes(const omni_layer_desc* desc, int32_t probe_block, int32_t b_cap) {
@@ -483,18 +491,11 @@ int omni_sparse_prefill(const omni_layer_desc* desc, const void* Q, const void* 
   const size_t sel_bytes = align_up(prefill_select_ws(L, desc->dtype, probe_block), 256);
   CHECK(check_ws(ws, ws_bytes, sel_bytes + attn_fwd_ws(L, desc->dtype, b_cap, true)));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws_score = static_cast<char*>(ws);
-  char* ws_probe = ws_score + align_up(score_queries_ws(L), 256);
-  char* ws_stats = ws_probe + align_up(probe_ws(L, desc->dtype, probe_block), 256);
-  char* ws_sel = ws_stats + align_up(budget_stats_ws(L), 256);
   char* ws_fwd = static_cast<char*>(ws) + sel_bytes;
-  CHECK(run_probe_keys(L, desc->dtype, K, probe_keys, ws_score, st));
-  CHECK(run_probe(L, desc->dtype, Q, K, probe_block, key_scores, ws_probe, st, probe_keys, scores));
-  CHECK(run_select_queries(L, scores, q_mode, q_param, q_idx, q_cnt, ws_sel, st));
-  CHECK(run_budget_stats(L, key_scores, recall_p, budget_mode, kurtosis, flattest, budget, recall, ws_stats, st, b_cap));
-  // the chunk counts of the key lists; the lists themselves come out of the attention's gather
-  SelectSource src;
-  CHECK(run_select_kv_counts(L, key_scores, ws_stats, b_cap, kv_idx, ws_sel, &src, st));
+  SelectSource src;                  // the key lists come out of the attention's gather
+  CHECK(run_prefill_select(L, desc->dtype, Ragged{}, Q, K, q_mode, q_param, recall_p, probe_block, budget_mode, probe_keys,
+                           scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st,
+                           &src));
   return run_attn_fwd(L, desc->dtype, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws_fwd, true, st, &src);
 }
 
@@ -524,36 +525,47 @@ int omni_prefill_select_varlen(const omni_layer_desc* desc, const void* Q, const
     if (!(v0 >= 0 && v0 < v1 && v1 <= n)) OMNI_FAIL(OMNI_ERR_INVALID, "sequence %d: need 0 <= vis_begin < vis_end <= seq_tokens", b);
     if (desc->sink_index >= n) OMNI_FAIL(OMNI_ERR_INVALID, "sequence %d: sink_index beyond the sequence", b);
   }
-  Layer Lmax = make_layer(desc);
-  Lmax.B = 1;
-  Lmax.bph = budget_mode == 2;
-  CHECK(check_ws(ws, ws_bytes, prefill_select_ws(Lmax, desc->dtype, probe_block)));
+  Layer L = make_layer(desc);
+  L.bph = budget_mode == 2;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t es = desc->dtype == OMNI_BF16 ? 2 : 4;
   const long long Hq = desc->n_q_heads, Hkv = desc->n_kv_heads, Np = desc->n_tokens, D = desc->head_dim;
+  // As many sequences in one set of launches as the workspace holds, at least one.  Every kernel works on a sequence's
+  // own length inside the padded strides, so a sequence gives bit for bit what it gives alone.  (One after the other,
+  // four sequences of 2.7k to 8k tokens took 72 launches of 5 to 17 us that each left most of the chip idle: 553 us.)
+  int longest = 1, n_vis = 1;
   for (int b = 0; b < desc->batch; ++b) {
-    // the sequence as a layer of its own inside the padded tensors: its length and visual range, the batch's row
-    // pitch; every kernel is sized to the sequence, and the result is bit for bit what the sequence gives alone
-    Layer L = Lmax;
-    L.N = seq_tokens[b];
-    L.v0 = seq_vis_begin[b];
-    L.v1 = seq_vis_end[b];
+    longest = std::max(longest, seq_tokens[b]);
+    n_vis = std::max(n_vis, seq_vis_end[b] - seq_vis_begin[b]);
+  }
+  L.N = longest;                     // sizes grids and scratch; L.ld stays the padded batch's row pitch
+  L.v0 = 0;
+  L.v1 = n_vis;
+  int together = std::min<int>(desc->batch, kMaxRagged);
+  for (; together > 1; --together) {
+    L.B = together;
+    if (ws_bytes >= prefill_select_ws(L, desc->dtype, probe_block)) break;
+  }
+  L.B = together;
+  CHECK(check_ws(ws, ws_bytes, prefill_select_ws(L, desc->dtype, probe_block)));
+  for (int b0 = 0; b0 < desc->batch; b0 += together) {
+    const int nb = std::min(together, desc->batch - b0);
+    Ragged rg{};
+    rg.on = 1;
+    for (int j = 0; j < nb; ++j) {
+      rg.n[j] = seq_tokens[b0 + j];
+      rg.v0[j] = seq_vis_begin[b0 + j];
+      rg.v1[j] = seq_vis_end[b0 + j];
+    }
+    L.B = nb;
+    const long long b = b0;
     const char* Qb = static_cast<const char*>(Q) + (size_t)b * desc->q_stride[0] * es;
     const char* Kb = static_cast<const char*>(K) + (size_t)b * desc->kv_stride[0] * es;
-    float* probe_b = probe_keys + b * Hkv * 2 * D;
-    float* scores_b = scores + b * Hq * Np;
-    float* a_b = key_scores + b * Hq * Np;
-    int32_t* budget_b = budget + (budget_mode == 2 ? b * Hq : b);
-    char* ws_score = static_cast<char*>(ws);
-    char* ws_probe = ws_score + align_up(score_queries_ws(L), 256);
-    char* ws_stats = ws_probe + align_up(probe_ws(L, desc->dtype, probe_block), 256);
-    char* ws_sel = ws_stats + align_up(budget_stats_ws(L), 256);
-    CHECK(run_probe_keys(L, desc->dtype, Kb, probe_b, ws_score, st));
-    CHECK(run_probe(L, desc->dtype, Qb, Kb, probe_block, a_b, ws_probe, st, probe_b, scores_b));
-    CHECK(run_select_queries(L, scores_b, q_mode, q_param, q_idx + b * Hq * Np, q_cnt + b * Hq, ws_sel, st));
-    CHECK(run_budget_stats(L, a_b, recall_p, budget_mode, kurtosis + b * Hq, flattest + b, budget_b, recall + b * Hq,
-                           ws_stats, st, b_cap));
-    CHECK(run_select_kv_from_stats(L, a_b, ws_stats, b_cap, kv_idx + b * Hq * b_cap, ws_sel, st));
+    CHECK(run_prefill_select(L, desc->dtype, rg, Qb, Kb, q_mode, q_param, recall_p, probe_block, budget_mode,
+                             probe_keys + b * Hkv * 2 * D, scores + b * Hq * Np, q_idx + b * Hq * Np, q_cnt + b * Hq,
+                             key_scores + b * Hq * Np, kurtosis + b * Hq, flattest + b,
+                             budget + (budget_mode == 2 ? b * Hq : b), recall + b * Hq, kv_idx + b * Hq * b_cap, b_cap, ws,
+                             st, nullptr));
   }
   return OMNI_OK;
 }

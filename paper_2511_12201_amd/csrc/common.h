@@ -66,6 +66,14 @@ Layer make_layer(const omni_layer_desc* d);
 // Entry of a budget array that holds the key count of head bh (b = bh / Hq).
 __host__ __device__ inline int budget_slot(int bph, int b, int bh) { return bph ? bh : b; }
 
+// Sequences of different lengths in one padded batch (omni_prefill_select_varlen): lengths and visual ranges by value,
+// so that one launch serves them all; the layer then holds the padded length, which sizes grids and strides.
+constexpr int kMaxRagged = 32;
+struct Ragged {
+  int on;                        // 0: every batch item has the layer's own length and range
+  int n[kMaxRagged], v0[kMaxRagged], v1[kMaxRagged];
+};
+
 // Optional HIP-event timing of individual kernels (omni_profile_* in the C ABI).
 enum ProfId {
   kProfAttnFwd = 0, kProfPack = 1, kProfClear = 2, kProfPool = 3, kProfProbeLse = 4, kProfProbeSum = 5,
@@ -210,7 +218,31 @@ __device__ __forceinline__ int upper_count(const int* __restrict__ a, int n, int
   return lo;
 }
 
+__device__ __forceinline__ int seq_len(const Layer& L, const Ragged& rg, int b) { return rg.on ? rg.n[b] : L.N; }
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+
+// Lane exchange on the vector ALU (data-parallel primitives): lanes without a source, and rows outside row_mask, get 0.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned dpp_or_zero(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, true);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned long long dpp_or_zero(unsigned long long v) {
+  const unsigned lo = dpp_or_zero<CTRL, ROW_MASK>((unsigned)v), hi = dpp_or_zero<CTRL, ROW_MASK>((unsigned)(v >> 32));
+  return ((unsigned long long)hi << 32) | lo;
+}
+// Inclusive sum over the lanes up to this one: six vector-ALU steps where shuffles would be six trips through LDS.
+template <typename U>
+__device__ __forceinline__ U wave_scan(U v) {
+  v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1, 2, 4, 8: inside rows of 16
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {

@@ -9,7 +9,8 @@ namespace omni {
 size_t score_queries_ws(const Layer& L);
 int run_score_queries(const Layer& L, int dtype, const void* Q, const void* K, float* probe, float* scores, void* ws,
                       hipStream_t st);
-int run_probe_keys(const Layer& L, int dtype, const void* K, float* probe, void* ws, hipStream_t st);
+int run_probe_keys(const Layer& L, int dtype, const void* K, float* probe, void* ws, hipStream_t st,
+                   const Ragged& rg = Ragged{});
 
 // select.hip
 size_t select_ws(const Layer& L);
@@ -19,12 +20,10 @@ int run_select_kv(const Layer& L, const float* key_scores, const int* budget, in
                   hipStream_t st);
 size_t budget_stats_ws(const Layer& L);
 int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, int budget_mode, double* kurt,
-                     int* flattest, int* budget, float* recall, void* ws, hipStream_t st, int k_cap = 0x7fffffff);
-int run_select_kv_from_stats(const Layer& L, const float* key_scores, void* stats_ws, int b_cap, int* kv_idx,
-                             void* ws, hipStream_t st);
+                     int* flattest, int* budget, float* recall, void* ws, hipStream_t st);
 // The key lists as the packing kernel can form them itself: the scores, each head's cut (threshold key and number of
 // cut-valued elements to take) and, per chunk of kSelectChunk elements, how many kept elements precede it.  out
-// receives the lists ([B*Hq, out_stride], what run_select_kv_from_stats writes).
+// receives the lists ([B*Hq, out_stride], what run_select_lists writes without it).
 constexpr int kSelectChunk = 1024;
 struct SelectSource {
   const float* x;          // [B*Hq, ld]
@@ -36,9 +35,13 @@ struct SelectSource {
   int* out;
   int out_stride;
 };
-// the counting half of run_select_kv_from_stats: fills *src (pointers into the two workspaces), writes no list
-int run_select_kv_counts(const Layer& L, const float* key_scores, void* stats_ws, int b_cap, int* kv_idx, void* ws,
-                         SelectSource* src, hipStream_t st);
+// Both lists of a prefill step from the two score arrays: statistics of the key scores, the cuts, the lists (three
+// launches).  sel not null: the key lists are not written but described in *sel (pointers into the workspace).
+size_t select_lists_ws(const Layer& L);
+int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int q_mode, float q_param, int* q_idx,
+                     int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,
+                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st,
+                     SelectSource* sel = nullptr);
 int run_visual_subset(const Layer& L, const int* kv_idx, const int* budget, int b_cap, int* vis_idx, int* vis_cnt,
                       hipStream_t st);
 size_t group_subset_ws(const Layer& L);
@@ -49,7 +52,7 @@ int run_group_subset(const Layer& L, const int* kv_idx, const int* budget, int b
 size_t probe_ws(const Layer& L, int dtype, int pb);
 // probe_keys / scores not null: the pooling pass over Q also writes the lazy/active query scores
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
-              hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr);
+              hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
 
 // pack.hip (outputs that are nullptr are skipped; Kt / Vt / Qt / dOt exist for bf16 only; Vt holds f16 values)
 // sel not null (per_q_head only, src_idx ignored): the kernel forms the lists from *sel and writes them to sel->out

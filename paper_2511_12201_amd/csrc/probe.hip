@@ -35,7 +35,7 @@ constexpr int kQbarTerms = 2;
 // SCORE: the same pass over Q also writes the lazy/active score of every row (paper Sec. "Query Selection",
 // probe-softmax equation), with the arithmetic of the stand-alone scoring kernel, so that Q is read once.
 template <typename T, int D, bool SCORE>
-__global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restrict__ Q, Layer L, int pb, int nblk,
+__global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restrict__ Q, Layer L, Ragged rg, int pb, int nblk,
                                                                float* __restrict__ qbar, u16* __restrict__ qsplit,
                                                                const float* __restrict__ probe_keys,
                                                                float* __restrict__ scores) {
@@ -47,7 +47,9 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
   const int b = bh / L.Hq, i = bh % L.Hq;
   const T* base = Q + b * L.qs[0] + i * L.qs[1];
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
-  const int row_begin = min(j * pb, L.N), row_end = min(L.N, row_begin + pb);
+  const int N = seq_len(L, rg, b);
+  const int row_begin = min(j * pb, N), row_end = min(N, row_begin + pb);
+  if (rg.on && j >= cdiv(cdiv(N, pb), 32) * 32) return;       // beyond the last row block of a shorter sequence
   float acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
@@ -145,7 +147,7 @@ __host__ __device__ constexpr int probe_keys_per_wg() {
 // PASS 1: partial (max, sum) per pooled row for this workgroup's key range.
 // PASS 2: column sums.
 template <int D, int PASS>
-__global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __restrict__ K, Layer L, int pb, int nblk,
+__global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __restrict__ K, Layer Lp, Ragged rg, int pb, int nblk_p,
                                                             int nchunk, const float* __restrict__ qbar,
                                                             float* __restrict__ part_m, float* __restrict__ part_l,
                                                             const float* __restrict__ lse2w,
@@ -160,7 +162,11 @@ __global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __rest
   __shared__ float sRedM[4][32], sRedL[4][32];
 
   const int chunk = blockIdx.x, bh = blockIdx.y;
-  const int b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
+  const int b = bh / Lp.Hq, i = bh % Lp.Hq, g = i / Lp.G;
+  Layer L = Lp;                                  // the sequence's own length; nblk_p and nchunk are the padded strides
+  L.N = seq_len(Lp, rg, b);
+  if (chunk * KPG >= L.N) return;
+  const int nblk = cdiv(L.N, pb), nrb_p = cdiv(nblk_p, 32);
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int ln = lane & 31, h = lane >> 5;
   const int k0 = chunk * KPG + wave * KPW;       // first key of this wavefront
@@ -185,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __rest
 
   const int nrb = cdiv(nblk, 32);
   const int jb0 = L.causal ? ((chunk * KPG) / pb) / 32 : 0;
-  const float* qsrc = qbar + (long long)bh * nblk * D;
+  const float* qsrc = qbar + (long long)bh * nblk_p * D;
 
   for (int jb = jb0; jb < nrb; ++jb) {
     __syncthreads();          // previous iteration's LDS reads are done
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __rest
     }
     if (PASS == 2 && threadIdx.x < 32) {
       const int j = jb * 32 + threadIdx.x;
-      sLse[threadIdx.x] = j < nblk ? lse2w[(long long)bh * nrb * 32 + j] : 0.f;
+      sLse[threadIdx.x] = j < nblk ? lse2w[(long long)bh * nrb_p * 32 + j] : 0.f;
     }
     __syncthreads();
 
@@ -256,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void probe_f32_kernel(const float* __rest
           const float mw = sRedM[w][threadIdx.x];
           Ls += mw == -INFINITY ? 0.f : sRedL[w][threadIdx.x] * exp2f(mw - Mr);
         }
-        const long long o = ((long long)bh * nblk + jb * 32 + threadIdx.x) * nchunk + chunk;
+        const long long o = ((long long)bh * nblk_p + jb * 32 + threadIdx.x) * nchunk + chunk;
         part_m[o] = M;
         part_l[o] = Ls;
       }
@@ -323,7 +329,7 @@ __device__ __forceinline__ float half_wave_reduce_scatter(float (&v)[32], int ln
 // PASS 1: (max, sum) of every pooled row over this workgroup's 256 keys -> part_m / part_l.
 // PASS 2: a[head, key] = sum over pooled rows of exp2(s2 - lse2w[row]).
 template <int D, int PASS>
-__global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __restrict__ K, Layer L, int pb, int nblk,
+__global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __restrict__ K, Layer Lp, Ragged rg, int pb, int nblk_p,
                                                              int nchunk, const u16* __restrict__ qsplit,
                                                              float* __restrict__ part_m, float* __restrict__ part_l,
                                                              const float* __restrict__ lse2w,
@@ -340,9 +346,13 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
   __shared__ float sRedM[2][4][32], sRedL[2][4][32];
   __shared__ __attribute__((aligned(256))) float sLse[NS][64];
 
-  const int ngrp = L.B * L.Hkv;
+  const int ngrp = Lp.B * Lp.Hkv;
   const int chunk = blockIdx.x / ngrp, bg = blockIdx.x % ngrp;
-  const int b = bg / L.Hkv, g = bg % L.Hkv;
+  const int b = bg / Lp.Hkv, g = bg % Lp.Hkv;
+  Layer L = Lp;                                // the sequence's own length; nblk_p and nchunk are the padded strides
+  L.N = seq_len(Lp, rg, b);
+  if (chunk * KPG >= L.N) return;
+  const int nblk = cdiv(L.N, pb), nrb_p = cdiv(nblk_p, 32);
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int ln = lane & 31, h = lane >> 5;
@@ -359,7 +369,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
 
   auto issue = [&](int jh, int jb, int stage) {
     const unsigned char* src =
-        reinterpret_cast<const unsigned char*>(qsplit) + ((long long)(bh0 + jh) * nrb + jb) * kStage;
+        reinterpret_cast<const unsigned char*>(qsplit) + ((long long)(bh0 + jh) * nrb_p + jb) * kStage;
 #pragma unroll
     for (int q = 0; q < IPW; ++q)
       gload_lds16(src + q * 4096, lane_off, lds_base + stage * kStage + q * 4096 + wave * 1024);
@@ -367,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
     // whose wait would also drain the DMA queue -- sits in the loop; every wavefront fetches them (same bytes, same
     // place) so that all wavefronts have the same number of loads in flight
     if (PASS == 2)
-      gload_lds4(lse2w + ((long long)(bh0 + jh) * nrb + jb) * 32 + lane, lse_base + stage * 256);
+      gload_lds4(lse2w + ((long long)(bh0 + jh) * nrb_p + jb) * 32 + lane, lse_base + stage * 256);
   };
 
   // block `it` of this workgroup is (head jh, row block jb); the issue cursor runs NS-1 blocks ahead
@@ -418,7 +428,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
         const float mw = sRedM[buf][w][lane];
         Ls += mw == -INFINITY ? 0.f : sRedL[buf][w][lane] * fast_exp2(mw - Mr);
       }
-      const long long o = ((long long)(bh0 + jh) * nblk + j) * nchunk + chunk;
+      const long long o = ((long long)(bh0 + jh) * nblk_p + j) * nchunk + chunk;
       part_m[o] = M;
       part_l[o] = Ls;
     }
@@ -529,16 +539,17 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
 
 // One wavefront per pooled row: combine the per-chunk (max, sum) into
 // lse2w[j] = log2(sum_k 2^{s2_jk}) - log2(w_j).
-__global__ __launch_bounds__(kThreads) void probe_lse_kernel(Layer L, int pb, int nblk, int nchunk, int keys_per_chunk,
+__global__ __launch_bounds__(kThreads) void probe_lse_kernel(Layer L, Ragged rg, int pb, int nblk, int nchunk, int keys_per_chunk,
                                                             const float* __restrict__ part_m,
                                                             const float* __restrict__ part_l,
                                                             float* __restrict__ lse2w) {
   const int bh = blockIdx.y;
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= nblk) return;
+  const int N = seq_len(L, rg, bh / L.Hq);
+  if (j >= cdiv(N, pb)) return;
   const int lane = lane_id();
-  const int row_end = min((j + 1) * pb, L.N);
-  const int vis_end = L.causal ? row_end : L.N;
+  const int row_end = min((j + 1) * pb, N);
+  const int vis_end = L.causal ? row_end : N;
   const int nvis = cdiv(vis_end, keys_per_chunk);            // chunks that hold a visible key
   const float* pm = part_m + ((long long)bh * nblk + j) * nchunk;
   const float* pl = part_l + ((long long)bh * nblk + j) * nchunk;
@@ -583,7 +594,7 @@ ProbeWs carve_probe(Arena& a, const Layer& L, int pb) {
 
 template <typename T, int D>
 int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* key_scores, void* ws, hipStream_t st,
-                 const float* probe_keys, float* scores) {
+                 const float* probe_keys, float* scores, const Ragged& rg) {
   Arena a(ws);
   ProbeWs w = carve_probe<T>(a, L, pb);
   const int nblk = cdiv(L.N, pb);
@@ -595,10 +606,10 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
     const int pooled_rows = sizeof(T) == 2 ? cdiv(nblk, 32) * 32 : nblk;
     if (scores) {
       hipLaunchKernelGGL((pool_queries_kernel<T, D, true>), dim3(pooled_rows, BH), dim3(kThreads), 0, st,
-                         static_cast<const T*>(Q), L, pb, nblk, w.qbar, w.qsplit, probe_keys, scores);
+                         static_cast<const T*>(Q), L, rg, pb, nblk, w.qbar, w.qsplit, probe_keys, scores);
     } else {
       hipLaunchKernelGGL((pool_queries_kernel<T, D, false>), dim3(pooled_rows, BH), dim3(kThreads), 0, st,
-                         static_cast<const T*>(Q), L, pb, nblk, w.qbar, w.qsplit, (const float*)nullptr,
+                         static_cast<const T*>(Q), L, rg, pb, nblk, w.qbar, w.qsplit, (const float*)nullptr,
                          (float*)nullptr);
     }
     OMNI_LAUNCH_CHECK();
@@ -608,16 +619,16 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
     const int nwg = nchunk * L.B * L.Hkv;
     {
       ProfScope prof__(kProfProbeLse, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, pb, nblk, nchunk, w.qsplit,
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
                          w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr);
       OMNI_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, pb, nblk, nchunk, KPG,
+    hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
                        w.part_m, w.part_l, w.lse2w);
     OMNI_LAUNCH_CHECK();
     {
       ProfScope prof__(kProfProbeSum, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, pb, nblk, nchunk, w.qsplit,
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
                          (float*)nullptr, (float*)nullptr, w.lse2w, key_scores);
       OMNI_LAUNCH_CHECK();
     }
@@ -625,17 +636,17 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
   } else {
   {
     ProfScope prof__(kProfProbeLse, st);
-    hipLaunchKernelGGL((probe_f32_kernel<D, 1>), dim3(nchunk, BH), dim3(kThreads), 0, st, static_cast<const T*>(K), L, pb,
-                       nblk, nchunk, w.qbar, w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr);
+    hipLaunchKernelGGL((probe_f32_kernel<D, 1>), dim3(nchunk, BH), dim3(kThreads), 0, st, static_cast<const T*>(K), L, rg,
+                       pb, nblk, nchunk, w.qbar, w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr);
     OMNI_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, pb, nblk, nchunk, KPG,
+  hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
                      w.part_m, w.part_l, w.lse2w);
   OMNI_LAUNCH_CHECK();
   {
     ProfScope prof__(kProfProbeSum, st);
-    hipLaunchKernelGGL((probe_f32_kernel<D, 2>), dim3(nchunk, BH), dim3(kThreads), 0, st, static_cast<const T*>(K), L, pb,
-                       nblk, nchunk, w.qbar, (float*)nullptr, (float*)nullptr, w.lse2w, key_scores);
+    hipLaunchKernelGGL((probe_f32_kernel<D, 2>), dim3(nchunk, BH), dim3(kThreads), 0, st, static_cast<const T*>(K), L, rg,
+                       pb, nblk, nchunk, w.qbar, (float*)nullptr, (float*)nullptr, w.lse2w, key_scores);
     OMNI_LAUNCH_CHECK();
   }
   return OMNI_OK;
@@ -651,13 +662,13 @@ size_t probe_ws(const Layer& L, int dtype, int pb) {
 }
 
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
-              hipStream_t st, const float* probe_keys, float* scores) {
+              hipStream_t st, const float* probe_keys, float* scores, const Ragged& rg) {
   if (dtype == OMNI_BF16) {
-    if (L.D == 128) return launch_probe<u16, 128>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores);
-    return launch_probe<u16, 64>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores);
+    if (L.D == 128) return launch_probe<u16, 128>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
+    return launch_probe<u16, 64>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
   }
-  if (L.D == 128) return launch_probe<float, 128>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores);
-  return launch_probe<float, 64>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores);
+  if (L.D == 128) return launch_probe<float, 128>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
+  return launch_probe<float, 64>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
 }
 
 }  // namespace omni

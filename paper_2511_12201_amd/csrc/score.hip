@@ -16,7 +16,7 @@ constexpr int kThreads = 256;
 constexpr int kMeanRowsPerChunk = 256;     // ~1000 workgroups at 64k: enough to fill the memory system
 
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __restrict__ K, Layer L, int nchunk,
+__global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __restrict__ K, Layer L, Ragged rg, int nchunk,
                                                                    float* __restrict__ partial) {
   constexpr int E = Elem<T>::kPer16B;
   constexpr int LPR = D / E;              // lanes per row
@@ -27,8 +27,10 @@ __global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __r
   const int b = bg / L.Hkv, g = bg % L.Hkv;
   const T* base = K + b * L.ks[0] + g * L.ks[1];
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
-  const int row_begin = L.v0 + chunk * kMeanRowsPerChunk;
-  const int row_end = min(L.v1, row_begin + kMeanRowsPerChunk);
+  const int v1 = rg.on ? rg.v1[b] : L.v1;
+  const int row_begin = (rg.on ? rg.v0[b] : L.v0) + chunk * kMeanRowsPerChunk;
+  const int row_end = min(v1, row_begin + kMeanRowsPerChunk);
+  if (row_begin >= v1) return;             // a shorter sequence of a padded batch
   float acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
@@ -53,16 +55,18 @@ __global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __r
 constexpr int kFinalSplit = 8;
 
 template <typename T, int D>
-__global__ void probe_keys_finalize_kernel(const T* __restrict__ K, Layer L, int nchunk,
+__global__ void probe_keys_finalize_kernel(const T* __restrict__ K, Layer L, Ragged rg, int nchunk,
                                            const float* __restrict__ partial, float* __restrict__ probe) {
   const int bg = blockIdx.x;
   const int b = bg / L.Hkv, g = bg % L.Hkv;
   // blockDim.x = kFinalSplit * D: kFinalSplit interleaved partial sums per element, added in a fixed order
   __shared__ float part[kFinalSplit][128];
   const int t = threadIdx.x % D, k = threadIdx.x / D;
+  const int n_vis = rg.on ? rg.v1[b] - rg.v0[b] : L.v1 - L.v0;
+  const int chunks = cdiv(n_vis, kMeanRowsPerChunk);
   float s = 0.f;
 #pragma unroll 4
-  for (int c = k; c < nchunk; c += kFinalSplit) s += partial[((long long)bg * nchunk + c) * D + t];
+  for (int c = k; c < chunks; c += kFinalSplit) s += partial[((long long)bg * nchunk + c) * D + t];
   part[k][t] = s;
   __syncthreads();
   if (k != 0) return;
@@ -71,7 +75,7 @@ __global__ void probe_keys_finalize_kernel(const T* __restrict__ K, Layer L, int
   for (int j = 0; j < kFinalSplit; ++j) s += part[j][t];
   const T* sink = K + b * L.ks[0] + g * L.ks[1] + (long long)L.sink * L.ks[2];
   probe[((long long)bg * 2 + 0) * D + t] = Elem<T>::load(sink + t);
-  probe[((long long)bg * 2 + 1) * D + t] = s / (float)(L.v1 - L.v0);
+  probe[((long long)bg * 2 + 1) * D + t] = s / (float)n_vis;
 }
 
 // score = softmax([q.k_lazy, q.k_act] * scale)[1] = 1 / (1 + exp(-(q.(k_act - k_lazy)) * scale))
@@ -112,13 +116,14 @@ __global__ __launch_bounds__(kThreads) void score_queries_kernel(const T* __rest
 }
 
 template <typename T, int D>
-int launch_probe_keys(const Layer& L, const void* K, float* probe, float* partial, int nchunk, hipStream_t st) {
+int launch_probe_keys(const Layer& L, const Ragged& rg, const void* K, float* probe, float* partial, int nchunk,
+                      hipStream_t st) {
   const T* k = static_cast<const T*>(K);
-  hipLaunchKernelGGL((mean_key_partial_kernel<T, D>), dim3(nchunk, L.B * L.Hkv), dim3(kThreads), 0, st, k, L, nchunk,
-                     partial);
+  hipLaunchKernelGGL((mean_key_partial_kernel<T, D>), dim3(nchunk, L.B * L.Hkv), dim3(kThreads), 0, st, k, L, rg,
+                     nchunk, partial);
   OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL((probe_keys_finalize_kernel<T, D>), dim3(L.B * L.Hkv), dim3(kFinalSplit * D), 0, st, k, L, nchunk, partial,
-                     probe);
+  hipLaunchKernelGGL((probe_keys_finalize_kernel<T, D>), dim3(L.B * L.Hkv), dim3(kFinalSplit * D), 0, st, k, L, rg,
+                     nchunk, partial, probe);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
@@ -127,7 +132,7 @@ template <typename T, int D>
 int launch_score(const Layer& L, const void* Q, const void* K, float* probe, float* scores, float* partial,
                  int nchunk, hipStream_t st) {
   const T* q = static_cast<const T*>(Q);
-  const int rc = launch_probe_keys<T, D>(L, K, probe, partial, nchunk, st);
+  const int rc = launch_probe_keys<T, D>(L, Ragged{}, K, probe, partial, nchunk, st);
   if (rc != OMNI_OK) return rc;
   const int rows_per_block = 256;
   {
@@ -149,16 +154,16 @@ size_t score_queries_ws(const Layer& L) {
   return a.used();
 }
 
-int run_probe_keys(const Layer& L, int dtype, const void* K, float* probe, void* ws, hipStream_t st) {
+int run_probe_keys(const Layer& L, int dtype, const void* K, float* probe, void* ws, hipStream_t st, const Ragged& rg) {
   Arena a(ws);
   const int nchunk = score_mean_chunks(L);
   float* partial = a.take<float>((size_t)L.B * L.Hkv * nchunk * L.D);
   if (dtype == OMNI_BF16) {
-    if (L.D == 128) return launch_probe_keys<u16, 128>(L, K, probe, partial, nchunk, st);
-    return launch_probe_keys<u16, 64>(L, K, probe, partial, nchunk, st);
+    if (L.D == 128) return launch_probe_keys<u16, 128>(L, rg, K, probe, partial, nchunk, st);
+    return launch_probe_keys<u16, 64>(L, rg, K, probe, partial, nchunk, st);
   }
-  if (L.D == 128) return launch_probe_keys<float, 128>(L, K, probe, partial, nchunk, st);
-  return launch_probe_keys<float, 64>(L, K, probe, partial, nchunk, st);
+  if (L.D == 128) return launch_probe_keys<float, 128>(L, rg, K, probe, partial, nchunk, st);
+  return launch_probe_keys<float, 64>(L, rg, K, probe, partial, nchunk, st);
 }
 
 int run_score_queries(const Layer& L, int dtype, const void* Q, const void* K, float* probe, float* scores, void* ws,

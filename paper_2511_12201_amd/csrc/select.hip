@@ -21,306 +21,342 @@ namespace omni {
 namespace {
 
 constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kChunk = kSelectChunk;    // elements per compaction workgroup
 constexpr int kChunkThreads = 256;
 constexpr int kPerThread = kChunk / kChunkThreads;
 constexpr double kFixScale = 1099511627776.0;   // 2^40
 
+// a * 2^40 rounded towards zero, 0 for what is not positive, exact: the integer part of a * 2^8 and its fraction times
+// 2^32 are both exact in fp32.  (Through fp64 it is three times the instructions, and one workgroup converts a head.)
 __device__ __forceinline__ unsigned long long to_fixed(float a) {
-  return a > 0.f ? (unsigned long long)((double)a * kFixScale) : 0ull;
+  const float x = fmaxf(a, 0.f) * 256.f;
+  const unsigned hi = __float2uint_rz(x), lo = __float2uint_rz(__builtin_amdgcn_fractf(x) * 4294967296.f);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ float key_value(unsigned key) {         // inverse of float_key
+  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-constexpr int kRep = 32;     // replicas per histogram bin
-
-struct RadixShared {
-  // Every bin is replicated kRep times and a lane updates replica lane % kRep, so the lanes of one
-  // LDS atomic never collide on an address (scores cluster in a few exponent bins, which would
-  // otherwise serialise 64 ways) and each replica row maps to distinct banks.
-  unsigned rcnt[256 * kRep];
-  unsigned long long rsum[256 * kRep];
-  unsigned cnt[256];
-  unsigned long long sum[256];
-  unsigned prefix, mask;
-  long long remaining;                 // count (select) or fixed-point mass (budget) still to cover
-  unsigned long long cnt_above;
-  unsigned long long sum_above;
-  int done;
+// One workgroup finds a cut in a vector of any length: digits of 11, 11 and 10 bits from the top, a histogram pass each.
+// Only the first pass looks at the whole vector; the elements of the bin it picks (a quarter octave: a few percent of a
+// head's scores) are copied to LDS, and once no more than kFew are left they are ranked against each other.  On short
+// vectors the chain of barriers, scans and memory latencies bounds it, on long ones a CU's vector ALU walking the vector,
+// so sweeps are what is saved; one loop serves all passes, over the vector or the list alike, because the code is fetched
+// anew by every CU.  28 heads, kurtosis + budget + cuts of both lists, as four passes of 8 bits over the whole vector and
+// kernels of their own for arg-min, counts and scans (nine launches) -> score_stats_kernel + list_cut_kernel:
+// 1k scores 53 -> 24 us, 32k 105 -> 38 us, 64k 150 -> 83 us.
+constexpr int kBins = 2048;
+constexpr int kPitch = kBins + 8;       // words between two replicas of the count histogram: other banks for a bin's replicas
+constexpr int kRepCount = 8, kRepMass = 4;   // replicas of a bin, so that lanes on one bin rarely meet on an address
+constexpr int kCand = 8192;
+constexpr int kFew = 64;                // elements that are ranked against each other instead of histogrammed
+struct __attribute__((aligned(16))) RadixShared {
+  union {
+    unsigned cnt[kRepCount * kPitch];
+    unsigned long long sum[kRepMass * kPitch];
+  };
+  float cand[kCand], few[kFew];
+  unsigned few_key[kFew];
+  unsigned long long few_mass[kFew];
+  unsigned long long wave_tot[kSelWaves];
+  unsigned long long rem, above;
+  unsigned key;
+  int count, found;
 };
 
-// One radix pass: histogram (count and fixed-point mass) of the digit at `shift`
-// among elements of x[lo,hi) whose key matches (prefix, mask).
-__device__ __forceinline__ void radix_histogram(const float* __restrict__ x, int lo, int hi, int shift,
-                                                RadixShared& sh, bool with_sum) {
-  for (int t = threadIdx.x; t < 256 * kRep; t += blockDim.x) {
-    sh.rcnt[t] = 0;
-    if (with_sum) sh.rsum[t] = 0;
+struct RadixCut {
+  bool found;                           // false: the whole vector falls short of the target
+  unsigned key;                         // the cut: key of the last element taken
+  unsigned long long rem;               // count (or mass) still to take among the elements equal to the cut
+  unsigned long long above, other;      // count / mass of the elements above the cut: the target's kind, the other kind
+};
+
+__device__ __forceinline__ unsigned long long block_sum(unsigned long long v, RadixShared& sh) {
+  v = wave_scan(v);
+  __syncthreads();
+  if (lane_id() == 63) sh.wave_tot[threadIdx.x >> 6] = v;
+  __syncthreads();
+  unsigned long long t = 0;
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) t += sh.wave_tot[w];
+  return t;
+}
+
+// The vector x[0, n), which may lie in LDS, by the whole workgroup: f(v) for every kBatch elements of a thread.  Past the
+// end the value is the NaN of key 0, below every score, which a histogram may count: a cut never gets down to it.
+constexpr int kBatch = 8;               // loads in flight per thread
+typedef float Batch[kBatch];
+template <typename F>
+__device__ __forceinline__ void sweep(const float* x, int n, F f) {
+#pragma unroll 1
+  for (int at = 0; at < n; at += kBatch * kSelThreads) {
+    Batch v;
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) {
+      const int o = at + e * kSelThreads + (int)threadIdx.x;
+      const float t = x[min(o, n - 1)];
+      v[e] = o < n ? t : __uint_as_float(0xffffffffu);
+    }
+    f(v, n - at - (int)threadIdx.x);               // element e is a real one iff e * kSelThreads < the second argument
+  }
+}
+
+template <bool MASS>
+__device__ __forceinline__ void histogram_clear(RadixShared& sh, int reps) {
+  const int words = reps * kPitch * (MASS ? 2 : 1);
+  for (int t = 4 * threadIdx.x; t < words; t += 4 * kSelThreads)
+    *reinterpret_cast<u32x4*>(&sh.cnt[t]) = u32x4{0u, 0u, 0u, 0u};
+  if (threadIdx.x == 0) sh.found = 0;
+}
+template <bool MASS>
+__device__ __forceinline__ void histogram_add(RadixShared& sh, int rep, unsigned digit, float value) {
+  if (MASS) atomicAdd(&sh.sum[rep + digit], to_fixed(value));
+  else atomicAdd(&sh.cnt[rep + digit], 1u);
+}
+// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem and sh.above
+// moved on to it.  Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
+template <bool MASS>
+__device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int shift) {
+  __syncthreads();
+  unsigned long long c0 = 0, c1 = 0;
+  const int pair = kBins / 2 - 1 - (int)threadIdx.x;
+#pragma unroll 4
+  for (int r = 0; r < reps; ++r) {
+    if (MASS) {
+      c1 += sh.sum[r * kPitch + 2 * pair];
+      c0 += sh.sum[r * kPitch + 2 * pair + 1];
+    } else {
+      c1 += sh.cnt[r * kPitch + 2 * pair];
+      c0 += sh.cnt[r * kPitch + 2 * pair + 1];
+    }
+  }
+  unsigned long long incl = wave_scan(c0 + c1);
+  if (lane_id() == 63) sh.wave_tot[threadIdx.x >> 6] = incl;
+  const unsigned long long rem = sh.rem;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) incl += w < (int)(threadIdx.x >> 6) ? sh.wave_tot[w] : 0ull;
+  const unsigned long long excl = incl - c0 - c1;
+  if (excl < rem && rem <= incl) {                                   // one thread at most: its bins hold the crossing
+    const bool second = excl + c0 < rem;
+    sh.found = 1;
+    sh.key |= (unsigned)(kBins - 1 - 2 * (int)threadIdx.x - (second ? 1 : 0)) << shift;
+    sh.above += excl + (second ? c0 : 0);
+    sh.rem = rem - excl - (second ? c0 : 0);
   }
   __syncthreads();
-  const unsigned prefix = sh.prefix, mask = sh.mask;
-  const int rep = threadIdx.x & (kRep - 1);
-  // kBatch loads are in flight together: one workgroup walks a whole vector, and with one load per
-  // trip the pass would cost a memory latency per element
-  constexpr int kBatch = 16;
-  for (int n0 = lo + threadIdx.x; n0 < hi; n0 += kBatch * blockDim.x) {
-    float v[kBatch];
+  return sh.found;
+}
+
+// Cut of the vector x[0, n) at `target`: a number of elements (MASS false) or a fixed-point mass (MASS true), largest
+// first.  target >= 1.
+template <bool MASS>
+__device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, RadixShared& sh) {
+  constexpr int kRep = MASS ? kRepMass : kRepCount;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    sh.key = 0;
+    sh.rem = target;
+    sh.above = 0;
+  }
+  const float* src = x;                            // the elements that can still be the cut are among these m
+  int m = n, reps = kRep, left = n;
+  unsigned fixed = 0;                              // bits of sh.key that are decided
+  unsigned long long other = 0;
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    const unsigned digit = pass == 2 ? 1023u : 2047u;
+    histogram_clear<MASS>(sh, reps);
+    if (threadIdx.x == 0) sh.count = 0;
+    __syncthreads();
+    const unsigned before = sh.key;
+    const int rep = ((int)threadIdx.x & (reps - 1)) * kPitch;
+    sweep(src, m, [&](const Batch& v, int) {
 #pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int n = n0 + e * blockDim.x;
-      v[e] = n < hi ? x[n] : 0.f;
+      for (int e = 0; e < kBatch; ++e) {
+        const unsigned key = float_key(v[e]);
+        if (((key ^ before) & fixed) == 0) histogram_add<MASS>(sh, rep, (key >> shift) & digit, v[e]);
+      }
+    });
+    if (!histogram_pick<MASS>(sh, reps, shift)) return RadixCut{false, 0u, 0ull, 0ull, 0ull};   // first pass only
+    // What lies above the bin is taken whole, what lies in it is copied to LDS as far as it fits: the first time to the
+    // long list, from there to the short one.
+    const unsigned cut = sh.key;
+    float* list = src == sh.cand ? sh.few : sh.cand;
+    const int cap = src == sh.cand ? kFew : kCand;
+    sweep(src, m, [&](const Batch& v, int) {
+      unsigned mine = 0;
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const unsigned key = float_key(v[e]), a = key >> shift, c = cut >> shift;
+        const bool alive = ((key ^ before) & fixed) == 0;
+        mine |= alive && a == c ? 1u << e : 0u;
+        other += alive && a > c ? (MASS ? 1ull : to_fixed(v[e])) : 0ull;
+      }
+      if (!__any(mine)) return;
+      const unsigned n_mine = __popc(mine), incl = wave_scan(n_mine);
+      int at = 0;
+      if (lane_id() == 63) at = atomicAdd(&sh.count, (int)incl);
+      at = __builtin_amdgcn_readlane(at, 63) + (int)(incl - n_mine);
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        if (mine >> e & 1u) {
+          if (at < cap) list[at] = v[e];
+          ++at;
+        }
+      }
+    });
+    __syncthreads();
+    left = sh.count;
+    fixed = 0xffffffffu << shift;
+    if (left <= cap) {
+      src = list;
+      m = left;
+      reps = 1;
     }
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const unsigned key = float_key(v[e]);
-      if (n0 + e * (int)blockDim.x < hi && (key & mask) == prefix) {
-        const unsigned d = (key >> shift) & 255u;
-        atomicAdd(&sh.rcnt[d * kRep + rep], 1u);
-        if (with_sum) atomicAdd(&sh.rsum[d * kRep + rep], to_fixed(v[e]));
+    if (left <= kFew) break;
+    __syncthreads();                               // sh.count is set again
+  }
+  if (left <= kFew && fixed != 0xffffffffu) {
+    // Every element left against every other: the one whose own share crosses sh.rem is the cut (equal elements all
+    // write the same values).
+    const float* few = src == sh.cand ? sh.cand : sh.few;
+    const unsigned long long rem = sh.rem, above = sh.above;
+    __syncthreads();
+    if ((int)threadIdx.x < left) {
+      const float own = few[threadIdx.x];
+      const unsigned mine = float_key(own);
+      sh.few_key[threadIdx.x] = mine;
+      sh.few_mass[threadIdx.x] = to_fixed(own);
+    }
+    __syncthreads();
+    unsigned mine = 0;
+    if ((int)threadIdx.x < left) {
+      mine = sh.few_key[threadIdx.x];
+      unsigned more = 0, same = 0;
+      unsigned long long mass = 0;
+#pragma unroll 8
+      for (int t = 0; t < left; ++t) {
+        const unsigned k = sh.few_key[t];
+        more += k > mine;
+        same += k == mine;
+        if (MASS) mass += k > mine ? sh.few_mass[t] : 0ull;
+      }
+      const unsigned long long excl = MASS ? mass : more, own = MASS ? same * sh.few_mass[threadIdx.x] : same;
+      if (excl < rem && rem <= excl + own) {
+        sh.key = mine;
+        sh.rem = rem - excl;
+        sh.above = above + excl;
       }
     }
-  }
-  __syncthreads();
-  if (threadIdx.x < 256) {
-    unsigned c = 0;
-    unsigned long long m = 0;
-    for (int r = 0; r < kRep; ++r) {
-      const int o = threadIdx.x * kRep + ((r + threadIdx.x) & (kRep - 1));   // rotate: spread banks across lanes
-      c += sh.rcnt[o];
-      if (with_sum) m += sh.rsum[o];
-    }
-    sh.cnt[threadIdx.x] = c;
-    sh.sum[threadIdx.x] = m;
-  }
-  __syncthreads();
-}
-
-// Run by the first wavefront after a histogram pass.  Walks the 256 bins from the top and finds the
-// first bin at which the running total (of counts, or of fixed-point mass when by_sum) reaches
-// sh.remaining; updates prefix / mask / remaining / cnt_above / sum_above.  Returns false (all lanes)
-// when even the whole histogram falls short.  Each lane owns 4 consecutive bins; totals are combined
-// with a wavefront prefix scan.
-__device__ __forceinline__ bool radix_pick_bin(RadixShared& sh, int shift, bool by_sum) {
-  const int lane = threadIdx.x;
-  const int base = 255 - 4 * lane;
-  unsigned long long c[4], m[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    c[j] = sh.cnt[base - j];
-    m[j] = sh.sum[base - j];
-  }
-  const unsigned long long ctot = c[0] + c[1] + c[2] + c[3], mtot = m[0] + m[1] + m[2] + m[3];
-  unsigned long long cs = ctot, ms = mtot;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long tc = __shfl_up(cs, o, 64), tm = __shfl_up(ms, o, 64);
-    if (lane >= o) {
-      cs += tc;
-      ms += tm;
-    }
-  }
-  const long long rem = sh.remaining;
-  const bool cross = (long long)(by_sum ? ms : cs) >= rem;
-  const unsigned long long hit = __ballot(cross);
-  if (hit == 0) return false;
-  const int leader = __ffsll((long long)hit) - 1;
-  if (lane == leader) {
-    unsigned long long cb = cs - ctot, mb = ms - mtot;      // totals of the bins above this lane's
-    int j = 0;
-    for (; j < 3; ++j) {
-      if ((long long)((by_sum ? mb + m[j] : cb + c[j])) >= rem) break;
-      cb += c[j];
-      mb += m[j];
-    }
-    sh.remaining = rem - (long long)(by_sum ? mb : cb);
-    sh.cnt_above += cb;
-    sh.sum_above += mb;
-    sh.prefix |= (unsigned)(base - j) << shift;
-    sh.mask |= 255u << shift;
-  }
-  return true;
-}
-
-// k-th largest element of x[lo,hi): writes its key, the number of elements that
-// must be taken among those equal to it, and the fixed-point mass of the k
-// largest.  k <= 0 selects nothing, k >= hi-lo selects everything.
-__device__ void radix_select_block(const float* __restrict__ x, int lo, int hi, long long k, RadixShared& sh,
-                                   unsigned* thr_key, int* need_eq, unsigned long long* mass, bool with_sum) {
-  const int n = hi - lo;
-  if (k <= 0 || k >= n) {
-    unsigned long long total = 0;
-    if (with_sum && k >= n) {
-      if (threadIdx.x == 0) sh.sum_above = 0;
-      __syncthreads();
-      unsigned long long local = 0;
-      for (int j = lo + threadIdx.x; j < hi; j += blockDim.x) local += to_fixed(x[j]);
-      local = wave_sum(local);
-      if (lane_id() == 0) atomicAdd(&sh.sum_above, local);
-      __syncthreads();
-      total = sh.sum_above;
-    }
-    if (threadIdx.x == 0) {
-      *thr_key = k <= 0 ? 0xffffffffu : 0u;
-      *need_eq = 0;
-      if (mass) *mass = total;
-    }
     __syncthreads();
+    if ((int)threadIdx.x < left && mine > sh.key) other += MASS ? 1ull : sh.few_mass[threadIdx.x];
+  }
+  other = block_sum(other, sh);
+  const RadixCut cut{true, sh.key, sh.rem, sh.above, other};
+  __syncthreads();                                 // sh may be used again
+  return cut;
+}
+
+// Membership rule of a list.
+struct KeepRule {
+  int keep_all_head0;    // head 0 keeps everything
+  int visual_only;       // only the visual range is classified, elements outside are always kept (queries)
+  int use_table;         // thresholds from thr/need arrays, else from thr_scalar with need 0
+  unsigned thr_scalar;
+};
+
+// One list to form: the scores, the rule, the cut of every head and what comes out.
+struct ListJob {
+  const float* x;        // [B*H, ld]
+  KeepRule rule;
+  unsigned* thr;         // [B*H]
+  int* need;             // [B*H]
+  int* off_keep;         // [B*H, nchunk] exclusive counts of elements above the cut (or always kept), per chunk
+  int* off_eq;           // [B*H, nchunk] exclusive counts of elements at the cut
+  int* out;              // [B*H, out_stride]
+  int out_stride;
+  int* total;            // [B*H] length of the list, or null
+};
+
+// How many elements each head of a job takes.
+struct KeySource {
+  int mode;              // 0: budget of the flattest head, 1: largest budget of the heads, 2: the head's own (all from
+                         // own[B*H] and kurt), 3: given counts (budget array), 4: top fraction of the visual range
+  const int* own;        // [B*H] budget of every head's own scores
+  const double* kurt;    // [B*H]
+  int* flattest;         // [B] out (modes 0..2)
+  int* budget;           // [B] or [B*H] out (modes 0..2), in (mode 3)
+  int bph, k_cap;
+  float fraction;
+  float* recall;         // [B*H] out or null
+};
+
+__device__ __forceinline__ void classify(const KeepRule& r, int h, bool inside, float v, unsigned thr, bool& always,
+                                         bool& eq) {
+  if ((r.keep_all_head0 && h == 0) || (r.visual_only && !inside)) {
+    always = true;
+    eq = false;
     return;
   }
-  if (threadIdx.x == 0) {
-    sh.prefix = 0;
-    sh.mask = 0;
-    sh.remaining = k;
-    sh.cnt_above = 0;
-    sh.sum_above = 0;
-  }
-  __syncthreads();
-  // The four passes count only: the 64-bit mass atomics are the slow half of a histogram pass, and the mass of the
-  // k largest is one plain sweep once the cut is known (fixed point: the order of the additions does not matter).
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    radix_histogram(x, lo, hi, shift, sh, false);
-    if (threadIdx.x < 64) radix_pick_bin(sh, shift, false);     // k <= matching count: always found
-    __syncthreads();
-  }
-  if (with_sum) {
-    const unsigned cut = sh.prefix;
-    unsigned long long local = 0;
-    for (int j = lo + threadIdx.x; j < hi; j += blockDim.x) {
-      const float v = x[j];
-      if (float_key(v) > cut) local += to_fixed(v);
-    }
-    local = wave_sum(local);
-    if (lane_id() == 0 && local) atomicAdd(&sh.sum_above, local);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    *thr_key = sh.prefix;
-    *need_eq = (int)sh.remaining;
-    if (mass) {
-      // every element left in the last bin has the same bits: recover its value from the key
-      const unsigned key = sh.prefix;
-      const unsigned bits = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
-      *mass = sh.sum_above + (unsigned long long)sh.remaining * to_fixed(__uint_as_float(bits));
-    }
-  }
-  __syncthreads();
-}
-
-// Smallest count b such that the b largest elements of x[0,n) sum to >= target
-// (fixed point).  n if the whole vector falls short.
-__device__ int radix_budget_block(const float* __restrict__ x, int n, unsigned long long target, RadixShared& sh) {
-  if (threadIdx.x == 0) {
-    sh.prefix = 0;
-    sh.mask = 0;
-    sh.remaining = (long long)target;
-    sh.cnt_above = 0;
-    sh.sum_above = 0;
-    sh.done = 0;
-  }
-  __syncthreads();
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    if (sh.done) break;                   // uniform: written before the barrier below
-    radix_histogram(x, 0, n, shift, sh, true);
-    if (threadIdx.x < 64) {
-      const bool found = radix_pick_bin(sh, shift, true);
-      if (!found && threadIdx.x == 0) sh.done = 1;   // even all matching elements fall short: take everything
-    }
-    __syncthreads();
-  }
-  int b;
-  if (sh.done) {
-    b = n;
-  } else {
-    const unsigned key = sh.prefix;
-    const unsigned bits = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
-    const unsigned long long v = to_fixed(__uint_as_float(bits));
-    const long long rem = sh.remaining;
-    long long j = rem <= 0 ? 0 : (v ? (rem + (long long)v - 1) / (long long)v : 0);
-    if (j < 1) j = 1;           // the crossing element itself is always needed
-    b = (int)min((long long)n, (long long)sh.cnt_above + j);
-  }
-  __syncthreads();
-  return b;
+  const unsigned key = float_key(v);
+  always = key > thr;
+  eq = key == thr;
 }
 
 // ------------------------------------------------------------------ kernels
 
-// grid: B*H.  Threshold for "keep the k best of x[lo,hi)".  k from a scalar, or
-// min(k_dev[batch], k_cap) when k_dev is given.  skip_head0: head 0 gets the
-// keep-everything threshold (the first head's queries are all preserved).
-__global__ __launch_bounds__(kSelThreads) void radix_select_kernel(const float* __restrict__ x, int n_stride, int H,
-                                                                  int lo, int hi, int k_scalar,
-                                                                  const int* __restrict__ k_dev, int k_per_head,
-                                                                  int k_cap, int skip_head0, unsigned* __restrict__ thr,
-                                                                  int* __restrict__ need, float* __restrict__ recall,
-                                                                  float recall_div) {
+// grid: (H, B, 2).  Of every head's own scores: excess kurtosis m4/m2^2 - 3 in fp64 with a fixed reduction tree (z = 0),
+// and the smallest count whose largest elements reach recall_p of the mass (z = 1).  Every head finds its budget
+// although the shared budget needs the flattest head's only: the heads run side by side, and the search does not wait
+// for the arg-min.
+__global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* __restrict__ a, Layer L, Ragged rg,
+                                                                 double recall_p, double* __restrict__ kurt,
+                                                                 int* __restrict__ own) {
   __shared__ RadixShared sh;
-  const int bh = blockIdx.x;
-  const int b = bh / H, h = bh % H;
-  if (skip_head0 && h == 0) {
+  __shared__ double red[2][kSelWaves];
+  const int b = blockIdx.y, bh = b * L.Hq + blockIdx.x;
+  const int N = seq_len(L, rg, b);
+  const float* x = a + (long long)bh * L.ld;
+  if (blockIdx.z) {
+    // rounded up: the truncated element masses must never reach a target below the real one
+    const unsigned long long target = (unsigned long long)ceil(recall_p * (double)N * kFixScale);
+    const RadixCut cut = radix_cut<true>(x, N, target, sh);
     if (threadIdx.x == 0) {
-      thr[bh] = 0u;
-      need[bh] = 0;
+      int r = N;                                // even the whole vector falls short: take everything
+      if (cut.found) {
+        const unsigned long long v = to_fixed(key_value(cut.key));   // > 0: its bin crossed the target
+        r = (int)min((unsigned long long)N, cut.other + (cut.rem + v - 1) / v);
+      }
+      own[bh] = r;
     }
     return;
   }
-  long long k = k_dev ? (long long)min(k_dev[budget_slot(k_per_head, b, bh)], k_cap) : (long long)k_scalar;
-  __shared__ unsigned long long mass;
-  radix_select_block(x + (long long)bh * n_stride, lo, hi, k, sh, &thr[bh], &need[bh], recall ? &mass : nullptr,
-                     recall != nullptr);
-  if (recall && threadIdx.x == 0) recall[bh] = (float)((double)mass / kFixScale / (double)recall_div);
-}
-
-// grid: (H or 1, B).  Budget of head h (or of the flattest head when per_head == 0).
-__global__ __launch_bounds__(kSelThreads) void radix_budget_kernel(const float* __restrict__ a, int N, int ld, int H,
-                                                                  const int* __restrict__ flattest, int per_head,
-                                                                  double target_mass, int* __restrict__ out) {
-  __shared__ RadixShared sh;
-  const int b = blockIdx.y;
-  const int h = per_head ? (int)blockIdx.x : flattest[b];
-  // rounded up: the truncated element masses must never reach a target below the real one
-  const unsigned long long target = (unsigned long long)ceil(target_mass * kFixScale);
-  const int r = radix_budget_block(a + ((long long)b * H + h) * ld, N, target, sh);
-  if (threadIdx.x == 0) out[per_head ? b * H + h : b] = r;
-}
-
-__global__ void max_over_heads_kernel(const int* __restrict__ per_head, int H, int* __restrict__ out) {
-  const int b = blockIdx.x;
-  if (threadIdx.x == 0) {
-    int m = 0;
-    for (int h = 0; h < H; ++h) m = max(m, per_head[b * H + h]);
-    out[b] = m;
-  }
-}
-
-// grid: B*H.  Excess kurtosis m4/m2^2 - 3 in fp64 with a fixed reduction tree.
-__global__ __launch_bounds__(kSelThreads) void kurtosis_kernel(const float* __restrict__ a, int N, int ld,
-                                                              double* __restrict__ kurt) {
-  __shared__ double red[2][kSelThreads / 64];
-  __shared__ double mean_sh;
-  const float* x = a + (long long)blockIdx.x * ld;
   const int w = threadIdx.x >> 6;
   double s = 0.0;
-#pragma unroll 8
-  for (int n = threadIdx.x; n < N; n += kSelThreads) s += (double)x[n];
+  sweep(x, N, [&](const Batch& v, int left) {
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) s += e * kSelThreads < left ? (double)v[e] : 0.0;
+  });
   s = wave_sum(s);
   if (lane_id() == 0) red[0][w] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int i = 0; i < kSelThreads / 64; ++i) t += red[0][i];
-    mean_sh = t / (double)N;
-  }
-  __syncthreads();
-  const double mu = mean_sh;
+  double t = 0.0;
+#pragma unroll
+  for (int i = 0; i < kSelWaves; ++i) t += red[0][i];
+  const double mu = t / (double)N;
   double s2 = 0.0, s4 = 0.0;
-#pragma unroll 8
-  for (int n = threadIdx.x; n < N; n += kSelThreads) {
-    const double c = (double)x[n] - mu;
-    const double c2 = c * c;
-    s2 += c2;
-    s4 += c2 * c2;
-  }
+  sweep(x, N, [&](const Batch& v, int left) {
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) {
+      const double c = e * kSelThreads < left ? (double)v[e] - mu : 0.0;
+      const double c2 = c * c;
+      s2 += c2;
+      s4 += c2 * c2;
+    }
+  });
   s2 = wave_sum(s2);
   s4 = wave_sum(s4);
   __syncthreads();
@@ -331,94 +367,129 @@ __global__ __launch_bounds__(kSelThreads) void kurtosis_kernel(const float* __re
   __syncthreads();
   if (threadIdx.x == 0) {
     double t2 = 0.0, t4 = 0.0;
-    for (int i = 0; i < kSelThreads / 64; ++i) {
+#pragma unroll
+    for (int i = 0; i < kSelWaves; ++i) {
       t2 += red[0][i];
       t4 += red[1][i];
     }
     const double m2 = t2 / (double)N, m4 = t4 / (double)N;
-    kurt[blockIdx.x] = m2 > 0.0 ? m4 / (m2 * m2) - 3.0 : -2.0;
+    kurt[bh] = m2 > 0.0 ? m4 / (m2 * m2) - 3.0 : -2.0;
   }
 }
 
-__global__ void argmin_kernel(const double* __restrict__ kurt, int H, int* __restrict__ flattest) {
-  const int b = blockIdx.x;
-  if (threadIdx.x == 0) {
-    // heads within 1e-9 (relative) of the smallest kurtosis tie and the lowest index wins: for two or
-    // three scores the statistic is one constant for every head and rounding would pick the head
-    double v = kurt[b * H];
-    for (int h = 1; h < H; ++h) v = fmin(v, kurt[b * H + h]);
-    const double bar = v + 1e-9 * fabs(v);
-    int best = 0;
-    while (best < H - 1 && !(kurt[b * H + best] <= bar)) ++best;
-    flattest[b] = best;
-  }
-}
-
-// Membership rule shared by the counting and the writing pass.
-struct KeepRule {
-  int lo, hi;            // classified region; elements outside are always kept (queries) -- for keys lo=0, hi=N
-  int keep_all_head0;    // head 0 keeps everything
-  int use_table;         // thresholds from thr/need arrays, else from thr_scalar with need 0
-  unsigned thr_scalar;
-};
-
-__device__ __forceinline__ void classify(const KeepRule& r, int h, int n, float v, unsigned thr, bool& always,
-                                         bool& eq) {
-  if ((r.keep_all_head0 && h == 0) || n < r.lo || n >= r.hi) {
-    always = true;
-    eq = false;
-    return;
-  }
-  const unsigned key = float_key(v);
-  always = key > thr;
-  eq = key == thr;
-}
-
-// grid: (nchunk, B*H).  Per chunk: number of always-kept and of cut-valued elements.
-__global__ __launch_bounds__(kChunkThreads) void chunk_count_kernel(const float* __restrict__ x, int N, int ld, int H,
-                                                                   KeepRule rule, const unsigned* __restrict__ thr_tab,
-                                                                   int nchunk, int* __restrict__ cnt_keep,
-                                                                   int* __restrict__ cnt_eq) {
-  __shared__ int red[2][kChunkThreads / 64];
-  const int bh = blockIdx.y, h = bh % H;
-  const unsigned thr = rule.use_table ? thr_tab[bh] : rule.thr_scalar;
-  const float* row = x + (long long)bh * ld;
-  const int base = blockIdx.x * kChunk + threadIdx.x * kPerThread;
-  int ck = 0, ce = 0;
+// Wavefront-wide argmin over the heads' kurtoses: heads within 1e-9 (relative) of the smallest tie and the lowest index
+// wins (for two or three scores the statistic is one constant for every head and rounding would pick the head).
+__device__ __forceinline__ int flattest_head(const double* __restrict__ kurt, int H) {
+  double v = kurt[0];
+  for (int h = lane_id(); h < H; h += 64) v = fmin(v, kurt[h]);
 #pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const int n = base + e;
-    if (n < N) {
-      bool al, eq;
-      classify(rule, h, n, row[n], thr, al, eq);
-      ck += al;
-      ce += eq;
+  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+  const double bar = v + 1e-9 * fabs(v);
+  for (int h0 = 0; h0 < H; h0 += 64) {
+    const int h = h0 + lane_id();
+    const unsigned long long bal = __ballot(h < H && kurt[h] <= bar);
+    if (bal) return h0 + __ffsll((long long)bal) - 1;
+  }
+  return H - 1;
+}
+
+// grid: (H, B, jobs).  Per head: how many elements to take, the cut (threshold key, number of cut-valued elements to
+// take), the recall, and how many elements of the list precede each chunk of kChunk elements.
+__global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged rg, ListJob job0, KeySource src0,
+                                                              ListJob job1, KeySource src1) {
+  __shared__ RadixShared sh;
+  __shared__ int k_sh;
+  const ListJob& job = blockIdx.z ? job1 : job0;
+  const KeySource& src = blockIdx.z ? src1 : src0;
+  const int H = L.Hq, h = blockIdx.x, b = blockIdx.y, bh = b * H + h;
+  const int N = seq_len(L, rg, b), v0 = rg.on ? rg.v0[b] : L.v0, v1 = rg.on ? rg.v1[b] : L.v1;
+  const float* row = job.x + (long long)bh * L.ld;
+  unsigned thr = job.rule.thr_scalar;
+  int need = 0;
+  if (job.rule.use_table) {
+    if (src.mode <= 2 && threadIdx.x < 64) {
+      const int flat = flattest_head(src.kurt + (long long)b * H, H);
+      int k;
+      if (src.mode == 0) {
+        k = src.own[b * H + flat];
+      } else if (src.mode == 1) {
+        k = 0;
+        for (int i = threadIdx.x; i < H; i += 64) k = max(k, src.own[b * H + i]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) k = max(k, __shfl_xor(k, o, 64));
+      } else {
+        k = src.own[bh];
+      }
+      if (threadIdx.x == 0) {
+        k_sh = k;
+        if (h == 0) src.flattest[b] = flat;
+        if (src.mode == 2) src.budget[bh] = k;
+        else if (h == 0) src.budget[b] = k;
+      }
+    }
+    __syncthreads();
+    int lo = 0, hi = N;
+    long long k;
+    if (src.mode <= 2) {
+      k = min(k_sh, src.k_cap);
+    } else if (src.mode == 3) {
+      k = min(src.budget[budget_slot(src.bph, b, bh)], src.k_cap);
+    } else {
+      lo = v0, hi = v1;
+      k = (long long)ceil((double)src.fraction * (double)(v1 - v0));
+      k = k < 0 ? 0 : k;
+    }
+    const int n = hi - lo;
+    unsigned long long mass = 0;
+    if ((job.rule.keep_all_head0 && h == 0) || k >= n) {
+      thr = 0u;
+      if (src.recall) {
+        unsigned long long local = 0;
+        sweep(row + lo, n, [&](const Batch& v, int) {
+#pragma unroll
+          for (int e = 0; e < kBatch; ++e) local += to_fixed(v[e]);
+        });
+        mass = block_sum(local, sh);
+      }
+    } else if (k <= 0) {
+      thr = 0xffffffffu;
+    } else {
+      const RadixCut cut = radix_cut<false>(row + lo, n, k, sh);
+      thr = cut.key;
+      need = (int)cut.rem;
+      mass = cut.other + cut.rem * to_fixed(key_value(cut.key));
+    }
+    if (threadIdx.x == 0) {
+      job.thr[bh] = thr;
+      job.need[bh] = need;
+      if (src.recall) src.recall[bh] = (float)((double)mass / kFixScale / (double)(float)N);
     }
   }
-  ck = wave_sum(ck);
-  ce = wave_sum(ce);
-  if (lane_id() == 0) {
-    red[0][threadIdx.x >> 6] = ck;
-    red[1][threadIdx.x >> 6] = ce;
+  if (!job.off_keep) return;
+  // counts per chunk, then their exclusive scan; a wavefront counts one chunk
+  const int stride = cdiv(L.N, kChunk), nchunk = cdiv(N, kChunk);
+  int* ck = job.off_keep + (long long)bh * stride;
+  int* ce = job.off_eq + (long long)bh * stride;
+  for (int c = threadIdx.x >> 6; c < nchunk; c += kSelWaves) {
+    unsigned both = 0;                             // above the cut, at the cut << 16
+    float v[kChunk / 64];
+#pragma unroll
+    for (int e = 0; e < kChunk / 64; ++e) v[e] = row[min(c * kChunk + e * 64 + lane_id(), N - 1)];
+#pragma unroll
+    for (int e = 0; e < kChunk / 64; ++e) {
+      const int n = c * kChunk + e * 64 + lane_id();
+      bool al, eq;
+      classify(job.rule, h, n >= v0 && n < v1, v[e], thr, al, eq);
+      both += n < N ? (al ? 1u : 0u) + (eq ? 65536u : 0u) : 0u;
+    }
+    both = wave_scan(both);
+    if (lane_id() == 63) {
+      ck[c] = (int)(both & 0xffffu);
+      ce[c] = (int)(both >> 16);
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int a = 0, b = 0;
-    for (int i = 0; i < kChunkThreads / 64; ++i) {
-      a += red[0][i];
-      b += red[1][i];
-    }
-    cnt_keep[(long long)bh * nchunk + blockIdx.x] = a;
-    cnt_eq[(long long)bh * nchunk + blockIdx.x] = b;
-  }
-}
-
-// grid: B*H, one wavefront.  In-place exclusive scan over the chunks; total count out.
-__global__ void chunk_scan_kernel(int nchunk, KeepRule rule, const int* __restrict__ need_tab, int* __restrict__ cnt_keep,
-                                  int* __restrict__ cnt_eq, int* __restrict__ total_out, int out_cap) {
-  const int bh = blockIdx.x;
-  int* ck = cnt_keep + (long long)bh * nchunk;
-  int* ce = cnt_eq + (long long)bh * nchunk;
+  if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   int run_k = 0, run_e = 0;
   for (int c0 = 0; c0 < nchunk; c0 += 64) {
@@ -442,24 +513,19 @@ __global__ void chunk_scan_kernel(int nchunk, KeepRule rule, const int* __restri
     run_k += __shfl(sk, 63, 64);
     run_e += __shfl(se, 63, 64);
   }
-  if (lane == 0 && total_out) {
-    const int need = rule.use_table ? need_tab[bh] : 0;
-    total_out[bh] = min(out_cap, run_k + min(run_e, need));
-  }
+  if (lane == 0 && job.total) job.total[bh] = min(job.out_stride, run_k + min(run_e, need));
 }
 
-// grid: (nchunk, B*H).  Writes the kept indices of the chunk, ascending, at their global rank.
-__global__ __launch_bounds__(kChunkThreads) void chunk_write_kernel(const float* __restrict__ x, int N, int ld, int H,
-                                                                   KeepRule rule, const unsigned* __restrict__ thr_tab,
-                                                                   const int* __restrict__ need_tab, int nchunk,
-                                                                   const int* __restrict__ off_keep,
-                                                                   const int* __restrict__ off_eq,
-                                                                   int* __restrict__ out, int out_stride) {
+// grid: (nchunk, B*H, jobs).  Writes the kept indices of the chunk, ascending, at their global rank.
+__global__ __launch_bounds__(kChunkThreads) void list_write_kernel(Layer L, Ragged rg, ListJob job0, ListJob job1) {
   __shared__ int wsum[2][kChunkThreads / 64];
-  const int bh = blockIdx.y, h = bh % H;
-  const unsigned thr = rule.use_table ? thr_tab[bh] : rule.thr_scalar;
-  const int need = rule.use_table ? need_tab[bh] : 0;
-  const float* row = x + (long long)bh * ld;
+  const ListJob job = blockIdx.z ? job1 : job0;
+  const int bh = blockIdx.y, h = bh % L.Hq, b = bh / L.Hq;
+  const int N = seq_len(L, rg, b), v0 = rg.on ? rg.v0[b] : L.v0, v1 = rg.on ? rg.v1[b] : L.v1;
+  if (blockIdx.x * kChunk >= N) return;
+  const unsigned thr = job.rule.use_table ? job.thr[bh] : job.rule.thr_scalar;
+  const int need = job.rule.use_table ? job.need[bh] : 0;
+  const float* row = job.x + (long long)bh * L.ld;
   const int base = blockIdx.x * kChunk + threadIdx.x * kPerThread;
   bool al[kPerThread], eq[kPerThread];
   int ck = 0, ce = 0;
@@ -468,7 +534,7 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_write_kernel(const float*
     const int n = base + e;
     al[e] = false;
     eq[e] = false;
-    if (n < N) classify(rule, h, n, row[n], thr, al[e], eq[e]);
+    if (n < N) classify(job.rule, h, n >= v0 && n < v1, row[n], thr, al[e], eq[e]);
     ck += al[e];
     ce += eq[e];
   }
@@ -489,19 +555,20 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_write_kernel(const float*
     wsum[1][w] = se;
   }
   __syncthreads();
-  int pk = off_keep[(long long)bh * nchunk + blockIdx.x] + sk - ck;
-  int pe = off_eq[(long long)bh * nchunk + blockIdx.x] + se - ce;
+  const long long off = (long long)bh * cdiv(L.N, kChunk) + blockIdx.x;
+  int pk = job.off_keep[off] + sk - ck;
+  int pe = job.off_eq[off] + se - ce;
   for (int i = 0; i < w; ++i) {
     pk += wsum[0][i];
     pe += wsum[1][i];
   }
-  int* dst = out + (long long)bh * out_stride;
+  int* dst = job.out + (long long)bh * job.out_stride;
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {
     const bool take = al[e] || (eq[e] && pe < need);
     if (take) {
       const int pos = pk + min(pe, need);
-      if (pos < out_stride) dst[pos] = base + e;
+      if (pos < job.out_stride) dst[pos] = base + e;
     }
     pk += al[e];
     pe += eq[e];
@@ -530,21 +597,6 @@ __global__ void visual_subset_kernel(const int* __restrict__ kv_idx, const int* 
   if (threadIdx.x == 0) vis_cnt[bh] = cnt;
 }
 
-int compact(const float* x, int BH, int N, int ld, int H, const KeepRule& rule, const unsigned* thr, const int* need,
-            int* cnt_keep, int* cnt_eq, int* out, int out_stride, int* total_out, hipStream_t st) {
-  const int nchunk = cdiv(N, kChunk);
-  hipLaunchKernelGGL(chunk_count_kernel, dim3(nchunk, BH), dim3(kChunkThreads), 0, st, x, N, ld, H, rule, thr, nchunk,
-                     cnt_keep, cnt_eq);
-  OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(chunk_scan_kernel, dim3(BH), dim3(64), 0, st, nchunk, rule, need, cnt_keep, cnt_eq, total_out,
-                     out_stride);
-  OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(chunk_write_kernel, dim3(nchunk, BH), dim3(kChunkThreads), 0, st, x, N, ld, H, rule, thr, need, nchunk,
-                     cnt_keep, cnt_eq, out, out_stride);
-  OMNI_LAUNCH_CHECK();
-  return OMNI_OK;
-}
-
 struct SelWs {
   unsigned* thr;
   int* need;
@@ -562,6 +614,67 @@ SelWs carve_select(Arena& a, const Layer& L) {
   return w;
 }
 
+ListJob list_job(const SelWs& w, const float* x, const KeepRule& rule, int* out, int out_stride, int* total) {
+  ListJob j;
+  j.x = x;
+  j.rule = rule;
+  j.thr = w.thr;
+  j.need = w.need;
+  j.off_keep = w.cnt_keep;
+  j.off_eq = w.cnt_eq;
+  j.out = out;
+  j.out_stride = out_stride;
+  j.total = total;
+  return j;
+}
+
+ListJob query_job(const Layer& L, const SelWs& w, const float* scores, int mode, float param, int* q_idx, int* q_cnt,
+                  KeySource* src) {
+  KeepRule rule = {1, 1, mode != 0, 0u};
+  if (mode == 0) {
+    unsigned u;
+    std::memcpy(&u, &param, 4);
+    rule.thr_scalar = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  }
+  *src = KeySource{};
+  src->mode = 4;
+  src->fraction = param;
+  return list_job(w, scores, rule, q_idx, L.ld, q_cnt);
+}
+
+KeepRule key_rule() { return KeepRule{0, 0, 1, 0u}; }
+
+int launch_cut(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const KeySource& s0, const ListJob& j1,
+               const KeySource& s1, hipStream_t st) {
+  hipLaunchKernelGGL(list_cut_kernel, dim3(L.Hq, L.B, jobs), dim3(kSelThreads), 0, st, L, rg, j0, s0, j1, s1);
+  OMNI_LAUNCH_CHECK();
+  return OMNI_OK;
+}
+
+int launch_write(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const ListJob& j1, hipStream_t st) {
+  hipLaunchKernelGGL(list_write_kernel, dim3(cdiv(L.N, kChunk), L.B * L.Hq, jobs), dim3(kChunkThreads), 0, st, L, rg, j0,
+                     j1);
+  OMNI_LAUNCH_CHECK();
+  return OMNI_OK;
+}
+
+// kurtosis and own budgets of all heads, and where the counts of the key lists come from
+int launch_stats(const Layer& L, const Ragged& rg, const float* key_scores, float recall_p, int budget_mode, double* kurt,
+                 int* own, int* flattest, int* budget, float* recall, int k_cap, KeySource* src, hipStream_t st) {
+  hipLaunchKernelGGL(score_stats_kernel, dim3(L.Hq, L.B, 2), dim3(kSelThreads), 0, st, key_scores, L, rg, (double)recall_p,
+                     kurt, own);
+  OMNI_LAUNCH_CHECK();
+  *src = KeySource{};
+  src->mode = budget_mode;
+  src->own = own;
+  src->kurt = kurt;
+  src->flattest = flattest;
+  src->budget = budget;
+  src->k_cap = k_cap;
+  src->recall = recall;
+  return OMNI_OK;
+}
+
 }  // namespace
 
 size_t select_ws(const Layer& L) {
@@ -573,46 +686,23 @@ size_t select_ws(const Layer& L) {
 int run_select_queries(const Layer& L, const float* scores, int mode, float param, int* q_idx, int* q_cnt, void* ws,
                        hipStream_t st) {
   Arena a(ws);
-  SelWs w = carve_select(a, L);
-  const int BH = L.B * L.Hq;
-  KeepRule rule;
-  rule.lo = L.v0;
-  rule.hi = L.v1;
-  rule.keep_all_head0 = 1;
-  if (mode == 0) {
-    rule.use_table = 0;
-    unsigned u;
-    std::memcpy(&u, &param, 4);
-    rule.thr_scalar = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  } else {
-    rule.use_table = 1;
-    rule.thr_scalar = 0;
-    const int n_vis = L.v1 - L.v0;
-    long long want = (long long)std::ceil((double)param * (double)n_vis);
-    if (want < 0) want = 0;
-    if (want > n_vis) want = n_vis;
-    hipLaunchKernelGGL(radix_select_kernel, dim3(BH), dim3(kSelThreads), 0, st, scores, L.ld, L.Hq, L.v0, L.v1,
-                       (int)want, (const int*)nullptr, 0, 0, 1, w.thr, w.need, (float*)nullptr, 1.f);
-    OMNI_LAUNCH_CHECK();
-  }
-  return compact(scores, BH, L.N, L.ld, L.Hq, rule, w.thr, w.need, w.cnt_keep, w.cnt_eq, q_idx, L.ld, q_cnt, st);
+  KeySource src;
+  const ListJob job = query_job(L, carve_select(a, L), scores, mode, param, q_idx, q_cnt, &src);
+  const int rc = launch_cut(L, Ragged{}, 1, job, src, job, src, st);
+  return rc != OMNI_OK ? rc : launch_write(L, Ragged{}, 1, job, job, st);
 }
 
 int run_select_kv(const Layer& L, const float* key_scores, const int* budget, int b_cap, int* kv_idx, void* ws,
                   hipStream_t st) {
   Arena a(ws);
-  SelWs w = carve_select(a, L);
-  const int BH = L.B * L.Hq;
-  hipLaunchKernelGGL(radix_select_kernel, dim3(BH), dim3(kSelThreads), 0, st, key_scores, L.ld, L.Hq, 0, L.N, 0, budget,
-                     L.bph, b_cap, 0, w.thr, w.need, (float*)nullptr, 1.f);
-  OMNI_LAUNCH_CHECK();
-  KeepRule rule;
-  rule.lo = 0;
-  rule.hi = L.N;
-  rule.keep_all_head0 = 0;
-  rule.use_table = 1;
-  rule.thr_scalar = 0;
-  return compact(key_scores, BH, L.N, L.ld, L.Hq, rule, w.thr, w.need, w.cnt_keep, w.cnt_eq, kv_idx, b_cap, nullptr, st);
+  const ListJob job = list_job(carve_select(a, L), key_scores, key_rule(), kv_idx, b_cap, nullptr);
+  KeySource src{};
+  src.mode = 3;
+  src.budget = const_cast<int*>(budget);
+  src.bph = L.bph;
+  src.k_cap = b_cap;
+  const int rc = launch_cut(L, Ragged{}, 1, job, src, job, src, st);
+  return rc != OMNI_OK ? rc : launch_write(L, Ragged{}, 1, job, job, st);
 }
 
 size_t budget_stats_ws(const Layer& L) {
@@ -625,88 +715,53 @@ size_t budget_stats_ws(const Layer& L) {
 }
 
 int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, int budget_mode, double* kurt,
-                     int* flattest, int* budget, float* recall, void* ws, hipStream_t st, int k_cap) {
+                     int* flattest, int* budget, float* recall, void* ws, hipStream_t st) {
   Arena a(ws);
-  const int BH = L.B * L.Hq;
-  unsigned* thr = a.take<unsigned>(BH);
-  int* need = a.take<int>(BH);
-  int* per_head = a.take<int>(BH);
-  hipLaunchKernelGGL(kurtosis_kernel, dim3(BH), dim3(kSelThreads), 0, st, key_scores, L.N, L.ld, kurt);
-  OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(argmin_kernel, dim3(L.B), dim3(64), 0, st, kurt, L.Hq, flattest);
-  OMNI_LAUNCH_CHECK();
-  const double target = (double)recall_p * (double)L.N;
-  if (budget_mode == 2) {                      // every head its own budget, written straight to budget[B,Hq]
-    hipLaunchKernelGGL(radix_budget_kernel, dim3(L.Hq, L.B), dim3(kSelThreads), 0, st, key_scores, L.N, L.ld, L.Hq, flattest,
-                       1, target, budget);
-    OMNI_LAUNCH_CHECK();
-  } else if (budget_mode == 0) {
-    hipLaunchKernelGGL(radix_budget_kernel, dim3(1, L.B), dim3(kSelThreads), 0, st, key_scores, L.N, L.ld, L.Hq, flattest, 0,
-                       target, budget);
-    OMNI_LAUNCH_CHECK();
-  } else {
-    hipLaunchKernelGGL(radix_budget_kernel, dim3(L.Hq, L.B), dim3(kSelThreads), 0, st, key_scores, L.N, L.ld, L.Hq, flattest,
-                       1, target, per_head);
-    OMNI_LAUNCH_CHECK();
-    hipLaunchKernelGGL(max_over_heads_kernel, dim3(L.B), dim3(64), 0, st, per_head, L.Hq, budget);
-    OMNI_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(radix_select_kernel, dim3(BH), dim3(kSelThreads), 0, st, key_scores, L.ld, L.Hq, 0, L.N, 0, budget,
-                     budget_mode == 2 ? 1 : 0, std::min(k_cap, L.N), 0, thr, need, recall, (float)L.N);
-  OMNI_LAUNCH_CHECK();
-  return OMNI_OK;
+  const size_t BH = (size_t)L.B * L.Hq;
+  SelWs w{};
+  w.thr = a.take<unsigned>(BH);
+  w.need = a.take<int>(BH);
+  int* own = a.take<int>(BH);
+  KeySource src;
+  const int rc = launch_stats(L, Ragged{}, key_scores, recall_p, budget_mode, kurt, own, flattest, budget, recall, L.N,
+                              &src, st);
+  if (rc != OMNI_OK) return rc;
+  const ListJob job = list_job(w, key_scores, key_rule(), nullptr, 0, nullptr);   // the cut for the recall only: no list
+  return launch_cut(L, Ragged{}, 1, job, src, job, src, st);
 }
 
-// Key selection from the thresholds that run_budget_stats left in its workspace (the recall pass finds, per
-// head, the k-th largest score for k = min(budget, k_cap): the cut of the key-mask equation for that budget).
-int run_select_kv_from_stats(const Layer& L, const float* key_scores, void* stats_ws, int b_cap, int* kv_idx,
-                             void* ws, hipStream_t st) {
-  Arena sa(stats_ws);
-  const int BH = L.B * L.Hq;
-  const unsigned* thr = sa.take<unsigned>(BH);
-  const int* need = sa.take<int>(BH);
-  Arena a(ws);
-  SelWs w = carve_select(a, L);
-  KeepRule rule;
-  rule.lo = 0;
-  rule.hi = L.N;
-  rule.keep_all_head0 = 0;
-  rule.use_table = 1;
-  rule.thr_scalar = 0;
-  return compact(key_scores, BH, L.N, L.ld, L.Hq, rule, thr, need, w.cnt_keep, w.cnt_eq, kv_idx, b_cap, nullptr, st);
+size_t select_lists_ws(const Layer& L) {
+  Arena a(nullptr);
+  carve_select(a, L);
+  carve_select(a, L);
+  a.take<int>((size_t)L.B * L.Hq);
+  return a.used();
 }
 
-int run_select_kv_counts(const Layer& L, const float* key_scores, void* stats_ws, int b_cap, int* kv_idx, void* ws,
-                         SelectSource* src, hipStream_t st) {
-  Arena sa(stats_ws);
-  const int BH = L.B * L.Hq;
-  const unsigned* thr = sa.take<unsigned>(BH);
-  const int* need = sa.take<int>(BH);
+int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int q_mode, float q_param, int* q_idx,
+                     int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,
+                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st, SelectSource* sel) {
   Arena a(ws);
-  SelWs w = carve_select(a, L);
-  KeepRule rule;
-  rule.lo = 0;
-  rule.hi = L.N;
-  rule.keep_all_head0 = 0;
-  rule.use_table = 1;
-  rule.thr_scalar = 0;
-  const int nchunk = cdiv(L.N, kChunk);
-  hipLaunchKernelGGL(chunk_count_kernel, dim3(nchunk, BH), dim3(kChunkThreads), 0, st, key_scores, L.N, L.ld, L.Hq, rule,
-                     thr, nchunk, w.cnt_keep, w.cnt_eq);
-  OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL(chunk_scan_kernel, dim3(BH), dim3(64), 0, st, nchunk, rule, need, w.cnt_keep, w.cnt_eq,
-                     (int*)nullptr, b_cap);
-  OMNI_LAUNCH_CHECK();
-  src->x = key_scores;
-  src->ld = L.ld;
-  src->nchunk = nchunk;
-  src->thr = thr;
-  src->need = need;
-  src->off_keep = w.cnt_keep;
-  src->off_eq = w.cnt_eq;
-  src->out = kv_idx;
-  src->out_stride = b_cap;
-  return OMNI_OK;
+  const SelWs wk = carve_select(a, L), wq = carve_select(a, L);
+  int* own = a.take<int>((size_t)L.B * L.Hq);
+  KeySource ks, qs;
+  int rc = launch_stats(L, rg, key_scores, recall_p, budget_mode, kurt, own, flattest, budget, recall, b_cap, &ks, st);
+  if (rc != OMNI_OK) return rc;
+  const ListJob kj = list_job(wk, key_scores, key_rule(), kv_idx, b_cap, nullptr);
+  const ListJob qj = query_job(L, wq, scores, q_mode, q_param, q_idx, q_cnt, &qs);
+  rc = launch_cut(L, rg, 2, qj, qs, kj, ks, st);
+  if (rc != OMNI_OK) return rc;
+  if (!sel) return launch_write(L, rg, 2, qj, kj, st);
+  sel->x = key_scores;
+  sel->ld = L.ld;
+  sel->nchunk = cdiv(L.N, kChunk);
+  sel->thr = wk.thr;
+  sel->need = wk.need;
+  sel->off_keep = wk.cnt_keep;
+  sel->off_eq = wk.cnt_eq;
+  sel->out = kv_idx;
+  sel->out_stride = b_cap;
+  return launch_write(L, rg, 1, qj, qj, st);
 }
 
 // ---- union of the stored visual rows over the heads of a KV group, with a membership bit per head

@@ -1,0 +1,98 @@
+"""The cut search and the list writers on score vectors where they can go wrong: lengths at the edges of a trip, of a
+chunk and of a wavefront; more elements in one bin than the list in LDS holds; long runs of equal scores; few elements
+left to rank; negative, zero, infinite and NaN scores.  The oracle's selection on the same float32 arrays is the answer,
+bit for bit for the index sets and budgets."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import omni_oracle as oc
+from paper_2511_12201_amd import binding as ob
+from tests.helpers import check_selection_on_gpu_scores, padded_to_lists
+
+pytestmark = pytest.mark.gpu
+
+
+def _scores(kind, rng, H, N):
+    if kind == "lognormal":
+        a = np.exp(1.5 * rng.standard_normal((1, H, N)))
+    elif kind == "narrow":              # one bin of the first digit holds everything
+        a = 1.0 + 0.2 * rng.random((1, H, N))
+    elif kind == "equal":
+        a = np.full((1, H, N), 0.75)
+    elif kind == "steps":               # runs of equal scores, the cut inside one
+        a = np.floor(4 * rng.random((1, H, N))) + 0.5
+    else:                               # "zeros": more than half of the scores carry no mass
+        a = np.maximum(rng.standard_normal((1, H, N)) - 0.5, 0.0)
+        a[..., 0] = 1.0
+    return np.ascontiguousarray(a * (N / a.sum(-1, keepdims=True)), dtype=np.float32)
+
+
+def _desc(H, N, v0, v1):
+    q = torch.empty(1, H, N, 64, dtype=torch.bfloat16, device="cuda")
+    return ob.make_layer_desc(q, q, v0, v1, 0, True)
+
+
+@pytest.mark.parametrize("kind", ["lognormal", "narrow", "equal", "steps", "zeros"])
+@pytest.mark.parametrize("N", [1, 2, 63, 65, 1023, 1025, 8193, 20001])
+def test_budget_and_lists_on_scores_in_hand(N, kind):
+    H, rng = 3, np.random.default_rng(N)
+    a = _scores(kind, rng, H, N)
+    s = rng.random((1, H, N)).astype(np.float32) if kind != "equal" else np.full((1, H, N), 0.3, np.float32)
+    v0, v1 = (0, 1) if N < 3 else (1, N - 1)
+    d, da, ds = _desc(H, N, v0, v1), torch.from_numpy(a).cuda(), torch.from_numpy(s).cuda()
+    for mode, p, q_mode, q_param in ((0, 0.95, 0, 0.3), (1, 0.5, 1, 0.37), (2, 1.0, 1, 1.0), (2, 0.2, 0, 0.9)):
+        r = ob.omni_budget_from_scores(d, da, p, mode)
+        kv = (ob.omni_select_kv_per_head if mode == 2 else ob.omni_select_kv)(d, da, r.budget, N)
+        q_idx, q_cnt = ob.omni_select_queries(d, ds, q_mode, q_param)
+        torch.cuda.synchronize()
+        bud = r.budget.cpu().numpy()
+        check_selection_on_gpu_scores(oc, s, a, padded_to_lists(q_idx, q_cnt), r.flattest.cpu().numpy(), bud,
+                                      kv.cpu().numpy(), q_mode, q_param, p, mode, v0, v1)
+        for h in range(H):
+            top = np.sort(a[0, h].astype(np.float64))[::-1][: int(bud[0, h] if mode == 2 else bud[0])]
+            # masses are truncated to 2^-40 each, the recall is stored in fp32
+            assert abs(float(r.recall[0, h]) - top.sum() / N) <= 2.0 ** -23
+
+
+def test_lists_with_infinite_negative_and_nan_scores():
+    """The order of the keys is that of the floats, NaN above infinity; counts and ties follow it."""
+    N, H = 3000, 2
+    rng = np.random.default_rng(5)
+    a = rng.standard_normal((1, H, N)).astype(np.float32)
+    a[0, :, 10:20], a[0, :, 20:40], a[0, :, 40:60] = np.inf, -np.inf, np.nan
+    a[0, 1, 100:1500] = -3.0e38
+    d, da = _desc(H, N, 0, N), torch.from_numpy(a).cuda()
+    u = a.view(np.uint32).astype(np.int64)
+    key = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)
+    for b in (1, 25, 30, 700, 1600, 2985, N):
+        kv = ob.omni_select_kv(d, da, torch.tensor([b], dtype=torch.int32, device="cuda"), N).cpu().numpy()
+        for h in range(H):
+            order = np.lexsort((np.arange(N), -key[0, h]))
+            np.testing.assert_array_equal(kv[0, h, :b], np.sort(order[:b]))
+
+
+def test_padded_batch_with_scratch_for_one_sequence_gives_the_same():
+    """A workspace for one sequence takes a batch one sequence at a time: the outputs of the batch in one go."""
+    B, H, Hkv, N, D = 3, 4, 2, 700, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q = torch.randn(B, H, N, D, generator=g, device="cuda").bfloat16()
+    K = torch.randn(B, Hkv, N, D, generator=g, device="cuda").bfloat16()
+    d = ob.make_layer_desc(Q, K, 0, N - 9, 0, True)
+    one = ob.make_layer_desc(Q[:1], K[:1], 0, N - 9, 0, True)
+    args = ([700, 333, 40], [0, 5, 1], [690, 300, 33], 1, 0.4, 0.8, 32, 1)
+
+    class Small(ob.Workspace):
+        def get(self, call_id, desc, param=0):
+            return super().get(call_id, one, param)
+
+    x, y = (ob.omni_prefill_select_varlen(d, Q, K, *args, ws=w) for w in (ob.Workspace(), Small()))
+    torch.cuda.synchronize()
+    for i, n in enumerate(args[0]):
+        assert torch.equal(x.scores[i, :, :n], y.scores[i, :, :n])
+        assert torch.equal(x.budget.key_scores[i, :, :n], y.budget.key_scores[i, :, :n])
+        assert torch.equal(x.q_idx[i, 1, : int(x.q_cnt[i, 1])], y.q_idx[i, 1, : int(x.q_cnt[i, 1])])
+        assert torch.equal(x.kv_idx[i, :, : int(x.budget.budget[i])], y.kv_idx[i, :, : int(x.budget.budget[i])])
+    for u, v in ((x.q_cnt, y.q_cnt), (x.budget.budget, y.budget.budget), (x.budget.recall, y.budget.recall),
+                 (x.budget.kurtosis, y.budget.kurtosis), (x.probe_keys, y.probe_keys)):
+        assert torch.equal(u, v)
