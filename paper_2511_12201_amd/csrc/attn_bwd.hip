@@ -1157,29 +1157,10 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
 
 // ------------------------------------------------------------------ dK, dV = sum over the heads of a KV group
 
-// inv[bh, token] = slot of the token in the head's selected list, -1 if it is not selected: the reduction then
-// finds a head's partial row with one load instead of a binary search of dependent loads.
-__global__ __launch_bounds__(256) void fill_int_kernel(int* __restrict__ p, long long n, int v) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-// grid: (cdiv(b_cap, 256), B*Hq)
-__global__ __launch_bounds__(256) void inverse_list_kernel(const int* __restrict__ kv_idx, const int* __restrict__ budget,
-                                                           int bph, int Hq, int b_cap, int N, int* __restrict__ inv) {
-  const int bh = blockIdx.y, b = bh / Hq;
-  const int nkeys = min(budget[budget_slot(bph, b, bh)], b_cap);
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nkeys) return;
-  const int tok = kv_idx[(long long)bh * b_cap + t];
-  if (tok >= 0 && tok < N) inv[(long long)bh * N + tok] = t;
-}
-
-
 // grid: (ceil(N / rows_per_block), B*Hkv); one token row per D/4 lanes.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, const int* __restrict__ kv_idx,
-                                                                  const int* __restrict__ inv, T* __restrict__ dK,
-                                                                  T* __restrict__ dV) {
+__global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, const int* __restrict__ inv,
+                                                                  T* __restrict__ dK, T* __restrict__ dV) {
   constexpr int LPR = D / 4;
   constexpr int RPB = kThreads / LPR;
   const Layer& L = p.L;
@@ -1190,15 +1171,7 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, 
   f32x4 ak = {0.f, 0.f, 0.f, 0.f}, av = {0.f, 0.f, 0.f, 0.f};
   for (int j = 0; j < L.G; ++j) {
     const int bh = b * L.Hq + g * L.G + j;
-    int pos;
-    if (inv) {
-      pos = inv[(long long)bh * L.N + n];                       // slot of token n in the head's list, or -1
-    } else {
-      const int* list = kv_idx + (long long)bh * p.b_cap;
-      const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
-      pos = lower_pos(list, nkeys, n);
-      if (!(pos < nkeys && list[pos] == n)) pos = -1;
-    }
+    const int pos = inv[(long long)bh * L.N + n];               // slot of token n in the head's list, or -1
     if (pos >= 0) {
       int n_sp = 1;
       if (p.nsplit > 1) {                  // as the key kernels counted: the query tiles from the tile's first visible pair on
@@ -1224,20 +1197,6 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, 
   } else {
     *reinterpret_cast<f32x4*>(dK + o) = ak;
     *reinterpret_cast<f32x4*>(dV + o) = av;
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void clear_rows_kernel(T* __restrict__ X, Layer L) {
-  constexpr int E = Elem<T>::kPer16B;
-  const int CPR = L.D / E;
-  const int bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq;
-  T* base = X + b * L.qs[0] + i * L.qs[1];
-  const int row0 = blockIdx.x * 64;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int c = threadIdx.x; c < 64 * CPR; c += kThreads) {
-    const int r = row0 + c / CPR;
-    if (r < L.N) *reinterpret_cast<u32x4*>(base + (long long)r * L.qs[2] + (c % CPR) * E) = zero;
   }
 }
 
@@ -1345,9 +1304,6 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, dt == OMNI_BF16 ? w.Qn : nullptr,
                   dt == OMNI_BF16 ? w.dOn : nullptr, w.lse2c, w.deltac, st);
   if (rc != OMNI_OK) return rc;
-  hipLaunchKernelGGL((clear_rows_kernel<T>), dim3(cdiv(L.N, 64), L.B * L.Hq), dim3(kThreads), 0, st,
-                     static_cast<T*>(dQ), L);
-  OMNI_LAUNCH_CHECK();
   BwdParams p;
   p.Q = Q;
   p.dO = dO;
@@ -1381,12 +1337,28 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_stride = cap_keys / kTileN;
   p.npad_kv = BLOCKS ? npad_kv : npad;
   constexpr bool kFast = sizeof(T) == 2;
-  if constexpr (kFast) {
-    rc = run_visible_counts(L, q_idx, q_cnt, w.kidx, budget, b_cap, npad, w.qvis, w.kfirst, st);
+  const int tile_m = kFast ? kDqTileM : kTileM;
+  {
+    Bounds bn{};                                 // bf16: masks by position; both: slot map, cleared rows, dQ's work items
+    bn.q_idx = q_idx;
+    bn.q_cnt = q_cnt;
+    bn.klist = w.kidx;
+    bn.klist_stride = npad;
+    bn.budget = budget;
+    bn.b_cap = b_cap;
+    bn.npad = npad;
+    bn.qvis = kFast ? w.qvis : nullptr;
+    bn.kfirst = kFast ? w.kfirst : nullptr;
+    bn.inv = w.inv;
+    bn.X = dQ;
+    bn.elem_bytes = sizeof(T);
+    bn.tile_m = tile_m;
+    bn.sched = w.sched;
+    rc = run_bounds(L, bn, st);
     if (rc != OMNI_OK) return rc;
   }
-  p.order_off = sched_order_off(L.B * L.Hq, L.N, kFast ? kDqTileM : kTileM);
-  rc = run_schedule(L, q_cnt, budget, b_cap, kFast ? kDqTileM : kTileM, kFast ? w.qvis : nullptr, w.sched, st);
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
+  rc = run_order(L, q_cnt, tile_m, w.sched, st);
   if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfBwdDkDv, st);
@@ -1421,15 +1393,8 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   {
     ProfScope prof__(kProfBwdReduce, st);
     constexpr int RPB = kThreads / (D / 4);
-    const long long n_inv = (long long)L.B * L.Hq * L.N;
-    hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)std::min<long long>(cdiv(n_inv, 256LL), 8192)), dim3(256), 0, st,
-                       w.inv, n_inv, -1);
-    OMNI_LAUNCH_CHECK();
-    hipLaunchKernelGGL(inverse_list_kernel, dim3(cdiv(b_cap, 256), L.B * L.Hq), dim3(256), 0, st, kv_idx, budget, L.bph, L.Hq,
-                       b_cap, L.N, w.inv);
-    OMNI_LAUNCH_CHECK();
     hipLaunchKernelGGL((attn_bwd_reduce_kernel<T, D>), dim3(cdiv(L.N, RPB), L.B * L.Hkv), dim3(kThreads), 0, st, p,
-                       kv_idx, w.inv, static_cast<T*>(dK), static_cast<T*>(dV));
+                       w.inv, static_cast<T*>(dK), static_cast<T*>(dV));
     OMNI_LAUNCH_CHECK();
   }
   return OMNI_OK;

@@ -46,22 +46,6 @@ constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// O = 0, lse = -inf for every row (kept rows are overwritten by the attention kernel).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void clear_output_kernel(T* __restrict__ O, float* __restrict__ lse, Layer L) {
-  constexpr int E = Elem<T>::kPer16B;
-  const int CPR = L.D / E;
-  const int bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq;
-  T* base = O + b * L.qs[0] + i * L.qs[1];
-  const int row0 = blockIdx.x * 64;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int c = threadIdx.x; c < 64 * CPR; c += kThreads) {
-    const int r = row0 + c / CPR;
-    if (r < L.N) *reinterpret_cast<u32x4*>(base + (long long)r * L.qs[2] + (c % CPR) * E) = zero;
-  }
-  if (threadIdx.x < 64 && row0 + (int)threadIdx.x < L.N) lse[(long long)bh * L.N + row0 + threadIdx.x] = -INFINITY;
-}
-
 // ------------------------------------------------------------------ attention
 
 struct FwdParams {
@@ -836,6 +820,27 @@ FwdWs carve_fwd(Arena& a, const Layer& L, int dtype, int heads, int npad, bool s
   return w;
 }
 
+// What the forward needs to know about every token: visible counts, cleared rows, the items of the work list.
+int run_fwd_bounds(const Layer& L, const int* q_idx, const int* q_cnt, const int* klist, int klist_stride,
+                   const int* budget, int b_cap, int* qvis, void* O, int elem_bytes, float* lse, int tile_m, int* sched,
+                   hipStream_t st) {
+  ProfScope prof__(kProfClear, st);
+  Bounds b{};
+  b.q_idx = q_idx;
+  b.q_cnt = q_cnt;
+  b.klist = klist;
+  b.klist_stride = klist_stride;
+  b.budget = budget;
+  b.b_cap = b_cap;
+  b.qvis = qvis;
+  b.X = O;
+  b.elem_bytes = elem_bytes;
+  b.lse = lse;
+  b.tile_m = tile_m;
+  b.sched = sched;
+  return run_bounds(L, b, st);
+}
+
 template <typename T, int D>
 int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, const int* q_idx, const int* q_cnt,
                const int* kv_idx, const int* budget, int b_cap, void* O, float* lse, void* ws, bool sparse,
@@ -851,14 +856,6 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
                          dt == OMNI_BF16 ? nullptr : w.Vp, nullptr, dt == OMNI_BF16 ? w.Vp : nullptr, w.kidx, st,
                          sparse ? sel : nullptr);
     if (rc != OMNI_OK) return rc;
-  }
-  if (sparse) {
-    {
-      ProfScope prof__(kProfClear, st);
-      hipLaunchKernelGGL((clear_output_kernel<T>), dim3(cdiv(L.N, 64), L.B * L.Hq), dim3(kThreads), 0, st,
-                         static_cast<T*>(O), lse, L);
-      OMNI_LAUNCH_CHECK();
-    }
   }
   FwdParams p;
   p.Q = Q;
@@ -879,21 +876,22 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.qvis = w.qvis;
   p.tile_map = nullptr;
   p.tile_stride = 0;
-  if (w.qvis) {
-    int rc = run_visible_counts(L, q_idx, q_cnt, w.kidx, budget, b_cap, npad, w.qvis, nullptr, st);
-    if (rc != OMNI_OK) return rc;
-  }
   constexpr bool kFast = sizeof(T) == 2;
-  {
-    p.order_off = sched_order_off(L.B * L.Hq, L.N, kFast ? kFastTileM : kTileM);
-    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
-    // (16.2 -> 5.3 GB from beyond L2 per launch at 64k, at the same kernel time).  The dense baseline and the
-    // in-place block lists read one copy per KV group, which the heads of a group already share: splitting them
-    // over queues only costs (25.7 -> 25.9 ms dense).
-    int rc = run_schedule(L, q_cnt, budget, b_cap, kFast ? kFastTileM : kTileM, w.qvis, w.sched, st,
-                          kFast && sparse ? kSchedQueues : 1);
+  const int tile_m = kFast ? kFastTileM : kTileM;
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
+  int rc;
+  if (sparse) {
+    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m, w.sched, st);
     if (rc != OMNI_OK) return rc;
+    // Per-head gathered K/V: one queue per XCD where the launch is long enough, so that the workgroups on a head share
+    // its tiles in that XCD's L2 (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
+    // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
+    // costs (25.7 -> 25.9 ms dense).
+    rc = run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1);
+  } else {
+    rc = run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
   }
+  if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfAttnFwd, st);
     if constexpr (kFast) {
@@ -954,19 +952,14 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
                        w.f.kidx, st);
   if (rc != OMNI_OK) return rc;
-  {
-    ProfScope prof__(kProfClear, st);
-    hipLaunchKernelGGL((clear_output_kernel<T>), dim3(cdiv(L.N, 64), L.B * L.Hq), dim3(kThreads), 0, st,
-                       static_cast<T*>(O), lse, L);
-    OMNI_LAUNCH_CHECK();
-  }
   // token lists of the selected blocks (for the causal bounds) and the tile map
   rc = run_expand_blocks(L, blk_idx, blk_budget, blk_cap, block, w.klist, w.vbudget, cap_keys, st);
   if (rc != OMNI_OK) return rc;
   hipLaunchKernelGGL(tile_map_kernel, dim3(cdiv(blk_cap * tpb, 256), L.B * L.Hq), dim3(256), 0, st, blk_idx, blk_budget,
                      L.Hq, blk_cap, tpb, npad / kTileN - 1, w.tile_map);
   OMNI_LAUNCH_CHECK();
-  rc = run_visible_counts(L, q_idx, q_cnt, w.klist, w.vbudget, cap_keys, cap_keys, w.f.qvis, nullptr, st);
+  rc = run_fwd_bounds(L, q_idx, q_cnt, w.klist, cap_keys, w.vbudget, cap_keys, w.f.qvis, O, sizeof(T), lse, kFastTileM,
+                      w.f.sched, st);
   if (rc != OMNI_OK) return rc;
   FwdParams p;
   p.Q = Q;
@@ -988,7 +981,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   p.tile_map = w.tile_map;
   p.tile_stride = blk_cap * tpb;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, kFastTileM);
-  rc = run_schedule(L, q_cnt, w.vbudget, cap_keys, kFastTileM, w.f.qvis, w.f.sched, st);
+  rc = run_order(L, q_cnt, kFastTileM, w.f.sched, st);
   if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfAttnFwd, st);

@@ -22,10 +22,10 @@
 // Layout of the int array in device memory:
 //   [0] unused   [1] number of items   [2..3] unused
 //   [4 .. 11] cursor[q]: next position of queue q   [12 .. 19] end[q]   (one queue: cursor[0] = 0, end[0] = items)
-//   [20 .. 20 + BH]          head_prefix[BH + 1]  (cumulative tile counts, head-major item ids)
-//   [.. + BH]                head_cost[BH]        (sum of the head's item costs)
-//   [.. + BH]                head_place[BH]       (queue << 16 | position of the head inside its queue)
-//   [.. + 2 * cap]           sort keys of the items by id (64-bit, see sched_key)
+//   [20 .. 20 + BH]          head_prefix[BH + 1]  (cumulative tile counts, head-major item ids; host mirror only)
+//   [.. + BH]                head_cost[BH]        (sum of the head's item costs; host mirror only)
+//   [.. + BH]                head_place[BH]       (queue << 16 | position of the head inside its queue; host mirror only)
+//   [.. + 2 * cap]           items by id: (head << 16 | tile), cost
 //   [.. + cap]               order[k] = (head << 16 | tile) of the k-th item to hand out
 // with cap = BH * ceil(N / tile_m) the largest possible number of items.
 #pragma once
@@ -41,14 +41,32 @@ constexpr int kSchedMaxQueuedHeads = 1024;       // more heads than this: one qu
 inline size_t sched_cap(int BH, int N, int tile_m) { return (size_t)BH * ((N + tile_m - 1) / tile_m); }
 __host__ __device__ inline size_t sched_head_cost_off(int BH) { return (size_t)kSchedPrefix + BH + 1; }
 __host__ __device__ inline size_t sched_head_place_off(int BH) { return sched_head_cost_off(BH) + BH; }
-inline size_t sched_keys_off(int BH) { return (sched_head_place_off(BH) + BH + 1) & ~(size_t)1; }      // 8-byte aligned
+__host__ __device__ inline size_t sched_keys_off(int BH) { return (sched_head_place_off(BH) + BH + 1) & ~(size_t)1; }      // 8-byte aligned
 inline size_t sched_order_off(int BH, int N, int tile_m) { return sched_keys_off(BH) + 2 * sched_cap(BH, N, tile_m); }
 inline size_t sched_ints(int BH, int N, int tile_m) { return sched_order_off(BH, N, tile_m) + sched_cap(BH, N, tile_m); }
 
-// qvis (nullable): [B*Hq, N] visible packed keys per kept-query position, for exact costs
-// queues: 1 (one longest-first list) or kSchedQueues (one list per XCD, whole heads per queue)
-int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, const int* qvis, int* sched,
-                 hipStream_t st, int queues = 1);
+// What the kept-query and key lists say about every token, in one pass over the tokens (run_bounds); null: not wanted.
+struct Bounds {
+  const int *q_idx, *q_cnt;      // [B*Hq, N], [B*Hq]
+  const int* klist;              // [B*Hq, klist_stride] ascending token indices, the first min(budget, b_cap) of a head
+  int klist_stride;
+  const int* budget;
+  int b_cap, npad;
+  int* qvis;                     // [B*Hq, N] number of listed keys that kept query `pos` may see
+  int* kfirst;                   // [B*Hq, npad] first kept-query position that may see listed key `slot`
+  int* inv;                      // [B*Hq, N] slot of the token in the key list, -1: not listed
+  void* X;                       // rows of the Q-shaped tensor (16-byte aligned) that are not kept are set to zero
+  int elem_bytes;
+  float* lse;                    // [B*Hq, N] -inf for the rows that are not kept
+  int tile_m;                    // rows per work item
+  int* sched;                    // the items of the work list and their costs (not their order)
+};
+int run_bounds(const Layer& L, const Bounds& p, hipStream_t st);
+
+// The order of the work list from its items: queues = 1 (one longest-first list) or kSchedQueues (one list per XCD, whole
+// heads per queue, where that pays).  run_schedule forms the items too, with costs estimated from the tile's position.
+int run_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, hipStream_t st, int queues = 1);
+int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, int* sched, hipStream_t st);
 int persistent_grid();      // workgroups that fill the device at two per CU
 
 // Called by one thread.  Position in the hand-out order of the next item, or -1 when every queue is drained:
@@ -114,7 +132,15 @@ __host__ __device__ inline bool sched_queues_pay(long long total_cost, long long
   return 2 * largest_head * queues <= 3 * total_cost;
 }
 
-// Heads onto queues (host mirror of sched_assign_kernel).  Writes head_place, cursor and end.
+// A queue hands out head after head, so the long items of its last head start late: queues only pay where a workgroup's
+// share is several times the longest item.  Shares of 2.3 longest items (28 heads at 32k, a third of the queries kept):
+// 1569 us with queues, 1523 without; of 4.6 (64k): 5495 with, 5655 without; below that the list alone is up to 10 %
+// faster.  `workgroups`: one per CU.
+__host__ __device__ inline bool sched_long_enough(long long total_cost, long long largest_item, int workgroups) {
+  return 10 * total_cost >= 34 * largest_item * workgroups;
+}
+
+// Heads onto queues (host mirror of sched_order_kernel's placement).  Writes head_place, cursor and end.
 inline void sched_assign_host(int* sched, int BH, int queues) {
   const int* prefix = sched + kSchedPrefix;
   const int* hcost = sched + sched_head_cost_off(BH);

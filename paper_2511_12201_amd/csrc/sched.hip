@@ -1,4 +1,5 @@
-// Builds the cost-sorted work list described in sched.h (three tiny kernels, no host sync).
+// Builds the cost-sorted work list described in sched.h, and the visibility bounds it is priced by: two small kernels, no
+// host sync.
 #include "sched.h"
 
 #include <algorithm>
@@ -8,205 +9,250 @@ namespace omni {
 
 namespace {
 
-// one thread: cumulative tile counts of the heads, total, counter
-__global__ void sched_prefix_kernel(const int* __restrict__ q_cnt, int BH, int N, int tile_m, int* __restrict__ sched) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int items = 0;
-  for (int bh = 0; bh < BH; ++bh) {
-    const int nq = q_cnt ? q_cnt[bh] : N;
-    sched[kSchedPrefix + bh] = items;
-    items += nq > 0 ? (nq + tile_m - 1) / tile_m : 0;
+constexpr int kThreads = 256;
+
+__device__ __forceinline__ int tiles_of(const int* __restrict__ q_cnt, int bh, int N, int tile_m) {
+  const int nq = q_cnt ? q_cnt[bh] : N;
+  return nq > 0 ? (nq + tile_m - 1) / tile_m : 0;
+}
+
+// Items of the heads before bh; every lane of the wavefront gets the sum.
+__device__ __forceinline__ int items_before(const int* __restrict__ q_cnt, int bh, int N, int tile_m) {
+  int s = 0;
+  for (int i = lane_id(); i < bh; i += 64) s += tiles_of(q_cnt, i, N, tile_m);
+  return __builtin_amdgcn_readlane((int)wave_scan((unsigned)s), 63);
+}
+
+// First position of the ascending a[0, n) with a[pos] >= v, by a whole wavefront: 64 probes a step.
+__device__ __forceinline__ int wave_lower_bound(const int* __restrict__ a, int n, int v) {
+  int lo = 0, hi = n;
+  while (hi - lo > 64) {
+    const int step = (hi - lo + 63) >> 6, at = lo + (lane_id() + 1) * step - 1;
+    const int below = (int)__popcll(__ballot(at < hi && a[at] < v));
+    lo += below * step;
+    hi = min(lo + step, hi);
   }
-  sched[kSchedPrefix + BH] = items;
-  sched[kSchedTotal] = items;
-  for (int q = 0; q < kSchedQueues; ++q) {                 // one list; sched_assign_kernel cuts it into queues if asked to
-    sched[kSchedCursor + q] = q == 0 ? 0 : items;
-    sched[kSchedEnd + q] = items;
+  const int at = lo + lane_id();
+  return lo + (int)__popcll(__ballot(at < hi && a[at] < v));
+}
+
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+  v |= dpp_or_zero<0x111, 0xf>(v);
+  v |= dpp_or_zero<0x112, 0xf>(v);
+  v |= dpp_or_zero<0x114, 0xf>(v);
+  v |= dpp_or_zero<0x118, 0xf>(v);
+  v |= dpp_or_zero<0x142, 0xa>(v);
+  v |= dpp_or_zero<0x143, 0xc>(v);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Which of the tokens [r0, r0 + 64) the list holds (one bit each) and how many of its entries come before them.
+__device__ __forceinline__ unsigned long long list_window(const int* __restrict__ list, int n, int r0, int& before) {
+  before = wave_lower_bound(list, n, r0);
+  const int at = before + lane_id();
+  const int o = at < n ? list[at] - r0 : 64;
+  const unsigned lo = wave_or(o < 32 ? 1u << (o & 31) : 0u), hi = wave_or(o >= 32 && o < 64 ? 1u << (o & 31) : 0u);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// grid: (cdiv(max(N, npad), 256), B*Hq).  A wavefront owns 64 tokens: two windows of the lists give it the visible
+// counts, slots and kept rows of all of them, and it sets its dropped rows to zero meanwhile.  Bound by those stores (the
+// searches of the other wavefronts hide under them).  It took the place of a search per kept query and per key
+// (visibility_kernel), a fill and a scatter of the slot map, a clearing pass over all rows and two list kernels:
+// before / after at 64k, 28 heads, forward: 83 / 73 us; backward at 32k: 55 / 35 us.
+__global__ __launch_bounds__(kThreads) void bounds_kernel(Layer L, Bounds p) {
+  const int bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq, lane = lane_id();
+  const int r0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kThreads + (threadIdx.x & ~63)));
+  const int nq = p.q_cnt[bh], nkeys = max(min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap), 0);
+  const int* klist = p.klist + (long long)bh * p.klist_stride;
+  const int n = r0 + lane;
+  if (p.kfirst && n < p.npad) {                    // pad slots and listed pads past the last token: nobody sees them
+    if (n >= nkeys) p.kfirst[(long long)bh * p.npad + n] = nq;
+    else if (klist[n] >= L.N) p.kfirst[(long long)bh * p.npad + n] = L.causal ? nq : 0;
+  }
+  if (r0 >= L.N) return;
+  int q_before, k_before;
+  const unsigned long long kept = list_window(p.q_idx + (long long)bh * L.N, nq, r0, q_before);
+  const unsigned long long keys = list_window(klist, nkeys, r0, k_before);
+  if (p.X) {
+    const int per_row = L.D * p.elem_bytes / 16;   // lanes that store one row: 8, 16 or 32
+    char* base = static_cast<char*>(p.X) + (b * L.qs[0] + i * L.qs[1]) * p.elem_bytes + lane % per_row * 16;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int r = lane / per_row; r < 64; r += 64 / per_row)
+      if (r0 + r < L.N && !(kept >> r & 1)) *reinterpret_cast<u32x4*>(base + (r0 + r) * L.qs[2] * p.elem_bytes) = zero;
+  }
+  const bool live = n < L.N;                       // no early exit: the wavefront stays whole for the scan below
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const int pos = q_before + (int)__popcll(kept & below), slot = k_before + (int)__popcll(keys & below);
+  const bool is_kept = kept >> lane & 1, is_key = keys >> lane & 1;
+  if (p.lse && live && !is_kept) p.lse[(long long)bh * L.N + n] = -INFINITY;
+  if (p.inv && live) p.inv[(long long)bh * L.N + n] = is_key ? slot : -1;
+  if (p.kfirst && is_key) p.kfirst[(long long)bh * p.npad + slot] = L.causal ? pos : 0;
+  const int visible = L.causal ? slot + (is_key ? 1 : 0) : nkeys;
+  if (p.qvis && is_kept) p.qvis[(long long)bh * L.N + pos] = visible;
+  const bool last = is_kept && (pos % p.tile_m == p.tile_m - 1 || pos == nq - 1);       // last row of a work item
+  if (!p.sched || !__any(last)) return;
+  const int before = items_before(p.q_cnt, bh, L.N, p.tile_m);
+  if (last) {
+    const int tq = pos / p.tile_m;
+    reinterpret_cast<int2*>(p.sched + sched_keys_off(L.B * L.Hq))[before + tq] =
+        make_int2((int)(((unsigned)bh << 16) | (unsigned)tq), (visible + kTileN - 1) / kTileN);
   }
 }
 
-struct ItemRef {
-  int bh, tq, nt;
-};
-
-__device__ __forceinline__ ItemRef item_of(const int* __restrict__ prefix, int BH, int id) {
-  int lo = 0, hi = BH;                     // largest bh with prefix[bh] <= id
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (prefix[mid] <= id) lo = mid; else hi = mid;
-  }
-  ItemRef r;
-  r.bh = lo;
-  r.tq = id - prefix[lo];
-  r.nt = prefix[lo + 1] - prefix[lo];
-  return r;
-}
-
-// thread per item id: its cost key
-__global__ __launch_bounds__(256) void sched_cost_kernel(const int* __restrict__ q_cnt, const int* __restrict__ budget,
-                                                         const int* __restrict__ qvis, int bph, int BH, int Hq, int N, int b_cap,
-                                                         int causal, int tile_m, size_t keys_off, int* __restrict__ sched) {
-  const int id = blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= sched[kSchedTotal]) return;
-  const ItemRef it = item_of(sched + kSchedPrefix, BH, id);
-  int nk = budget ? budget[budget_slot(bph, it.bh / Hq, it.bh)] : N;
+// grid: B*Hq.  The items of a head with costs estimated from their position (no key lists: the dense baseline).
+__global__ __launch_bounds__(64) void sched_estimate_kernel(const int* __restrict__ q_cnt, const int* __restrict__ budget,
+                                                            int b_cap, Layer L, int tile_m, int* __restrict__ sched) {
+  const int bh = blockIdx.x;
+  const int nt = tiles_of(q_cnt, bh, L.N, tile_m), before = items_before(q_cnt, bh, L.N, tile_m);
+  int nk = budget ? budget[budget_slot(L.bph, bh / L.Hq, bh)] : L.N;
   nk = nk < 0 ? 0 : (nk > b_cap ? b_cap : nk);
-  int cost;
-  if (qvis) {
-    const int nq = q_cnt ? q_cnt[it.bh] : N;
-    const int last = min((it.tq + 1) * tile_m, nq) - 1;
-    cost = (qvis[(long long)it.bh * N + last] + kTileN - 1) / kTileN;
-  } else {
-    cost = sched_estimate(it.tq, it.nt, nk, causal);
-  }
-  reinterpret_cast<unsigned long long*>(sched + keys_off)[id] = sched_key(cost, id);
+  int2* items = reinterpret_cast<int2*>(sched + sched_keys_off(L.B * L.Hq));
+  for (int tq = threadIdx.x; tq < nt; tq += 64)
+    items[before + tq] = make_int2((int)(((unsigned)bh << 16) | (unsigned)tq), sched_estimate(tq, nt, nk, L.causal));
 }
 
-// One workgroup: cost of every head, heads onto queues (largest first onto the least loaded queue), queue bounds,
-// and the queue and position of its head folded into every item's sort key.  queues <= 1 or too many heads: one
-// queue.  Everything the serial placement loop and the binary searches touch sits in LDS.
-constexpr int kAssignThreads = 1024;
-__global__ __launch_bounds__(kAssignThreads) void sched_assign_kernel(int BH, int queues, size_t keys_off, int* __restrict__ sched) {
-  __shared__ int sPrefix[kSchedMaxQueuedHeads + 1], sCost[kSchedMaxQueuedHeads], sOrder[kSchedMaxQueuedHeads],
-      sPlace[kSchedMaxQueuedHeads], sRankItems[kSchedMaxQueuedHeads], sRankPlace[kSchedMaxQueuedHeads], sShift;
-  __shared__ unsigned sRankCost[kSchedMaxQueuedHeads];
-  const int items_all = sched[kSchedTotal];
-  auto one_queue = [&]() {                                // the keys already carry place 0
-    if (threadIdx.x < kSchedQueues) {
-      sched[kSchedCursor + threadIdx.x] = threadIdx.x == 0 ? 0 : items_all;
-      sched[kSchedEnd + threadIdx.x] = items_all;
-    }
-    for (int bh = threadIdx.x; bh < BH; bh += kAssignThreads) sched[sched_head_place_off(BH) + bh] = 0;
-  };
-  if (queues <= 1 || BH > kSchedMaxQueuedHeads) {
-    one_queue();
-    return;
-  }
-  unsigned long long* keys = reinterpret_cast<unsigned long long*>(sched + keys_off);
-  for (int bh = threadIdx.x; bh <= BH; bh += kAssignThreads) sPrefix[bh] = sched[kSchedPrefix + bh];
-  for (int bh = threadIdx.x; bh < BH; bh += kAssignThreads) sCost[bh] = 0;
-  __syncthreads();
-  // head costs: a wavefront's 64 consecutive items belong to one head most of the time.  kBatch key loads are in
-  // flight together (one workgroup walks the whole list: a load per trip would cost a memory latency per trip).
-  constexpr int kBatch = 8;
-  for (int base = (threadIdx.x & ~63); base < items_all; base += kBatch * kAssignThreads) {
-    unsigned long long kv[kBatch];
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int id = base + e * kAssignThreads + (threadIdx.x & 63);
-      kv[e] = id < items_all ? keys[id] : 0ull;
-    }
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int id = base + e * kAssignThreads + (threadIdx.x & 63);
-      int bh = -1, c = 0;
-      if (id < items_all) {
-        bh = item_of(sPrefix, BH, id).bh;
-        c = (int)((kv[e] >> 32) & 0xffffu);
-      }
-      const int first = __shfl(bh, 0, 64);
-      if (__all(bh == first || bh < 0)) {
-        c = wave_sum(c);
-        if ((threadIdx.x & 63) == 0 && first >= 0) atomicAdd(&sCost[first], c);
-      } else if (bh >= 0) {
-        atomicAdd(&sCost[bh], c);
-      }
-    }
-  }
-  __syncthreads();
-  for (int bh = threadIdx.x; bh < BH; bh += kAssignThreads) {       // rank of a head: cost descending, index ascending
-    const int mine = sCost[bh];
-    int r = 0;
-    for (int j = 0; j < BH; ++j) r += (sCost[j] > mine || (sCost[j] == mine && j < bh)) ? 1 : 0;
-    sOrder[r] = bh;
-  }
-  __syncthreads();
-  // cost and item count in rank order, so that the serial placement loop reads LDS sequentially
-  if (threadIdx.x == 0) {
-    long long total = 0;
-    for (int bh = 0; bh < BH; ++bh) total += sCost[bh];
-    sShift = sched_queues_pay(total, sCost[sOrder[0]], queues) ? sched_cost_shift(total) : -1;
-  }
-  __syncthreads();
-  if (sShift < 0) {                                       // a head too large for a queue of its own: one list
-    one_queue();
-    return;
-  }
-  for (int r = threadIdx.x; r < BH; r += kAssignThreads) {
-    const int bh = sOrder[r];
-    sRankCost[r] = (unsigned)(sCost[bh] >> sShift) << 3;
-    sRankItems[r] = sPrefix[bh + 1] - sPrefix[bh];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned load[kSchedQueues];               // load << 3 | queue: the least loaded queue is one unsigned minimum
-    int heads[kSchedQueues], items[kSchedQueues];
-#pragma unroll
-    for (int q = 0; q < kSchedQueues; ++q) load[q] = q < queues ? (unsigned)q : 0xffffffffu, heads[q] = 0, items[q] = 0;
-    for (int n = 0; n < BH; ++n) {
-      unsigned m = load[0];
-#pragma unroll
-      for (int r = 1; r < kSchedQueues; ++r) m = min(m, load[r]);
-      const int q = (int)(m & 7u);
-      const unsigned c = sRankCost[n];
-      const int ni = sRankItems[n];
-#pragma unroll
-      for (int r = 0; r < kSchedQueues; ++r)               // compile-time indices keep the arrays in registers
-        if (r == q) {
-          sRankPlace[n] = (r << 16) | heads[r];
-          heads[r] += 1;
-          load[r] += c;
-          items[r] += ni;
-        }
-    }
-    int start = 0;
-#pragma unroll
-    for (int q = 0; q < kSchedQueues; ++q) {
-      sched[kSchedCursor + q] = start;
-      start += items[q];
-      sched[kSchedEnd + q] = start;
-    }
-  }
-  __syncthreads();
-  for (int r = threadIdx.x; r < BH; r += kAssignThreads) sPlace[sOrder[r]] = sRankPlace[r];
-  __syncthreads();
-  for (int bh = threadIdx.x; bh < BH; bh += kAssignThreads) {
-    sched[sched_head_place_off(BH) + bh] = sPlace[bh];
-    sched[sched_head_cost_off(BH) + bh] = sCost[bh];
-  }
-  for (int base = threadIdx.x; base < items_all; base += kBatch * kAssignThreads) {
-    unsigned long long kv[kBatch];
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int id = base + e * kAssignThreads;
-      kv[e] = id < items_all ? keys[id] : 0ull;
-    }
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int id = base + e * kAssignThreads;
-      if (id < items_all)
-        keys[id] = sched_key((int)((kv[e] >> 32) & 0xffffu), id, (unsigned)sPlace[item_of(sPrefix, BH, id).bh]);
-    }
-  }
-}
-
-// kRankLanes threads per item id: its rank among the keys (all distinct) is its place in the hand-out order
-constexpr int kRankLanes = 4;
-constexpr int kRankItems = 256 / kRankLanes;                // items per workgroup
-__global__ __launch_bounds__(256) void sched_rank_kernel(int BH, size_t keys_off, size_t order_off, int* __restrict__ sched) {
+// grid: cdiv(cap, kRankItems).  The hand-out order of the items: an item's rank among the keys (all distinct) is its
+// place.  Every workgroup places the heads on the queues for itself (a few hundred instructions: less than a launch),
+// the first one writes the header.  One launch where there were three (prefix, cost, placement, rank: 21 -> 5 us at 1k, 37 -> 17 us at 64k).
+constexpr int kRankLanes = 16;
+constexpr int kRankItems = kThreads / kRankLanes;           // items per workgroup
+struct QueuePlaces {
+  int place[kSchedMaxQueuedHeads], cost[kSchedMaxQueuedHeads], items[kSchedMaxQueuedHeads], order[kSchedMaxQueuedHeads];
+};
+__global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __restrict__ q_cnt, int BH, int N, int tile_m,
+                                                               int queues, int workgroups, size_t order_off,
+                                                               int* __restrict__ sched) {
   constexpr int kTile = 2048;                               // keys staged per pass: a 64k layer's list in one
   __shared__ unsigned long long tile[kTile];
-  const int n = sched[kSchedTotal];
+  __shared__ QueuePlaces sh;
+  __shared__ int s_wave[kThreads / 64], s_big[kThreads / 64], s_head[kThreads / 64];
+  __shared__ long long s_tot[kThreads / 64];
+  __shared__ int s_end[kSchedQueues];
+  const int2* items = reinterpret_cast<const int2*>(sched + sched_keys_off(BH));
+  const int wave = threadIdx.x >> 6;
+  // number of items
+  int n = 0;
+  for (int bh = threadIdx.x; bh < BH; bh += kThreads) n += tiles_of(q_cnt, bh, N, tile_m);
+  n = wave_sum(n);
+  if (lane_id() == 0) s_wave[wave] = n;
+  __syncthreads();
+  n = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) n += s_wave[w];
+  if (blockIdx.x > 0 && (int)blockIdx.x * kRankItems >= n) return;
+  bool queued = queues > 1 && BH <= kSchedMaxQueuedHeads;
+  if (queued) {
+    // head costs; whether queues pay
+    for (int bh = threadIdx.x; bh < BH; bh += kThreads) {
+      sh.cost[bh] = 0;
+      sh.items[bh] = tiles_of(q_cnt, bh, N, tile_m);
+    }
+    __syncthreads();
+    int big = 0;
+    long long tot = 0;
+    constexpr int kBatch = 4;                               // loads in flight
+    for (int j0 = 0; j0 < n; j0 += kBatch * kThreads) {
+      int2 it[kBatch];
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const int j = j0 + e * kThreads + (int)threadIdx.x;
+        it[e] = j < n ? items[j] : make_int2(0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const int bh = (int)((unsigned)it[e].x >> 16), first = __builtin_amdgcn_readfirstlane(bh);
+        big = max(big, it[e].y);
+        tot += it[e].y;
+        if (__all(bh == first || it[e].y == 0)) {           // 64 consecutive items belong to one head most of the time
+          const int c = (int)wave_scan((unsigned)it[e].y);
+          if (lane_id() == 63 && c) atomicAdd(&sh.cost[first], c);
+        } else if (it[e].y) {
+          atomicAdd(&sh.cost[bh], it[e].y);
+        }
+      }
+    }
+    __syncthreads();
+    int head = 0;
+    for (int bh = threadIdx.x; bh < BH; bh += kThreads) head = max(head, sh.cost[bh]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      big = max(big, __shfl_xor(big, o, 64));
+      head = max(head, __shfl_xor(head, o, 64));
+      tot += __shfl_xor(tot, o, 64);
+    }
+    if (lane_id() == 0) {
+      s_big[wave] = big;
+      s_head[wave] = head;
+      s_tot[wave] = tot;
+    }
+    __syncthreads();
+    big = head = 0;
+    tot = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+      big = max(big, s_big[w]);
+      head = max(head, s_head[w]);
+      tot += s_tot[w];
+    }
+    queued = sched_queues_pay(tot, head, queues) && sched_long_enough(tot, big, workgroups);
+    if (queued) {
+      const int shift = sched_cost_shift(tot);
+      for (int bh = threadIdx.x; bh < BH; bh += kThreads) {     // rank of a head: cost descending, index ascending
+        const int mine = sh.cost[bh];
+        int r = 0;
+        for (int j = 0; j < BH; ++j) r += (sh.cost[j] > mine || (sh.cost[j] == mine && j < bh)) ? 1 : 0;
+        sh.order[r] = bh;
+      }
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        unsigned load[kSchedQueues];           // load << 3 | queue: the least loaded queue is one unsigned minimum
+        int heads[kSchedQueues], count[kSchedQueues];
+#pragma unroll
+        for (int q = 0; q < kSchedQueues; ++q) load[q] = q < queues ? (unsigned)q : 0xffffffffu, heads[q] = 0, count[q] = 0;
+        for (int k = 0; k < BH; ++k) {
+          const int bh = sh.order[k];
+          unsigned m = load[0];
+#pragma unroll
+          for (int r = 1; r < kSchedQueues; ++r) m = min(m, load[r]);
+          const int q = (int)(m & 7u);
+          const unsigned c = (unsigned)(sh.cost[bh] >> shift) << 3;
+          const int ni = sh.items[bh];
+#pragma unroll
+          for (int r = 0; r < kSchedQueues; ++r)               // compile-time indices keep the arrays in registers
+            if (r == q) {
+              sh.place[bh] = (r << 16) | heads[r];
+              heads[r] += 1;
+              load[r] += c;
+              count[r] += ni;
+            }
+        }
+        int start = 0;
+#pragma unroll
+        for (int q = 0; q < kSchedQueues; ++q) s_end[q] = start += count[q];
+      }
+      __syncthreads();
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x < kSchedQueues) {
+    const int q = threadIdx.x;
+    sched[kSchedEnd + q] = queued ? s_end[q] : n;
+    sched[kSchedCursor + q] = q == 0 ? 0 : (queued ? s_end[q - 1] : n);
+    if (q == 0) sched[kSchedTotal] = n;
+  }
+  auto key_of = [&](int2 it, int id) {
+    return sched_key(it.y, id, queued ? (unsigned)sh.place[(unsigned)it.x >> 16] : 0u);
+  };
   const int id = blockIdx.x * kRankItems + threadIdx.x / kRankLanes, sub = threadIdx.x % kRankLanes;
-  const unsigned long long* keys = reinterpret_cast<const unsigned long long*>(sched + keys_off);
-  const unsigned long long mine = id < n ? keys[id] : 0ull;
+  const int2 own = id < n ? items[id] : make_int2(0, 0);
+  const unsigned long long mine = key_of(own, id);
   int rank = 0;
   for (int j0 = 0; j0 < n; j0 += kTile) {                   // uniform trip count: every thread helps to stage
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kTile / 256; ++u) {                 // independent loads: one memory latency per pass
-      const int j = j0 + u * 256 + (int)threadIdx.x;
-      tile[u * 256 + threadIdx.x] = j < n ? keys[j] : 0ull;
+    for (int u = 0; u < kTile / kThreads; ++u) {            // independent loads: one memory latency per pass
+      const int j = j0 + u * kThreads + (int)threadIdx.x;
+      tile[u * kThreads + threadIdx.x] = j < n ? key_of(items[j], j) : 0ull;
     }
     __syncthreads();
     const int m = min(kTile, n - j0);
@@ -215,34 +261,35 @@ __global__ __launch_bounds__(256) void sched_rank_kernel(int BH, size_t keys_off
   }
 #pragma unroll
   for (int o = 1; o < kRankLanes; o <<= 1) rank += __shfl_xor(rank, o, 64);
-  if (id < n && sub == 0) {
-    const ItemRef it = item_of(sched + kSchedPrefix, BH, id);
-    sched[order_off + rank] = (int)(((unsigned)it.bh << 16) | (unsigned)it.tq);
-  }
+  if (id < n && sub == 0) sched[order_off + rank] = own.x;
 }
 
 }  // namespace
 
-int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, const int* qvis, int* sched,
-                 hipStream_t st, int queues) {
-  const int BH = L.B * L.Hq;
-  if (BH >= 65536 || cdiv(L.N, tile_m) >= 65536) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
-  const size_t cap = sched_cap(BH, L.N, tile_m);
-  const size_t keys_off = sched_keys_off(BH), order_off = sched_order_off(BH, L.N, tile_m);
-  hipLaunchKernelGGL(sched_prefix_kernel, dim3(1), dim3(64), 0, st, q_cnt, BH, L.N, tile_m, sched);
-  OMNI_LAUNCH_CHECK();
-  const int blocks = (int)cdiv(cap, (size_t)256);
-  hipLaunchKernelGGL(sched_cost_kernel, dim3(blocks), dim3(256), 0, st, q_cnt, budget, qvis, L.bph, BH, L.Hq, L.N, b_cap, L.causal,
-                     tile_m, keys_off, sched);
-  OMNI_LAUNCH_CHECK();
-  if (queues > 1 && BH <= kSchedMaxQueuedHeads) {
-    hipLaunchKernelGGL(sched_assign_kernel, dim3(1), dim3(kAssignThreads), 0, st, BH, queues, keys_off, sched);
-    OMNI_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(sched_rank_kernel, dim3((unsigned)cdiv(cap, (size_t)kRankItems)), dim3(256), 0, st, BH, keys_off, order_off,
-                     sched);
+int run_bounds(const Layer& L, const Bounds& p, hipStream_t st) {
+  const int BH = L.B * L.Hq, n = p.kfirst ? max(L.N, p.npad) : L.N;
+  if (p.sched && (BH >= 65536 || cdiv(L.N, p.tile_m) >= 65536))
+    OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
+  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH), dim3(kThreads), 0, st, L, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
+}
+
+int run_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, hipStream_t st, int queues) {
+  const int BH = L.B * L.Hq;
+  const size_t cap = sched_cap(BH, L.N, tile_m);
+  hipLaunchKernelGGL(sched_order_kernel, dim3((unsigned)cdiv(cap, (size_t)kRankItems)), dim3(kThreads), 0, st, q_cnt, BH,
+                     L.N, tile_m, queues, persistent_grid() / 2, sched_order_off(BH, L.N, tile_m), sched);
+  OMNI_LAUNCH_CHECK();
+  return OMNI_OK;
+}
+
+int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, int* sched, hipStream_t st) {
+  const int BH = L.B * L.Hq;
+  if (BH >= 65536 || cdiv(L.N, tile_m) >= 65536) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
+  hipLaunchKernelGGL(sched_estimate_kernel, dim3(BH), dim3(64), 0, st, q_cnt, budget, b_cap, L, tile_m, sched);
+  OMNI_LAUNCH_CHECK();
+  return run_order(L, q_cnt, tile_m, sched, st);
 }
 
 void sched_build_host(const int* q_cnt, const int* budget, int B, int Hq, int N, int b_cap, int causal, int tile_m,

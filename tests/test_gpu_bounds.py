@@ -1,0 +1,60 @@
+"""The pass that turns the kept-query and key lists into visible counts, slots, cleared rows and work items: token counts
+at the edges of its 64-token windows and 256-row items, empty and full lists, outputs that start as NaN."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import omni_oracle as oc
+from paper_2511_12201_amd import binding as ob
+from paper_2511_12201_amd import synth
+from tests.helpers import grad_bar, lists_to_padded, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(rng, H, N):
+    """Kept queries: all, none, one, and random shares; keys: random sets of per-head sizes 0 .. N."""
+    pick = lambda n: np.sort(rng.choice(N, n, replace=False)).astype(np.int32)  # noqa: E731
+    q = [np.arange(N, dtype=np.int32), pick(0), pick(1), pick(-(-N // 3))]
+    k = [pick(n) for n in (-(-N // 2), N, 0, min(N, 70))]
+    return [q[:H]], [k[:H]]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 255, 257, 600])
+@pytest.mark.parametrize("causal", [True, False])
+def test_rows_slots_and_items_at_window_edges(N, dtype, d, causal):
+    H, Hkv, rng = 4, 2, np.random.default_rng(N + d)
+    mk = lambda h, s=1.0: s * rng.standard_normal((1, h, N, d)).astype(np.float32)  # noqa: E731
+    Q, K, V, dO = mk(H), mk(Hkv), mk(Hkv), mk(H, d ** -0.5)
+    if dtype == "bf16":
+        Q, K, V, dO = (synth.round_to_bf16(x) for x in (Q, K, V, dO))
+    q_lists, kv_lists = _lists(rng, H, N)
+    q_idx, q_cnt = lists_to_padded(q_lists, H, N)
+    kv_idx, budget = lists_to_padded(kv_lists, H, N)
+    tq, tk, tv, tg = (to_device(x, dtype) for x in (Q, K, V, dO))
+    desc = ob.make_layer_desc(tq, tk, 0, N, 0, causal)
+    nan = lambda x: torch.full_like(x, float("nan"))  # noqa: E731
+    O, lse = nan(tq), torch.full((1, H, N), float("nan"), device="cuda")
+    ob.omni_sparse_attn_fwd_per_head(desc, tq, tk, tv, q_idx, q_cnt, kv_idx, budget, N, O, lse)
+    dQ, dK, dV = ob.omni_sparse_attn_bwd_per_head(desc, tq, tk, tv, O, tg, lse, q_idx, q_cnt, kv_idx, budget, N, nan(tq),
+                                                  nan(tk), nan(tv))
+    torch.cuda.synchronize()
+    scale = d ** -0.5
+    Oo, Lo = oc.sparse_attn_fwd(Q, K, V, q_lists, kv_lists, causal, scale)
+    tol = 1e-4 if dtype == "f32" else 2e-2             # the bars of the parity tests
+    assert np.max(np.abs(to_host(O) - Oo)) <= tol
+    got = to_host(lse)
+    np.testing.assert_array_equal(np.isfinite(got), np.isfinite(Lo))
+    fin = np.isfinite(Lo)
+    if fin.any():
+        assert np.max(np.abs(got[fin] - Lo[fin])) <= (1e-4 if dtype == "f32" else 2e-3)
+    dropped = np.ones((1, H, N), dtype=bool)
+    for h in range(H):
+        dropped[0, h, q_lists[0][h]] = False
+    assert not to_host(O)[dropped].any() and not to_host(dQ)[dropped].any() and np.all(got[dropped] == -np.inf)
+    stored = to_host(O)
+    want = oc.sparse_attn_bwd(Q, K, V, dO, q_lists, kv_lists, causal, scale, O=stored)
+    rss = oc.sparse_attn_bwd_term_rss(Q, K, V, dO, q_lists, kv_lists, causal, scale, O=stored)
+    for x, w, r in zip((dQ, dK, dV), want, rss):
+        assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, dtype, r))
