@@ -28,6 +28,7 @@
 //    runs under the MFMAs of tile t+1.  Work items come from a persistent,
 //    longest-first work list with one queue per XCD (sched.hip); causal masks are
 //    position compares against per-query visible-prefix counts (pack.hip).
+//    Short sequences go through attn_fwd_split_kernel: 32-row items, key tiles dealt to the wavefronts.
 //  * fp32 inputs (attn_fwd_kernel, the accuracy path of the 1e-4 parity cases):
 //    256 threads = 4 wavefronts x 32 rows, fp32 32x32x2 MFMA, register-staged
 //    double buffer; not tuned.
@@ -791,6 +792,190 @@ __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParam
   }  // work-item loop
 }
 
+// ------------------------------------------------------------------ bf16, short sequences
+//
+// The kernel above needs long items: 256 rows keep its eight wavefronts busy for 2 us a tile, and a launch of a few dozen
+// items leaves most CUs idle while each walks its tiles one after the other (36 us for 60 items of at most 10 tiles).
+// Here an item is 32 kept queries and its four wavefronts share the key tiles, every fourth tile each, with softmax states
+// of their own that are merged at the end: eight times the items, a quarter of the chain.  No staging and no barrier in
+// the loop: both operands lie in fragment order in memory, so that a fragment is one contiguous kilobyte per wavefront, and
+// the next K tile is loaded under the softmax and the second product.  Every item reads its whole K/V prefix through the
+// CU's L1 (64 bytes a clock), which is what bounds it: an item of the kernel above shares those bytes between 256 rows.
+constexpr int kSplitWaves = 4;
+constexpr int kSplitThreads = kSplitWaves * 64;
+constexpr int kSplitRows = 32;
+
+// grid: (B*Hq, cdiv(N, kSplitRows)); a head's last rows, which see the most keys, first
+template <int D, bool TILEMAP>
+__global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdParams p) {
+  typedef u16 T;
+  constexpr int CH = D / 8, KS = D / 16, NB = D / 32;
+  constexpr int OP = D + 4;                          // floats between rows of the merge buffer
+  __shared__ __attribute__((aligned(16))) unsigned char sQ[kSplitRows * D * 2];
+  __shared__ __attribute__((aligned(16))) float sO[kSplitWaves][kSplitRows][OP];
+  __shared__ float sM[kSplitWaves][kSplitRows], sL[kSplitWaves][kSplitRows];
+  const Layer& L = p.L;
+  const int bh = blockIdx.x, b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
+  const int nq = p.q_cnt[bh];
+  const int tq = cdiv(nq, kSplitRows) - 1 - (int)blockIdx.y;
+  if (tq < 0) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int* qlist = p.q_idx + (long long)bh * L.N;
+  const int* qvis = p.qvis + (long long)bh * L.N;
+  const int pos_first = tq * kSplitRows, pos_last = min(pos_first + kSplitRows, nq) - 1;
+  const int n_full_tiles = qvis[pos_first] / kTileN, ntiles = cdiv(qvis[pos_last], kTileN);
+  const int pos_c = min(pos_first + ln, nq - 1);
+  const int qvisible = qvis[pos_c] - 4 * h;
+  const T* qhead = static_cast<const T*>(p.Q) + b * L.qs[0] + i * L.qs[1];
+#pragma unroll
+  for (int c = threadIdx.x; c < kSplitRows * CH; c += kSplitThreads) {
+    const int row = c / CH, chunk = c % CH;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(qhead + (long long)qlist[min(pos_first + row, nq - 1)] * L.qs[2] + chunk * 8);
+    *reinterpret_cast<u32x4*>(sQ + (row * CH + (chunk ^ (row % CH))) * 16) = v;
+  }
+  const int bhx = p.per_q_head ? bh : b * L.Hkv + g;
+  const unsigned char* kp = static_cast<const unsigned char*>(p.Kp) + (long long)bhx * p.npad * D * 2 + lane * 16;
+  const unsigned char* vp = static_cast<const unsigned char*>(p.Vp) + (long long)bhx * p.npad * D * 2 + (h * D + ln) * 16;
+  const int* tile_map = TILEMAP ? p.tile_map + (long long)bh * p.tile_stride : nullptr;
+  auto tile_bytes = [&](int t) {
+    const int src = TILEMAP ? __builtin_amdgcn_readfirstlane(tile_map[t]) : t;
+    return (long long)src * (kTileN * D * 2);
+  };
+  bf16x8 kf[2][KS];
+  auto load_k = [&](int t) {
+    const unsigned char* k = kp + tile_bytes(t);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[kb][ks] = *reinterpret_cast<const bf16x8*>(k + (kb * KS + ks) * 1024);
+  };
+  f32x16 o[NB];
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  if (wave < ntiles) load_k(wave);
+  __syncthreads();
+  for (int t = wave; t < ntiles; t += kSplitWaves) {
+    f16x8 vf[2][NB];
+    const unsigned char* v = vp + tile_bytes(t);
+    auto load_v = [&](int half) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int db = 0; db < NB; ++db) vf[u][db] = *reinterpret_cast<const f16x8*>(v + ((half * 2 + u) * 2 * D + db * 32) * 16);
+    };
+    load_v(0);
+    f32x16 s[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 qf = *reinterpret_cast<const bf16x8*>(sQ + (ln * CH + ((2 * ks + h) ^ (ln % CH))) * 16);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][ks], qf, s[kb], 0, 0, 0);
+    }
+    if (t + kSplitWaves < ntiles) load_k(t + kSplitWaves);
+    if (t >= n_full_tiles) {
+      const int rel = qvisible - t * kTileN;         // keys of this tile at positions >= rel are hidden (pad rows too)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb * 32 + 8 * (r >> 2) + (r & 3) >= rel) s[kb][r] = -INFINITY;
+    }
+    float m = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, s[kb][r]);
+    m = fmaxf(m_run, pair_max(m));
+    const float m_ref = m == -INFINITY ? 0.f : m, mc = m_ref * c2;
+    if (__any(m > m_run)) {
+      const float alpha = fast_exp2((m_run - m_ref) * c2);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < NB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      m_run = m;
+    }
+    union { f16x8 v[4]; f16x2 h2[16]; } pf;
+#pragma unroll
+    for (int r = 0; r < 32; r += 2) {
+      f32x2 pv;
+      pv[0] = fast_exp2(fmaf(s[r / 16][r % 16], c2, -mc));
+      pv[1] = fast_exp2(fmaf(s[r / 16][r % 16 + 1], c2, -mc));
+      const f16x2 pk = __builtin_convertvector(pv, f16x2);
+      pf.h2[r / 2] = pk;
+      l_run += (float)pk[0] + (float)pk[1];          // the weights as rounded: numerator and normaliser agree
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int db = 0; db < NB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[u][db], pf.v[half * 2 + u], o[db], 0, 0, 0);
+      if (half == 0) load_v(1);
+    }
+  }
+
+  // merge the wavefronts in their order
+  const float l_own = pair_sum(l_run);
+  if (h == 0) {
+    sM[wave][ln] = m_run;
+    sL[wave][ln] = l_own;
+  }
+  __syncthreads();
+  float top = sM[0][ln];
+#pragma unroll
+  for (int w = 1; w < kSplitWaves; ++w) top = fmaxf(top, sM[w][ln]);
+  const float ref = top == -INFINITY ? 0.f : top;
+  float total = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) total += sL[w][ln] * fast_exp2((sM[w][ln] - ref) * c2);
+  const float mine = total > 0.f ? fast_exp2((m_run - ref) * c2) / total : 0.f;
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 v = {o[db][q4 * 4] * mine, o[db][q4 * 4 + 1] * mine, o[db][q4 * 4 + 2] * mine, o[db][q4 * 4 + 3] * mine};
+      *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
+    }
+  if (threadIdx.x < kSplitRows && pos_first + (int)threadIdx.x < nq)
+    p.lse[(long long)bh * L.N + qlist[pos_first + threadIdx.x]] = total > 0.f ? (top * c2 + log2f(total)) * kLn2 : -INFINITY;
+  __syncthreads();
+  T* ohead = static_cast<T*>(p.O) + b * L.qs[0] + i * L.qs[1];
+#pragma unroll
+  for (int c = threadIdx.x; c < kSplitRows * CH; c += kSplitThreads) {
+    const int row = c / CH, d = c % CH * 8;
+    if (pos_first + row >= nq) continue;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+      x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
+      y += *reinterpret_cast<const f32x4*>(&sO[w][row][d + 4]);
+    }
+    const u32x4 out = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    *reinterpret_cast<u32x4*>(ohead + (long long)qlist[pos_first + row] * L.qs[2] + d) = out;
+  }
+}
+
+// Which of the two bf16 kernels: the bytes an item streams alone make the split kernel the slower one once the work per
+// CU outweighs the length of a chain.  Whole attention call in us, (heads, d) N: split / the other, a third of the
+// queries and half of the keys kept: (28, 128) 1072: 30 / 55, 3101: 60 / 83, 4096: 85 / 100, 6000: 134 / 129,
+// (28, 64) 4096: 53 / 78, 8192: 122 / 119, (8, 128) 6000: 85 / 110, 8192: 139 / 137, (8, 64) 8192: 76 / 104,
+// 12000: 140 / 140; not causal (28, 128) 3101: 81 / 85.  The line lies below all crossings; it looks at the shape only, so
+// that the gathered and the in-place lists of the same layer take the same kernel.
+bool split_pays(const Layer& L) {
+  return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0) <= 6.5e10;
+}
+
 // Rows of a head's packed K/V buffer: whole tiles, and never a multiple of 4096 rows -- with a power-of-two
 // stride between the heads, workgroups that stream different heads at the same tile index (all of them start
 // at tile 0 together) hit the same cache sets and memory channels.
@@ -818,6 +1003,15 @@ FwdWs carve_fwd(Arena& a, const Layer& L, int dtype, int heads, int npad, bool s
   w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
   w.qvis = (sparse && dtype == OMNI_BF16) ? a.take<int>((size_t)L.B * L.Hq * L.N) : nullptr;
   return w;
+}
+
+template <int D, bool TILEMAP>
+int launch_split(const FwdParams& p, hipStream_t st) {
+  ProfScope prof__(kProfAttnFwd, st);
+  hipLaunchKernelGGL((attn_fwd_split_kernel<D, TILEMAP>), dim3(p.L.B * p.L.Hq, cdiv(p.L.N, kSplitRows)), dim3(kSplitThreads),
+                     0, st, p);
+  OMNI_LAUNCH_CHECK();
+  return OMNI_OK;
 }
 
 // What the forward needs to know about every token: visible counts, cleared rows, the items of the work list.
@@ -849,12 +1043,13 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int heads = sparse ? L.Hq : L.Hkv;
   const int npad = fwd_npad(sparse ? b_cap : L.N);
   FwdWs w = carve_fwd(a, L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, heads, npad, sparse);
+  const bool split = sparse && sizeof(T) == 2 && split_pays(L);
   {
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
     // bf16: K natural + V k-packed and converted to f16; fp32: both natural
     int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp,
                          dt == OMNI_BF16 ? nullptr : w.Vp, nullptr, dt == OMNI_BF16 ? w.Vp : nullptr, w.kidx, st,
-                         sparse ? sel : nullptr);
+                         sparse ? sel : nullptr, split);
     if (rc != OMNI_OK) return rc;
   }
   FwdParams p;
@@ -881,10 +1076,13 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
   int rc;
   if (sparse) {
-    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m, w.sched, st);
+    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m,
+                        split ? nullptr : w.sched, st);
     if (rc != OMNI_OK) return rc;
-    // Per-head gathered K/V: one queue per XCD where the launch is long enough, so that the workgroups on a head share
-    // its tiles in that XCD's L2 (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
+    if constexpr (kFast) {
+      if (split) return launch_split<D, false>(p, st);
+    }
+    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2 (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
     // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
     // costs (25.7 -> 25.9 ms dense).
     rc = run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1);
@@ -949,8 +1147,9 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   BlockFwdWs w = carve_block_fwd(a, L, cap_keys);
   const int npad = fwd_npad(L.N);
   // K and V of every KV head once, in the kernel's tile layouts, in token order: shared by the heads of a group
+  const bool split = split_pays(L);
   int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
-                       w.f.kidx, st);
+                       w.f.kidx, st, nullptr, split);
   if (rc != OMNI_OK) return rc;
   // token lists of the selected blocks (for the causal bounds) and the tile map
   rc = run_expand_blocks(L, blk_idx, blk_budget, blk_cap, block, w.klist, w.vbudget, cap_keys, st);
@@ -959,7 +1158,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
                      L.Hq, blk_cap, tpb, npad / kTileN - 1, w.tile_map);
   OMNI_LAUNCH_CHECK();
   rc = run_fwd_bounds(L, q_idx, q_cnt, w.klist, cap_keys, w.vbudget, cap_keys, w.f.qvis, O, sizeof(T), lse, kFastTileM,
-                      w.f.sched, st);
+                      split ? nullptr : w.f.sched, st);
   if (rc != OMNI_OK) return rc;
   FwdParams p;
   p.Q = Q;
@@ -981,6 +1180,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   p.tile_map = w.tile_map;
   p.tile_stride = blk_cap * tpb;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, kFastTileM);
+  if (split) return launch_split<D, true>(p, st);
   rc = run_order(L, q_cnt, kFastTileM, w.f.sched, st);
   if (rc != OMNI_OK) return rc;
   {

@@ -4,10 +4,8 @@
 // blocks, and the selected blocks are handed to the attention kernels as token lists.
 //
 //  * pool_rows_kernel: block means of the rows of one head, fp32 (HBM-bound, one pass over Q and K).
-//  * block_scores_kernel: one workgroup per query head.  Thread m owns key block m: for every query block
-//    j it computes the pooled logit, the row's softmax over the visible key blocks (a key block of c
-//    tokens weighs c), and adds w_j P_j[m] to its own register -- column sums without atomics, in a fixed
-//    order.  n_blocks^2 * d MACs per head: a few tens of microseconds at 256 blocks.
+//  * block_rows_kernel, block_cols_kernel: the pooled map twice, by rows for every row's softmax statistics, then by
+//    columns for a[m] = sum_j w_j P_j[m] (a key block of c tokens weighs c in a row), in a fixed order without atomics.
 //  * expand_blocks_kernel: ascending block ids -> ascending token ids (tokens past the end of the sequence
 //    in a partial last block become pad entries, which the packers turn into zero rows nobody sees).
 #include "common.h"
@@ -54,80 +52,128 @@ __global__ __launch_bounds__(kThreads) void pool_rows_kernel(const T* __restrict
   }
 }
 
-// grid: B * Hq, kThreads threads; thread t owns the key blocks t, t + kThreads, ... (kMaxOwn of them at most)
-constexpr int kMaxOwn = 8;
+// The pooled map has n_blocks^2 logits of D products per head: little work, so what counts is how many workgroups share
+// it and how long a thread's chain of dependent multiply-adds is.  Every thread keeps one key block and forms the logits
+// of several query blocks side by side; the map is formed twice, which is cheaper than keeping it (4 n_blocks^2 bytes a
+// head).  One workgroup per head walking its rows one after the other took 251 us at 64 blocks, 28 heads, d = 128; the two
+// kernels take 17.
+constexpr int kRowsPerWg = 8;                // query blocks of a row workgroup
+constexpr int kColsPerWg = 32;               // key blocks of a column workgroup ...
+constexpr int kColSlices = kThreads / kColsPerWg;   // ... whose rows are dealt to this many slices
+constexpr int kColBatch = 4;                 // rows a thread forms side by side
+constexpr int kMaxBlocks = 2048;
 
+// dot[r] = q row r . k, in the order of d, for R rows of sq (LDS, D floats each)
+template <int D, int R>
+__device__ __forceinline__ void dots(const float* sq, const float* __restrict__ k, float (&dot)[R]) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) dot[r] = 0.f;
+#pragma unroll 4
+  for (int d = 0; d < D; d += 4) {
+    const f32x4 kv = *reinterpret_cast<const f32x4*>(k + d);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const f32x4 qv = *reinterpret_cast<const f32x4*>(sq + r * D + d);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dot[r] = fmaf(qv[e], kv[e], dot[r]);
+    }
+  }
+}
+
+// tokens of block m
+__device__ __forceinline__ float block_tokens(int m, int block, int N) { return (float)(min(N, (m + 1) * block) - m * block); }
+
+// grid: (cdiv(n_blocks, kRowsPerWg), B * Hq).  Of every pooled row: the largest logit and (queries of the block) /
+// (sum of the key blocks' weights against it).
 template <int D>
-__global__ __launch_bounds__(kThreads) void block_scores_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
-                                                               int Hq, int Hkv, int N, int block, int nblk, int causal,
-                                                               float scale, float* __restrict__ out) {
-  __shared__ float sq[D];
-  __shared__ float sred[kThreads / 64];
-  __shared__ float sbc;
-  const int bh = blockIdx.x, b = bh / Hq, i = bh % Hq, g = i / (Hq / Hkv);
-  const float* qh = qbar + (long long)bh * nblk * D;
+__global__ __launch_bounds__(kThreads) void block_rows_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
+                                                             int Hq, int Hkv, int N, int block, int nblk, int causal,
+                                                             float scale, float2* __restrict__ stats) {
+  __shared__ __attribute__((aligned(16))) float sq[kRowsPerWg * D];
+  __shared__ float sm[kRowsPerWg][kThreads / 64], ss[kRowsPerWg][kThreads / 64];
+  const int bh = blockIdx.y, b = bh / Hq, i = bh % Hq, g = i / (Hq / Hkv), j0 = blockIdx.x * kRowsPerWg;
+  const float* qh = qbar + ((long long)bh * nblk + j0) * D;
   const float* kh = kbar + (long long)(b * Hkv + g) * nblk * D;
   const float c2 = scale * kLog2e;
-  float acc[kMaxOwn];
+  const int rows = min(kRowsPerWg, nblk - j0);
+  for (int t = threadIdx.x; t < kRowsPerWg * D; t += kThreads) sq[t] = t < rows * D ? qh[t] : 0.f;
+  __syncthreads();
+  float mx[kRowsPerWg], sum[kRowsPerWg];
 #pragma unroll
-  for (int o = 0; o < kMaxOwn; ++o) acc[o] = 0.f;
-  auto block_reduce = [&](float v, bool is_max) {
-    v = is_max ? wave_max(v) : wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sred[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float r = sred[0];
-      for (int w = 1; w < kThreads / 64; ++w) r = is_max ? fmaxf(r, sred[w]) : r + sred[w];
-      sbc = r;
+  for (int r = 0; r < kRowsPerWg; ++r) mx[r] = -INFINITY, sum[r] = 0.f;
+  const int end = causal ? j0 + rows : nblk;       // no row of this workgroup sees a key block past this
+  for (int m = threadIdx.x; m < end; m += kThreads) {
+    float dot[kRowsPerWg];
+    dots<D, kRowsPerWg>(sq, kh + (long long)m * D, dot);
+    const float cm = block_tokens(m, block, N);
+#pragma unroll
+    for (int r = 0; r < kRowsPerWg; ++r) {
+      if (causal && m > j0 + r) continue;
+      const float l = dot[r] * c2, top = fmaxf(mx[r], l);
+      sum[r] = sum[r] * exp2f(mx[r] - top) + cm * exp2f(l - top);
+      mx[r] = top;
     }
-    __syncthreads();
-    return sbc;
-  };
-  for (int j = 0; j < nblk; ++j) {
-    __syncthreads();
-    for (int d = threadIdx.x; d < D; d += kThreads) sq[d] = qh[(long long)j * D + d];
-    __syncthreads();
-    const int last = causal ? j : nblk - 1;                  // visible key blocks: 0 .. last
-    float l[kMaxOwn], mx = -INFINITY;
-#pragma unroll
-    for (int o = 0; o < kMaxOwn; ++o) {
-      const int m = threadIdx.x + o * kThreads;
-      l[o] = -INFINITY;
-      if (m <= last) {
-        const float* kr = kh + (long long)m * D;
-        float dot = 0.f;
-#pragma unroll 8
-        for (int d = 0; d < D; d += 4) {
-          const f32x4 kv = *reinterpret_cast<const f32x4*>(kr + d);
-          dot = fmaf(sq[d], kv[0], dot);
-          dot = fmaf(sq[d + 1], kv[1], dot);
-          dot = fmaf(sq[d + 2], kv[2], dot);
-          dot = fmaf(sq[d + 3], kv[3], dot);
-        }
-        l[o] = dot * c2;
-        mx = fmaxf(mx, l[o]);
-      }
-    }
-    mx = block_reduce(mx, true);
-    float pw[kMaxOwn], sum = 0.f;
-#pragma unroll
-    for (int o = 0; o < kMaxOwn; ++o) {
-      const int m = threadIdx.x + o * kThreads;
-      const float cm = (float)(min(N, (m + 1) * block) - m * block);      // tokens in key block m
-      pw[o] = m <= last ? cm * exp2f(l[o] - mx) : 0.f;
-      sum += pw[o];
-    }
-    sum = block_reduce(sum, false);
-    const float wj = (float)(min(N, (j + 1) * block) - j * block) / sum;   // queries in block j over the row's normaliser
-#pragma unroll
-    for (int o = 0; o < kMaxOwn; ++o) acc[o] = fmaf(wj, pw[o], acc[o]);
   }
-  const float norm = (float)nblk / (float)N;                              // scores sum to the number of blocks
+  const int wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int o = 0; o < kMaxOwn; ++o) {
-    const int m = threadIdx.x + o * kThreads;
-    if (m < nblk) out[(long long)bh * nblk + m] = acc[o] * norm;
+  for (int r = 0; r < kRowsPerWg; ++r) {
+    const float top = wave_max(mx[r]);
+    const float part = wave_sum(mx[r] == -INFINITY ? 0.f : sum[r] * exp2f(mx[r] - top));
+    if (lane_id() == 0) sm[r][wave] = top, ss[r][wave] = part;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < rows) {
+    const int r = threadIdx.x;
+    float top = sm[r][0], part = 0.f;
+#pragma unroll
+    for (int w = 1; w < kThreads / 64; ++w) top = fmaxf(top, sm[r][w]);
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) part += sm[r][w] == -INFINITY ? 0.f : ss[r][w] * exp2f(sm[r][w] - top);
+    stats[(long long)bh * nblk + j0 + r] = make_float2(top, block_tokens(j0 + r, block, N) / part);
+  }
+}
+
+// grid: (cdiv(n_blocks, kColsPerWg), B * Hq).  Column sums; slice s of a column takes the rows of its own batches, the
+// slices are added in order.
+template <int D>
+__global__ __launch_bounds__(kThreads) void block_cols_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
+                                                             int Hq, int Hkv, int N, int block, int nblk, int causal,
+                                                             float scale, const float2* __restrict__ stats,
+                                                             float* __restrict__ out) {
+  constexpr int kTrip = kColSlices * kColBatch;    // rows staged per trip
+  __shared__ __attribute__((aligned(16))) float sq[kTrip * D];
+  __shared__ float2 sst[kTrip];
+  __shared__ float sacc[kColSlices][kColsPerWg];
+  const int bh = blockIdx.y, b = bh / Hq, i = bh % Hq, g = i / (Hq / Hkv);
+  const int col = threadIdx.x % kColsPerWg, slice = threadIdx.x / kColsPerWg, m = blockIdx.x * kColsPerWg + col;
+  const float* qh = qbar + (long long)bh * nblk * D;
+  const float* kr = kbar + ((long long)(b * Hkv + g) * nblk + min(m, nblk - 1)) * D;
+  const float c2 = scale * kLog2e, cm = m < nblk ? block_tokens(m, block, N) : 0.f;
+  float acc = 0.f;
+  const int begin = causal ? (int)blockIdx.x * kColsPerWg / kTrip * kTrip : 0;    // earlier rows see none of these columns
+  for (int j0 = begin; j0 < nblk; j0 += kTrip) {
+    __syncthreads();
+    const int rows = min(kTrip, nblk - j0);
+    for (int t = threadIdx.x; t < kTrip * D; t += kThreads) sq[t] = t < rows * D ? qh[(long long)j0 * D + t] : 0.f;
+    if (threadIdx.x < kTrip)
+      sst[threadIdx.x] = (int)threadIdx.x < rows ? stats[(long long)bh * nblk + j0 + threadIdx.x] : make_float2(0.f, 0.f);
+    __syncthreads();
+    float dot[kColBatch];
+    dots<D, kColBatch>(sq + slice * kColBatch * D, kr, dot);
+#pragma unroll
+    for (int r = 0; r < kColBatch; ++r) {
+      const int j = j0 + slice * kColBatch + r;
+      const float2 st = sst[slice * kColBatch + r];
+      if (j < nblk && (!causal || m <= j)) acc = fmaf(st.y, cm * exp2f(dot[r] * c2 - st.x), acc);
+    }
+  }
+  sacc[slice][col] = acc;
+  __syncthreads();
+  if (threadIdx.x < kColsPerWg && m < nblk) {
+    float a = 0.f;
+#pragma unroll
+    for (int s = 0; s < kColSlices; ++s) a += sacc[s][col];
+    out[(long long)bh * nblk + m] = a * ((float)nblk / (float)N);        // scores sum to the number of blocks
   }
 }
 
@@ -147,12 +193,14 @@ __global__ __launch_bounds__(256) void expand_blocks_kernel(const int* __restric
 struct BlockWs {
   float* qbar;
   float* kbar;
+  float2* stats;
 };
 
 BlockWs carve_block(Arena& a, const Layer& L, int nblk) {
   BlockWs w;
   w.qbar = a.take<float>((size_t)L.B * L.Hq * nblk * L.D);
   w.kbar = a.take<float>((size_t)L.B * L.Hkv * nblk * L.D);
+  w.stats = a.take<float2>((size_t)L.B * L.Hq * nblk);
   return w;
 }
 
@@ -167,15 +215,18 @@ int launch_block_scores(const Layer& L, const void* Q, const void* K, int block,
   hipLaunchKernelGGL((pool_rows_kernel<T, D>), dim3(nblk, L.B * L.Hkv), dim3(kThreads), 0, st, static_cast<const T*>(K),
                      L.ks[0], L.ks[1], L.ks[2], L.Hkv, L.N, block, nblk, w.kbar);
   OMNI_LAUNCH_CHECK();
-  hipLaunchKernelGGL((block_scores_kernel<D>), dim3(L.B * L.Hq), dim3(kThreads), 0, st, w.qbar, w.kbar, L.Hq, L.Hkv, L.N,
-                     block, nblk, L.causal, L.scale, out);
+  hipLaunchKernelGGL((block_rows_kernel<D>), dim3(cdiv(nblk, kRowsPerWg), L.B * L.Hq), dim3(kThreads), 0, st, w.qbar, w.kbar,
+                     L.Hq, L.Hkv, L.N, block, nblk, L.causal, L.scale, w.stats);
+  OMNI_LAUNCH_CHECK();
+  hipLaunchKernelGGL((block_cols_kernel<D>), dim3(cdiv(nblk, kColsPerWg), L.B * L.Hq), dim3(kThreads), 0, st, w.qbar, w.kbar,
+                     L.Hq, L.Hkv, L.N, block, nblk, L.causal, L.scale, w.stats, out);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
 
 }  // namespace
 
-int block_scores_max_blocks() { return kThreads * kMaxOwn; }
+int block_scores_max_blocks() { return kMaxBlocks; }
 
 size_t block_scores_ws(const Layer& L, int block) {
   Arena a(nullptr);

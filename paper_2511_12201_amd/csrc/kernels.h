@@ -55,10 +55,12 @@ int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, f
               hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
 
 // pack.hip (outputs that are nullptr are skipped; Kt / Vt / Qt / dOt exist for bf16 only; Vt holds f16 values)
+// k_frag (bf16): Kn in the order of a 32x32x16 MFMA's A operand instead of row by row, [32-row block][16-wide k step][lane]
+// of 16 bytes (lane = 32 * half + row)
 // sel not null (per_q_head only, src_idx ignored): the kernel forms the lists from *sel and writes them to sel->out
 int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
                 int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
-                void* Vt, int* kidx, hipStream_t st, const SelectSource* sel = nullptr);
+                void* Vt, int* kidx, hipStream_t st, const SelectSource* sel = nullptr, bool k_frag = false);
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
                const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
                float* deltac, hipStream_t st);

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
                                                           int idx_stride, const int* __restrict__ budget, int b_cap,
                                                           int npad, int pad_to, T* __restrict__ Kn, T* __restrict__ Vn,
                                                           T* __restrict__ Kt, T* __restrict__ Vt,
-                                                          int* __restrict__ kidx, SelectSource sel) {
+                                                          int* __restrict__ kidx, SelectSource sel, int k_frag) {
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int E = Elem<T>::kPer16B;
   constexpr int CPR = D / E;
@@ -168,7 +168,16 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
   const T* vbase = V + b * L.ks[0] + g * L.ks[1];
   const long long tile_off = ((long long)bhx * npad + tile * kTileN) * D;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  if (Kn || Vn) {
+  if (kBf16 && k_frag) {
+    // consecutive threads take consecutive rows of one 16-byte column: the writes are contiguous, the reads meet in L1
+    for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
+      const int r32 = c & 31, chunk = c / 32 % CPR, row = c / (32 * CPR) * 32 + r32;
+      const int id = sIdx[row];
+      u32x4 v = zero;
+      if (id != kPadKeyIndex) v = *reinterpret_cast<const u32x4*>(kbase + (long long)id * L.ks[2] + chunk * E);
+      *reinterpret_cast<u32x4*>(Kn + tile_off + c * E) = v;
+    }
+  } else if (Kn || Vn) {
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
       const int row = c / CPR, col = (c % CPR) * E;
       const int id = sIdx[row];
@@ -293,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ 
 template <typename T, int D>
 int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head, const int* src_idx, int idx_stride,
                    const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt, void* Vt,
-                   int* kidx, hipStream_t st, const SelectSource* sel) {
+                   int* kidx, hipStream_t st, const SelectSource* sel, int k_frag) {
   const int heads = per_q_head ? L.Hq : L.Hkv;
   ProfScope prof__(kProfPack, st);
   if (sel) {
@@ -301,12 +310,12 @@ int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head,
     hipLaunchKernelGGL((pack_kv_kernel<T, D, true>), dim3(npad / kTileN, L.B * heads), dim3(kThreads), 0, st,
                        static_cast<const T*>(K), static_cast<const T*>(V), L, per_q_head, src_idx, idx_stride, budget,
                        b_cap, npad, pad_to, static_cast<T*>(Kn), static_cast<T*>(Vn), static_cast<T*>(Kt),
-                       static_cast<T*>(Vt), kidx, *sel);
+                       static_cast<T*>(Vt), kidx, *sel, k_frag);
   } else {
     hipLaunchKernelGGL((pack_kv_kernel<T, D, false>), dim3(npad / kTileN, L.B * heads), dim3(kThreads), 0, st,
                        static_cast<const T*>(K), static_cast<const T*>(V), L, per_q_head, src_idx, idx_stride, budget,
                        b_cap, npad, pad_to, static_cast<T*>(Kn), static_cast<T*>(Vn), static_cast<T*>(Kt),
-                       static_cast<T*>(Vt), kidx, SelectSource{});
+                       static_cast<T*>(Vt), kidx, SelectSource{}, k_frag);
   }
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
@@ -328,19 +337,19 @@ int launch_pack_q(const Layer& L, const void* Q, const void* O, const void* dO, 
 
 int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
                 int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
-                void* Vt, int* kidx, hipStream_t st, const SelectSource* sel) {
+                void* Vt, int* kidx, hipStream_t st, const SelectSource* sel, bool k_frag) {
   if (dtype == OMNI_BF16) {
     if (L.D == 128)
       return launch_pack_kv<u16, 128>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn, Kt,
-                                      Vt, kidx, st, sel);
+                                      Vt, kidx, st, sel, k_frag);
     return launch_pack_kv<u16, 64>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn, Kt, Vt,
-                                   kidx, st, sel);
+                                   kidx, st, sel, k_frag);
   }
   if (L.D == 128)
     return launch_pack_kv<float, 128>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                      nullptr, nullptr, kidx, st, sel);
+                                      nullptr, nullptr, kidx, st, sel, k_frag);
   return launch_pack_kv<float, 64>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                   nullptr, nullptr, kidx, st, sel);
+                                   nullptr, nullptr, kidx, st, sel, k_frag);
 }
 
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,

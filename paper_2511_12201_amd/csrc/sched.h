@@ -12,8 +12,8 @@
 //
 // The list can be cut into kSchedQueues queues, one per XCD (workgroups are dealt to the XCDs round-robin, so
 // workgroup i sits on XCD i % 8): whole heads are assigned to queues, largest first onto the least loaded
-// queue, and inside a queue the heads follow one another, each longest item first (one list after all if some
-// head outweighs a queue's fair share, see sched_queues_pay).  The 32 workgroups of an
+// queue, and inside a queue the heads follow one another, each longest item first, or all its items longest first
+// (sched_long_enough); one list after all if some head outweighs a queue's fair share (sched_queues_pay).  The 32 workgroups of an
 // XCD then stream the K/V tiles of one head a few tiles apart and find them in the XCD's own L2 instead of
 // each fetching its own copy; a workgroup whose queue is drained takes from the queue with the most items left.
 // On the 64k forward this cuts the traffic from beyond L2 to a third and leaves the kernel time where it was: the
@@ -132,10 +132,12 @@ __host__ __device__ inline bool sched_queues_pay(long long total_cost, long long
   return 2 * largest_head * queues <= 3 * total_cost;
 }
 
-// A queue hands out head after head, so the long items of its last head start late: queues only pay where a workgroup's
-// share is several times the longest item.  Shares of 2.3 longest items (28 heads at 32k, a third of the queries kept):
-// 1569 us with queues, 1523 without; of 4.6 (64k): 5495 with, 5655 without; below that the list alone is up to 10 %
-// faster.  `workgroups`: one per CU.
+// Inside a queue head follows head where a workgroup's share is several times the longest item; elsewhere the long items
+// of the last head would start late, and the queue hands out its items longest first, whatever their head (the heads of a
+// queue then advance side by side, a few workgroups each).  Attention call, 28 heads, a third of the queries kept: head
+// after head against one list 5.50 / 5.65 ms at 64k (a share is 4.6 longest items) but 1.57 / 1.52 at 32k (2.3); longest
+// first in the queue against one list 1.435 / 1.459 ms at 32k, 821 / 815 us at 24k, 437 / 445 at 16k, 167 / 171 at 8k.
+// `workgroups`: one per CU.
 __host__ __device__ inline bool sched_long_enough(long long total_cost, long long largest_item, int workgroups) {
   return 10 * total_cost >= 34 * largest_item * workgroups;
 }

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __rest
 #pragma unroll
   for (int w = 0; w < kThreads / 64; ++w) n += s_wave[w];
   if (blockIdx.x > 0 && (int)blockIdx.x * kRankItems >= n) return;
-  bool queued = queues > 1 && BH <= kSchedMaxQueuedHeads;
+  bool queued = queues > 1 && BH <= kSchedMaxQueuedHeads, by_head = true;
   if (queued) {
     // head costs; whether queues pay
     for (int bh = threadIdx.x; bh < BH; bh += kThreads) {
@@ -195,7 +195,8 @@ __global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __rest
       head = max(head, s_head[w]);
       tot += s_tot[w];
     }
-    queued = sched_queues_pay(tot, head, queues) && sched_long_enough(tot, big, workgroups);
+    queued = sched_queues_pay(tot, head, queues);
+    by_head = sched_long_enough(tot, big, workgroups);
     if (queued) {
       const int shift = sched_cost_shift(tot);
       for (int bh = threadIdx.x; bh < BH; bh += kThreads) {     // rank of a head: cost descending, index ascending
@@ -241,7 +242,8 @@ __global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __rest
     if (q == 0) sched[kSchedTotal] = n;
   }
   auto key_of = [&](int2 it, int id) {
-    return sched_key(it.y, id, queued ? (unsigned)sh.place[(unsigned)it.x >> 16] : 0u);
+    const unsigned place = queued ? (unsigned)sh.place[(unsigned)it.x >> 16] : 0u;
+    return sched_key(it.y, id, by_head ? place : place & 0xffff0000u);
   };
   const int id = blockIdx.x * kRankItems + threadIdx.x / kRankLanes, sub = threadIdx.x % kRankLanes;
   const int2 own = id < n ? items[id] : make_int2(0, 0);

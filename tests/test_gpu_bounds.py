@@ -58,3 +58,35 @@ def test_rows_slots_and_items_at_window_edges(N, dtype, d, causal):
     rss = oc.sparse_attn_bwd_term_rss(Q, K, V, dO, q_lists, kv_lists, causal, scale, O=stored)
     for x, w, r in zip((dQ, dK, dV), want, rss):
         assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, dtype, r))
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
+    """Shapes just below and just above the line between the two bf16 forward kernels (batch * heads * N^2 * d, twice
+    that without the mask, against 6.5e10), on the same random lists; a whole number of 32-row items and one row more."""
+    H, Hkv, B = 16, 1, 8
+    line = int((6.5e10 / (B * H * d * (1 if causal else 2))) ** 0.5)
+    for N in (line // 32 * 32, line // 32 * 32 + 33):
+        rng = np.random.default_rng(N)
+        g = torch.Generator(device="cuda").manual_seed(N)
+        rand = lambda h: torch.randn(B, h, N, d, generator=g, device="cuda").bfloat16()  # noqa: E731
+        Q, K, V = rand(H), rand(Hkv), rand(Hkv)
+        desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
+        sizes = [(N, 65), (N // 5, N // 3), (33, N), (31, 1)]
+        q_lists = [[np.sort(rng.choice(N, sizes[h % 4][0], replace=False)) for h in range(H)] for _ in range(B)]
+        k_lists = [[np.sort(rng.choice(N, sizes[h % 4][1], replace=False)) for h in range(H)] for _ in range(B)]
+        q_idx, q_cnt = lists_to_padded(q_lists, H, N)
+        kv_idx, budget = lists_to_padded(k_lists, H, N)
+        O, lse = ob.omni_sparse_attn_fwd_per_head(desc, Q, K, V, q_idx, q_cnt, kv_idx, budget, N)
+        for b, h in ((0, 0), (B - 1, 1), (3, 2), (5, 3)):
+            q, k = torch.from_numpy(q_lists[b][h]).cuda(), torch.from_numpy(k_lists[b][h]).cuda()
+            z = Q[b, h, q].double() @ K[b, 0, k].double().T * d ** -0.5
+            if causal:
+                z = z.masked_fill(k[None] > q[:, None], -float("inf"))
+            want = torch.nan_to_num(torch.softmax(z, -1)) @ V[b, 0, k].double()
+            assert float((O[b, h, q].double() - want).abs().max()) <= 2e-2
+            m = torch.logsumexp(z, -1)
+            fin = torch.isfinite(m)
+            assert torch.equal(torch.isfinite(lse[b, h, q]), fin)
+            assert float((lse[b, h, q][fin] - m[fin]).abs().max()) <= 2e-3
