@@ -18,8 +18,7 @@
 //    shared by up to four workgroups, each with a partial plane of its own.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
-// fp32 inputs (the 1e-4 parity cases) keep the older register-staged pair attn_bwd_dkdv_kernel (128 keys per
-// workgroup, dK' and dV' together) / attn_bwd_dq_kernel on the fp32 32x32x2 MFMA with natural layouts.
+// fp32 inputs: attn_bwd_key_f32_kernel (dK' and dV' of 32 keys together) and attn_bwd_dq_f32_kernel on the fp32 32x32x2 MFMA.
 #include <algorithm>
 
 #include <type_traits>
@@ -34,8 +33,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kBwdKeys = 128;     // keys per dkdv workgroup
-constexpr int kBwdQ = 64;         // queries per dkdv iteration
 
 struct BwdParams {
   const void* Q;
@@ -47,11 +44,11 @@ struct BwdParams {
   int b_cap, npad, nqpad;
   const void* Kn;       // packed natural K, V
   const void* Vn;
-  const void* Kt;       // k-packed K (bf16 only)
+  const void* Kt;       // k-packed K
   const int* kidx;
-  const void* Qt;       // k-packed kept Q, dO (bf16 only)
+  const void* Qt;       // k-packed kept Q, dO
   const void* dOt;
-  const void* Qn;       // kept Q, dO rows in kept order, contiguous (bf16 only)
+  const void* Qn;       // kept Q, dO rows in kept order, contiguous (fp32: in fragment order, as Kn and Vn)
   const void* dOn;
   const float* lse2c;   // per kept position: lse * log2e (+inf: contributes nothing)
   const float* deltac;
@@ -60,7 +57,7 @@ struct BwdParams {
   void* dQ;
   int* sched;           // work list of the dQ kernel (sched.h)
   size_t order_off;     // where its hand-out order starts
-  const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position (bf16 fast path)
+  const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position
   const int* kfirst;    // [B*Hq, npad] first kept-query position that sees a packed key
   int head_group;       // heads per dispatch group of the key kernels
   int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernels)
@@ -74,25 +71,6 @@ struct BwdParams {
   int npad_kv;          // rows per (head) buffer of Kn / Vn / Kt: npad for the gathered copies
 };
 
-// first position in ascending a[0,n) with a[pos] >= v
-__device__ __forceinline__ int lower_pos(const int* __restrict__ a, int n, int v) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < v) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-// number of entries <= v
-__device__ __forceinline__ int upper_cnt(const int* __restrict__ a, int n, int v) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] <= v) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int r0) {
   union { bf16x8 v; unsigned u[4]; } o;
 #pragma unroll
@@ -100,483 +78,199 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int r0) {
   return o.v;
 }
 
-// ------------------------------------------------------------------ dK', dV'
+constexpr int kKeyWaves = 8;
+constexpr int kKeyThreads = kKeyWaves * 64;
+constexpr int kKeyTile = kKeyWaves * 32;     // packed keys per workgroup
+constexpr int kKeyQ = 64;                    // queries per streamed tile
+// A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
+// against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
+// query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
+constexpr int kKeySplitLenF32 = 4;           // fp32: a workgroup owns 32 keys and needs company sooner
+constexpr int kKeySplitLen = 128;            // query tiles per split, at least (64..128 measure alike, 32 and 256 worse)
+constexpr int kKeyMaxSplits = 4;             // at most 8: a work item carries the split in 3 bits
+__host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
+  const int s = n_qtiles / split_len;
+  return s < 1 ? 1 : (s > max_splits ? max_splits : s);
+}
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(BwdParams p) {
-  constexpr bool kBf16 = sizeof(T) == 2;
-  constexpr int LD = D + 8;                               // row pitch of natural tiles (elements)
-  constexpr int NBUF = kBf16 ? 2 : 1;
-  constexpr int kNatBytes = kBwdQ * LD * (int)sizeof(T);
-  constexpr int kPackBytes = kBf16 ? kBwdQ * D * 2 : 16;
-  __shared__ __attribute__((aligned(16))) unsigned char sQn_raw[NBUF * kNatBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sGn_raw[NBUF * kNatBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sQt_raw[NBUF * kPackBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sGt_raw[NBUF * kPackBytes];
-  __shared__ __attribute__((aligned(16))) float sLse[NBUF][kBwdQ];
-  __shared__ __attribute__((aligned(16))) float sDel[NBUF][kBwdQ];
-  __shared__ __attribute__((aligned(16))) int sQi[NBUF][kBwdQ];
-  __shared__ int sBound[2];
+// ------------------------------------------------------------------ fp32
+//
+// Both kernels divide the work as the fp32 forward does: a workgroup owns 32 rows (keys, or kept queries), its
+// wavefronts share the 32-row blocks of the other side, every fourth or eighth block each, and add their partial gradients at the
+// end in wavefront order.  Operands come straight from memory in the order of the matrix instructions (pack.hip).  Bound
+// by the fp32 matrix cores (64 cycles per 32x32x2 step); four times the workgroups and a quarter of the chain of the
+// kernels with 128 rows per workgroup and tiles staged without overlap: 161 + 71 us -> 19 + 21 us at 1k tokens, 2 heads,
+// d = 64 (of the 19 us, 39 without the splits of the queries).
+// Wavefronts per workgroup: as many as its registers allow (d = 64 fits two per SIMD: 36 workgroups of
+// four took 44 us in the key kernel where eight took 39).
+template <int D>
+constexpr int kF32Waves = D == 64 ? 8 : 4;
+template <int D>
+constexpr int kF32Threads = kF32Waves<D> * 64;
 
-  const Layer& L = p.L;
-  const int ktile = blockIdx.x, bh = blockIdx.y;
-  const int b = bh / L.Hq, i = bh % L.Hq;
-  const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
-  if (ktile * kBwdKeys >= nkeys) return;
-  const int nq = p.q_cnt[bh];
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int ln = lane & 31, h = lane >> 5;
-  const int* kidx = p.kidx + (long long)bh * p.npad;
-  const int* qlist = p.q_idx + (long long)bh * L.N;
-  const int slot0 = ktile * kBwdKeys;
-  const int slot = slot0 + wave * 32 + ln;                  // this lane's key slot (< npad by construction)
-  const int my_kidx = kidx[slot];
-  const float c2 = L.scale * kLog2e;
-
-  // query range that can see this key tile, and the part of it that sees every key of the tile
-  if (threadIdx.x == 0 || threadIdx.x == 64) {
-    const int which = threadIdx.x ? 1 : 0;
-    const int last_slot = min(slot0 + kBwdKeys, nkeys) - 1;
-    int v;
-    if (!L.causal) v = 0;
-    else v = lower_pos(qlist, nq, which ? kidx[last_slot] : kidx[slot0]);
-    sBound[which] = v;
-  }
+// out[row][d] = scale * sum over the wavefronts of acc (a 32 x D tile held as accumulators: column = row, registers = d)
+template <int D, typename Store>
+__device__ __forceinline__ void merge_waves(float (*sO)[32][D + 4], const f32x16 (&acc)[D / 32], float scale, Store store) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6, ln = lane & 31, h = lane >> 5;
   __syncthreads();
-  const bool has_pad = slot0 + kBwdKeys > nkeys;
-  const int q_begin = sBound[0] / kBwdQ;                    // first query tile with an admissible pair
-  const int q_full_pos = has_pad ? 0x7fffffff : sBound[1];  // tiles starting at or after this position need no mask
-  const int n_qtiles = cdiv(nq, kBwdQ);
-
-  // resident K, V fragments (B operands: lane = key column)
-  const T* krow = static_cast<const T*>(p.Kn) + ((long long)bh * p.npad + slot) * D;
-  const T* vrow = static_cast<const T*>(p.Vn) + ((long long)bh * p.npad + slot) * D;
-  bf16x8 kf16[kBf16 ? D / 16 : 1], vf16[kBf16 ? D / 16 : 1];
-  f32x4 kf32[kBf16 ? 1 : D / 8], vf32[kBf16 ? 1 : D / 8];
-  if constexpr (kBf16) {
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      kf16[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * 16 + h * 8);
-      vf16[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * 16 + h * 8);
-    }
-  } else {
-#pragma unroll
-    for (int ks = 0; ks < D / 8; ++ks) {
-      kf32[ks] = *reinterpret_cast<const f32x4*>(krow + ks * 8 + h * 4);
-      vf32[ks] = *reinterpret_cast<const f32x4*>(vrow + ks * 8 + h * 4);
-    }
-  }
-
-  f32x16 dk[D / 32], dv[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      dk[db][r] = 0.f;
-      dv[db][r] = 0.f;
-    }
-
-  // ---- staging of a 64-query tile
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int CPR = D / E;
-  constexpr int kChunks = kBwdQ * CPR / kThreads;
-  const T* qbase = static_cast<const T*>(p.Q) + b * L.qs[0] + i * L.qs[1];
-  const T* gbase = static_cast<const T*>(p.dO) + b * L.qs[0] + i * L.qs[1];
-  const T* qt = static_cast<const T*>(p.Qt) + (long long)bh * p.nqpad * D;
-  const T* gt = static_cast<const T*>(p.dOt) + (long long)bh * p.nqpad * D;
-  const float* lsec = p.lse2c + (long long)bh * p.nqpad;
-  const float* delc = p.deltac + (long long)bh * p.nqpad;
-  u32x4 stQ[kChunks], stG[kChunks], stQt[kBf16 ? kChunks : 1], stGt[kBf16 ? kChunks : 1];
-  float stL = 0.f, stD = 0.f;
-  int stI = -1;
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-  auto load_tile = [&](int t) {
-    const int pos0 = t * kBwdQ;
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      const int row = ch / CPR, col = (ch % CPR) * E;
-      const int pos = pos0 + row;
-      stQ[c] = zero4;
-      stG[c] = zero4;
-      if (pos < nq) {
-        const long long qrow = qlist[pos];
-        stQ[c] = *reinterpret_cast<const u32x4*>(qbase + qrow * L.qs[2] + col);
-        stG[c] = *reinterpret_cast<const u32x4*>(gbase + qrow * L.qs[2] + col);
-      }
-      if constexpr (kBf16) {
-        stQt[c] = *reinterpret_cast<const u32x4*>(qt + (long long)pos0 * D + ch * E);
-        stGt[c] = *reinterpret_cast<const u32x4*>(gt + (long long)pos0 * D + ch * E);
-      }
-    }
-    if (threadIdx.x < kBwdQ) {
-      const int pos = pos0 + threadIdx.x;
-      stL = lsec[pos];
-      stD = delc[pos];
-      stI = pos < nq ? qlist[pos] : -1;
-    }
-  };
-  auto store_tile = [&](int buf) {
-    T* sq = reinterpret_cast<T*>(sQn_raw + buf * kNatBytes);
-    T* sg = reinterpret_cast<T*>(sGn_raw + buf * kNatBytes);
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      const int row = ch / CPR, col = (ch % CPR) * E;
-      *reinterpret_cast<u32x4*>(sq + row * LD + col) = stQ[c];
-      *reinterpret_cast<u32x4*>(sg + row * LD + col) = stG[c];
-      if constexpr (kBf16) {
-        *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(sQt_raw + buf * kPackBytes) + ch * E) = stQt[c];
-        *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(sGt_raw + buf * kPackBytes) + ch * E) = stGt[c];
-      }
-    }
-    if (threadIdx.x < kBwdQ) {
-      sLse[buf][threadIdx.x] = stL;
-      sDel[buf][threadIdx.x] = stD;
-      sQi[buf][threadIdx.x] = stI;
-    }
-  };
-
-  auto compute_tile = [&](int buf, bool masked) {
-    const T* sq = reinterpret_cast<const T*>(sQn_raw + buf * kNatBytes);
-    const T* sg = reinterpret_cast<const T*>(sGn_raw + buf * kNatBytes);
-#pragma unroll
-    for (int qb = 0; qb < kBwdQ / 32; ++qb) {
-      f32x16 s, dp;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = 0.f;
-        dp[r] = 0.f;
-      }
-      if constexpr (kBf16) {
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          const bf16x8 qa = *reinterpret_cast<const bf16x8*>(sq + (qb * 32 + ln) * LD + ks * 16 + h * 8);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf16[ks], s, 0, 0, 0);
-          const bf16x8 ga = *reinterpret_cast<const bf16x8*>(sg + (qb * 32 + ln) * LD + ks * 16 + h * 8);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vf16[ks], dp, 0, 0, 0);
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < D / 8; ++ks) {
-          const f32x4 qa = *reinterpret_cast<const f32x4*>(sq + (qb * 32 + ln) * LD + ks * 8 + h * 4);
-          const f32x4 ga = *reinterpret_cast<const f32x4*>(sg + (qb * 32 + ln) * LD + ks * 8 + h * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[e], kf32[ks][e], s, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x2f32(ga[e], vf32[ks][e], dp, 0, 0, 0);
-          }
-        }
-      }
-      // accumulator rows are queries 8 (r/4) + 4 h + r%4 of this block, the column is this lane's key
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int qo = qb * 32 + 8 * q4 + 4 * h;
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sLse[buf][qo]);
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sDel[buf][qo]);
-        i32x4 qi4 = {0, 0, 0, 0};
-        if (masked) qi4 = *reinterpret_cast<const i32x4*>(&sQi[buf][qo]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = q4 * 4 + e;
-          float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
-          if (masked) {
-            const int qcmp = L.causal ? qi4[e] : kPadKeyIndex - 1;
-            if (my_kidx > qcmp) pv = 0.f;
-          }
-          s[r] = pv;
-          dp[r] = pv * (dp[r] - d4[e]);
-        }
-      }
-      if constexpr (kBf16) {
-        const T* sqt = reinterpret_cast<const T*>(sQt_raw + buf * kPackBytes);
-        const T* sgt = reinterpret_cast<const T*>(sGt_raw + buf * kPackBytes);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int t16 = qb * 2 + u;
-          const bf16x8 pf = pack8(s, u * 8);
-          const bf16x8 dsf = pack8(dp, u * 8);
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db) {
-            const bf16x8 ga = *reinterpret_cast<const bf16x8*>(sgt + ((t16 * 2 + h) * D + db * 32 + ln) * 8);
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, pf, dv[db], 0, 0, 0);
-            const bf16x8 qa = *reinterpret_cast<const bf16x8*>(sqt + ((t16 * 2 + h) * D + db * 32 + ln) * 8);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, dsf, dk[db], 0, 0, 0);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int qrow = qb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db) {
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sg[qrow * LD + db * 32 + ln], s[r], dv[db], 0, 0, 0);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sq[qrow * LD + db * 32 + ln], dp[r], dk[db], 0, 0, 0);
-          }
-        }
-      }
-    }
-  };
-
-  if (q_begin < n_qtiles) {
-    if constexpr (kBf16) {
-      load_tile(q_begin);
-      store_tile(0);
-      __syncthreads();
-      for (int t = q_begin; t < n_qtiles; ++t) {
-        const int buf = (t - q_begin) & 1;
-        if (t + 1 < n_qtiles) load_tile(t + 1);
-        compute_tile(buf, t * kBwdQ < q_full_pos || (t + 1) * kBwdQ > nq);
-        if (t + 1 < n_qtiles) store_tile(buf ^ 1);
-        __syncthreads();
-      }
-    } else {
-      for (int t = q_begin; t < n_qtiles; ++t) {
-        __syncthreads();
-        load_tile(t);
-        store_tile(0);
-        __syncthreads();
-        compute_tile(0, t * kBwdQ < q_full_pos || (t + 1) * kBwdQ > nq);
-      }
-    }
-  }
-
-  // ---- write dK' (scaled) and dV' for this lane's key slot; accumulator rows are d
-  float* dkrow = p.dKp + ((long long)bh * p.npad + slot) * D;
-  float* dvrow = p.dVp + ((long long)bh * p.npad + slot) * D;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      const int d = db * 32 + 8 * q4 + 4 * h;
-      f32x4 a = {dk[db][q4 * 4] * L.scale, dk[db][q4 * 4 + 1] * L.scale, dk[db][q4 * 4 + 2] * L.scale,
-                 dk[db][q4 * 4 + 3] * L.scale};
-      f32x4 c = {dv[db][q4 * 4], dv[db][q4 * 4 + 1], dv[db][q4 * 4 + 2], dv[db][q4 * 4 + 3]};
-      *reinterpret_cast<f32x4*>(dkrow + d) = a;
-      *reinterpret_cast<f32x4*>(dvrow + d) = c;
+      const f32x4 v = {acc[db][q4 * 4], acc[db][q4 * 4 + 1], acc[db][q4 * 4 + 2], acc[db][q4 * 4 + 3]};
+      *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
     }
+  __syncthreads();
+#pragma unroll
+  for (int c = threadIdx.x; c < 32 * (D / 4); c += kF32Threads<D>) {
+    const int row = c / (D / 4), d = c % (D / 4) * 4;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kF32Waves<D>; ++w) x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
+    store(row, d, x * scale);
+  }
 }
 
-// ------------------------------------------------------------------ dQ
-
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 1) void attn_bwd_dq_kernel(BwdParams p) {
-  constexpr bool kBf16 = sizeof(T) == 2;
-  constexpr int LD = D + 8;
-  constexpr int NBUF = kBf16 ? 2 : 1;
-  constexpr int kNatBytes = kTileN * LD * (int)sizeof(T);
-  constexpr int kPackBytes = kBf16 ? kTileN * D * 2 : 16;
-  __shared__ __attribute__((aligned(16))) unsigned char sK_raw[NBUF * kNatBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sV_raw[NBUF * kNatBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sKt_raw[NBUF * kPackBytes];
-  __shared__ __attribute__((aligned(16))) int sIdx[NBUF][kTileN];
-  __shared__ int sBound[2];
-
-  __shared__ int sItem;
-  const Layer& L = p.L;
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int ln = lane & 31, h = lane >> 5;
-
-  for (;;) {                                 // persistent: one (head, query tile) per iteration
-  __syncthreads();
-  if (threadIdx.x == 0) sItem = sched_next(p.sched);
-  __syncthreads();
-  const int item = sItem;
-  if (item < 0) break;
-  int bh, tq;
-  sched_decode(p.sched, p.order_off, item, bh, tq);
-  const int b = bh / L.Hq, i = bh % L.Hq;
-  const int nq = p.q_cnt[bh];
-  const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
-  const int* kidx = p.kidx + (long long)bh * p.npad;
-  const int* qlist = p.q_idx + (long long)bh * L.N;
-
-  const int pos_first = tq * kTileM, pos_last = min(pos_first + kTileM, nq) - 1;
-  if (threadIdx.x == 0 || threadIdx.x == 64) {
-    const int which = threadIdx.x ? 1 : 0;
-    const int row = qlist[which ? pos_last : pos_first];
-    sBound[which] = L.causal ? upper_cnt(kidx, nkeys, row) : nkeys;
-  }
-  __syncthreads();
-  const int n_full_tiles = sBound[0] / kTileN;
-  const int ntiles = cdiv(sBound[1], kTileN);
-
-  const int qpos = pos_first + wave * 32 + ln;
-  const bool qvalid = qpos < nq;
-  const int qpos_c = min(qpos, nq - 1);
-  const int qrow = qlist[qpos_c];
-  const int qcmp = L.causal ? qrow : kPadKeyIndex - 1;
-  const float lse2 = p.lse2c[(long long)bh * p.nqpad + qpos_c];
-  const float delta = p.deltac[(long long)bh * p.nqpad + qpos_c];
-  const float c2 = L.scale * kLog2e;
-  const T* qptr = static_cast<const T*>(p.Q) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
-  const T* gptr = static_cast<const T*>(p.dO) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
-  bf16x8 qf16[kBf16 ? D / 16 : 1], gf16[kBf16 ? D / 16 : 1];
-  f32x4 qf32[kBf16 ? 1 : D / 8], gf32[kBf16 ? 1 : D / 8];
-  if constexpr (kBf16) {
+// One 32-row block in fragment order (A or B operand of a product that contracts over d) / in k-packed order (A operand of
+// a product that contracts over the rows).
+template <int D>
+__device__ __forceinline__ void load_frag(f32x4 (&f)[D / 8], const float* block) {
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      qf16[ks] = *reinterpret_cast<const bf16x8*>(qptr + ks * 16 + h * 8);
-      gf16[ks] = *reinterpret_cast<const bf16x8*>(gptr + ks * 16 + h * 8);
-    }
-  } else {
+  for (int ks = 0; ks < D / 8; ++ks) f[ks] = *reinterpret_cast<const f32x4*>(block + (ks * 64 + lane_id()) * 4);
+}
+template <int D>
+__device__ __forceinline__ void load_packed(f32x4 (&f)[4][D / 32], const float* block) {
 #pragma unroll
-    for (int ks = 0; ks < D / 8; ++ks) {
-      qf32[ks] = *reinterpret_cast<const f32x4*>(qptr + ks * 8 + h * 4);
-      gf32[ks] = *reinterpret_cast<const f32x4*>(gptr + ks * 8 + h * 4);
-    }
-  }
-  f32x16 dq[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
-
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int CPR = D / E;
-  constexpr int kChunks = kTileN * CPR / kThreads;
-  const T* kn = static_cast<const T*>(p.Kn) + (long long)bh * p.npad * D;
-  const T* vn = static_cast<const T*>(p.Vn) + (long long)bh * p.npad * D;
-  const T* kt = static_cast<const T*>(p.Kt) + (long long)bh * p.npad * D;
-  u32x4 stK[kChunks], stV[kChunks], stKt[kBf16 ? kChunks : 1];
-  i32x4 stI;
-
-  auto load_tile = [&](int t) {
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      stK[c] = *reinterpret_cast<const u32x4*>(kn + (long long)t * kTileN * D + ch * E);
-      stV[c] = *reinterpret_cast<const u32x4*>(vn + (long long)t * kTileN * D + ch * E);
-      if constexpr (kBf16) stKt[c] = *reinterpret_cast<const u32x4*>(kt + (long long)t * kTileN * D + ch * E);
-    }
-    if (threadIdx.x < kTileN / 4) stI = *reinterpret_cast<const i32x4*>(kidx + t * kTileN + threadIdx.x * 4);
-  };
-  auto store_tile = [&](int buf) {
-    T* sk = reinterpret_cast<T*>(sK_raw + buf * kNatBytes);
-    T* sv = reinterpret_cast<T*>(sV_raw + buf * kNatBytes);
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      const int row = ch / CPR, col = (ch % CPR) * E;
-      *reinterpret_cast<u32x4*>(sk + row * LD + col) = stK[c];
-      *reinterpret_cast<u32x4*>(sv + row * LD + col) = stV[c];
-      if constexpr (kBf16) *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(sKt_raw + buf * kPackBytes) + ch * E) = stKt[c];
-    }
-    if (threadIdx.x < kTileN / 4) *reinterpret_cast<i32x4*>(&sIdx[buf][threadIdx.x * 4]) = stI;
-  };
-  auto compute_tile = [&](int buf, bool masked) {
-    const T* sk = reinterpret_cast<const T*>(sK_raw + buf * kNatBytes);
-    const T* sv = reinterpret_cast<const T*>(sV_raw + buf * kNatBytes);
-    f32x16 s[2], dp[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[kb][r] = 0.f;
-        dp[kb][r] = 0.f;
-      }
-      if constexpr (kBf16) {
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          const bf16x8 ka = *reinterpret_cast<const bf16x8*>(sk + (kb * 32 + ln) * LD + ks * 16 + h * 8);
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf16[ks], s[kb], 0, 0, 0);
-          const bf16x8 va = *reinterpret_cast<const bf16x8*>(sv + (kb * 32 + ln) * LD + ks * 16 + h * 8);
-          dp[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, gf16[ks], dp[kb], 0, 0, 0);
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < D / 8; ++ks) {
-          const f32x4 ka = *reinterpret_cast<const f32x4*>(sk + (kb * 32 + ln) * LD + ks * 8 + h * 4);
-          const f32x4 va = *reinterpret_cast<const f32x4*>(sv + (kb * 32 + ln) * LD + ks * 8 + h * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[e], qf32[ks][e], s[kb], 0, 0, 0);
-            dp[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[e], gf32[ks][e], dp[kb], 0, 0, 0);
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        i32x4 id = {0, 0, 0, 0};
-        if (masked) id = *reinterpret_cast<const i32x4*>(&sIdx[buf][kb * 32 + 8 * q4 + 4 * h]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = q4 * 4 + e;
-          float pv = fast_exp2(fmaf(s[kb][r], c2, -lse2));
-          if (masked && id[e] > qcmp) pv = 0.f;
-          dp[kb][r] = pv * (dp[kb][r] - delta);
-        }
-      }
-    if constexpr (kBf16) {
-      const T* skt = reinterpret_cast<const T*>(sKt_raw + buf * kPackBytes);
-#pragma unroll
-      for (int t16 = 0; t16 < 4; ++t16) {
-        const bf16x8 dsf = pack8(dp[t16 >> 1], (t16 & 1) * 8);
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
-          const bf16x8 ka = *reinterpret_cast<const bf16x8*>(skt + ((t16 * 2 + h) * D + db * 32 + ln) * 8);
-          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, dsf, dq[db], 0, 0, 0);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int ks_slot = kb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db)
-            dq[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sk[ks_slot * LD + db * 32 + ln], dp[kb][r], dq[db], 0, 0, 0);
-        }
-    }
-  };
-
-  if (ntiles > 0) {
-    if constexpr (kBf16) {
-      load_tile(0);
-      store_tile(0);
-      __syncthreads();
-      for (int t = 0; t < ntiles; ++t) {
-        if (t + 1 < ntiles) load_tile(t + 1);
-        compute_tile(t & 1, t >= n_full_tiles);
-        if (t + 1 < ntiles) store_tile((t + 1) & 1);
-        __syncthreads();
-      }
-    } else {
-      for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();
-        load_tile(t);
-        store_tile(0);
-        __syncthreads();
-        compute_tile(0, t >= n_full_tiles);
-      }
-    }
-  }
-  if (qvalid) {
-    T* optr = static_cast<T*>(p.dQ) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
+  for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
+      f[q4][db] = *reinterpret_cast<const f32x4*>(block + ((q4 * (D / 32) + db) * 64 + lane_id()) * 4);
+}
+template <int D>
+__device__ __forceinline__ f32x16 product_d(const f32x4 (&a)[D / 8], const f32x4 (&b)[D / 8]) {
+  f32x16 s;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = db * 32 + 8 * q4 + 4 * h;
-        const float v0 = dq[db][q4 * 4 + 0] * L.scale, v1 = dq[db][q4 * 4 + 1] * L.scale;
-        const float v2 = dq[db][q4 * 4 + 2] * L.scale, v3 = dq[db][q4 * 4 + 3] * L.scale;
-        if constexpr (kBf16) {
-          uint2 w;
-          w.x = pack_bf16x2(v0, v1);
-          w.y = pack_bf16x2(v2, v3);
-          *reinterpret_cast<uint2*>(optr + d) = w;
-        } else {
-          f32x4 w = {v0, v1, v2, v3};
-          *reinterpret_cast<f32x4*>(optr + d) = w;
-        }
-      }
+  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 8; ++ks)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ks][e], b[ks][e], s, 0, 0, 0);
+  return s;
+}
+template <int D>
+__device__ __forceinline__ void add_product_rows(f32x16 (&acc)[D / 32], const f32x4 (&a)[4][D / 32], const f32x16& x) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+      acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r >> 2][db][r & 3], x[r], acc[db], 0, 0, 0);
+}
+
+// grid: npad / 32 * nsplit * B*Hq, heads fastest; the first keys, which the most queries see, first.  dK', dV' of 32 listed
+// keys, or of the share of the queries that a split of their 256-key tile takes (as in the bf16 kernels).
+template <int D>
+__global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_key_f32_kernel(BwdParams p) {
+  constexpr int NB = D / 32;
+  __shared__ __attribute__((aligned(16))) float sO[kF32Waves<D>][32][D + 4];
+  const Layer& L = p.L;
+  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, sp = (int)(blockIdx.x / BH) % p.nsplit, b = bh / L.Hq;
+  const int slot0 = (int)(blockIdx.x / BH) / p.nsplit * 32;
+  const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
+  if (slot0 >= nkeys) return;
+  const int nq = p.q_cnt[bh];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int* kfirst = p.kfirst + (long long)bh * p.npad;
+  const int my_first = kfirst[slot0 + ln] - 4 * h;          // query positions below it do not see this lane's key
+  const int q_first = kfirst[slot0 / kKeyTile * kKeyTile] / kKeyQ, n_all = cdiv(nq, kKeyQ) - q_first;
+  const int n_sp = key_tile_splits(n_all, p.nsplit, p.split_len), per_split = cdiv(n_all, n_sp) * kKeyQ;
+  if (sp >= n_sp) return;
+  const int q_begin = max(kfirst[slot0], q_first * kKeyQ + sp * per_split) / 32;
+  const int q_end = min(nq, q_first * kKeyQ + (sp + 1) * per_split);
+  const long long kv = ((long long)bh * p.npad + slot0) * D, qo = (long long)bh * p.nqpad;
+  f32x4 kf[D / 8], vf[D / 8];
+  load_frag<D>(kf, static_cast<const float*>(p.Kn) + kv);
+  load_frag<D>(vf, static_cast<const float*>(p.Vn) + kv);
+  f32x16 dk[NB], dv[NB];
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dk[db][r] = 0.f, dv[db][r] = 0.f;
+  for (int t = q_begin + wave; t * 32 < q_end; t += kF32Waves<D>) {
+    const long long row = (qo + t * 32) * D;
+    f32x4 qa[D / 8], ga[D / 8], qt[4][NB], gt[4][NB], lse[4], del[4];
+    load_frag<D>(qa, static_cast<const float*>(p.Qn) + row);
+    load_frag<D>(ga, static_cast<const float*>(p.dOn) + row);
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      lse[q4] = *reinterpret_cast<const f32x4*>(p.lse2c + qo + t * 32 + 8 * q4 + 4 * h);
+      del[q4] = *reinterpret_cast<const f32x4*>(p.deltac + qo + t * 32 + 8 * q4 + 4 * h);
+    }
+    load_packed<D>(qt, static_cast<const float*>(p.Qt) + row);
+    load_packed<D>(gt, static_cast<const float*>(p.dOt) + row);
+    f32x16 s = product_d<D>(qa, kf), dp = product_d<D>(ga, vf);      // rows: queries 8 (r / 4) + 4 h + r % 4
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float pv = fast_exp2(fmaf(s[r], c2, -lse[r >> 2][r & 3]));
+      if (t * 32 + 8 * (r >> 2) + (r & 3) < my_first) pv = 0.f;
+      s[r] = pv;
+      dp[r] = pv * (dp[r] - del[r >> 2][r & 3]);
+    }
+    add_product_rows<D>(dv, gt, s);
+    add_product_rows<D>(dk, qt, dp);
   }
-  }  // work-item loop
+  float *dkp = p.dKp + sp * p.plane + kv, *dvp = p.dVp + sp * p.plane + kv;
+  merge_waves<D>(sO, dk, L.scale, [&](int row, int d, const f32x4& x) { *reinterpret_cast<f32x4*>(dkp + row * D + d) = x; });
+  merge_waves<D>(sO, dv, 1.f, [&](int row, int d, const f32x4& x) { *reinterpret_cast<f32x4*>(dvp + row * D + d) = x; });
+}
+
+// grid: cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first.  dQ of 32 kept queries.
+template <int D>
+__global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_dq_f32_kernel(BwdParams p) {
+  constexpr int NB = D / 32;
+  __shared__ __attribute__((aligned(16))) float sO[kF32Waves<D>][32][D + 4];
+  const Layer& L = p.L;
+  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq;
+  const int nq = p.q_cnt[bh];
+  const int tq = cdiv(nq, 32) - 1 - (int)(blockIdx.x / BH);
+  if (tq < 0) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int* qlist = p.q_idx + (long long)bh * L.N;
+  const int* qvis = p.qvis + (long long)bh * L.N;
+  const long long qo = (long long)bh * p.nqpad + tq * 32;
+  const int pos_c = min(tq * 32 + ln, nq - 1);
+  const int qvisible = qvis[pos_c] - 4 * h, nblocks = cdiv(qvis[min(tq * 32 + 31, nq - 1)], 32);
+  const float lse = p.lse2c[qo + ln], delta = p.deltac[qo + ln];
+  f32x4 qf[D / 8], gf[D / 8];
+  load_frag<D>(qf, static_cast<const float*>(p.Qn) + qo * D);
+  load_frag<D>(gf, static_cast<const float*>(p.dOn) + qo * D);
+  f32x16 dq[NB];
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+  for (int t = wave; t < nblocks; t += kF32Waves<D>) {
+    const long long kv = ((long long)bh * p.npad + t * 32) * D;
+    f32x4 kf[D / 8], vf[D / 8], kt[4][NB];
+    load_frag<D>(kf, static_cast<const float*>(p.Kn) + kv);
+    load_frag<D>(vf, static_cast<const float*>(p.Vn) + kv);
+    load_packed<D>(kt, static_cast<const float*>(p.Kt) + kv);
+    f32x16 s = product_d<D>(kf, qf), dp = product_d<D>(vf, gf);      // rows: keys 8 (r / 4) + 4 h + r % 4
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float pv = fast_exp2(fmaf(s[r], c2, -lse));
+      if (t * 32 + 8 * (r >> 2) + (r & 3) >= qvisible) pv = 0.f;
+      dp[r] = pv * (dp[r] - delta);
+    }
+    add_product_rows<D>(dq, kt, dp);
+  }
+  float* head = static_cast<float*>(p.dQ) + b * L.qs[0] + i * L.qs[1];
+  merge_waves<D>(sO, dq, L.scale, [&](int row, int d, const f32x4& x) {
+    if (tq * 32 + row < nq) *reinterpret_cast<f32x4*>(head + (long long)qlist[tq * 32 + row] * L.qs[2] + d) = x;
+  });
 }
 
 // ------------------------------------------------------------------ dQ, bf16 fast path
@@ -811,20 +505,6 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
 //   MODE 1 (dV): streams Q (natural) and dO (k-packed):     S -> P;       dV'^T += dO^T P
 // lse * log2e and delta of the tile's queries come with the tile (LDS-DMA of 4 bytes per lane); the causal
 // mask is a comparison of the query position with the first position that sees the lane's key.
-
-constexpr int kKeyWaves = 8;
-constexpr int kKeyThreads = kKeyWaves * 64;
-constexpr int kKeyTile = kKeyWaves * 32;     // packed keys per workgroup
-constexpr int kKeyQ = 64;                    // queries per streamed tile
-// A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
-// against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
-// query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
-constexpr int kKeySplitLen = 128;            // query tiles per split, at least (64..128 measure alike, 32 and 256 worse)
-constexpr int kKeyMaxSplits = 4;             // at most 8: a work item carries the split in 3 bits
-__host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
-  const int s = n_qtiles / split_len;
-  return s < 1 ? 1 : (s > max_splits ? max_splits : s);
-}
 
 // Work items of the key kernels: (head, key tile, split), in dispatch order -- heads in groups of p.head_group,
 // inside a group key tile by key tile (the first key tiles, seen by the most queries, first), the splits of a
@@ -1233,20 +913,19 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   const size_t kvrows = npad_kv > 0 ? (size_t)L.B * L.Hkv * npad_kv : krows;
   w.Kn = a.take<unsigned char>(kvrows * L.D * es);
   w.Vn = a.take<unsigned char>(kvrows * L.D * es);
-  w.Kt = a.take<unsigned char>(dtype == OMNI_BF16 ? kvrows * L.D * es : 16);
-  w.Qt = a.take<unsigned char>(dtype == OMNI_BF16 ? qrows * L.D * es : 16);
-  w.dOt = a.take<unsigned char>(dtype == OMNI_BF16 ? qrows * L.D * es : 16);
-  w.Qn = a.take<unsigned char>(dtype == OMNI_BF16 ? qrows * L.D * es : 16);
-  w.dOn = a.take<unsigned char>(dtype == OMNI_BF16 ? qrows * L.D * es : 16);
+  w.Kt = a.take<unsigned char>(kvrows * L.D * es);
+  w.Qt = a.take<unsigned char>(qrows * L.D * es);
+  w.dOt = a.take<unsigned char>(qrows * L.D * es);
+  w.Qn = a.take<unsigned char>(qrows * L.D * es);
+  w.dOn = a.take<unsigned char>(qrows * L.D * es);
   w.kidx = a.take<int>(krows);
   w.lse2c = a.take<float>(qrows);
   w.deltac = a.take<float>(qrows);
-  const size_t planes = dtype == OMNI_BF16 ? kKeyMaxSplits : 1;
-  w.dKp = a.take<float>(planes * krows * L.D);
-  w.dVp = a.take<float>(planes * krows * L.D);
+  w.dKp = a.take<float>(kKeyMaxSplits * krows * L.D);
+  w.dVp = a.take<float>(kKeyMaxSplits * krows * L.D);
   w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
-  w.qvis = a.take<int>(dtype == OMNI_BF16 ? BH * L.N : 4);
-  w.kfirst = a.take<int>(dtype == OMNI_BF16 ? krows : 4);
+  w.qvis = a.take<int>(BH * L.N);
+  w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
   w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad));
   w.kidx_kv = a.take<int>(npad_kv > 0 ? kvrows : 4);
@@ -1258,7 +937,7 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
 // Rows of a head's packed buffers: whole workgroup tiles, and never a multiple of 4096 rows -- with a
 // power-of-two stride between the heads, workgroups that stream different heads at the same tile index hit the
 // same cache sets and memory channels.
-int bwd_npad(int b_cap) {                     // a multiple of kKeyTile, hence of kBwdKeys
+int bwd_npad(int b_cap) {                     // a multiple of kKeyTile
   int n = (int)align_up(b_cap, kKeyTile);
   if (n % 4096 == 0) n += kKeyTile;
   return n;
@@ -1297,12 +976,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     budget = w.vbudget;
     b_cap = npad;                             // the lists' row pitch; their lengths are in vbudget
   } else {
-    rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn,
-                     dt == OMNI_BF16 ? w.Kt : nullptr, nullptr, w.kidx, st);
+    rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, w.Kt, nullptr, w.kidx, st,
+                     nullptr, dt == OMNI_F32);
     if (rc != OMNI_OK) return rc;
   }
-  rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, dt == OMNI_BF16 ? w.Qn : nullptr,
-                  dt == OMNI_BF16 ? w.dOn : nullptr, w.lse2c, w.deltac, st);
+  rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, w.Qn, w.dOn, w.lse2c,
+                  w.deltac, st);
   if (rc != OMNI_OK) return rc;
   BwdParams p;
   p.Q = Q;
@@ -1326,8 +1005,8 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.deltac = w.deltac;
   p.dKp = w.dKp;
   p.dVp = w.dVp;
-  p.nsplit = sizeof(T) == 2 ? kKeyMaxSplits : 1;
-  p.split_len = g_key_split_len;
+  p.nsplit = kKeyMaxSplits;
+  p.split_len = sizeof(T) == 2 ? g_key_split_len : kKeySplitLenF32;
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
   p.sched = w.sched;
@@ -1337,9 +1016,10 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_stride = cap_keys / kTileN;
   p.npad_kv = BLOCKS ? npad_kv : npad;
   constexpr bool kFast = sizeof(T) == 2;
-  const int tile_m = kFast ? kDqTileM : kTileM;
+  rc = check_work_list(L, kFast ? kDqTileM : kTileM);
+  if (rc != OMNI_OK) return rc;
   {
-    Bounds bn{};                                 // bf16: masks by position; both: slot map, cleared rows, dQ's work items
+    Bounds bn{};                                 // masks by position, slot map, cleared rows, the bf16 dQ kernel's work items
     bn.q_idx = q_idx;
     bn.q_cnt = q_cnt;
     bn.klist = w.kidx;
@@ -1347,19 +1027,21 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     bn.budget = budget;
     bn.b_cap = b_cap;
     bn.npad = npad;
-    bn.qvis = kFast ? w.qvis : nullptr;
-    bn.kfirst = kFast ? w.kfirst : nullptr;
+    bn.qvis = w.qvis;
+    bn.kfirst = w.kfirst;
     bn.inv = w.inv;
     bn.X = dQ;
     bn.elem_bytes = sizeof(T);
-    bn.tile_m = tile_m;
-    bn.sched = w.sched;
+    bn.tile_m = kDqTileM;
+    bn.sched = kFast ? w.sched : nullptr;
     rc = run_bounds(L, bn, st);
     if (rc != OMNI_OK) return rc;
   }
-  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
-  rc = run_order(L, q_cnt, tile_m, w.sched, st);
-  if (rc != OMNI_OK) return rc;
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, kDqTileM);
+  if constexpr (kFast) {
+    rc = run_order(L, q_cnt, kDqTileM, w.sched, st);
+    if (rc != OMNI_OK) return rc;
+  }
   {
     ProfScope prof__(kProfBwdDkDv, st);
     if constexpr (sizeof(T) == 2) {
@@ -1378,7 +1060,9 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
       OMNI_LAUNCH_CHECK();
       hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 0, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
     } else {
-      hipLaunchKernelGGL((attn_bwd_dkdv_kernel<T, D>), dim3(npad / kBwdKeys, L.B * L.Hq), dim3(kThreads), 0, st, p);
+      hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),
+                         dim3(kF32Threads<D>),
+                         0, st, p);
     }
     OMNI_LAUNCH_CHECK();
   }
@@ -1387,7 +1071,8 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     if constexpr (kFast)
       hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
     else
-      hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), dim3(persistent_grid() / 2), dim3(kThreads), 0, st, p);
+      hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)), dim3(kF32Threads<D>),
+                         0, st, p);
     OMNI_LAUNCH_CHECK();
   }
   {

@@ -29,9 +29,8 @@
 //    longest-first work list with one queue per XCD (sched.hip); causal masks are
 //    position compares against per-query visible-prefix counts (pack.hip).
 //    Short sequences go through attn_fwd_split_kernel: 32-row items, key tiles dealt to the wavefronts.
-//  * fp32 inputs (attn_fwd_kernel, the accuracy path of the 1e-4 parity cases):
-//    256 threads = 4 wavefronts x 32 rows, fp32 32x32x2 MFMA, register-staged
-//    double buffer; not tuned.
+//  * fp32 inputs (attn_fwd_f32_kernel, the accuracy path of the 1e-4 parity cases): the division of labour of the split
+//    kernel on the fp32 32x32x2 MFMA.
 
 #include <type_traits>
 
@@ -70,319 +69,6 @@ struct FwdParams {
   const int* tile_map;  // in-place variant: [B*Hq, tile_stride] tile of the packed K/V that tile t of a head's key list is
   int tile_stride;
 };
-
-// number of entries <= v in ascending a[0,n)
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(FwdParams p) {
-  constexpr bool kBf16 = sizeof(T) == 2;
-  constexpr int KLD = kBf16 ? D + 8 : D + 4;        // K tile row pitch in elements
-  constexpr int VLD = D + 8;                        // fp32 V tile row pitch
-  constexpr int NBUF = kBf16 ? 2 : 1;
-  constexpr int kKBytes = kTileN * KLD * (int)sizeof(T);
-  constexpr int kVBytes = kBf16 ? kTileN * D * 2 : kTileN * VLD * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char sK_raw[NBUF * kKBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char sV_raw[NBUF * kVBytes];
-  __shared__ __attribute__((aligned(16))) int sIdx[NBUF][kTileN];
-  __shared__ int sBound[2];
-
-  __shared__ int sItem;
-  const Layer& L = p.L;
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int ln = lane & 31, h = lane >> 5;
-  const float c2 = L.scale * kLog2e;
-
-  for (;;) {                                 // persistent: one work item (head, query tile) per iteration
-  __syncthreads();                           // LDS of the previous item is no longer read
-  if (threadIdx.x == 0) sItem = sched_next(p.sched);
-  __syncthreads();
-  const int item = sItem;
-  if (item < 0) break;
-  int bh, tq;
-  sched_decode(p.sched, p.order_off, item, bh, tq);
-  const int b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
-  const int nq = p.q_cnt ? p.q_cnt[bh] : L.N;
-  const int nkeys = p.budget ? min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap) : L.N;
-  const int bhx = p.per_q_head ? bh : b * L.Hkv + g;
-  const int* kidx = p.kidx + (long long)bhx * p.npad;
-  const int* qlist = p.q_idx ? p.q_idx + (long long)bh * L.N : nullptr;
-
-  // ---- key range of this query tile
-  const int pos_first = tq * kTileM, pos_last = min(pos_first + kTileM, nq) - 1;
-  if (threadIdx.x == 0 || threadIdx.x == 64) {
-    const int which = threadIdx.x ? 1 : 0;
-    const int pos = which ? pos_last : pos_first;
-    const int row = qlist ? qlist[pos] : pos;
-    int cnt;
-    if (!L.causal) cnt = nkeys;
-    else if (p.identity_keys) cnt = min(row + 1, nkeys);
-    else cnt = upper_count(kidx, nkeys, row);
-    sBound[which] = cnt;
-  }
-  __syncthreads();
-  const int n_full_tiles = sBound[0] / kTileN;         // tiles with every key admissible for every row
-  const int ntiles = cdiv(sBound[1], kTileN);
-
-  // ---- this lane's query row
-  const int qpos = pos_first + wave * 32 + ln;
-  const bool qvalid = qpos < nq;
-  const int qpos_c = min(qpos, nq - 1);
-  const int qrow = qlist ? qlist[qpos_c] : qpos_c;
-  const int qcmp = L.causal ? qrow : kPadKeyIndex - 1;  // key admissible iff its index <= qcmp
-  const T* qptr = static_cast<const T*>(p.Q) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
-
-  bf16x8 qf16[kBf16 ? D / 16 : 1];
-  f32x4 qf32[kBf16 ? 1 : D / 8];
-  if constexpr (kBf16) {
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) qf16[ks] = *reinterpret_cast<const bf16x8*>(qptr + ks * 16 + h * 8);
-  } else {
-#pragma unroll
-    for (int ks = 0; ks < D / 8; ++ks) qf32[ks] = *reinterpret_cast<const f32x4*>(qptr + ks * 8 + h * 4);
-  }
-
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  // ---- tile staging
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int CPR = D / E;
-  constexpr int kChunks = kTileN * CPR / kThreads;   // 16-byte chunks per thread per operand
-  const T* kp = static_cast<const T*>(p.Kp) + (long long)bhx * p.npad * D;
-  const T* vp = static_cast<const T*>(p.Vp) + (long long)bhx * p.npad * D;
-  u32x4 stK[kChunks], stV[kChunks];
-  i32x4 stI;
-
-  auto load_k = [&](int t) {
-    const T* ks = kp + (long long)t * kTileN * D;
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) stK[c] = *reinterpret_cast<const u32x4*>(ks + (threadIdx.x + c * kThreads) * E);
-  };
-  auto load_v = [&](int t) {
-    const T* vs = vp + (long long)t * kTileN * D;
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) stV[c] = *reinterpret_cast<const u32x4*>(vs + (threadIdx.x + c * kThreads) * E);
-    if (threadIdx.x < kTileN / 4) stI = *reinterpret_cast<const i32x4*>(kidx + t * kTileN + threadIdx.x * 4);
-  };
-  auto store_k = [&](int buf) {
-    T* sk = reinterpret_cast<T*>(sK_raw + buf * kKBytes);
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      *reinterpret_cast<u32x4*>(sk + (ch / CPR) * KLD + (ch % CPR) * E) = stK[c];
-    }
-  };
-  auto store_v = [&](int buf) {          // the slot indices travel with the V tile
-    T* sv = reinterpret_cast<T*>(sV_raw + buf * kVBytes);
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      const int ch = threadIdx.x + c * kThreads;
-      if constexpr (kBf16) *reinterpret_cast<u32x4*>(sv + ch * E) = stV[c];
-      else *reinterpret_cast<u32x4*>(sv + (ch / CPR) * VLD + (ch % CPR) * E) = stV[c];
-    }
-    if (threadIdx.x < kTileN / 4) *reinterpret_cast<i32x4*>(&sIdx[buf][threadIdx.x * 4]) = stI;
-  };
-
-  // S^T tile = K tile . Q^T (64 keys x 32 queries per wavefront)
-  auto qk_tile = [&](int buf, f32x16 (&s)[2]) {
-    const T* sk = reinterpret_cast<const T*>(sK_raw + buf * kKBytes);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-      if constexpr (kBf16) {
-        // LDS fragment reads are issued one group of 4 ahead of the MFMAs that consume them; the
-        // scheduling fences keep the compiler from pulling each read back next to its MFMA
-        // (which would expose the full LDS latency 16 times per tile).
-        constexpr int NG = D / 64;          // groups of 4 k-steps
-        bf16x8 ka[4], kb4[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          ka[j] = *reinterpret_cast<const bf16x8*>(sk + (kb * 32 + ln) * KLD + j * 16 + h * 8);
-#pragma unroll
-        for (int gi = 0; gi < NG; ++gi) {
-          __builtin_amdgcn_sched_barrier(0);
-          if (gi + 1 < NG) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              kb4[j] = *reinterpret_cast<const bf16x8*>(sk + (kb * 32 + ln) * KLD + ((gi + 1) * 4 + j) * 16 + h * 8);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[j], qf16[gi * 4 + j], s[kb], 0, 0, 0);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) ka[j] = kb4[j];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < D / 8; ++ks) {
-          const f32x4 kf = *reinterpret_cast<const f32x4*>(sk + (kb * 32 + ln) * KLD + ks * 8 + h * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf32[ks][e], s[kb], 0, 0, 0);
-        }
-      }
-    }
-  };
-
-  // mask + online softmax on a finished S^T tile; leaves P in s
-  auto softmax_tile = [&](int buf, bool masked, f32x16 (&s)[2]) {
-    if (masked) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const i32x4 id = *reinterpret_cast<const i32x4*>(&sIdx[buf][kb * 32 + 8 * q4 + 4 * h]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (id[e] > qcmp) s[kb][q4 * 4 + e] = -INFINITY;
-        }
-    }
-    // this lane and lane^32 share the query row
-    float mloc = s[0][0];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, s[kb][r]);
-    mloc = pair_max(mloc);
-    const float m_new = fmaxf(m_run, mloc);
-    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-    if (__any(m_new > m_run)) {
-      const float alpha = fast_exp2((m_run - m_ref) * c2);
-      l_run *= alpha;
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      m_run = m_new;
-    }
-    const float mc = m_ref * c2;
-    float lsum = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pv = fast_exp2(fmaf(s[kb][r], c2, -mc));
-        s[kb][r] = pv;
-        lsum += pv;
-      }
-    l_run += lsum;
-  };
-
-  // O^T += V^T . P^T
-  auto pv_tile = [&](int buf, const f32x16 (&s)[2]) {
-    const T* sv = reinterpret_cast<const T*>(sV_raw + buf * kVBytes);
-    if constexpr (kBf16) {
-      constexpr int NB = D / 32;
-      bf16x8 va[NB], vb[NB];
-#pragma unroll
-      for (int db = 0; db < NB; ++db)
-        va[db] = *reinterpret_cast<const bf16x8*>(sv + ((0 * 2 + h) * D + db * 32 + ln) * 8);
-#pragma unroll
-      for (int t16 = 0; t16 < 4; ++t16) {
-        const int kb = t16 >> 1, r0 = (t16 & 1) * 8;
-        __builtin_amdgcn_sched_barrier(0);
-        if (t16 + 1 < 4) {
-#pragma unroll
-          for (int db = 0; db < NB; ++db)
-            vb[db] = *reinterpret_cast<const bf16x8*>(sv + (((t16 + 1) * 2 + h) * D + db * 32 + ln) * 8);
-        }
-        union { bf16x8 v; unsigned u[4]; } pf;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) pf.u[jj] = pack_bf16x2(s[kb][r0 + 2 * jj], s[kb][r0 + 2 * jj + 1]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int db = 0; db < NB; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db], pf.v, o[db], 0, 0, 0);
-#pragma unroll
-        for (int db = 0; db < NB; ++db) va[db] = vb[db];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    } else {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int slot = kb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db) {
-            const float vf = sv[slot * VLD + db * 32 + ln];
-            o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf, s[kb][r], o[db], 0, 0, 0);
-          }
-        }
-    }
-  };
-
-  if (ntiles > 0) {
-    if constexpr (kBf16) {
-      f32x16 s[2];
-      load_k(0);
-      load_v(0);
-      store_k(0);
-      store_v(0);
-      __syncthreads();
-      for (int t = 0; t < ntiles; ++t) {
-        if (t + 1 < ntiles) {
-          load_k(t + 1);
-          load_v(t + 1);
-        }
-        qk_tile(t & 1, s);
-        softmax_tile(t & 1, t >= n_full_tiles, s);
-        pv_tile(t & 1, s);
-        if (t + 1 < ntiles) {
-          store_k((t + 1) & 1);
-          store_v((t + 1) & 1);
-        }
-        __syncthreads();
-      }
-    } else {
-      f32x16 s[2];
-      for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();
-        load_k(t);
-        load_v(t);
-        store_k(0);
-        store_v(0);
-        __syncthreads();
-        qk_tile(0, s);
-        softmax_tile(0, t >= n_full_tiles, s);
-        pv_tile(0, s);
-      }
-    }
-  }
-
-  // ---- epilogue
-  const float l_tot = pair_sum(l_run);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if (qvalid) {
-    T* optr = static_cast<T*>(p.O) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = db * 32 + 8 * q4 + 4 * h;
-        const float v0 = o[db][q4 * 4 + 0] * inv, v1 = o[db][q4 * 4 + 1] * inv;
-        const float v2 = o[db][q4 * 4 + 2] * inv, v3 = o[db][q4 * 4 + 3] * inv;
-        if constexpr (kBf16) {
-          uint2 w;
-          w.x = pack_bf16x2(v0, v1);
-          w.y = pack_bf16x2(v2, v3);
-          *reinterpret_cast<uint2*>(optr + d) = w;
-        } else {
-          f32x4 w = {v0, v1, v2, v3};
-          *reinterpret_cast<f32x4*>(optr + d) = w;
-        }
-      }
-    if (h == 0)
-      p.lse[(long long)bh * L.N + qrow] = l_tot > 0.f ? (m_run * c2 + log2f(l_tot)) * kLn2 : -INFINITY;
-  }
-  }  // work-item loop
-}
 
 // ------------------------------------------------------------------ bf16 fast path
 //
@@ -805,7 +491,7 @@ constexpr int kSplitWaves = 4;
 constexpr int kSplitThreads = kSplitWaves * 64;
 constexpr int kSplitRows = 32;
 
-// grid: (B*Hq, cdiv(N, kSplitRows)); a head's last rows, which see the most keys, first
+// grid: cdiv(N, kSplitRows) * B*Hq, heads fastest; a head's last rows, which see the most keys, first
 template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdParams p) {
   typedef u16 T;
@@ -815,9 +501,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdPar
   __shared__ __attribute__((aligned(16))) float sO[kSplitWaves][kSplitRows][OP];
   __shared__ float sM[kSplitWaves][kSplitRows], sL[kSplitWaves][kSplitRows];
   const Layer& L = p.L;
-  const int bh = blockIdx.x, b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
+  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
   const int nq = p.q_cnt[bh];
-  const int tq = cdiv(nq, kSplitRows) - 1 - (int)blockIdx.y;
+  const int tq = cdiv(nq, kSplitRows) - 1 - (int)(blockIdx.x / BH);
   if (tq < 0) return;
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int ln = lane & 31, h = lane >> 5;
@@ -966,6 +652,156 @@ __global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdPar
   }
 }
 
+// ------------------------------------------------------------------ fp32
+//
+// The same division of labour on the fp32 matrix cores (32x32x2, one element per lane and step): an item is 32 query rows,
+// its four wavefronts share the 64-key tiles, both operands come straight from memory, four elements of a lane with one
+// 16-byte read.  Bound by those matrix instructions (64 cycles each, 128 of them per tile at d = 64: 4 us), whose chain
+// per item this cuts to a quarter; tiles staged through LDS for four wavefronts of 32 rows, without overlap, took 62 us on
+// 24 items of 1k tokens, this takes 18.  No list, longest items first: the dispatcher balances.
+template <int D>
+__global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_fwd_f32_kernel(FwdParams p) {
+  constexpr int CH = D / 4, KS = D / 8, NB = D / 32;
+  constexpr int OP = D + 4;                          // floats between rows of the merge buffer
+  __shared__ __attribute__((aligned(16))) float sO[kSplitWaves][kSplitRows][OP];
+  __shared__ float sM[kSplitWaves][kSplitRows], sL[kSplitWaves][kSplitRows];
+  const Layer& L = p.L;
+  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
+  const int nq = p.q_cnt ? p.q_cnt[bh] : L.N;
+  const int tq = cdiv(nq, kSplitRows) - 1 - (int)(blockIdx.x / BH);
+  if (tq < 0) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int* qlist = p.q_idx ? p.q_idx + (long long)bh * L.N : nullptr;       // null: all rows, all keys (dense baseline)
+  const int* qvis = p.qvis ? p.qvis + (long long)bh * L.N : nullptr;
+  auto row_of = [&](int pos) { return qlist ? qlist[pos] : pos; };
+  auto visible = [&](int pos) { return qvis ? qvis[pos] : (L.causal ? pos + 1 : L.N); };
+  const int pos_first = tq * kSplitRows, pos_last = min(pos_first + kSplitRows, nq) - 1;
+  const int n_full_tiles = visible(pos_first) / kTileN, ntiles = cdiv(visible(pos_last), kTileN);
+  const int pos_c = min(pos_first + ln, nq - 1);
+  const int qvisible = visible(pos_c) - 4 * h;
+  const float* qhead = static_cast<const float*>(p.Q) + b * L.qs[0] + i * L.qs[1];
+  const float* qrow = qhead + (long long)row_of(pos_c) * L.qs[2];
+  f32x4 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const f32x4*>(qrow + ks * 8 + h * 4);
+  const int bhx = p.per_q_head ? bh : b * L.Hkv + g;
+  const float* kp = static_cast<const float*>(p.Kp) + (long long)bhx * p.npad * D + lane * 4;
+  const float* vp = static_cast<const float*>(p.Vp) + (long long)bhx * p.npad * D + lane * 4;
+  f32x4 kf[2][KS];
+  auto load_k = [&](int t) {
+    const float* k = kp + (long long)t * kTileN * D;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[kb][ks] = *reinterpret_cast<const f32x4*>(k + (kb * KS + ks) * 256);
+  };
+  f32x16 o[NB];
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  if (wave < ntiles) load_k(wave);
+  for (int t = wave; t < ntiles; t += kSplitWaves) {
+    f32x4 vf[2][4][NB];
+    const float* v = vp + (long long)t * kTileN * D;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+        for (int db = 0; db < NB; ++db) vf[kb][q4][db] = *reinterpret_cast<const f32x4*>(v + ((kb * 4 + q4) * NB + db) * 256);
+    f32x16 s[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kb][ks][e], qf[ks][e], s[kb], 0, 0, 0);
+    if (t + kSplitWaves < ntiles) load_k(t + kSplitWaves);
+    if (t >= n_full_tiles) {
+      const int rel = qvisible - t * kTileN;         // keys of this tile at positions >= rel are hidden (pad rows too)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb * 32 + 8 * (r >> 2) + (r & 3) >= rel) s[kb][r] = -INFINITY;
+    }
+    float m = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, s[kb][r]);
+    m = fmaxf(m_run, pair_max(m));
+    const float m_ref = m == -INFINITY ? 0.f : m, mc = m_ref * c2;
+    if (__any(m > m_run)) {
+      const float alpha = fast_exp2((m_run - m_ref) * c2);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < NB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      m_run = m;
+    }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[kb][r] = fast_exp2(fmaf(s[kb][r], c2, -mc));
+        l_run += s[kb][r];
+      }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[kb][r >> 2][db][r & 3], s[kb][r], o[db], 0, 0, 0);
+  }
+
+  // merge the wavefronts in their order
+  const float l_own = pair_sum(l_run);
+  if (h == 0) {
+    sM[wave][ln] = m_run;
+    sL[wave][ln] = l_own;
+  }
+  __syncthreads();
+  float top = sM[0][ln];
+#pragma unroll
+  for (int w = 1; w < kSplitWaves; ++w) top = fmaxf(top, sM[w][ln]);
+  const float ref = top == -INFINITY ? 0.f : top;
+  float total = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) total += sL[w][ln] * fast_exp2((sM[w][ln] - ref) * c2);
+  const float mine = total > 0.f ? fast_exp2((m_run - ref) * c2) / total : 0.f;
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 v = {o[db][q4 * 4] * mine, o[db][q4 * 4 + 1] * mine, o[db][q4 * 4 + 2] * mine, o[db][q4 * 4 + 3] * mine};
+      *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
+    }
+  if (threadIdx.x < kSplitRows && pos_first + (int)threadIdx.x < nq)
+    p.lse[(long long)bh * L.N + row_of(pos_first + threadIdx.x)] = total > 0.f ? (top * c2 + log2f(total)) * kLn2 : -INFINITY;
+  __syncthreads();
+  float* ohead = static_cast<float*>(p.O) + b * L.qs[0] + i * L.qs[1];
+#pragma unroll
+  for (int c = threadIdx.x; c < kSplitRows * CH; c += kSplitThreads) {
+    const int row = c / CH, d = c % CH * 4;
+    if (pos_first + row >= nq) continue;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
+    *reinterpret_cast<f32x4*>(ohead + (long long)row_of(pos_first + row) * L.qs[2] + d) = x;
+  }
+}
+
 // Which of the two bf16 kernels: the bytes an item streams alone make the split kernel the slower one once the work per
 // CU outweighs the length of a chain.  Whole attention call in us, (heads, d) N: split / the other, a third of the
 // queries and half of the keys kept: (28, 128) 1072: 30 / 55, 3101: 60 / 83, 4096: 85 / 100, 6000: 134 / 129,
@@ -1001,14 +837,16 @@ FwdWs carve_fwd(Arena& a, const Layer& L, int dtype, int heads, int npad, bool s
   w.Vp = a.take<unsigned char>(rows * L.D * es);
   w.kidx = a.take<int>(rows);
   w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
-  w.qvis = (sparse && dtype == OMNI_BF16) ? a.take<int>((size_t)L.B * L.Hq * L.N) : nullptr;
+  w.qvis = sparse ? a.take<int>((size_t)L.B * L.Hq * L.N) : nullptr;
   return w;
 }
+
+unsigned split_grid(const Layer& L) { return (unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, kSplitRows); }
 
 template <int D, bool TILEMAP>
 int launch_split(const FwdParams& p, hipStream_t st) {
   ProfScope prof__(kProfAttnFwd, st);
-  hipLaunchKernelGGL((attn_fwd_split_kernel<D, TILEMAP>), dim3(p.L.B * p.L.Hq, cdiv(p.L.N, kSplitRows)), dim3(kSplitThreads),
+  hipLaunchKernelGGL((attn_fwd_split_kernel<D, TILEMAP>), dim3(split_grid(p.L)), dim3(kSplitThreads),
                      0, st, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
@@ -1046,10 +884,9 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const bool split = sparse && sizeof(T) == 2 && split_pays(L);
   {
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
-    // bf16: K natural + V k-packed and converted to f16; fp32: both natural
-    int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp,
-                         dt == OMNI_BF16 ? nullptr : w.Vp, nullptr, dt == OMNI_BF16 ? w.Vp : nullptr, w.kidx, st,
-                         sparse ? sel : nullptr, split);
+    // K natural or in fragment order, V k-packed (bf16: converted to f16)
+    int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp, nullptr, nullptr,
+                         w.Vp, w.kidx, st, sparse ? sel : nullptr, split || sizeof(T) == 4);
     if (rc != OMNI_OK) return rc;
   }
   FwdParams p;
@@ -1072,33 +909,31 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_map = nullptr;
   p.tile_stride = 0;
   constexpr bool kFast = sizeof(T) == 2;
-  const int tile_m = kFast ? kFastTileM : kTileM;
-  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
-  int rc;
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, kFastTileM);
+  int rc = OMNI_OK;
+  rc = check_work_list(L, kFast ? kFastTileM : kTileM);
+  if (rc != OMNI_OK) return rc;
   if (sparse) {
-    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m,
-                        split ? nullptr : w.sched, st);
+    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, kFastTileM,
+                        kFast && !split ? w.sched : nullptr, st);
     if (rc != OMNI_OK) return rc;
-    if constexpr (kFast) {
-      if (split) return launch_split<D, false>(p, st);
-    }
-    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2 (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
+  }
+  if constexpr (kFast) {
+    if (split) return launch_split<D, false>(p, st);
+    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
+    // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
     // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
     // costs (25.7 -> 25.9 ms dense).
-    rc = run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1);
-  } else {
-    rc = run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
+    rc = sparse ? run_order(L, q_cnt, kFastTileM, w.sched, st, kSchedQueues)
+                : run_schedule(L, q_cnt, budget, b_cap, kFastTileM, w.sched, st);
+    if (rc != OMNI_OK) return rc;
   }
-  if (rc != OMNI_OK) return rc;
-  {
-    ProfScope prof__(kProfAttnFwd, st);
-    if constexpr (kFast) {
-      hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, false>), dim3(persistent_grid() / 2), dim3(kFastThreads), 0, st, p);
-    } else {
-      hipLaunchKernelGGL((attn_fwd_kernel<T, D>), dim3(persistent_grid()), dim3(kThreads), 0, st, p);
-    }
-    OMNI_LAUNCH_CHECK();
-  }
+  ProfScope prof__(kProfAttnFwd, st);
+  if constexpr (kFast)
+    hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, false>), dim3(persistent_grid() / 2), dim3(kFastThreads), 0, st, p);
+  else
+    hipLaunchKernelGGL((attn_fwd_f32_kernel<D>), dim3(split_grid(L)), dim3(kSplitThreads), 0, st, p);
+  OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
 

@@ -6,10 +6,12 @@
 // request: "natural" [slot][d], and "k-packed" [16-slot group][half h][d][8 slots]
 // with slot(group,h,j) = 16 group + 8 (j/4) + 4 h + j%4 -- the order in which a
 // 32x32 MFMA accumulator holds its rows -- so that the operand of a GEMM that
-// contracts over the slots is one 16-byte LDS read per lane.  fp32 inputs only
-// use the natural layout (the fp32 MFMA takes one element per lane).  The k-packed
+// contracts over the slots is one 16-byte read per lane.  The k-packed
 // V (the forward's operand; the backward does not use it) is written in f16: the
-// forward multiplies its f16-rounded weights with it.
+// forward multiplies its f16-rounded weights with it.  fp32 inputs: "fragment order"
+// for natural rows ([32-row block][8-wide k step][lane] of 16 bytes, lane = 32 h + row),
+// and k-packed [32-slot block][q4][d / 32][h][d % 32][4 slots], slot = 8 q4 + 4 h + e: the
+// fp32 MFMA takes one element per lane, four of them arrive with one 16-byte read.
 //
 // pack_q: for the backward pass, the kept rows of Q and dO in the k-packed
 // layout (contraction over queries) and, for bf16, also as contiguous natural
@@ -53,6 +55,17 @@ __device__ __forceinline__ void transpose8x8_store(const u32x4 (&in)[8], u16* ds
     }
     u32x4 o = {w[0], w[1], w[2], w[3]};
     *reinterpret_cast<u32x4*>(dst + e * 8) = o;
+  }
+}
+
+// 4 rows x 4 floats -> 4 columns x 4 rows in the fp32 k-packed order; dst: the 32-slot block, unit = q4 * 2 + h
+template <int D>
+__device__ __forceinline__ void transpose4x4_store(const u32x4 (&in)[4], float* dst, int q4, int h, int dc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int d = dc * 4 + e;
+    const u32x4 o = {in[0][e], in[1][e], in[2][e], in[3][e]};
+    *reinterpret_cast<u32x4*>(dst + (((q4 * (D / 32) + d / 32) * 2 + h) * 32 + d % 32) * 4) = o;
   }
 }
 
@@ -168,14 +181,17 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
   const T* vbase = V + b * L.ks[0] + g * L.ks[1];
   const long long tile_off = ((long long)bhx * npad + tile * kTileN) * D;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  if (kBf16 && k_frag) {
+  if (k_frag) {
     // consecutive threads take consecutive rows of one 16-byte column: the writes are contiguous, the reads meet in L1
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
       const int r32 = c & 31, chunk = c / 32 % CPR, row = c / (32 * CPR) * 32 + r32;
       const int id = sIdx[row];
-      u32x4 v = zero;
-      if (id != kPadKeyIndex) v = *reinterpret_cast<const u32x4*>(kbase + (long long)id * L.ks[2] + chunk * E);
-      *reinterpret_cast<u32x4*>(Kn + tile_off + c * E) = v;
+      const long long src = (long long)id * L.ks[2] + chunk * E;
+      u32x4 k = zero, v = zero;
+      if (Kn && id != kPadKeyIndex) k = *reinterpret_cast<const u32x4*>(kbase + src);
+      if (Vn && id != kPadKeyIndex) v = *reinterpret_cast<const u32x4*>(vbase + src);
+      if (Kn) *reinterpret_cast<u32x4*>(Kn + tile_off + c * E) = k;
+      if (Vn) *reinterpret_cast<u32x4*>(Vn + tile_off + c * E) = v;
     }
   } else if (Kn || Vn) {
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
@@ -213,6 +229,23 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
         if (which) in[j] = bf16x8_to_f16x8(in[j]);     // the forward multiplies its weights and V in f16
       }
       transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
+    }
+  } else {
+    // work item = (tensor, 4-slot group, 4-wide d chunk)
+    constexpr int kItems = (kTileN / 4) * (D / 4);
+    for (int it0 = threadIdx.x; it0 < 2 * kItems; it0 += kThreads) {
+      const int which = it0 / kItems, dc = it0 % (D / 4), grp = it0 % kItems / (D / 4);
+      T* dst_t = which ? Vt : Kt;
+      if (!dst_t) continue;
+      const T* src = which ? vbase : kbase;
+      u32x4 in[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int id = sIdx[grp * 4 + j];
+        in[j] = zero;
+        if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + dc * 4);
+      }
+      transpose4x4_store<D>(in, reinterpret_cast<float*>(dst_t) + tile_off + grp / 8 * 32 * D, grp / 2 % 4, grp & 1, dc);
     }
   }
 }
@@ -258,8 +291,9 @@ __global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ 
 #pragma unroll
       for (int e = 0; e < E; ++e) dot = fmaf(av[e], gv[e], dot);
     }
-    if (Qn) {                                   // natural packed copies (pad rows zero)
-      const long long o = ((long long)bh * nqpad + tile * 64 + r) * D + c * E;
+    if (Qn) {                                   // packed copies, natural or in fragment order (pad rows zero)
+      const long long o = kBf16 ? ((long long)bh * nqpad + tile * 64 + r) * D + c * E
+                                : ((long long)bh * nqpad + tile * 64 + r / 32 * 32) * D + (c * 32 + r % 32) * E;
       *reinterpret_cast<u32x4*>(Qn + o) = qc;
       *reinterpret_cast<u32x4*>(dOn + o) = g;
     }
@@ -295,6 +329,23 @@ __global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ 
         if (row >= 0) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)row * L.qs[2] + dc * 8);
       }
       transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
+    }
+  } else {
+    constexpr int kItems = (64 / 4) * (D / 4);
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const long long tile_off = ((long long)bh * nqpad + tile * 64) * D;
+    for (int it0 = threadIdx.x; it0 < 2 * kItems; it0 += kThreads) {
+      const int which = it0 / kItems, dc = it0 % (D / 4), grp = it0 % kItems / (D / 4);
+      const T* src = (which ? dO : Q) + head_off;
+      T* dst_t = which ? dOt : Qt;
+      u32x4 in[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = sIdx[grp * 4 + j];
+        in[j] = zero;
+        if (row >= 0) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)row * L.qs[2] + dc * 4);
+      }
+      transpose4x4_store<D>(in, reinterpret_cast<float*>(dst_t) + tile_off + grp / 8 * 32 * D, grp / 2 % 4, grp & 1, dc);
     }
   }
 }
@@ -347,9 +398,9 @@ int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per
   }
   if (L.D == 128)
     return launch_pack_kv<float, 128>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                      nullptr, nullptr, kidx, st, sel, k_frag);
+                                      Kt, Vt, kidx, st, sel, k_frag);
   return launch_pack_kv<float, 64>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                   nullptr, nullptr, kidx, st, sel, k_frag);
+                                   Kt, Vt, kidx, st, sel, k_frag);
 }
 
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
@@ -361,8 +412,8 @@ int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const vo
     return launch_pack_q<u16, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
   }
   if (L.D == 128)
-    return launch_pack_q<float, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, nullptr, nullptr, lse2c, deltac, st);
-  return launch_pack_q<float, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, nullptr, nullptr, lse2c, deltac, st);
+    return launch_pack_q<float, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
+  return launch_pack_q<float, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
 }
 
 }  // namespace omni

@@ -61,6 +61,7 @@ struct Bounds {
   int tile_m;                    // rows per work item
   int* sched;                    // the items of the work list and their costs (not their order)
 };
+int check_work_list(const Layer& L, int tile_m);     // the items' fields are 16 bits wide: error if they do not fit
 int run_bounds(const Layer& L, const Bounds& p, hipStream_t st);
 
 // The order of the work list from its items: queues = 1 (one longest-first list) or kSchedQueues (one list per XCD, whole

@@ -268,10 +268,13 @@ __global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __rest
 
 }  // namespace
 
+int check_work_list(const Layer& L, int tile_m) {
+  if (L.B * L.Hq >= 65536 || cdiv(L.N, tile_m) >= 65536) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
+  return OMNI_OK;
+}
+
 int run_bounds(const Layer& L, const Bounds& p, hipStream_t st) {
   const int BH = L.B * L.Hq, n = p.kfirst ? max(L.N, p.npad) : L.N;
-  if (p.sched && (BH >= 65536 || cdiv(L.N, p.tile_m) >= 65536))
-    OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
   hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH), dim3(kThreads), 0, st, L, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
@@ -288,7 +291,6 @@ int run_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, hipStrea
 
 int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, int* sched, hipStream_t st) {
   const int BH = L.B * L.Hq;
-  if (BH >= 65536 || cdiv(L.N, tile_m) >= 65536) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "work list: too many heads or tiles");
   hipLaunchKernelGGL(sched_estimate_kernel, dim3(BH), dim3(64), 0, st, q_cnt, budget, b_cap, L, tile_m, sched);
   OMNI_LAUNCH_CHECK();
   return run_order(L, q_cnt, tile_m, sched, st);
