@@ -61,9 +61,10 @@ struct BwdParams {
   const int* kfirst;    // [B*Hq, npad] first kept-query position that sees a packed key
   int head_group;       // heads per dispatch group of the key kernels
   int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernels)
-  int split_len;        // query tiles per split, at least
+  int split_len;        // query tiles per split, at least (bf16: at most, see key_list_kernel)
+  int key_wgs;          // workgroups that share the key kernels' items
   long long plane;      // floats between the partial-gradient planes of two splits
-  int* klist;           // work list of the key kernels: [0], [1] counters (dV, dK kernel), [2] items, [4..] items
+  int* klist;           // work list of the key kernels: [0], [1] counters (dV, dK kernel), [2] items, [3] split length, [4..] items; null: fp32
   // In-place block lists (TILEMAP kernels): Kn, Vn, Kt hold every KV head once, in token order ([B*Hkv, npad_kv, D]),
   // and tile t of a head's key list is tile tile_map[bh * tile_stride + t] of its KV head's copy.
   const int* tile_map;
@@ -508,58 +509,63 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
 
 // Work items of the key kernels: (head, key tile, split), in dispatch order -- heads in groups of p.head_group,
 // inside a group key tile by key tile (the first key tiles, seen by the most queries, first), the splits of a
-// tile side by side.  Slot i of that order decodes to an item; most slots are empty (key tiles beyond a head's
-// budget, splits a tile does not need), so one workgroup compacts the live ones into a list that the
-// persistent key kernels pull from: an empty workgroup would still wait for a whole CU's LDS.
-constexpr int kKeyListHeader = 4;
-__device__ __forceinline__ int key_slot_item(const BwdParams& p, long long i) {
+// tile side by side.  Slot i of that order is a (head, key tile); most are empty (key tiles beyond a head's
+// budget), so one workgroup lists the live ones with their splits, and the persistent key kernels pull from
+// the list: an empty workgroup would still wait for a whole CU's LDS.
+constexpr int kKeyListHeader = 4;            // counters (dV, dK kernel), items, query tiles per split
+
+// head and key tile of slot i, and how many query tiles see it (0: nothing to do)
+__device__ __forceinline__ int key_slot(const BwdParams& p, long long i, int& bh, int& ktile) {
   const Layer& L = p.L;
   const int BH = L.B * L.Hq, nkt = p.npad / kKeyTile;
-  const long long per_group = (long long)p.head_group * nkt * p.nsplit;
-  const int grp = (int)(i / per_group);
-  const int within = (int)(i % per_group);
+  const long long per_group = (long long)p.head_group * nkt;
+  const int grp = (int)(i / per_group), within = (int)(i % per_group);
   const int heads_here = min(p.head_group, BH - grp * p.head_group);
-  if (heads_here <= 0) return -1;
-  const int kts = within / heads_here, bh = grp * p.head_group + within % heads_here;
-  const int ktile = kts / p.nsplit, sp = kts % p.nsplit;
-  if (ktile >= nkt) return -1;
-  const int nkeys = min(p.budget[budget_slot(L.bph, bh / L.Hq, bh)], p.b_cap);
-  if (ktile * kKeyTile >= nkeys) return -1;
-  if (sp > 0) {
-    const int first = p.kfirst[(long long)bh * p.npad + ktile * kKeyTile];
-    if (sp >= key_tile_splits(cdiv(p.q_cnt[bh], kKeyQ) - first / kKeyQ, p.nsplit, p.split_len)) return -1;
-  }
-  return (bh << 16) | (ktile << 3) | sp;
+  if (heads_here <= 0) return 0;
+  ktile = within / heads_here;
+  bh = grp * p.head_group + within % heads_here;
+  if (ktile >= nkt) return 0;
+  if (ktile * kKeyTile >= min(p.budget[budget_slot(L.bph, bh / L.Hq, bh)], p.b_cap)) return 0;
+  return max(1, cdiv(p.q_cnt[bh], kKeyQ) - p.kfirst[(long long)bh * p.npad + ktile * kKeyTile] / kKeyQ);
 }
 
-// one workgroup of 1024 threads; stable compaction of the live slots
+// One workgroup of 1024 threads: the list, and the length of a split: a workgroup's share of all query tiles (a longer
+// chain would outlast the others), between 8 and p.split_len.  At 3k tokens, two sequences of 28 heads, the longest chain
+// is head 0's 49 query tiles while a share is 9: dK' 87 -> 44 us, dV' 63 -> 34 us.
 __global__ __launch_bounds__(1024) void key_list_kernel(BwdParams p, long long n_slots) {
   __shared__ int wave_cnt[16];
-  __shared__ int base;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) base = 0;
+  int bh, ktile, tiles = 0;
+  for (long long i = threadIdx.x; i < n_slots; i += 1024) tiles += key_slot(p, i, bh, ktile);
+  tiles = wave_sum(tiles);
+  if (lane == 0) wave_cnt[wave] = tiles;
   __syncthreads();
+  tiles = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) tiles += wave_cnt[w];
+  const int split_len = min(p.split_len, max(8, cdiv(tiles, p.key_wgs)));
+  int base = 0;
   for (long long i0 = 0; i0 < n_slots; i0 += 1024) {
     const long long i = i0 + threadIdx.x;
-    const int item = i < n_slots ? key_slot_item(p, i) : -1;
-    const unsigned long long live = __ballot(item >= 0);
-    if (lane == 0) wave_cnt[wave] = __popcll(live);
+    const int seen = i < n_slots ? key_slot(p, i, bh, ktile) : 0;
+    const int n_sp = seen ? key_tile_splits(seen, p.nsplit, split_len) : 0;
+    const int incl = (int)wave_scan((unsigned)n_sp);
     __syncthreads();
-    int before = base;
-    for (int w = 0; w < wave; ++w) before += wave_cnt[w];
-    if (item >= 0) p.klist[kKeyListHeader + before + __popcll(live & ((1ull << lane) - 1ull))] = item;
+    if (lane == 63) wave_cnt[wave] = incl;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = base;
-      for (int w = 0; w < 16; ++w) t += wave_cnt[w];
-      base = t;
+    int at = base + incl - n_sp;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      at += w < wave ? wave_cnt[w] : 0;
+      base += wave_cnt[w];
     }
-    __syncthreads();
+    for (int sp = 0; sp < n_sp; ++sp) p.klist[kKeyListHeader + at + sp] = (bh << 16) | (ktile << 3) | sp;
   }
   if (threadIdx.x == 0) {
     p.klist[0] = 0;
     p.klist[1] = 0;
     p.klist[2] = base;
+    p.klist[3] = split_len;
   }
 }
 
@@ -616,7 +622,7 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   const int n_qtiles = cdiv(nq, kKeyQ);
   const int q_first = sBound[0] / kKeyQ;                    // first query tile with an admissible pair
   const int n_all = n_qtiles - q_first;
-  const int n_sp = key_tile_splits(n_all, p.nsplit, p.split_len);
+  const int n_sp = key_tile_splits(n_all, p.nsplit, p.klist[3]);
   const int per_split = cdiv(n_all, n_sp);
   const int q_begin = q_first + sp * per_split;             // this workgroup's query tiles: [q_begin, q_begin + n)
 
@@ -856,7 +862,7 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, 
       int n_sp = 1;
       if (p.nsplit > 1) {                  // as the key kernels counted: the query tiles from the tile's first visible pair on
         const int first = p.kfirst[(long long)bh * p.npad + pos / kKeyTile * kKeyTile];
-        n_sp = key_tile_splits(cdiv(p.q_cnt[bh], kKeyQ) - first / kKeyQ, p.nsplit, p.split_len);
+        n_sp = key_tile_splits(cdiv(p.q_cnt[bh], kKeyQ) - first / kKeyQ, p.nsplit, p.klist ? p.klist[3] : p.split_len);
       }
       const long long o = ((long long)bh * p.npad + pos) * D + c * 4;
       for (int sp = 0; sp < n_sp; ++sp) {
@@ -898,9 +904,9 @@ struct BlockLists {
 
 constexpr int kKeyHeadGroup = 7;
 int g_key_split_len = kKeySplitLen;          // omni_debug_key_split_len: tests split short key tiles too
-// slots of the key kernels' dispatch order (an upper bound of the live items)
+// slots of the key kernels' dispatch order
 size_t key_list_slots(const Layer& L, int npad) {
-  return (size_t)cdiv(L.B * L.Hq, kKeyHeadGroup) * kKeyHeadGroup * (npad / kKeyTile) * kKeyMaxSplits;
+  return (size_t)cdiv(L.B * L.Hq, kKeyHeadGroup) * kKeyHeadGroup * (npad / kKeyTile);
 }
 
 // npad_kv > 0: Kn, Vn, Kt hold every KV head once ([B*Hkv, npad_kv, D], the in-place block lists) instead of one
@@ -927,7 +933,7 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.qvis = a.take<int>(BH * L.N);
   w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
-  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad));
+  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * kKeyMaxSplits);
   w.kidx_kv = a.take<int>(npad_kv > 0 ? kvrows : 4);
   w.vbudget = a.take<int>(L.B);
   w.tile_map = a.take<int>(npad_kv > 0 ? BH * cap_tiles : 4);
@@ -1009,6 +1015,8 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.split_len = sizeof(T) == 2 ? g_key_split_len : kKeySplitLenF32;
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
+  p.klist = nullptr;
+  p.key_wgs = 1;
   p.sched = w.sched;
   p.qvis = w.qvis;
   p.kfirst = w.kfirst;
@@ -1053,9 +1061,10 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
       if (L.B * L.Hq >= 32768 || npad / kKeyTile >= 8192)
         OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "key work list: too many heads or key tiles");
       p.klist = w.klist;
+      const unsigned key_wgs = (unsigned)persistent_grid() / 2;       // one workgroup per CU (its LDS ring fills it)
+      p.key_wgs = (int)key_wgs;
       hipLaunchKernelGGL(key_list_kernel, dim3(1), dim3(1024), 0, st, p, (long long)key_list_slots(L, npad));
       OMNI_LAUNCH_CHECK();
-      const unsigned key_wgs = (unsigned)persistent_grid() / 2;       // one workgroup per CU (its LDS ring fills it)
       hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 1, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
       OMNI_LAUNCH_CHECK();
       hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 0, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);

@@ -90,3 +90,27 @@ def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
             fin = torch.isfinite(m)
             assert torch.equal(torch.isfinite(lse[b, h, q]), fin)
             assert float((lse[b, h, q][fin] - m[fin]).abs().max()) <= 2e-3
+
+
+@pytest.mark.parametrize("kept", [1, 64, 513, 2049])
+def test_key_gradients_when_a_few_long_key_tiles_are_split(kept):
+    """One head keeps every query (its key tiles are shared between workgroups), the others few: dK and dV of the split
+    tiles against 64-bit sums, at counts around whole query tiles and splits."""
+    H, Hkv, N, d = 4, 1, 2304, 64
+    g = torch.Generator(device="cuda").manual_seed(kept)
+    rand = lambda h, s=1.0: (s * torch.randn(1, h, N, d, generator=g, device="cuda")).bfloat16()  # noqa: E731
+    Q, K, V, dO = rand(H), rand(Hkv), rand(Hkv), rand(H, d ** -0.5)
+    rng = np.random.default_rng(kept)
+    q_lists = [[np.arange(N)] + [np.sort(rng.choice(N, kept, replace=False)) for _ in range(H - 1)]]
+    k_lists = [[np.sort(rng.choice(N, n, replace=False)) for n in (1500, 257, 1, 700)]]
+    q_idx, q_cnt = lists_to_padded(q_lists, H, N)
+    kv_idx, budget = lists_to_padded(k_lists, H, N)
+    desc = ob.make_layer_desc(Q, K, 0, N, 0, True)
+    O, lse = ob.omni_sparse_attn_fwd_per_head(desc, Q, K, V, q_idx, q_cnt, kv_idx, budget, N)
+    got = ob.omni_sparse_attn_bwd_per_head(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, kv_idx, budget, N)
+    torch.cuda.synchronize()
+    args = [to_host(x) for x in (Q, K, V, dO)] + [q_lists, k_lists, True, d ** -0.5]
+    want = oc.sparse_attn_bwd(*args, O=to_host(O))
+    rss = oc.sparse_attn_bwd_term_rss(*args, O=to_host(O))
+    for x, w, r in zip(got, want, rss):
+        assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, "bf16", r))
