@@ -244,6 +244,22 @@ __device__ __forceinline__ U wave_scan(U v) {
   return v;
 }
 
+// Sum over the W lanes that hold a row, in the order of an exchange with lane ^ W/2, .., ^ 1.  Rows of 16 lanes rotate on
+// the vector ALU: after the step with distance d all values repeat every d lanes, so lane + d is lane ^ d.
+template <int W>
+__device__ __forceinline__ float row_lanes_sum(float v) {
+  if constexpr (W == 16) {
+    v += __uint_as_float(dpp_or_zero<0x128, 0xf>(__float_as_uint(v)));   // row_ror:8, 4, 2, 1
+    v += __uint_as_float(dpp_or_zero<0x124, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x122, 0xf>(__float_as_uint(v)));
+    v += __uint_as_float(dpp_or_zero<0x121, 0xf>(__float_as_uint(v)));
+  } else {
+#pragma unroll
+    for (int o = W / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  }
+  return v;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll

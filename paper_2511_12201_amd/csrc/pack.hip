@@ -183,6 +183,7 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
   const u32x4 zero = {0u, 0u, 0u, 0u};
   if (k_frag) {
     // consecutive threads take consecutive rows of one 16-byte column: the writes are contiguous, the reads meet in L1
+#pragma unroll                                      // all loads of a thread in flight together
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
       const int r32 = c & 31, chunk = c / 32 % CPR, row = c / (32 * CPR) * 32 + r32;
       const int id = sIdx[row];
@@ -194,6 +195,7 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
       if (Vn) *reinterpret_cast<u32x4*>(Vn + tile_off + c * E) = v;
     }
   } else if (Kn || Vn) {
+#pragma unroll
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
       const int row = c / CPR, col = (c % CPR) * E;
       const int id = sIdx[row];

@@ -17,6 +17,8 @@
 // One workgroup serves all query heads of a KV group with one K fragment; the
 // Qbar blocks of its heads arrive by global->LDS DMA, double buffered, one
 // barrier per block.  fp32 inputs use the fp32 MFMA and stage Qbar by hand.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -29,6 +31,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // bf16 terms that carry the fp32 pooled query into the bf16 matrix cores (hi + mid [+ lo])
 constexpr int kQbarTerms = 2;
+constexpr int kProbeWgs = 768;          // workgroups of a probe pass up to which a KV group's heads are dealt out
 
 // ---------------------------------------------------------------- pooling
 
@@ -59,7 +62,7 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
 #pragma unroll
     for (int e = 0; e < E; ++e) diff[e] = pk[D + c * E + e] - pk[c * E + e];
     float* out = scores + (long long)bh * L.ld;
-    constexpr int kRowsInFlight = 4;                       // loads of this many rows per lane group are issued together
+    constexpr int kRowsInFlight = 16;                      // loads of this many rows per lane group are issued together
     for (int rb = row_begin; rb < row_end; rb += RPP * kRowsInFlight) {   // uniform trip count: shuffles need every lane
       u32x4 raw[kRowsInFlight];
 #pragma unroll
@@ -82,8 +85,7 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
             dot = fmaf(v[e], diff[e], dot);
           }
         }
-#pragma unroll
-        for (int o = LPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
+        dot = row_lanes_sum<LPR>(dot);
         if (live && c == 0) out[r] = 1.0f / (1.0f + expf(-dot * L.scale));
       }
     }
@@ -325,7 +327,8 @@ __device__ __forceinline__ float half_wave_reduce_scatter(float (&v)[32], int ln
   return v[0];
 }
 
-// grid: nchunk * B*Hkv workgroups, chunk-major (the chunks of low key index see the most pooled rows: longest first).
+// grid: (nchunk * B*Hkv, pieces), chunk-major (the chunks of low key index see the most pooled rows: longest first); a
+// workgroup takes the heads [piece * per_piece, + per_piece) of its KV group.
 // PASS 1: (max, sum) of every pooled row over this workgroup's 256 keys -> part_m / part_l.
 // PASS 2: a[head, key] = sum over pooled rows of exp2(s2 - lse2w[row]).
 template <int D, int PASS>
@@ -333,7 +336,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
                                                              int nchunk, const u16* __restrict__ qsplit,
                                                              float* __restrict__ part_m, float* __restrict__ part_l,
                                                              const float* __restrict__ lse2w,
-                                                             float* __restrict__ a_out) {
+                                                             float* __restrict__ a_out, int per_piece) {
   constexpr int KB = 2;                        // 32-key blocks per wavefront
   constexpr int KPW = KB * 32, KPG = 4 * KPW;
   constexpr int CH = D / 8;                    // 16-byte chunks per row
@@ -361,8 +364,9 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
   const float c2 = L.scale * kLog2e;
   const int nrb = cdiv(nblk, 32);
   const int jb0 = L.causal ? ((chunk * KPG) / pb) / 32 : 0;
-  const int n_it = L.G * (nrb - jb0);
-  const int bh0 = b * L.Hq + g * L.G;
+  const int head0 = blockIdx.y * per_piece, heads = min(per_piece, L.G - head0);
+  const int n_it = heads * (nrb - jb0);
+  const int bh0 = b * L.Hq + g * L.G + head0;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&sQ[0][0];
   const unsigned lane_off = (unsigned)(wave * 1024 + lane * 16);
   const unsigned lse_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&sLse[0][0];
@@ -616,11 +620,17 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
   }
   if constexpr (sizeof(T) == 2) {
     const u16* Kp = static_cast<const u16*>(K);
+    // Heads of a group per workgroup: all of them share one K fragment, but a workgroup walks them one after the other,
+    // which on short sequences is the whole time (1k tokens: 20 workgroups of 7 heads).  Both passes: 32 -> 12 us
+    // there.  From 768 workgroups on (all that fit at once) a second start costs more than the balance brings (8k tokens,
+    // four sequences, 512 workgroups: 47 us undivided, 49 and 54 in two and three pieces).
     const int nwg = nchunk * L.B * L.Hkv;
+    const int per_piece = cdiv(L.G, std::max(1, std::min(L.G, kProbeWgs / nwg)));
+    const dim3 grid(nwg, cdiv(L.G, per_piece));
     {
       ProfScope prof__(kProfProbeLse, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
-                         w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr);
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), grid, dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
+                         w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr, per_piece);
       OMNI_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
@@ -628,8 +638,8 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
     OMNI_LAUNCH_CHECK();
     {
       ProfScope prof__(kProfProbeSum, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), dim3(nwg), dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
-                         (float*)nullptr, (float*)nullptr, w.lse2w, key_scores);
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), grid, dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
+                         (float*)nullptr, (float*)nullptr, w.lse2w, key_scores, per_piece);
       OMNI_LAUNCH_CHECK();
     }
     return OMNI_OK;

@@ -34,12 +34,22 @@ __global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __r
   float acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
-  for (int r = row_begin + r0; r < row_end; r += RPP) {
-    u32x4 raw = *reinterpret_cast<const u32x4*>(base + (long long)r * L.ks[2] + c * E);
-    float v[E];
-    unpack16(raw, v, (const T*)nullptr);
+  constexpr int kRowsInFlight = 8;         // loads issued together; added in ascending order of the rows
+  for (int rb = row_begin + r0; rb < row_end; rb += RPP * kRowsInFlight) {
+    u32x4 raw[kRowsInFlight];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += v[e];
+    for (int u = 0; u < kRowsInFlight; ++u) {
+      const int r = rb + u * RPP;
+      if (r < row_end) raw[u] = *reinterpret_cast<const u32x4*>(base + (long long)r * L.ks[2] + c * E);
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsInFlight; ++u) {
+      if (rb + u * RPP >= row_end) break;
+      float v[E];
+      unpack16(raw[u], v, (const T*)nullptr);
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] += v[e];
+    }
   }
 #pragma unroll
   for (int e = 0; e < E; ++e) red[r0][c * E + e] = acc[e];
@@ -109,8 +119,7 @@ __global__ __launch_bounds__(kThreads) void score_queries_kernel(const T* __rest
 #pragma unroll
       for (int e = 0; e < E; ++e) dot = fmaf(v[e], diff[e], dot);
     }
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
+    dot = row_lanes_sum<LPR>(dot);
     if (live && c == 0) out[r] = 1.0f / (1.0f + expf(-dot * L.scale));
   }
 }
