@@ -70,6 +70,7 @@ struct BwdParams {
   const int* tile_map;
   int tile_stride;
   int npad_kv;          // rows per (head) buffer of Kn / Vn / Kt: npad for the gathered copies
+  int k_frag;           // bf16: Kn, Vn in fragment order instead of row by row
 };
 
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int r0) {
@@ -494,6 +495,129 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
   }  // work-item loop
 }
 
+// ------------------------------------------------------------------ dQ, bf16, short sequences
+//
+// As the forward on short sequences (attn_fwd.hip): an item is 32 kept queries, its four wavefronts share the 32-key
+// blocks, operands straight from memory in fragment order, partial sums added in wavefront order; no work list.  A 256-row
+// item walks its tiles one after the other at 1.5 to 2 us each, and short sequences have a few dozen of them.  At d = 128
+// one workgroup fits a CU (304 registers); a layout for two (K^T in halves, the sums over the Q and dO rows) measured the
+// same within 4 % either way.
+constexpr int kSplitWaves = 4;
+constexpr int kSplitThreads = kSplitWaves * 64;
+// Which of the two dQ kernels, by the shape only (the gathered and the in-place lists of a layer take the same one).  Forward
+// and backward of a layer in us, (heads, d) N: split / the other, a third of the queries and half of the keys kept:
+// (28, 128) 1072: 149 / 170, 2048: 203 / 224, 4096 (6.0e10): 346 / 347, (56, 64) 3101 (3.4e10): 203 / 220, (28, 64) 6000
+// (6.5e10): 363 / 375, (8, 128) 4096 (1.7e10): 227 / 259, 7500 (5.8e10): 457 / 442.
+constexpr double kSplitWork = 4.0e10;
+
+// grid: cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first
+template <int D, bool TILEMAP>
+__global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_split_kernel(BwdParams p) {
+  typedef u16 T;
+  constexpr int CH = D / 8, KS = D / 16, NB = D / 32;
+  __shared__ __attribute__((aligned(16))) unsigned char sQ[32 * D * 2], sG[32 * D * 2];
+  __shared__ __attribute__((aligned(16))) float sO[kSplitWaves][32][D + 4];
+  const Layer& L = p.L;
+  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq;
+  const int nq = p.q_cnt[bh];
+  const int tq = cdiv(nq, 32) - 1 - (int)(blockIdx.x / BH);
+  if (tq < 0) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int* qlist = p.q_idx + (long long)bh * L.N;
+  const int* qvis = p.qvis + (long long)bh * L.N;
+  const long long qo = (long long)bh * p.nqpad + tq * 32;
+  const int qvisible = qvis[min(tq * 32 + ln, nq - 1)] - 4 * h;
+  const int n_full = qvis[tq * 32] / 32, nblocks = cdiv(qvis[min(tq * 32 + 31, nq - 1)], 32);
+  const float lse = p.lse2c[qo + ln], delta = p.deltac[qo + ln];
+#pragma unroll
+  for (int c = threadIdx.x; c < 32 * CH; c += kSplitThreads) {
+    const int row = c / CH, chunk = c % CH, at = (row * CH + (chunk ^ (row % CH))) * 16;
+    *reinterpret_cast<u32x4*>(sQ + at) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.Qn) + (qo + row) * D + chunk * 8);
+    *reinterpret_cast<u32x4*>(sG + at) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.dOn) + (qo + row) * D + chunk * 8);
+  }
+  const int bhx = TILEMAP ? b * L.Hkv + i / L.G : bh;
+  const long long head = (long long)bhx * p.npad_kv * D;
+  const T *kn = static_cast<const T*>(p.Kn) + head + lane * 8, *vn = static_cast<const T*>(p.Vn) + head + lane * 8;
+  const T* kt = static_cast<const T*>(p.Kt) + head + (h * D + ln) * 8;
+  auto block_off = [&](int t) {
+    if (!TILEMAP) return (long long)t * 32 * D;
+    return (long long)(__builtin_amdgcn_readfirstlane(p.tile_map[(long long)bh * p.tile_stride + t / 2]) * 2 + t % 2) * 32 * D;
+  };
+  bf16x8 kf[KS], vf[KS];
+  auto load_kv = [&](int t) {
+    const long long o = block_off(t);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      kf[ks] = *reinterpret_cast<const bf16x8*>(kn + o + ks * 512);
+      vf[ks] = *reinterpret_cast<const bf16x8*>(vn + o + ks * 512);
+    }
+  };
+  f32x16 dq[NB];
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+  if (wave < nblocks) load_kv(wave);
+  __syncthreads();
+  for (int t = wave; t < nblocks; t += kSplitWaves) {
+    bf16x8 ktf[2][NB];
+    const T* ktb = kt + block_off(t);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int db = 0; db < NB; ++db) ktf[u][db] = *reinterpret_cast<const bf16x8*>(ktb + (u * 2 * D + db * 32) * 8);
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f, dp[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int at = (ln * CH + ((2 * ks + h) ^ (ln % CH))) * 16;
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], *reinterpret_cast<const bf16x8*>(sQ + at), s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], *reinterpret_cast<const bf16x8*>(sG + at), dp, 0, 0, 0);
+    }
+    if (t + kSplitWaves < nblocks) load_kv(t + kSplitWaves);
+    const bool masked = t >= n_full;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float pv = fast_exp2(fmaf(s[r], c2, -lse));
+      if (masked && t * 32 + 8 * (r >> 2) + (r & 3) >= qvisible) pv = 0.f;
+      dp[r] = pv * (dp[r] - delta);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bf16x8 ds = pack8(dp, u * 8);
+#pragma unroll
+      for (int db = 0; db < NB; ++db) dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[u][db], ds, dq[db], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int db = 0; db < NB; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 v = {dq[db][q4 * 4], dq[db][q4 * 4 + 1], dq[db][q4 * 4 + 2], dq[db][q4 * 4 + 3]};
+      *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
+    }
+  __syncthreads();
+  T* out = static_cast<T*>(p.dQ) + b * L.qs[0] + i * L.qs[1];
+#pragma unroll
+  for (int c = threadIdx.x; c < 32 * CH; c += kSplitThreads) {
+    const int row = c / CH, d = c % CH * 8;
+    if (tq * 32 + row >= nq) continue;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+      x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
+      y += *reinterpret_cast<const f32x4*>(&sO[w][row][d + 4]);
+    }
+    x *= L.scale;
+    y *= L.scale;
+    const u32x4 o = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    *reinterpret_cast<u32x4*>(out + (long long)qlist[tq * 32 + row] * L.qs[2] + d) = o;
+  }
+}
+
 // ------------------------------------------------------------------ dK' and dV', bf16 fast path
 //
 // Two kernels of the same shape as the dQ kernel with the roles of keys and queries swapped: a workgroup
@@ -633,13 +757,16 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
     const int src = t < p.tile_stride ? p.tile_map[(long long)bh * p.tile_stride + t] : 0;
     kv_row = (long long)(b * L.Hkv + (bh % L.Hq) / L.G) * p.npad_kv + (long long)src * kTileN + slot % kTileN;
   }
-  const T* krow = static_cast<const T*>(p.Kn) + kv_row * D;
-  const T* vrow = static_cast<const T*>(p.Vn) + kv_row * D;
+  // natural rows, or (short sequences) the 32-row blocks of the fragment order
+  const long long kv_at = p.k_frag ? (kv_row & ~31ll) * D + lane * 8 : kv_row * D + h * 8;
+  const int kv_step = p.k_frag ? 512 : 16;
+  const T* krow = static_cast<const T*>(p.Kn) + kv_at;
+  const T* vrow = static_cast<const T*>(p.Vn) + kv_at;
   bf16x8 kf[D / 16], vf[MODE == 0 ? D / 16 : 1];
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) {
-    kf[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * 16 + h * 8);
-    if (MODE == 0) vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * 16 + h * 8);
+    kf[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * kv_step);
+    if (MODE == 0) vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * kv_step);
   }
   // finish every ordinary load here: a compiler-placed wait inside the tile loop would drain the ring
 #pragma unroll
@@ -968,10 +1095,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int npad = bwd_npad(cap_keys), nqpad = bwd_nqpad(L);
   const int npad_kv = BLOCKS ? bwd_npad_kv(L) : 0;
   BwdWs w = carve_bwd(a, L, dt, npad, nqpad, npad_kv, cap_keys / kTileN);
+  const bool split = sizeof(T) == 2 && attention_work(L) <= kSplitWork;
   int rc;
   if constexpr (BLOCKS) {
     // K, V (natural) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
-    rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st);
+    rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st,
+                     nullptr, split);
     if (rc != OMNI_OK) return rc;
     // token lists of the selected blocks (causal bounds, the reduction's slot map), rows npad apart, and the tile map
     rc = run_expand_blocks(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, w.kidx, w.vbudget, npad, st);
@@ -983,7 +1112,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     b_cap = npad;                             // the lists' row pitch; their lengths are in vbudget
   } else {
     rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, w.Kt, nullptr, w.kidx, st,
-                     nullptr, dt == OMNI_F32);
+                     nullptr, split || dt == OMNI_F32);
     if (rc != OMNI_OK) return rc;
   }
   rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, w.Qn, w.dOn, w.lse2c,
@@ -1016,6 +1145,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
   p.klist = nullptr;
+  p.k_frag = split;
   p.key_wgs = 1;
   p.sched = w.sched;
   p.qvis = w.qvis;
@@ -1041,12 +1171,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     bn.X = dQ;
     bn.elem_bytes = sizeof(T);
     bn.tile_m = kDqTileM;
-    bn.sched = kFast ? w.sched : nullptr;
+    bn.sched = kFast && !split ? w.sched : nullptr;
     rc = run_bounds(L, bn, st);
     if (rc != OMNI_OK) return rc;
   }
   p.order_off = sched_order_off(L.B * L.Hq, L.N, kDqTileM);
-  if constexpr (kFast) {
+  if (kFast && !split) {
     rc = run_order(L, q_cnt, kDqTileM, w.sched, st);
     if (rc != OMNI_OK) return rc;
   }
@@ -1077,9 +1207,13 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   }
   {
     ProfScope prof__(kProfBwdDq, st);
-    if constexpr (kFast)
-      hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
-    else
+    if constexpr (kFast) {
+      if (split)
+        hipLaunchKernelGGL((attn_bwd_dq_split_kernel<D, BLOCKS>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)),
+                           dim3(kSplitThreads), 0, st, p);
+      else
+        hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
+    } else
       hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)), dim3(kF32Threads<D>),
                          0, st, p);
     OMNI_LAUNCH_CHECK();

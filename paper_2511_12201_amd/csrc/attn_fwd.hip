@@ -808,9 +808,7 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_fwd_f32_k
 // (28, 64) 4096: 53 / 78, 8192: 122 / 119, (8, 128) 6000: 85 / 110, 8192: 139 / 137, (8, 64) 8192: 76 / 104,
 // 12000: 140 / 140; not causal (28, 128) 3101: 81 / 85.  The line lies below all crossings; it looks at the shape only, so
 // that the gathered and the in-place lists of the same layer take the same kernel.
-bool split_pays(const Layer& L) {
-  return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0) <= 6.5e10;
-}
+constexpr double kSplitWork = 6.5e10;
 
 // Rows of a head's packed K/V buffer: whole tiles, and never a multiple of 4096 rows -- with a power-of-two
 // stride between the heads, workgroups that stream different heads at the same tile index (all of them start
@@ -881,7 +879,7 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int heads = sparse ? L.Hq : L.Hkv;
   const int npad = fwd_npad(sparse ? b_cap : L.N);
   FwdWs w = carve_fwd(a, L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, heads, npad, sparse);
-  const bool split = sparse && sizeof(T) == 2 && split_pays(L);
+  const bool split = sparse && sizeof(T) == 2 && attention_work(L) <= kSplitWork;
   {
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
     // K natural or in fragment order, V k-packed (bf16: converted to f16)
@@ -982,7 +980,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   BlockFwdWs w = carve_block_fwd(a, L, cap_keys);
   const int npad = fwd_npad(L.N);
   // K and V of every KV head once, in the kernel's tile layouts, in token order: shared by the heads of a group
-  const bool split = split_pays(L);
+  const bool split = attention_work(L) <= kSplitWork;
   int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
                        w.f.kidx, st, nullptr, split);
   if (rc != OMNI_OK) return rc;

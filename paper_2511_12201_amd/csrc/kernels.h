@@ -67,6 +67,8 @@ int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const vo
                float* deltac, hipStream_t st);
 
 // attn_fwd.hip
+// products of the dense attention of a layer: what the rules between kernels for short and long sequences look at
+inline double attention_work(const Layer& L) { return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0); }
 size_t attn_fwd_ws(const Layer& L, int dtype, int b_cap, bool sparse);
 // sel not null: kv_idx is an output, formed from *sel by the packing kernel (sparse only)
 int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const void* V, const int* q_idx,

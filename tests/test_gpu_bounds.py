@@ -7,7 +7,7 @@ import torch
 from oracle import omni_oracle as oc
 from paper_2511_12201_amd import binding as ob
 from paper_2511_12201_amd import synth
-from tests.helpers import grad_bar, lists_to_padded, to_device, to_host
+from tests.helpers import GRAD_RSS, bf16_ulp, grad_bar, lists_to_padded, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -90,6 +90,58 @@ def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
             fin = torch.isfinite(m)
             assert torch.equal(torch.isfinite(lse[b, h, q]), fin)
             assert float((lse[b, h, q][fin] - m[fin]).abs().max()) <= 2e-3
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal):
+    """Shapes just below and just above the lines between the dQ kernels (4.0e10) and the forward kernels (6.5e10; the
+    backward takes each forward's output): block lists in place give the bits of their token lists, and the gradients of
+    the first and the last sequence are those of 64-bit sums over the listed pairs."""
+    H, Hkv, B, block = 16, 1, 4, 64
+    for line in (4.0e10, 6.5e10):
+        N0 = int((line / (B * H * d * (1 if causal else 2))) ** 0.5) // block * block
+        for N in (N0, N0 + block):
+            rng = np.random.default_rng(N + d)
+            g = torch.Generator(device="cuda").manual_seed(N)
+            rand = lambda h, s=1.0: (s * torch.randn(B, h, N, d, generator=g, device="cuda")).bfloat16()  # noqa: E731
+            Q, K, V, dO = rand(H), rand(Hkv), rand(Hkv), rand(H, d ** -0.5)
+            desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
+            nb, nsel = N // block, N // block // 3
+            blocks = [[np.sort(rng.choice(nb, nsel, replace=False)) for _ in range(H)] for _ in range(B)]
+            rows = [[np.sort(rng.choice(N, (N, N // 5, 33, 31)[h % 4], replace=False)) for h in range(H)] for _ in range(B)]
+            q_idx, q_cnt = lists_to_padded(rows, H, N)
+            blk_idx, _ = lists_to_padded(blocks, H, nb)
+            blk_budget = torch.full((B,), nsel, dtype=torch.int32, device="cuda")
+            kv_idx, budget = ob.omni_expand_blocks(desc, blk_idx, blk_budget, block)
+            O, lse = ob.omni_block_attn_fwd(desc, Q, K, V, q_idx, q_cnt, blk_idx, blk_budget, block)
+            O2, lse2 = ob.omni_sparse_attn_fwd(desc, Q, K, V, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
+            assert torch.equal(O, O2) and torch.equal(lse, lse2)
+            got = ob.omni_block_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, blk_idx, blk_budget, block)
+            got2 = ob.omni_sparse_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
+            for x, y in zip(got, got2):
+                assert torch.equal(x, y)
+            for b in (0, B - 1):
+                k64, v64 = K[b, 0].double(), V[b, 0].double()
+                want = [torch.zeros(H, N, d, dtype=torch.float64, device="cuda")] + [torch.zeros_like(k64) for _ in range(2)]
+                rss = [torch.zeros_like(x) for x in want]
+                for h in range(H):
+                    q = torch.from_numpy(rows[b][h]).cuda()
+                    k = (torch.from_numpy(blocks[b][h]).cuda()[:, None] * block + torch.arange(block, device="cuda")).flatten()
+                    z = Q[b, h, q].double() @ k64[k].T * d ** -0.5
+                    if causal:
+                        z = z.masked_fill(k[None] > q[:, None], -float("inf"))
+                    P = torch.nan_to_num(torch.softmax(z, -1))
+                    go = dO[b, h, q].double()
+                    dS = P * (go @ v64[k].T - (go * O[b, h, q].double()).sum(-1, keepdim=True)) * d ** -0.5
+                    for out, f in ((want, lambda x: x), (rss, torch.square)):
+                        out[0][h, q] = f(dS) @ f(k64[k])
+                        out[1][k] += f(dS).T @ f(Q[b, h, q].double())
+                        out[2][k] += f(P).T @ f(go)
+                for x, w, r in zip((got[0][b], got[1][b, 0], got[2][b, 0]), want, rss):
+                    ulp = torch.from_numpy(bf16_ulp(w.cpu().numpy())).cuda()
+                    bar = torch.clamp(GRAD_RSS * r.sqrt() + 0.5 * ulp, min=2e-2)      # grad_bar
+                    assert bool(((x.double() - w).abs() <= bar).all())
 
 
 @pytest.mark.parametrize("kept", [1, 64, 513, 2049])
