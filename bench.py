@@ -224,9 +224,8 @@ def main():
                                           "frac": round(pool_bytes / kern["pool_q"] / 1e6 / PEAK_HBM_GBS, 4)}
 
     if not args.no_extras:
-        # the same step through omni_sparse_prefill (key lists formed inside the attention's gather: one launch and one
-        # pass over the lists fewer), outputs bit-identical; interleaved with the two-call step so that both see the
-        # same clocks
+        # the same step through omni_sparse_prefill, outputs bit-identical; interleaved with the two-call step so that
+        # both see the same clocks
         O1, lse1 = torch.empty_like(O), torch.empty_like(lse)
 
         def one_call():

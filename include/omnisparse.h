@@ -224,12 +224,7 @@ int omni_prefill_select(const omni_layer_desc* desc, const void* Q, const void* 
  * followed by omni_sparse_attn_fwd (the _per_head forms when budget_mode is 2),
  * i.e. Sec. "Query Selection", Sec. "KV Selection" and the sparse attention of
  * Sec. "Preliminary" under the two masks.  Every output (the selection's arrays,
- * O and lse) is bit-identical to what the two calls write.  What the fusion
- * changes is the hand-over between them: the kernel that gathers each head's
- * selected K and V rows into the attention's tile layout forms the key lists
- * itself, from the accumulated key scores and the head's cut (key-mask
- * equation), and writes kv_idx on the way; the list is neither written by a
- * pass of its own nor read back.
+ * O and lse) is bit-identical to what the two calls write.
  * Arguments: as in omni_prefill_select, then V, O and lse as in
  * omni_sparse_attn_fwd.
  * Workspace: omni_sparse_prefill_workspace_bytes(desc, probe_block, b_cap)
@@ -625,8 +620,9 @@ int omni_profile_read(int kernel_id, float* total_ms /* host */, int* launches /
  * uses exact counts where it has them).  queues = 1: one list, longest item first,
  * handed out from one atomic counter.  queues = 8 (the sparse bf16 forward): one list
  * per XCD -- whole heads are placed on queues, largest head first onto the least loaded
- * queue; inside a queue head follows head, each longest item first; a workgroup takes
- * from its XCD's queue and, once that is drained, from the queue with the most items left.  All pointers are
+ * queue; inside a queue head follows head, each longest item first (the device hands a
+ * queue out longest item first where its items are long against a workgroup's share);
+ * short sequences run without a list; a workgroup takes from its XCD's queue and, once that is drained, from the queue with the most items left.  All pointers are
  * HOST pointers.  q_cnt [batch * n_q_heads] (null: every head keeps n_tokens rows),
  * budget [batch] (null: n_tokens); item_head / item_tile / item_cost [capacity] out,
  * queue after queue in hand-out order; queue_end [8] out (nullable): queue q is the
@@ -659,8 +655,9 @@ int omni_debug_mfma_rate(int random_operands, int iters, double* tflops /* host 
 
 /*
  * Diagnostic: the backward pass shares a key tile that is seen by very many query tiles (a head
- * that keeps every query, at long context) between several workgroups, from `tiles` 64-query
- * tiles per share on (default 128).  A small value makes short test inputs take that path.
+ * that keeps every query) between several workgroups.  A share is as many 64-query tiles as a
+ * workgroup's part of all of them, between 8 and `tiles` (default 128): a value below 8 makes short test inputs
+ * take that path.
  * tiles <= 0 restores the default.  Process-wide; not for use while a backward call is running.
  */
 int omni_debug_key_split_len(int tiles);

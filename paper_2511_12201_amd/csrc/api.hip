@@ -139,7 +139,7 @@ static size_t prefill_select_ws(const Layer& L, int dtype, int pb) {
 static int run_prefill_select(const Layer& L, int dtype, const Ragged& rg, const void* Q, const void* K, int q_mode,
                               float q_param, float recall_p, int pb, int budget_mode, float* probe_keys, float* scores,
                               int* q_idx, int* q_cnt, float* key_scores, double* kurtosis, int* flattest, int* budget,
-                              float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st, SelectSource* sel) {
+                              float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st) {
   char* ws_lists = static_cast<char*>(ws) + align_up(probe_ws(L, dtype, pb), 256);
   int rc = run_probe_keys(L, dtype, K, probe_keys, ws, st, rg);
   if (rc != OMNI_OK) return rc;
@@ -147,7 +147,7 @@ static int run_prefill_select(const Layer& L, int dtype, const Ragged& rg, const
   rc = run_probe(L, dtype, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
   if (rc != OMNI_OK) return rc;
   return run_select_lists(L, rg, scores, q_mode, q_param, q_idx, q_cnt, key_scores, recall_p, budget_mode, kurtosis,
-                          flattest, budget, recall, kv_idx, b_cap, ws_lists, st, sel);
+                          flattest, budget, recall, kv_idx, b_cap, ws_lists, st);
 }
 
 static size_t kv_budget_ws(const Layer& L, int dtype, int pb) {
@@ -455,8 +455,7 @@ int omni_prefill_select(const omni_layer_desc* desc, const void* Q, const void* 
   CHECK(check_ws(ws, ws_bytes, prefill_select_ws(L, desc->dtype, probe_block)));
   hipStream_t st = static_cast<hipStream_t>(stream);
   return run_prefill_select(L, desc->dtype, Ragged{}, Q, K, q_mode, q_param, recall_p, probe_block, budget_mode, probe_keys,
-                            scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st,
-                            nullptr);
+                            scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st);
 }
 
 size_t omni_sparse_prefill_workspace_bytes(const omni_layer_desc* desc, int32_t probe_block, int32_t b_cap) {
@@ -492,11 +491,9 @@ int omni_sparse_prefill(const omni_layer_desc* desc, const void* Q, const void* 
   CHECK(check_ws(ws, ws_bytes, sel_bytes + attn_fwd_ws(L, desc->dtype, b_cap, true)));
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws_fwd = static_cast<char*>(ws) + sel_bytes;
-  SelectSource src;                  // the key lists come out of the attention's gather
   CHECK(run_prefill_select(L, desc->dtype, Ragged{}, Q, K, q_mode, q_param, recall_p, probe_block, budget_mode, probe_keys,
-                           scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st,
-                           &src));
-  return run_attn_fwd(L, desc->dtype, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws_fwd, true, st, &src);
+                           scores, q_idx, q_cnt, key_scores, kurtosis, flattest, budget, recall, kv_idx, b_cap, ws, st));
+  return run_attn_fwd(L, desc->dtype, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws_fwd, true, st);
 }
 
 int omni_prefill_select_varlen(const omni_layer_desc* desc, const void* Q, const void* K, const int32_t* seq_tokens,
@@ -565,7 +562,7 @@ int omni_prefill_select_varlen(const omni_layer_desc* desc, const void* Q, const
                              probe_keys + b * Hkv * 2 * D, scores + b * Hq * Np, q_idx + b * Hq * Np, q_cnt + b * Hq,
                              key_scores + b * Hq * Np, kurtosis + b * Hq, flattest + b,
                              budget + (budget_mode == 2 ? b * Hq : b), recall + b * Hq, kv_idx + b * Hq * b_cap, b_cap, ws,
-                             st, nullptr));
+                             st));
   }
   return OMNI_OK;
 }

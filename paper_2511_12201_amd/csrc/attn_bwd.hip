@@ -1100,7 +1100,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   if constexpr (BLOCKS) {
     // K, V (natural) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
     rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st,
-                     nullptr, split);
+                     split);
     if (rc != OMNI_OK) return rc;
     // token lists of the selected blocks (causal bounds, the reduction's slot map), rows npad apart, and the tile map
     rc = run_expand_blocks(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, w.kidx, w.vbudget, npad, st);
@@ -1112,7 +1112,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     b_cap = npad;                             // the lists' row pitch; their lengths are in vbudget
   } else {
     rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, w.Kt, nullptr, w.kidx, st,
-                     nullptr, split || dt == OMNI_F32);
+                     split || dt == OMNI_F32);
     if (rc != OMNI_OK) return rc;
   }
   rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, w.Qn, w.dOn, w.lse2c,

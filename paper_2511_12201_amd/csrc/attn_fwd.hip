@@ -874,7 +874,7 @@ int run_fwd_bounds(const Layer& L, const int* q_idx, const int* q_cnt, const int
 template <typename T, int D>
 int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, const int* q_idx, const int* q_cnt,
                const int* kv_idx, const int* budget, int b_cap, void* O, float* lse, void* ws, bool sparse,
-               hipStream_t st, const SelectSource* sel) {
+               hipStream_t st) {
   Arena a(ws);
   const int heads = sparse ? L.Hq : L.Hkv;
   const int npad = fwd_npad(sparse ? b_cap : L.N);
@@ -884,7 +884,7 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
     // K natural or in fragment order, V k-packed (bf16: converted to f16)
     int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp, nullptr, nullptr,
-                         w.Vp, w.kidx, st, sparse ? sel : nullptr, split || sizeof(T) == 4);
+                         w.Vp, w.kidx, st, split || sizeof(T) == 4);
     if (rc != OMNI_OK) return rc;
   }
   FwdParams p;
@@ -982,7 +982,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   // K and V of every KV head once, in the kernel's tile layouts, in token order: shared by the heads of a group
   const bool split = attention_work(L) <= kSplitWork;
   int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
-                       w.f.kidx, st, nullptr, split);
+                       w.f.kidx, st, split);
   if (rc != OMNI_OK) return rc;
   // token lists of the selected blocks (for the causal bounds) and the tile map
   rc = run_expand_blocks(L, blk_idx, blk_budget, blk_cap, block, w.klist, w.vbudget, cap_keys, st);
@@ -1059,15 +1059,15 @@ size_t attn_fwd_ws(const Layer& L, int dtype, int b_cap, bool sparse) {
 
 int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const void* V, const int* q_idx,
                  const int* q_cnt, const int* kv_idx, const int* budget, int b_cap, void* O, float* lse, void* ws,
-                 bool sparse, hipStream_t st, const SelectSource* sel) {
+                 bool sparse, hipStream_t st) {
   if (dtype == OMNI_BF16) {
     if (L.D == 128)
-      return launch_fwd<u16, 128>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st, sel);
-    return launch_fwd<u16, 64>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st, sel);
+      return launch_fwd<u16, 128>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st);
+    return launch_fwd<u16, 64>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st);
   }
   if (L.D == 128)
-    return launch_fwd<float, 128>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st, sel);
-  return launch_fwd<float, 64>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st, sel);
+    return launch_fwd<float, 128>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st);
+  return launch_fwd<float, 64>(L, Q, K, V, q_idx, q_cnt, kv_idx, budget, b_cap, O, lse, ws, sparse, st);
 }
 
 }  // namespace omni

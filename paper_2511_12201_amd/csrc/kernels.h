@@ -21,27 +21,12 @@ int run_select_kv(const Layer& L, const float* key_scores, const int* budget, in
 size_t budget_stats_ws(const Layer& L);
 int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, int budget_mode, double* kurt,
                      int* flattest, int* budget, float* recall, void* ws, hipStream_t st);
-// The key lists as the packing kernel can form them itself: the scores, each head's cut (threshold key and number of
-// cut-valued elements to take) and, per chunk of kSelectChunk elements, how many kept elements precede it.  out
-// receives the lists ([B*Hq, out_stride], what run_select_lists writes without it).
-constexpr int kSelectChunk = 1024;
-struct SelectSource {
-  const float* x;          // [B*Hq, ld]
-  int ld, nchunk;
-  const unsigned* thr;     // [B*Hq]
-  const int* need;         // [B*Hq]
-  const int* off_keep;     // [B*Hq, nchunk] exclusive counts of elements above the cut
-  const int* off_eq;       // [B*Hq, nchunk] exclusive counts of elements at the cut
-  int* out;
-  int out_stride;
-};
 // Both lists of a prefill step from the two score arrays: statistics of the key scores, the cuts, the lists (three
-// launches).  sel not null: the key lists are not written but described in *sel (pointers into the workspace).
+// launches).
 size_t select_lists_ws(const Layer& L);
 int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int q_mode, float q_param, int* q_idx,
                      int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,
-                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st,
-                     SelectSource* sel = nullptr);
+                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st);
 int run_visual_subset(const Layer& L, const int* kv_idx, const int* budget, int b_cap, int* vis_idx, int* vis_cnt,
                       hipStream_t st);
 size_t group_subset_ws(const Layer& L);
@@ -58,10 +43,9 @@ int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, f
 // fragment order)
 // k_frag: Kn, Vn in the order of a 32x32 MFMA's A operand instead of row by row, [32-row block][k step][lane] of 16 bytes
 // (lane = 32 * half + row; a k step is 16 bf16 or 8 fp32 values wide)
-// sel not null (per_q_head only, src_idx ignored): the kernel forms the lists from *sel and writes them to sel->out
 int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
                 int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
-                void* Vt, int* kidx, hipStream_t st, const SelectSource* sel = nullptr, bool k_frag = false);
+                void* Vt, int* kidx, hipStream_t st, bool k_frag = false);
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
                const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
                float* deltac, hipStream_t st);
@@ -70,10 +54,9 @@ int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const vo
 // products of the dense attention of a layer: what the rules between kernels for short and long sequences look at
 inline double attention_work(const Layer& L) { return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0); }
 size_t attn_fwd_ws(const Layer& L, int dtype, int b_cap, bool sparse);
-// sel not null: kv_idx is an output, formed from *sel by the packing kernel (sparse only)
 int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const void* V, const int* q_idx,
                  const int* q_cnt, const int* kv_idx, const int* budget, int b_cap, void* O, float* lse, void* ws,
-                 bool sparse, hipStream_t st, const SelectSource* sel = nullptr);
+                 bool sparse, hipStream_t st);
 
 // bf16 only, block % 64 == 0: the forward pass on block lists without a gathered copy of K/V per query head
 int attn_fwd_blocks_max_keys();

@@ -22,7 +22,7 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kChunk = kSelectChunk;    // elements per compaction workgroup
+constexpr int kChunk = 1024;            // elements per compaction workgroup
 constexpr int kChunkThreads = 256;
 constexpr int kPerThread = kChunk / kChunkThreads;
 constexpr double kFixScale = 1099511627776.0;   // 2^40
@@ -746,7 +746,7 @@ size_t select_lists_ws(const Layer& L) {
 
 int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int q_mode, float q_param, int* q_idx,
                      int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,
-                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st, SelectSource* sel) {
+                     int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st) {
   Arena a(ws);
   const SelWs wk = carve_select(a, L), wq = carve_select(a, L);
   int* own = a.take<int>((size_t)L.B * L.Hq);
@@ -757,17 +757,7 @@ int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int 
   const ListJob qj = query_job(L, wq, scores, q_mode, q_param, q_idx, q_cnt, &qs);
   rc = launch_cut(L, rg, 2, qj, qs, kj, ks, st);
   if (rc != OMNI_OK) return rc;
-  if (!sel) return launch_write(L, rg, 2, qj, kj, st);
-  sel->x = key_scores;
-  sel->ld = L.ld;
-  sel->nchunk = cdiv(L.N, kChunk);
-  sel->thr = wk.thr;
-  sel->need = wk.need;
-  sel->off_keep = wk.cnt_keep;
-  sel->off_eq = wk.cnt_eq;
-  sel->out = kv_idx;
-  sel->out_stride = b_cap;
-  return launch_write(L, rg, 1, qj, qj, st);
+  return launch_write(L, rg, 2, qj, kj, st);
 }
 
 // ---- union of the stored visual rows over the heads of a KV group, with a membership bit per head
