@@ -73,8 +73,14 @@ __device__ __forceinline__ void transpose4x4_store(const u32x4 (&in)[4], float* 
 // here from the scores and the head's cut saves the list writer nothing (it still runs, for the queries) and puts a search,
 // a scan and a ranking before every gather.  One-call prefill in us, formed here / read: 1072 tokens 93.3 / 90.6, 4096:
 // 153 / 148, 16384: 526 / 520, 65536: 4797 / 4792; 8 heads, 16384: 313 / 302.
+// bf16: two wavefronts per output, so that a thread has one batch of loads and the outputs do not wait for each other.  (The copies
+// by all threads, then the transposes by those that had one, was a second memory latency for every workgroup.)  Memory-bound
+// on long sequences.  Layer in us, before / after, with the same change in pack_q below: forward, 1072 tokens 89.5 / 87.3,
+// 16391: 432.5 / 430.3, d = 64, 3000: 41.7 / 40.1; forward and backward, two clips of 3101, d = 64: 202.4 / 198.3, 32768:
+// 7364 / 7339.  (d threads per output: 8192 at d = 64 2.5 % slower.)
+constexpr int kOutThreads = 128;
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__ K, const T* __restrict__ V, Layer L,
+__global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void pack_kv_kernel(const T* __restrict__ K, const T* __restrict__ V, Layer L,
                                                           int per_q_head, const int* __restrict__ src_idx,
                                                           int idx_stride, const int* __restrict__ budget, int b_cap,
                                                           int npad, int pad_to, T* __restrict__ Kn, T* __restrict__ Vn,
@@ -102,8 +108,47 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
   const T* vbase = V + b * L.ks[0] + g * L.ks[1];
   const long long tile_off = ((long long)bhx * npad + tile * kTileN) * D;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  if (k_frag) {
-    // consecutive threads take consecutive rows of one 16-byte column: the writes are contiguous, the reads meet in L1
+  if constexpr (kBf16) {
+    const int t = threadIdx.x % kOutThreads;
+    int unit = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kOutThreads));
+    // row by row, or in fragment order: consecutive threads take consecutive rows of one 16-byte column, so the writes are
+    // contiguous and the reads meet in L1
+    auto copy = [&](const T* src, T* dst) {
+      constexpr int kEach = kTileN * CPR / kOutThreads;
+      u32x4 in[kEach];
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {
+        const int c = j * kOutThreads + t, row = k_frag ? c / (32 * CPR) * 32 + (c & 31) : c / CPR, chunk = k_frag ? c / 32 % CPR : c % CPR;
+        const int id = sIdx[row];
+        in[j] = zero;
+        if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + chunk * E);
+      }
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) *reinterpret_cast<u32x4*>(dst + tile_off + (j * kOutThreads + t) * E) = in[j];
+    };
+    // thread = (16-slot group, half, 8-wide d chunk): 8x8 transpose in registers
+    auto transposed = [&](const T* src, T* dst, bool f16) {
+      if (t >= (kTileN / 16) * 2 * (D / 8)) return;
+      u32x4 in[8];
+      const int dc = t % (D / 8), h = (t / (D / 8)) & 1, grp = t / (D / 8) / 2;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int id = sIdx[16 * grp + 8 * (j >> 2) + 4 * h + (j & 3)];
+        in[j] = zero;
+        if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + dc * 8);
+      }
+      if (f16) {                                       // the forward multiplies its weights and V in f16
+#pragma unroll
+        for (int j = 0; j < 8; ++j) in[j] = bf16x8_to_f16x8(in[j]);
+      }
+      transpose8x8_store(in, reinterpret_cast<u16*>(dst) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
+    };
+    if (Kn && unit-- == 0) copy(kbase, Kn);
+    if (Vn && unit-- == 0) copy(vbase, Vn);
+    if (Kt && unit-- == 0) transposed(kbase, Kt, false);
+    if (Vt && unit-- == 0) transposed(vbase, Vt, true);
+  } else {
+    // always in fragment order
 #pragma unroll                                      // all loads of a thread in flight together
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
       const int r32 = c & 31, chunk = c / 32 % CPR, row = c / (32 * CPR) * 32 + r32;
@@ -115,45 +160,6 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
       if (Kn) *reinterpret_cast<u32x4*>(Kn + tile_off + c * E) = k;
       if (Vn) *reinterpret_cast<u32x4*>(Vn + tile_off + c * E) = v;
     }
-  } else if (Kn || Vn) {
-#pragma unroll
-    for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
-      const int row = c / CPR, col = (c % CPR) * E;
-      const int id = sIdx[row];
-      if (Kn) {
-        u32x4 v = zero;
-        if (id != kPadKeyIndex) v = *reinterpret_cast<const u32x4*>(kbase + (long long)id * L.ks[2] + col);
-        *reinterpret_cast<u32x4*>(Kn + tile_off + row * D + col) = v;
-      }
-      if (Vn) {
-        u32x4 v = zero;
-        if (id != kPadKeyIndex) v = *reinterpret_cast<const u32x4*>(vbase + (long long)id * L.ks[2] + col);
-        *reinterpret_cast<u32x4*>(Vn + tile_off + row * D + col) = v;
-      }
-    }
-  }
-  if constexpr (kBf16) {
-    // work item = (tensor, 16-slot group, half, 8-wide d chunk): 8x8 transpose in registers
-    constexpr int kItems = (kTileN / 16) * 2 * (D / 8);
-    for (int it0 = threadIdx.x; it0 < 2 * kItems; it0 += kThreads) {
-      const int which = it0 / kItems, it = it0 % kItems;
-      T* dst_t = which ? Vt : Kt;
-      if (!dst_t) continue;
-      const T* src = which ? vbase : kbase;
-      const int dc = it % (D / 8);
-      const int h = (it / (D / 8)) & 1;
-      const int grp = it / (D / 8) / 2;
-      u32x4 in[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int id = sIdx[16 * grp + 8 * (j >> 2) + 4 * h + (j & 3)];
-        in[j] = zero;
-        if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + dc * 8);
-        if (which) in[j] = bf16x8_to_f16x8(in[j]);     // the forward multiplies its weights and V in f16
-      }
-      transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
-    }
-  } else {
     // work item = (tensor, 4-slot group, 4-wide d chunk)
     constexpr int kItems = (kTileN / 4) * (D / 4);
     for (int it0 = threadIdx.x; it0 < 2 * kItems; it0 += kThreads) {
@@ -174,8 +180,11 @@ __global__ __launch_bounds__(kThreads) void pack_kv_kernel(const T* __restrict__
 }
 
 // grid: (ceil(N/64), B*Hq).  Tile t covers kept positions [64 t, 64 t + 64).
+// bf16: the wavefronts past the first four write the k-packed copies meanwhile, D threads each.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ Q, const T* __restrict__ O,
+constexpr int kPackQThreads = kThreads + (sizeof(T) == 2 ? 2 * D : 0);
+template <typename T, int D>
+__global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* __restrict__ Q, const T* __restrict__ O,
                                                          const T* __restrict__ dO, const float* __restrict__ lse,
                                                          Layer L, const int* __restrict__ q_idx,
                                                          const int* __restrict__ q_cnt, int nqpad,
@@ -199,6 +208,8 @@ __global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ 
   const long long head_off = b * L.qs[0] + i * L.qs[1];
   // delta = rowsum(dO * O), lse in log2 units; rows that contribute nothing get lse = +inf (P = 0)
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
+  if (!kBf16 || threadIdx.x < kThreads) {
+#pragma unroll                                      // all loads of a thread in flight together
   for (int rb = 0; rb < 64; rb += RPP) {
     const int r = rb + r0;
     const int row = sIdx[r];
@@ -233,12 +244,14 @@ __global__ __launch_bounds__(kThreads) void pack_q_kernel(const T* __restrict__ 
       deltac[o] = row >= 0 ? dot : 0.f;
     }
   }
+  }
   if constexpr (kBf16) {
     constexpr int kItems = (64 / 16) * 2 * (D / 8);
     const u32x4 zero = {0u, 0u, 0u, 0u};
     const long long tile_off = ((long long)bh * nqpad + tile * 64) * D;
-    for (int it0 = threadIdx.x; it0 < 2 * kItems; it0 += kThreads) {
-      const int which = it0 / kItems, it = it0 % kItems;
+    static_assert(kItems == D, "one item per thread");
+    if (threadIdx.x >= kThreads) {
+      const int it0 = threadIdx.x - kThreads, which = it0 / kItems, it = it0 % kItems;
       const T* src = (which ? dO : Q) + head_off;
       T* dst_t = which ? dOt : Qt;
       const int dc = it % (D / 8);
@@ -279,7 +292,9 @@ int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head,
                    int* kidx, hipStream_t st, int k_frag) {
   const int heads = per_q_head ? L.Hq : L.Hkv;
   ProfScope prof__(kProfPack, st);
-  hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kTileN, L.B * heads), dim3(kThreads), 0, st,
+  const int outputs = (Kn != nullptr) + (Vn != nullptr) + (Kt != nullptr) + (Vt != nullptr);
+  const int threads = sizeof(T) == 2 ? kOutThreads * outputs : kThreads;
+  hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kTileN, L.B * heads), dim3(threads), 0, st,
                      static_cast<const T*>(K), static_cast<const T*>(V), L, per_q_head, src_idx, idx_stride, budget, b_cap,
                      npad, pad_to, static_cast<T*>(Kn), static_cast<T*>(Vn), static_cast<T*>(Kt), static_cast<T*>(Vt), kidx,
                      k_frag);
@@ -291,7 +306,7 @@ template <typename T, int D>
 int launch_pack_q(const Layer& L, const void* Q, const void* O, const void* dO, const float* lse, const int* q_idx,
                   const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c, float* deltac,
                   hipStream_t st) {
-  hipLaunchKernelGGL((pack_q_kernel<T, D>), dim3(nqpad / 64, L.B * L.Hq), dim3(kThreads), 0, st,
+  hipLaunchKernelGGL((pack_q_kernel<T, D>), dim3(nqpad / 64, L.B * L.Hq), dim3(kPackQThreads<T, D>), 0, st,
                      static_cast<const T*>(Q), static_cast<const T*>(O), static_cast<const T*>(dO), lse, L, q_idx,
                      q_cnt, nqpad, static_cast<T*>(Qt), static_cast<T*>(dOt), static_cast<T*>(Qn), static_cast<T*>(dOn),
                      lse2c, deltac);
