@@ -330,8 +330,11 @@ int omni_group_subset_per_head(const omni_layer_desc* desc, const int32_t* kv_id
  * absolute accuracy of 3e-8.  The dense baseline and the block-list calls share
  * the kernel and the limit.
  *   q_idx/q_cnt as written by omni_select_queries, kv_idx/budget as written by
- *   omni_select_kv / omni_kv_budget (both index lists ascending); the effective
- *   number of keys per head is min(budget[batch], b_cap).
+ *   omni_select_kv / omni_kv_budget: both index lists strictly ascending, every
+ *   index once and inside the sequence (without the causal mask in any order).  A
+ *   list of valid indices in another order keeps every access inside the arrays, but
+ *   its results are not those of the definition above.  The effective number of keys
+ *   per head is min(budget[batch], b_cap).
  *   O   [batch, n_q_heads, n_tokens, head_dim] dtype, out (fully written)
  *   lse [batch, n_q_heads, n_tokens] f32, out: natural-log sum of exp of the
  *       scaled logits over the admissible keys

@@ -1116,7 +1116,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     if (rc != OMNI_OK) return rc;
   }
   rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, w.Qn, w.dOn, w.lse2c,
-                  w.deltac, st);
+                  w.deltac, w.inv, st);
   if (rc != OMNI_OK) return rc;
   BwdParams p;
   p.Q = Q;

@@ -48,7 +48,7 @@ int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per
                 void* Vt, int* kidx, hipStream_t st, bool k_frag = false);
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
                const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
-               float* deltac, hipStream_t st);
+               float* deltac, int* inv, hipStream_t st);
 
 // attn_fwd.hip
 // products of the dense attention of a layer: what the rules between kernels for short and long sequences look at

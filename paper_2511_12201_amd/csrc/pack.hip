@@ -16,7 +16,8 @@
 // pack_q: for the backward pass, the kept rows of Q and dO in the k-packed
 // layout (contraction over queries) and, for bf16, also as contiguous natural
 // rows in kept order (so that a tile of them is one linear stream), plus per
-// kept row lse * log2(e) and delta = rowsum(dO * O).
+// kept row lse * log2(e) and delta = rowsum(dO * O).  On the way every token's entry of the
+// key lists' slot map is set to "not listed".
 #include "common.h"
 #include "kernels.h"
 
@@ -190,7 +191,8 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
                                                          const int* __restrict__ q_cnt, int nqpad,
                                                          T* __restrict__ Qt, T* __restrict__ dOt,
                                                          T* __restrict__ Qn, T* __restrict__ dOn,
-                                                         float* __restrict__ lse2c, float* __restrict__ deltac) {
+                                                         float* __restrict__ lse2c, float* __restrict__ deltac,
+                                                         int* __restrict__ inv) {
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int E = Elem<T>::kPer16B;
   constexpr int LPR = D / E;
@@ -199,6 +201,7 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
   const int tile = blockIdx.x, bh = blockIdx.y;
   const int b = bh / L.Hq, i = bh % L.Hq;
   const int nq = q_cnt[bh];
+  if (threadIdx.x < 64 && tile * 64 + (int)threadIdx.x < L.N) inv[(long long)bh * L.N + tile * 64 + threadIdx.x] = -1;
   if (tile * 64 >= nq) return;
   if (threadIdx.x < 64) {
     const int p = tile * 64 + threadIdx.x;
@@ -305,11 +308,11 @@ int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head,
 template <typename T, int D>
 int launch_pack_q(const Layer& L, const void* Q, const void* O, const void* dO, const float* lse, const int* q_idx,
                   const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c, float* deltac,
-                  hipStream_t st) {
+                  int* inv, hipStream_t st) {
   hipLaunchKernelGGL((pack_q_kernel<T, D>), dim3(nqpad / 64, L.B * L.Hq), dim3(kPackQThreads<T, D>), 0, st,
                      static_cast<const T*>(Q), static_cast<const T*>(O), static_cast<const T*>(dO), lse, L, q_idx,
                      q_cnt, nqpad, static_cast<T*>(Qt), static_cast<T*>(dOt), static_cast<T*>(Qn), static_cast<T*>(dOn),
-                     lse2c, deltac);
+                     lse2c, deltac, inv);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
@@ -335,15 +338,15 @@ int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per
 
 int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
                const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
-               float* deltac, hipStream_t st) {
+               float* deltac, int* inv, hipStream_t st) {
   if (dtype == OMNI_BF16) {
     if (L.D == 128)
-      return launch_pack_q<u16, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
-    return launch_pack_q<u16, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
+      return launch_pack_q<u16, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
+    return launch_pack_q<u16, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
   }
   if (L.D == 128)
-    return launch_pack_q<float, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
-  return launch_pack_q<float, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, st);
+    return launch_pack_q<float, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
+  return launch_pack_q<float, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
 }
 
 }  // namespace omni

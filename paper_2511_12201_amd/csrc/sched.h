@@ -45,16 +45,16 @@ __host__ __device__ inline size_t sched_keys_off(int BH) { return (sched_head_pl
 inline size_t sched_order_off(int BH, int N, int tile_m) { return sched_keys_off(BH) + 2 * sched_cap(BH, N, tile_m); }
 inline size_t sched_ints(int BH, int N, int tile_m) { return sched_order_off(BH, N, tile_m) + sched_cap(BH, N, tile_m); }
 
-// What the kept-query and key lists say about every token, in one pass over the tokens (run_bounds); null: not wanted.
+// What the kept-query and key lists say about every position and token, in one launch (run_bounds); null: not wanted.
 struct Bounds {
   const int *q_idx, *q_cnt;      // [B*Hq, N], [B*Hq]
-  const int* klist;              // [B*Hq, klist_stride] ascending token indices, the first min(budget, b_cap) of a head
+  const int* klist;              // [B*Hq, klist_stride] token indices, the first min(budget, b_cap) of a head
   int klist_stride;
   const int* budget;
   int b_cap, npad;
   int* qvis;                     // [B*Hq, N] number of listed keys that kept query `pos` may see
   int* kfirst;                   // [B*Hq, npad] first kept-query position that may see listed key `slot`
-  int* inv;                      // [B*Hq, N] slot of the token in the key list, -1: not listed
+  int* inv;                      // [B*Hq, N] slot of the token in the key list (listed tokens only; with kfirst)
   void* X;                       // rows of the Q-shaped tensor (16-byte aligned) that are not kept are set to zero
   int elem_bytes;
   float* lse;                    // [B*Hq, N] -inf for the rows that are not kept

@@ -46,55 +46,71 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Which of the tokens [r0, r0 + 64) the list holds (one bit each) and how many of its entries come before them.
-__device__ __forceinline__ unsigned long long list_window(const int* __restrict__ list, int n, int r0, int& before) {
-  before = wave_lower_bound(list, n, r0);
-  const int at = before + lane_id();
-  const int o = at < n ? list[at] - r0 : 64;
-  const unsigned lo = wave_or(o < 32 ? 1u << (o & 31) : 0u), hi = wave_or(o >= 32 && o < 64 ? 1u << (o & 31) : 0u);
+// Which of the tokens [r0, r0 + 64) the list holds, one bit each.  A set bit is always an entry; of a list that is not
+// strictly ascending some entries may be missed.
+__device__ __forceinline__ unsigned long long list_window(const int* __restrict__ list, int n, int r0) {
+  const int at = wave_lower_bound(list, n, r0) + lane_id();
+  const unsigned o = at < n ? (unsigned)(list[at] - r0) : 64u;
+  const unsigned lo = wave_or(o < 32u ? 1u << o : 0u), hi = wave_or(o >= 32u && o < 64u ? 1u << (o & 31u) : 0u);
   return ((unsigned long long)hi << 32) | lo;
 }
 
-// grid: (cdiv(max(N, npad), 256), B*Hq).  A wavefront owns 64 tokens: two windows of the lists give it the visible
-// counts, slots and kept rows of all of them, and it sets its dropped rows to zero meanwhile.  Bound by those stores (the
-// searches of the other wavefronts hide under them).  It took the place of a search per kept query and per key
-// (visibility_kernel), a fill and a scatter of the slot map, a clearing pass over all rows and two list kernels:
-// before / after at 64k, 28 heads, forward: 83 / 73 us; backward at 32k: 55 / 35 us.
+// Per lane: first position of the ascending a[0, n) with a[pos] >= v, for values that ascend from lane to lane: the wavefront
+// finds where its first and its last value fall, a lane searches between.  Whatever the list holds the result is in [0, n].
+__device__ __forceinline__ int lanes_lower_bound(const int* __restrict__ a, int n, int v) {
+  int lo = wave_lower_bound(a, n, __builtin_amdgcn_readfirstlane(v));
+  int hi = max(lo, wave_lower_bound(a, n, __builtin_amdgcn_readlane(v, 63)));
+  while (__any(lo < hi)) {
+    const int mid = (lo + hi) >> 1;
+    if (lo < hi) {
+      if (a[mid] < v) lo = mid + 1;
+      else hi = mid;
+    }
+  }
+  return lo;
+}
+
+// grid: (cdiv(max(N, npad), 256), B*Hq, 2).  z = 1: a wavefront owns 64 tokens and sets those of its rows that the window of
+// the kept-query list does not show to zero (one that it misses is set to zero too, and written again by the attention).
+// z = 0: a wavefront owns 64 positions of the lists and finds by search what each one sees.  Every entry of qvis and kfirst
+// up to the counts, and every work item, is written from its own position, so that a list that repeats an index or (without
+// the causal mask, where nothing has to be searched) is in any order gives what it means, and no list leaves an entry
+// unwritten that a kernel then takes for a size.  Bound by the stores of the zeros (the searches of the other wavefronts hide
+// under them).  It took the place of two search kernels, a fill and a scatter of the slot map, a clearing pass over all rows
+// and two list kernels.
 __global__ __launch_bounds__(kThreads) void bounds_kernel(Layer L, Bounds p) {
   const int bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq, lane = lane_id();
-  const int r0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kThreads + (threadIdx.x & ~63)));
-  const int nq = p.q_cnt[bh], nkeys = max(min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap), 0);
-  const int* klist = p.klist + (long long)bh * p.klist_stride;
-  const int n = r0 + lane;
-  if (p.kfirst && n < p.npad) {                    // pad slots and listed pads past the last token: nobody sees them
-    if (n >= nkeys) p.kfirst[(long long)bh * p.npad + n] = nq;
-    else if (klist[n] >= L.N) p.kfirst[(long long)bh * p.npad + n] = L.causal ? nq : 0;
-  }
-  if (r0 >= L.N) return;
-  int q_before, k_before;
-  const unsigned long long kept = list_window(p.q_idx + (long long)bh * L.N, nq, r0, q_before);
-  const unsigned long long keys = list_window(klist, nkeys, r0, k_before);
-  if (p.X) {
+  const int r0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kThreads + (threadIdx.x & ~63))), n = r0 + lane;
+  const int nq = p.q_cnt[bh];
+  const int* qlist = p.q_idx + (long long)bh * L.N;
+  if (blockIdx.z == 1) {
+    if (r0 >= L.N) return;
+    const unsigned long long kept = list_window(qlist, nq, r0);
     const int per_row = L.D * p.elem_bytes / 16;   // lanes that store one row: 8, 16 or 32
     char* base = static_cast<char*>(p.X) + (b * L.qs[0] + i * L.qs[1]) * p.elem_bytes + lane % per_row * 16;
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int r = lane / per_row; r < 64; r += 64 / per_row)
       if (r0 + r < L.N && !(kept >> r & 1)) *reinterpret_cast<u32x4*>(base + (r0 + r) * L.qs[2] * p.elem_bytes) = zero;
+    if (p.lse && n < L.N && !(kept >> lane & 1)) p.lse[(long long)bh * L.N + n] = -INFINITY;
+    return;
   }
-  const bool live = n < L.N;                       // no early exit: the wavefront stays whole for the scan below
-  const unsigned long long below = (1ull << lane) - 1ull;
-  const int pos = q_before + (int)__popcll(kept & below), slot = k_before + (int)__popcll(keys & below);
-  const bool is_kept = kept >> lane & 1, is_key = keys >> lane & 1;
-  if (p.lse && live && !is_kept) p.lse[(long long)bh * L.N + n] = -INFINITY;
-  if (p.inv && live) p.inv[(long long)bh * L.N + n] = is_key ? slot : -1;
-  if (p.kfirst && is_key) p.kfirst[(long long)bh * p.npad + slot] = L.causal ? pos : 0;
-  const int visible = L.causal ? slot + (is_key ? 1 : 0) : nkeys;
-  if (p.qvis && is_kept) p.qvis[(long long)bh * L.N + pos] = visible;
-  const bool last = is_kept && (pos % p.tile_m == p.tile_m - 1 || pos == nq - 1);       // last row of a work item
+  const int nkeys = max(min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap), 0);
+  const int* klist = p.klist + (long long)bh * p.klist_stride;
+  if (p.kfirst && r0 < p.npad) {                   // slots: who is the first to see the key (pads: nobody)
+    const int tok = r0 < nkeys ? klist[min(n, nkeys - 1)] : 0;
+    const int first = r0 < nkeys && L.causal ? lanes_lower_bound(qlist, nq, tok) : 0;
+    if (n < p.npad) p.kfirst[(long long)bh * p.npad + n] = n < nkeys ? first : nq;
+    if (p.inv && n < nkeys && (unsigned)tok < (unsigned)L.N) p.inv[(long long)bh * L.N + tok] = n;
+  }
+  if (r0 >= nq) return;
+  const int row = qlist[min(n, nq - 1)];           // kept queries: how many keys they see
+  const int visible = L.causal ? lanes_lower_bound(klist, nkeys, row + 1) : nkeys;
+  if (p.qvis && n < nq) p.qvis[(long long)bh * L.N + n] = visible;
+  const bool last = n < nq && (n % p.tile_m == p.tile_m - 1 || n == nq - 1);       // last row of a work item
   if (!p.sched || !__any(last)) return;
   const int before = items_before(p.q_cnt, bh, L.N, p.tile_m);
   if (last) {
-    const int tq = pos / p.tile_m;
+    const int tq = n / p.tile_m;
     reinterpret_cast<int2*>(p.sched + sched_keys_off(L.B * L.Hq))[before + tq] =
         make_int2((int)(((unsigned)bh << 16) | (unsigned)tq), (visible + kTileN - 1) / kTileN);
   }
@@ -275,7 +291,7 @@ int check_work_list(const Layer& L, int tile_m) {
 
 int run_bounds(const Layer& L, const Bounds& p, hipStream_t st) {
   const int BH = L.B * L.Hq, n = p.kfirst ? max(L.N, p.npad) : L.N;
-  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH), dim3(kThreads), 0, st, L, p);
+  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH, 2), dim3(kThreads), 0, st, L, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }

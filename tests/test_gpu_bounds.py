@@ -60,6 +60,61 @@ def test_rows_slots_and_items_at_window_edges(N, dtype, d, causal):
         assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, dtype, r))
 
 
+def _check_layer(dtype, d, N, q_lists, kv_lists, causal, backward=True):
+    """Forward (and backward) of four heads on these lists against the oracle, outputs that start as NaN."""
+    H, Hkv, rng = 4, 2, np.random.default_rng(N + d)
+    mk = lambda h, s=1.0: s * rng.standard_normal((1, h, N, d)).astype(np.float32)  # noqa: E731
+    Q, K, V, dO = mk(H), mk(Hkv), mk(Hkv), mk(H, d ** -0.5)
+    if dtype == "bf16":
+        Q, K, V, dO = (synth.round_to_bf16(x) for x in (Q, K, V, dO))
+    q_idx, q_cnt = lists_to_padded(q_lists, H, N)
+    kv_idx, budget = lists_to_padded(kv_lists, H, N)
+    tq, tk, tv, tg = (to_device(x, dtype) for x in (Q, K, V, dO))
+    desc = ob.make_layer_desc(tq, tk, 0, N, 0, causal)
+    nan = lambda x: torch.full_like(x, float("nan"))  # noqa: E731
+    O, lse = nan(tq), torch.full((1, H, N), float("nan"), device="cuda")
+    ob.omni_sparse_attn_fwd_per_head(desc, tq, tk, tv, q_idx, q_cnt, kv_idx, budget, N, O, lse)
+    scale = d ** -0.5
+    Oo, Lo = oc.sparse_attn_fwd(Q, K, V, q_lists, kv_lists, causal, scale)
+    assert np.max(np.abs(to_host(O) - Oo)) <= (1e-4 if dtype == "f32" else 2e-2)      # the bars of the parity tests
+    got, fin = to_host(lse), np.isfinite(Lo)
+    np.testing.assert_array_equal(np.isfinite(got), fin)
+    assert np.max(np.abs(got[fin] - Lo[fin])) <= (1e-4 if dtype == "f32" else 2e-3)
+    if not backward:
+        return
+    grads = ob.omni_sparse_attn_bwd_per_head(desc, tq, tk, tv, O, tg, lse, q_idx, q_cnt, kv_idx, budget, N, nan(tq), nan(tk),
+                                             nan(tv))
+    torch.cuda.synchronize()
+    want = oc.sparse_attn_bwd(Q, K, V, dO, q_lists, kv_lists, causal, scale, O=to_host(O))
+    rss = oc.sparse_attn_bwd_term_rss(Q, K, V, dO, q_lists, kv_lists, causal, scale, O=to_host(O))
+    for x, w, r in zip(grads, want, rss):
+        assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, dtype, r))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("N", [65, 600])
+def test_lists_in_any_order_without_the_causal_mask(N, dtype, d):
+    """Nothing has to be searched then: kept queries and keys may come in any order."""
+    rng = np.random.default_rng(N)
+    q_lists, kv_lists = _lists(rng, 4, N)
+    mix = lambda lists: [[rng.permutation(x) for x in lists[0]]]  # noqa: E731
+    _check_layer(dtype, d, N, mix(q_lists), mix(kv_lists), False)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("N", [65, 600])
+@pytest.mark.parametrize("causal", [True, False])
+def test_forward_on_ascending_lists_that_repeat_an_index(N, dtype, d, causal):
+    """A kept query listed twice is computed twice, a key listed twice counts twice; also more repeats than a window of 64
+    entries holds."""
+    rng = np.random.default_rng(N)
+    twice = lambda n: np.sort(rng.integers(0, N, n)).astype(np.int32)  # noqa: E731
+    run = lambda n, at: np.sort(np.concatenate([np.full(n // 2, at), rng.integers(0, N, n - n // 2)])).astype(np.int32)  # noqa: E731
+    q_lists = [[np.arange(N, dtype=np.int32), twice(N), run(N, N // 2), run(N // 3, 3)]]
+    kv_lists = [[twice(N), run(N, N // 3), twice(N // 2), run(N, 0)]]
+    _check_layer(dtype, d, N, q_lists, kv_lists, causal, backward=False)
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
 def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
