@@ -32,6 +32,7 @@ EXPORTED = [
     "omni_visual_subset_per_head", "omni_prefill_select", "omni_compact_cache", "omni_slim_decode_compact",
     "omni_compact_cache_paged", "omni_slim_decode_paged",
     "omni_group_subset_per_head", "omni_debug_key_split_len",
+    "omni_debug_attention_route",
     "omni_slim_decode_grouped_static", "omni_static_scratch_bytes",
     "omni_sparse_prefill", "omni_sparse_prefill_workspace_bytes", "omni_slim_decode_prepare",
 ]
@@ -143,6 +144,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.omni_profile_enable.argtypes = [C.c_int]
     lib.omni_debug_copy.argtypes = [vp, vp, sz, vp]
     lib.omni_debug_key_split_len.argtypes = [C.c_int]
+    lib.omni_debug_attention_route.argtypes = [C.c_int]
     lib.omni_debug_mfma_rate.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     lib.omni_debug_work_list.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, i32, vp, vp]   # same shape: three output arrays
     lib.omni_profile_read.argtypes = [C.c_int, C.POINTER(C.c_float), C.POINTER(C.c_int)]
@@ -243,6 +245,11 @@ def debug_copy(src, dst):
 def debug_key_split_len(tiles: int):
     """Query tiles per share of a split key tile in the backward pass (<= 0: default)."""
     _check(load_library().omni_debug_key_split_len(int(tiles)))
+
+
+def debug_attention_route(route: int):
+    """Attention kernels of this host thread's calls: 0 by the shape, 1 those for short, 2 those for long sequences."""
+    _check(load_library().omni_debug_attention_route(int(route)))
 
 
 def debug_mfma_rate(random_operands, iters: int = 40000):

@@ -128,6 +128,9 @@ void prof_end(int id, hipStream_t st) {
   e.used++;
 }
 
+static thread_local int g_route = 0;
+int attention_route() { return g_route; }
+
 static bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // The partial sums of the probe keys are used up before the probe's scratch is first written: they share the space.
@@ -306,6 +309,13 @@ int omni_debug_copy(const void* src, void* dst, size_t bytes, void* stream) {
 int omni_debug_key_split_len(int tiles) {
   clear_error();
   set_key_split_len(tiles);
+  return OMNI_OK;
+}
+
+int omni_debug_attention_route(int route) {
+  clear_error();
+  if (route < 0 || route > 2) OMNI_FAIL(OMNI_ERR_INVALID, "route must be 0, 1 or 2");
+  g_route = route;
   return OMNI_OK;
 }
 

@@ -1095,7 +1095,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int npad = bwd_npad(cap_keys), nqpad = bwd_nqpad(L);
   const int npad_kv = BLOCKS ? bwd_npad_kv(L) : 0;
   BwdWs w = carve_bwd(a, L, dt, npad, nqpad, npad_kv, cap_keys / kTileN);
-  const bool split = sizeof(T) == 2 && attention_work(L) <= kSplitWork;
+  const bool split = sizeof(T) == 2 && short_route(attention_work(L) <= kSplitWork);
   int rc;
   if constexpr (BLOCKS) {
     // K, V (natural) and K (k-packed) of every KV head once, in token order: shared by the heads of a group

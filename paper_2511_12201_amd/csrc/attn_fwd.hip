@@ -879,7 +879,7 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int heads = sparse ? L.Hq : L.Hkv;
   const int npad = fwd_npad(sparse ? b_cap : L.N);
   FwdWs w = carve_fwd(a, L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, heads, npad, sparse);
-  const bool split = sparse && sizeof(T) == 2 && attention_work(L) <= kSplitWork;
+  const bool split = sparse && sizeof(T) == 2 && short_route(attention_work(L) <= kSplitWork);
   {
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
     // K natural or in fragment order, V k-packed (bf16: converted to f16)
@@ -980,7 +980,7 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   BlockFwdWs w = carve_block_fwd(a, L, cap_keys);
   const int npad = fwd_npad(L.N);
   // K and V of every KV head once, in the kernel's tile layouts, in token order: shared by the heads of a group
-  const bool split = attention_work(L) <= kSplitWork;
+  const bool split = short_route(attention_work(L) <= kSplitWork);
   int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
                        w.f.kidx, st, split);
   if (rc != OMNI_OK) return rc;

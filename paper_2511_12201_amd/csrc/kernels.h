@@ -52,6 +52,8 @@ int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const vo
 
 // attn_fwd.hip
 // products of the dense attention of a layer: what the rules between kernels for short and long sequences look at
+int attention_route();                       // omni_debug_attention_route of this thread; 0: by the shape
+inline bool short_route(bool by_shape) { return attention_route() ? attention_route() == 1 : by_shape; }
 inline double attention_work(const Layer& L) { return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0); }
 size_t attn_fwd_ws(const Layer& L, int dtype, int b_cap, bool sparse);
 int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const void* V, const int* q_idx,

@@ -165,6 +165,8 @@ def test_argument_errors(lib):
     assert lib.omni_slim_decode_paged(C.byref(dd), FAKE, FAKE, FAKE, FAKE, FAKE, None, FAKE, FAKE, FAKE, 64, FAKE,
                                       FAKE, FAKE, 1 << 30, None) == -1
     assert lib.omni_debug_key_split_len(0) == 0
+    assert lib.omni_debug_attention_route(-1) == -1 and lib.omni_debug_attention_route(3) == -1 and "route" in ob.last_error()
+    assert lib.omni_debug_attention_route(2) == 0 and lib.omni_debug_attention_route(0) == 0
     # a successful validation path clears the message
     assert ob.workspace_bytes(ob.CALL_SELECT_KV, d) > 0
     assert ob.last_error() == ""

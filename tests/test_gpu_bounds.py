@@ -20,6 +20,7 @@ def _lists(rng, H, N):
     return [q[:H]], [k[:H]]
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("N", [1, 63, 64, 65, 255, 257, 600])
 @pytest.mark.parametrize("causal", [True, False])
@@ -91,6 +92,7 @@ def _check_layer(dtype, d, N, q_lists, kv_lists, causal, backward=True):
         assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, dtype, r))
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("N", [65, 600])
 def test_lists_in_any_order_without_the_causal_mask(N, dtype, d):
@@ -101,6 +103,7 @@ def test_lists_in_any_order_without_the_causal_mask(N, dtype, d):
     _check_layer(dtype, d, N, mix(q_lists), mix(kv_lists), False)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("N", [65, 600])
 @pytest.mark.parametrize("causal", [True, False])
@@ -199,6 +202,7 @@ def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal):
                     assert bool(((x.double() - w).abs() <= bar).all())
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("kept", [1, 64, 513, 2049])
 def test_key_gradients_when_a_few_long_key_tiles_are_split(kept):
     """One head keeps every query (its key tiles are shared between workgroups), the others few: dK and dV of the split

@@ -196,6 +196,7 @@ def _check_fwd(c, O, lse, Oo, Lo):
     assert np.all(O[~fin] == 0)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 def test_sparse_attn_fwd_on_oracle_selection(cfg):
     c = case_for(cfg)
@@ -205,6 +206,7 @@ def test_sparse_attn_fwd_on_oracle_selection(cfg):
     _check_fwd(c, O, lse, Oo, Lo)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_F32], ids=lambda c: c.name)
 def test_sparse_attn_fwd_edge_sets(cfg):
     """Tiny budgets, a head with no kept query past the first keys, a head whose queries precede all its keys."""
@@ -228,6 +230,7 @@ def _plain_bf16_layer(seed, N, H, Hkv, d):
     return mk(1, H, N, d), mk(1, Hkv, N, d), mk(1, Hkv, N, d)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("ramp", [3.0, 12.0, 40.0])
 def test_forward_when_the_logits_keep_rising_along_the_key_list(ramp):
     """Keys whose logits grow with their index by up to `ramp` per 64-key tile in the exponent's base-2 units, and
@@ -260,6 +263,7 @@ def test_forward_when_the_logits_keep_rising_along_the_key_list(ramp):
             assert np.max(np.abs(to_host(got_l) - Lo)) <= 2e-3 * max(1.0, float(np.max(np.abs(Lo))) / 64)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("causal", [True, False])
 def test_forward_returns_the_value_row_of_a_key_that_dominates(causal):
     """Every query's own key beats all others by more than 40 in the exponent: the softmax is one-hot to any working
@@ -288,6 +292,7 @@ def test_forward_returns_the_value_row_of_a_key_that_dominates(causal):
     np.testing.assert_allclose(to_host(lse)[0], own, rtol=2e-6, atol=1e-4)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("vscale", [2.0 ** -12, 1.0, 2.0 ** 13])
 def test_forward_value_range(vscale):
     """The second product runs in f16: V is converted exactly inside [2^-14, 65504].  Outputs follow V's scale with the
@@ -314,6 +319,7 @@ def test_forward_value_range(vscale):
         assert np.max(np.abs(got - Oc)) <= TOL_OUT["bf16"] * vscale + 2.0 ** -8 * 65504
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 @pytest.mark.parametrize("causal", [True, False])
 def test_dense_attn_fwd_and_full_budget_sparse_equal_dense_definition(cfg, causal):
@@ -773,6 +779,7 @@ def _same_selection(f, g, cfg, budget_mode):
             np.testing.assert_array_equal(got[b, h, :n], want[b, h, :n], err_msg=f"kv list, batch {b} head {h}")
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 @pytest.mark.parametrize("budget_mode", [0, 1, 2])
 def test_prefill_step_in_one_call_writes_what_selection_and_attention_write(cfg, budget_mode):
@@ -798,6 +805,7 @@ def test_prefill_step_in_one_call_writes_what_selection_and_attention_write(cfg,
     _check_fwd(c, to_host(O), to_host(lse), Oo, Lo)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cap", [1, 63, 64, 200, 777])
 def test_prefill_step_in_one_call_with_a_capacity_below_the_budget(cap):
     cfg = CFG_BF16
@@ -843,6 +851,7 @@ def test_prefill_step_in_one_call_on_tied_key_scores():
 
 # ------------------------------------------------------------------ block-granular KV selection
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 @pytest.mark.parametrize("block", [64, 100])
 def test_block_granular_selection_and_attention(cfg, block):
@@ -895,6 +904,7 @@ CFG_BF16_NC = synth.C2_16K.scaled(name="bf16_noncausal", frames=4, tok_per_frame
                                   causal=False, seed=31)          # 1024 tokens: a multiple of every block size below
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_BF16_64, CFG_BF16_NC], ids=lambda c: c.name)
 @pytest.mark.parametrize("block,frac", [(64, 0.4), (128, 0.5), (256, 1.0), (192, 0.3)])
 def test_block_attention_in_place_equals_gathered_path_and_oracle(cfg, block, frac):
@@ -926,6 +936,7 @@ def test_block_attention_in_place_equals_gathered_path_and_oracle(cfg, block, fr
     assert np.max(np.abs(to_host(lse1)[fin] - Lo[fin])) <= 2e-2
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_BF16_64, CFG_BF16_NC], ids=lambda c: c.name)
 @pytest.mark.parametrize("block,frac", [(64, 0.4), (128, 0.5), (256, 1.0), (192, 0.3)])
 @pytest.mark.parametrize("split_len", [0, 2])
@@ -962,6 +973,7 @@ def test_block_attention_backward_in_place_equals_gathered_path_and_oracle(cfg, 
     _check_grads(cfg, g1, want, c.o_qidx, tok)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_F32], ids=lambda c: c.name)
 def test_block_lists_train_through_their_token_lists(cfg):
     """Training on block lists: expanded to token lists they go through the same forward and backward, and the
@@ -990,6 +1002,7 @@ def test_block_lists_train_through_their_token_lists(cfg):
     _check_grads(cfg, grads, want, c.o_qidx, tok)
 
 
+@pytest.mark.usefixtures("attention_route")
 def test_sparse_forward_with_more_heads_than_the_queued_scheduler_places():
     """Batch 150 x 8 heads = 1200 (batch, head) pairs: above 1024 the work list falls back to one queue.  Every batch
     entry holds the same sequence, so every one must give the oracle's output for it."""
@@ -1013,6 +1026,7 @@ def test_sparse_forward_with_more_heads_than_the_queued_scheduler_places():
     assert np.array_equal(Og[0], Og[-1]) and np.array_equal(Og[0], Og[B // 2])
 
 
+@pytest.mark.usefixtures("attention_route")
 def test_block_attention_in_place_edge_budgets():
     """Block budget 0: every kept query sees no key (zero output, lse = -inf).  A budget above blk_cap is clamped to
     it.  Both as the gathered path does it."""
@@ -1101,6 +1115,7 @@ def _check_grads(cfg, got, want, q_lists, kv_lists):
             assert np.all(dK[b, g, out] == 0) and np.all(dV[b, g, out] == 0)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 def test_sparse_attn_bwd_on_oracle_selection(cfg):
     c = case_for(cfg)
@@ -1120,6 +1135,7 @@ def test_sparse_attn_bwd_on_oracle_selection(cfg):
         assert np.all(np.abs(to_host(x) - to_host(y)) <= grad_bar(w, cfg.dtype, r)), name
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_F32_128], ids=lambda c: c.name)
 @pytest.mark.parametrize("causal", [True, False])
 def test_sparse_attn_bwd_full_sets_is_dense_attention_gradient(cfg, causal):
@@ -1134,6 +1150,7 @@ def test_sparse_attn_bwd_full_sets_is_dense_attention_gradient(cfg, causal):
     _check_grads(cfg, got, want, full, full)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16_64, CFG_F32], ids=lambda c: c.name)
 def test_sparse_attn_bwd_edge_sets(cfg):
     c = case_for(cfg)
@@ -1151,6 +1168,7 @@ def test_sparse_attn_bwd_edge_sets(cfg):
         assert np.all(to_host(got[0])[0, 1] == 0)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_BF16_64], ids=lambda c: c.name)
 @pytest.mark.parametrize("split_len", [1, 3])
 def test_sparse_attn_bwd_with_key_tiles_shared_between_workgroups(cfg, split_len):
@@ -1171,6 +1189,7 @@ def test_sparse_attn_bwd_with_key_tiles_shared_between_workgroups(cfg, split_len
         assert torch.equal(x, y)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("one_call", [False, True], ids=["two_calls", "one_call"])
 def test_prefill_step_replays_from_a_hip_graph(one_call):
     """No call of the step allocates, synchronises or clears memory from the host, so a caller may capture it.
@@ -1309,6 +1328,7 @@ def test_prefill_step_in_one_call_on_a_batch_of_two(budget_mode):
     test_prefill_step_in_one_call_writes_what_selection_and_attention_write(CFG_B2, budget_mode)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("budget_mode", [0, 2])
 def test_two_sequences_in_a_batch_have_their_own_sets_budgets_and_gradients(budget_mode):
     cfg = CFG_B2
@@ -1506,6 +1526,7 @@ def test_padded_batch_with_sequences_of_two_tokens_and_of_the_full_length(dtype)
 
 # ------------------------------------------------------------------ strides
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_F32], ids=lambda c: c.name)
 def test_token_major_memory_layout_gives_the_same_bits(cfg):
     """Q, K, V as a projection leaves them in memory ([batch, token, head, dim], viewed as [batch, head, token, dim]):
@@ -1578,6 +1599,7 @@ def test_decode_on_a_token_major_cache_gives_the_same_bits(cfg, batch):
 
 # ------------------------------------------------------------------ visual tokens in the middle of the sequence
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_F32], ids=lambda c: c.name)
 def test_visual_range_between_two_text_segments_and_a_sink_that_is_not_token_0(cfg):
     """[system text][visual tokens][question]: the visual range, the sink and the rows a decode step always reads
@@ -1678,6 +1700,7 @@ def test_decode_with_other_group_sizes(G, hkv, d):
 
 # ------------------------------------------------------------------ odd layouts of the visual range and the sink
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("layout", ["all_visual", "sink_not_first", "two_visual_tokens", "text_on_both_sides",
                                     "visual_at_the_end"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

@@ -89,6 +89,7 @@ def _run_fwd_bwd_per_head(c, q_lists, kv_lists, dO_np=None):
     return to_host(O), to_host(lse), grads, want
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", ALL_CFGS, ids=lambda c: c.name)
 def test_attention_fwd_bwd_on_the_oracles_per_head_selection(cfg):
     c = case_for(cfg)
@@ -102,6 +103,7 @@ def test_attention_fwd_bwd_on_the_oracles_per_head_selection(cfg):
     _check_grads(cfg, grads, want, c.o_qidx, kv_lists)
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", [CFG_BF16, CFG_BF16_64, CFG_F32], ids=lambda c: c.name)
 def test_attention_fwd_bwd_with_ragged_budgets_including_an_empty_head(cfg):
     c = case_for(cfg)
@@ -124,6 +126,7 @@ def test_attention_fwd_bwd_with_ragged_budgets_including_an_empty_head(cfg):
         assert np.all(to_host(grads[0])[0, h] == 0)
 
 
+@pytest.mark.usefixtures("attention_route")
 def test_equal_per_head_budgets_reproduce_the_shared_budget_calls_bit_for_bit():
     cfg = CFG_BF16
     c = case_for(cfg)

@@ -44,6 +44,7 @@ def _tiny_shapes():
     return out
 
 
+@pytest.mark.usefixtures("attention_route")
 @pytest.mark.parametrize("cfg", _shapes() + _tiny_shapes(), ids=lambda c: f"{c.name}-N{c.n_tokens}-H{c.n_q_heads}x{c.n_kv_heads}-d{c.head_dim}-{c.dtype}")
 def test_prefill_path_on_a_seeded_random_shape(cfg):
     pb = [32, 64, 100, 256][cfg.seed % 4]
