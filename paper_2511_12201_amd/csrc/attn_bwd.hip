@@ -18,7 +18,8 @@
 //    shared by up to four workgroups, each with a partial plane of its own.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
-// fp32 inputs: attn_bwd_key_f32_kernel (dK' and dV' of 32 keys together) and attn_bwd_dq_f32_kernel on the fp32 32x32x2 MFMA.
+// fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_key_f32_kernel (dK' and dV' of 32 keys together) and attn_bwd_dq_f32_kernel;
+// on long sequences attn_bwd_key_f32_long_kernel (128 keys) and attn_bwd_dq_f32_long_kernel (128 queries of the work list).
 #include <algorithm>
 
 #include <type_traits>
@@ -46,7 +47,7 @@ struct BwdParams {
   const void* Vn;
   const void* Kt;       // k-packed K
   const int* kidx;
-  const void* Qt;       // k-packed kept Q, dO
+  const void* Qt;       // k-packed kept Q, dO (these and the next two, and Kt: not for fp32 on long sequences)
   const void* dOt;
   const void* Qn;       // kept Q, dO rows in kept order, contiguous (fp32: in fragment order, as Kn and Vn)
   const void* dOn;
@@ -273,6 +274,233 @@ __global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_dq_f32_kernel(BwdP
   merge_waves<D>(sO, dq, L.scale, [&](int row, int d, const f32x4& x) {
     if (tq * 32 + row < nq) *reinterpret_cast<f32x4*>(head + (long long)qlist[tq * 32 + row] * L.qs[2] + d) = x;
   });
+}
+
+// fp32, long sequences (f32_short): workgroups of 128 keys, or of 128 kept queries from the work list, 32 per wavefront; tiles of 64 rows of the
+// other side staged row by row through LDS, Q and dO straight from the caller's arrays.  One plane of dK', dV', no other
+// copies than K and V: a quarter of the scratch.
+constexpr int kF32Keys = 128;
+
+// grid: (npad / 128, B*Hq)
+template <int D>
+__global__ __launch_bounds__(kThreads, 1) void attn_bwd_key_f32_long_kernel(BwdParams p) {
+  constexpr int LD = D + 8;                                 // row pitch of the tiles
+  constexpr int CPR = D / 4, kChunks = kKeyQ * CPR / kThreads;
+  __shared__ __attribute__((aligned(16))) float sq[kKeyQ * LD], sg[kKeyQ * LD];
+  __shared__ __attribute__((aligned(16))) float sLse[kKeyQ], sDel[kKeyQ];
+  const Layer& L = p.L;
+  const int slot0 = blockIdx.x * kF32Keys, bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq;
+  const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
+  if (slot0 >= nkeys) return;
+  const int nq = p.q_cnt[bh];
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int ln = lane & 31, h = lane >> 5;
+  const int slot = slot0 + wave * 32 + ln;                  // this lane's key slot (< npad by construction)
+  const float c2 = L.scale * kLog2e;
+  const int* qlist = p.q_idx + (long long)bh * L.N;
+  const int* kfirst = p.kfirst + (long long)bh * p.npad;
+  const int my_first = kfirst[slot] - 4 * h;                // query positions below it do not see this lane's key
+  const bool has_pad = slot0 + kF32Keys > nkeys;
+  const int q_full_pos = has_pad ? 0x7fffffff : kfirst[slot0 + kF32Keys - 1];    // tiles from this position on need no mask
+  const int n_qtiles = cdiv(nq, kKeyQ);
+  f32x4 kf[D / 8], vf[D / 8];                               // resident: B operands, lane = key column
+  const long long kv = ((long long)bh * p.npad + slot) * D;
+#pragma unroll
+  for (int ks = 0; ks < D / 8; ++ks) {
+    kf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Kn) + kv + ks * 8 + h * 4);
+    vf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Vn) + kv + ks * 8 + h * 4);
+  }
+  f32x16 dk[D / 32], dv[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dk[db][r] = 0.f, dv[db][r] = 0.f;
+  const float* qbase = static_cast<const float*>(p.Q) + b * L.qs[0] + i * L.qs[1];
+  const float* gbase = static_cast<const float*>(p.dO) + b * L.qs[0] + i * L.qs[1];
+  for (int t = kfirst[slot0] / kKeyQ; t < n_qtiles; ++t) {
+    const int pos0 = t * kKeyQ;
+    __syncthreads();
+    u32x4 stQ[kChunks], stG[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int ch = threadIdx.x + c * kThreads, col = ch % CPR * 4, pos = pos0 + ch / CPR;
+      stQ[c] = stG[c] = u32x4{0u, 0u, 0u, 0u};
+      if (pos < nq) {
+        const long long at = (long long)qlist[pos] * L.qs[2] + col;
+        stQ[c] = *reinterpret_cast<const u32x4*>(qbase + at);
+        stG[c] = *reinterpret_cast<const u32x4*>(gbase + at);
+      }
+    }
+    float stL = 0.f, stD = 0.f;
+    if (threadIdx.x < kKeyQ) {
+      stL = p.lse2c[(long long)bh * p.nqpad + pos0 + threadIdx.x];
+      stD = p.deltac[(long long)bh * p.nqpad + pos0 + threadIdx.x];
+    }
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int ch = threadIdx.x + c * kThreads, at = ch / CPR * LD + ch % CPR * 4;
+      *reinterpret_cast<u32x4*>(sq + at) = stQ[c];
+      *reinterpret_cast<u32x4*>(sg + at) = stG[c];
+    }
+    if (threadIdx.x < kKeyQ) {
+      sLse[threadIdx.x] = stL;
+      sDel[threadIdx.x] = stD;
+    }
+    __syncthreads();
+    const bool masked = pos0 < q_full_pos;
+#pragma unroll
+    for (int qb = 0; qb < kKeyQ / 32; ++qb) {
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f, dp[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < D / 8; ++ks) {
+        const f32x4 qa = *reinterpret_cast<const f32x4*>(sq + (qb * 32 + ln) * LD + ks * 8 + h * 4);
+        const f32x4 ga = *reinterpret_cast<const f32x4*>(sg + (qb * 32 + ln) * LD + ks * 8 + h * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[e], kf[ks][e], s, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x2f32(ga[e], vf[ks][e], dp, 0, 0, 0);
+        }
+      }
+      // accumulator rows are queries 8 (r/4) + 4 h + r%4 of this block, the column is this lane's key
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int qo = qb * 32 + 8 * q4 + 4 * h;
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sLse[qo]), d4 = *reinterpret_cast<const f32x4*>(&sDel[qo]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = q4 * 4 + e;
+          float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
+          if (masked && pos0 + qb * 32 + 8 * q4 + e < my_first) pv = 0.f;
+          s[r] = pv;
+          dp[r] = pv * (dp[r] - d4[e]);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int qrow = qb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) {
+          dv[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sg[qrow * LD + db * 32 + ln], s[r], dv[db], 0, 0, 0);
+          dk[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sq[qrow * LD + db * 32 + ln], dp[r], dk[db], 0, 0, 0);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const long long at = kv + db * 32 + 8 * q4 + 4 * h;
+      const f32x4 x = {dk[db][q4 * 4], dk[db][q4 * 4 + 1], dk[db][q4 * 4 + 2], dk[db][q4 * 4 + 3]};
+      const f32x4 y = {dv[db][q4 * 4], dv[db][q4 * 4 + 1], dv[db][q4 * 4 + 2], dv[db][q4 * 4 + 3]};
+      *reinterpret_cast<f32x4*>(p.dKp + at) = x * L.scale;
+      *reinterpret_cast<f32x4*>(p.dVp + at) = y;
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 1) void attn_bwd_dq_f32_long_kernel(BwdParams p) {
+  constexpr int LD = D + 8;
+  constexpr int CPR = D / 4, kChunks = kTileN * CPR / kThreads;
+  __shared__ __attribute__((aligned(16))) float sk[kTileN * LD], sv[kTileN * LD];
+  __shared__ int sItem;
+  const Layer& L = p.L;
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  for (;;) {                                 // persistent: one (head, query tile) per iteration
+    __syncthreads();
+    if (threadIdx.x == 0) sItem = sched_next(p.sched, 1);
+    __syncthreads();
+    const int item = sItem;
+    if (item < 0) break;
+    int bh, tq;
+    sched_decode(p.sched, p.order_off, item, bh, tq);
+    const int b = bh / L.Hq, i = bh % L.Hq, nq = p.q_cnt[bh];
+    const int* qlist = p.q_idx + (long long)bh * L.N;
+    const int* qvis = p.qvis + (long long)bh * L.N;
+    const int pos_first = tq * kTileM, pos_last = min(pos_first + kTileM, nq) - 1;
+    const int n_full_tiles = qvis[pos_first] / kTileN, ntiles = cdiv(qvis[pos_last], kTileN);
+    const int qpos = pos_first + wave * 32 + ln, qpos_c = min(qpos, nq - 1), qvisible = qvis[qpos_c] - 4 * h;
+    const float lse2 = p.lse2c[(long long)bh * p.nqpad + qpos_c], delta = p.deltac[(long long)bh * p.nqpad + qpos_c];
+    const long long row_off = b * L.qs[0] + i * L.qs[1] + (long long)qlist[qpos_c] * L.qs[2];
+    f32x4 qf[D / 8], gf[D / 8];
+#pragma unroll
+    for (int ks = 0; ks < D / 8; ++ks) {
+      qf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Q) + row_off + ks * 8 + h * 4);
+      gf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.dO) + row_off + ks * 8 + h * 4);
+    }
+    f32x16 dq[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+    const float* kn = static_cast<const float*>(p.Kn) + (long long)bh * p.npad * D;
+    const float* vn = static_cast<const float*>(p.Vn) + (long long)bh * p.npad * D;
+    for (int t = 0; t < ntiles; ++t) {
+      __syncthreads();
+      u32x4 stK[kChunks], stV[kChunks];
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) {
+        const long long at = (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4;
+        stK[c] = *reinterpret_cast<const u32x4*>(kn + at);
+        stV[c] = *reinterpret_cast<const u32x4*>(vn + at);
+      }
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) {
+        const int ch = threadIdx.x + c * kThreads, at = ch / CPR * LD + ch % CPR * 4;
+        *reinterpret_cast<u32x4*>(sk + at) = stK[c];
+        *reinterpret_cast<u32x4*>(sv + at) = stV[c];
+      }
+      __syncthreads();
+      f32x16 s[2], dp[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f, dp[kb][r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < D / 8; ++ks) {
+          const f32x4 ka = *reinterpret_cast<const f32x4*>(sk + (kb * 32 + ln) * LD + ks * 8 + h * 4);
+          const f32x4 va = *reinterpret_cast<const f32x4*>(sv + (kb * 32 + ln) * LD + ks * 8 + h * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[e], qf[ks][e], s[kb], 0, 0, 0);
+            dp[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[e], gf[ks][e], dp[kb], 0, 0, 0);
+          }
+        }
+      }
+      const bool masked = t >= n_full_tiles;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float pv = fast_exp2(fmaf(s[kb][r], c2, -lse2));
+          if (masked && t * kTileN + kb * 32 + 8 * (r >> 2) + (r & 3) >= qvisible) pv = 0.f;
+          dp[kb][r] = pv * (dp[kb][r] - delta);
+        }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int slot = kb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db)
+            dq[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sk[slot * LD + db * 32 + ln], dp[kb][r], dq[db], 0, 0, 0);
+        }
+    }
+    if (qpos < nq) {
+      float* out = static_cast<float*>(p.dQ) + row_off;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 x = {dq[db][q4 * 4], dq[db][q4 * 4 + 1], dq[db][q4 * 4 + 2], dq[db][q4 * 4 + 3]};
+          *reinterpret_cast<f32x4*>(out + db * 32 + 8 * q4 + 4 * h) = x * L.scale;
+        }
+    }
+  }
 }
 
 // ------------------------------------------------------------------ dQ, bf16 fast path
@@ -1046,16 +1274,18 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   const size_t kvrows = npad_kv > 0 ? (size_t)L.B * L.Hkv * npad_kv : krows;
   w.Kn = a.take<unsigned char>(kvrows * L.D * es);
   w.Vn = a.take<unsigned char>(kvrows * L.D * es);
-  w.Kt = a.take<unsigned char>(kvrows * L.D * es);
-  w.Qt = a.take<unsigned char>(qrows * L.D * es);
-  w.dOt = a.take<unsigned char>(qrows * L.D * es);
-  w.Qn = a.take<unsigned char>(qrows * L.D * es);
-  w.dOn = a.take<unsigned char>(qrows * L.D * es);
+  const bool copies = dtype == OMNI_BF16 || f32_short(L);
+  const size_t planes = copies ? kKeyMaxSplits : 1;
+  w.Kt = a.take<unsigned char>(copies ? kvrows * L.D * es : 4);
+  w.Qt = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
+  w.dOt = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
+  w.Qn = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
+  w.dOn = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
   w.kidx = a.take<int>(krows);
   w.lse2c = a.take<float>(qrows);
   w.deltac = a.take<float>(qrows);
-  w.dKp = a.take<float>(kKeyMaxSplits * krows * L.D);
-  w.dVp = a.take<float>(kKeyMaxSplits * krows * L.D);
+  w.dKp = a.take<float>(planes * krows * L.D);
+  w.dVp = a.take<float>(planes * krows * L.D);
   w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
   w.qvis = a.take<int>(BH * L.N);
   w.kfirst = a.take<int>(krows);
@@ -1095,7 +1325,10 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int npad = bwd_npad(cap_keys), nqpad = bwd_nqpad(L);
   const int npad_kv = BLOCKS ? bwd_npad_kv(L) : 0;
   BwdWs w = carve_bwd(a, L, dt, npad, nqpad, npad_kv, cap_keys / kTileN);
-  const bool split = sizeof(T) == 2 && short_route(attention_work(L) <= kSplitWork);
+  constexpr bool kFast = sizeof(T) == 2;
+  constexpr int tile_m = kFast ? kDqTileM : kTileM;
+  const bool split = kFast ? short_route(attention_work(L) <= kSplitWork) : f32_short(L);      // short sequences: no work list
+  const bool copies = kFast || split;                  // fp32 on long sequences: only K and V, row by row
   int rc;
   if constexpr (BLOCKS) {
     // K, V (natural) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
@@ -1111,12 +1344,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     budget = w.vbudget;
     b_cap = npad;                             // the lists' row pitch; their lengths are in vbudget
   } else {
-    rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, w.Kt, nullptr, w.kidx, st,
-                     split || dt == OMNI_F32);
+    rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, copies ? w.Kt : nullptr, nullptr,
+                     w.kidx, st, split);
     if (rc != OMNI_OK) return rc;
   }
-  rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, w.Qt, w.dOt, w.Qn, w.dOn, w.lse2c,
-                  w.deltac, w.inv, st);
+  rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, copies ? w.Qt : nullptr, copies ? w.dOt : nullptr,
+                  copies ? w.Qn : nullptr, copies ? w.dOn : nullptr, w.lse2c, w.deltac, w.inv, st);
   if (rc != OMNI_OK) return rc;
   BwdParams p;
   p.Q = Q;
@@ -1140,7 +1373,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.deltac = w.deltac;
   p.dKp = w.dKp;
   p.dVp = w.dVp;
-  p.nsplit = kKeyMaxSplits;
+  p.nsplit = kFast || split ? kKeyMaxSplits : 1;
   p.split_len = sizeof(T) == 2 ? g_key_split_len : kKeySplitLenF32;
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
@@ -1153,8 +1386,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_map = w.tile_map;
   p.tile_stride = cap_keys / kTileN;
   p.npad_kv = BLOCKS ? npad_kv : npad;
-  constexpr bool kFast = sizeof(T) == 2;
-  rc = check_work_list(L, kFast ? kDqTileM : kTileM);
+  rc = check_work_list(L, tile_m);
   if (rc != OMNI_OK) return rc;
   {
     Bounds bn{};                                 // masks by position, slot map, cleared rows, the bf16 dQ kernel's work items
@@ -1170,14 +1402,14 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     bn.inv = w.inv;
     bn.X = dQ;
     bn.elem_bytes = sizeof(T);
-    bn.tile_m = kDqTileM;
-    bn.sched = kFast && !split ? w.sched : nullptr;
+    bn.tile_m = tile_m;
+    bn.sched = split ? nullptr : w.sched;
     rc = run_bounds(L, bn, st);
     if (rc != OMNI_OK) return rc;
   }
-  p.order_off = sched_order_off(L.B * L.Hq, L.N, kDqTileM);
-  if (kFast && !split) {
-    rc = run_order(L, q_cnt, kDqTileM, w.sched, st);
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
+  if (!split) {
+    rc = run_order(L, q_cnt, tile_m, w.sched, st);
     if (rc != OMNI_OK) return rc;
   }
   {
@@ -1199,9 +1431,11 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
       OMNI_LAUNCH_CHECK();
       hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 0, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
     } else {
-      hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),
-                         dim3(kF32Threads<D>),
-                         0, st, p);
+      if (split)
+        hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),
+                           dim3(kF32Threads<D>), 0, st, p);
+      else
+        hipLaunchKernelGGL((attn_bwd_key_f32_long_kernel<D>), dim3(npad / kF32Keys, L.B * L.Hq), dim3(kThreads), 0, st, p);
     }
     OMNI_LAUNCH_CHECK();
   }
@@ -1213,9 +1447,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
                            dim3(kSplitThreads), 0, st, p);
       else
         hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
-    } else
+    } else if (split) {
       hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)), dim3(kF32Threads<D>),
                          0, st, p);
+    } else {
+      hipLaunchKernelGGL((attn_bwd_dq_f32_long_kernel<D>), dim3(persistent_grid() / 2), dim3(kThreads), 0, st, p);
+    }
     OMNI_LAUNCH_CHECK();
   }
   {

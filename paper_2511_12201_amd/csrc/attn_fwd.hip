@@ -29,8 +29,9 @@
 //    longest-first work list with one queue per XCD (sched.hip); causal masks are
 //    position compares against per-query visible-prefix counts (pack.hip).
 //    Short sequences go through attn_fwd_split_kernel: 32-row items, key tiles dealt to the wavefronts.
-//  * fp32 inputs (attn_fwd_f32_kernel, the accuracy path of the 1e-4 parity cases): the division of labour of the split
-//    kernel on the fp32 32x32x2 MFMA.
+//  * fp32 inputs (the accuracy path of the 1e-4 parity cases): the fp32 32x32x2 MFMA.  Short sequences
+//    (attn_fwd_f32_kernel) have the division of labour of the split kernel, long ones (attn_fwd_f32_long_kernel) 128-row
+//    work items with the tiles in LDS.
 
 #include <type_traits>
 
@@ -55,8 +56,8 @@ struct FwdParams {
   Layer L;
   const int* q_idx;     // [B*Hq, N] kept query rows, ascending; nullptr: all rows
   const int* q_cnt;     // [B*Hq]; nullptr: N
-  const void* Kp;       // packed keys  [BHx, npad, D]
-  const void* Vp;       // packed values, tile layout (bf16) or row-major (fp32)
+  const void* Kp;       // packed keys  [BHx, npad, D]: row-major, or in fragment order (short sequences)
+  const void* Vp;       // packed values: k-packed, or row-major (fp32 on long sequences)
   const int* kidx;      // [BHx, npad] original token index of every slot
   const int* budget;    // [B] (or [B,Hq] when L.bph) number of packed keys (device); nullptr: N
   int b_cap;
@@ -802,6 +803,132 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_fwd_f32_k
   }
 }
 
+// fp32, long sequences: 128-row items from the work list, 32 rows per wavefront, K/V tiles staged row by row through LDS.  An
+// item of 32 rows streams its whole K/V prefix for itself, and once the 128-row items fill the chip that is what costs
+// (f32_short says where the line lies).
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void attn_fwd_f32_long_kernel(FwdParams p) {
+  constexpr int KLD = D + 4, VLD = D + 8;            // row pitches of the tiles
+  constexpr int CPR = D / 4, kChunks = kTileN * CPR / kThreads;      // 16-byte chunks per row, per thread and operand
+  __shared__ __attribute__((aligned(16))) float sK[kTileN * KLD], sV[kTileN * VLD];
+  __shared__ int sItem;
+  const Layer& L = p.L;
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  for (;;) {                                         // persistent: one work item (head, query tile) per iteration
+    __syncthreads();                                 // LDS of the previous item is no longer read
+    if (threadIdx.x == 0) sItem = sched_next(p.sched, 1);
+    __syncthreads();
+    const int item = sItem;
+    if (item < 0) break;
+    int bh, tq;
+    sched_decode(p.sched, p.order_off, item, bh, tq);
+    const int b = bh / L.Hq, i = bh % L.Hq, g = i / L.G;
+    const int nq = p.q_cnt ? p.q_cnt[bh] : L.N;
+    const int* qlist = p.q_idx ? p.q_idx + (long long)bh * L.N : nullptr;       // null: all rows, all keys (dense baseline)
+    const int* qvis = p.qvis ? p.qvis + (long long)bh * L.N : nullptr;
+    auto visible = [&](int pos) { return qvis ? qvis[pos] : (L.causal ? pos + 1 : L.N); };
+    const int pos_first = tq * kTileM, pos_last = min(pos_first + kTileM, nq) - 1;
+    const int n_full_tiles = visible(pos_first) / kTileN, ntiles = cdiv(visible(pos_last), kTileN);
+    const int qpos = pos_first + wave * 32 + ln, qpos_c = min(qpos, nq - 1);
+    const int qrow = qlist ? qlist[qpos_c] : qpos_c, qvisible = visible(qpos_c) - 4 * h;
+    const long long row_off = b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
+    f32x4 qf[D / 8];
+#pragma unroll
+    for (int ks = 0; ks < D / 8; ++ks) qf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Q) + row_off + ks * 8 + h * 4);
+    f32x16 o[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    const long long head = (long long)(p.per_q_head ? bh : b * L.Hkv + g) * p.npad * D;
+    const float *kp = static_cast<const float*>(p.Kp) + head, *vp = static_cast<const float*>(p.Vp) + head;
+    for (int t = 0; t < ntiles; ++t) {
+      __syncthreads();
+      u32x4 stK[kChunks], stV[kChunks];
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) stK[c] = *reinterpret_cast<const u32x4*>(kp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) stV[c] = *reinterpret_cast<const u32x4*>(vp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) {
+        const int ch = threadIdx.x + c * kThreads, row = ch / CPR, col = ch % CPR * 4;
+        *reinterpret_cast<u32x4*>(sK + row * KLD + col) = stK[c];
+        *reinterpret_cast<u32x4*>(sV + row * VLD + col) = stV[c];
+      }
+      __syncthreads();
+      f32x16 s[2];                                   // S^T tile = K tile . Q^T
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < D / 8; ++ks) {
+          const f32x4 kf = *reinterpret_cast<const f32x4*>(sK + (kb * 32 + ln) * KLD + ks * 8 + h * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[ks][e], s[kb], 0, 0, 0);
+        }
+      }
+      if (t >= n_full_tiles) {
+        const int rel = qvisible - t * kTileN;       // keys of this tile at positions >= rel are hidden (pad rows too)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kb * 32 + 8 * (r >> 2) + (r & 3) >= rel) s[kb][r] = -INFINITY;
+      }
+      float m = s[0][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) m = fmaxf(m, s[kb][r]);
+      m = fmaxf(m_run, pair_max(m));
+      const float m_ref = m == -INFINITY ? 0.f : m, mc = m_ref * c2;
+      if (__any(m > m_run)) {
+        const float alpha = fast_exp2((m_run - m_ref) * c2);
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        m_run = m;
+      }
+      float lsum = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          s[kb][r] = fast_exp2(fmaf(s[kb][r], c2, -mc));
+          lsum += s[kb][r];
+        }
+      l_run += lsum;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)                 // O^T += V^T . P^T
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int slot = kb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db)
+            o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(sV[slot * VLD + db * 32 + ln], s[kb][r], o[db], 0, 0, 0);
+        }
+    }
+    const float l_tot = pair_sum(l_run), inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    if (qpos < nq) {
+      float* out = static_cast<float*>(p.O) + row_off;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 w = {o[db][q4 * 4] * inv, o[db][q4 * 4 + 1] * inv, o[db][q4 * 4 + 2] * inv, o[db][q4 * 4 + 3] * inv};
+          *reinterpret_cast<f32x4*>(out + db * 32 + 8 * q4 + 4 * h) = w;
+        }
+      if (h == 0) p.lse[(long long)bh * L.N + qrow] = l_tot > 0.f ? (m_run * c2 + log2f(l_tot)) * kLn2 : -INFINITY;
+    }
+  }
+}
+
 // Which of the two bf16 kernels: the bytes an item streams alone make the split kernel the slower one once the work per
 // CU outweighs the length of a chain.  Whole attention call in us, (heads, d) N: split / the other, a third of the
 // queries and half of the keys kept: (28, 128) 1072: 30 / 55, 3101: 60 / 83, 4096: 85 / 100, 6000: 134 / 129,
@@ -879,12 +1006,14 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const int heads = sparse ? L.Hq : L.Hkv;
   const int npad = fwd_npad(sparse ? b_cap : L.N);
   FwdWs w = carve_fwd(a, L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, heads, npad, sparse);
-  const bool split = sparse && sizeof(T) == 2 && short_route(attention_work(L) <= kSplitWork);
+  // short sequences: 32-row items without a work list
+  const bool split = sizeof(T) == 2 ? sparse && short_route(attention_work(L) <= kSplitWork) : f32_short(L);
   {
     const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
-    // K natural or in fragment order, V k-packed (bf16: converted to f16)
-    int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp, nullptr, nullptr,
-                         w.Vp, w.kidx, st, split || sizeof(T) == 4);
+    // K natural or in fragment order; V k-packed (bf16: converted to f16), for fp32 on long sequences natural
+    const bool v_rows = sizeof(T) == 4 && !split;
+    int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp,
+                         v_rows ? w.Vp : nullptr, nullptr, v_rows ? nullptr : w.Vp, w.kidx, st, split);
     if (rc != OMNI_OK) return rc;
   }
   FwdParams p;
@@ -907,30 +1036,34 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_map = nullptr;
   p.tile_stride = 0;
   constexpr bool kFast = sizeof(T) == 2;
-  p.order_off = sched_order_off(L.B * L.Hq, L.N, kFastTileM);
+  constexpr int tile_m = kFast ? kFastTileM : kTileM;
+  p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
   int rc = OMNI_OK;
-  rc = check_work_list(L, kFast ? kFastTileM : kTileM);
+  rc = check_work_list(L, tile_m);
   if (rc != OMNI_OK) return rc;
   if (sparse) {
-    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, kFastTileM,
-                        kFast && !split ? w.sched : nullptr, st);
+    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m,
+                        split ? nullptr : w.sched, st);
     if (rc != OMNI_OK) return rc;
   }
-  if constexpr (kFast) {
-    if (split) return launch_split<D, false>(p, st);
-    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
-    // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
-    // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
-    // costs (25.7 -> 25.9 ms dense).
-    rc = sparse ? run_order(L, q_cnt, kFastTileM, w.sched, st, kSchedQueues)
-                : run_schedule(L, q_cnt, budget, b_cap, kFastTileM, w.sched, st);
-    if (rc != OMNI_OK) return rc;
+  if (split) {
+    if constexpr (kFast) return launch_split<D, false>(p, st);
+    ProfScope prof__(kProfAttnFwd, st);
+    if constexpr (!kFast) hipLaunchKernelGGL((attn_fwd_f32_kernel<D>), dim3(split_grid(L)), dim3(kSplitThreads), 0, st, p);
+    OMNI_LAUNCH_CHECK();
+    return OMNI_OK;
   }
+  // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
+  // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
+  // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
+  // costs (25.7 -> 25.9 ms dense).
+  rc = sparse ? run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1) : run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
+  if (rc != OMNI_OK) return rc;
   ProfScope prof__(kProfAttnFwd, st);
   if constexpr (kFast)
     hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, false>), dim3(persistent_grid() / 2), dim3(kFastThreads), 0, st, p);
   else
-    hipLaunchKernelGGL((attn_fwd_f32_kernel<D>), dim3(split_grid(L)), dim3(kSplitThreads), 0, st, p);
+    hipLaunchKernelGGL((attn_fwd_f32_long_kernel<D>), dim3(persistent_grid()), dim3(kThreads), 0, st, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }

@@ -39,8 +39,7 @@ size_t probe_ws(const Layer& L, int dtype, int pb);
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
               hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
 
-// pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values; fp32: Kn, Vn with k_frag, Qn, dOn always in
-// fragment order)
+// pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values; fp32: Qn, dOn in fragment order)
 // k_frag: Kn, Vn in the order of a 32x32 MFMA's A operand instead of row by row, [32-row block][k step][lane] of 16 bytes
 // (lane = 32 * half + row; a k step is 16 bf16 or 8 fp32 values wide)
 int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
@@ -55,6 +54,19 @@ int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const vo
 int attention_route();                       // omni_debug_attention_route of this thread; 0: by the shape
 inline bool short_route(bool by_shape) { return attention_route() ? attention_route() == 1 : by_shape; }
 inline double attention_work(const Layer& L) { return (double)L.B * L.Hq * L.N * L.N * L.D * (L.causal ? 1.0 : 2.0); }
+// fp32, forward and backward: 32-row items whose wavefronts share the other side (as short sequences need them), or 128-row
+// items with tiles in LDS.  The long items are the faster ones once they fill the chip, which their number decides (rows of
+// all heads, twice as many without the causal mask: each works twice as long); the longer the sequence, the longer the chains
+// that the short items save; below 1400 tokens there is little to save and the width counts (at d = 128 one workgroup of the
+// short items fills a CU).  Call in us, short / long items; batch x heads, d, N; a third of the queries and half of the keys kept, or all
+// (full).  Forward and backward, below the lines: 1 x 28, 128, 1072 289 / 671 and (full) 634 / 919; 6 x 28, 128, 256 251 / 357 and
+// (full) 417 / 450; 1 x 28, 128, 3500 1562 / 1983 and (full) 4712 / 4918; 1 x 8, 128, 8192 4300 / 4407 and (full) 6339 / 8282; above
+// them: 8 x 28, 128, 256 319 / 385 but (full) 537 / 519; 1 x 28, 128, 4096 2002 / 2356 but (full) 6183 / 6132; 1 x 8, 128, 10000 6226 / 5405;
+// 1 x 28, 128, 8192 6860 / 5747 and (full) 24707 / 21438; forward 16 x 28, 128, 512 (full) 681 / 521.
+inline bool f32_short(const Layer& L) {
+  const double rows = (double)L.B * L.Hq * L.N * (L.causal ? 1.0 : 2.0);
+  return short_route(L.N < 1400 ? rows * L.D <= 6.0e6 : rows <= (L.N <= 3500 ? 9.8e4 : 6.6e4));
+}
 size_t attn_fwd_ws(const Layer& L, int dtype, int b_cap, bool sparse);
 int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const void* V, const int* q_idx,
                  const int* q_cnt, const int* kv_idx, const int* budget, int b_cap, void* O, float* lse, void* ws,

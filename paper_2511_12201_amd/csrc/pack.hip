@@ -149,10 +149,9 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
     if (Kt && unit-- == 0) transposed(kbase, Kt, false);
     if (Vt && unit-- == 0) transposed(vbase, Vt, true);
   } else {
-    // always in fragment order
 #pragma unroll                                      // all loads of a thread in flight together
     for (int c = threadIdx.x; c < kTileN * CPR; c += kThreads) {
-      const int r32 = c & 31, chunk = c / 32 % CPR, row = c / (32 * CPR) * 32 + r32;
+      const int row = k_frag ? c / (32 * CPR) * 32 + (c & 31) : c / CPR, chunk = k_frag ? c / 32 % CPR : c % CPR;
       const int id = sIdx[row];
       const long long src = (long long)id * L.ks[2] + chunk * E;
       u32x4 k = zero, v = zero;
@@ -277,6 +276,7 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
       const int which = it0 / kItems, dc = it0 % (D / 4), grp = it0 % kItems / (D / 4);
       const T* src = (which ? dO : Q) + head_off;
       T* dst_t = which ? dOt : Qt;
+      if (!dst_t) break;                               // both or neither
       u32x4 in[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {

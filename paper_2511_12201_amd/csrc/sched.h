@@ -71,9 +71,11 @@ int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap,
 int persistent_grid();      // workgroups that fill the device at two per CU
 
 // Called by one thread.  Position in the hand-out order of the next item, or -1 when every queue is drained:
-// the workgroup's own queue (its XCD's) while it lasts, then whichever queue has the most items left.
-__device__ __forceinline__ int sched_next(int* __restrict__ sched) {
-  const int home = blockIdx.x % kSchedQueues;
+// the workgroup's own queue (its XCD's) while it lasts, then whichever queue has the most items left.  queues = 1: a list
+// that is known to be one queue, where nobody should come late because its XCD's is empty (with two workgroups per CU the
+// first XCD would take two of the longest items to each of its CUs: fp32 forward, 8 heads, d = 128, 10000 tokens 1380 -> 1210 us).
+__device__ __forceinline__ int sched_next(int* __restrict__ sched, int queues = kSchedQueues) {
+  const int home = blockIdx.x % queues;
   {
     const int end = sched[kSchedEnd + home];
     if (__atomic_load_n(sched + kSchedCursor + home, __ATOMIC_RELAXED) < end) {

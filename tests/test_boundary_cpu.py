@@ -314,3 +314,13 @@ def test_queued_work_list_places_whole_heads_and_balances_the_queues(lib, q_cnt,
             sim_order[q].append(h)
     assert sim_order == order_in_queue
     assert loads == sim_load
+
+
+@pytest.mark.parametrize("tokens,units", [(16384, 4), (1072, 15)])
+def test_scratch_of_the_fp32_backward(lib, tokens, units):
+    """Long sequences keep K, V and one plane of dK', dV'; short ones copies of Q and dO and four planes too.  A unit is one
+    row per query head and token; a sixth more for padding, lists and per-row values."""
+    d = ob.LayerDesc(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=64, n_tokens=tokens, vis_begin=0, vis_end=tokens, sink_index=0,
+                     causal=1, dtype=ob.OMNI_F32, softmax_scale=0.125, q_stride=(8 * tokens * 64, tokens * 64, 64),
+                     kv_stride=(2 * tokens * 64, tokens * 64, 64))
+    assert units <= ob.workspace_bytes(ob.CALL_SPARSE_ATTN_BWD, d, tokens) / (8 * tokens * 64 * 4) <= units * 7 / 6 + 0.5
