@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kThreads) void block_rows_kernel(const float* __res
     const float cm = block_tokens(m, block, N);
 #pragma unroll
     for (int r = 0; r < kRowsPerWg; ++r) {
-      if (causal && m > j0 + r) continue;
       const float l = dot[r] * c2, top = fmaxf(mx[r], l);
+      if ((causal && m > j0 + r) || l == -INFINITY) continue;      // no weight (and no maximum to compare with)
       sum[r] = sum[r] * exp2f(mx[r] - top) + cm * exp2f(l - top);
       mx[r] = top;
     }
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kThreads) void block_rows_kernel(const float* __res
 #pragma unroll
   for (int r = 0; r < kRowsPerWg; ++r) {
     const float top = wave_max(mx[r]);
-    const float part = wave_sum(mx[r] == -INFINITY ? 0.f : sum[r] * exp2f(mx[r] - top));
+    const float part = wave_sum(sum[r] == 0.f ? 0.f : sum[r] * exp2f(mx[r] - top));    // a NaN logit stays in the sum
     if (lane_id() == 0) sm[r][wave] = top, ss[r][wave] = part;
   }
   __syncthreads();
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void block_rows_kernel(const float* __res
 #pragma unroll
     for (int w = 1; w < kThreads / 64; ++w) top = fmaxf(top, sm[r][w]);
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) part += sm[r][w] == -INFINITY ? 0.f : ss[r][w] * exp2f(sm[r][w] - top);
+    for (int w = 0; w < kThreads / 64; ++w) part += ss[r][w] == 0.f ? 0.f : ss[r][w] * exp2f(sm[r][w] - top);
     stats[(long long)bh * nblk + j0 + r] = make_float2(top, block_tokens(j0 + r, block, N) / part);
   }
 }

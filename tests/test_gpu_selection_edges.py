@@ -72,6 +72,39 @@ def test_lists_with_infinite_negative_and_nan_scores():
             np.testing.assert_array_equal(kv[0, h, :b], np.sort(order[:b]))
 
 
+@pytest.mark.parametrize("block", [1, 64])
+@pytest.mark.parametrize("causal", [True, False])
+def test_block_scores_with_keys_that_are_not_finite(block, causal):
+    """A key at -inf on a coordinate where every query is positive has no weight in any row, and the other scores are those of
+    64-bit softmaxes without it; a NaN key makes every row that sees it NaN.  700 blocks: several per thread."""
+    N, H, d = 700, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(1)
+    Q = torch.randn(1, H, N, d, generator=g, device="cuda").bfloat16()
+    K = torch.randn(1, 1, N, d, generator=g, device="cuda").bfloat16()
+    Q[..., 0] = Q[..., 0].abs() + 0.1
+    desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
+    nb = -(-N // block)
+    ends = torch.arange(block, N + block, block, device="cuda").clamp(max=N)
+    width = torch.diff(ends, prepend=ends.new_zeros(1)).double()
+    pool = lambda x: torch.stack([x[..., j * block: (j + 1) * block, :].double().mean(-2) for j in range(nb)], -2)  # noqa: E731
+    K2 = K.clone()
+    K2[..., 0, 0] = -float("inf")
+    z = pool(Q)[0] @ pool(K2)[0, 0].T * d ** -0.5 + width.log()
+    if causal:
+        z = z.masked_fill(torch.ones(nb, nb, dtype=torch.bool, device="cuda").triu(1), -float("inf"))
+    first = 1 if causal else 0                                   # causal: the first row sees that key only
+    want = width[first:] @ torch.softmax(z[:, first:], -1) * (nb / N)
+    got = ob.omni_block_scores(desc, Q, K2, block)[0]
+    if causal:
+        assert bool(torch.isnan(got[:, 0]).all())                              # as the first row's softmax
+        got, want = got[:, 1:], want[:, 1:]
+    else:
+        assert not got[:, 0].any()
+    assert float((got.double() - want).abs().max()) <= 1e-4 * float(want.max())       # the key scores' bar
+    K2[..., 0, 0] = float("nan")
+    assert bool(torch.isnan(ob.omni_block_scores(desc, Q, K2, block)).all())
+
+
 def test_padded_batch_with_scratch_for_one_sequence_gives_the_same():
     """A workspace for one sequence takes a batch one sequence at a time: the outputs of the batch in one go."""
     B, H, Hkv, N, D = 3, 4, 2, 700, 64
