@@ -187,7 +187,9 @@ int omni_kv_budget(const omni_layer_desc* desc, const void* Q, const void* K,
  * omni_budget_from_scores -- the second half of omni_kv_budget on key scores
  * the caller already holds (same section: kurtosis, flattest head, budget
  * equation, per-head recall).  Arguments as in omni_kv_budget; key_scores is an
- * input here.
+ * input here: the mass of a head's positive scores counts, up to a sum of 2^24 (the
+ * scores of omni_kv_budget sum to n_tokens); a score that reaches the recall target by
+ * itself, infinite or not, makes the head's budget 1.
  */
 int omni_budget_from_scores(const omni_layer_desc* desc, const float* key_scores,
                             float recall_p, int budget_mode,

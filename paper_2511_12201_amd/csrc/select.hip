@@ -60,16 +60,17 @@ struct __attribute__((aligned(16))) RadixShared {
   unsigned few_key[kFew];
   unsigned long long few_mass[kFew];
   unsigned long long wave_tot[kSelWaves];
-  unsigned long long rem, above;
+  unsigned long long rem;
   unsigned key;
-  int count, found;
+  int count, found, alone;
 };
 
 struct RadixCut {
   bool found;                           // false: the whole vector falls short of the target
+  bool alone;                           // mass: the largest element reaches the target by itself, the rest is not set
   unsigned key;                         // the cut: key of the last element taken
   unsigned long long rem;               // count (or mass) still to take among the elements equal to the cut
-  unsigned long long above, other;      // count / mass of the elements above the cut: the target's kind, the other kind
+  unsigned long long other;             // mass (or count) of the elements above the cut
 };
 
 __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, RadixShared& sh) {
@@ -107,15 +108,14 @@ __device__ __forceinline__ void histogram_clear(RadixShared& sh, int reps) {
   const int words = reps * kPitch * (MASS ? 2 : 1);
   for (int t = 4 * threadIdx.x; t < words; t += 4 * kSelThreads)
     *reinterpret_cast<u32x4*>(&sh.cnt[t]) = u32x4{0u, 0u, 0u, 0u};
-  if (threadIdx.x == 0) sh.found = 0;
+  if (threadIdx.x == 0) sh.found = 0, sh.alone = 0;
 }
 template <bool MASS>
 __device__ __forceinline__ void histogram_add(RadixShared& sh, int rep, unsigned digit, float value) {
   if (MASS) atomicAdd(&sh.sum[rep + digit], to_fixed(value));
   else atomicAdd(&sh.cnt[rep + digit], 1u);
 }
-// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem and sh.above
-// moved on to it.  Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
+// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem moved on to it.  Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
 template <bool MASS>
 __device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int shift) {
   __syncthreads();
@@ -142,7 +142,6 @@ __device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int sh
     const bool second = excl + c0 < rem;
     sh.found = 1;
     sh.key |= (unsigned)(kBins - 1 - 2 * (int)threadIdx.x - (second ? 1 : 0)) << shift;
-    sh.above += excl + (second ? c0 : 0);
     sh.rem = rem - excl - (second ? c0 : 0);
   }
   __syncthreads();
@@ -158,7 +157,6 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
   if (threadIdx.x == 0) {
     sh.key = 0;
     sh.rem = target;
-    sh.above = 0;
   }
   const float* src = x;                            // the elements that can still be the cut are among these m
   int m = n, reps = kRep, left = n;
@@ -173,14 +171,20 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
     __syncthreads();
     const unsigned before = sh.key;
     const int rep = ((int)threadIdx.x & (reps - 1)) * kPitch;
+    float top = 0.f;
     sweep(src, m, [&](const Batch& v, int) {
 #pragma unroll
       for (int e = 0; e < kBatch; ++e) {
         const unsigned key = float_key(v[e]);
         if (((key ^ before) & fixed) == 0) histogram_add<MASS>(sh, rep, (key >> shift) & digit, v[e]);
+        if (MASS) top = fmaxf(top, v[e]);
       }
     });
-    if (!histogram_pick<MASS>(sh, reps, shift)) return RadixCut{false, 0u, 0ull, 0ull, 0ull};   // first pass only
+    // infinite and huge elements: the sums may have left 64 bits
+    if (MASS && (top >= 16777216.f || to_fixed(top) >= target)) sh.alone = 1;
+    const bool found = histogram_pick<MASS>(sh, reps, shift);
+    if (MASS && sh.alone) return RadixCut{true, true, 0u, 0ull, 0ull};
+    if (!found) return RadixCut{false, false, 0u, 0ull, 0ull};                                  // first pass only
     // What lies above the bin is taken whole, what lies in it is copied to LDS as far as it fits: the first time to the
     // long list, from there to the short one.
     const unsigned cut = sh.key;
@@ -229,7 +233,7 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
     // Every element left against every other: the one whose own share crosses sh.rem is the cut (equal elements all
     // write the same values).
     const float* few = src == sh.cand ? sh.cand : sh.few;
-    const unsigned long long rem = sh.rem, above = sh.above;
+    const unsigned long long rem = sh.rem;
     __syncthreads();
     if ((int)threadIdx.x < left) {
       const float own = few[threadIdx.x];
@@ -254,14 +258,13 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
       if (excl < rem && rem <= excl + own) {
         sh.key = mine;
         sh.rem = rem - excl;
-        sh.above = above + excl;
       }
     }
     __syncthreads();
     if ((int)threadIdx.x < left && mine > sh.key) other += MASS ? 1ull : sh.few_mass[threadIdx.x];
   }
   other = block_sum(other, sh);
-  const RadixCut cut{true, sh.key, sh.rem, sh.above, other};
+  const RadixCut cut{true, false, sh.key, sh.rem, other};
   __syncthreads();                                 // sh may be used again
   return cut;
 }
@@ -332,9 +335,11 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
     const RadixCut cut = radix_cut<true>(x, N, target, true, sh);
     if (threadIdx.x == 0) {
       int r = N;                                // even the whole vector falls short: take everything
-      if (cut.found) {
+      if (cut.alone) {
+        r = 1;
+      } else if (cut.found) {
         const unsigned long long v = to_fixed(key_value(cut.key));   // > 0: its bin crossed the target
-        r = (int)min((unsigned long long)N, cut.other + (cut.rem + v - 1) / v);
+        r = max(1, (int)min((unsigned long long)N, cut.other + (cut.rem + v - 1) / v));
       }
       own[bh] = r;
     }

@@ -72,6 +72,29 @@ def test_lists_with_infinite_negative_and_nan_scores():
             np.testing.assert_array_equal(kv[0, h, :b], np.sort(order[:b]))
 
 
+@pytest.mark.parametrize("N", [700, 8193, 20001])
+@pytest.mark.parametrize("value", [float("inf"), 3.0e38, 2.0e7, "just", "just_not"])
+def test_budget_where_one_score_outweighs_the_target(N, value):
+    """A score that reaches recall * N by itself is the whole budget; so it is with several of them, in every head that has one;
+    the other heads' budgets do not move.  At the target exactly, and one step of the float grid below."""
+    H, rng = 3, np.random.default_rng(N)
+    a, p = _scores("lognormal", rng, H, N), 0.75
+    target = np.float32(p * N)                          # exact in float32
+    v = {"just": target, "just_not": np.nextafter(target, np.float32(0))}.get(value, value)
+    d = _desc(H, N, 0, N)
+    plain = ob.omni_budget_from_scores(d, torch.from_numpy(a).cuda(), p, 2).budget.cpu().numpy()
+    for at in ([N // 3], [0, N // 2, N - 1]):
+        b = a.copy()
+        b[0, 1, at] = v
+        r = ob.omni_budget_from_scores(d, torch.from_numpy(b).cuda(), p, 2).budget
+        want = oc.budget_of(b[0, 1], p, N)
+        assert want == (2 if value == "just_not" else 1)
+        assert r[0].tolist() == [plain[0, 0], want, plain[0, 2]]
+        kv = ob.omni_select_kv_per_head(d, torch.from_numpy(b).cuda(), r, N)
+        assert kv[0, 1, :want].tolist()[0] in at or want == 2
+        assert int(ob.omni_budget_from_scores(d, torch.from_numpy(b).cuda(), p, 1).budget[0]) == plain[0, [0, 2]].max()
+
+
 @pytest.mark.parametrize("block", [1, 64])
 @pytest.mark.parametrize("causal", [True, False])
 def test_block_scores_with_keys_that_are_not_finite(block, causal):
