@@ -317,19 +317,37 @@ __device__ __forceinline__ void classify(const KeepRule& r, int h, bool inside, 
 
 // ------------------------------------------------------------------ kernels
 
+// Wavefront-wide argmin over the heads' kurtoses: heads within 1e-9 (relative) of the smallest tie and the lowest index
+// wins (for two or three scores the statistic is one constant for every head and rounding would pick the head).
+__device__ __forceinline__ int flattest_head(const double* __restrict__ kurt, int H) {
+  double v = kurt[0];
+  for (int h = lane_id(); h < H; h += 64) v = fmin(v, kurt[h]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+  const double bar = v + 1e-9 * fabs(v);
+  for (int h0 = 0; h0 < H; h0 += 64) {
+    const int h = h0 + lane_id();
+    const unsigned long long bal = __ballot(h < H && kurt[h] <= bar);
+    if (bal) return h0 + __ffsll((long long)bal) - 1;
+  }
+  return H - 1;
+}
+
 // grid: (H, B, 2).  Of every head's own scores: excess kurtosis m4/m2^2 - 3 in fp64 with a fixed reduction tree (z = 0),
 // and the smallest count whose largest elements reach recall_p of the mass (z = 1).  Every head finds its budget
 // although the shared budget needs the flattest head's only: the heads run side by side, and the search does not wait
 // for the arg-min.
+// only_flattest: grid (1, B), the budget of every sequence's flattest head, after a launch of (H, B, 1) (see launch_stats).
 __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* __restrict__ a, Layer L, Ragged rg,
-                                                                 double recall_p, double* __restrict__ kurt,
-                                                                 int* __restrict__ own) {
+                                                                 double recall_p, int only_flattest,
+                                                                 double* __restrict__ kurt, int* __restrict__ own) {
   __shared__ RadixShared sh;
   __shared__ double red[2][kSelWaves];
-  const int b = blockIdx.y, bh = b * L.Hq + blockIdx.x;
+  const int b = blockIdx.y, head = only_flattest ? flattest_head(kurt + (long long)b * L.Hq, L.Hq) : (int)blockIdx.x;
+  const int bh = b * L.Hq + __builtin_amdgcn_readfirstlane(head);
   const int N = seq_len(L, rg, b);
   const float* x = a + (long long)bh * L.ld;
-  if (blockIdx.z) {
+  if (blockIdx.z || only_flattest) {
     // rounded up: the truncated element masses must never reach a target below the real one
     const unsigned long long target = (unsigned long long)ceil(recall_p * (double)N * kFixScale);
     const RadixCut cut = radix_cut<true>(x, N, target, true, sh);
@@ -386,22 +404,6 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
     const double m2 = t2 / (double)N, m4 = t4 / (double)N;
     kurt[bh] = m2 > 0.0 ? m4 / (m2 * m2) - 3.0 : -2.0;
   }
-}
-
-// Wavefront-wide argmin over the heads' kurtoses: heads within 1e-9 (relative) of the smallest tie and the lowest index
-// wins (for two or three scores the statistic is one constant for every head and rounding would pick the head).
-__device__ __forceinline__ int flattest_head(const double* __restrict__ kurt, int H) {
-  double v = kurt[0];
-  for (int h = lane_id(); h < H; h += 64) v = fmin(v, kurt[h]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  const double bar = v + 1e-9 * fabs(v);
-  for (int h0 = 0; h0 < H; h0 += 64) {
-    const int h = h0 + lane_id();
-    const unsigned long long bal = __ballot(h < H && kurt[h] <= bar);
-    if (bal) return h0 + __ffsll((long long)bal) - 1;
-  }
-  return H - 1;
 }
 
 // grid: (H, B, jobs).  Per head: how many elements to take, the cut (threshold key, number of cut-valued elements to
@@ -669,12 +671,24 @@ int launch_write(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, 
   return OMNI_OK;
 }
 
+// A shared budget (mode 0) needs the flattest head's own only.  While the heads are fewer than the CUs the search of all of
+// them beside the kurtoses costs nothing and saves a launch; with more it is work that nobody asked for.  Both lists, all heads /
+// the flattest in a launch of its own, us: 4 sequences of 28 heads, 8192 tokens 60.5 / 68.4, 8 69.6 / 72.3, 12 (4096 tokens)
+// 107.8 / 104.7, 32 240 / 220, 64 (2048 tokens) 362 / 305.
+constexpr int kBudgetHeads = 256;
+
 // kurtosis and own budgets of all heads, and where the counts of the key lists come from
 int launch_stats(const Layer& L, const Ragged& rg, const float* key_scores, float recall_p, int budget_mode, double* kurt,
                  int* own, int* flattest, int* budget, float* recall, int k_cap, KeySource* src, hipStream_t st) {
-  hipLaunchKernelGGL(score_stats_kernel, dim3(L.Hq, L.B, 2), dim3(kSelThreads), 0, st, key_scores, L, rg, (double)recall_p,
-                     kurt, own);
+  const bool after = budget_mode == 0 && L.B * L.Hq > kBudgetHeads;
+  hipLaunchKernelGGL(score_stats_kernel, dim3(L.Hq, L.B, after ? 1 : 2), dim3(kSelThreads), 0, st, key_scores, L, rg,
+                     (double)recall_p, 0, kurt, own);
   OMNI_LAUNCH_CHECK();
+  if (after) {
+    hipLaunchKernelGGL(score_stats_kernel, dim3(1, L.B), dim3(kSelThreads), 0, st, key_scores, L, rg, (double)recall_p, 1, kurt,
+                       own);
+    OMNI_LAUNCH_CHECK();
+  }
   *src = KeySource{};
   src->mode = budget_mode;
   src->own = own;

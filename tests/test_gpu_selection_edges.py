@@ -72,6 +72,25 @@ def test_lists_with_infinite_negative_and_nan_scores():
             np.testing.assert_array_equal(kv[0, h, :b], np.sort(order[:b]))
 
 
+@pytest.mark.parametrize("B", [64, 65])
+def test_shared_budget_with_fewer_and_more_heads_than_the_search_of_all_takes(B):
+    """256 heads and 260: the budgets, flattest heads and recalls of every sequence are those of the sequence alone, bit for bit."""
+    H, N, rng = 4, 300, np.random.default_rng(B)
+    a = torch.from_numpy(np.concatenate([_scores("lognormal", rng, H, N) for _ in range(B)])).cuda()
+    q = torch.empty(B, H, N, 64, dtype=torch.bfloat16, device="cuda")
+    d = ob.make_layer_desc(q, q, 0, N, 0, True)
+    r = ob.omni_budget_from_scores(d, a, 0.9, 0)
+    kv = ob.omni_select_kv(d, a, r.budget, N)
+    one = ob.make_layer_desc(q[:1], q[:1], 0, N, 0, True)
+    for b in (0, 1, B // 2, B - 1):
+        s = ob.omni_budget_from_scores(one, a[b:b + 1], 0.9, 0)
+        for x, y in ((r.budget, s.budget), (r.flattest, s.flattest), (r.kurtosis, s.kurtosis), (r.recall, s.recall)):
+            assert torch.equal(x[b], y[0])
+        n = int(s.budget[0])
+        assert n == oc.budget_of(a[b, int(s.flattest[0])].cpu().numpy(), 0.9, N)
+        assert torch.equal(kv[b, :, :n], ob.omni_select_kv(one, a[b:b + 1], s.budget, N)[0, :, :n])
+
+
 @pytest.mark.parametrize("N", [700, 8193, 20001])
 @pytest.mark.parametrize("value", [float("inf"), 3.0e38, 2.0e7, "just", "just_not"])
 def test_budget_where_one_score_outweighs_the_target(N, value):
