@@ -261,8 +261,8 @@ int omni_sparse_prefill(const omni_layer_desc* desc, const void* Q, const void* 
  * entries beyond a sequence's length / counts are unspecified.  Sequences go through
  * the selection's launches together, as many at a time as the workspace holds (32 at
  * most).  Padding rows of Q and K are never read.
- * Workspace: OMNI_CALL_PREFILL_SELECT with param = probe_block for desc; the one of a
- * descriptor with batch 1 suffices (one sequence at a time then).
+ * Workspace: OMNI_CALL_PREFILL_SELECT with param = probe_block for desc with a batch of
+ * min(batch, 32); the one for a batch of 1 suffices (one sequence at a time then).
  */
 int omni_prefill_select_varlen(const omni_layer_desc* desc, const void* Q, const void* K,
                                const int32_t* seq_tokens, const int32_t* seq_vis_begin,

@@ -474,7 +474,9 @@ def omni_prefill_select_varlen(desc: LayerDesc, Q, K, seq_tokens, seq_vis_begin,
         torch.empty(B, H, b_cap, dtype=i32, device=dev))
     arr = lambda x: (C.c_int32 * B)(*[int(v) for v in x])
     n_arr, v0_arr, v1_arr = arr(seq_tokens), arr(seq_vis_begin), arr(seq_vis_end)
-    buf = ws.get(CALL_PREFILL_SELECT, desc, probe_block)
+    some = LayerDesc.from_buffer_copy(desc)
+    some.batch = min(B, 32)                       # as many sequences as go through the launches together
+    buf = ws.get(CALL_PREFILL_SELECT, some, probe_block)
     _check(lib.omni_prefill_select_varlen(C.byref(desc), _ptr(Q), _ptr(K), n_arr, v0_arr, v1_arr, q_mode, q_param, recall_p,
                                           probe_block, budget_mode, _ptr(out.probe_keys), _ptr(out.scores), _ptr(out.q_idx),
                                           _ptr(out.q_cnt), _ptr(bud.key_scores), _ptr(bud.kurtosis), _ptr(bud.flattest),

@@ -137,6 +137,13 @@ static bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 1
 static size_t prefill_select_ws(const Layer& L, int dtype, int pb) {
   return std::max(score_queries_ws(L), align_up(probe_ws(L, dtype, pb), 256) + select_lists_ws(L));
 }
+// What a caller is told to bring: for the largest visual range that the tokens allow, because the sequences of a padded batch
+// have ranges of their own.
+static size_t prefill_select_ws_any_range(Layer L, int dtype, int pb) {
+  L.v0 = 0;
+  L.v1 = L.N;
+  return prefill_select_ws(L, dtype, pb);
+}
 
 // The selection of a prefill step (scores, probe, both lists) on a workspace of prefill_select_ws bytes.
 static int run_prefill_select(const Layer& L, int dtype, const Ragged& rg, const void* Q, const void* K, int q_mode,
@@ -381,7 +388,7 @@ size_t omni_workspace_bytes(int call_id, const void* desc, int32_t param) {
     case OMNI_CALL_GROUP_SUBSET: return group_subset_ws(L);
     case OMNI_CALL_PREFILL_SELECT:
       if (param < 1) { set_error("probe block must be >= 1"); return 0; }
-      return prefill_select_ws(L, d->dtype, param);
+      return prefill_select_ws_any_range(L, d->dtype, param);
     case OMNI_CALL_BLOCK_SCORES:
       if (param < 1) { set_error("block must be >= 1"); return 0; }
       return block_scores_ws(L, param);

@@ -316,6 +316,16 @@ def test_queued_work_list_places_whole_heads_and_balances_the_queues(lib, q_cnt,
     assert loads == sim_load
 
 
+def test_scratch_of_the_selection_does_not_depend_on_the_visual_range(lib):
+    """The sequences of a padded batch have ranges of their own: the size for a descriptor of as many tokens is enough for any."""
+    tokens = 65536
+    size = lambda v0, v1: ob.workspace_bytes(ob.CALL_PREFILL_SELECT, ob.LayerDesc(  # noqa: E731
+        batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, n_tokens=tokens, vis_begin=v0, vis_end=v1, sink_index=0, causal=1,
+        dtype=ob.OMNI_BF16, softmax_scale=0.088, q_stride=(tokens * 128, tokens * 128, 128),
+        kv_stride=(tokens * 128, tokens * 128, 128)), tokens)
+    assert size(5, 6) == size(0, tokens) >= 131072
+
+
 @pytest.mark.parametrize("tokens,units", [(16384, 4), (1072, 15)])
 def test_scratch_of_the_fp32_backward(lib, tokens, units):
     """Long sequences keep K, V and one plane of dK', dV'; short ones copies of Q and dO and four planes too.  A unit is one

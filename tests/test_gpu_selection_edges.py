@@ -147,6 +147,68 @@ def test_block_scores_with_keys_that_are_not_finite(block, causal):
     assert bool(torch.isnan(ob.omni_block_scores(desc, Q, K2, block)).all())
 
 
+def _same_selection(x, y, lengths):
+    for i, n in enumerate(lengths):
+        assert torch.equal(x.scores[i, :, :n], y.scores[i, :, :n])
+        assert torch.equal(x.budget.key_scores[i, :, :n], y.budget.key_scores[i, :, :n])
+        assert torch.equal(x.q_idx[i, 1, : int(x.q_cnt[i, 1])], y.q_idx[i, 1, : int(x.q_cnt[i, 1])])
+        assert torch.equal(x.kv_idx[i, :, : int(x.budget.budget[i])], y.kv_idx[i, :, : int(x.budget.budget[i])])
+    for u, v in ((x.q_cnt, y.q_cnt), (x.budget.budget, y.budget.budget), (x.budget.recall, y.budget.recall),
+                 (x.budget.kurtosis, y.budget.kurtosis), (x.probe_keys, y.probe_keys)):
+        assert torch.equal(u, v)
+
+
+class _ScratchFor(ob.Workspace):
+    """A workspace of just the size that the library asks for a batch of `batch`, whatever the call would like."""
+    def __init__(self, batch):
+        super().__init__()
+        self.batch = batch
+
+    def get(self, call_id, desc, param=0):
+        some = ob.LayerDesc.from_buffer_copy(desc)
+        some.batch, some.vis_begin, some.vis_end = self.batch, 0, 1
+        n = ob.workspace_bytes(call_id, some, param)
+        self.raw = torch.empty(n + 256, dtype=torch.uint8, device="cuda")
+        at = -self.raw.data_ptr() % 256
+        return self.raw[at: at + n]
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("probe_block", [32, 700])
+def test_padded_batch_with_scratch_for_some_of_its_sequences_gives_the_same(batch, probe_block):
+    """Three sequences on exactly the scratch that is asked for one or two (a full group and a rest), by a descriptor whose own
+    visual range is a single token: the outputs of the batch in one go."""
+    B, H, Hkv, N, D = 3, 4, 2, 700, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q = torch.randn(B, H, N, D, generator=g, device="cuda").bfloat16()
+    K = torch.randn(B, Hkv, N, D, generator=g, device="cuda").bfloat16()
+    d = ob.make_layer_desc(Q, K, 0, 1, 0, True)
+    args = ([700, 333, 40], [0, 5, 1], [690, 300, 33], 1, 0.4, 0.8, probe_block, 1)
+    x, y = (ob.omni_prefill_select_varlen(d, Q, K, *args, ws=w) for w in (ob.Workspace(), _ScratchFor(batch)))
+    torch.cuda.synchronize()
+    _same_selection(x, y, args[0])
+
+
+@pytest.mark.parametrize("mode", [0, 2])
+def test_padded_batch_of_more_sequences_than_one_set_of_launches_takes(mode):
+    """35 sequences: a full group of 32 and a rest of 3, each as it is alone."""
+    B, H, Hkv, N, D = 35, 2, 1, 130, 64
+    g = torch.Generator(device="cuda").manual_seed(4)
+    Q = torch.randn(B, H, N, D, generator=g, device="cuda").bfloat16()
+    K = torch.randn(B, Hkv, N, D, generator=g, device="cuda").bfloat16()
+    n = [130 - 3 * b for b in range(B)]
+    v1 = [max(1, x - 5) for x in n]
+    x = ob.omni_prefill_select_varlen(ob.make_layer_desc(Q, K, 0, N, 0, True), Q, K, n, [0] * B, v1, 1, 0.4, 0.8, 32, mode)
+    for b in (0, 1, 31, 32, 33, 34):
+        q, k = Q[b:b + 1, :, :n[b]].contiguous(), K[b:b + 1, :, :n[b]].contiguous()
+        y = ob.omni_prefill_select(ob.make_layer_desc(q, k, 0, v1[b], 0, True), q, k, 1, 0.4, 0.8, 32, mode)
+        assert torch.equal(x.scores[b, :, :n[b]], y.scores[0]) and torch.equal(x.budget.key_scores[b, :, :n[b]], y.budget.key_scores[0])
+        assert torch.equal(x.q_cnt[b], y.q_cnt[0]) and torch.equal(x.budget.budget[b], y.budget.budget[0])
+        for h in range(H):
+            c, m = int(y.q_cnt[0, h]), int(y.budget.budget[0, h] if mode == 2 else y.budget.budget[0])
+            assert torch.equal(x.q_idx[b, h, :c], y.q_idx[0, h, :c]) and torch.equal(x.kv_idx[b, h, :m], y.kv_idx[0, h, :m])
+
+
 def test_padded_batch_with_scratch_for_one_sequence_gives_the_same():
     """A workspace for one sequence takes a batch one sequence at a time: the outputs of the batch in one go."""
     B, H, Hkv, N, D = 3, 4, 2, 700, 64
