@@ -788,15 +788,21 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
                         static_cast<const T*>(p.V) + b * p.ks[0] + g * p.ks[1], p.ks[2]);
 }
 
-// Merges the slices of one head.  grid = (B * Hq, kCombineCuts), kCombineThreads threads: a workgroup owns D / kCombineCuts
+// Merges the slices of one head.  grid = (B * Hq, CUTS), kCombineThreads threads: a workgroup owns D / CUTS
 // output elements; lane groups of one thread per two elements take the slices round-robin, each with a running maximum
 // of its own and the loads of kInFlight slices together, then the groups are merged in group order.  Bound by latency: 28
 // heads x 225 slices are 3 MB, and 28 workgroups that first looked for the maximum took 6.6 us; 4.3 to 5.2 now (131k cache).
-constexpr int kCombineThreads = 1024, kCombineCuts = 2;
+constexpr int kCombineThreads = 1024;
+// Two workgroups a head halve the trips over the slices, which pays where there are several (one cut takes 64 slices a trip at
+// d = 128); elsewhere the second one costs its launch and reads every maximum and sum again.  Decode step on group lists in
+// us, one cut / two / before either: 28 heads, d = 128, 131072 tokens (257 slices) 34.6 / 33.1 / 36.9, 16000 (201) 15.7 / 15.1 / 17.0, four sequences of
+// 16000 (57) 23.0 / 23.3 / 24.6, one of 4108 (66) 10.4 / 10.6 / 11.4, 32 x 4108 35.7 / 38.1 / 36.4; d = 64 (128 a trip), 16000 11.1 / 11.6 / 11.9,
+// 32 x 700 12.1 / 15.0 / 13.0; 8 heads, d = 128, four of 16000 (105) 15.1 / 14.6 / 16.0, eight (57) 22.1 / 22.3 / 23.4.
+inline int combine_cuts(int D, int slices) { return D == 128 && slices > 96 ? 2 : 1; }
 
-template <typename T, int D>
+template <typename T, int D, int CUTS>
 __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeParams p) {
-  constexpr int W = D / kCombineCuts;              // output elements of this workgroup
+  constexpr int W = D / CUTS;                      // output elements of this workgroup
   constexpr int LG = W / 2;                        // threads per slice
   constexpr int NG = kCombineThreads / LG;         // slices in flight per pass
   constexpr int kInFlight = 4;
@@ -937,7 +943,10 @@ int launch_decode(const DecodeParams& p, hipStream_t st) {
       default: launch_rows<T, D, 1>(p, st); break;
     }
     OMNI_LAUNCH_CHECK();
-    hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(p.B * p.Hq, kCombineCuts), dim3(kCombineThreads), 0, st, p);
+    if (combine_cuts(D, p.n_shared + p.n_head) == 2)
+      hipLaunchKernelGGL((decode_combine_kernel<T, D, 2>), dim3(p.B * p.Hq, 2), dim3(kCombineThreads), 0, st, p);
+    else
+      hipLaunchKernelGGL((decode_combine_kernel<T, D, 1>), dim3(p.B * p.Hq), dim3(kCombineThreads), 0, st, p);
     OMNI_LAUNCH_CHECK();
   }
   return OMNI_OK;

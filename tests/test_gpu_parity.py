@@ -1698,6 +1698,22 @@ def test_decode_with_other_group_sizes(G, hkv, d):
     assert np.max(np.abs(to_host(Od) - oc.dense_decode(q, Kc, Vc, ctx, cfg.scale))) <= TOL_OUT[cfg.dtype]
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("rows", [64, 65, 96 * 64, 96 * 64 + 1, 200 * 64 + 5])
+def test_decode_at_the_edges_of_how_a_head_is_combined(rows, dtype, d):
+    """One slice, 96 slices and one more (where d = 128 goes to two workgroups a head), several trips; the last slices hold no
+    row of a shorter sequence."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)  # noqa: E731
+    q, K, V = rand(2, 2, d), rand(2, 1, rows, d), rand(2, 1, rows, d)
+    ctx = torch.tensor([rows, max(1, rows // 3)], dtype=torch.int32, device="cuda")
+    O = ob.omni_dense_decode(ob.make_decode_desc(q, K, 0, 0, 0.0), q, K, V, ctx)
+    for b in range(2):
+        n = int(ctx[b])
+        p = torch.softmax(q[b].double() @ K[b, 0, :n].double().T * d ** -0.5, -1)
+        assert float((O[b].double() - p @ V[b, 0, :n].double()).abs().max()) <= TOL_OUT[dtype]
+
+
 # ------------------------------------------------------------------ odd layouts of the visual range and the sink
 
 @pytest.mark.usefixtures("attention_route")
