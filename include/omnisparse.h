@@ -619,16 +619,16 @@ int omni_profile_read(int kernel_id, float* total_ms /* host */, int* launches /
 
 /*
  * Diagnostic, host only: the work list the query-tile kernels (attention forward,
- * backward dQ) build on the device, computed by the same rule on the host.  Work item
+ * backward dQ; short sequences run without one) build on the device, computed by the same rule on the host.  Work item
  * = one tile of tile_rows (128 or 256) kept queries of a head, its cost the number of
  * 64-key tiles it streams (estimated here from the position of the tile; the device
  * uses exact counts where it has them).  queues = 1: one list, longest item first,
  * handed out from one atomic counter.  queues = 8 (the sparse bf16 forward): one list
  * per XCD -- whole heads are placed on queues, largest head first onto the least loaded
- * queue; inside a queue head follows head, each longest item first (the device hands a
- * queue out longest item first where its items are long against a workgroup's share);
- * short sequences run without a list; a workgroup takes from its XCD's queue and, once that is drained, from the queue with the most items left.  All pointers are
- * HOST pointers.  q_cnt [batch * n_q_heads] (null: every head keeps n_tokens rows),
+ * queue (one list after all if a head outweighs 1.5 fair shares); inside a queue head
+ * follows head, each longest item first, where the work of a CU (of 256) is at least 3.4 longest
+ * items, else all items longest first; a workgroup takes from its XCD's queue and, once
+ * that is drained, from the queue with the most items left.  All pointers are HOST pointers.  q_cnt [batch * n_q_heads] (null: every head keeps n_tokens rows),
  * budget [batch] (null: n_tokens); item_head / item_tile / item_cost [capacity] out,
  * queue after queue in hand-out order; queue_end [8] out (nullable): queue q is the
  * positions [queue_end[q-1], queue_end[q]); n_items out.  OMNI_ERR_WORKSPACE if
@@ -638,6 +638,19 @@ int omni_debug_work_list(const omni_layer_desc* desc, const int32_t* q_cnt, cons
                          int32_t b_cap, int32_t tile_rows, int32_t queues, int32_t* item_head,
                          int32_t* item_tile, int32_t* item_cost, int32_t capacity, int32_t* n_items,
                          int32_t* queue_end);
+
+/*
+ * Diagnostic: the same list as the device builds it from index lists (DEVICE pointers as in
+ * omni_sparse_attn_fwd; per_head: one budget per head), into list (DEVICE, 16-byte
+ * aligned): [1] number of items, [4..11] next position and [12..19] end of every queue.
+ * layout [3] (HOST, out): ints that the list takes, where the items by id start ((head <<
+ * 16 | tile), cost) and where the hand-out order starts (head << 16 | tile).  With list
+ * null only layout is written.
+ */
+int omni_debug_device_work_list(const omni_layer_desc* desc, const int32_t* q_idx, const int32_t* q_cnt,
+                                const int32_t* kv_idx, const int32_t* budget, int per_head, int32_t b_cap,
+                                int32_t tile_rows, int32_t queues, int32_t* list, size_t list_ints,
+                                int64_t* layout, void* stream);
 
 /*
  * Diagnostic: copy `bytes` (a positive multiple of 16) from src to dst, both DEVICE pointers

@@ -32,7 +32,7 @@ EXPORTED = [
     "omni_visual_subset_per_head", "omni_prefill_select", "omni_compact_cache", "omni_slim_decode_compact",
     "omni_compact_cache_paged", "omni_slim_decode_paged",
     "omni_group_subset_per_head", "omni_debug_key_split_len",
-    "omni_debug_attention_route",
+    "omni_debug_attention_route", "omni_debug_device_work_list",
     "omni_slim_decode_grouped_static", "omni_static_scratch_bytes",
     "omni_sparse_prefill", "omni_sparse_prefill_workspace_bytes", "omni_slim_decode_prepare",
 ]
@@ -147,6 +147,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.omni_debug_attention_route.argtypes = [C.c_int]
     lib.omni_debug_mfma_rate.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     lib.omni_debug_work_list.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, i32, vp, vp]   # same shape: three output arrays
+    lib.omni_debug_device_work_list.argtypes = [vp, vp, vp, vp, vp, C.c_int, i32, i32, i32, vp, sz, vp, vp]
     lib.omni_profile_read.argtypes = [C.c_int, C.POINTER(C.c_float), C.POINTER(C.c_int)]
     for name in EXPORTED:
         fn = getattr(lib, name)
@@ -233,6 +234,21 @@ def debug_work_list(desc: LayerDesc, q_cnt=None, budget=None, b_cap: int = 1, ti
     if queues > 1:
         return head[: n.value], tile[: n.value], cost[: n.value], qend
     return head[: n.value], tile[: n.value], cost[: n.value]
+
+
+def debug_device_work_list(desc: LayerDesc, q_idx, q_cnt, kv_idx, budget, tile_rows: int = 256, queues: int = 8):
+    """The work list as the device builds it: (items [n, 2] of (head << 16 | tile) and cost by id, order [n] of
+    head << 16 | tile, starts [8], ends [8] of the queues), host arrays."""
+    lib, layout = load_library(), (C.c_int64 * 3)()
+    call = lambda ptr, n: _check(lib.omni_debug_device_work_list(  # noqa: E731
+        C.byref(desc), _ptr(q_idx), _ptr(q_cnt), _ptr(kv_idx), _ptr(budget), int(budget.dim() == 2), kv_idx.shape[-1], tile_rows,
+        queues, ptr, n, layout, _stream()))
+    call(None, 0)
+    buf = torch.full((layout[0],), -1, dtype=torch.int32, device=q_idx.device)
+    call(_ptr(buf), buf.numel())
+    h = buf.cpu().numpy()
+    n = int(h[1])
+    return h[layout[1]: layout[1] + 2 * n].reshape(n, 2), h[layout[2]: layout[2] + n], h[4:12], h[12:20]
 
 
 def debug_copy(src, dst):

@@ -283,27 +283,53 @@ int omni_debug_work_list(const omni_layer_desc* desc, const int32_t* q_cnt, cons
   if (b_cap < 1) OMNI_FAIL(OMNI_ERR_INVALID, "b_cap must be >= 1");
   if (tile_rows != 128 && tile_rows != 256) OMNI_FAIL(OMNI_ERR_INVALID, "tile_rows must be 128 or 256");
   if (queues != 1 && queues != kSchedQueues) OMNI_FAIL(OMNI_ERR_INVALID, "queues must be 1 or %d", kSchedQueues);
-  const int BH = desc->batch * desc->n_q_heads;
-  std::vector<int> sched(sched_ints(BH, desc->n_tokens, tile_rows));
-  sched_build_host(q_cnt, budget, desc->batch, desc->n_q_heads, desc->n_tokens, b_cap, desc->causal, tile_rows,
-                   sched.data(), queues);
-  const int items = sched[kSchedTotal];
+  constexpr int kCus = 256;                        // of the MI355X: the device's order depends on them
+  const HostWorkList list = sched_build_host(q_cnt, budget, desc->batch, desc->n_q_heads, desc->n_tokens, b_cap, desc->causal,
+                                             tile_rows, queues, kCus);
+  const int items = (int)list.packed.size();
   *n_items = items;
   if (queue_end)
-    for (int q = 0; q < kSchedQueues; ++q) queue_end[q] = sched[kSchedEnd + q];
+    for (int q = 0; q < kSchedQueues; ++q) queue_end[q] = list.end[q];
   if (items > capacity) OMNI_FAIL(OMNI_ERR_WORKSPACE, "work list has %d items, capacity is %d", items, capacity);
-  const size_t order_off = sched_order_off(BH, desc->n_tokens, tile_rows);
   for (int it = 0; it < items; ++it) {
-    int bh, tq;
-    sched_decode(sched.data(), order_off, it, bh, tq);
-    item_head[it] = bh;
-    item_tile[it] = tq;
-    const int nt = sched[kSchedPrefix + bh + 1] - sched[kSchedPrefix + bh];
-    int nk = budget ? budget[bh / desc->n_q_heads] : desc->n_tokens;
-    nk = nk < 0 ? 0 : (nk > b_cap ? b_cap : nk);
-    item_cost[it] = sched_estimate(tq, nt, nk, desc->causal);
+    item_head[it] = (int)((unsigned)list.packed[it] >> 16);
+    item_tile[it] = list.packed[it] & 0xffff;
+    item_cost[it] = list.cost[it];
   }
   return OMNI_OK;
+}
+
+int omni_debug_device_work_list(const omni_layer_desc* desc, const int32_t* q_idx, const int32_t* q_cnt,
+                                const int32_t* kv_idx, const int32_t* budget, int per_head, int32_t b_cap, int32_t tile_rows,
+                                int32_t queues, int32_t* list, size_t list_ints, int64_t* layout, void* stream) {
+  clear_error();
+  CHECK(validate_layer(desc));
+  REQUIRE_PTR(layout);
+  if (b_cap < 1) OMNI_FAIL(OMNI_ERR_INVALID, "b_cap must be >= 1");
+  if (tile_rows != 128 && tile_rows != 256) OMNI_FAIL(OMNI_ERR_INVALID, "tile_rows must be 128 or 256");
+  if (queues != 1 && queues != kSchedQueues) OMNI_FAIL(OMNI_ERR_INVALID, "queues must be 1 or %d", kSchedQueues);
+  Layer L = make_layer(desc);
+  L.bph = per_head != 0;
+  CHECK(check_work_list(L, tile_rows));
+  const int BH = L.B * L.Hq;
+  layout[0] = (int64_t)sched_ints(BH, L.N, tile_rows);
+  layout[1] = kSchedItems;
+  layout[2] = (int64_t)sched_order_off(BH, L.N, tile_rows);
+  if (!list) return OMNI_OK;
+  REQUIRE_PTR(q_idx); REQUIRE_PTR(q_cnt); REQUIRE_PTR(kv_idx); REQUIRE_PTR(budget);
+  REQUIRE_ALIGNED(list);
+  if (list_ints < (size_t)layout[0]) OMNI_FAIL(OMNI_ERR_WORKSPACE, "work list needs %lld ints", (long long)layout[0]);
+  Bounds b{};
+  b.q_idx = q_idx;
+  b.q_cnt = q_cnt;
+  b.klist = kv_idx;
+  b.klist_stride = b_cap;
+  b.budget = budget;
+  b.b_cap = b_cap;
+  b.tile_m = tile_rows;
+  b.sched = list;
+  CHECK(run_bounds(L, b, static_cast<hipStream_t>(stream)));
+  return run_order(L, q_cnt, tile_rows, list, static_cast<hipStream_t>(stream), queues);
 }
 
 int omni_debug_copy(const void* src, void* dst, size_t bytes, void* stream) {

@@ -7,8 +7,7 @@
 // (measured: 17 % of the kernel time).  So the items are sorted by cost, longest first, and every
 // workgroup pulls the next one from a single atomic counter -- the classic longest-processing-time
 // rule, whose tail is bounded by the shortest items.  The cost of an item is the number of key tiles
-// it streams: exact when the per-query visible-prefix counts are given, else estimated from the
-// position of the tile.
+// it streams: exact where there are index lists, estimated from the position of the tile for the dense baseline.
 //
 // The list can be cut into kSchedQueues queues, one per XCD (workgroups are dealt to the XCDs round-robin, so
 // workgroup i sits on XCD i % 8): whole heads are assigned to queues, largest first onto the least loaded
@@ -22,27 +21,24 @@
 // Layout of the int array in device memory:
 //   [0] unused   [1] number of items   [2..3] unused
 //   [4 .. 11] cursor[q]: next position of queue q   [12 .. 19] end[q]   (one queue: cursor[0] = 0, end[0] = items)
-//   [20 .. 20 + BH]          head_prefix[BH + 1]  (cumulative tile counts, head-major item ids; host mirror only)
-//   [.. + BH]                head_cost[BH]        (sum of the head's item costs; host mirror only)
-//   [.. + BH]                head_place[BH]       (queue << 16 | position of the head inside its queue; host mirror only)
-//   [.. + 2 * cap]           items by id: (head << 16 | tile), cost
+//   [20 .. + 2 * cap]        items by id: (head << 16 | tile), cost
 //   [.. + cap]               order[k] = (head << 16 | tile) of the k-th item to hand out
 // with cap = BH * ceil(N / tile_m) the largest possible number of items.
 #pragma once
+
+#include <vector>
 
 #include "common.h"
 
 namespace omni {
 
 constexpr int kSchedQueues = 8;
-constexpr int kSchedTotal = 1, kSchedCursor = 4, kSchedEnd = kSchedCursor + kSchedQueues, kSchedPrefix = kSchedEnd + kSchedQueues;
+constexpr int kSchedTotal = 1, kSchedCursor = 4, kSchedEnd = kSchedCursor + kSchedQueues;
+constexpr int kSchedItems = kSchedEnd + kSchedQueues;      // even: the items are read as pairs
 constexpr int kSchedMaxQueuedHeads = 1024;       // more heads than this: one queue (the placement is a serial loop)
 
 inline size_t sched_cap(int BH, int N, int tile_m) { return (size_t)BH * ((N + tile_m - 1) / tile_m); }
-__host__ __device__ inline size_t sched_head_cost_off(int BH) { return (size_t)kSchedPrefix + BH + 1; }
-__host__ __device__ inline size_t sched_head_place_off(int BH) { return sched_head_cost_off(BH) + BH; }
-__host__ __device__ inline size_t sched_keys_off(int BH) { return (sched_head_place_off(BH) + BH + 1) & ~(size_t)1; }      // 8-byte aligned
-inline size_t sched_order_off(int BH, int N, int tile_m) { return sched_keys_off(BH) + 2 * sched_cap(BH, N, tile_m); }
+inline size_t sched_order_off(int BH, int N, int tile_m) { return (size_t)kSchedItems + 2 * sched_cap(BH, N, tile_m); }
 inline size_t sched_ints(int BH, int N, int tile_m) { return sched_order_off(BH, N, tile_m) + sched_cap(BH, N, tile_m); }
 
 // What the kept-query and key lists say about every position and token, in one launch (run_bounds); null: not wanted.
@@ -55,7 +51,7 @@ struct Bounds {
   int* qvis;                     // [B*Hq, N] number of listed keys that kept query `pos` may see
   int* kfirst;                   // [B*Hq, npad] first kept-query position that may see listed key `slot`
   int* inv;                      // [B*Hq, N] slot of the token in the key list (listed tokens only; with kfirst)
-  void* X;                       // rows of the Q-shaped tensor (16-byte aligned) that are not kept are set to zero
+  void* X;                       // nullable (then lse is not written either): rows of the Q-shaped tensor (16-byte aligned) that are not kept are set to zero
   int elem_bytes;
   float* lse;                    // [B*Hq, N] -inf for the rows that are not kept
   int tile_m;                    // rows per work item
@@ -145,47 +141,13 @@ __host__ __device__ inline bool sched_long_enough(long long total_cost, long lon
   return 10 * total_cost >= 34 * largest_item * workgroups;
 }
 
-// Heads onto queues (host mirror of sched_order_kernel's placement).  Writes head_place, cursor and end.
-inline void sched_assign_host(int* sched, int BH, int queues) {
-  const int* prefix = sched + kSchedPrefix;
-  const int* hcost = sched + sched_head_cost_off(BH);
-  int* place = sched + sched_head_place_off(BH);
-  int items[kSchedQueues], heads[kSchedQueues];
-  unsigned load[kSchedQueues];
-  for (int q = 0; q < kSchedQueues; ++q) items[q] = 0, heads[q] = 0, load[q] = (unsigned)q;
-  long long total = 0;
-  for (int bh = 0; bh < BH; ++bh) total += hcost[bh];
-  const int shift = sched_cost_shift(total);
-  long long largest = 0;
-  for (int bh = 0; bh < BH; ++bh) largest = hcost[bh] > largest ? hcost[bh] : largest;
-  if (queues <= 1 || BH > kSchedMaxQueuedHeads || !sched_queues_pay(total, largest, queues)) {
-    for (int bh = 0; bh < BH; ++bh) place[bh] = 0;
-    items[0] = prefix[BH];
-  } else {
-    for (int bh = 0; bh < BH; ++bh) place[bh] = -1;
-    for (int n = 0; n < BH; ++n) {
-      int best = -1;                                   // largest head not placed yet (lowest index among equals)
-      for (int bh = 0; bh < BH; ++bh)
-        if (place[bh] < 0 && (best < 0 || hcost[bh] > hcost[best])) best = bh;
-      unsigned m = load[0];
-      for (int r = 1; r < queues; ++r) m = load[r] < m ? load[r] : m;
-      const int q = (int)(m & 7u);
-      place[best] = (q << 16) | heads[q];
-      heads[q] += 1;
-      load[q] += (unsigned)(hcost[best] >> shift) << 3;
-      items[q] += prefix[best + 1] - prefix[best];
-    }
-  }
-  int start = 0;
-  for (int q = 0; q < kSchedQueues; ++q) {
-    sched[kSchedCursor + q] = start;
-    start += items[q];
-    sched[kSchedEnd + q] = start;
-  }
-}
-
-// Host mirror of the device kernels (diagnostic entry point and CPU tests): fills prefix, total and order.
-void sched_build_host(const int* q_cnt, const int* budget, int B, int Hq, int N, int b_cap, int causal, int tile_m,
-                      int* sched, int queues = 1);
+// The same list on the host, with estimated costs (diagnostic entry point): the items in hand-out order and the ends of the
+// queues.
+struct HostWorkList {
+  std::vector<int> packed, cost;
+  int end[kSchedQueues];
+};
+HostWorkList sched_build_host(const int* q_cnt, const int* budget, int B, int Hq, int N, int b_cap, int causal, int tile_m,
+                              int queues, int workgroups);
 
 }  // namespace omni

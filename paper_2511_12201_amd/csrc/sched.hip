@@ -3,7 +3,6 @@
 #include "sched.h"
 
 #include <algorithm>
-#include <vector>
 
 namespace omni {
 
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(kThreads) void bounds_kernel(Layer L, Bounds p) {
   const int before = items_before(p.q_cnt, bh, L.N, p.tile_m);
   if (last) {
     const int tq = n / p.tile_m;
-    reinterpret_cast<int2*>(p.sched + sched_keys_off(L.B * L.Hq))[before + tq] =
+    reinterpret_cast<int2*>(p.sched + kSchedItems)[before + tq] =
         make_int2((int)(((unsigned)bh << 16) | (unsigned)tq), (visible + kTileN - 1) / kTileN);
   }
 }
@@ -123,7 +122,7 @@ __global__ __launch_bounds__(64) void sched_estimate_kernel(const int* __restric
   const int nt = tiles_of(q_cnt, bh, L.N, tile_m), before = items_before(q_cnt, bh, L.N, tile_m);
   int nk = budget ? budget[budget_slot(L.bph, bh / L.Hq, bh)] : L.N;
   nk = nk < 0 ? 0 : (nk > b_cap ? b_cap : nk);
-  int2* items = reinterpret_cast<int2*>(sched + sched_keys_off(L.B * L.Hq));
+  int2* items = reinterpret_cast<int2*>(sched + kSchedItems);
   for (int tq = threadIdx.x; tq < nt; tq += 64)
     items[before + tq] = make_int2((int)(((unsigned)bh << 16) | (unsigned)tq), sched_estimate(tq, nt, nk, L.causal));
 }
@@ -145,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void sched_order_kernel(const int* __rest
   __shared__ int s_wave[kThreads / 64], s_big[kThreads / 64], s_head[kThreads / 64];
   __shared__ long long s_tot[kThreads / 64];
   __shared__ int s_end[kSchedQueues];
-  const int2* items = reinterpret_cast<const int2*>(sched + sched_keys_off(BH));
+  const int2* items = reinterpret_cast<const int2*>(sched + kSchedItems);
   const int wave = threadIdx.x >> 6;
   // number of items
   int n = 0;
@@ -291,7 +290,7 @@ int check_work_list(const Layer& L, int tile_m) {
 
 int run_bounds(const Layer& L, const Bounds& p, hipStream_t st) {
   const int BH = L.B * L.Hq, n = p.kfirst ? max(L.N, p.npad) : L.N;
-  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH, 2), dim3(kThreads), 0, st, L, p);
+  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH, p.X ? 2 : 1), dim3(kThreads), 0, st, L, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
@@ -312,36 +311,62 @@ int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap,
   return run_order(L, q_cnt, tile_m, sched, st);
 }
 
-void sched_build_host(const int* q_cnt, const int* budget, int B, int Hq, int N, int b_cap, int causal, int tile_m,
-                      int* sched, int queues) {
+HostWorkList sched_build_host(const int* q_cnt, const int* budget, int B, int Hq, int N, int b_cap, int causal, int tile_m,
+                              int queues, int workgroups) {
   const int BH = B * Hq;
-  int items = 0;
-  std::vector<int> costs, packed;
+  std::vector<int> packed, costs, head_items(BH);
+  std::vector<long long> head_cost(BH);
+  long long total = 0, largest_head = 0, largest_item = 0;
   for (int bh = 0; bh < BH; ++bh) {
-    const int nq = q_cnt ? q_cnt[bh] : N;
-    const int nt = nq > 0 ? (nq + tile_m - 1) / tile_m : 0;
+    const int nq = q_cnt ? q_cnt[bh] : N, nt = nq > 0 ? (nq + tile_m - 1) / tile_m : 0;
     int nk = budget ? budget[bh / Hq] : N;
     nk = nk < 0 ? 0 : (nk > b_cap ? b_cap : nk);
-    sched[kSchedPrefix + bh] = items;
-    sched[sched_head_cost_off(BH) + bh] = 0;
     for (int tq = 0; tq < nt; ++tq) {
-      costs.push_back(sched_estimate(tq, nt, nk, causal));
-      sched[sched_head_cost_off(BH) + bh] += costs.back();
       packed.push_back((int)(((unsigned)bh << 16) | (unsigned)tq));
+      costs.push_back(sched_estimate(tq, nt, nk, causal));
+      head_cost[bh] += costs.back();
+      largest_item = std::max(largest_item, (long long)costs.back());
     }
-    items += nt;
+    head_items[bh] = nt;
+    total += head_cost[bh];
+    largest_head = std::max(largest_head, head_cost[bh]);
   }
-  sched[kSchedPrefix + BH] = items;
-  sched[kSchedTotal] = items;
-  sched_assign_host(sched, BH, queues);
-  std::vector<unsigned long long> keys(items);
-  for (int id = 0; id < items; ++id)
-    keys[id] = sched_key(costs[id], id, (unsigned)sched[sched_head_place_off(BH) + (int)((unsigned)packed[id] >> 16)]);
+  const int items = (int)packed.size();
+  const bool queued = queues > 1 && BH <= kSchedMaxQueuedHeads && sched_queues_pay(total, largest_head, queues);
+  const bool by_head = sched_long_enough(total, largest_item, workgroups);
+  std::vector<unsigned> place(BH, 0u);
+  int count[kSchedQueues] = {};
+  if (queued) {
+    std::vector<int> heads(BH);                          // by cost, lower index first among equals
+    for (int bh = 0; bh < BH; ++bh) heads[bh] = bh;
+    std::stable_sort(heads.begin(), heads.end(), [&](int x, int y) { return head_cost[x] > head_cost[y]; });
+    const int shift = sched_cost_shift(total);
+    unsigned load[kSchedQueues];
+    int placed[kSchedQueues] = {};
+    for (int q = 0; q < kSchedQueues; ++q) load[q] = q < queues ? (unsigned)q : 0xffffffffu;
+    for (int bh : heads) {
+      const int q = (int)(*std::min_element(load, load + kSchedQueues) & 7u);
+      place[bh] = ((unsigned)q << 16) | (unsigned)placed[q]++;
+      load[q] += (unsigned)(head_cost[bh] >> shift) << 3;
+      count[q] += head_items[bh];
+    }
+  } else {
+    count[0] = items;
+  }
+  HostWorkList list;
+  for (int q = 0, end = 0; q < kSchedQueues; ++q) list.end[q] = end += count[q];
   std::vector<int> idx(items);
   for (int i = 0; i < items; ++i) idx[i] = i;
-  std::sort(idx.begin(), idx.end(), [&](int a, int b) { return keys[a] > keys[b]; });
-  const size_t order_off = sched_order_off(BH, N, tile_m);
-  for (int k = 0; k < items; ++k) sched[order_off + k] = packed[idx[k]];
+  auto key = [&](int id) {
+    const unsigned at = place[(unsigned)packed[id] >> 16];
+    return sched_key(costs[id], id, by_head ? at : at & 0xffff0000u);
+  };
+  std::sort(idx.begin(), idx.end(), [&](int x, int y) { return key(x) > key(y); });
+  for (int id : idx) {
+    list.packed.push_back(packed[id]);
+    list.cost.push_back(costs[id]);
+  }
+  return list;
 }
 
 int persistent_grid() {

@@ -118,6 +118,71 @@ def test_forward_on_ascending_lists_that_repeat_an_index(N, dtype, d, causal):
     _check_layer(dtype, d, N, q_lists, kv_lists, causal, backward=False)
 
 
+def _hand_out_order(cost, head, queues, cus):
+    """(order of the item ids, queue ends): the rule of the work list, from exact costs."""
+    H, total = int(head.max()) + 1 if len(head) else 1, int(cost.sum())
+    per_head = np.bincount(head, cost, minlength=H).astype(np.int64)
+    if queues == 1 or H > 1024 or 2 * int(per_head.max()) * queues > 3 * total:
+        return np.lexsort((np.arange(len(cost)), -cost)), np.full(8, len(cost))
+    queue, pos, load, held, shift = np.zeros(H, int), np.zeros(H, int), [0] * 8, [0] * 8, 0
+    while total >> shift >= 1 << 27:
+        shift += 1
+    for h in sorted(range(H), key=lambda x: (-per_head[x], x)):
+        q = min(range(8), key=lambda r: (load[r], r))
+        queue[h], pos[h] = q, held[q]
+        held[q] += 1
+        load[q] += int(per_head[h]) >> shift
+    if 10 * total < 34 * int(cost.max()) * cus:            # long items against a CU's work: whatever their head
+        pos[:] = 0
+    return np.lexsort((np.arange(len(cost)), -cost, pos[head], queue[head])), np.cumsum(np.bincount(queue[head], minlength=8))
+
+
+def _work_list_lists(kind, rng):
+    """(N, kept queries and keys per head)."""
+    pick = lambda N, n: np.sort(rng.choice(N, n, replace=False)).astype(np.int32)  # noqa: E731
+    if kind == "edges":                                      # counts around one and several items, empty heads, empty key lists
+        N = 1100
+        return N, [pick(N, n) for n in (N, 0, 1, 127, 128, 129, 255, 256, 257, 0, 512, 513)],             [pick(N, n) for n in (600, 5, 0, N, 64, 65, 1, 700, 333, 0, 2, N)]
+    if kind == "even":                                       # no head outweighs a queue
+        N = 2000
+        return N, [pick(N, 600 + 13 * h) for h in range(24)], [pick(N, 900 - h) for h in range(24)]
+    if kind == "long":                                       # the work of a CU is several longest items: head after head
+        N = 65536
+        return N, [np.arange(N, dtype=np.int32)] + [pick(N, 21000 + 11 * h) for h in range(27)], [pick(N, 35000)] * 28
+    N = 300                                                  # "many": more heads than queues place
+    return N, [pick(N, int(n)) for n in rng.integers(0, N + 1, 1100)], [pick(N, 200)] * 1100
+
+
+@pytest.mark.parametrize("kind", ["edges", "even", "long", "many"])
+@pytest.mark.parametrize("queues", [1, 8])
+@pytest.mark.parametrize("tile_rows", [128, 256])
+@pytest.mark.parametrize("causal", [True, False])
+def test_work_list_of_the_device(kind, queues, tile_rows, causal):
+    """Items, costs and hand-out order that the device builds from index lists: those of the rule replayed from exact counts."""
+    N, q, k = _work_list_lists(kind, np.random.default_rng(7))
+    H, cap = len(q), max(1, max(len(x) for x in k))
+    q_idx, q_cnt = lists_to_padded([q], H, N)
+    kv_idx, budget = lists_to_padded([k], H, cap)
+    desc = ob.LayerDesc(batch=1, n_q_heads=H, n_kv_heads=H, head_dim=64, n_tokens=N, vis_begin=0, vis_end=N, sink_index=0,
+                        causal=int(causal), dtype=ob.OMNI_BF16, softmax_scale=0.125, q_stride=(H * N * 64, N * 64, 64),
+                        kv_stride=(H * N * 64, N * 64, 64))
+    items, order, starts, ends = ob.debug_device_work_list(desc, q_idx, q_cnt, kv_idx, budget, tile_rows, queues)
+    head, tile, cost = [], [], []
+    for h in range(H):
+        for t in range(-(-len(q[h]) // tile_rows)):
+            last = q[h][min((t + 1) * tile_rows, len(q[h])) - 1]
+            seen = np.searchsorted(k[h], last, side="right") if causal else len(k[h])
+            head.append(h), tile.append(t), cost.append(-(-int(seen) // 64))
+    packed, cost, head = np.array(head) << 16 | np.array(tile), np.array(cost), np.array(head)
+    np.testing.assert_array_equal(items[:, 0], packed)
+    np.testing.assert_array_equal(items[:, 1], cost)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    by, at = _hand_out_order(cost, head, queues, cus)
+    np.testing.assert_array_equal(order, packed[by])
+    np.testing.assert_array_equal(ends, at)
+    np.testing.assert_array_equal(starts, np.concatenate([[0], at[:-1]]))
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
 def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
