@@ -46,7 +46,6 @@ struct BwdParams {
   const void* Kn;       // packed natural K, V
   const void* Vn;
   const void* Kt;       // k-packed K
-  const int* kidx;
   const void* Qt;       // k-packed kept Q, dO (these and the next two, and Kt: not for fp32 on long sequences)
   const void* dOt;
   const void* Qn;       // kept Q, dO rows in kept order, contiguous (fp32: in fragment order, as Kn and Vn)
@@ -88,8 +87,8 @@ constexpr int kKeyQ = 64;                    // queries per streamed tile
 // A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
 // against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
 // query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
-constexpr int kKeySplitLenF32 = 4;           // fp32: a workgroup owns 32 keys and needs company sooner
-constexpr int kKeySplitLen = 128;            // query tiles per split, at least (64..128 measure alike, 32 and 256 worse)
+constexpr int kKeySplitLenF32 = 4;           // fp32: query tiles per split, at least; a workgroup owns 32 keys and needs company sooner
+constexpr int kKeySplitLen = 128;            // bf16: query tiles per split, at most (64..128 measure alike, 32 and 256 worse)
 constexpr int kKeyMaxSplits = 4;             // at most 8: a work item carries the split in 3 bits
 __host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
   const int s = n_qtiles / split_len;
@@ -1286,7 +1285,7 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.deltac = a.take<float>(qrows);
   w.dKp = a.take<float>(planes * krows * L.D);
   w.dVp = a.take<float>(planes * krows * L.D);
-  w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
+  w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, dtype == OMNI_BF16 ? kDqTileM : kTileM));
   w.qvis = a.take<int>(BH * L.N);
   w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
@@ -1364,7 +1363,6 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.Kn = w.Kn;
   p.Vn = w.Vn;
   p.Kt = w.Kt;
-  p.kidx = w.kidx;
   p.Qt = w.Qt;
   p.dOt = w.dOt;
   p.Qn = w.Qn;

@@ -58,13 +58,12 @@ struct FwdParams {
   const int* q_cnt;     // [B*Hq]; nullptr: N
   const void* Kp;       // packed keys  [BHx, npad, D]: row-major, or in fragment order (short sequences)
   const void* Vp;       // packed values: k-packed, or row-major (fp32 on long sequences)
-  const int* kidx;      // [BHx, npad] original token index of every slot
   const int* budget;    // [B] (or [B,Hq] when L.bph) number of packed keys (device); nullptr: N
   int b_cap;
   int npad;
   int per_q_head;       // packed buffers per query head (sparse) or per KV head (dense)
-  int identity_keys;
-  const int* qvis;       // [B*Hq, N] visible packed keys per kept-query position (sparse bf16 path), else nullptr    // kidx[p] == p: causal bounds by arithmetic
+  int identity_keys;    // slot p is token p: causal bounds by arithmetic (dense baseline)
+  const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position; nullptr with identity_keys
   int* sched;           // work list (sched.h)
   size_t order_off;     // where its hand-out order starts
   const int* tile_map;  // in-place variant: [B*Hq, tile_stride] tile of the packed K/V that tile t of a head's key list is
@@ -141,16 +140,15 @@ __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParam
   const int nq = p.q_cnt ? p.q_cnt[bh] : L.N;
   const int nkeys = p.budget ? min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap) : L.N;
   const int bhx = p.per_q_head ? bh : b * L.Hkv + g;
-  const int* kidx = p.kidx + (long long)bhx * p.npad;
   const int* qlist = p.q_idx ? p.q_idx + (long long)bh * L.N : nullptr;
 
   const int pos_first = tq * kFastTileM, pos_last = min(pos_first + kFastTileM, nq) - 1;
-  const int* qvis = p.qvis ? p.qvis + (long long)bh * L.N : nullptr;
+  const int* qvis = p.qvis + (long long)bh * L.N;          // not read for the dense baseline
   // visible prefix length of the packed key list for a kept-query position
   auto visible = [&](int pos, int row) {
     if (!L.causal) return nkeys;
     if (p.identity_keys) return min(row + 1, nkeys);
-    return qvis ? qvis[pos] : upper_count(kidx, nkeys, row);
+    return qvis[pos];
   };
   if (threadIdx.x == 0 || threadIdx.x == 64) {
     const int which = threadIdx.x ? 1 : 0;
@@ -961,7 +959,7 @@ FwdWs carve_fwd(Arena& a, const Layer& L, int dtype, int heads, int npad, bool s
   w.Kp = a.take<unsigned char>(rows * L.D * es);
   w.Vp = a.take<unsigned char>(rows * L.D * es);
   w.kidx = a.take<int>(rows);
-  w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, kTileM));   // sized for the smaller tile: the longer list
+  w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, dtype == OMNI_BF16 ? kFastTileM : kTileM));
   w.qvis = sparse ? a.take<int>((size_t)L.B * L.Hq * L.N) : nullptr;
   return w;
 }
@@ -1025,7 +1023,6 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.q_cnt = q_cnt;
   p.Kp = w.Kp;
   p.Vp = w.Vp;
-  p.kidx = w.kidx;
   p.budget = budget;
   p.b_cap = b_cap;
   p.npad = npad;
@@ -1135,7 +1132,6 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   p.q_cnt = q_cnt;
   p.Kp = w.f.Kp;
   p.Vp = w.f.Vp;
-  p.kidx = w.f.kidx;
   p.budget = w.vbudget;
   p.b_cap = cap_keys;
   p.npad = npad;

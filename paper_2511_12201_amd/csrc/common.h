@@ -89,7 +89,7 @@ struct ProfScope {
   ~ProfScope() { prof_end(id, st); }
 };
 
-constexpr int kTileM = 128;   // query rows per attention workgroup
+constexpr int kTileM = 128;   // query rows per work item of the fp32 kernels on long sequences
 constexpr int kTileN = 64;    // keys per attention tile
 constexpr int kPadKeyIndex = 0x7fffffff;
 
@@ -207,15 +207,6 @@ __device__ __forceinline__ void gload_lds4(const void* gptr, unsigned lds_addr) 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-__device__ __forceinline__ int upper_count(const int* __restrict__ a, int n, int v) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] <= v) lo = mid + 1; else hi = mid;
-  }
-  return lo;
 }
 
 __device__ __forceinline__ int seq_len(const Layer& L, const Ragged& rg, int b) { return rg.on ? rg.n[b] : L.N; }
