@@ -183,11 +183,13 @@ def test_work_list_of_the_device(kind, queues, tile_rows, causal):
     np.testing.assert_array_equal(starts, np.concatenate([[0], at[:-1]]))
 
 
+@pytest.mark.parametrize("full", [False, True])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
-def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
+def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal, full):
     """Shapes just below and just above the line between the two bf16 forward kernels (batch * heads * N^2 * d, twice
-    that without the mask, against 6.5e10), on the same random lists; a whole number of 32-row items and one row more."""
+    that without the mask, against 6.5e10), on the same random lists, or on lists of everything; a whole number of 32-row
+    items and one row more."""
     H, Hkv, B = 16, 1, 8
     line = int((6.5e10 / (B * H * d * (1 if causal else 2))) ** 0.5)
     for N in (line // 32 * 32, line // 32 * 32 + 33):
@@ -196,7 +198,7 @@ def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
         rand = lambda h: torch.randn(B, h, N, d, generator=g, device="cuda").bfloat16()  # noqa: E731
         Q, K, V = rand(H), rand(Hkv), rand(Hkv)
         desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
-        sizes = [(N, 65), (N // 5, N // 3), (33, N), (31, 1)]
+        sizes = [(N, N)] * 4 if full else [(N, 65), (N // 5, N // 3), (33, N), (31, 1)]
         q_lists = [[np.sort(rng.choice(N, sizes[h % 4][0], replace=False)) for h in range(H)] for _ in range(B)]
         k_lists = [[np.sort(rng.choice(N, sizes[h % 4][1], replace=False)) for h in range(H)] for _ in range(B)]
         q_idx, q_cnt = lists_to_padded(q_lists, H, N)
@@ -215,9 +217,10 @@ def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal):
             assert float((lse[b, h, q][fin] - m[fin]).abs().max()) <= 2e-3
 
 
+@pytest.mark.parametrize("full", [False, True])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
-def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal):
+def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal, full):
     """Shapes just below and just above the lines between the dQ kernels (4.0e10) and the forward kernels (6.5e10; the
     backward takes each forward's output): block lists in place give the bits of their token lists, and the gradients of
     the first and the last sequence are those of 64-bit sums over the listed pairs."""
@@ -230,9 +233,11 @@ def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal):
             rand = lambda h, s=1.0: (s * torch.randn(B, h, N, d, generator=g, device="cuda")).bfloat16()  # noqa: E731
             Q, K, V, dO = rand(H), rand(Hkv), rand(Hkv), rand(H, d ** -0.5)
             desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
-            nb, nsel = N // block, N // block // 3
+            nb = N // block
+            nsel = nb if full else nb // 3
             blocks = [[np.sort(rng.choice(nb, nsel, replace=False)) for _ in range(H)] for _ in range(B)]
-            rows = [[np.sort(rng.choice(N, (N, N // 5, 33, 31)[h % 4], replace=False)) for h in range(H)] for _ in range(B)]
+            kept = (N, N, N, N) if full else (N, N // 5, 33, 31)
+            rows = [[np.sort(rng.choice(N, kept[h % 4], replace=False)) for h in range(H)] for _ in range(B)]
             q_idx, q_cnt = lists_to_padded(rows, H, N)
             blk_idx, _ = lists_to_padded(blocks, H, nb)
             blk_budget = torch.full((B,), nsel, dtype=torch.int32, device="cuda")
