@@ -69,9 +69,9 @@ __device__ __forceinline__ int lanes_lower_bound(const int* __restrict__ a, int 
   return lo;
 }
 
-// grid: (cdiv(max(N, npad), 256), B*Hq, 2).  z = 1: a wavefront owns 64 tokens and sets those of its rows that the window of
-// the kept-query list does not show to zero (one that it misses is set to zero too, and written again by the attention).
-// z = 0: a wavefront owns 64 positions of the lists and finds by search what each one sees.  Every entry of qvis and kfirst
+// grid: (cdiv(max(N, npad), 256), B*Hq, 1 to 3).  z = 1: a wavefront owns 64 tokens and sets those of its rows that the window
+// of the kept-query list does not show to zero (one that it misses is set to zero too, and written again by the attention).
+// z = 0 and 2: a wavefront owns 64 kept queries, or 64 slots of the key list, and finds by search what each one sees.  Every entry of qvis and kfirst
 // up to the counts, and every work item, is written from its own position, so that a list that repeats an index or (without
 // the causal mask, where nothing has to be searched) is in any order gives what it means, and no list leaves an entry
 // unwritten that a kernel then takes for a size.  Bound by the stores of the zeros (the searches of the other wavefronts hide
@@ -95,11 +95,13 @@ __global__ __launch_bounds__(kThreads) void bounds_kernel(Layer L, Bounds p) {
   }
   const int nkeys = max(min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap), 0);
   const int* klist = p.klist + (long long)bh * p.klist_stride;
-  if (p.kfirst && r0 < p.npad) {                   // slots: who is the first to see the key (pads: nobody)
+  if (blockIdx.z == 2) {                           // slots: who is the first to see the key (pads: nobody)
+    if (r0 >= p.npad) return;
     const int tok = r0 < nkeys ? klist[min(n, nkeys - 1)] : 0;
     const int first = r0 < nkeys && L.causal ? lanes_lower_bound(qlist, nq, tok) : 0;
     if (n < p.npad) p.kfirst[(long long)bh * p.npad + n] = n < nkeys ? first : nq;
-    if (p.inv && n < nkeys && (unsigned)tok < (unsigned)L.N) p.inv[(long long)bh * L.N + tok] = n;
+    if (n < nkeys && (unsigned)tok < (unsigned)L.N) p.inv[(long long)bh * L.N + tok] = n;
+    return;
   }
   if (r0 >= nq) return;
   const int row = qlist[min(n, nq - 1)];           // kept queries: how many keys they see
@@ -290,7 +292,7 @@ int check_work_list(const Layer& L, int tile_m) {
 
 int run_bounds(const Layer& L, const Bounds& p, hipStream_t st) {
   const int BH = L.B * L.Hq, n = p.kfirst ? max(L.N, p.npad) : L.N;
-  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH, p.X ? 2 : 1), dim3(kThreads), 0, st, L, p);
+  hipLaunchKernelGGL(bounds_kernel, dim3(cdiv(n, kThreads), BH, p.kfirst ? 3 : p.X ? 2 : 1), dim3(kThreads), 0, st, L, p);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
