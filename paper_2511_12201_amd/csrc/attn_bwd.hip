@@ -734,7 +734,9 @@ constexpr int kSplitThreads = kSplitWaves * 64;
 // Which of the two dQ kernels, by the shape only (the gathered and the in-place lists of a layer take the same one).  Forward
 // and backward of a layer in us, (heads, d) N: split / the other, a third of the queries and half of the keys kept:
 // (28, 128) 1072: 149 / 170, 2048: 203 / 224, 4096 (6.0e10): 346 / 347, (56, 64) 3101 (3.4e10): 203 / 220, (28, 64) 6000
-// (6.5e10): 363 / 375, (8, 128) 4096 (1.7e10): 227 / 259, 7500 (5.8e10): 457 / 442.
+// (6.5e10): 363 / 375, (8, 128) 4096 (1.7e10): 227 / 259, 7500 (5.8e10): 457 / 442.  On lists of everything (both rules' split
+// kernels / the others / the 256-row items that all shapes had before): (28, 128) 2048: 364 / 392 / 434, 3300 (3.9e10): 724 /
+// 661 / 735, (28, 64) 4600 (3.8e10): 697 / 688 / 747, (8, 128) 6000 (3.7e10): 627 / 711 / 831.
 constexpr double kSplitWork = 4.0e10;
 
 // grid: cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first

@@ -931,8 +931,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_f32_long_kernel(FwdParam
 // CU outweighs the length of a chain.  Whole attention call in us, (heads, d) N: split / the other, a third of the
 // queries and half of the keys kept: (28, 128) 1072: 30 / 55, 3101: 60 / 83, 4096: 85 / 100, 6000: 134 / 129,
 // (28, 64) 4096: 53 / 78, 8192: 122 / 119, (8, 128) 6000: 85 / 110, 8192: 139 / 137, (8, 64) 8192: 76 / 104,
-// 12000: 140 / 140; not causal (28, 128) 3101: 81 / 85.  The line lies below all crossings; it looks at the shape only, so
-// that the gathered and the in-place lists of the same layer take the same kernel.
+// 12000: 140 / 140; not causal (28, 128) 3101: 81 / 85.  The line lies below all crossings of such lists; it looks at the shape
+// only (the counts are on the device), so that the gathered and the in-place lists of the same layer take the same kernel.
+// On lists of everything the other kernel is ahead from about 2.4e10 on, split / the other / the 256-row items that all
+// shapes had before: (28, 128) 2048: 75 / 96 / 111, 3101: 135 / 132 / 177, 4096: 226 / 181 / 229, (28, 64) 4600: 140 / 145 /
+// 186, 5900: 225 / 208 / 248, (8, 128) 7900: 197 / 210 / 226, not causal (28, 128) 2900: 209 / 192 / 209.
 constexpr double kSplitWork = 6.5e10;
 
 // Rows of a head's packed K/V buffer: whole tiles, and never a multiple of 4096 rows -- with a power-of-two
