@@ -628,9 +628,9 @@ int omni_profile_read(int kernel_id, float* total_ms /* host */, int* launches /
  * queue (one list after all if a head outweighs 1.5 fair shares); inside a queue head
  * follows head, each longest item first, where the work of a CU (of 256) is at least 3.4 longest
  * items, else all items longest first; a workgroup takes from its XCD's queue and, once
- * that is drained, from the queue with the most items left.  All pointers are HOST pointers.  q_cnt [batch * n_q_heads] (null: every head keeps n_tokens rows),
- * budget [batch] (null: n_tokens); item_head / item_tile / item_cost [capacity] out,
- * queue after queue in hand-out order; queue_end [8] out (nullable): queue q is the
+ * that is drained, from the queue with the most items left.  All pointers are HOST pointers.
+ * q_cnt [batch * n_q_heads] (null: every head keeps n_tokens rows), budget [batch]
+ * (null: n_tokens); item_head / item_tile / item_cost [capacity] out, queue after queue in hand-out order; queue_end [8] out (nullable): queue q is the
  * positions [queue_end[q-1], queue_end[q]); n_items out.  OMNI_ERR_WORKSPACE if
  * capacity is too small (n_items is still written).
  */

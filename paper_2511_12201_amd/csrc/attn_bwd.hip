@@ -64,7 +64,8 @@ struct BwdParams {
   int split_len;        // query tiles per split, at least (bf16: at most, see key_list_kernel)
   int key_wgs;          // workgroups that share the key kernels' items
   long long plane;      // floats between the partial-gradient planes of two splits
-  int* klist;           // work list of the key kernels: [0], [1] counters (dV, dK kernel), [2] items, [3] split length, [4..] items; null: fp32
+  int* klist;           // work list of the key kernels: [0], [1] counters (dV, dK kernel), [2] number of items, [3] split
+                        // length, [4..] items; null: fp32
   // In-place block lists (TILEMAP kernels): Kn, Vn, Kt hold every KV head once, in token order ([B*Hkv, npad_kv, D]),
   // and tile t of a head's key list is tile tile_map[bh * tile_stride + t] of its KV head's copy.
   const int* tile_map;
@@ -87,7 +88,7 @@ constexpr int kKeyQ = 64;                    // queries per streamed tile
 // A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
 // against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
 // query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
-constexpr int kKeySplitLenF32 = 4;           // fp32: query tiles per split, at least; a workgroup owns 32 keys and needs company sooner
+constexpr int kKeySplitLenF32 = 4;           // fp32: query tiles per split, at least (a workgroup owns 32 keys: needed sooner)
 constexpr int kKeySplitLen = 128;            // bf16: query tiles per split, at most (64..128 measure alike, 32 and 256 worse)
 constexpr int kKeyMaxSplits = 4;             // at most 8: a work item carries the split in 3 bits
 __host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
@@ -275,9 +276,9 @@ __global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_dq_f32_kernel(BwdP
   });
 }
 
-// fp32, long sequences (f32_short): workgroups of 128 keys, or of 128 kept queries from the work list, 32 per wavefront; tiles of 64 rows of the
-// other side staged row by row through LDS, Q and dO straight from the caller's arrays.  One plane of dK', dV', no other
-// copies than K and V: a quarter of the scratch.
+// fp32, long sequences (f32_short): workgroups of 128 keys, or of 128 kept queries from the work list, 32 per wavefront;
+// tiles of 64 rows of the other side staged row by row through LDS, Q and dO straight from the caller's arrays.  One plane
+// of dK', dV', no other copies than K and V: a quarter of the scratch.
 constexpr int kF32Keys = 128;
 
 // grid: (npad / 128, B*Hq)

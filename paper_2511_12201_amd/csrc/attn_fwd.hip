@@ -834,7 +834,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_f32_long_kernel(FwdParam
     const long long row_off = b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
     f32x4 qf[D / 8];
 #pragma unroll
-    for (int ks = 0; ks < D / 8; ++ks) qf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Q) + row_off + ks * 8 + h * 4);
+    for (int ks = 0; ks < D / 8; ++ks)
+      qf[ks] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.Q) + row_off + ks * 8 + h * 4);
     f32x16 o[D / 32];
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -847,9 +848,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_f32_long_kernel(FwdParam
       __syncthreads();
       u32x4 stK[kChunks], stV[kChunks];
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) stK[c] = *reinterpret_cast<const u32x4*>(kp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
+      for (int c = 0; c < kChunks; ++c)
+        stK[c] = *reinterpret_cast<const u32x4*>(kp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) stV[c] = *reinterpret_cast<const u32x4*>(vp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
+      for (int c = 0; c < kChunks; ++c)
+        stV[c] = *reinterpret_cast<const u32x4*>(vp + (long long)t * kTileN * D + (threadIdx.x + c * kThreads) * 4);
 #pragma unroll
       for (int c = 0; c < kChunks; ++c) {
         const int ch = threadIdx.x + c * kThreads, row = ch / CPR, col = ch % CPR * 4;
@@ -1057,7 +1060,8 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
   // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
   // costs (25.7 -> 25.9 ms dense).
-  rc = sparse ? run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1) : run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
+  rc = sparse ? run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1)
+              : run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
   if (rc != OMNI_OK) return rc;
   ProfScope prof__(kProfAttnFwd, st);
   if constexpr (kFast)

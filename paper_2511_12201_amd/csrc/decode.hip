@@ -795,9 +795,10 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
 constexpr int kCombineThreads = 1024;
 // Two workgroups a head halve the trips over the slices, which pays where there are several (one cut takes 64 slices a trip at
 // d = 128); elsewhere the second one costs its launch and reads every maximum and sum again.  Decode step on group lists in
-// us, one cut / two / before either: 28 heads, d = 128, 131072 tokens (257 slices) 34.6 / 33.1 / 36.9, 16000 (201) 15.7 / 15.1 / 17.0, four sequences of
-// 16000 (57) 23.0 / 23.3 / 24.6, one of 4108 (66) 10.4 / 10.6 / 11.4, 32 x 4108 35.7 / 38.1 / 36.4; d = 64 (128 a trip), 16000 11.1 / 11.6 / 11.9,
-// 32 x 700 12.1 / 15.0 / 13.0; 8 heads, d = 128, four of 16000 (105) 15.1 / 14.6 / 16.0, eight (57) 22.1 / 22.3 / 23.4.
+// us, one cut / two / before either: 28 heads, d = 128, 131072 tokens (257 slices) 34.6 / 33.1 / 36.9, 16000 (201) 15.7 /
+// 15.1 / 17.0, four sequences of 16000 (57) 23.0 / 23.3 / 24.6, one of 4108 (66) 10.4 / 10.6 / 11.4, 32 x 4108 35.7 / 38.1 /
+// 36.4; d = 64 (128 a trip), 16000 11.1 / 11.6 / 11.9, 32 x 700 12.1 / 15.0 / 13.0; 8 heads, d = 128, four of 16000 (105)
+// 15.1 / 14.6 / 16.0, eight (57) 22.1 / 22.3 / 23.4.
 inline int combine_cuts(int D, int slices) { return D == 128 && slices > 96 ? 2 : 1; }
 
 template <typename T, int D, int CUTS>

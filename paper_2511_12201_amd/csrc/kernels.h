@@ -58,11 +58,12 @@ inline double attention_work(const Layer& L) { return (double)L.B * L.Hq * L.N *
 // items with tiles in LDS.  The long items are the faster ones once they fill the chip, which their number decides (rows of
 // all heads, twice as many without the causal mask: each works twice as long); the longer the sequence, the longer the chains
 // that the short items save; below 1400 tokens there is little to save and the width counts (at d = 128 one workgroup of the
-// short items fills a CU).  Call in us, short / long items; batch x heads, d, N; a third of the queries and half of the keys kept, or all
-// (full).  Forward and backward, below the lines: 1 x 28, 128, 1072 289 / 671 and (full) 634 / 919; 6 x 28, 128, 256 251 / 357 and
-// (full) 417 / 450; 1 x 28, 128, 3500 1562 / 1983 and (full) 4712 / 4918; 1 x 8, 128, 8192 4300 / 4407 and (full) 6339 / 8282; above
-// them: 8 x 28, 128, 256 319 / 385 but (full) 537 / 519; 1 x 28, 128, 4096 2002 / 2356 but (full) 6183 / 6132; 1 x 8, 128, 10000 6226 / 5405;
-// 1 x 28, 128, 8192 6860 / 5747 and (full) 24707 / 21438; forward 16 x 28, 128, 512 (full) 681 / 521.
+// short items fills a CU).  Call in us, short / long items; batch x heads, d, N; a third of the queries and half of the keys
+// kept, or all (full).  Forward and backward, below the lines: 1 x 28, 128, 1072 289 / 671 and (full) 634 / 919; 6 x 28,
+// 128, 256 251 / 357 and (full) 417 / 450; 1 x 28, 128, 3500 1562 / 1983 and (full) 4712 / 4918; 1 x 8, 128, 8192 4300 /
+// 4407 and (full) 6339 / 8282; above them: 8 x 28, 128, 256 319 / 385 but (full) 537 / 519; 1 x 28, 128, 4096 2002 / 2356
+// but (full) 6183 / 6132; 1 x 8, 128, 10000 6226 / 5405; 1 x 28, 128, 8192 6860 / 5747 and (full) 24707 / 21438; forward
+// 16 x 28, 128, 512 (full) 681 / 521.
 inline bool f32_short(const Layer& L) {
   const double rows = (double)L.B * L.Hq * L.N * (L.causal ? 1.0 : 2.0);
   return short_route(L.N < 1400 ? rows * L.D <= 6.0e6 : rows <= (L.N <= 3500 ? 9.8e4 : 6.6e4));

@@ -74,9 +74,9 @@ __device__ __forceinline__ void transpose4x4_store(const u32x4 (&in)[4], float* 
 // here from the scores and the head's cut saves the list writer nothing (it still runs, for the queries) and puts a search,
 // a scan and a ranking before every gather.  One-call prefill in us, formed here / read: 1072 tokens 93.3 / 90.6, 4096:
 // 153 / 148, 16384: 526 / 520, 65536: 4797 / 4792; 8 heads, 16384: 313 / 302.
-// bf16: two wavefronts per output, so that a thread has one batch of loads and the outputs do not wait for each other.  (The copies
-// by all threads, then the transposes by those that had one, was a second memory latency for every workgroup.)  Memory-bound
-// on long sequences.  Layer in us, before / after, with the same change in pack_q below: forward, 1072 tokens 89.5 / 87.3,
+// bf16: two wavefronts per output, so that a thread has one batch of loads and the outputs do not wait for each other.  (The
+// copies by all threads, then the transposes by those that had one, was a second memory latency for every workgroup.)
+// Memory-bound on long sequences.  Layer in us, before / after, with the same change in pack_q below: forward, 1072 tokens 89.5 / 87.3,
 // 16391: 432.5 / 430.3, d = 64, 3000: 41.7 / 40.1; forward and backward, two clips of 3101, d = 64: 202.4 / 198.3, 32768:
 // 7364 / 7339.  (d threads per output: 8192 at d = 64 2.5 % slower.)
 constexpr int kOutThreads = 128;
@@ -119,7 +119,8 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
       u32x4 in[kEach];
 #pragma unroll
       for (int j = 0; j < kEach; ++j) {
-        const int c = j * kOutThreads + t, row = k_frag ? c / (32 * CPR) * 32 + (c & 31) : c / CPR, chunk = k_frag ? c / 32 % CPR : c % CPR;
+        const int c = j * kOutThreads + t;
+        const int row = k_frag ? c / (32 * CPR) * 32 + (c & 31) : c / CPR, chunk = k_frag ? c / 32 % CPR : c % CPR;
         const int id = sIdx[row];
         in[j] = zero;
         if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + chunk * E);

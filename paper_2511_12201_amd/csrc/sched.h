@@ -51,7 +51,8 @@ struct Bounds {
   int* qvis;                     // [B*Hq, N] number of listed keys that kept query `pos` may see
   int* kfirst;                   // [B*Hq, npad] first kept-query position that may see listed key `slot` (needs inv and X)
   int* inv;                      // [B*Hq, N] slot of the token in the key list (listed tokens only)
-  void* X;                       // nullable (then lse is not written either): rows of the Q-shaped tensor (16-byte aligned) that are not kept are set to zero
+  void* X;                       // nullable (then lse is not written either): rows of the Q-shaped tensor (16-byte aligned)
+                                 // that are not kept are set to zero
   int elem_bytes;
   float* lse;                    // [B*Hq, N] -inf for the rows that are not kept
   int tile_m;                    // rows per work item

@@ -71,12 +71,14 @@ __device__ __forceinline__ int lanes_lower_bound(const int* __restrict__ a, int 
 
 // grid: (cdiv(max(N, npad), 256), B*Hq, 1 to 3).  z = 1: a wavefront owns 64 tokens and sets those of its rows that the window
 // of the kept-query list does not show to zero (one that it misses is set to zero too, and written again by the attention).
-// z = 0 and 2: a wavefront owns 64 kept queries, or 64 slots of the key list, and finds by search what each one sees.  Every entry of qvis and kfirst
-// up to the counts, and every work item, is written from its own position, so that a list that repeats an index or (without
-// the causal mask, where nothing has to be searched) is in any order gives what it means, and no list leaves an entry
-// unwritten that a kernel then takes for a size.  Bound by the stores of the zeros (the searches of the other wavefronts hide
-// under them).  It took the place of two search kernels, a fill and a scatter of the slot map, a clearing pass over all rows
-// and two list kernels.
+// z = 0 and 2: a wavefront owns 64 kept queries, or 64 slots of the key list, and finds by search what each one sees.  Every
+// entry of qvis and kfirst up to the counts, and every work item, is written from its own position, so that a list that
+// repeats an index or (without the causal mask, where nothing has to be searched) is in any order gives what it means, and
+// no list leaves an entry unwritten that a kernel then takes for a size.  Bound by the stores of the zeros (375 MB in all at
+// 64k, three quarters of the rows dropped: 5.5 TB/s); the searches of the other wavefronts hide under them.  It took the
+// place of a search kernel, a clearing pass over all rows, the pricing of the items and, in the backward, a fill and a
+// scatter of the slot map: 28 heads, d = 128, 64k forward 88 -> 67 us, 32k forward and backward 111 -> 65 us; d = 64, two
+// clips of 3101, forward and backward 43 -> 14 us.
 __global__ __launch_bounds__(kThreads) void bounds_kernel(Layer L, Bounds p) {
   const int bh = blockIdx.y, b = bh / L.Hq, i = bh % L.Hq, lane = lane_id();
   const int r0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kThreads + (threadIdx.x & ~63))), n = r0 + lane;
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(64) void sched_estimate_kernel(const int* __restric
 
 // grid: cdiv(cap, kRankItems).  The hand-out order of the items: an item's rank among the keys (all distinct) is its
 // place.  Every workgroup places the heads on the queues for itself (a few hundred instructions: less than a launch),
-// the first one writes the header.  One launch where there were three (prefix, cost, placement, rank: 21 -> 5 us at 1k, 37 -> 17 us at 64k).
+// the first one writes the header.  One launch where there were three (prefix, placement, rank): 31 -> 18 us at 64k, 29 -> 11 at 32k.
 constexpr int kRankLanes = 16;
 constexpr int kRankItems = kThreads / kRankLanes;           // items per workgroup
 struct QueuePlaces {

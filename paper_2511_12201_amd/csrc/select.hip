@@ -115,7 +115,8 @@ __device__ __forceinline__ void histogram_add(RadixShared& sh, int rep, unsigned
   if (MASS) atomicAdd(&sh.sum[rep + digit], to_fixed(value));
   else atomicAdd(&sh.cnt[rep + digit], 1u);
 }
-// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem moved on to it.  Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
+// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem moved on to it.
+// Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
 template <bool MASS>
 __device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int shift) {
   __syncthreads();

@@ -142,7 +142,8 @@ def _work_list_lists(kind, rng):
     pick = lambda N, n: np.sort(rng.choice(N, n, replace=False)).astype(np.int32)  # noqa: E731
     if kind == "edges":                                      # counts around one and several items, empty heads, empty key lists
         N = 1100
-        return N, [pick(N, n) for n in (N, 0, 1, 127, 128, 129, 255, 256, 257, 0, 512, 513)],             [pick(N, n) for n in (600, 5, 0, N, 64, 65, 1, 700, 333, 0, 2, N)]
+        return N, [pick(N, n) for n in (N, 0, 1, 127, 128, 129, 255, 256, 257, 0, 512, 513)], \
+            [pick(N, n) for n in (600, 5, 0, N, 64, 65, 1, 700, 333, 0, 2, N)]
     if kind == "even":                                       # no head outweighs a queue
         N = 2000
         return N, [pick(N, 600 + 13 * h) for h in range(24)], [pick(N, 900 - h) for h in range(24)]
