@@ -9,7 +9,7 @@
 // (8 wavefronts, LDS-DMA ring, position masks from the visible-prefix counts):
 //  * attn_bwd_dq_bf16_kernel: a work item is 256 kept queries of a head (32 per wavefront) from the forward's
 //    longest-first list; it streams 64-key tiles of K, V (natural) and K^T (k-packed): S^T = K Q^T,
-//    dP^T = V dO^T, dQ^T += K^T dS^T.
+//    dP^T = V dO^T, dQ^T += K^T dS^T.  Short sequences: attn_bwd_dq_split_kernel, 32 queries an item, no list.
 //  * attn_bwd_key_bf16_kernel<D, MODE>: a workgroup owns 256 packed keys of a query head (32 per wavefront, K or V
 //    fragments resident) and streams 64-query tiles of the packed kept rows (Q, dO natural and k-packed, lse and
 //    delta by 4-byte LDS-DMA).  MODE 0 forms dK' = dS^T Q, MODE 1 dV' = P^T dO: two launches, because the resident

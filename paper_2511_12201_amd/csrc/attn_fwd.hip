@@ -4,9 +4,10 @@
 //
 // Design for gfx950:
 //  * A pack pass (pack.hip) gathers each head's selected K rows into a dense
-//    row-major buffer and its V rows into the exact operand order the matrix
-//    cores need (below), zero-padding to whole 64-key tiles and recording the
-//    original token index of every slot.  The dense baseline runs the same pack
+//    buffer (row-major, or in fragment order for the kernels that read it without
+//    LDS) and its V rows into the exact operand order the matrix cores need
+//    (below; rows as they are for the long fp32 kernel), zero-padding to whole
+//    64-key tiles and recording the original token index of every slot.  The dense baseline runs the same pack
 //    with identity indices per KV head.  The main loop is then free of gathers.
 //  * Both GEMMs are computed transposed, S^T = K Q^T and O^T = V^T P^T, with
 //    32x32 MFMA tiles.  Each lane then owns one query column: the softmax row
@@ -27,7 +28,7 @@
 //    s_waitcnt), one barrier per tile; inside a wavefront the softmax of tile t
 //    runs under the MFMAs of tile t+1.  Work items come from a persistent,
 //    longest-first work list with one queue per XCD (sched.hip); causal masks are
-//    position compares against per-query visible-prefix counts (pack.hip).
+//    position compares against per-query visible-prefix counts (bounds_kernel, sched.hip).
 //    Short sequences go through attn_fwd_split_kernel: 32-row items, key tiles dealt to the wavefronts.
 //  * fp32 inputs (the accuracy path of the 1e-4 parity cases): the fp32 32x32x2 MFMA.  Short sequences
 //    (attn_fwd_f32_kernel) have the division of labour of the split kernel, long ones (attn_fwd_f32_long_kernel) 128-row

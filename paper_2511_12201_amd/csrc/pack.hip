@@ -8,10 +8,12 @@
 // 32x32 MFMA accumulator holds its rows -- so that the operand of a GEMM that
 // contracts over the slots is one 16-byte read per lane.  The k-packed
 // V (the forward's operand; the backward does not use it) is written in f16: the
-// forward multiplies its f16-rounded weights with it.  fp32 inputs: "fragment order"
-// for natural rows ([32-row block][8-wide k step][lane] of 16 bytes, lane = 32 h + row),
-// and k-packed [32-slot block][q4][d / 32][h][d % 32][4 slots], slot = 8 q4 + 4 h + e: the
-// fp32 MFMA takes one element per lane, four of them arrive with one 16-byte read.
+// forward multiplies its f16-rounded weights with it.  k_frag: natural rows in "fragment
+// order" instead, [32-row block][k step][lane] of 16 bytes, lane = 32 h + row (a k step is 16
+// elements of bf16, 8 of fp32), for the kernels of short sequences, which take their operands
+// straight from memory.  fp32 inputs, k-packed: [32-slot block][q4][d / 32][h][d % 32][4
+// slots], slot = 8 q4 + 4 h + e: the fp32 MFMA takes one element per lane, four of them
+// arrive with one 16-byte read.
 //
 // pack_q: for the backward pass, the kept rows of Q and dO in the k-packed
 // layout (contraction over queries) and, for bf16, also as contiguous natural
