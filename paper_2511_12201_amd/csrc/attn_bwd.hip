@@ -10,12 +10,11 @@
 //  * attn_bwd_dq_bf16_kernel: a work item is 256 kept queries of a head (32 per wavefront) from the forward's
 //    longest-first list; it streams 64-key tiles of K, V (natural) and K^T (k-packed): S^T = K Q^T,
 //    dP^T = V dO^T, dQ^T += K^T dS^T.  Short sequences: attn_bwd_dq_split_kernel, 32 queries an item, no list.
-//  * attn_bwd_key_bf16_kernel<D, MODE>: a workgroup owns 256 packed keys of a query head (32 per wavefront, K or V
-//    fragments resident) and streams 64-query tiles of the packed kept rows (Q, dO natural and k-packed, lse and
-//    delta by 4-byte LDS-DMA).  MODE 0 forms dK' = dS^T Q, MODE 1 dV' = P^T dO: two launches, because the resident
-//    fragments and accumulators of both do not fit two wavefronts per SIMD; S = Q K^T is computed in both.  Items
-//    (head, key tile, split) come from a list a small kernel compacts; a key tile seen by many query tiles is
-//    shared by up to four workgroups, each with a partial plane of its own.
+//  * attn_bwd_key_bf16_kernel: a workgroup owns 256 packed keys of a query head (32 per wavefront, K and V fragments
+//    resident) and streams 32-query tiles (d = 64: 64) of the packed kept rows (Q, dO natural and k-packed, lse and
+//    delta by 4-byte LDS-DMA): S = Q K^T, dP = dO V^T, dV' += P^T dO, dK' += dS^T Q.  Items (head, key tile, split)
+//    come from a list a small kernel compacts; a key tile seen by many query tiles is shared by up to four workgroups,
+//    each with a partial plane of its own.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
 // fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_key_f32_kernel (dK' and dV' of 32 keys together) and attn_bwd_dq_f32_kernel;
@@ -59,13 +58,13 @@ struct BwdParams {
   size_t order_off;     // where its hand-out order starts
   const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position
   const int* kfirst;    // [B*Hq, npad] first kept-query position that sees a packed key
-  int head_group;       // heads per dispatch group of the key kernels
-  int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernels)
+  int head_group;       // heads per dispatch group of the key kernel
+  int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernel)
   int split_len;        // query tiles per split, at least (bf16: at most, see key_list_kernel)
-  int key_wgs;          // workgroups that share the key kernels' items
+  int key_wgs;          // workgroups that share the key kernel's items
   long long plane;      // floats between the partial-gradient planes of two splits
-  int* klist;           // work list of the key kernels: [0], [1] counters (dV, dK kernel), [2] number of items, [3] split
-                        // length, [4..] items; null: fp32
+  int* klist;           // work list of the key kernel: [0] counter, [1] number of items, [2] split length, [4..] items;
+                        // null: fp32
   // In-place block lists (TILEMAP kernels): Kn, Vn, Kt hold every KV head once, in token order ([B*Hkv, npad_kv, D]),
   // and tile t of a head's key list is tile tile_map[bh * tile_stride + t] of its KV head's copy.
   const int* tile_map;
@@ -850,23 +849,28 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
 
 // ------------------------------------------------------------------ dK' and dV', bf16 fast path
 //
-// Two kernels of the same shape as the dQ kernel with the roles of keys and queries swapped: a workgroup
-// of 8 wavefronts owns 256 packed keys of one query head (32 per wavefront, K and V fragments resident in
-// registers) and streams 64-query tiles of the packed kept rows memory -> LDS with LDS-DMA loads into a
-// ring.  Keeping dK and dV in one kernel needs 192 registers for the resident fragments and the two
-// accumulators alone, which does not fit two wavefronts per SIMD; split, each kernel does, and the price
-// is that S = Q K^T is computed twice (8 GEMMs per pair in the whole backward instead of 7).
-//   MODE 0 (dK): streams Q, dO (natural) and Q (k-packed):  S, dP -> dS;  dK'^T += Q^T dS
-//   MODE 1 (dV): streams Q (natural) and dO (k-packed):     S -> P;       dV'^T += dO^T P
+// The dQ kernel with the roles of keys and queries swapped: a workgroup of 8 wavefronts owns 256 packed keys of one
+// query head (32 per wavefront, K and V fragments resident in registers) and streams tiles of the packed kept rows
+// memory -> LDS with LDS-DMA loads into a ring of four: Q and dO row by row (operands of S and dP) and k-packed (of the
+// updates), 8 KB each, so that a wavefront issues one load per operand and tile, three tiles ahead.  Per 32 queries and
+// wavefront: S (D/16 matrix instructions), dP with the weights P of S on the vector ALU under it, dV' += P^T dO with dS
+// under it, dK' += dS^T Q.  At d = 128 the fragments (64 registers), the two accumulators (128), S and dP (32) and what
+// the loop needs around them are exactly the 256 registers of two wavefronts per SIMD: nothing of the tile loop is
+// spilled, and the other wavefront works on the matrix cores while this one packs its weights.  Tiles of 32 queries,
+// because a stage of 64 would leave the ring two stages.
+// Bound: matrix cores, waiting in part for their wavefronts.  dK' and dV' as two kernels, each with an S of its own (5
+// products where 4 are needed, Q read twice), took 2226 + 1384 us at 32k, 28 heads, d = 128; forward and backward there
+// 7537 -> 6968 us, two clips of 3101 at d = 64 215 -> 187 us, blocks at 16k 3380 -> 3124 us, with the same results to the
+// last bit.
 // lse * log2e and delta of the tile's queries come with the tile (LDS-DMA of 4 bytes per lane); the causal
 // mask is a comparison of the query position with the first position that sees the lane's key.
 
-// Work items of the key kernels: (head, key tile, split), in dispatch order -- heads in groups of p.head_group,
+// Work items of the key kernel: (head, key tile, split), in dispatch order -- heads in groups of p.head_group,
 // inside a group key tile by key tile (the first key tiles, seen by the most queries, first), the splits of a
 // tile side by side.  Slot i of that order is a (head, key tile); most are empty (key tiles beyond a head's
-// budget), so one workgroup lists the live ones with their splits, and the persistent key kernels pull from
+// budget), so one workgroup lists the live ones with their splits, and the persistent key kernel pulls from
 // the list: an empty workgroup would still wait for a whole CU's LDS.
-constexpr int kKeyListHeader = 4;            // counters (dV, dK kernel), items, query tiles per split
+constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, -
 
 // head and key tile of slot i, and how many query tiles see it (0: nothing to do)
 __device__ __forceinline__ int key_slot(const BwdParams& p, long long i, int& bh, int& ktile) {
@@ -917,27 +921,26 @@ __global__ __launch_bounds__(1024) void key_list_kernel(BwdParams p, long long n
   }
   if (threadIdx.x == 0) {
     p.klist[0] = 0;
-    p.klist[1] = 0;
-    p.klist[2] = base;
-    p.klist[3] = split_len;
+    p.klist[1] = base;
+    p.klist[2] = split_len;
   }
 }
 
-template <int D, int MODE, bool TILEMAP>
+template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdParams p) {
   typedef u16 T;
   constexpr int CH = D / 8;
   constexpr int NB = D / 32;
-  constexpr int NOPS = MODE == 0 ? 3 : 2;            // streamed operand tiles
-  constexpr int kStages = MODE == 0 ? 3 : 4;
+  constexpr int KS = D / 16;
+  constexpr int kRows = 4096 / D;                    // queries per streamed tile: 8 KB an operand, one load a wavefront
+  constexpr int kStages = 4;
   constexpr int kAheadTiles = kStages - 1;
-  constexpr int NSMALL = MODE == 0 ? 2 : 1;          // wavefronts that also bring a 256-byte per-query array
-  constexpr int kOpBytes = kKeyQ * D * 2;
-  constexpr int kSmallOff = NOPS * kOpBytes;
-  constexpr int kStageBytes = kSmallOff + 1024;
-  constexpr int LPH = kOpBytes / 1024 / kKeyWaves;
-  constexpr int LPT = NOPS * LPH;
-  static_assert(LPH >= 1, "tile too small for the copy scheme");
+  constexpr int NSMALL = kRows / 32;                 // wavefronts that also bring lse and delta of 32 queries
+  constexpr int kOpBytes = kRows * D * 2;
+  constexpr int kSmallOff = 4 * kOpBytes;
+  constexpr int kStageBytes = kSmallOff + NSMALL * 256;
+  constexpr int LPT = 4;                             // loads of a wavefront per tile
+  static_assert(kOpBytes == kKeyWaves * 1024 && kKeyQ % kRows == 0, "one 1 KB load per wavefront and operand");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * kStageBytes];
   __shared__ int sBound[2];
   __shared__ int sItem;
@@ -952,8 +955,8 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   for (;;) {                                   // persistent: one item of the work list per iteration
   __syncthreads();                             // LDS of the previous item is no longer read
   if (threadIdx.x == 0) {
-    const int k = atomicAdd(&p.klist[MODE], 1);
-    sItem = k < p.klist[2] ? p.klist[kKeyListHeader + k] : -1;
+    const int k = atomicAdd(&p.klist[0], 1);
+    sItem = k < p.klist[1] ? p.klist[kKeyListHeader + k] : -1;
   }
   __syncthreads();
   const int item = __builtin_amdgcn_readfirstlane(sItem);
@@ -976,11 +979,11 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   const int n_qtiles = cdiv(nq, kKeyQ);
   const int q_first = sBound[0] / kKeyQ;                    // first query tile with an admissible pair
   const int n_all = n_qtiles - q_first;
-  const int n_sp = key_tile_splits(n_all, p.nsplit, p.klist[3]);
+  const int n_sp = key_tile_splits(n_all, p.nsplit, p.klist[2]);
   const int per_split = cdiv(n_all, n_sp);
-  const int q_begin = q_first + sp * per_split;             // this workgroup's query tiles: [q_begin, q_begin + n)
+  const int q_begin = q_first + sp * per_split;             // this workgroup's query tiles: [q_begin, q_begin + per_split)
 
-  // resident K (and V) fragments: B operands, lane = key column
+  // resident K and V fragments: B operands, lane = key column
   long long kv_row = (long long)bh * p.npad + slot;
   if constexpr (TILEMAP) {           // the slot's row inside its KV head's token-ordered copy (slots past the map: masked)
     const int t = slot / kTileN;
@@ -992,167 +995,130 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   const int kv_step = p.k_frag ? 512 : 16;
   const T* krow = static_cast<const T*>(p.Kn) + kv_at;
   const T* vrow = static_cast<const T*>(p.Vn) + kv_at;
-  bf16x8 kf[D / 16], vf[MODE == 0 ? D / 16 : 1];
+  bf16x8 kf[KS], vf[KS];
 #pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
+  for (int ks = 0; ks < KS; ++ks) {
     kf[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * kv_step);
-    if (MODE == 0) vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * kv_step);
+    vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * kv_step);
   }
   // finish every ordinary load here: a compiler-placed wait inside the tile loop would drain the ring
 #pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
+  for (int ks = 0; ks < KS; ++ks) {
     asm volatile("" : "+v"(kf[ks]));
-    if (MODE == 0) asm volatile("" : "+v"(vf[ks]));
+    asm volatile("" : "+v"(vf[ks]));
   }
   asm volatile("" : "+v"(my_first));
   const int first_h = my_first - 4 * h;
 
-  f32x16 acc[NB];
+  f32x16 dk[NB], dv[NB];
 #pragma unroll
   for (int db = 0; db < NB; ++db)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+    for (int r = 0; r < 16; ++r) dk[db][r] = 0.f, dv[db][r] = 0.f;
 
-  unsigned ngoff[LPH], pgoff[LPH];                          // byte offsets of this lane's chunk: natural (swizzled), packed
-#pragma unroll
-  for (int j = 0; j < LPH; ++j) {
-    const int pchunk = (j * kKeyWaves + wave) * 64 + lane;
-    const int row = pchunk / CH, pc = pchunk % CH;
-    ngoff[j] = (row * D + ((pc ^ (row % CH)) << 3)) * 2;      // bytes
-    pgoff[j] = pchunk << 4;
-  }
+  // byte offsets of this lane's 16-byte chunk of a tile: natural rows (swizzled), k-packed
+  const unsigned chunk0 = wave * 64 + lane;
+  const unsigned ngoff = (chunk0 / CH * D + ((chunk0 % CH ^ chunk0 / CH % CH) << 3)) * 2, pgoff = chunk0 << 4;
   const int krow_b = ln * (CH * 16);
   const int khx = (h << 4) ^ ((ln % CH) << 4);
   const int plane_b = (h * D + ln) * 16;
 
-  const T* qn = static_cast<const T*>(p.Qn) + (long long)bh * p.nqpad * D;
-  const T* gn = static_cast<const T*>(p.dOn) + (long long)bh * p.nqpad * D;
-  const T* qt = static_cast<const T*>(p.Qt) + (long long)bh * p.nqpad * D;
-  const T* gt = static_cast<const T*>(p.dOt) + (long long)bh * p.nqpad * D;
-  const float* lsec = p.lse2c + (long long)bh * p.nqpad;
-  const float* delc = p.deltac + (long long)bh * p.nqpad;
+  const long long q_row = (long long)bh * p.nqpad + (long long)q_begin * kKeyQ;    // first row of this workgroup's tiles
+  const T* qn = static_cast<const T*>(p.Qn) + q_row * D;
+  const T* gn = static_cast<const T*>(p.dOn) + q_row * D;
+  const T* qt = static_cast<const T*>(p.Qt) + q_row * D;
+  const T* gt = static_cast<const T*>(p.dOt) + q_row * D;
   const bool has_small = wave < NSMALL;
+  const float* small = p.lse2c + q_row + (has_small ? wave * 32 : 0);
+  const unsigned small_off = (unsigned)(h ? (p.deltac - p.lse2c) * 4 : 0) + ln * 4;      // delta lies behind lse (carve_bwd)
 
-  // u = tile index relative to q_begin (ring position); operand order: MODE 0: Q nat, dO nat, Q packed; MODE 1: Q nat, dO packed
-  auto issue_part = [&](int u, int part) {
-    const int op = part / LPH, j = part % LPH;
-    const unsigned dst = lds_base + (unsigned)(u % kStages) * kStageBytes + op * kOpBytes + (j * kKeyWaves + wave) * 1024;
-    const long long tile_off = (long long)(q_begin + u) * kKeyQ * D;
-    if (op == 0) gload_lds16(qn + tile_off, ngoff[j], dst);
-    else if (MODE == 0 && op == 1) gload_lds16(gn + tile_off, ngoff[j], dst);
-    else if (MODE == 0) gload_lds16(qt + tile_off, pgoff[j], dst);
-    else gload_lds16(gt + tile_off, pgoff[j], dst);
+  // u = tile index relative to the workgroup's first (ring position)
+  auto issue_part = [&](int u, int op) {
+    const unsigned dst = lds_base + (unsigned)(u % kStages) * kStageBytes + op * kOpBytes + wave * 1024;
+    const long long tile_off = (long long)u * kRows * D;
+    if (op == 0) gload_lds16(qn + tile_off, ngoff, dst);
+    else if (op == 1) gload_lds16(gn + tile_off, ngoff, dst);
+    else if (op == 2) gload_lds16(gt + tile_off, pgoff, dst);
+    else gload_lds16(qt + tile_off, pgoff, dst);
   };
   auto issue_small = [&](int u) {
-    if (!has_small) return;
-    const unsigned dst = lds_base + (unsigned)(u % kStages) * kStageBytes + kSmallOff + wave * 256;
-    const float* src = (wave == 0 ? lsec : delc) + (long long)(q_begin + u) * kKeyQ + lane;
-    gload_lds4(src, dst);
+    if (has_small) gload_lds4(small + u * kRows, small_off, lds_base + (unsigned)(u % kStages) * kStageBytes + kSmallOff + wave * 256);
   };
   auto issue_tile = [&](int u) {
 #pragma unroll
-    for (int j = 0; j < LPT; ++j) issue_part(u, j);
+    for (int op = 0; op < 4; ++op) issue_part(u, op);
     issue_small(u);
   };
 
-  constexpr int NA = (MODE == 0 ? 2 : 1) * (D / 16);   // MFMAs of phase A per 32-query block
-  constexpr int NC = 4 * NB;
-  constexpr int kAhead = 2;                    // fragment reads run this many MFMAs ahead
+  constexpr int NC = 2 * NB;                   // matrix instructions of a 32-query block in each of the two updates
+  constexpr int kAhead = 2;                    // fragment reads run this many of them ahead
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
   auto compute_tile = [&](int u, int pre, bool masked) {
     const unsigned char* st = smem + (u % kStages) * kStageBytes;
-    const int rel = first_h - (q_begin + u) * kKeyQ;                 // query positions below rel do not see this key
-    auto cfrag = [&](int c) {
-      const int t16 = c / NB, db = c % NB;
-      return *reinterpret_cast<const bf16x8*>(st + (NOPS - 1) * kOpBytes + plane_b + (t16 * 2 * D + db * 32) * 16);
-    };
-    // phase A of query block qb: S^T (and dP^T) of its 32 queries; under(c) is vector work placed behind MFMA c
-    auto phase_a = [&](int qb, f32x16& s, f32x16& dp, auto under) {
-      // chunk c: k-step ks, operand (0: Q for S, 1: dO for dP)
-      auto afrag = [&](int c) {
-        const int which = MODE == 0 ? c % 2 : 0, ks = MODE == 0 ? c / 2 : c;
-        return *reinterpret_cast<const bf16x8*>(st + which * kOpBytes + qb * (32 * CH * 16) + krow_b + ((ks << 5) ^ khx));
-      };
-      bf16x8 fa[kAhead];
-#pragma unroll
-      for (int c = 0; c < kAhead; ++c) fa[c] = afrag(c);
-#pragma unroll
-      for (int c = 0; c < NA; ++c) {
-        const int which = MODE == 0 ? c % 2 : 0, ks = MODE == 0 ? c / 2 : c;
-        __builtin_amdgcn_sched_barrier(0);
-        if (which == 0) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], kf[ks], ks == 0 ? zero16 : s, 0, 0, 0);
-        else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], vf[MODE == 0 ? ks : 0], ks == 0 ? zero16 : dp, 0, 0, 0);
-        if (c + kAhead < NA) fa[c % kAhead] = afrag(c + kAhead);
-        under(c);
-        // natural operand parts of the tile to prefetch: NOPS - 1 operands x LPH parts over 2 * NA MFMAs
-        constexpr int kParts = (NOPS - 1) * LPH, kEvery = 2 * NA / kParts;
-        if ((qb * NA + c) % kEvery == 0 && pre >= 0) issue_part(pre, (qb * NA + c) / kEvery);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    // weights (MODE 1) or dS (MODE 0) of four queries of block qb, in place: accumulator rows are queries
-    // 8 (r/4) + 4 h + r%4 of the block, the column is this lane's key.  Only the query tiles at the causal diagonal
-    // of the key tile pay for the position compares (with_mask; a wavefront-uniform choice).
-    auto quad = [&](auto with_mask, int qb, f32x16& s, const f32x16& dp, int q4) {
-      const int qo = qb * 32 + 8 * q4 + 4 * h;
-      const f32x4 l4 = *reinterpret_cast<const f32x4*>(st + kSmallOff + qo * 4);
-      f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
-      if (MODE == 0) d4 = *reinterpret_cast<const f32x4*>(st + kSmallOff + 256 + qo * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = q4 * 4 + e;
-        float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
-        if (decltype(with_mask)::value && qb * 32 + 8 * q4 + e < rel) pv = 0.f;
-        s[r] = MODE == 0 ? pv * (dp[r] - d4[e]) : pv;
-      }
-    };
-    // phase C of block qb: its P (or dS), as two B operands of 16 queries each, into the update
-    auto phase_c = [&](int qb, const f32x16& s, auto under) {
-      bf16x8 bfrag[2];
-      bfrag[0] = pack8(s, 0);
-      bfrag[1] = pack8(s, 8);
-      bf16x8 fc[kAhead];
-#pragma unroll
-      for (int c = 0; c < kAhead; ++c) fc[c] = cfrag(qb * (NC / 2) + c);
-#pragma unroll
-      for (int c = 0; c < NC / 2; ++c) {
-        const int cc = qb * (NC / 2) + c, db = cc % NB;
-        __builtin_amdgcn_sched_barrier(0);
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[c % kAhead], bfrag[c / NB], acc[db], 0, 0, 0);
-        if (c + kAhead < NC / 2) fc[c % kAhead] = cfrag(cc + kAhead);
-        under(c);
-        if (cc % (NC / LPH) == 0 && pre >= 0) issue_part(pre, (NOPS - 1) * LPH + cc / (NC / LPH));   // k-packed operand parts
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto nothing = [](int) {};
+    const int rel = first_h - q_begin * kKeyQ - u * kRows;           // query positions below rel do not see this key
     auto run = [&](auto with_mask) {
-      if constexpr (MODE == 1) {
-        // dV': the weights of a block run on the vector ALU under the matrix-core work of the other block -- S of
-        // block 1 over the weights of block 0, the update of block 0 over the weights of block 1 (a quad of queries
-        // behind every second MFMA).  Two S accumulators are live at once; this kernel has the registers for it.
-        static_assert(MODE != 1 || (NA == 2 * 4 || NA == 4) && NC / 2 >= 4, "a quad per MFMA or per two");
-        constexpr int kPerA = NA / 4, kPerC = (NC / 2) / 4;
-        f32x16 s0, s1, none;
-        phase_a(0, s0, none, nothing);
-        if (pre >= 0) issue_small(pre);
-        phase_a(1, s1, none, [&](int c) { if (c % kPerA == 0) quad(with_mask, 0, s0, none, c / kPerA); });
-        phase_c(0, s0, [&](int c) { if (c % kPerC == 0 && c / kPerC < 4) quad(with_mask, 1, s1, none, c / kPerC); });
-        phase_c(1, s1, nothing);
-      } else {
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          f32x16 s, dp;
-          phase_a(qb, s, dp, nothing);
-          if (qb == 0 && pre >= 0) issue_small(pre);
+      for (int qb = 0; qb < kRows / 32; ++qb) {
+        // S^T and dP^T of the block's 32 queries: chunk c = operand (0: Q, 1: dO), k step
+        auto afrag = [&](int c) {
+          return *reinterpret_cast<const bf16x8*>(st + (c / KS) * kOpBytes + qb * (32 * CH * 16) + krow_b + (((c % KS) << 5) ^ khx));
+        };
+        // dO, then Q, k-packed: chunk c = operand, 16-query step, 32-column block
+        auto cfrag = [&](int c) {
+          return *reinterpret_cast<const bf16x8*>(st + (2 + c / NC) * kOpBytes + plane_b +
+                                                  ((qb * 2 + c % NC / NB) * 2 * D + c % NB * 32) * 16);
+        };
+        const unsigned char* small_b = st + kSmallOff + qb * 256 + 16 * h;
+        f32x16 s, dp;
+        bf16x8 fa[kAhead];
+        bf16x8 pf[2], df[2];
+        // weights of four queries: accumulator rows are queries 8 (r/4) + 4 h + r%4 of the block, the column is this
+        // lane's key.  Only the query tiles at the causal diagonal of the key tile pay for the position compares.
+        auto weights = [&](int q4) {
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(small_b + 32 * q4);
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            quad(with_mask, qb, s, dp, q4);
-            __builtin_amdgcn_sched_barrier(0);    // one quad of lse / delta values in registers at a time
+          for (int e = 0; e < 4; ++e) {
+            const int r = q4 * 4 + e;
+            float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
+            if (decltype(with_mask)::value && qb * 32 + 8 * q4 + e < rel) pv = 0.f;
+            s[r] = pv;
           }
-          phase_c(qb, s, nothing);                // the two blocks stay apart: their accumulators would double up
+        };
+        auto ds = [&](int q4) {
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(small_b + 128 + 32 * q4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dp[q4 * 4 + e] = s[q4 * 4 + e] * (dp[q4 * 4 + e] - d4[e]);
+        };
+#pragma unroll
+        for (int c = 0; c < kAhead; ++c) fa[c] = afrag(c);
+#pragma unroll
+        for (int c = 0; c < 2 * KS; ++c) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (c < KS) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], kf[c % KS], c == 0 ? zero16 : s, 0, 0, 0);
+          else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], vf[c % KS], c == KS ? zero16 : dp, 0, 0, 0);
+          if (c + kAhead < 2 * KS) fa[c % kAhead] = afrag(c + kAhead);
+          else fa[c % kAhead] = cfrag(c + kAhead - 2 * KS);
+          if (c >= KS && (c - KS) % (KS / 4) == 0) weights((c - KS) / (KS / 4));      // under the products of dP
+          if (qb == 0 && c < 4 && pre >= 0) issue_part(pre, c);
+          if (qb == 0 && c == 4 % (2 * KS) && pre >= 0) issue_small(pre);
         }
+        pf[0] = pack8(s, 0);
+        pf[1] = pack8(s, 8);
+#pragma unroll
+        for (int c = 0; c < 2 * NC; ++c) {
+          const int db = c % NB;
+          __builtin_amdgcn_sched_barrier(0);
+          if (c == NC) {
+            df[0] = pack8(dp, 0);
+            df[1] = pack8(dp, 8);
+          }
+          if (c < NC) dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], pf[c % NC / NB], dv[db], 0, 0, 0);
+          else dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], df[c % NC / NB], dk[db], 0, 0, 0);
+          if (c + kAhead < 2 * NC) fa[c % kAhead] = cfrag(c + kAhead);
+          if (c < NC && c % (NC / 4) == 0) ds(c / (NC / 4));                          // under the products of dV
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
     if (masked) run(std::true_type{});
@@ -1161,7 +1127,7 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
 
   // Ring of kStages buffers, one barrier per tile: at the top of step u the tiles up to u + kStages - 2 have
   // been issued; after its barrier everyone is done with tile u-1, whose buffer takes tile u + kStages - 1.
-  const int n = min(per_split, n_qtiles - q_begin);
+  const int n = min(per_split, n_qtiles - q_begin) * (kKeyQ / kRows);
   if (n > 0) {
     wait_vmcnt<0>();
 #pragma unroll
@@ -1179,21 +1145,22 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
         else wait_vmcnt<0>();
       }
       __syncthreads();
-      const int pos0 = (q_begin + u) * kKeyQ;
+      const int pos0 = q_begin * kKeyQ + u * kRows;
       compute_tile(u, u + kAheadTiles < n ? u + kAheadTiles : -1, pos0 < q_full_pos);
     }
   }
 
-  // ---- write dK' (scaled) or dV' for this lane's key slot; accumulator rows are d
-  float* orow = (MODE == 0 ? p.dKp : p.dVp) + sp * p.plane + ((long long)bh * p.npad + slot) * D;
-  const float osc = MODE == 0 ? L.scale : 1.0f;
+  // ---- write dK' (scaled) and dV' for this lane's key slot; accumulator rows are d
+  const long long out = sp * p.plane + ((long long)bh * p.npad + slot) * D;
 #pragma unroll
   for (int db = 0; db < NB; ++db)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const int d = db * 32 + 8 * q4 + 4 * h;
-      f32x4 a = {acc[db][q4 * 4] * osc, acc[db][q4 * 4 + 1] * osc, acc[db][q4 * 4 + 2] * osc, acc[db][q4 * 4 + 3] * osc};
-      *reinterpret_cast<f32x4*>(orow + d) = a;
+      const f32x4 x = {dk[db][q4 * 4], dk[db][q4 * 4 + 1], dk[db][q4 * 4 + 2], dk[db][q4 * 4 + 3]};
+      const f32x4 y = {dv[db][q4 * 4], dv[db][q4 * 4 + 1], dv[db][q4 * 4 + 2], dv[db][q4 * 4 + 3]};
+      *reinterpret_cast<f32x4*>(p.dKp + out + d) = x * L.scale;
+      *reinterpret_cast<f32x4*>(p.dVp + out + d) = y;
     }
   }   // items
 }
@@ -1217,9 +1184,9 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, 
     const int pos = inv[(long long)bh * L.N + n];               // slot of token n in the head's list, or -1
     if (pos >= 0) {
       int n_sp = 1;
-      if (p.nsplit > 1) {                  // as the key kernels counted: the query tiles from the tile's first visible pair on
+      if (p.nsplit > 1) {                  // as the key kernel counted: the query tiles from the tile's first visible pair on
         const int first = p.kfirst[(long long)bh * p.npad + pos / kKeyTile * kKeyTile];
-        n_sp = key_tile_splits(cdiv(p.q_cnt[bh], kKeyQ) - first / kKeyQ, p.nsplit, p.klist ? p.klist[3] : p.split_len);
+        n_sp = key_tile_splits(cdiv(p.q_cnt[bh], kKeyQ) - first / kKeyQ, p.nsplit, p.klist ? p.klist[2] : p.split_len);
       }
       const long long o = ((long long)bh * p.npad + pos) * D + c * 4;
       for (int sp = 0; sp < n_sp; ++sp) {
@@ -1261,7 +1228,7 @@ struct BlockLists {
 
 constexpr int kKeyHeadGroup = 7;
 int g_key_split_len = kKeySplitLen;          // omni_debug_key_split_len: tests split short key tiles too
-// slots of the key kernels' dispatch order
+// slots of the key kernel's dispatch order
 size_t key_list_slots(const Layer& L, int npad) {
   return (size_t)cdiv(L.B * L.Hq, kKeyHeadGroup) * kKeyHeadGroup * (npad / kKeyTile);
 }
@@ -1428,9 +1395,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
       p.key_wgs = (int)key_wgs;
       hipLaunchKernelGGL(key_list_kernel, dim3(1), dim3(1024), 0, st, p, (long long)key_list_slots(L, npad));
       OMNI_LAUNCH_CHECK();
-      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 1, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
-      OMNI_LAUNCH_CHECK();
-      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, 0, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
+      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
     } else {
       if (split)
         hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),

@@ -204,6 +204,18 @@ __device__ __forceinline__ void gload_lds4(const void* gptr, unsigned lds_addr) 
       : "v"(gptr), "s"(lds_addr)
       : "memory");
 }
+__device__ __forceinline__ void gload_lds4(const void* sbase, unsigned lane_off, unsigned lds_addr) {
+  unsigned saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %1, %2\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(lane_off), "s"(sbase), "s"(lds_addr)
+      : "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
