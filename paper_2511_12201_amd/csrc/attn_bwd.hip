@@ -8,10 +8,10 @@
 // Deterministic, no floating-point atomics.  bf16 (the measured path), three kernels in the forward's style
 // (8 wavefronts, LDS-DMA ring, position masks from the visible-prefix counts):
 //  * attn_bwd_dq_bf16_kernel: a work item is 256 kept queries of a head (32 per wavefront) from the forward's
-//    longest-first list; it streams 64-key tiles of K, V (natural) and K^T (k-packed): S^T = K Q^T,
+//    longest-first list; it streams 64-key tiles of K, V (fragment order) and K^T (k-packed): S^T = K Q^T,
 //    dP^T = V dO^T, dQ^T += K^T dS^T.  Short sequences: attn_bwd_dq_split_kernel, 32 queries an item, no list.
 //  * attn_bwd_key_bf16_kernel: a workgroup owns 256 packed keys of a query head (32 per wavefront, K and V fragments
-//    resident) and streams 32-query tiles (d = 64: 64) of the packed kept rows (Q, dO natural and k-packed, lse and
+//    resident) and streams 32-query tiles (d = 64: 64) of the packed kept rows (Q, dO in fragment order and k-packed, lse and
 //    delta by 4-byte LDS-DMA): S = Q K^T, dP = dO V^T, dV' += P^T dO, dK' += dS^T Q.  Items (head, key tile, split)
 //    come from a list a small kernel compacts; a key tile seen by many query tiles is shared by up to four workgroups,
 //    each with a partial plane of its own.
@@ -42,12 +42,12 @@ struct BwdParams {
   const int* q_cnt;
   const int* budget;
   int b_cap, npad, nqpad;
-  const void* Kn;       // packed natural K, V
+  const void* Kn;       // packed K, V in fragment order (fp32 on long sequences: row by row)
   const void* Vn;
   const void* Kt;       // k-packed K
   const void* Qt;       // k-packed kept Q, dO (these and the next two, and Kt: not for fp32 on long sequences)
   const void* dOt;
-  const void* Qn;       // kept Q, dO rows in kept order, contiguous (fp32: in fragment order, as Kn and Vn)
+  const void* Qn;       // kept Q, dO rows in kept order, in fragment order
   const void* dOn;
   const float* lse2c;   // per kept position: lse * log2e (+inf: contributes nothing)
   const float* deltac;
@@ -70,7 +70,6 @@ struct BwdParams {
   const int* tile_map;
   int tile_stride;
   int npad_kv;          // rows per (head) buffer of Kn / Vn / Kt: npad for the gathered copies
-  int k_frag;           // bf16: Kn, Vn in fragment order instead of row by row
 };
 
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int r0) {
@@ -506,7 +505,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dq_f32_long_kernel(BwdPa
 //
 // Same organisation as the bf16 forward kernel: 512 threads = 8 wavefronts x 32 kept queries (256-row work
 // items from the longest-first persistent list), K / V / K^T tiles of 64 keys streamed memory -> LDS with
-// LDS-DMA loads into a ring of kDqStages buffers (natural tiles unpadded with the XOR chunk swizzle), one
+// LDS-DMA loads into a ring of kDqStages buffers in fragment order, one
 // barrier per tile, the loads of tile t+2 spread over the MFMAs of tile t, causal mask from the per-query
 // visible-prefix count.  Per tile and wavefront: S^T = K Q^T and dP^T = V dO^T (32 MFMAs), dS^T on the
 // vector ALU, dQ^T += K^T dS^T (16 MFMAs).
@@ -521,9 +520,8 @@ constexpr int kBwdMaxMapTiles = 2048;               // key tiles of one head in 
 template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdParams p) {
   typedef u16 T;
-  constexpr int CH = D / 8;                          // 16-byte chunks per natural row
   constexpr int kOpBytes = kTileN * D * 2;           // one operand tile
-  constexpr int kStageBytes = 3 * kOpBytes;          // K natural, V natural, K k-packed
+  constexpr int kStageBytes = 3 * kOpBytes;          // K, V, K k-packed
   constexpr int LPH = kOpBytes / 1024 / kDqWaves;    // load instructions per operand per wavefront per tile
   constexpr int LPT = 3 * LPH;
   constexpr int NB = D / 32;
@@ -540,17 +538,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
   const float c2 = L.scale * kLog2e;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  unsigned ngoff[LPH], pgoff[LPH];                   // byte offsets of this lane's 16-byte chunk: natural (swizzled), packed
-#pragma unroll
-  for (int j = 0; j < LPH; ++j) {
-    const int pchunk = (j * kDqWaves + wave) * 64 + lane;
-    const int row = pchunk / CH, pc = pchunk % CH;
-    ngoff[j] = (row * D + ((pc ^ (row % CH)) << 3)) * 2;
-    pgoff[j] = pchunk << 4;
-  }
-  const int krow_b = ln * (CH * 16);
-  const int khx = (h << 4) ^ ((ln % CH) << 4);
-  const int plane_b = (h * D + ln) * 16;
+  const int lane_b = lane * 16;                      // copies and fragment reads: 16 bytes a lane, in lane order
 
   for (;;) {
   __syncthreads();
@@ -614,13 +602,11 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
   const T* kt = static_cast<const T*>(p.Kt) + (long long)bhx * p.npad_kv * D;
   auto issue_part = [&](int t, int part) {
     const int op = part / LPH, j = part % LPH;
-    const unsigned dst = lds_base + (unsigned)(t % kDqStages) * kStageBytes + op * kOpBytes + (j * kDqWaves + wave) * 1024;
+    const int at = j * kDqWaves + wave;
+    const unsigned dst = lds_base + (unsigned)(t % kDqStages) * kStageBytes + op * kOpBytes + at * 1024;
     // where tile t of the key list lives (wave-uniform: the tile base stays in scalar registers)
     const int src = TILEMAP ? __builtin_amdgcn_readfirstlane(sTileMap[t]) : t;
-    const long long tile_off = (long long)src * kTileN * D;
-    if (op == 0) gload_lds16(kn + tile_off, ngoff[j], dst);
-    else if (op == 1) gload_lds16(vn + tile_off, ngoff[j], dst);
-    else gload_lds16(kt + tile_off, pgoff[j], dst);
+    gload_lds16((op == 0 ? kn : op == 1 ? vn : kt) + (long long)src * kTileN * D + at * 512, lane_b, dst);
   };
   auto issue_tile = [&](int t) {
 #pragma unroll
@@ -638,11 +624,10 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
     // chunk c of phase A: key block kb, k-step ks, operand (0: K for S, 1: V for dP)
     auto afrag = [&](int c) {
       const int which = c % 2, ks = (c / 2) % (D / 16), kb = c / (D / 8);
-      return *reinterpret_cast<const bf16x8*>(st + which * kOpBytes + kb * (32 * CH * 16) + krow_b + ((ks << 5) ^ khx));
+      return *reinterpret_cast<const bf16x8*>(st + lane_b + which * kOpBytes + (kb * (D / 16) + ks) * 1024);
     };
     auto cfrag = [&](int c) {
-      const int t16 = c / NB, db = c % NB;
-      return *reinterpret_cast<const bf16x8*>(st + 2 * kOpBytes + plane_b + (t16 * 2 * D + db * 32) * 16);
+      return *reinterpret_cast<const bf16x8*>(st + lane_b + 2 * kOpBytes + c * 1024);
     };
     f32x16 s[2], dp[2];
     bf16x8 fa[kAhead];
@@ -762,14 +747,13 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
   const float lse = p.lse2c[qo + ln], delta = p.deltac[qo + ln];
 #pragma unroll
   for (int c = threadIdx.x; c < 32 * CH; c += kSplitThreads) {
-    const int row = c / CH, chunk = c % CH, at = (row * CH + (chunk ^ (row % CH))) * 16;
-    *reinterpret_cast<u32x4*>(sQ + at) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.Qn) + (qo + row) * D + chunk * 8);
-    *reinterpret_cast<u32x4*>(sG + at) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.dOn) + (qo + row) * D + chunk * 8);
+    *reinterpret_cast<u32x4*>(sQ + c * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.Qn) + qo * D + c * 8);
+    *reinterpret_cast<u32x4*>(sG + c * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.dOn) + qo * D + c * 8);
   }
   const int bhx = TILEMAP ? b * L.Hkv + i / L.G : bh;
   const long long head = (long long)bhx * p.npad_kv * D;
   const T *kn = static_cast<const T*>(p.Kn) + head + lane * 8, *vn = static_cast<const T*>(p.Vn) + head + lane * 8;
-  const T* kt = static_cast<const T*>(p.Kt) + head + (h * D + ln) * 8;
+  const T* kt = static_cast<const T*>(p.Kt) + head + lane * 8;
   auto block_off = [&](int t) {
     if (!TILEMAP) return (long long)t * 32 * D;
     return (long long)(__builtin_amdgcn_readfirstlane(p.tile_map[(long long)bh * p.tile_stride + t / 2]) * 2 + t % 2) * 32 * D;
@@ -796,13 +780,13 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int db = 0; db < NB; ++db) ktf[u][db] = *reinterpret_cast<const bf16x8*>(ktb + (u * 2 * D + db * 32) * 8);
+      for (int db = 0; db < NB; ++db) ktf[u][db] = *reinterpret_cast<const bf16x8*>(ktb + (u * NB + db) * 512);
     f32x16 s, dp;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f, dp[r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int at = (ln * CH + ((2 * ks + h) ^ (ln % CH))) * 16;
+      const int at = (ks * 64 + lane) * 16;
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], *reinterpret_cast<const bf16x8*>(sQ + at), s, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], *reinterpret_cast<const bf16x8*>(sG + at), dp, 0, 0, 0);
     }
@@ -851,17 +835,19 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
 //
 // The dQ kernel with the roles of keys and queries swapped: a workgroup of 8 wavefronts owns 256 packed keys of one
 // query head (32 per wavefront, K and V fragments resident in registers) and streams tiles of the packed kept rows
-// memory -> LDS with LDS-DMA loads into a ring of four: Q and dO row by row (operands of S and dP) and k-packed (of the
+// memory -> LDS with LDS-DMA loads into a ring of four: Q and dO in fragment order (operands of S and dP) and k-packed (of the
 // updates), 8 KB each, so that a wavefront issues one load per operand and tile, three tiles ahead.  Per 32 queries and
 // wavefront: S (D/16 matrix instructions), dP with the weights P of S on the vector ALU under it, dV' += P^T dO with dS
-// under it, dK' += dS^T Q.  At d = 128 the fragments (64 registers), the two accumulators (128), S and dP (32) and what
-// the loop needs around them are exactly the 256 registers of two wavefronts per SIMD: nothing of the tile loop is
-// spilled, and the other wavefront works on the matrix cores while this one packs its weights.  Tiles of 32 queries,
-// because a stage of 64 would leave the ring two stages.
+// under it, dK' += dS^T Q.  At d = 128 the fragments (64 registers), the two accumulators (128), S and dP (32), P
+// packed and the operands in flight leave a handful of the 256 registers of two wavefronts per SIMD for everything else, so
+// all operands lie in lane order (one address for a tile's fragments), what depends on the lane is formed anew per tile
+// (loop_lane), and tiles at the causal diagonal have a loop of their own instead of a branch.  A single register that the
+// tile loop reloads from scratch costs a tenth of the kernel, because its wait drains the loads in flight: 3084 -> 2750 us at
+// 32k, 28 heads.  Tiles of 32 queries, because a stage of 64 would leave the ring two stages.
 // Bound: matrix cores, waiting in part for their wavefronts.  dK' and dV' as two kernels, each with an S of its own (5
-// products where 4 are needed, Q read twice), took 2226 + 1384 us at 32k, 28 heads, d = 128; forward and backward there
-// 7537 -> 6968 us, two clips of 3101 at d = 64 215 -> 187 us, blocks at 16k 3380 -> 3124 us, with the same results to the
-// last bit.
+// products where 4 are needed, Q read twice), took 2226 + 1384 us at 32k, 28 heads, d = 128, this one 2660 to 2750: forward
+// and backward there 7500 -> 6541 us, two clips of 3101 at d = 64 214 -> 178 us, blocks at 16k 3540 -> 3044 us (the packs,
+// faster too, are a fifth of that), with the same results to the last bit.
 // lse * log2e and delta of the tile's queries come with the tile (LDS-DMA of 4 bytes per lane); the causal
 // mask is a comparison of the query position with the first position that sees the lane's key.
 
@@ -990,16 +976,14 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
     const int src = t < p.tile_stride ? p.tile_map[(long long)bh * p.tile_stride + t] : 0;
     kv_row = (long long)(b * L.Hkv + (bh % L.Hq) / L.G) * p.npad_kv + (long long)src * kTileN + slot % kTileN;
   }
-  // natural rows, or (short sequences) the 32-row blocks of the fragment order
-  const long long kv_at = p.k_frag ? (kv_row & ~31ll) * D + lane * 8 : kv_row * D + h * 8;
-  const int kv_step = p.k_frag ? 512 : 16;
+  const long long kv_at = (kv_row & ~31ll) * D + lane * 8;
   const T* krow = static_cast<const T*>(p.Kn) + kv_at;
   const T* vrow = static_cast<const T*>(p.Vn) + kv_at;
   bf16x8 kf[KS], vf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    kf[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * kv_step);
-    vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * kv_step);
+    kf[ks] = *reinterpret_cast<const bf16x8*>(krow + ks * 512);
+    vf[ks] = *reinterpret_cast<const bf16x8*>(vrow + ks * 512);
   }
   // finish every ordinary load here: a compiler-placed wait inside the tile loop would drain the ring
 #pragma unroll
@@ -1016,33 +1000,27 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[db][r] = 0.f, dv[db][r] = 0.f;
 
-  // byte offsets of this lane's 16-byte chunk of a tile: natural rows (swizzled), k-packed
-  const unsigned chunk0 = wave * 64 + lane;
-  const unsigned ngoff = (chunk0 / CH * D + ((chunk0 % CH ^ chunk0 / CH % CH) << 3)) * 2, pgoff = chunk0 << 4;
-  const int krow_b = ln * (CH * 16);
-  const int khx = (h << 4) ^ ((ln % CH) << 4);
-  const int plane_b = (h * D + ln) * 16;
 
   const long long q_row = (long long)bh * p.nqpad + (long long)q_begin * kKeyQ;    // first row of this workgroup's tiles
   const T* qn = static_cast<const T*>(p.Qn) + q_row * D;
   const T* gn = static_cast<const T*>(p.dOn) + q_row * D;
   const T* qt = static_cast<const T*>(p.Qt) + q_row * D;
   const T* gt = static_cast<const T*>(p.dOt) + q_row * D;
-  const bool has_small = wave < NSMALL;
-  const float* small = p.lse2c + q_row + (has_small ? wave * 32 : 0);
-  const unsigned small_off = (unsigned)(h ? (p.deltac - p.lse2c) * 4 : 0) + ln * 4;      // delta lies behind lse (carve_bwd)
+  const float* small = p.lse2c + q_row + wave % NSMALL * 32;       // every wavefront brings one: the same count of loads for all
+  const unsigned delta_off = (unsigned)((p.deltac - p.lse2c) * 4);     // delta lies behind lse (carve_bwd)
 
-  // u = tile index relative to the workgroup's first (ring position)
+  const int n = min(per_split, n_qtiles - q_begin) * (kKeyQ / kRows);
+  // u = tile index relative to the workgroup's first (ring position); past the end the last tile comes again, into a stage
+  // that nobody reads any more, so that the loads in flight are the same number in every step
   auto issue_part = [&](int u, int op) {
     const unsigned dst = lds_base + (unsigned)(u % kStages) * kStageBytes + op * kOpBytes + wave * 1024;
-    const long long tile_off = (long long)u * kRows * D;
-    if (op == 0) gload_lds16(qn + tile_off, ngoff, dst);
-    else if (op == 1) gload_lds16(gn + tile_off, ngoff, dst);
-    else if (op == 2) gload_lds16(gt + tile_off, pgoff, dst);
-    else gload_lds16(qt + tile_off, pgoff, dst);
+    const long long tile_off = (long long)min(u, n - 1) * kRows * D;
+    gload_lds16((op == 0 ? qn : op == 1 ? gn : op == 2 ? gt : qt) + tile_off + wave * 512, (unsigned)loop_lane() * 16, dst);
   };
   auto issue_small = [&](int u) {
-    if (has_small) gload_lds4(small + u * kRows, small_off, lds_base + (unsigned)(u % kStages) * kStageBytes + kSmallOff + wave * 256);
+    const unsigned l = (unsigned)loop_lane();
+    gload_lds4(small + min(u, n - 1) * kRows, (l < 32 ? l : l - 32) * 4 + (l < 32 ? 0u : delta_off),
+               lds_base + (unsigned)(u % kStages) * kStageBytes + kSmallOff + wave % NSMALL * 256);
   };
   auto issue_tile = [&](int u) {
 #pragma unroll
@@ -1054,100 +1032,96 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   constexpr int kAhead = 2;                    // fragment reads run this many of them ahead
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  auto compute_tile = [&](int u, int pre, bool masked) {
-    const unsigned char* st = smem + (u % kStages) * kStageBytes;
+  auto compute_tile = [&](int u, auto with_mask) {
+    const int l = loop_lane();
+    const unsigned char* stage = smem + (u % kStages) * kStageBytes;
+    const unsigned char* st = stage + l * 16;                        // fragments: 16 bytes a lane, in lane order
     const int rel = first_h - q_begin * kKeyQ - u * kRows;           // query positions below rel do not see this key
-    auto run = [&](auto with_mask) {
 #pragma unroll
-      for (int qb = 0; qb < kRows / 32; ++qb) {
-        // S^T and dP^T of the block's 32 queries: chunk c = operand (0: Q, 1: dO), k step
-        auto afrag = [&](int c) {
-          return *reinterpret_cast<const bf16x8*>(st + (c / KS) * kOpBytes + qb * (32 * CH * 16) + krow_b + (((c % KS) << 5) ^ khx));
-        };
-        // dO, then Q, k-packed: chunk c = operand, 16-query step, 32-column block
-        auto cfrag = [&](int c) {
-          return *reinterpret_cast<const bf16x8*>(st + (2 + c / NC) * kOpBytes + plane_b +
-                                                  ((qb * 2 + c % NC / NB) * 2 * D + c % NB * 32) * 16);
-        };
-        const unsigned char* small_b = st + kSmallOff + qb * 256 + 16 * h;
-        f32x16 s, dp;
-        bf16x8 fa[kAhead];
-        bf16x8 pf[2], df[2];
-        // weights of four queries: accumulator rows are queries 8 (r/4) + 4 h + r%4 of the block, the column is this
-        // lane's key.  Only the query tiles at the causal diagonal of the key tile pay for the position compares.
-        auto weights = [&](int q4) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(small_b + 32 * q4);
+    for (int qb = 0; qb < kRows / 32; ++qb) {
+      // S^T and dP^T of the block's 32 queries: chunk c = operand (0: Q, 1: dO), k step
+      auto afrag = [&](int c) {
+        return *reinterpret_cast<const bf16x8*>(st + (c / KS) * kOpBytes + (qb * KS + c % KS) * 1024);
+      };
+      // dO, then Q, k-packed: chunk c = operand, 16-query step, 32-column block
+      auto cfrag = [&](int c) {
+        return *reinterpret_cast<const bf16x8*>(st + (2 + c / NC) * kOpBytes + (qb * NC + c % NC) * 1024);
+      };
+      const unsigned char* small_b = stage + (l >> 5) * 16 + kSmallOff + qb * 256;
+      f32x16 s, dp;
+      bf16x8 fa[kAhead];
+      bf16x8 pf[2], df[2];
+      // weights of four queries: accumulator rows are queries 8 (r/4) + 4 h + r%4 of the block, the column is this
+      // lane's key.  Only the query tiles at the causal diagonal of the key tile pay for the position compares.
+      // lse of the next four, then delta, is read while these are formed.
+      f32x4 next = *reinterpret_cast<const f32x4*>(small_b);
+      auto weights = [&](int q4) {
+        const f32x4 l4 = next;
+        next = *reinterpret_cast<const f32x4*>(small_b + (q4 < 3 ? 32 * (q4 + 1) : 128));
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int r = q4 * 4 + e;
-            float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
-            if (decltype(with_mask)::value && qb * 32 + 8 * q4 + e < rel) pv = 0.f;
-            s[r] = pv;
-          }
-        };
-        auto ds = [&](int q4) {
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(small_b + 128 + 32 * q4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dp[q4 * 4 + e] = s[q4 * 4 + e] * (dp[q4 * 4 + e] - d4[e]);
-        };
-#pragma unroll
-        for (int c = 0; c < kAhead; ++c) fa[c] = afrag(c);
-#pragma unroll
-        for (int c = 0; c < 2 * KS; ++c) {
-          __builtin_amdgcn_sched_barrier(0);
-          if (c < KS) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], kf[c % KS], c == 0 ? zero16 : s, 0, 0, 0);
-          else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], vf[c % KS], c == KS ? zero16 : dp, 0, 0, 0);
-          if (c + kAhead < 2 * KS) fa[c % kAhead] = afrag(c + kAhead);
-          else fa[c % kAhead] = cfrag(c + kAhead - 2 * KS);
-          if (c >= KS && (c - KS) % (KS / 4) == 0) weights((c - KS) / (KS / 4));      // under the products of dP
-          if (qb == 0 && c < 4 && pre >= 0) issue_part(pre, c);
-          if (qb == 0 && c == 4 % (2 * KS) && pre >= 0) issue_small(pre);
+        for (int e = 0; e < 4; ++e) {
+          const int r = q4 * 4 + e;
+          float pv = fast_exp2(fmaf(s[r], c2, -l4[e]));
+          if (decltype(with_mask)::value && qb * 32 + 8 * q4 + e < rel) pv = 0.f;
+          s[r] = pv;
         }
-        pf[0] = pack8(s, 0);
-        pf[1] = pack8(s, 8);
+      };
+      auto ds = [&](int q4) {
+        const f32x4 d4 = next;
+        if (q4 < 3) next = *reinterpret_cast<const f32x4*>(small_b + 128 + 32 * (q4 + 1));
 #pragma unroll
-        for (int c = 0; c < 2 * NC; ++c) {
-          const int db = c % NB;
-          __builtin_amdgcn_sched_barrier(0);
-          if (c == NC) {
-            df[0] = pack8(dp, 0);
-            df[1] = pack8(dp, 8);
-          }
-          if (c < NC) dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], pf[c % NC / NB], dv[db], 0, 0, 0);
-          else dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], df[c % NC / NB], dk[db], 0, 0, 0);
-          if (c + kAhead < 2 * NC) fa[c % kAhead] = cfrag(c + kAhead);
-          if (c < NC && c % (NC / 4) == 0) ds(c / (NC / 4));                          // under the products of dV
-        }
+        for (int e = 0; e < 4; ++e) dp[q4 * 4 + e] = s[q4 * 4 + e] * (dp[q4 * 4 + e] - d4[e]);
+      };
+      constexpr int kPerW = KS / 4, kPerD = NC / 4;      // matrix instructions per quad of weights, of dS
+#pragma unroll
+      for (int c = 0; c < kAhead; ++c) fa[c] = afrag(c);
+#pragma unroll
+      for (int c = 0; c < 2 * KS; ++c) {
         __builtin_amdgcn_sched_barrier(0);
+        if (c < KS) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], kf[c % KS], c == 0 ? zero16 : s, 0, 0, 0);
+        else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], vf[c % KS], c == KS ? zero16 : dp, 0, 0, 0);
+        if (c + kAhead < 2 * KS) fa[c % kAhead] = afrag(c + kAhead);
+        else fa[c % kAhead] = cfrag(c + kAhead - 2 * KS);
+        if (c >= KS && (c - KS) % kPerW == kPerW - 1) weights((c - KS) / kPerW);      // under the products of dP
+        if (qb == 0 && c < 4) issue_part(u + kAheadTiles, c);
       }
-    };
-    if (masked) run(std::true_type{});
-    else run(std::false_type{});
+      pf[0] = pack8(s, 0);
+      pf[1] = pack8(s, 8);
+#pragma unroll
+      for (int c = 0; c < 2 * NC; ++c) {
+        const int db = c % NB;
+        __builtin_amdgcn_sched_barrier(0);
+        if (c == NC) {
+          df[0] = pack8(dp, 0);
+          df[1] = pack8(dp, 8);
+        }
+        if (c < NC) dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], pf[c % NC / NB], dv[db], 0, 0, 0);
+        else dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c % kAhead], df[c % NC / NB], dk[db], 0, 0, 0);
+        if (c + kAhead < 2 * NC) fa[c % kAhead] = cfrag(c + kAhead);
+        if (c < NC && c % kPerD == kPerD - 1) ds(c / kPerD);                          // under the products of dV
+        if (qb == 0 && c == 0) issue_small(u + kAheadTiles);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
   // Ring of kStages buffers, one barrier per tile: at the top of step u the tiles up to u + kStages - 2 have
   // been issued; after its barrier everyone is done with tile u-1, whose buffer takes tile u + kStages - 1.
-  const int n = min(per_split, n_qtiles - q_begin) * (kKeyQ / kRows);
   if (n > 0) {
     wait_vmcnt<0>();
 #pragma unroll
-    for (int a = 0; a < kAheadTiles; ++a)
-      if (a < n) issue_tile(a);
-    for (int u = 0; u < n; ++u) {
-      const int ahead = min(n - 1 - u, kAheadTiles - 1);      // tiles issued after tile u
-      if (has_small) {
-        if (ahead >= 2) wait_vmcnt<2 * (LPT + 1)>();
-        else if (ahead == 1) wait_vmcnt<LPT + 1>();
-        else wait_vmcnt<0>();
-      } else {
-        if (ahead >= 2) wait_vmcnt<2 * LPT>();
-        else if (ahead == 1) wait_vmcnt<LPT>();
-        else wait_vmcnt<0>();
+    for (int a = 0; a < kAheadTiles; ++a) issue_tile(a);
+    const int n_masked = __builtin_amdgcn_readfirstlane(cdiv(min(n * kRows, max(0, q_full_pos - q_begin * kKeyQ)), kRows));
+    auto tiles = [&](int from, int to, auto with_mask) {
+      for (int u = from; u < to; ++u) {
+        wait_vmcnt<(kAheadTiles - 1) * (LPT + 1)>();
+        __syncthreads();
+        compute_tile(u, with_mask);
       }
-      __syncthreads();
-      const int pos0 = q_begin * kKeyQ + u * kRows;
-      compute_tile(u, u + kAheadTiles < n ? u + kAheadTiles : -1, pos0 < q_full_pos);
-    }
+    };
+    tiles(0, n_masked, std::true_type{});
+    tiles(n_masked, n, std::false_type{});
+    wait_vmcnt<0>();                           // nothing may land in LDS any more
   }
 
   // ---- write dK' (scaled) and dV' for this lane's key slot; accumulator rows are d
@@ -1300,9 +1274,8 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   const bool copies = kFast || split;                  // fp32 on long sequences: only K and V, row by row
   int rc;
   if constexpr (BLOCKS) {
-    // K, V (natural) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
-    rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st,
-                     split);
+    // K, V (fragment order) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
+    rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st);
     if (rc != OMNI_OK) return rc;
     // token lists of the selected blocks (causal bounds, the reduction's slot map), rows npad apart, and the tile map
     rc = run_expand_blocks(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, w.kidx, w.vbudget, npad, st);
@@ -1346,7 +1319,6 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
   p.klist = nullptr;
-  p.k_frag = split;
   p.key_wgs = 1;
   p.sched = w.sched;
   p.qvis = w.qvis;

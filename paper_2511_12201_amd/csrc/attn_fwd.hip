@@ -4,8 +4,7 @@
 //
 // Design for gfx950:
 //  * A pack pass (pack.hip) gathers each head's selected K rows into a dense
-//    buffer (row-major, or in fragment order for the kernels that read it without
-//    LDS) and its V rows into the exact operand order the matrix cores need
+//    buffer in fragment order (the long fp32 kernel: rows as they are) and its V rows into the exact operand order the matrix cores need
 //    (below; rows as they are for the long fp32 kernel), zero-padding to whole
 //    64-key tiles and recording the original token index of every slot.  The dense baseline runs the same pack
 //    with identity indices per KV head.  The main loop is then free of gathers.
@@ -15,7 +14,7 @@
 //    holds the other half of the keys), and the S^T accumulator registers are
 //    already in the B-operand order of the second GEMM, so P never moves.
 //  * V is packed so that the A operand of O^T = V^T P^T is one 16-byte LDS read:
-//    [16-key group][half h][d][8 keys], key(group,h,j) = 16 group + 8 (j/4) + 4 h + j%4,
+//    [16-key group][d / 32][half h][d % 32][8 keys], key(group,h,j) = 16 group + 8 (j/4) + 4 h + j%4,
 //    which is the order in which the S^T accumulators hold the keys.
 //  * bf16 inputs, second product in f16: S^T = K Q^T runs on the bf16 matrix cores; the weights are rounded to
 //    f16 (11 significant bits against bf16's 8, same matrix-core rate) and multiplied with V converted to f16 by
@@ -95,7 +94,6 @@ constexpr int kMaxMapTiles = 2048;                   // key tiles of one head in
 template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParams p) {
   typedef u16 T;
-  constexpr int CH = D / 8;                          // 16-byte chunks per K row
   constexpr int kKBytes = kTileN * D * 2;
   constexpr int kStageBytes = 2 * kKBytes;           // K tile then V tile
   constexpr int LPH = kKBytes / 1024 / kFastWaves;   // load instructions per operand per wavefront per tile
@@ -113,19 +111,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParam
   const float c2 = L.scale * kLog2e;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  // per-lane pieces of the copy: which global chunk lands in this lane's LDS slot
-  unsigned kgoff[LPH], vgoff[LPH];                             // byte offsets inside a tile
-#pragma unroll
-  for (int j = 0; j < LPH; ++j) {
-    const int pchunk = (j * kFastWaves + wave) * 64 + lane;   // physical 16-byte slot in the K tile
-    const int row = pchunk / CH, pc = pchunk % CH;
-    kgoff[j] = (row * D + ((pc ^ (row % CH)) << 3)) * 2;
-    vgoff[j] = pchunk << 4;
-  }
-  // per-lane pieces of the fragment reads
-  const int krow_b = ln * (CH * 16);                           // byte offset of row ln in a 32-row block
-  const int khx = (h << 4) ^ ((ln % CH) << 4);                 // (chunk ^ swizzle) << 4 = (ks << 5) ^ khx
-  const int vlane_b = (h * D + ln) * 16;
+  const int lane_b = lane * 16;                                // copies and fragment reads: 16 bytes a lane, in lane order
 
   for (;;) {
   __syncthreads();
@@ -195,10 +181,11 @@ __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParam
     // where tile t of the key list lives (wave-uniform: the tile base stays in scalar registers)
     const int src = TILEMAP ? __builtin_amdgcn_readfirstlane(sTileMap[t]) : t;
     if (part < LPH) {
-      gload_lds16(kp + (long long)src * kTileN * D, kgoff[part], dst + (part * kFastWaves + wave) * 1024);
+      const int at = part * kFastWaves + wave;
+      gload_lds16(kp + (long long)src * kTileN * D + at * 512, lane_b, dst + at * 1024);
     } else {
-      const int j = part - LPH;
-      gload_lds16(vp + (long long)src * kTileN * D, vgoff[j], dst + kKBytes + (j * kFastWaves + wave) * 1024);
+      const int at = (part - LPH) * kFastWaves + wave;
+      gload_lds16(vp + (long long)src * kTileN * D + at * 512, lane_b, dst + kKBytes + at * 1024);
     }
   };
   auto issue_tile = [&](int t) {
@@ -223,11 +210,10 @@ __global__ __launch_bounds__(kFastThreads, 2) void attn_fwd_bf16_kernel(FwdParam
 
   auto kfrag = [&](const unsigned char* sk, int c) {
     const int kb = c % 2, ks = c / 2;
-    return *reinterpret_cast<const bf16x8*>(sk + kb * (32 * CH * 16) + krow_b + ((ks << 5) ^ khx));
+    return *reinterpret_cast<const bf16x8*>(sk + lane_b + (kb * (D / 16) + ks) * 1024);
   };
   auto vfrag = [&](const unsigned char* sv, int c) {
-    const int t16 = c / NB, db = c % NB;
-    return *reinterpret_cast<const f16x8*>(sv + vlane_b + (t16 * 2 * D + db * 32) * 16);
+    return *reinterpret_cast<const f16x8*>(sv + lane_b + c * 1024);
   };
 
   // S^T of tile t alone (first tile of an item)
@@ -523,7 +509,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdPar
   }
   const int bhx = p.per_q_head ? bh : b * L.Hkv + g;
   const unsigned char* kp = static_cast<const unsigned char*>(p.Kp) + (long long)bhx * p.npad * D * 2 + lane * 16;
-  const unsigned char* vp = static_cast<const unsigned char*>(p.Vp) + (long long)bhx * p.npad * D * 2 + (h * D + ln) * 16;
+  const unsigned char* vp = static_cast<const unsigned char*>(p.Vp) + (long long)bhx * p.npad * D * 2 + lane * 16;
   const int* tile_map = TILEMAP ? p.tile_map + (long long)bh * p.tile_stride : nullptr;
   auto tile_bytes = [&](int t) {
     const int src = TILEMAP ? __builtin_amdgcn_readfirstlane(tile_map[t]) : t;
@@ -552,7 +538,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void attn_fwd_split_kernel(FwdPar
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int db = 0; db < NB; ++db) vf[u][db] = *reinterpret_cast<const f16x8*>(v + ((half * 2 + u) * 2 * D + db * 32) * 16);
+        for (int db = 0; db < NB; ++db) vf[u][db] = *reinterpret_cast<const f16x8*>(v + ((half * 2 + u) * NB + db) * 1024);
     };
     load_v(0);
     f32x16 s[2];

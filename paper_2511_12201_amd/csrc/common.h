@@ -224,6 +224,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ int seq_len(const Layer& L, const Ragged& rg, int b) { return rg.on ? rg.n[b] : L.N; }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+// The lane's number formed anew: where no register is free to hold it, or anything made of it, across a loop.
+__device__ __forceinline__ int loop_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 
 // Lane exchange on the vector ALU (data-parallel primitives): lanes without a source, and rows outside row_mask, get 0.
 template <int CTRL, int ROW_MASK>

@@ -39,9 +39,9 @@ size_t probe_ws(const Layer& L, int dtype, int pb);
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
               hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
 
-// pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values; fp32: Qn, dOn in fragment order)
-// k_frag: Kn, Vn in the order of a 32x32 MFMA's A operand instead of row by row, [32-row block][k step][lane] of 16 bytes
-// (lane = 32 * half + row; a k step is 16 bf16 or 8 fp32 values wide)
+// pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values, and not both Kt and Vt in one call)
+// Kn, Vn, Qn, dOn in the order of a 32x32 MFMA's A operand, [32-row block][k step][lane] of 16 bytes (lane = 32 * half + row; a
+// k step is 16 bf16 or 8 fp32 values wide); fp32 without k_frag: Kn, Vn row by row
 int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
                 int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
                 void* Vt, int* kidx, hipStream_t st, bool k_frag = false);

@@ -2,23 +2,22 @@
 //
 // pack_kv: per head, the selected K/V rows are gathered into dense buffers,
 // padded with zero rows to whole 64-key tiles, and the original token index of
-// every slot is recorded (pad slots: kPadKeyIndex).  Two layouts are produced on
-// request: "natural" [slot][d], and "k-packed" [16-slot group][half h][d][8 slots]
+// every slot is recorded (pad slots: kPadKeyIndex).  Layouts: "fragment order"
+// [32-row block][k step][lane] of 16 bytes, lane = 32 h + row (a k step is 16 elements of
+// bf16, 8 of fp32): the A or B operand of a 32x32 MFMA that contracts over d, a kilobyte
+// per operand with the lanes side by side, in memory and in LDS alike (no swizzle, one
+// address register for all of a tile's fragments); and "k-packed" [16-slot group][d / 32][half h][d % 32][8 slots]
 // with slot(group,h,j) = 16 group + 8 (j/4) + 4 h + j%4 -- the order in which a
 // 32x32 MFMA accumulator holds its rows -- so that the operand of a GEMM that
 // contracts over the slots is one 16-byte read per lane.  The k-packed
 // V (the forward's operand; the backward does not use it) is written in f16: the
-// forward multiplies its f16-rounded weights with it.  k_frag: natural rows in "fragment
-// order" instead, [32-row block][k step][lane] of 16 bytes, lane = 32 h + row (a k step is 16
-// elements of bf16, 8 of fp32), for the kernels of short sequences, which take their operands
-// straight from memory.  fp32 inputs, k-packed: [32-slot block][q4][d / 32][h][d % 32][4
+// forward multiplies its f16-rounded weights with it.  fp32 inputs on long sequences
+// (k_frag false): rows as they are.  fp32 inputs, k-packed: [32-slot block][q4][d / 32][h][d % 32][4
 // slots], slot = 8 q4 + 4 h + e: the fp32 MFMA takes one element per lane, four of them
 // arrive with one 16-byte read.
 //
 // pack_q: for the backward pass, the kept rows of Q and dO in the k-packed
-// layout (contraction over queries) and, for bf16, also as contiguous natural
-// rows in kept order (so that a tile of them is one linear stream), plus per
-// kept row lse * log2(e) and delta = rowsum(dO * O).  On the way every token's entry of the
+// layout (contraction over queries) and in fragment order, plus per kept row lse * log2(e) and delta = rowsum(dO * O).  On the way every token's entry of the
 // key lists' slot map is set to "not listed".
 #include "common.h"
 #include "kernels.h"
@@ -44,20 +43,36 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4& x) {
   return r;
 }
 
-// 8 rows x 8 bf16 (one 16-byte chunk per row) -> 8 columns x 8 rows, written as 8 x 16 bytes
-__device__ __forceinline__ void transpose8x8_store(const u32x4 (&in)[8], u16* dst) {
+// Unit t of a 64-slot tile in the bf16 k-packed order: (16-slot group, half, 8-wide d chunk), 128 bytes of output, the units in
+// the order of the output.
+template <int D>
+__device__ __forceinline__ void packed_unit(int t, int& grp, int& h, int& dc) {
+  constexpr int NB = D / 32;
+  dc = (t >> 3) % NB * 4 + (t & 3);
+  h = (t >> 2) & 1;
+  grp = t / (8 * NB);
+}
+
+// 8 rows x 8 bf16 (one 16-byte chunk per row) of every lane -> its 8 columns x 8 rows, 128 bytes; the wavefront's 8 KB are
+// contiguous in lane order and leave through `lds` (8 KB of its own) as eight whole kilobytes: straight from the registers a
+// store would touch 64 cache lines with 16 bytes each.
+__device__ __forceinline__ void transpose8x8_store(const u32x4 (&in)[8], u16* wave_dst, unsigned char* lds) {
+  const int l = lane_id();
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     unsigned w[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
       const unsigned a = in[2 * jj][e >> 1], b = in[2 * jj + 1][e >> 1];
-      const unsigned lo = (e & 1) ? (a >> 16) : (a & 0xffffu);
-      const unsigned hi = (e & 1) ? (b >> 16) : (b & 0xffffu);
-      w[jj] = lo | (hi << 16);
+      w[jj] = __builtin_amdgcn_perm(b, a, (e & 1) ? 0x07060302u : 0x05040100u);       // high or low halves of a, then b
     }
-    u32x4 o = {w[0], w[1], w[2], w[3]};
-    *reinterpret_cast<u32x4*>(dst + e * 8) = o;
+    *reinterpret_cast<u32x4*>(lds + (l * 8 + (e ^ (l & 7))) * 16) = u32x4{w[0], w[1], w[2], w[3]};
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int p = j * 64 + l, from = p >> 3;
+    *reinterpret_cast<u32x4*>(wave_dst + p * 8) = *reinterpret_cast<const u32x4*>(lds + (from * 8 + ((p & 7) ^ (from & 7))) * 16);
   }
 }
 
@@ -78,9 +93,13 @@ __device__ __forceinline__ void transpose4x4_store(const u32x4 (&in)[4], float* 
 // 153 / 148, 16384: 526 / 520, 65536: 4797 / 4792; 8 heads, 16384: 313 / 302.
 // bf16: two wavefronts per output, so that a thread has one batch of loads and the outputs do not wait for each other.  (The
 // copies by all threads, then the transposes by those that had one, was a second memory latency for every workgroup.)
-// Memory-bound on long sequences.  Layer in us, before / after, with the same change in pack_q below: forward, 1072 tokens 89.5 / 87.3,
-// 16391: 432.5 / 430.3, d = 64, 3000: 41.7 / 40.1; forward and backward, two clips of 3101, d = 64: 202.4 / 198.3, 32768:
-// 7364 / 7339.  (d threads per output: 8192 at d = 64 2.5 % slower.)
+// Layer in us, before / after, with the same change in pack_q below: forward, 1072 tokens 89.5 / 87.3, 16391: 432.5 / 430.3,
+// d = 64, 3000: 41.7 / 40.1; forward and backward, two clips of 3101, d = 64: 202.4 / 198.3, 32768: 7364 / 7339.  (d threads
+// per output: 8192 at d = 64 2.5 % slower.)
+// Bound on long sequences: the writes (the K/V of the KV heads, read once per query head, come from the caches), so every
+// store instruction covers whole lines (transpose8x8_store; 128-byte pieces in the copies).  28 heads, d = 128, stores of 16
+// bytes to 64 lines at once / whole lines: for the forward 16391 46.9 / 39.4 us, 32768 91 / 72 us (253 MB written: 3.5
+// TB/s), for the backward 109 / 97 us, pack_q there 168 / 131 us.
 constexpr int kOutThreads = 128;
 template <typename T, int D>
 __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void pack_kv_kernel(const T* __restrict__ K, const T* __restrict__ V, Layer L,
@@ -93,6 +112,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
   constexpr int E = Elem<T>::kPer16B;
   constexpr int CPR = D / E;
   __shared__ int sIdx[kTileN];
+  __shared__ __attribute__((aligned(16))) unsigned char sT[kBf16 ? D / 64 : 1][kBf16 ? 8192 : 16];
   const int tile = blockIdx.x, bhx = blockIdx.y;
   const int H = per_q_head ? L.Hq : L.Hkv;
   const int b = bhx / H, hx = bhx % H;
@@ -114,27 +134,28 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
   if constexpr (kBf16) {
     const int t = threadIdx.x % kOutThreads;
     int unit = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kOutThreads));
-    // row by row, or in fragment order: consecutive threads take consecutive rows of one 16-byte column, so the writes are
-    // contiguous and the reads meet in L1
+    // fragment order: a wavefront takes 8 rows of 128 bytes at a time and leaves 8 columns of 128 bytes
     auto copy = [&](const T* src, T* dst) {
       constexpr int kEach = kTileN * CPR / kOutThreads;
       u32x4 in[kEach];
+      int at[kEach];
 #pragma unroll
       for (int j = 0; j < kEach; ++j) {
-        const int c = j * kOutThreads + t;
-        const int row = k_frag ? c / (32 * CPR) * 32 + (c & 31) : c / CPR, chunk = k_frag ? c / 32 % CPR : c % CPR;
+        const int u = j * (kOutThreads / 64) + t / 64, row = u % 8 * 8 + (t & 7), chunk = u / 8 * 8 + (t >> 3 & 7);
         const int id = sIdx[row];
+        at[j] = (row / 32 * 32 * CPR + chunk * 32 + row % 32) * E;
         in[j] = zero;
         if (id != kPadKeyIndex) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)id * L.ks[2] + chunk * E);
       }
 #pragma unroll
-      for (int j = 0; j < kEach; ++j) *reinterpret_cast<u32x4*>(dst + tile_off + (j * kOutThreads + t) * E) = in[j];
+      for (int j = 0; j < kEach; ++j) *reinterpret_cast<u32x4*>(dst + tile_off + at[j]) = in[j];
     };
-    // thread = (16-slot group, half, 8-wide d chunk): 8x8 transpose in registers
+    // a thread transposes 8 slots x 8 of d in registers
     auto transposed = [&](const T* src, T* dst, bool f16) {
-      if (t >= (kTileN / 16) * 2 * (D / 8)) return;
+      if (t >= D) return;
       u32x4 in[8];
-      const int dc = t % (D / 8), h = (t / (D / 8)) & 1, grp = t / (D / 8) / 2;
+      int grp, h, dc;
+      packed_unit<D>(t, grp, h, dc);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int id = sIdx[16 * grp + 8 * (j >> 2) + 4 * h + (j & 3)];
@@ -145,7 +166,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
 #pragma unroll
         for (int j = 0; j < 8; ++j) in[j] = bf16x8_to_f16x8(in[j]);
       }
-      transpose8x8_store(in, reinterpret_cast<u16*>(dst) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
+      transpose8x8_store(in, reinterpret_cast<u16*>(dst) + tile_off + t / 64 * 4096, sT[t / 64]);
     };
     if (Kn && unit-- == 0) copy(kbase, Kn);
     if (Vn && unit-- == 0) copy(vbase, Vn);
@@ -200,6 +221,7 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
   constexpr int LPR = D / E;
   constexpr int RPP = kThreads / LPR;
   __shared__ int sIdx[64];
+  __shared__ __attribute__((aligned(16))) unsigned char sT[kBf16 ? 2 * D / 64 : 1][kBf16 ? 8192 : 16];
   const int tile = blockIdx.x, bh = blockIdx.y;
   const int b = bh / L.Hq, i = bh % L.Hq;
   const int nq = q_cnt[bh];
@@ -230,9 +252,8 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
 #pragma unroll
       for (int e = 0; e < E; ++e) dot = fmaf(av[e], gv[e], dot);
     }
-    if (Qn) {                                   // packed copies, natural or in fragment order (pad rows zero)
-      const long long o = kBf16 ? ((long long)bh * nqpad + tile * 64 + r) * D + c * E
-                                : ((long long)bh * nqpad + tile * 64 + r / 32 * 32) * D + (c * 32 + r % 32) * E;
+    if (Qn) {                                   // packed copies in fragment order (pad rows zero)
+      const long long o = ((long long)bh * nqpad + tile * 64 + r / 32 * 32) * D + (c * 32 + r % 32) * E;
       *reinterpret_cast<u32x4*>(Qn + o) = qc;
       *reinterpret_cast<u32x4*>(dOn + o) = g;
     }
@@ -259,9 +280,8 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
       const int it0 = threadIdx.x - kThreads, which = it0 / kItems, it = it0 % kItems;
       const T* src = (which ? dO : Q) + head_off;
       T* dst_t = which ? dOt : Qt;
-      const int dc = it % (D / 8);
-      const int h = (it / (D / 8)) & 1;
-      const int grp = it / (D / 8) / 2;
+      int grp, h, dc;
+      packed_unit<D>(it, grp, h, dc);
       u32x4 in[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -269,7 +289,7 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
         in[j] = zero;
         if (row >= 0) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)row * L.qs[2] + dc * 8);
       }
-      transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + ((grp * 2 + h) * D + dc * 8) * 8);
+      transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + it / 64 * 4096, sT[it0 / 64]);
     }
   } else {
     constexpr int kItems = (64 / 4) * (D / 4);
@@ -298,6 +318,7 @@ int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head,
                    int* kidx, hipStream_t st, int k_frag) {
   const int heads = per_q_head ? L.Hq : L.Hkv;
   ProfScope prof__(kProfPack, st);
+  if (sizeof(T) == 2 && Kt && Vt) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "pack: one k-packed copy at a time");   // they share sT
   const int outputs = (Kn != nullptr) + (Vn != nullptr) + (Kt != nullptr) + (Vt != nullptr);
   const int threads = sizeof(T) == 2 ? kOutThreads * outputs : kThreads;
   hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kTileN, L.B * heads), dim3(threads), 0, st,
