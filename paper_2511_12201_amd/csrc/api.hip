@@ -328,8 +328,9 @@ int omni_debug_device_work_list(const omni_layer_desc* desc, const int32_t* q_id
   b.b_cap = b_cap;
   b.tile_m = tile_rows;
   b.sched = list;
-  CHECK(run_bounds(L, b, static_cast<hipStream_t>(stream)));
-  return run_order(L, q_cnt, tile_rows, list, static_cast<hipStream_t>(stream), queues);
+  const Order order = make_order(L, q_cnt, tile_rows, list, queues);
+  CHECK(run_prepare(L, OMNI_BF16, false, nullptr, nullptr, &b, nullptr, nullptr, static_cast<hipStream_t>(stream)));
+  return run_prepare(L, OMNI_BF16, false, nullptr, nullptr, nullptr, &order, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int omni_debug_copy(const void* src, void* dst, size_t bytes, void* stream) {

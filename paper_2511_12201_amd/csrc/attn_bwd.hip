@@ -56,12 +56,12 @@ struct BwdParams {
   void* dQ;
   int* sched;           // work list of the dQ kernel (sched.h)
   size_t order_off;     // where its hand-out order starts
+  const int* list;      // [B*Hq, list_stride] the heads' key lists
+  int list_stride;
   const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position
   const int* kfirst;    // [B*Hq, npad] first kept-query position that sees a packed key
-  int head_group;       // heads per dispatch group of the key kernel
   int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernel)
   int split_len;        // query tiles per split, at least (bf16: at most, see key_list_kernel)
-  int key_wgs;          // workgroups that share the key kernel's items
   long long plane;      // floats between the partial-gradient planes of two splits
   int* klist;           // work list of the key kernel: [0] counter, [1] number of items, [2] split length, [4..] items;
                         // null: fp32
@@ -81,19 +81,10 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int r0) {
 
 constexpr int kKeyWaves = 8;
 constexpr int kKeyThreads = kKeyWaves * 64;
-constexpr int kKeyTile = kKeyWaves * 32;     // packed keys per workgroup
-constexpr int kKeyQ = 64;                    // queries per streamed tile
-// A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
-// against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
-// query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
+static_assert(kKeyTile == kKeyWaves * 32, "32 keys per wavefront");
 constexpr int kKeySplitLenF32 = 4;           // fp32: query tiles per split, at least (a workgroup owns 32 keys: needed sooner)
 constexpr int kKeySplitLen = 128;            // bf16: query tiles per split, at most (64..128 measure alike, 32 and 256 worse)
 constexpr int kKeyMaxSplits = 4;             // at most 8: a work item carries the split in 3 bits
-__host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
-  const int s = n_qtiles / split_len;
-  return s < 1 ? 1 : (s > max_splits ? max_splits : s);
-}
-
 // ------------------------------------------------------------------ fp32
 //
 // Both kernels divide the work as the fp32 forward does: a workgroup owns 32 rows (keys, or kept queries), its
@@ -851,67 +842,6 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
 // lse * log2e and delta of the tile's queries come with the tile (LDS-DMA of 4 bytes per lane); the causal
 // mask is a comparison of the query position with the first position that sees the lane's key.
 
-// Work items of the key kernel: (head, key tile, split), in dispatch order -- heads in groups of p.head_group,
-// inside a group key tile by key tile (the first key tiles, seen by the most queries, first), the splits of a
-// tile side by side.  Slot i of that order is a (head, key tile); most are empty (key tiles beyond a head's
-// budget), so one workgroup lists the live ones with their splits, and the persistent key kernel pulls from
-// the list: an empty workgroup would still wait for a whole CU's LDS.
-constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, -
-
-// head and key tile of slot i, and how many query tiles see it (0: nothing to do)
-__device__ __forceinline__ int key_slot(const BwdParams& p, long long i, int& bh, int& ktile) {
-  const Layer& L = p.L;
-  const int BH = L.B * L.Hq, nkt = p.npad / kKeyTile;
-  const long long per_group = (long long)p.head_group * nkt;
-  const int grp = (int)(i / per_group), within = (int)(i % per_group);
-  const int heads_here = min(p.head_group, BH - grp * p.head_group);
-  if (heads_here <= 0) return 0;
-  ktile = within / heads_here;
-  bh = grp * p.head_group + within % heads_here;
-  if (ktile >= nkt) return 0;
-  if (ktile * kKeyTile >= min(p.budget[budget_slot(L.bph, bh / L.Hq, bh)], p.b_cap)) return 0;
-  return max(1, cdiv(p.q_cnt[bh], kKeyQ) - p.kfirst[(long long)bh * p.npad + ktile * kKeyTile] / kKeyQ);
-}
-
-// One workgroup of 1024 threads: the list, and the length of a split: a workgroup's share of all query tiles (a longer
-// chain would outlast the others), between 8 and p.split_len.  At 3k tokens, two sequences of 28 heads, the longest chain
-// is head 0's 49 query tiles while a share is 9: dK' 87 -> 44 us, dV' 63 -> 34 us.
-__global__ __launch_bounds__(1024) void key_list_kernel(BwdParams p, long long n_slots) {
-  __shared__ int wave_cnt[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int bh, ktile, tiles = 0;
-  for (long long i = threadIdx.x; i < n_slots; i += 1024) tiles += key_slot(p, i, bh, ktile);
-  tiles = wave_sum(tiles);
-  if (lane == 0) wave_cnt[wave] = tiles;
-  __syncthreads();
-  tiles = 0;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) tiles += wave_cnt[w];
-  const int split_len = min(p.split_len, max(8, cdiv(tiles, p.key_wgs)));
-  int base = 0;
-  for (long long i0 = 0; i0 < n_slots; i0 += 1024) {
-    const long long i = i0 + threadIdx.x;
-    const int seen = i < n_slots ? key_slot(p, i, bh, ktile) : 0;
-    const int n_sp = seen ? key_tile_splits(seen, p.nsplit, split_len) : 0;
-    const int incl = (int)wave_scan((unsigned)n_sp);
-    __syncthreads();
-    if (lane == 63) wave_cnt[wave] = incl;
-    __syncthreads();
-    int at = base + incl - n_sp;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      at += w < wave ? wave_cnt[w] : 0;
-      base += wave_cnt[w];
-    }
-    for (int sp = 0; sp < n_sp; ++sp) p.klist[kKeyListHeader + at + sp] = (bh << 16) | (ktile << 3) | sp;
-  }
-  if (threadIdx.x == 0) {
-    p.klist[0] = 0;
-    p.klist[1] = base;
-    p.klist[2] = split_len;
-  }
-}
-
 template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdParams p) {
   typedef u16 T;
@@ -1155,8 +1085,10 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_reduce_kernel(BwdParams p, 
   f32x4 ak = {0.f, 0.f, 0.f, 0.f}, av = {0.f, 0.f, 0.f, 0.f};
   for (int j = 0; j < L.G; ++j) {
     const int bh = b * L.Hq + g * L.G + j;
-    const int pos = inv[(long long)bh * L.N + n];               // slot of token n in the head's list, or -1
-    if (pos >= 0) {
+    // Slot of token n in the head's list, if it has one: of the other tokens nobody has written the entry, so what it says is
+    // looked up in the list (a fill of the map would stand between it and the pass that writes it).
+    const int pos = inv[(long long)bh * L.N + n], nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
+    if (pos >= 0 && pos < nkeys && p.list[(long long)bh * p.list_stride + pos] == n) {
       int n_sp = 1;
       if (p.nsplit > 1) {                  // as the key kernel counted: the query tiles from the tile's first visible pair on
         const int first = p.kfirst[(long long)bh * p.npad + pos / kKeyTile * kKeyTile];
@@ -1190,7 +1122,7 @@ struct BwdWs {
   float *lse2c, *deltac, *dKp, *dVp;
   int* sched;
   int *qvis, *kfirst, *inv, *klist;
-  int *kidx_kv, *vbudget, *tile_map;      // in-place block lists only
+  int *vbudget, *tile_map;                // in-place block lists only, as kidx
 };
 
 // Block lists walked in place (omni_block_attn_bwd): ascending block ids per head, one budget per batch item.
@@ -1224,7 +1156,7 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.dOt = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
   w.Qn = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
   w.dOn = a.take<unsigned char>(copies ? qrows * L.D * es : 4);
-  w.kidx = a.take<int>(krows);
+  w.kidx = a.take<int>(npad_kv > 0 ? krows : 4);
   w.lse2c = a.take<float>(qrows);
   w.deltac = a.take<float>(qrows);
   w.dKp = a.take<float>(planes * krows * L.D);
@@ -1234,7 +1166,6 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
   w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * kKeyMaxSplits);
-  w.kidx_kv = a.take<int>(npad_kv > 0 ? kvrows : 4);
   w.vbudget = a.take<int>(L.B);
   w.tile_map = a.take<int>(npad_kv > 0 ? BH * cap_tiles : 4);
   return w;
@@ -1272,27 +1203,55 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   constexpr int tile_m = kFast ? kDqTileM : kTileM;
   const bool split = kFast ? short_route(attention_work(L) <= kSplitWork) : f32_short(L);      // short sequences: no work list
   const bool copies = kFast || split;                  // fp32 on long sequences: only K and V, row by row
-  int rc;
+  int rc = check_work_list(L, tile_m);
+  if (rc != OMNI_OK) return rc;
+  // the bf16 key kernel's list: heads and key tiles in 16 and 13 bits of an item
+  if (kFast && (L.B * L.Hq >= 32768 || npad / kKeyTile >= 8192))
+    OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "key work list: too many heads or key tiles");
+  PackKv kv{};
+  kv.K = K;
+  kv.V = V;
+  kv.Kn = w.Kn;
+  kv.Vn = w.Vn;
+  kv.Kt = copies ? w.Kt : nullptr;
+  kv.k_frag = split;
   if constexpr (BLOCKS) {
     // K, V (fragment order) and K (k-packed) of every KV head once, in token order: shared by the heads of a group
-    rc = run_pack_kv(L, dt, K, V, 0, nullptr, L.N, nullptr, L.N, npad_kv, kTileN, w.Kn, w.Vn, w.Kt, nullptr, w.kidx_kv, st);
-    if (rc != OMNI_OK) return rc;
+    kv.b_cap = L.N;
+    kv.npad = npad_kv;
+    kv.pad_to = kTileN;
     // token lists of the selected blocks (causal bounds, the reduction's slot map), rows npad apart, and the tile map
-    rc = run_expand_blocks(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, w.kidx, w.vbudget, npad, st);
-    if (rc != OMNI_OK) return rc;
-    rc = run_tile_map(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, npad_kv / kTileN - 1, w.tile_map, st);
+    rc = run_expand_blocks(L, blk->blk_idx, blk->blk_budget, blk->blk_cap, blk->block, w.kidx, w.vbudget, npad, st, w.tile_map,
+                           npad_kv / kTileN - 1);
     if (rc != OMNI_OK) return rc;
     kv_idx = w.kidx;
     budget = w.vbudget;
     b_cap = npad;                             // the lists' row pitch; their lengths are in vbudget
   } else {
-    rc = run_pack_kv(L, dt, K, V, 1, kv_idx, b_cap, budget, b_cap, npad, kKeyTile, w.Kn, w.Vn, copies ? w.Kt : nullptr, nullptr,
-                     w.kidx, st, split);
-    if (rc != OMNI_OK) return rc;
+    kv.per_q_head = 1;
+    kv.src_idx = kv_idx;
+    kv.idx_stride = b_cap;
+    kv.budget = budget;
+    kv.b_cap = b_cap;
+    kv.npad = npad;
+    kv.pad_to = kKeyTile;
   }
-  rc = run_pack_q(L, dt, Q, O, dO, lse, q_idx, q_cnt, nqpad, copies ? w.Qt : nullptr, copies ? w.dOt : nullptr,
-                  copies ? w.Qn : nullptr, copies ? w.dOn : nullptr, w.lse2c, w.deltac, w.inv, st);
-  if (rc != OMNI_OK) return rc;
+  PackQ pq{};
+  pq.Q = Q;
+  pq.O = O;
+  pq.dO = dO;
+  pq.lse = lse;
+  pq.q_idx = q_idx;
+  pq.q_cnt = q_cnt;
+  pq.nqpad = nqpad;
+  if (copies) {
+    pq.Qt = w.Qt;
+    pq.dOt = w.dOt;
+    pq.Qn = w.Qn;
+    pq.dOn = w.dOn;
+  }
+  pq.lse2c = w.lse2c;
+  pq.deltac = w.deltac;
   BwdParams p;
   p.Q = Q;
   p.dO = dO;
@@ -1319,55 +1278,60 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.plane = (long long)L.B * L.Hq * npad * D;
   p.dQ = dQ;
   p.klist = nullptr;
-  p.key_wgs = 1;
+  p.list = kv_idx;
+  p.list_stride = b_cap;
   p.sched = w.sched;
   p.qvis = w.qvis;
   p.kfirst = w.kfirst;
   p.tile_map = w.tile_map;
   p.tile_stride = cap_keys / kTileN;
   p.npad_kv = BLOCKS ? npad_kv : npad;
-  rc = check_work_list(L, tile_m);
-  if (rc != OMNI_OK) return rc;
-  {
-    Bounds bn{};                                 // masks by position, slot map, cleared rows, the bf16 dQ kernel's work items
-    bn.q_idx = q_idx;
-    bn.q_cnt = q_cnt;
-    bn.klist = w.kidx;
-    bn.klist_stride = npad;
-    bn.budget = budget;
-    bn.b_cap = b_cap;
-    bn.npad = npad;
-    bn.qvis = w.qvis;
-    bn.kfirst = w.kfirst;
-    bn.inv = w.inv;
-    bn.X = dQ;
-    bn.elem_bytes = sizeof(T);
-    bn.tile_m = tile_m;
-    bn.sched = split ? nullptr : w.sched;
-    rc = run_bounds(L, bn, st);
-    if (rc != OMNI_OK) return rc;
-  }
+  Bounds bn{};                                 // masks by position, slot map, cleared rows, the bf16 dQ kernel's work items
+  bn.q_idx = q_idx;
+  bn.q_cnt = q_cnt;
+  bn.klist = kv_idx;
+  bn.klist_stride = b_cap;
+  bn.budget = budget;
+  bn.b_cap = b_cap;
+  bn.npad = npad;
+  bn.qvis = w.qvis;
+  bn.kfirst = w.kfirst;
+  bn.inv = w.inv;
+  bn.X = dQ;
+  bn.elem_bytes = sizeof(T);
+  bn.tile_m = tile_m;
+  bn.sched = split ? nullptr : w.sched;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
-  if (!split) {
-    rc = run_order(L, q_cnt, tile_m, w.sched, st);
+  if (!kFast && split) {                       // no list at all: one launch
+    rc = run_prepare(L, dt, true, &kv, &pq, &bn, nullptr, nullptr, st);
+  } else {                                     // the lists, a few serial workgroups, hide under the packs
+    // Dispatch order of the key kernel: heads in groups of 7, key tile by key tile inside a group.  Head after head leaves the
+    // long first key tiles of the last heads for the end (measured 3.9 ms at 32k), all heads at once spreads 28
+    // query streams over the caches (4.4 ms); groups of 7 take 3.4 ms.  Group sizes that share a factor with
+    // the 8 XCDs (workgroup i runs on XCD i mod 8) pin heads to XCDs and unbalance them: 8 takes 5.6 ms.
+    KeyList kl{};
+    kl.q_cnt = q_cnt;
+    kl.budget = budget;
+    kl.b_cap = b_cap;
+    kl.npad = npad;
+    kl.kfirst = w.kfirst;
+    kl.head_group = kKeyHeadGroup;
+    kl.nsplit = p.nsplit;
+    kl.split_len = p.split_len;
+    kl.key_wgs = persistent_grid() / 2;        // one workgroup per CU (its LDS ring fills it)
+    kl.n_slots = (int)key_list_slots(L, npad);
+    kl.klist = w.klist;
+    if (kFast) p.klist = w.klist;
+    const Order order = make_order(L, q_cnt, tile_m, w.sched);
+    rc = run_prepare(L, dt, true, nullptr, nullptr, &bn, nullptr, nullptr, st);
     if (rc != OMNI_OK) return rc;
+    rc = run_prepare(L, dt, true, &kv, &pq, nullptr, split ? nullptr : &order, kFast ? &kl : nullptr, st);
   }
+  if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfBwdDkDv, st);
     if constexpr (sizeof(T) == 2) {
-      // Dispatch order: heads in groups of 7, key tile by key tile inside a group.  Head after head leaves the long
-      // first key tiles of the last heads for the end (measured 3.9 ms at 32k), all heads at once spreads 28
-      // query streams over the caches (4.4 ms); groups of 7 take 3.4 ms.  Group sizes that share a factor with
-      // the 8 XCDs (workgroup i runs on XCD i mod 8) pin heads to XCDs and unbalance them: 8 takes 5.6 ms.
-      p.head_group = kKeyHeadGroup;
-      if (L.B * L.Hq >= 32768 || npad / kKeyTile >= 8192)
-        OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "key work list: too many heads or key tiles");
-      p.klist = w.klist;
-      const unsigned key_wgs = (unsigned)persistent_grid() / 2;       // one workgroup per CU (its LDS ring fills it)
-      p.key_wgs = (int)key_wgs;
-      hipLaunchKernelGGL(key_list_kernel, dim3(1), dim3(1024), 0, st, p, (long long)key_list_slots(L, npad));
-      OMNI_LAUNCH_CHECK();
-      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, BLOCKS>), dim3(key_wgs), dim3(kKeyThreads), 0, st, p);
+      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, BLOCKS>), dim3((unsigned)persistent_grid() / 2), dim3(kKeyThreads), 0, st, p);
     } else {
       if (split)
         hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),

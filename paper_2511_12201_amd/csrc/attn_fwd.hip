@@ -940,7 +940,6 @@ int fwd_npad(int rows) {
 struct FwdWs {
   void* Kp;
   void* Vp;
-  int* kidx;
   int* sched;
   int* qvis;
 };
@@ -951,7 +950,6 @@ FwdWs carve_fwd(Arena& a, const Layer& L, int dtype, int heads, int npad, bool s
   const size_t rows = (size_t)L.B * heads * npad;
   w.Kp = a.take<unsigned char>(rows * L.D * es);
   w.Vp = a.take<unsigned char>(rows * L.D * es);
-  w.kidx = a.take<int>(rows);
   w.sched = a.take<int>(sched_ints(L.B * L.Hq, L.N, dtype == OMNI_BF16 ? kFastTileM : kTileM));
   w.qvis = sparse ? a.take<int>((size_t)L.B * L.Hq * L.N) : nullptr;
   return w;
@@ -969,10 +967,8 @@ int launch_split(const FwdParams& p, hipStream_t st) {
 }
 
 // What the forward needs to know about every token: visible counts, cleared rows, the items of the work list.
-int run_fwd_bounds(const Layer& L, const int* q_idx, const int* q_cnt, const int* klist, int klist_stride,
-                   const int* budget, int b_cap, int* qvis, void* O, int elem_bytes, float* lse, int tile_m, int* sched,
-                   hipStream_t st) {
-  ProfScope prof__(kProfClear, st);
+Bounds fwd_bounds(const int* q_idx, const int* q_cnt, const int* klist, int klist_stride, const int* budget, int b_cap, int* qvis,
+                  void* O, int elem_bytes, float* lse, int tile_m, int* sched) {
   Bounds b{};
   b.q_idx = q_idx;
   b.q_cnt = q_cnt;
@@ -986,7 +982,17 @@ int run_fwd_bounds(const Layer& L, const int* q_idx, const int* q_cnt, const int
   b.lse = lse;
   b.tile_m = tile_m;
   b.sched = sched;
-  return run_bounds(L, b, st);
+  return b;
+}
+
+// Bounds, packs and order of the work list.  Short sequences have no list: one launch, where each of the two passes alone takes
+// little longer than an empty one.  On long ones the bounds go first, so that the order, a few serial workgroups, hides under the packs.
+int prepare_fwd(const Layer& L, int dtype, const PackKv& kv, const Bounds& bn, bool split, int queues, hipStream_t st) {
+  if (split) return run_prepare(L, dtype, false, &kv, nullptr, &bn, nullptr, nullptr, st);
+  const int rc = run_prepare(L, dtype, false, nullptr, nullptr, &bn, nullptr, nullptr, st);
+  if (rc != OMNI_OK) return rc;
+  const Order order = make_order(L, bn.q_cnt, bn.tile_m, bn.sched, queues);
+  return run_prepare(L, dtype, false, &kv, nullptr, nullptr, &order, nullptr, st);
 }
 
 template <typename T, int D>
@@ -999,14 +1005,6 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   FwdWs w = carve_fwd(a, L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, heads, npad, sparse);
   // short sequences: 32-row items without a work list
   const bool split = sizeof(T) == 2 ? sparse && short_route(attention_work(L) <= kSplitWork) : f32_short(L);
-  {
-    const int dt = sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32;
-    // K natural or in fragment order; V k-packed (bf16: converted to f16), for fp32 on long sequences natural
-    const bool v_rows = sizeof(T) == 4 && !split;
-    int rc = run_pack_kv(L, dt, K, V, sparse ? 1 : 0, kv_idx, b_cap, budget, b_cap, npad, kTileN, w.Kp,
-                         v_rows ? w.Vp : nullptr, nullptr, v_rows ? nullptr : w.Vp, w.kidx, st, split);
-    if (rc != OMNI_OK) return rc;
-  }
   FwdParams p;
   p.Q = Q;
   p.O = O;
@@ -1028,12 +1026,34 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   constexpr bool kFast = sizeof(T) == 2;
   constexpr int tile_m = kFast ? kFastTileM : kTileM;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
-  int rc = OMNI_OK;
-  rc = check_work_list(L, tile_m);
+  int rc = check_work_list(L, tile_m);
   if (rc != OMNI_OK) return rc;
-  if (sparse) {
-    rc = run_fwd_bounds(L, q_idx, q_cnt, w.kidx, npad, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m,
-                        split ? nullptr : w.sched, st);
+  {
+    constexpr int dt = kFast ? OMNI_BF16 : OMNI_F32;
+    const bool v_rows = !kFast && !split;            // V k-packed (bf16: converted to f16); for fp32 on long sequences as it is
+    PackKv kv{};
+    kv.K = K;
+    kv.V = V;
+    kv.per_q_head = sparse ? 1 : 0;
+    kv.src_idx = kv_idx;
+    kv.idx_stride = b_cap;
+    kv.budget = budget;
+    kv.b_cap = b_cap;
+    kv.npad = npad;
+    kv.pad_to = kTileN;
+    kv.Kn = w.Kp;
+    kv.Vn = v_rows ? w.Vp : nullptr;
+    kv.Vt = v_rows ? nullptr : w.Vp;
+    kv.k_frag = split;
+    // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
+    // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
+    // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
+    // costs (25.7 -> 25.9 ms dense).
+    if (sparse)
+      rc = prepare_fwd(L, dt, kv, fwd_bounds(q_idx, q_cnt, kv_idx, b_cap, budget, b_cap, w.qvis, O, sizeof(T), lse, tile_m,
+                                             split ? nullptr : w.sched), split, kFast ? kSchedQueues : 1, st);
+    else
+      rc = run_prepare(L, dt, false, &kv, nullptr, nullptr, nullptr, nullptr, st);
     if (rc != OMNI_OK) return rc;
   }
   if (split) {
@@ -1043,13 +1063,10 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
   }
-  // Per-head gathered K/V: one queue per XCD, so that the workgroups on a head share its tiles in that XCD's L2
-  // (16.2 -> 5.3 GB from beyond L2 per launch at 64k).  The dense baseline and the in-place
-  // block lists read one copy per KV group, which the heads of a group already share: splitting them over queues only
-  // costs (25.7 -> 25.9 ms dense).
-  rc = sparse ? run_order(L, q_cnt, tile_m, w.sched, st, kFast ? kSchedQueues : 1)
-              : run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
-  if (rc != OMNI_OK) return rc;
+  if (!sparse) {
+    rc = run_schedule(L, q_cnt, budget, b_cap, tile_m, w.sched, st);
+    if (rc != OMNI_OK) return rc;
+  }
   ProfScope prof__(kProfAttnFwd, st);
   if constexpr (kFast)
     hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, false>), dim3(persistent_grid() / 2), dim3(kFastThreads), 0, st, p);
@@ -1060,21 +1077,6 @@ int launch_fwd(const Layer& L, const void* Q, const void* K, const void* V, cons
 }
 
 // ---- in-place variant for block lists (the paper's block-sparse kernel: no gather)
-
-// tile_map[bh, t] = tile of the KV head's packed K/V that holds tile t of the head's key list
-// grid: (cdiv(blk_cap * tiles_per_block, 256), B*Hq)
-__global__ __launch_bounds__(256) void tile_map_kernel(const int* __restrict__ blk_idx, const int* __restrict__ blk_budget,
-                                                       int Hq, int blk_cap, int tiles_per_block, int last_tile,
-                                                       int* __restrict__ tile_map) {
-  const int bh = blockIdx.y, b = bh / Hq;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int nb = min(blk_budget[b], blk_cap);
-  if (t >= blk_cap * tiles_per_block) return;
-  int tile = 0;
-  if (t < nb * tiles_per_block)
-    tile = min(blk_idx[(long long)bh * blk_cap + t / tiles_per_block] * tiles_per_block + t % tiles_per_block, last_tile);
-  tile_map[(long long)bh * blk_cap * tiles_per_block + t] = tile;
-}
 
 struct BlockFwdWs {
   FwdWs f;
@@ -1105,17 +1107,19 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   const int npad = fwd_npad(L.N);
   // K and V of every KV head once, in the kernel's tile layouts, in token order: shared by the heads of a group
   const bool split = short_route(attention_work(L) <= kSplitWork);
-  int rc = run_pack_kv(L, OMNI_BF16, K, V, 0, nullptr, L.N, nullptr, L.N, npad, kTileN, w.f.Kp, nullptr, nullptr, w.f.Vp,
-                       w.f.kidx, st, split);
-  if (rc != OMNI_OK) return rc;
   // token lists of the selected blocks (for the causal bounds) and the tile map
-  rc = run_expand_blocks(L, blk_idx, blk_budget, blk_cap, block, w.klist, w.vbudget, cap_keys, st);
+  int rc = run_expand_blocks(L, blk_idx, blk_budget, blk_cap, block, w.klist, w.vbudget, cap_keys, st, w.tile_map, npad / kTileN - 1);
   if (rc != OMNI_OK) return rc;
-  hipLaunchKernelGGL(tile_map_kernel, dim3(cdiv(blk_cap * tpb, 256), L.B * L.Hq), dim3(256), 0, st, blk_idx, blk_budget,
-                     L.Hq, blk_cap, tpb, npad / kTileN - 1, w.tile_map);
-  OMNI_LAUNCH_CHECK();
-  rc = run_fwd_bounds(L, q_idx, q_cnt, w.klist, cap_keys, w.vbudget, cap_keys, w.f.qvis, O, sizeof(T), lse, kFastTileM,
-                      split ? nullptr : w.f.sched, st);
+  PackKv kv{};
+  kv.K = K;
+  kv.V = V;
+  kv.b_cap = L.N;
+  kv.npad = npad;
+  kv.pad_to = kTileN;
+  kv.Kn = w.f.Kp;
+  kv.Vt = w.f.Vp;
+  rc = prepare_fwd(L, OMNI_BF16, kv, fwd_bounds(q_idx, q_cnt, w.klist, cap_keys, w.vbudget, cap_keys, w.f.qvis, O, sizeof(T), lse,
+                                                kFastTileM, split ? nullptr : w.f.sched), split, 1, st);
   if (rc != OMNI_OK) return rc;
   FwdParams p;
   p.Q = Q;
@@ -1137,8 +1141,6 @@ int launch_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* 
   p.tile_stride = blk_cap * tpb;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, kFastTileM);
   if (split) return launch_split<D, true>(p, st);
-  rc = run_order(L, q_cnt, kFastTileM, w.f.sched, st);
-  if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfAttnFwd, st);
     hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, true>), dim3(persistent_grid() / 2), dim3(kFastThreads), 0, st, p);
@@ -1156,15 +1158,6 @@ size_t attn_fwd_blocks_ws(const Layer& L, int cap_keys) {
 }
 
 int attn_fwd_blocks_max_keys() { return kMaxMapTiles * kTileN; }
-
-int run_tile_map(const Layer& L, const int* blk_idx, const int* blk_budget, int blk_cap, int block, int last_tile,
-                 int* tile_map, hipStream_t st) {
-  const int tpb = block / kTileN;
-  hipLaunchKernelGGL(tile_map_kernel, dim3(cdiv(blk_cap * tpb, 256), L.B * L.Hq), dim3(256), 0, st, blk_idx, blk_budget,
-                     L.Hq, blk_cap, tpb, last_tile, tile_map);
-  OMNI_LAUNCH_CHECK();
-  return OMNI_OK;
-}
 
 int run_attn_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* V, const int* q_idx, const int* q_cnt,
                         const int* blk_idx, const int* blk_budget, int blk_cap, int block, void* O, float* lse,

@@ -177,14 +177,20 @@ __global__ __launch_bounds__(kThreads) void block_cols_kernel(const float* __res
   }
 }
 
-// grid: (cdiv(blk_cap * block, 256), B * Hq)
+// grid: (cdiv(blk_cap * block, 256), B * Hq).  tile_map (block % 64 == 0), if wanted: [B*Hq, blk_cap * block / 64] tile of the
+// KV head's token-ordered K/V that holds tile t of the head's key list.
 __global__ __launch_bounds__(256) void expand_blocks_kernel(const int* __restrict__ blk_idx, const int* __restrict__ blk_budget,
                                                             int Hq, int blk_cap, int block, int N, int b_cap,
-                                                            int* __restrict__ kv_idx, int* __restrict__ budget) {
+                                                            int* __restrict__ kv_idx, int* __restrict__ budget,
+                                                            int last_tile, int* __restrict__ tile_map) {
   const int bh = blockIdx.y, b = bh / Hq;
   const int nb = min(blk_budget[b], blk_cap);
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (bh % Hq == 0 && t == 0) budget[b] = min(nb * block, b_cap);
+  if (tile_map && t % kTileN == 0 && t < blk_cap * block) {
+    const int at = t < nb * block ? min((blk_idx[(long long)bh * blk_cap + t / block] * block + t % block) / kTileN, last_tile) : 0;
+    tile_map[((long long)bh * blk_cap * block + t) / kTileN] = at;
+  }
   if (t >= nb * block || t >= b_cap) return;
   const int tok = blk_idx[(long long)bh * blk_cap + t / block] * block + t % block;
   kv_idx[(long long)bh * b_cap + t] = tok < N ? tok : kPadKeyIndex;
@@ -245,9 +251,9 @@ int run_block_scores(const Layer& L, int dtype, const void* Q, const void* K, in
 }
 
 int run_expand_blocks(const Layer& L, const int* blk_idx, const int* blk_budget, int blk_cap, int block, int* kv_idx,
-                      int* budget, int b_cap, hipStream_t st) {
+                      int* budget, int b_cap, hipStream_t st, int* tile_map, int last_tile) {
   hipLaunchKernelGGL(expand_blocks_kernel, dim3(cdiv((long long)blk_cap * block, 256LL), L.B * L.Hq), dim3(256), 0, st,
-                     blk_idx, blk_budget, L.Hq, blk_cap, block, L.N, b_cap, kv_idx, budget);
+                     blk_idx, blk_budget, L.Hq, blk_cap, block, L.N, b_cap, kv_idx, budget, last_tile, tile_map);
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }

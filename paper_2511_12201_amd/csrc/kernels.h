@@ -42,12 +42,31 @@ int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, f
 // pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values, and not both Kt and Vt in one call)
 // Kn, Vn, Qn, dOn in the order of a 32x32 MFMA's A operand, [32-row block][k step][lane] of 16 bytes (lane = 32 * half + row; a
 // k step is 16 bf16 or 8 fp32 values wide); fp32 without k_frag: Kn, Vn row by row
-int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
-                int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
-                void* Vt, int* kidx, hipStream_t st, bool k_frag = false);
-int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
-               const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
-               float* deltac, int* inv, hipStream_t st);
+struct PackKv {
+  const void *K, *V;
+  int per_q_head;                // a copy per query head of the listed rows, or per KV head of all rows
+  const int* src_idx;            // [.., idx_stride] token of a slot; null: the slot itself
+  int idx_stride;
+  const int* budget;             // null: N
+  int b_cap, npad, pad_to;       // rows of a head's copy; slots are filled up with zero rows to a multiple of pad_to
+  void *Kn, *Vn, *Kt, *Vt;
+  int k_frag;
+};
+struct PackQ {
+  const void *Q, *O, *dO;
+  const float* lse;
+  const int *q_idx, *q_cnt;
+  int nqpad;
+  void *Qt, *dOt, *Qn, *dOn;
+  float *lse2c, *deltac;
+};
+// What precedes an attention kernel, in one launch: any of the packs and the passes over the lists (sched.h); none may need
+// another's results.
+struct Bounds;
+struct Order;
+struct KeyList;
+int run_prepare(const Layer& L, int dtype, bool backward, const PackKv* kv, const PackQ* q, const Bounds* bn, const Order* od,
+                const KeyList* kl, hipStream_t st);
 
 // attn_fwd.hip
 // products of the dense attention of a layer: what the rules between kernels for short and long sequences look at
@@ -75,9 +94,6 @@ int run_attn_fwd(const Layer& L, int dtype, const void* Q, const void* K, const 
 
 // bf16 only, block % 64 == 0: the forward pass on block lists without a gathered copy of K/V per query head
 int attn_fwd_blocks_max_keys();
-// tile_map[bh, t] = tile of the KV head's token-ordered K/V copy that holds tile t of the head's block list
-int run_tile_map(const Layer& L, const int* blk_idx, const int* blk_budget, int blk_cap, int block, int last_tile,
-                 int* tile_map, hipStream_t st);
 size_t attn_fwd_blocks_ws(const Layer& L, int cap_keys);   // cap_keys = blk_cap * block
 int run_attn_fwd_blocks(const Layer& L, const void* Q, const void* K, const void* V, const int* q_idx, const int* q_cnt,
                         const int* blk_idx, const int* blk_budget, int blk_cap, int block, void* O, float* lse,
@@ -119,7 +135,7 @@ size_t block_scores_ws(const Layer& L, int block);
 int run_block_scores(const Layer& L, int dtype, const void* Q, const void* K, int block, float* out, void* ws,
                      hipStream_t st);
 int run_expand_blocks(const Layer& L, const int* blk_idx, const int* blk_budget, int blk_cap, int block, int* kv_idx,
-                      int* budget, int b_cap, hipStream_t st);
+                      int* budget, int b_cap, hipStream_t st, int* tile_map = nullptr, int last_tile = 0);
 
 // diag.hip
 int run_calibration_copy(const void* src, void* dst, size_t bytes, hipStream_t st);

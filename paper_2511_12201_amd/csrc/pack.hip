@@ -17,10 +17,19 @@
 // arrive with one 16-byte read.
 //
 // pack_q: for the backward pass, the kept rows of Q and dO in the k-packed
-// layout (contraction over queries) and in fragment order, plus per kept row lse * log2(e) and delta = rowsum(dO * O).  On the way every token's entry of the
-// key lists' slot map is set to "not listed".
+// layout (contraction over queries) and in fragment order, plus per kept row
+// lse * log2(e) and delta = rowsum(dO * O).
+//
+// Both, and the passes over the lists (sched_dev.h), are roles of one kernel: on short sequences a launch that does nothing
+// takes 4 us, as long as most of these passes, and on long ones the serial work-list blocks hide under the packs.  Launches
+// before -> now and the whole call in us: one-call prefill of 1072 tokens 12 -> 11, 87.5 -> 84.4; fp32 forward and backward,
+// 1024 tokens, 9 -> 6, 87 -> 75; two clips of 3101 at d = 64, 10 -> 7, 178 -> 168; forward of 16391 tokens 4 -> 3, 430 ->
+// 427; blocks at 16k, forward and backward, 24 -> 18, 3044 -> 3001.
 #include "common.h"
 #include "kernels.h"
+#include "sched_dev.h"
+
+#include <algorithm>
 
 namespace omni {
 
@@ -101,30 +110,34 @@ __device__ __forceinline__ void transpose4x4_store(const u32x4 (&in)[4], float* 
 // bytes to 64 lines at once / whole lines: for the forward 16391 46.9 / 39.4 us, 32768 91 / 72 us (253 MB written: 3.5
 // TB/s), for the backward 109 / 97 us, pack_q there 168 / 131 us.
 constexpr int kOutThreads = 128;
-template <typename T, int D>
-__global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void pack_kv_kernel(const T* __restrict__ K, const T* __restrict__ V, Layer L,
-                                                          int per_q_head, const int* __restrict__ src_idx,
-                                                          int idx_stride, const int* __restrict__ budget, int b_cap,
-                                                          int npad, int pad_to, T* __restrict__ Kn, T* __restrict__ Vn,
-                                                          T* __restrict__ Kt, T* __restrict__ Vt,
-                                                          int* __restrict__ kidx, int k_frag) {
+template <int WAVES>
+struct PackShared {                      // exchange areas of the wavefronts that write k-packed copies (bf16)
+  __attribute__((aligned(16))) unsigned char t[WAVES][8192];
+  int idx[64];
+};
+template <>
+struct PackShared<0> {
+  int idx[64];
+};
+template <typename T, int D, typename Shared>
+__device__ __forceinline__ void pack_kv_block(const Layer& L, const PackKv& p, int tile, int bhx, Shared& sh) {
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int E = Elem<T>::kPer16B;
   constexpr int CPR = D / E;
-  __shared__ int sIdx[kTileN];
-  __shared__ __attribute__((aligned(16))) unsigned char sT[kBf16 ? D / 64 : 1][kBf16 ? 8192 : 16];
-  const int tile = blockIdx.x, bhx = blockIdx.y;
+  const T *K = static_cast<const T*>(p.K), *V = static_cast<const T*>(p.V);
+  T *Kn = static_cast<T*>(p.Kn), *Vn = static_cast<T*>(p.Vn), *Kt = static_cast<T*>(p.Kt), *Vt = static_cast<T*>(p.Vt);
+  const int npad = p.npad, k_frag = p.k_frag, per_q_head = p.per_q_head;
+  int* sIdx = sh.idx;
   const int H = per_q_head ? L.Hq : L.Hkv;
   const int b = bhx / H, hx = bhx % H;
   const int g = per_q_head ? hx / L.G : hx;
-  const int nkeys = budget ? min(budget[per_q_head ? budget_slot(L.bph, b, bhx) : b], b_cap) : L.N;
-  if (tile * kTileN >= (int)align_up((size_t)max(nkeys, 0), (size_t)pad_to)) return;   // consumers read whole pad_to-slot groups
+  const int nkeys = p.budget ? min(p.budget[per_q_head ? budget_slot(L.bph, b, bhx) : b], p.b_cap) : L.N;
+  if (tile * kTileN >= (int)align_up((size_t)max(nkeys, 0), (size_t)p.pad_to)) return;   // consumers read whole pad_to-slot groups
   if (threadIdx.x < kTileN) {
-    const int p = tile * kTileN + threadIdx.x;
+    const int slot = tile * kTileN + threadIdx.x;
     int id = kPadKeyIndex;
-    if (p < nkeys) id = src_idx ? src_idx[(long long)bhx * idx_stride + p] : p;
+    if (slot < nkeys) id = p.src_idx ? p.src_idx[(long long)bhx * p.idx_stride + slot] : slot;
     sIdx[threadIdx.x] = id;
-    kidx[(long long)bhx * npad + p] = id;
   }
   __syncthreads();
   const T* kbase = K + b * L.ks[0] + g * L.ks[1];
@@ -166,7 +179,7 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
 #pragma unroll
         for (int j = 0; j < 8; ++j) in[j] = bf16x8_to_f16x8(in[j]);
       }
-      transpose8x8_store(in, reinterpret_cast<u16*>(dst) + tile_off + t / 64 * 4096, sT[t / 64]);
+      transpose8x8_store(in, reinterpret_cast<u16*>(dst) + tile_off + t / 64 * 4096, sh.t[t / 64]);
     };
     if (Kn && unit-- == 0) copy(kbase, Kn);
     if (Vn && unit-- == 0) copy(vbase, Vn);
@@ -203,33 +216,24 @@ __global__ __launch_bounds__(sizeof(T) == 2 ? 4 * kOutThreads : kThreads) void p
   }
 }
 
-// grid: (ceil(N/64), B*Hq).  Tile t covers kept positions [64 t, 64 t + 64).
+// Tile t covers kept positions [64 t, 64 t + 64).
 // bf16: the wavefronts past the first four write the k-packed copies meanwhile, D threads each.
-template <typename T, int D>
-constexpr int kPackQThreads = kThreads + (sizeof(T) == 2 ? 2 * D : 0);
-template <typename T, int D>
-__global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* __restrict__ Q, const T* __restrict__ O,
-                                                         const T* __restrict__ dO, const float* __restrict__ lse,
-                                                         Layer L, const int* __restrict__ q_idx,
-                                                         const int* __restrict__ q_cnt, int nqpad,
-                                                         T* __restrict__ Qt, T* __restrict__ dOt,
-                                                         T* __restrict__ Qn, T* __restrict__ dOn,
-                                                         float* __restrict__ lse2c, float* __restrict__ deltac,
-                                                         int* __restrict__ inv) {
+template <typename T, int D, typename Shared>
+__device__ __forceinline__ void pack_q_block(const Layer& L, const PackQ& p, int tile, int bh, Shared& sh) {
+  const T *Q = static_cast<const T*>(p.Q), *O = static_cast<const T*>(p.O), *dO = static_cast<const T*>(p.dO);
+  T *Qt = static_cast<T*>(p.Qt), *dOt = static_cast<T*>(p.dOt), *Qn = static_cast<T*>(p.Qn), *dOn = static_cast<T*>(p.dOn);
+  const int nqpad = p.nqpad;
+  int* sIdx = sh.idx;
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int E = Elem<T>::kPer16B;
   constexpr int LPR = D / E;
   constexpr int RPP = kThreads / LPR;
-  __shared__ int sIdx[64];
-  __shared__ __attribute__((aligned(16))) unsigned char sT[kBf16 ? 2 * D / 64 : 1][kBf16 ? 8192 : 16];
-  const int tile = blockIdx.x, bh = blockIdx.y;
   const int b = bh / L.Hq, i = bh % L.Hq;
-  const int nq = q_cnt[bh];
-  if (threadIdx.x < 64 && tile * 64 + (int)threadIdx.x < L.N) inv[(long long)bh * L.N + tile * 64 + threadIdx.x] = -1;
+  const int nq = p.q_cnt[bh];
   if (tile * 64 >= nq) return;
   if (threadIdx.x < 64) {
-    const int p = tile * 64 + threadIdx.x;
-    sIdx[threadIdx.x] = p < nq ? q_idx[(long long)bh * L.N + p] : -1;
+    const int pos = tile * 64 + threadIdx.x;
+    sIdx[threadIdx.x] = pos < nq ? p.q_idx[(long long)bh * L.N + pos] : -1;
   }
   __syncthreads();
   const long long head_off = b * L.qs[0] + i * L.qs[1];
@@ -263,11 +267,11 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
       const long long o = (long long)bh * nqpad + tile * 64 + r;
       float l2 = INFINITY;
       if (row >= 0) {
-        const float lv = lse[(long long)bh * L.N + row];
+        const float lv = p.lse[(long long)bh * L.N + row];
         l2 = lv == -INFINITY ? INFINITY : lv * kLog2e;
       }
-      lse2c[o] = l2;
-      deltac[o] = row >= 0 ? dot : 0.f;
+      p.lse2c[o] = l2;
+      p.deltac[o] = row >= 0 ? dot : 0.f;
     }
   }
   }
@@ -289,7 +293,7 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
         in[j] = zero;
         if (row >= 0) in[j] = *reinterpret_cast<const u32x4*>(src + (long long)row * L.qs[2] + dc * 8);
       }
-      transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + it / 64 * 4096, sT[it0 / 64]);
+      transpose8x8_store(in, reinterpret_cast<u16*>(dst_t) + tile_off + it / 64 * 4096, sh.t[it0 / 64]);
     }
   } else {
     constexpr int kItems = (64 / 4) * (D / 4);
@@ -312,65 +316,87 @@ __global__ __launch_bounds__((kPackQThreads<T, D>)) void pack_q_kernel(const T* 
   }
 }
 
-template <typename T, int D>
-int launch_pack_kv(const Layer& L, const void* K, const void* V, int per_q_head, const int* src_idx, int idx_stride,
-                   const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt, void* Vt,
-                   int* kidx, hipStream_t st, int k_frag) {
-  const int heads = per_q_head ? L.Hq : L.Hkv;
-  ProfScope prof__(kProfPack, st);
-  if (sizeof(T) == 2 && Kt && Vt) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "pack: one k-packed copy at a time");   // they share sT
-  const int outputs = (Kn != nullptr) + (Vn != nullptr) + (Kt != nullptr) + (Vt != nullptr);
-  const int threads = sizeof(T) == 2 ? kOutThreads * outputs : kThreads;
-  hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kTileN, L.B * heads), dim3(threads), 0, st,
-                     static_cast<const T*>(K), static_cast<const T*>(V), L, per_q_head, src_idx, idx_stride, budget, b_cap,
-                     npad, pad_to, static_cast<T*>(Kn), static_cast<T*>(Vn), static_cast<T*>(Kt), static_cast<T*>(Vt), kidx,
-                     k_frag);
+// grid: the blocks of the roles one after the other, those that take longest first
+struct Roles {
+  int order, keys, bounds, q;            // blocks of each; the rest is K/V tiles
+  int bounds_x, q_x, kv_x;
+};
+template <typename T, int D, int NT, bool Q_ROLE>
+__global__ __launch_bounds__(NT) void prepare_kernel(Layer L, Roles r, PackKv kv, PackQ q, Bounds bn, Order od, KeyList kl) {
+  constexpr int kWaves = sizeof(T) == 4 ? 0 : Q_ROLE ? 2 * D / 64 : D / 64;       // Q and dO at once, or V
+  __shared__ union {
+    PackShared<kWaves> pack;
+    OrderShared<NT> order;
+    int wave_cnt[NT / 64];
+  } sh;
+  int i = blockIdx.x;
+  if (i < r.order) return order_block<NT>(od, i, sh.order);
+  i -= r.order;
+  if (i < r.keys) return key_list_block<NT>(L, kl, sh.wave_cnt);
+  i -= r.keys;
+  const int BH = L.B * L.Hq;
+  if (i < r.bounds) return bounds_block<NT>(L, bn, i % r.bounds_x, i / r.bounds_x % BH, i / r.bounds_x / BH);
+  i -= r.bounds;
+  if constexpr (Q_ROLE) {
+    if (i < r.q) return pack_q_block<T, D>(L, q, i % r.q_x, i / r.q_x, sh.pack);
+    i -= r.q;
+  }
+  pack_kv_block<T, D>(L, kv, i % r.kv_x, i / r.kv_x, sh.pack);
+}
+
+template <typename T, int D, int NT, bool Q_ROLE>
+int launch_prepare(const Layer& L, const PackKv* kv, const PackQ* q, const Bounds* bn, const Order* od, const KeyList* kl,
+                   hipStream_t st) {
+  Roles r{};
+  const int BH = L.B * L.Hq;
+  if (od) r.order = (int)cdiv(sched_cap(od->BH, od->N, od->tile_m), (size_t)(NT / kRankLanes));
+  r.keys = kl ? 1 : 0;
+  if (bn) {
+    r.bounds_x = cdiv(bn->kfirst ? std::max(L.N, bn->npad) : L.N, NT);
+    r.bounds = r.bounds_x * BH * (bn->kfirst ? 3 : bn->X ? 2 : 1);
+  }
+  if (q) {
+    r.q_x = q->nqpad / 64;
+    r.q = r.q_x * BH;
+  }
+  long long blocks = (long long)r.order + r.keys + r.bounds + r.q;
+  if (kv) {
+    const int outputs = (kv->Kn != nullptr) + (kv->Vn != nullptr) + (kv->Kt != nullptr) + (kv->Vt != nullptr);
+    if (sizeof(T) == 2 && (outputs * kOutThreads > NT || (kv->Kt && kv->Vt)))
+      OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "pack: more copies than the workgroup has room for");
+    r.kv_x = kv->npad / kTileN;
+    blocks += (long long)r.kv_x * L.B * (kv->per_q_head ? L.Hq : L.Hkv);
+  }
+  if (blocks >= 0xffffffffll / NT) OMNI_FAIL(OMNI_ERR_UNSUPPORTED, "pack: too many tiles");
+  ProfScope prof__(kv || q ? kProfPack : kProfClear, st);
+  hipLaunchKernelGGL((prepare_kernel<T, D, NT, Q_ROLE>), dim3((unsigned)blocks), dim3(NT), 0, st, L, r, kv ? *kv : PackKv{},
+                     q ? *q : PackQ{}, bn ? *bn : Bounds{}, od ? *od : Order{}, kl ? *kl : KeyList{});
   OMNI_LAUNCH_CHECK();
   return OMNI_OK;
 }
 
+// Threads of a workgroup: what the tiles' copies need side by side.
 template <typename T, int D>
-int launch_pack_q(const Layer& L, const void* Q, const void* O, const void* dO, const float* lse, const int* q_idx,
-                  const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c, float* deltac,
-                  int* inv, hipStream_t st) {
-  hipLaunchKernelGGL((pack_q_kernel<T, D>), dim3(nqpad / 64, L.B * L.Hq), dim3(kPackQThreads<T, D>), 0, st,
-                     static_cast<const T*>(Q), static_cast<const T*>(O), static_cast<const T*>(dO), lse, L, q_idx,
-                     q_cnt, nqpad, static_cast<T*>(Qt), static_cast<T*>(dOt), static_cast<T*>(Qn), static_cast<T*>(dOn),
-                     lse2c, deltac, inv);
-  OMNI_LAUNCH_CHECK();
-  return OMNI_OK;
+int launch_prepare(const Layer& L, const PackKv* kv, const PackQ* q, const Bounds* bn, const Order* od, const KeyList* kl,
+                   bool backward, hipStream_t st) {
+  if constexpr (sizeof(T) == 2) {
+    if (backward) return launch_prepare<T, D, kThreads + 2 * D, true>(L, kv, q, bn, od, kl, st);
+  } else if (backward) {
+    return launch_prepare<T, D, kThreads, true>(L, kv, q, bn, od, kl, st);
+  }
+  return launch_prepare<T, D, kThreads, false>(L, kv, q, bn, od, kl, st);
 }
 
 }  // namespace
 
-int run_pack_kv(const Layer& L, int dtype, const void* K, const void* V, int per_q_head, const int* src_idx,
-                int idx_stride, const int* budget, int b_cap, int npad, int pad_to, void* Kn, void* Vn, void* Kt,
-                void* Vt, int* kidx, hipStream_t st, bool k_frag) {
+int run_prepare(const Layer& L, int dtype, bool backward, const PackKv* kv, const PackQ* q, const Bounds* bn, const Order* od,
+                const KeyList* kl, hipStream_t st) {
   if (dtype == OMNI_BF16) {
-    if (L.D == 128)
-      return launch_pack_kv<u16, 128>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn, Kt,
-                                      Vt, kidx, st, k_frag);
-    return launch_pack_kv<u16, 64>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn, Kt, Vt,
-                                   kidx, st, k_frag);
+    if (L.D == 128) return launch_prepare<u16, 128>(L, kv, q, bn, od, kl, backward, st);
+    return launch_prepare<u16, 64>(L, kv, q, bn, od, kl, backward, st);
   }
-  if (L.D == 128)
-    return launch_pack_kv<float, 128>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                      Kt, Vt, kidx, st, k_frag);
-  return launch_pack_kv<float, 64>(L, K, V, per_q_head, src_idx, idx_stride, budget, b_cap, npad, pad_to, Kn, Vn,
-                                   Kt, Vt, kidx, st, k_frag);
-}
-
-int run_pack_q(const Layer& L, int dtype, const void* Q, const void* O, const void* dO, const float* lse,
-               const int* q_idx, const int* q_cnt, int nqpad, void* Qt, void* dOt, void* Qn, void* dOn, float* lse2c,
-               float* deltac, int* inv, hipStream_t st) {
-  if (dtype == OMNI_BF16) {
-    if (L.D == 128)
-      return launch_pack_q<u16, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
-    return launch_pack_q<u16, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
-  }
-  if (L.D == 128)
-    return launch_pack_q<float, 128>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
-  return launch_pack_q<float, 64>(L, Q, O, dO, lse, q_idx, q_cnt, nqpad, Qt, dOt, Qn, dOn, lse2c, deltac, inv, st);
+  if (L.D == 128) return launch_prepare<float, 128>(L, kv, q, bn, od, kl, backward, st);
+  return launch_prepare<float, 64>(L, kv, q, bn, od, kl, backward, st);
 }
 
 }  // namespace omni

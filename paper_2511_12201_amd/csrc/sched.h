@@ -50,7 +50,7 @@ struct Bounds {
   int b_cap, npad;
   int* qvis;                     // [B*Hq, N] number of listed keys that kept query `pos` may see
   int* kfirst;                   // [B*Hq, npad] first kept-query position that may see listed key `slot` (needs inv and X)
-  int* inv;                      // [B*Hq, N] slot of the token in the key list (listed tokens only)
+  int* inv;                      // [B*Hq, N] slot of the token in the key list (listed tokens; the others are not written)
   void* X;                       // nullable (then lse is not written either): rows of the Q-shaped tensor (16-byte aligned)
                                  // that are not kept are set to zero
   int elem_bytes;
@@ -59,11 +59,41 @@ struct Bounds {
   int* sched;                    // the items of the work list and their costs (not their order)
 };
 int check_work_list(const Layer& L, int tile_m);     // the items' fields are 16 bits wide: error if they do not fit
-int run_bounds(const Layer& L, const Bounds& p, hipStream_t st);
 
 // The order of the work list from its items: queues = 1 (one longest-first list) or kSchedQueues (one list per XCD, whole
-// heads per queue, where that pays).  run_schedule forms the items too, with costs estimated from the tile's position.
-int run_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, hipStream_t st, int queues = 1);
+// heads per queue, where that pays).
+struct Order {
+  const int* q_cnt;              // [BH], null: N each
+  int BH, N, tile_m, queues;
+  int workgroups;                // one per CU
+  size_t order_off;
+  int* sched;
+};
+Order make_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, int queues = 1);
+
+// The work list of the bf16 key kernel of the backward (attn_bwd.hip): (head, key tile, split) in dispatch order.
+constexpr int kKeyTile = 256;                // packed keys per workgroup
+constexpr int kKeyQ = 64;                    // queries per tile, as the splits count them
+constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, -
+struct KeyList {
+  const int *q_cnt, *budget;
+  int b_cap, npad;
+  const int* kfirst;             // [B*Hq, npad], as in Bounds
+  int head_group;                // heads per dispatch group
+  int nsplit, split_len;         // most workgroups that share the query tiles of a key tile, tiles per split at most
+  int key_wgs;                   // workgroups that share the items
+  int n_slots;
+  int* klist;
+};
+// A key tile seen by many query tiles (the first tiles of a head that keeps every query: 512 query tiles at 32k,
+// against a few dozen for most workgroups) is shared by several workgroups, each with a contiguous range of the
+// query tiles and a partial-gradient plane of its own; the group reduction adds the planes in split order.
+__host__ __device__ inline int key_tile_splits(int n_qtiles, int max_splits, int split_len) {
+  const int s = n_qtiles / split_len;
+  return s < 1 ? 1 : (s > max_splits ? max_splits : s);
+}
+
+// Forms the items with costs estimated from the tile's position, and their order (the dense baseline).
 int run_schedule(const Layer& L, const int* q_cnt, const int* budget, int b_cap, int tile_m, int* sched, hipStream_t st);
 int persistent_grid();      // workgroups that fill the device at two per CU
 

@@ -296,3 +296,33 @@ def test_key_gradients_when_a_few_long_key_tiles_are_split(kept):
     rss = oc.sparse_attn_bwd_term_rss(*args, O=to_host(O))
     for x, w, r in zip(got, want, rss):
         assert np.all(np.abs(to_host(x) - w) <= grad_bar(w, "bf16", r))
+
+
+@pytest.mark.usefixtures("attention_route")
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("N", [64, 65, 300])
+def test_what_the_scratch_held_before_does_not_show(N, dtype, d):
+    """The slot map is written for listed tokens only: whatever the scratch says of the others, slots in range among it, their
+    gradients are zero and all others the same to the last bit."""
+    rng = np.random.default_rng(N)
+    q_lists, kv_lists = _lists(rng, 4, N)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    rand = lambda h, s=1.0: to_device((s * torch.randn(1, h, N, d, generator=g, device="cuda")).cpu().numpy(), dtype)  # noqa: E731
+    Q, K, V, dO = rand(4), rand(2), rand(2), rand(4, d ** -0.5)
+    desc = ob.make_layer_desc(Q, K, 0, N, 0, True)
+    q_idx, q_cnt = lists_to_padded(q_lists, 4, N)
+    kv_idx, budget = lists_to_padded(kv_lists, 4, N)
+    lists, results = (q_idx, q_cnt, kv_idx, budget, N), []
+    for fill in (0, 1, -1, None):
+        ws = ob.Workspace()
+        for call in (ob.CALL_SPARSE_ATTN_FWD, ob.CALL_SPARSE_ATTN_BWD):
+            words = ws.get(call, desc, N)
+            words = words[:words.numel() // 4 * 4].view(torch.int32)
+            words.copy_(torch.arange(len(words), device="cuda") % N if fill is None else torch.full_like(words, fill))
+        O, lse = ob.omni_sparse_attn_fwd_per_head(desc, Q, K, V, *lists, ws=ws)
+        results.append((O, lse, *ob.omni_sparse_attn_bwd_per_head(desc, Q, K, V, O, dO, lse, *lists, ws=ws)))
+    for other in results[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(results[0], other))
+    for group, x in ((g, x) for x in results[0][3:] for g in range(2)):
+        unlisted = np.setdiff1d(np.arange(N), np.concatenate(kv_lists[0][2 * group:2 * group + 2]))
+        assert not x[0, group, torch.from_numpy(unlisted).cuda()].any()
