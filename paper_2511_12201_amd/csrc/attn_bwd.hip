@@ -17,7 +17,7 @@
 //    each with a partial plane of its own.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
-// fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_key_f32_kernel (dK' and dV' of 32 keys together) and attn_bwd_dq_f32_kernel;
+// fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_f32_kernel (blocks for dK' and dV' of 32 keys, and for dQ);
 // on long sequences attn_bwd_key_f32_long_kernel (128 keys) and attn_bwd_dq_f32_long_kernel (128 queries of the work list).
 #include <algorithm>
 
@@ -158,15 +158,14 @@ __device__ __forceinline__ void add_product_rows(f32x16 (&acc)[D / 32], const f3
       acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r >> 2][db][r & 3], x[r], acc[db], 0, 0, 0);
 }
 
-// grid: npad / 32 * nsplit * B*Hq, heads fastest; the first keys, which the most queries see, first.  dK', dV' of 32 listed
-// keys, or of the share of the queries that a split of their 256-key tile takes (as in the bf16 kernels).
+// Block `block` of npad / 32 * nsplit * B*Hq, heads fastest; the first keys, which the most queries see, first.  dK', dV' of 32
+// listed keys, or of the share of the queries that a split of their 256-key tile takes (as in the bf16 kernel).
 template <int D>
-__global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_key_f32_kernel(BwdParams p) {
+__device__ __forceinline__ void key_f32_block(const BwdParams& p, int block, float (*sO)[32][D + 4]) {
   constexpr int NB = D / 32;
-  __shared__ __attribute__((aligned(16))) float sO[kF32Waves<D>][32][D + 4];
   const Layer& L = p.L;
-  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, sp = (int)(blockIdx.x / BH) % p.nsplit, b = bh / L.Hq;
-  const int slot0 = (int)(blockIdx.x / BH) / p.nsplit * 32;
+  const int BH = L.B * L.Hq, bh = block % BH, sp = block / BH % p.nsplit, b = bh / L.Hq;
+  const int slot0 = block / BH / p.nsplit * 32;
   const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
   if (slot0 >= nkeys) return;
   const int nq = p.q_cnt[bh];
@@ -217,15 +216,14 @@ __global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_key_f32_kernel(Bwd
   merge_waves<D>(sO, dv, 1.f, [&](int row, int d, const f32x4& x) { *reinterpret_cast<f32x4*>(dvp + row * D + d) = x; });
 }
 
-// grid: cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first.  dQ of 32 kept queries.
+// Block `block` of cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first.  dQ of 32 kept queries.
 template <int D>
-__global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_dq_f32_kernel(BwdParams p) {
+__device__ __forceinline__ void dq_f32_block(const BwdParams& p, int block, float (*sO)[32][D + 4]) {
   constexpr int NB = D / 32;
-  __shared__ __attribute__((aligned(16))) float sO[kF32Waves<D>][32][D + 4];
   const Layer& L = p.L;
-  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq;
+  const int BH = L.B * L.Hq, bh = block % BH, b = bh / L.Hq, i = bh % L.Hq;
   const int nq = p.q_cnt[bh];
-  const int tq = cdiv(nq, 32) - 1 - (int)(blockIdx.x / BH);
+  const int tq = cdiv(nq, 32) - 1 - block / BH;
   if (tq < 0) return;
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int ln = lane & 31, h = lane >> 5;
@@ -263,6 +261,15 @@ __global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_dq_f32_kernel(BwdP
   merge_waves<D>(sO, dq, L.scale, [&](int row, int d, const f32x4& x) {
     if (tq * 32 + row < nq) *reinterpret_cast<f32x4*>(head + (long long)qlist[tq * 32 + row] * L.qs[2] + d) = x;
   });
+}
+
+// Both in one launch, key blocks first: neither fills the chip on the sequences that come here (1024 tokens, 2 heads, d = 64: 19
+// and 20 us one after the other), and neither needs the other.
+template <int D>
+__global__ __launch_bounds__(kF32Threads<D>, 1) void attn_bwd_f32_kernel(BwdParams p, int key_blocks) {
+  __shared__ __attribute__((aligned(16))) float sO[kF32Waves<D>][32][D + 4];
+  if ((int)blockIdx.x < key_blocks) return key_f32_block<D>(p, blockIdx.x, sO);
+  dq_f32_block<D>(p, (int)blockIdx.x - key_blocks, sO);
 }
 
 // fp32, long sequences (f32_short): workgroups of 128 keys, or of 128 kept queries from the work list, 32 per wavefront;
@@ -1333,9 +1340,10 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     if constexpr (sizeof(T) == 2) {
       hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, BLOCKS>), dim3((unsigned)persistent_grid() / 2), dim3(kKeyThreads), 0, st, p);
     } else {
+      const unsigned heads = (unsigned)(L.B * L.Hq), key_blocks = heads * (unsigned)(npad / 32) * kKeyMaxSplits;
       if (split)
-        hipLaunchKernelGGL((attn_bwd_key_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)(npad / 32) * kKeyMaxSplits),
-                           dim3(kF32Threads<D>), 0, st, p);
+        hipLaunchKernelGGL((attn_bwd_f32_kernel<D>), dim3(key_blocks + heads * (unsigned)cdiv(L.N, 32)), dim3(kF32Threads<D>), 0, st,
+                           p, (int)key_blocks);
       else
         hipLaunchKernelGGL((attn_bwd_key_f32_long_kernel<D>), dim3(npad / kF32Keys, L.B * L.Hq), dim3(kThreads), 0, st, p);
     }
@@ -1349,10 +1357,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
                            dim3(kSplitThreads), 0, st, p);
       else
         hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
-    } else if (split) {
-      hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)), dim3(kF32Threads<D>),
-                         0, st, p);
-    } else {
+    } else if (!split) {
       hipLaunchKernelGGL((attn_bwd_dq_f32_long_kernel<D>), dim3(persistent_grid() / 2), dim3(kThreads), 0, st, p);
     }
     OMNI_LAUNCH_CHECK();
