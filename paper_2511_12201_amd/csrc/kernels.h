@@ -21,8 +21,8 @@ int run_select_kv(const Layer& L, const float* key_scores, const int* budget, in
 size_t budget_stats_ws(const Layer& L);
 int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, int budget_mode, double* kurt,
                      int* flattest, int* budget, float* recall, void* ws, hipStream_t st);
-// Both lists of a prefill step from the two score arrays: statistics of the key scores, the cuts, the lists (three
-// launches).
+// Both lists of a prefill step from the two score arrays: statistics of the key scores, the cuts and lists (two
+// launches, or three).
 size_t select_lists_ws(const Layer& L);
 int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int q_mode, float q_param, int* q_idx,
                      int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,

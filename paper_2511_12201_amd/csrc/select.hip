@@ -22,9 +22,6 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kChunk = 1024;            // elements per compaction workgroup
-constexpr int kChunkThreads = 256;
-constexpr int kPerThread = kChunk / kChunkThreads;
 constexpr double kFixScale = 1099511627776.0;   // 2^40
 
 // a * 2^40 rounded towards zero, 0 for what is not positive, exact: the integer part of a * 2^8 and its fraction times
@@ -38,30 +35,31 @@ __device__ __forceinline__ float key_value(unsigned key) {         // inverse of
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-// One workgroup finds a cut in a vector of any length: digits of 11, 11 and 10 bits from the top, a histogram pass each.
-// Only the first pass looks at the whole vector; the elements of the bin it picks (a quarter octave: a few percent of a
-// head's scores) are copied to LDS, and once no more than kFew are left they are ranked against each other.  On short
-// vectors the chain of barriers, scans and memory latencies bounds it, on long ones a CU's vector ALU walking the vector,
-// so sweeps are what is saved; one loop serves all passes, over the vector or the list alike, because the code is fetched
-// anew by every CU.  28 heads, kurtosis + budget + cuts of both lists, as four passes of 8 bits over the whole vector and
-// kernels of their own for arg-min, counts and scans (nine launches) -> score_stats_kernel + list_cut_kernel:
-// 1k scores 53 -> 24 us, 32k 105 -> 38 us, 64k 150 -> 83 us.
+// One workgroup finds a cut in a vector of any length: histograms of 2048 bins over an interval of keys that shrinks to the
+// bin of the cut, pass by pass.  The first interval is that of a sample (vectors in LDS: of all elements), the two end bins
+// taking what lies outside: scores fill a few octaves, and bins of a fixed quarter octave put a third of a head's elements
+// on one address of the histogram, which then takes them one after the other.  Only the first pass looks at the whole
+// vector; the elements of the bin it picks are copied to LDS, and once no more than kFew are left they are ranked against
+// each other.  28 heads, kurtosis + budget + cuts of both lists, as four passes of 8 bits over the whole vector and
+// kernels of their own for arg-min, counts, scans and lists (nine launches) / digits of 11, 11 and 10 bits and a kernel for
+// the lists / now: 1k scores 53 / 28 / 21 us, 64k 150 / 95 / 77 us; the three calls on scores in hand at 32k 79 -> 59 us.
 constexpr int kBins = 2048;
 constexpr int kPitch = kBins + 8;       // words between two replicas of the count histogram: other banks for a bin's replicas
-constexpr int kRepCount = 8, kRepMass = 4;   // replicas of a bin, so that lanes on one bin rarely meet on an address
+constexpr int kReps = 4;                // replicas of a bin, so that lanes on one bin rarely meet on an address
 constexpr int kCand = 8192;
 constexpr int kFew = 64;                // elements that are ranked against each other instead of histogrammed
 struct __attribute__((aligned(16))) RadixShared {
   union {
-    unsigned cnt[kRepCount * kPitch];
-    unsigned long long sum[kRepMass * kPitch];
+    unsigned cnt[kReps * kPitch];
+    unsigned long long sum[kReps * kPitch];
   };
   float cand[kCand], few[kFew];
   unsigned few_key[kFew];
   unsigned long long few_mass[kFew];
   unsigned long long wave_tot[kSelWaves];
   unsigned long long rem;
-  unsigned key;
+  unsigned key, bin;
+  unsigned top, not_bottom;               // range of the sampled keys: the largest, and the complement of the smallest
   int count, found, alone;
 };
 
@@ -84,22 +82,82 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, Ra
   return t;
 }
 
-// The vector x[0, n), which may lie in LDS, by the whole workgroup: f(v) for every kBatch elements of a thread.  Past the
-// end the value is the NaN of key 0, below every score, which a histogram may count: a cut never gets down to it.
+// The vector x[0, n) by the whole workgroup: f(v) for every kBatch elements of a thread.  Past the end the value is the NaN of
+// key 0, below every score, which a histogram may count: a cut never gets down to it.
 constexpr int kBatch = 8;               // loads in flight per thread
 typedef float Batch[kBatch];
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));      // rows start at any multiple of four bytes
+// Element i of a head's vector: one 32-bit offset to a base in scalar registers (a vector is shorter than 2^29 elements).
+template <typename V = float>
+__device__ __forceinline__ V element(const float* __restrict__ row, int i) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(row) + (unsigned)i * 4u);
+}
+// In LDS or in memory, an element per load.  f's second argument: how many of the eight anybody has; the loops end there, because on
+// short vectors the fetch of the code, 0.4 us a kilobyte, is a good part of a kernel's time.
 template <typename F>
 __device__ __forceinline__ void sweep(const float* x, int n, F f) {
 #pragma unroll 1
   for (int at = 0; at < n; at += kBatch * kSelThreads) {
+    const int some = min(kBatch, cdiv(n - at, kSelThreads));
     Batch v;
 #pragma unroll
     for (int e = 0; e < kBatch; ++e) {
+      if (e >= some) break;
       const int o = at + e * kSelThreads + (int)threadIdx.x;
       const float t = x[min(o, n - 1)];
       v[e] = o < n ? t : __uint_as_float(0xffffffffu);
     }
-    f(v, n - at - (int)threadIdx.x);               // element e is a real one iff e * kSelThreads < the second argument
+    f(v, some);
+  }
+}
+// In memory: four neighbours per load, the next sixteen elements of a thread in flight under those in hand, nothing checked but in
+// the last stretch.  Bound by the vector ALU of the one CU (a few dozen instructions per 64 elements).
+template <typename F>
+__device__ __forceinline__ void sweep_memory(const float* __restrict__ x, int n, F f) {
+  constexpr int kLoads = 4, kStep = 4 * kLoads * kSelThreads;
+  f32x4_any next[kLoads];
+  auto load = [&](int at) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      next[u] = element<f32x4_any>(x, at + 4 * (u * kSelThreads + (int)threadIdx.x));
+  };
+  const int whole = n / kStep * kStep;
+  if (whole) load(0);
+#pragma unroll 1
+  for (int at = 0; at < whole; at += kStep) {
+    Batch v[2];
+#pragma unroll
+    for (int e = 0; e < 2 * kBatch; ++e) v[e / kBatch][e % kBatch] = next[e / 4][e % 4];
+    if (at + kStep < whole) load(at + kStep);
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      if (half) {
+#pragma unroll
+        for (int e = 0; e < kBatch; ++e) v[0][e] = v[1][e];
+      }
+      f(v[0], kBatch);
+    }
+  }
+  if (whole < n) sweep(x + whole, n - whole, f);
+}
+
+// Every element in memory, nothing in the place of those past the end.
+template <typename F>
+__device__ __forceinline__ void sweep_real(const float* __restrict__ x, int n, F f) {
+#pragma unroll 1
+  for (int at = 0; at < n; at += kBatch * kSelThreads) {
+    Batch v;
+    const int some = min(kBatch, cdiv(n - at, kSelThreads));
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) {
+      if (e >= some) break;
+      v[e] = element(x, min(at + e * kSelThreads + (int)threadIdx.x, n - 1));
+    }
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) {
+      if (e >= some) break;
+      if (at + e * kSelThreads + (int)threadIdx.x < n) f(v[e]);
+    }
   }
 }
 
@@ -115,10 +173,10 @@ __device__ __forceinline__ void histogram_add(RadixShared& sh, int rep, unsigned
   if (MASS) atomicAdd(&sh.sum[rep + digit], to_fixed(value));
   else atomicAdd(&sh.cnt[rep + digit], 1u);
 }
-// The bin at which the running total from the top reaches sh.rem: into sh.key (at `shift`), with sh.rem moved on to it.
+// The bin at which the running total from the top reaches sh.rem: into sh.bin, with sh.rem moved on to it.
 // Thread t owns the bins 2047 - 2t and 2046 - 2t.  False: the histogram falls short.
 template <bool MASS>
-__device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int shift) {
+__device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps) {
   __syncthreads();
   unsigned long long c0 = 0, c1 = 0;
   const int pair = kBins / 2 - 1 - (int)threadIdx.x;
@@ -142,69 +200,126 @@ __device__ __forceinline__ bool histogram_pick(RadixShared& sh, int reps, int sh
   if (excl < rem && rem <= incl) {                                   // one thread at most: its bins hold the crossing
     const bool second = excl + c0 < rem;
     sh.found = 1;
-    sh.key |= (unsigned)(kBins - 1 - 2 * (int)threadIdx.x - (second ? 1 : 0)) << shift;
+    sh.bin = (unsigned)(kBins - 1 - 2 * (int)threadIdx.x - (second ? 1 : 0));
     sh.rem = rem - excl - (second ? c0 : 0);
   }
   __syncthreads();
   return sh.found;
 }
 
+__device__ __forceinline__ unsigned wave_max_unsigned(unsigned v) {        // in lane 63
+  v = max(v, dpp_or_zero<0x111, 0xf>(v));
+  v = max(v, dpp_or_zero<0x112, 0xf>(v));
+  v = max(v, dpp_or_zero<0x114, 0xf>(v));
+  v = max(v, dpp_or_zero<0x118, 0xf>(v));
+  v = max(v, dpp_or_zero<0x142, 0xa>(v));
+  v = max(v, dpp_or_zero<0x143, 0xc>(v));
+  return v;
+}
+
 // Cut of the vector x[0, n) at `target`: a number of elements (MASS false) or a fixed-point mass (MASS true), largest
 // first.  target >= 1.  want_other: whether the cut's `other` is of use.
 template <bool MASS>
 __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, bool want_other, RadixShared& sh) {
-  constexpr int kRep = MASS ? kRepMass : kRepCount;
+  // short vectors go to LDS first: the passes over them are then free of memory latencies
+  constexpr int kEach = kCand / kSelThreads;
+  const bool staged = n <= kCand;
+  float sample[kEach];
+  if (staged) {
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+      if (e * kSelThreads >= n) break;
+      sample[e] = element(x, min(e * kSelThreads + (int)threadIdx.x, n - 1));
+    }
+  } else {
+    sample[0] = x[(long long)n * threadIdx.x / kSelThreads];
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    sh.key = 0;
     sh.rem = target;
+    sh.top = sh.not_bottom = 0u;
   }
-  const float* src = x;                            // the elements that can still be the cut are among these m
-  int m = n, reps = kRep, left = n;
-  unsigned fixed = 0;                              // bits of sh.key that are decided
+  unsigned lo = 0u, hi = 0xffffffffu;              // the cut's key is one of these
+  const float* src = staged ? sh.cand : x;         // the elements that can still be the cut are among these m
+  int m = n, reps = kReps, left = n;
   unsigned long long other = 0;
+  float top = 0.f;
 #pragma unroll 1
-  for (int pass = 0; pass < 3; ++pass) {
-    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-    const unsigned digit = pass == 2 ? 1023u : 2047u;
+  for (int pass = 0; pass < 4 && lo != hi; ++pass) {         // intervals of at most 2^32, 2^32, 2^21, 2^10 and one key
     histogram_clear<MASS>(sh, reps);
     if (threadIdx.x == 0) sh.count = 0;
     __syncthreads();
-    const unsigned before = sh.key;
-    const int rep = ((int)threadIdx.x & (reps - 1)) * kPitch;
-    float top = 0.f;
-    sweep(src, m, [&](const Batch& v, int) {
+    unsigned from = lo, range = hi - lo;           // the bins cover the keys from .. from + range, and more where that is free
+    if (pass == 0) {
+      unsigned mx = float_key(sample[0]), nmn = ~mx;
+      if (staged) {
 #pragma unroll
-      for (int e = 0; e < kBatch; ++e) {
-        const unsigned key = float_key(v[e]);
-        if (((key ^ before) & fixed) == 0) histogram_add<MASS>(sh, rep, (key >> shift) & digit, v[e]);
-        if (MASS) top = fmaxf(top, v[e]);
+        for (int e = 0; e < kEach; ++e) {
+          if (e * kSelThreads >= n) break;
+          const unsigned key = float_key(sample[e]);
+          mx = max(mx, key);
+          nmn = max(nmn, ~key);
+          if (e * kSelThreads + (int)threadIdx.x < n) sh.cand[e * kSelThreads + threadIdx.x] = sample[e];
+        }
       }
-    });
+      mx = wave_max_unsigned(mx);
+      nmn = wave_max_unsigned(nmn);
+      if (lane_id() == 63) {
+        atomicMax(&sh.top, mx);
+        atomicMax(&sh.not_bottom, nmn);
+      }
+      __syncthreads();
+      from = ~sh.not_bottom;
+      range = sh.top - from;
+    }
+    const int shift = max(0, 21 - __clz((int)range));                  // 32 - 11 significant bits
+    auto bin_of = [&](unsigned key) { return key <= from ? 0u : min((key - from) >> shift, (unsigned)kBins - 1); };
+    const int rep = ((int)threadIdx.x & (reps - 1)) * kPitch;
+    const bool first = pass == 0 && !staged;       // the whole vector, in memory
+    if (first) {
+      sweep_memory(x, n, [&](const Batch& v, int some) {
+#pragma unroll
+        for (int e = 0; e < kBatch; ++e) {
+          if (e >= some) break;
+          histogram_add<MASS>(sh, rep, bin_of(float_key(v[e])), v[e]);
+          if (MASS) top = fmaxf(top, v[e]);
+        }
+      });
+    } else {
+      sweep(src, m, [&](const Batch& v, int some) {
+#pragma unroll
+        for (int e = 0; e < kBatch; ++e) {
+          if (e >= some) break;
+          const unsigned key = float_key(v[e]);
+          if (key - lo <= hi - lo) histogram_add<MASS>(sh, rep, bin_of(key), v[e]);
+          if (MASS) top = fmaxf(top, v[e]);
+        }
+      });
+    }
     // infinite and huge elements: the sums may have left 64 bits
     if (MASS && (top >= 16777216.f || to_fixed(top) >= target)) sh.alone = 1;
-    const bool found = histogram_pick<MASS>(sh, reps, shift);
+    const bool found = histogram_pick<MASS>(sh, reps);
     if (MASS && sh.alone) return RadixCut{true, true, 0u, 0ull, 0ull};
     if (!found) return RadixCut{false, false, 0u, 0ull, 0ull};                                  // first pass only
     // What lies above the bin is taken whole, what lies in it is copied to LDS as far as it fits: the first time to the
     // long list, from there to the short one.
-    const unsigned cut = sh.key;
+    const unsigned bin = sh.bin;
+    const unsigned long long begin = (unsigned long long)from + ((unsigned long long)bin << shift), end = begin + (1ull << shift) - 1;
+    const unsigned before = hi, lo1 = bin == 0u ? lo : (unsigned)begin;
+    hi = bin == kBins - 1u || end > hi ? hi : (unsigned)end;
+    lo = lo1;
     float* list = src == sh.cand ? sh.few : sh.cand;
     const int cap = src == sh.cand ? kFew : kCand;
-    sweep(src, m, [&](const Batch& v, int) {
-      unsigned mine = 0, over = 0;
+    auto part = [&](const Batch& v, int some) {
+      unsigned mine = 0;
 #pragma unroll
       for (int e = 0; e < kBatch; ++e) {
-        const unsigned key = float_key(v[e]), a = key >> shift, c = cut >> shift;
-        const bool alive = ((key ^ before) & fixed) == 0;
-        mine |= alive && a == c ? 1u << e : 0u;
-        over |= alive && a > c ? 1u << e : 0u;
-      }
-      if (MASS) {
-        other += __popc(over);
-      } else if (want_other) {                     // a third of the sweep's instructions: both lists of 32k tokens 80 -> 78 us
-#pragma unroll
-        for (int e = 0; e < kBatch; ++e) other += over >> e & 1u ? to_fixed(v[e]) : 0ull;
+        if (e >= some) break;
+        const unsigned key = float_key(v[e]);
+        const bool over = key > hi && key <= before;
+        mine |= key - lo <= hi - lo ? 1u << e : 0u;
+        if (MASS) other += over;
+        else if (want_other) other += over ? to_fixed(v[e]) : 0ull;    // a third of the sweep's instructions
       }
       if (!__any(mine)) return;
       const unsigned n_mine = __popc(mine), incl = wave_scan(n_mine);
@@ -213,15 +328,17 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
       at = __builtin_amdgcn_readlane(at, 63) + (int)(incl - n_mine);
 #pragma unroll
       for (int e = 0; e < kBatch; ++e) {
+        if (e >= some) break;
         if (mine >> e & 1u) {
           if (at < cap) list[at] = v[e];
           ++at;
         }
       }
-    });
+    };
+    if (first) sweep_memory(x, n, part);
+    else sweep(src, m, part);
     __syncthreads();
     left = sh.count;
-    fixed = 0xffffffffu << shift;
     if (left <= cap) {
       src = list;
       m = left;
@@ -230,10 +347,11 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
     if (left <= kFew) break;
     __syncthreads();                               // sh.count is set again
   }
-  if (left <= kFew && fixed != 0xffffffffu) {
+  if (threadIdx.x == 0) sh.key = lo;
+  if (left <= kFew && lo != hi) {
     // Every element left against every other: the one whose own share crosses sh.rem is the cut (equal elements all
     // write the same values).
-    const float* few = src == sh.cand ? sh.cand : sh.few;
+    const float* few = src;                        // the short list, or the long one where that was enough
     const unsigned long long rem = sh.rem;
     __syncthreads();
     if ((int)threadIdx.x < left) {
@@ -282,20 +400,31 @@ struct KeepRule {
 struct ListJob {
   const float* x;        // [B*H, ld]
   KeepRule rule;
-  unsigned* thr;         // [B*H]
+  unsigned* thr;         // [B*H] the cut, from the kernel that finds it for the one that writes the list (long vectors)
   int* need;             // [B*H]
-  int* off_keep;         // [B*H, nchunk] exclusive counts of elements above the cut (or always kept), per chunk
-  int* off_eq;           // [B*H, nchunk] exclusive counts of elements at the cut
-  int* out;              // [B*H, out_stride]
+  int* off_keep;         // [B*H, nchunk] and the elements always taken, and those at the cut, before each chunk of kChunk
+  int* off_eq;           // elements
+  int* out;              // [B*H, out_stride], or null: no list
   int out_stride;
   int* total;            // [B*H] length of the list, or null
 };
+
+// Cut of a head's own budget, as the budget search leaves it: elements above `key` and `need` of those at it.
+// need < 0: not known (the whole vector, or one element that is infinite or beyond the fixed point).
+struct OwnCut {
+  unsigned key;
+  int need;
+};
+__device__ __forceinline__ float recall_of(unsigned long long mass, int N) {
+  return (float)((double)mass / kFixScale / (double)(float)N);
+}
 
 // How many elements each head of a job takes.
 struct KeySource {
   int mode;              // 0: budget of the flattest head, 1: largest budget of the heads, 2: the head's own (all from
                          // own[B*H] and kurt), 3: given counts (budget array), 4: top fraction of the visual range
   const int* own;        // [B*H] budget of every head's own scores
+  const OwnCut* cut;     // [B*H] and the cut that this budget makes, or null
   const double* kurt;    // [B*H]
   int* flattest;         // [B] out (modes 0..2)
   int* budget;           // [B] or [B*H] out (modes 0..2), in (mode 3)
@@ -341,7 +470,8 @@ __device__ __forceinline__ int flattest_head(const double* __restrict__ kurt, in
 // only_flattest: grid (1, B), the budget of every sequence's flattest head, after a launch of (H, B, 1) (see launch_stats).
 __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* __restrict__ a, Layer L, Ragged rg,
                                                                  double recall_p, int only_flattest,
-                                                                 double* __restrict__ kurt, int* __restrict__ own) {
+                                                                 double* __restrict__ kurt, int* __restrict__ own,
+                                                                 OwnCut* __restrict__ own_cut, float* __restrict__ recall) {
   __shared__ RadixShared sh;
   __shared__ double red[2][kSelWaves];
   const int b = blockIdx.y, head = only_flattest ? flattest_head(kurt + (long long)b * L.Hq, L.Hq) : (int)blockIdx.x;
@@ -354,22 +484,25 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
     const RadixCut cut = radix_cut<true>(x, N, target, true, sh);
     if (threadIdx.x == 0) {
       int r = N;                                // even the whole vector falls short: take everything
+      OwnCut oc = {0u, -1};
       if (cut.alone) {
         r = 1;
       } else if (cut.found) {
-        const unsigned long long v = to_fixed(key_value(cut.key));   // > 0: its bin crossed the target
-        r = max(1, (int)min((unsigned long long)N, cut.other + (cut.rem + v - 1) / v));
+        const unsigned long long v = to_fixed(key_value(cut.key)), q = (cut.rem + v - 1) / v;   // v > 0: its bin crossed the target
+        r = max(1, (int)min((unsigned long long)N, cut.other + q));
+        if (cut.other + q == (unsigned long long)r && r < N) {
+          oc = OwnCut{cut.key, (int)q};
+          if (recall) recall[bh] = recall_of(target - cut.rem + q * v, N);
+        }
       }
       own[bh] = r;
+      own_cut[bh] = oc;
     }
     return;
   }
   const int w = threadIdx.x >> 6;
   double s = 0.0;
-  sweep(x, N, [&](const Batch& v, int left) {
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) s += e * kSelThreads < left ? (double)v[e] : 0.0;
-  });
+  sweep_real(x, N, [&](float v) { s += (double)v; });
   s = wave_sum(s);
   if (lane_id() == 0) red[0][w] = s;
   __syncthreads();
@@ -378,14 +511,10 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
   for (int i = 0; i < kSelWaves; ++i) t += red[0][i];
   const double mu = t / (double)N;
   double s2 = 0.0, s4 = 0.0;
-  sweep(x, N, [&](const Batch& v, int left) {
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const double c = e * kSelThreads < left ? (double)v[e] - mu : 0.0;
-      const double c2 = c * c;
-      s2 += c2;
-      s4 += c2 * c2;
-    }
+  sweep_real(x, N, [&](float v) {
+    const double c = (double)v - mu, c2 = c * c;
+    s2 += c2;
+    s4 += c2 * c2;
   });
   s2 = wave_sum(s2);
   s4 = wave_sum(s4);
@@ -407,11 +536,150 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
   }
 }
 
+constexpr int kSpan = 8 * kSelThreads;   // elements of a vector whose list the workgroup that finds the cut writes itself
+struct ListShared {
+  int keep[kSelWaves], eq[kSelWaves];
+};
+// The list of a vector of at most kSpan elements, ascending: every wavefront holds up to 512 neighbours and ranks them by 64-bit
+// masks.
+__device__ __forceinline__ void short_list(const ListJob& job, const float* __restrict__ row, int h, int bh, int N, int v0, int v1,
+                                           unsigned thr, int need, ListShared& sh) {
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = lane_id();
+  const bool all = job.rule.keep_all_head0 && h == 0;
+  const int lo = all ? N : job.rule.visual_only ? v0 : 0, hi = all ? N : job.rule.visual_only ? v1 : N;
+  // elements outside [lo, hi) are always taken, those inside by the cut
+  const int blocks = cdiv(N, kSelThreads);                 // of 64 elements, for each wavefront
+  const int own = w * blocks * 64;
+  float v[kSpan / kSelThreads];
+#pragma unroll
+  for (int e = 0; e < kSpan / kSelThreads; ++e) {
+    if (e >= blocks) break;
+    v[e] = element(row, min(own + e * 64 + lane, N - 1));
+  }
+  // of the 64 elements from n0 on: those always taken, those at the cut
+  const bool plain = own >= lo && own + blocks * 64 <= hi;
+  auto masks = [&](int n0, float x, unsigned long long& above, unsigned long long& at_cut) {
+    const unsigned key = float_key(x);
+    if (plain) {
+      above = __ballot(key > thr);
+      at_cut = __ballot(key == thr);
+    } else {
+      const int n = n0 + lane;
+      const bool real = n < N, free = n < lo || n >= hi;
+      above = __ballot(real && (free || key > thr));
+      at_cut = __ballot(real && !free && key == thr);
+    }
+  };
+  int keep = 0, eq = 0;
+#pragma unroll
+  for (int e = 0; e < kSpan / kSelThreads; ++e) {
+    if (e >= blocks) break;
+    unsigned long long above, at_cut;
+    masks(own + e * 64, v[e], above, at_cut);
+    keep += (int)__popcll(above);
+    eq += (int)__popcll(at_cut);
+  }
+  if (lane == 0) {
+    sh.keep[w] = keep;
+    sh.eq[w] = eq;
+  }
+  __syncthreads();
+  int pk = 0, pe = 0, all_k = 0, all_e = 0;                // before this wavefront's elements, in all
+#pragma unroll
+  for (int i = 0; i < kSelWaves; ++i) {
+    const int k = sh.keep[i], e = sh.eq[i];
+    pk += i < w ? k : 0;
+    pe += i < w ? e : 0;
+    all_k += k;
+    all_e += e;
+  }
+  if (threadIdx.x == 0 && job.total) job.total[bh] = min(job.out_stride, all_k + min(all_e, need));
+  const auto below = [](unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+  };
+  int* dst = job.out + (long long)bh * job.out_stride;
+#pragma unroll
+  for (int e = 0; e < kSpan / kSelThreads; ++e) {
+    const int n0 = own + e * 64;
+    if (e >= blocks) break;
+    unsigned long long above, at_cut;
+    masks(n0, v[e], above, at_cut);
+    int pos = pk + below(above) + min(pe, need);
+    bool take = above >> lane & 1ull;
+    if (at_cut) {
+      const int q = pe + below(at_cut);
+      pos += min(q, need) - min(pe, need);
+      take = take || ((at_cut >> lane & 1ull) && q < need);
+    }
+    if (take && pos < job.out_stride) dst[pos] = n0 + lane;
+    pk += (int)__popcll(above);
+    pe += (int)__popcll(at_cut);
+  }
+}
+
+constexpr int kChunk = 1024;            // elements per workgroup of the list writer
+constexpr int kChunkThreads = 256;
+constexpr int kPerThread = kChunk / kChunkThreads;
+// Longer vectors: the counts before every chunk; a wavefront counts a chunk at a time.
+__device__ __forceinline__ void chunk_counts(const ListJob& job, const float* __restrict__ row, int h, int bh, int N, int stride,
+                                             int v0, int v1, unsigned thr, int need) {
+  const int lane = lane_id(), nchunk = cdiv(N, kChunk);
+  const bool all = job.rule.keep_all_head0 && h == 0;
+  const int lo = all ? N : job.rule.visual_only ? v0 : 0, hi = all ? N : job.rule.visual_only ? v1 : N;
+  int* ck = job.off_keep + (long long)bh * stride;
+  int* ce = job.off_eq + (long long)bh * stride;
+#pragma unroll 1
+  for (int c = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); c < nchunk; c += kSelWaves) {
+    float v[kChunk / 64];
+#pragma unroll
+    for (int e = 0; e < kChunk / 64; ++e) v[e] = element(row, min(c * kChunk + e * 64 + lane, N - 1));
+    unsigned above = 0, at_cut = 0;
+    if (c * kChunk >= lo && (c + 1) * kChunk <= hi) {
+#pragma unroll
+      for (int e = 0; e < kChunk / 64; ++e) {
+        const unsigned key = float_key(v[e]);
+        above += key > thr;
+        at_cut += key == thr;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < kChunk / 64; ++e) {
+        const int n = c * kChunk + e * 64 + lane;
+        const unsigned key = float_key(v[e]);
+        const bool real = n < N, free = n < lo || n >= hi;
+        above += real && (free || key > thr);
+        at_cut += real && !free && key == thr;
+      }
+    }
+    const unsigned both = wave_scan(above | at_cut << 16);
+    if (lane == 63) {
+      ck[c] = (int)(both & 0xffffu);
+      ce[c] = (int)(both >> 16);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  int run_k = 0, run_e = 0;
+  for (int c0 = 0; c0 < nchunk; c0 += 64) {
+    const int c = c0 + lane;
+    const unsigned vk = c < nchunk ? ck[c] : 0, ve = c < nchunk ? ce[c] : 0;
+    const unsigned sk = wave_scan(vk), se = wave_scan(ve);
+    if (c < nchunk) {
+      ck[c] = run_k + (int)(sk - vk);
+      ce[c] = run_e + (int)(se - ve);
+    }
+    run_k += __builtin_amdgcn_readlane((int)sk, 63);
+    run_e += __builtin_amdgcn_readlane((int)se, 63);
+  }
+  if (lane == 0 && job.total) job.total[bh] = min(job.out_stride, run_k + min(run_e, need));
+}
+
 // grid: (H, B, jobs).  Per head: how many elements to take, the cut (threshold key, number of cut-valued elements to
-// take), the recall, and how many elements of the list precede each chunk of kChunk elements.
+// take), the recall.  Vectors of one span: and the list, which a launch of its own (list_write_kernel) writes otherwise.
 __global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged rg, ListJob job0, KeySource src0,
                                                               ListJob job1, KeySource src1) {
   __shared__ RadixShared sh;
+  __shared__ ListShared lsh;
   __shared__ int k_sh;
   const ListJob& job = blockIdx.z ? job1 : job0;
   const KeySource& src = blockIdx.z ? src1 : src0;
@@ -455,14 +723,15 @@ __global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged r
     }
     const int n = hi - lo;
     unsigned long long mass = 0;
-    if ((job.rule.keep_all_head0 && h == 0) || k >= n) {
+    const bool known = src.mode <= 2 && src.cut && k == src.own[bh] && src.cut[bh].need >= 0;     // found by the search for the budget, with
+    if (known) {                                                                        // its recall
+      thr = src.cut[bh].key;
+      need = src.cut[bh].need;
+    } else if ((job.rule.keep_all_head0 && h == 0) || k >= n) {
       thr = 0u;
       if (src.recall) {
         unsigned long long local = 0;
-        sweep(row + lo, n, [&](const Batch& v, int) {
-#pragma unroll
-          for (int e = 0; e < kBatch; ++e) local += to_fixed(v[e]);
-        });
+        sweep_real(row + lo, n, [&](float v) { local += to_fixed(v); });
         mass = block_sum(local, sh);
       }
     } else if (k <= 0) {
@@ -473,61 +742,18 @@ __global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged r
       need = (int)cut.rem;
       mass = cut.other + cut.rem * to_fixed(key_value(cut.key));
     }
-    if (threadIdx.x == 0) {
-      job.thr[bh] = thr;
-      job.need[bh] = need;
-      if (src.recall) src.recall[bh] = (float)((double)mass / kFixScale / (double)(float)N);
-    }
+    if (threadIdx.x == 0 && src.recall && !known) src.recall[bh] = recall_of(mass, N);
   }
-  if (!job.off_keep) return;
-  // counts per chunk, then their exclusive scan; a wavefront counts one chunk
-  const int stride = cdiv(L.N, kChunk), nchunk = cdiv(N, kChunk);
-  int* ck = job.off_keep + (long long)bh * stride;
-  int* ce = job.off_eq + (long long)bh * stride;
-  for (int c = threadIdx.x >> 6; c < nchunk; c += kSelWaves) {
-    unsigned both = 0;                             // above the cut, at the cut << 16
-    float v[kChunk / 64];
-#pragma unroll
-    for (int e = 0; e < kChunk / 64; ++e) v[e] = row[min(c * kChunk + e * 64 + lane_id(), N - 1)];
-#pragma unroll
-    for (int e = 0; e < kChunk / 64; ++e) {
-      const int n = c * kChunk + e * 64 + lane_id();
-      bool al, eq;
-      classify(job.rule, h, n >= v0 && n < v1, v[e], thr, al, eq);
-      both += n < N ? (al ? 1u : 0u) + (eq ? 65536u : 0u) : 0u;
-    }
-    both = wave_scan(both);
-    if (lane_id() == 63) {
-      ck[c] = (int)(both & 0xffffu);
-      ce[c] = (int)(both >> 16);
-    }
+  if (!job.out) return;
+  if (L.N <= kSpan) {
+    short_list(job, row, h, bh, N, v0, v1, thr, need, lsh);
+    return;
   }
-  __syncthreads();
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  int run_k = 0, run_e = 0;
-  for (int c0 = 0; c0 < nchunk; c0 += 64) {
-    const int c = c0 + lane;
-    const int vk = c < nchunk ? ck[c] : 0;
-    const int ve = c < nchunk ? ce[c] : 0;
-    int sk = vk, se = ve;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int tk = __shfl_up(sk, o, 64);
-      const int te = __shfl_up(se, o, 64);
-      if (lane >= o) {
-        sk += tk;
-        se += te;
-      }
-    }
-    if (c < nchunk) {
-      ck[c] = run_k + sk - vk;
-      ce[c] = run_e + se - ve;
-    }
-    run_k += __shfl(sk, 63, 64);
-    run_e += __shfl(se, 63, 64);
+  if (threadIdx.x == 0) {
+    job.thr[bh] = thr;
+    job.need[bh] = need;
   }
-  if (lane == 0 && job.total) job.total[bh] = min(job.out_stride, run_k + min(run_e, need));
+  chunk_counts(job, row, h, bh, N, cdiv(L.N, kChunk), v0, v1, thr, need);
 }
 
 // grid: (nchunk, B*H, jobs).  Writes the kept indices of the chunk, ascending, at their global rank.
@@ -611,24 +837,23 @@ __global__ void visual_subset_kernel(const int* __restrict__ kv_idx, const int* 
   if (threadIdx.x == 0) vis_cnt[bh] = cnt;
 }
 
-struct SelWs {
+struct CutWs {
   unsigned* thr;
   int* need;
   int* cnt_keep;
   int* cnt_eq;
 };
-
-SelWs carve_select(Arena& a, const Layer& L) {
-  SelWs w;
-  const size_t BH = (size_t)L.B * L.Hq;
-  w.thr = a.take<unsigned>(BH);
-  w.need = a.take<int>(BH);
-  w.cnt_keep = a.take<int>(BH * cdiv(L.N, kChunk));
-  w.cnt_eq = a.take<int>(BH * cdiv(L.N, kChunk));
+CutWs carve_cut(Arena& a, const Layer& L) {
+  CutWs w;
+  w.thr = a.take<unsigned>((size_t)L.B * L.Hq);
+  w.need = a.take<int>((size_t)L.B * L.Hq);
+  const size_t chunks = L.N > kSpan ? (size_t)L.B * L.Hq * cdiv(L.N, kChunk) : 0;
+  w.cnt_keep = a.take<int>(chunks);
+  w.cnt_eq = a.take<int>(chunks);
   return w;
 }
 
-ListJob list_job(const SelWs& w, const float* x, const KeepRule& rule, int* out, int out_stride, int* total) {
+ListJob list_job(const CutWs& w, const float* x, const KeepRule& rule, int* out, int out_stride, int* total) {
   ListJob j;
   j.x = x;
   j.rule = rule;
@@ -642,7 +867,7 @@ ListJob list_job(const SelWs& w, const float* x, const KeepRule& rule, int* out,
   return j;
 }
 
-ListJob query_job(const Layer& L, const SelWs& w, const float* scores, int mode, float param, int* q_idx, int* q_cnt,
+ListJob query_job(const Layer& L, const CutWs& w, const float* scores, int mode, float param, int* q_idx, int* q_cnt,
                   KeySource* src) {
   KeepRule rule = {1, 1, mode != 0, 0u};
   if (mode == 0) {
@@ -658,17 +883,16 @@ ListJob query_job(const Layer& L, const SelWs& w, const float* scores, int mode,
 
 KeepRule key_rule() { return KeepRule{0, 0, 1, 0u}; }
 
-int launch_cut(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const KeySource& s0, const ListJob& j1,
-               const KeySource& s1, hipStream_t st) {
+// The cuts and the lists of one or two jobs: in one launch where a vector is short, else the lists in a launch of their own with a
+// workgroup per kChunk elements.  28 heads, both lists, one launch / two: 1072 scores 12.7 us / 16.3, 65536: 64 / 48.
+int launch_lists(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const KeySource& s0, const ListJob& j1,
+                 const KeySource& s1, hipStream_t st) {
   hipLaunchKernelGGL(list_cut_kernel, dim3(L.Hq, L.B, jobs), dim3(kSelThreads), 0, st, L, rg, j0, s0, j1, s1);
   OMNI_LAUNCH_CHECK();
-  return OMNI_OK;
-}
-
-int launch_write(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const ListJob& j1, hipStream_t st) {
-  hipLaunchKernelGGL(list_write_kernel, dim3(cdiv(L.N, kChunk), L.B * L.Hq, jobs), dim3(kChunkThreads), 0, st, L, rg, j0,
-                     j1);
-  OMNI_LAUNCH_CHECK();
+  if (L.N > kSpan && j0.out) {
+    hipLaunchKernelGGL(list_write_kernel, dim3(cdiv(L.N, kChunk), L.B * L.Hq, jobs), dim3(kChunkThreads), 0, st, L, rg, j0, j1);
+    OMNI_LAUNCH_CHECK();
+  }
   return OMNI_OK;
 }
 
@@ -678,21 +902,33 @@ int launch_write(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, 
 // 107.8 / 104.7, 32 240 / 220, 64 (2048 tokens) 362 / 305.
 constexpr int kBudgetHeads = 256;
 
+struct StatsWs {
+  int* own;
+  OwnCut* cut;
+};
+StatsWs carve_stats(Arena& a, const Layer& L) {
+  StatsWs w;
+  w.own = a.take<int>((size_t)L.B * L.Hq);
+  w.cut = a.take<OwnCut>((size_t)L.B * L.Hq);
+  return w;
+}
+
 // kurtosis and own budgets of all heads, and where the counts of the key lists come from
 int launch_stats(const Layer& L, const Ragged& rg, const float* key_scores, float recall_p, int budget_mode, double* kurt,
-                 int* own, int* flattest, int* budget, float* recall, int k_cap, KeySource* src, hipStream_t st) {
+                 const StatsWs& w, int* flattest, int* budget, float* recall, int k_cap, KeySource* src, hipStream_t st) {
   const bool after = budget_mode == 0 && L.B * L.Hq > kBudgetHeads;
   hipLaunchKernelGGL(score_stats_kernel, dim3(L.Hq, L.B, after ? 1 : 2), dim3(kSelThreads), 0, st, key_scores, L, rg,
-                     (double)recall_p, 0, kurt, own);
+                     (double)recall_p, 0, kurt, w.own, w.cut, recall);
   OMNI_LAUNCH_CHECK();
   if (after) {
     hipLaunchKernelGGL(score_stats_kernel, dim3(1, L.B), dim3(kSelThreads), 0, st, key_scores, L, rg, (double)recall_p, 1, kurt,
-                       own);
+                       w.own, w.cut, recall);
     OMNI_LAUNCH_CHECK();
   }
   *src = KeySource{};
   src->mode = budget_mode;
-  src->own = own;
+  src->own = w.own;
+  src->cut = after ? nullptr : w.cut;              // known for every head only where all were searched
   src->kurt = kurt;
   src->flattest = flattest;
   src->budget = budget;
@@ -705,7 +941,7 @@ int launch_stats(const Layer& L, const Ragged& rg, const float* key_scores, floa
 
 size_t select_ws(const Layer& L) {
   Arena a(nullptr);
-  carve_select(a, L);
+  carve_cut(a, L);
   return a.used();
 }
 
@@ -713,54 +949,44 @@ int run_select_queries(const Layer& L, const float* scores, int mode, float para
                        hipStream_t st) {
   Arena a(ws);
   KeySource src;
-  const ListJob job = query_job(L, carve_select(a, L), scores, mode, param, q_idx, q_cnt, &src);
-  const int rc = launch_cut(L, Ragged{}, 1, job, src, job, src, st);
-  return rc != OMNI_OK ? rc : launch_write(L, Ragged{}, 1, job, job, st);
+  const ListJob job = query_job(L, carve_cut(a, L), scores, mode, param, q_idx, q_cnt, &src);
+  return launch_lists(L, Ragged{}, 1, job, src, job, src, st);
 }
 
 int run_select_kv(const Layer& L, const float* key_scores, const int* budget, int b_cap, int* kv_idx, void* ws,
                   hipStream_t st) {
   Arena a(ws);
-  const ListJob job = list_job(carve_select(a, L), key_scores, key_rule(), kv_idx, b_cap, nullptr);
+  const ListJob job = list_job(carve_cut(a, L), key_scores, key_rule(), kv_idx, b_cap, nullptr);
   KeySource src{};
   src.mode = 3;
   src.budget = const_cast<int*>(budget);
   src.bph = L.bph;
   src.k_cap = b_cap;
-  const int rc = launch_cut(L, Ragged{}, 1, job, src, job, src, st);
-  return rc != OMNI_OK ? rc : launch_write(L, Ragged{}, 1, job, job, st);
+  return launch_lists(L, Ragged{}, 1, job, src, job, src, st);
 }
 
 size_t budget_stats_ws(const Layer& L) {
   Arena a(nullptr);
-  const size_t BH = (size_t)L.B * L.Hq;
-  a.take<unsigned>(BH);
-  a.take<int>(BH);
-  a.take<int>(BH);
+  carve_stats(a, L);
   return a.used();
 }
 
 int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, int budget_mode, double* kurt,
                      int* flattest, int* budget, float* recall, void* ws, hipStream_t st) {
   Arena a(ws);
-  const size_t BH = (size_t)L.B * L.Hq;
-  SelWs w{};
-  w.thr = a.take<unsigned>(BH);
-  w.need = a.take<int>(BH);
-  int* own = a.take<int>(BH);
   KeySource src;
-  const int rc = launch_stats(L, Ragged{}, key_scores, recall_p, budget_mode, kurt, own, flattest, budget, recall, L.N,
-                              &src, st);
+  const int rc = launch_stats(L, Ragged{}, key_scores, recall_p, budget_mode, kurt, carve_stats(a, L), flattest, budget, recall,
+                              L.N, &src, st);
   if (rc != OMNI_OK) return rc;
-  const ListJob job = list_job(w, key_scores, key_rule(), nullptr, 0, nullptr);   // the cut for the recall only: no list
-  return launch_cut(L, Ragged{}, 1, job, src, job, src, st);
+  const ListJob job = list_job(CutWs{}, key_scores, key_rule(), nullptr, 0, nullptr);   // the cut for the recall only: no list
+  return launch_lists(L, Ragged{}, 1, job, src, job, src, st);
 }
 
 size_t select_lists_ws(const Layer& L) {
   Arena a(nullptr);
-  carve_select(a, L);
-  carve_select(a, L);
-  a.take<int>((size_t)L.B * L.Hq);
+  carve_stats(a, L);
+  carve_cut(a, L);
+  carve_cut(a, L);
   return a.used();
 }
 
@@ -768,16 +994,13 @@ int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int 
                      int* q_cnt, const float* key_scores, float recall_p, int budget_mode, double* kurt, int* flattest,
                      int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st) {
   Arena a(ws);
-  const SelWs wk = carve_select(a, L), wq = carve_select(a, L);
-  int* own = a.take<int>((size_t)L.B * L.Hq);
   KeySource ks, qs;
-  int rc = launch_stats(L, rg, key_scores, recall_p, budget_mode, kurt, own, flattest, budget, recall, b_cap, &ks, st);
+  const int rc = launch_stats(L, rg, key_scores, recall_p, budget_mode, kurt, carve_stats(a, L), flattest, budget, recall, b_cap,
+                              &ks, st);
   if (rc != OMNI_OK) return rc;
-  const ListJob kj = list_job(wk, key_scores, key_rule(), kv_idx, b_cap, nullptr);
-  const ListJob qj = query_job(L, wq, scores, q_mode, q_param, q_idx, q_cnt, &qs);
-  rc = launch_cut(L, rg, 2, qj, qs, kj, ks, st);
-  if (rc != OMNI_OK) return rc;
-  return launch_write(L, rg, 2, qj, kj, st);
+  const ListJob kj = list_job(carve_cut(a, L), key_scores, key_rule(), kv_idx, b_cap, nullptr);
+  const ListJob qj = query_job(L, carve_cut(a, L), scores, q_mode, q_param, q_idx, q_cnt, &qs);
+  return launch_lists(L, rg, 2, qj, qs, kj, ks, st);
 }
 
 // ---- union of the stored visual rows over the heads of a KV group, with a membership bit per head

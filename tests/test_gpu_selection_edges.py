@@ -55,6 +55,30 @@ def test_budget_and_lists_on_scores_in_hand(N, kind):
             assert abs(float(r.recall[0, h]) - top.sum() / N) <= 2.0 ** -23
 
 
+@pytest.mark.parametrize("N", [8191, 8192, 8193, 16384, 33000])
+def test_cuts_among_scores_that_no_sample_shows(N):
+    """Nearly all scores within a thousandth of each other, a hundred far above and a hundred far below at positions between those
+    that the bins are laid out by: cuts on both sides of every such group, and budgets of their mass."""
+    H, rng = 2, np.random.default_rng(N)
+    a = (1.0 + 1e-3 * rng.random((1, H, N))).astype(np.float32)
+    seen = N * np.arange(1024) // 1024
+    at = rng.choice(np.setdiff1d(np.arange(N), seen) if N > 8192 else np.arange(N), 200, replace=False)
+    a[0, :, at[:100]] = np.exp2(20 * rng.random((100, 1))).astype(np.float32)
+    a[0, :, at[100:]] = np.exp2(-20 * rng.random((100, 1)) - 1).astype(np.float32)
+    d, da = _desc(H, N, 0, N), torch.from_numpy(a).cuda()
+    for b in (1, 50, 99, 100, 101, N // 2, N - 101, N - 100, N - 99, N - 1):
+        kv = ob.omni_select_kv(d, da, torch.tensor([b], dtype=torch.int32, device="cuda"), N).cpu().numpy()
+        for h in range(H):
+            np.testing.assert_array_equal(kv[0, h, :b], np.sort(np.lexsort((np.arange(N), -a[0, h]))[:b]))
+    for p in (1e-3, 0.5, 0.9, 0.999):
+        c = np.ascontiguousarray(a * (N / a.sum(-1, keepdims=True, dtype=np.float64)), dtype=np.float32)
+        r = ob.omni_budget_from_scores(d, torch.from_numpy(c).cuda(), p, 2)
+        for h in range(H):
+            b = int(r.budget[0, h])
+            assert b == oc.budget_of(c[0, h], p, N)
+            assert abs(float(r.recall[0, h]) - np.sort(c[0, h].astype(np.float64))[::-1][:b].sum() / N) <= 2.0 ** -23
+
+
 def test_lists_with_infinite_negative_and_nan_scores():
     """The order of the keys is that of the floats, NaN above infinity; counts and ties follow it."""
     N, H = 3000, 2
