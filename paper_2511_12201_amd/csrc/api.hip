@@ -151,10 +151,8 @@ static int run_prefill_select(const Layer& L, int dtype, const Ragged& rg, const
                               int* q_idx, int* q_cnt, float* key_scores, double* kurtosis, int* flattest, int* budget,
                               float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st) {
   char* ws_lists = static_cast<char*>(ws) + align_up(probe_ws(L, dtype, pb), 256);
-  int rc = run_probe_keys(L, dtype, K, probe_keys, ws, st, rg);
-  if (rc != OMNI_OK) return rc;
-  // one pass over Q: lazy/active scores and pooled queries; then the two probe passes over K
-  rc = run_probe(L, dtype, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
+  // probe keys; one pass over Q: lazy/active scores and pooled queries; then the two probe passes over K
+  const int rc = run_probe(L, dtype, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
   if (rc != OMNI_OK) return rc;
   return run_select_lists(L, rg, scores, q_mode, q_param, q_idx, q_cnt, key_scores, recall_p, budget_mode, kurtosis,
                           flattest, budget, recall, kv_idx, b_cap, ws_lists, st);

@@ -9,6 +9,7 @@ namespace omni {
 size_t score_queries_ws(const Layer& L);
 int run_score_queries(const Layer& L, int dtype, const void* Q, const void* K, float* probe, float* scores, void* ws,
                       hipStream_t st);
+int score_mean_chunks(const Layer& L);
 int run_probe_keys(const Layer& L, int dtype, const void* K, float* probe, void* ws, hipStream_t st,
                    const Ragged& rg = Ragged{});
 
@@ -35,9 +36,9 @@ int run_group_subset(const Layer& L, const int* kv_idx, const int* budget, int b
 
 // probe.hip
 size_t probe_ws(const Layer& L, int dtype, int pb);
-// probe_keys / scores not null: the pooling pass over Q also writes the lazy/active query scores
+// probe_keys / scores not null: and the probe keys and the lazy/active query scores (no extra pass over Q)
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
-              hipStream_t st, const float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
+              hipStream_t st, float* probe_keys = nullptr, float* scores = nullptr, const Ragged& rg = Ragged{});
 
 // pack.hip (outputs that are nullptr are skipped; bf16: Vt holds f16 values, and not both Kt and Vt in one call)
 // Kn, Vn, Qn, dOn in the order of a 32x32 MFMA's A operand, [32-row block][k step][lane] of 16 bytes (lane = 32 * half + row; a

@@ -21,6 +21,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "score_dev.h"
 
 namespace omni {
 
@@ -38,15 +39,14 @@ constexpr int kProbeWgs = 768;          // workgroups of a probe pass up to whic
 // SCORE: the same pass over Q also writes the lazy/active score of every row (paper Sec. "Query Selection",
 // probe-softmax equation), with the arithmetic of the stand-alone scoring kernel, so that Q is read once.
 template <typename T, int D, bool SCORE>
-__global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restrict__ Q, Layer L, Ragged rg, int pb, int nblk,
-                                                               float* __restrict__ qbar, u16* __restrict__ qsplit,
-                                                               const float* __restrict__ probe_keys,
-                                                               float* __restrict__ scores) {
+__device__ __forceinline__ void pool_block(const T* __restrict__ Q, const Layer& L, const Ragged& rg, int pb, int nblk, int j, int bh,
+                                           float* __restrict__ qbar, u16* __restrict__ qsplit,
+                                           const float* __restrict__ probe_keys, float* __restrict__ scores, float* red_) {
   constexpr int E = Elem<T>::kPer16B;
   constexpr int LPR = D / E;
   constexpr int RPP = kThreads / LPR;
-  __shared__ float red[RPP][D];
-  const int j = blockIdx.x, bh = blockIdx.y;          // j >= nblk (bf16 only): a zero row that pads the last 32-row block
+  float (*red)[D] = reinterpret_cast<float (*)[D]>(red_);
+  // j >= nblk (bf16 only): a zero row that pads the last 32-row block
   const int b = bh / L.Hq, i = bh % L.Hq;
   const T* base = Q + b * L.qs[0] + i * L.qs[1];
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
@@ -63,6 +63,7 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
     for (int e = 0; e < E; ++e) diff[e] = pk[D + c * E + e] - pk[c * E + e];
     float* out = scores + (long long)bh * L.ld;
     constexpr int kRowsInFlight = 16;                      // loads of this many rows per lane group are issued together
+    constexpr int kTurn = LPR < kRowsInFlight ? LPR : kRowsInFlight;
     for (int rb = row_begin; rb < row_end; rb += RPP * kRowsInFlight) {   // uniform trip count: shuffles need every lane
       u32x4 raw[kRowsInFlight];
 #pragma unroll
@@ -71,31 +72,46 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
         raw[u] = u32x4{0u, 0u, 0u, 0u};
         if (r < row_end) raw[u] = *reinterpret_cast<const u32x4*>(base + (long long)r * L.qs[2] + c * E);
       }
+      // Rows in ascending order: the sums match the plain pooling pass.  Every lane of a row's lane group ends up with one row's
+      // dot product, so that the exponential is evaluated once for kTurn rows.
 #pragma unroll
-      for (int u = 0; u < kRowsInFlight; ++u) {            // rows in ascending order: the sums match the plain pooling pass
-        const int r = rb + u * RPP + r0;
-        const bool live = r < row_end;
-        float dot = 0.f;
-        if (live) {
-          float v[E];
-          unpack16(raw[u], v, (const T*)nullptr);
+      for (int u0 = 0; u0 < kRowsInFlight; u0 += kTurn) {
+        float mine = 0.f;
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            acc[e] += v[e];
-            dot = fmaf(v[e], diff[e], dot);
+        for (int u = u0; u < u0 + kTurn; ++u) {
+          const bool live = rb + u * RPP + r0 < row_end;
+          float dot = 0.f;
+          if (live) {
+            float v[E];
+            unpack16(raw[u], v, (const T*)nullptr);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              acc[e] += v[e];
+              dot = fmaf(v[e], diff[e], dot);
+            }
           }
+          dot = row_lanes_sum<LPR>(dot);
+          mine = c == u - u0 ? dot : mine;
         }
-        dot = row_lanes_sum<LPR>(dot);
-        if (live && c == 0) out[r] = 1.0f / (1.0f + expf(-dot * L.scale));
+        const int r = rb + (u0 + c) * RPP + r0;
+        if (c < kTurn && r < row_end) out[r] = 1.0f / (1.0f + expf(-mine * L.scale));
       }
     }
   } else {
-    for (int r = row_begin + r0; r < row_end; r += RPP) {
-      u32x4 raw = *reinterpret_cast<const u32x4*>(base + (long long)r * L.qs[2] + c * E);
-      float v[E];
-      unpack16(raw, v, (const T*)nullptr);
+    constexpr int kRowsInFlight = 8;
+    for (int rb = row_begin + r0; rb < row_end; rb += RPP * kRowsInFlight) {
+      u32x4 raw[kRowsInFlight];
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += v[e];
+      for (int u = 0; u < kRowsInFlight; ++u)
+        raw[u] = *reinterpret_cast<const u32x4*>(base + (long long)min(rb + u * RPP, row_end - 1) * L.qs[2] + c * E);
+#pragma unroll
+      for (int u = 0; u < kRowsInFlight; ++u) {
+        if (rb + u * RPP >= row_end) break;
+        float v[E];
+        unpack16(raw[u], v, (const T*)nullptr);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += v[e];
+      }
     }
   }
 #pragma unroll
@@ -125,6 +141,28 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restr
       qbar[((long long)bh * nblk + j) * D + threadIdx.x] = mean;
     }
   }
+}
+
+template <typename T, int D, bool SCORE>
+__global__ __launch_bounds__(kThreads) void pool_queries_kernel(const T* __restrict__ Q, Layer L, Ragged rg, int pb, int nblk,
+                                                               float* __restrict__ qbar, u16* __restrict__ qsplit,
+                                                               const float* __restrict__ probe_keys,
+                                                               float* __restrict__ scores) {
+  __shared__ float red[kThreads / (D / Elem<T>::kPer16B) * D];
+  pool_block<T, D, SCORE>(Q, L, rg, pb, nblk, blockIdx.x, blockIdx.y, qbar, qsplit, probe_keys, scores, red);
+}
+
+// Short selections (bf16): the pooled queries and the sums of the visual keys in one launch; the scores come with the first
+// probe pass, on rows of Q that are in the caches by then.  grid: pooled rows x B*Hq, then mean chunks x B*Hkv.
+template <int D>
+__global__ __launch_bounds__(kThreads) void pool_and_mean_kernel(const u16* __restrict__ Q, const u16* __restrict__ K, Layer L,
+                                                                Ragged rg, int pb, int nblk, int pooled_rows, int mean_chunks,
+                                                                u16* __restrict__ qsplit, float* __restrict__ partial) {
+  __shared__ float red[kThreads / (D / 8) * D];
+  const int n_pool = pooled_rows * L.B * L.Hq, i = (int)blockIdx.x - n_pool;
+  if (i < 0) pool_block<u16, D, false>(Q, L, rg, pb, nblk, blockIdx.x % pooled_rows, blockIdx.x / pooled_rows, nullptr, qsplit, nullptr,
+                                       nullptr, red);
+  else mean_key_block<u16, D>(K, L, rg, mean_chunks, i % mean_chunks, i / mean_chunks, partial, red);
 }
 
 // ---------------------------------------------------------------- probe passes
@@ -327,8 +365,19 @@ __device__ __forceinline__ float half_wave_reduce_scatter(float (&v)[32], int ln
   return v[0];
 }
 
-// grid: (nchunk * B*Hkv, pieces), chunk-major (the chunks of low key index see the most pooled rows: longest first); a
-// workgroup takes the heads [piece * per_piece, + per_piece) of its KV group.
+// What a short selection has the two passes do besides (all zero: nothing): the scores of the rows in pass 1, each pooled row's
+// log-sum-exp from the chunks' partials in pass 2.
+constexpr int kShortChunks = 16, kShortRows = 256;     // key chunks; (head, pooled row) pairs of a workgroup
+struct ShortRoles {
+  const u16* Q;
+  const float* partial;                       // sums of the visual keys
+  int mean_chunks, score_blocks;              // blocks of kScoreRows rows of a head
+  float *probe, *scores;
+  const float *part_m, *part_l;
+};
+
+// grid: nchunk * B*Hkv * pieces (then the score rows), chunk-major (the chunks of low key index see the most pooled rows: longest
+// first); a workgroup takes the heads [piece * per_piece, + per_piece) of its KV group.
 // PASS 1: (max, sum) of every pooled row over this workgroup's 256 keys -> part_m / part_l.
 // PASS 2: a[head, key] = sum over pooled rows of exp2(s2 - lse2w[row]).
 template <int D, int PASS>
@@ -336,7 +385,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
                                                              int nchunk, const u16* __restrict__ qsplit,
                                                              float* __restrict__ part_m, float* __restrict__ part_l,
                                                              const float* __restrict__ lse2w,
-                                                             float* __restrict__ a_out, int per_piece) {
+                                                             float* __restrict__ a_out, int per_piece, ShortRoles sr) {
   constexpr int KB = 2;                        // 32-key blocks per wavefront
   constexpr int KPW = KB * 32, KPG = 4 * KPW;
   constexpr int CH = D / 8;                    // 16-byte chunks per row
@@ -349,8 +398,18 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
   __shared__ float sRedM[2][4][32], sRedL[2][4][32];
   __shared__ __attribute__((aligned(256))) float sLse[NS][64];
 
-  const int ngrp = Lp.B * Lp.Hkv;
-  const int chunk = blockIdx.x / ngrp, bg = blockIdx.x % ngrp;
+  __shared__ float sRowLse[PASS == 2 ? kShortRows : 1];
+
+  const int ngrp = Lp.B * Lp.Hkv, nwg = nchunk * ngrp, piece = blockIdx.x / nwg, wg = blockIdx.x % nwg;
+  if constexpr (PASS == 1) {
+    const int i = (int)blockIdx.x - nwg * cdiv(Lp.G, per_piece);
+    if (i >= 0) {
+      score_rows_block<u16, D>(sr.Q, K, Lp, rg, sr.mean_chunks, sr.partial, i % sr.score_blocks, i / sr.score_blocks, sr.probe, sr.scores,
+                               reinterpret_cast<float*>(&sQ[0][0]));
+      return;
+    }
+  }
+  const int chunk = wg / ngrp, bg = wg % ngrp;
   const int b = bg / Lp.Hkv, g = bg % Lp.Hkv;
   Layer L = Lp;                                // the sequence's own length; nblk_p and nchunk are the padded strides
   L.N = seq_len(Lp, rg, b);
@@ -364,7 +423,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
   const float c2 = L.scale * kLog2e;
   const int nrb = cdiv(nblk, 32);
   const int jb0 = L.causal ? ((chunk * KPG) / pb) / 32 : 0;
-  const int head0 = blockIdx.y * per_piece, heads = min(per_piece, L.G - head0);
+  const int head0 = piece * per_piece, heads = min(per_piece, L.G - head0);
   const int n_it = heads * (nrb - jb0);
   const int bh0 = b * L.Hq + g * L.G + head0;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&sQ[0][0];
@@ -417,6 +476,34 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
   float colacc[32];
 #pragma unroll
   for (int r = 0; r < 32; ++r) colacc[r] = 0.f;
+
+  const bool own_lse = PASS == 2 && sr.part_m;
+  if constexpr (PASS == 2) {
+    // as probe_lse_kernel, a thread per row and in the order of its exchanges
+    if (own_lse && (int)threadIdx.x < heads * nblk) {
+      const int jh = threadIdx.x / nblk, j = threadIdx.x % nblk;
+      const int row_end = min((j + 1) * pb, L.N), nvis = cdiv(L.causal ? row_end : L.N, KPG);
+      const long long o = ((long long)(bh0 + jh) * nblk_p + j) * nchunk;
+      float m[kShortChunks], l[kShortChunks], M = -INFINITY;
+#pragma unroll
+      for (int c = 0; c < kShortChunks; ++c) {
+        const int at = min(c, nvis - 1);
+        m[c] = sr.part_m[o + at];
+        l[c] = sr.part_l[o + at];
+      }
+#pragma unroll
+      for (int c = 0; c < kShortChunks; ++c) M = c < nvis ? fmaxf(M, m[c]) : M;
+      const float Mr = M == -INFINITY ? 0.f : M;
+#pragma unroll
+      for (int c = 0; c < kShortChunks; ++c) l[c] = c < nvis && m[c] != -INFINITY ? l[c] * exp2f(m[c] - Mr) : 0.f;
+#pragma unroll
+      for (int w = kShortChunks / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int c = 0; c < w; ++c) l[c] += l[c + w];
+      sRowLse[threadIdx.x] = Mr + log2f(l[0]) - log2f((float)(row_end - j * pb));
+    }
+    // the first __syncthreads of the loop stands before the first read
+  }
 
   // combine the four wavefronts' (max, sum) of one row block and write the workgroup's partial
   auto combine = [&](int jh, int jb, int buf) {
@@ -507,7 +594,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_bf16_kernel(const u16* __re
         sRedL[it & 1][wave][ln] = l;
       }
     } else {
-      const float lse = sLse[it % NS][ln];
+      const float lse = own_lse ? sRowLse[jh * nblk + min(j, nblk - 1)] : sLse[it % NS][ln];
       if (full) {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -596,18 +683,49 @@ ProbeWs carve_probe(Arena& a, const Layer& L, int pb) {
   return w;
 }
 
+// Short selections: key chunks and pooled rows few enough for pass 2 to form the rows' log-sum-exp by itself, and the mean's
+// partial sums fit where the key scores will be.  mean, pool + scores, pass 1, log-sum-exp, pass 2 as five launches (and one for
+// the probe keys) / pool + mean, pass 1 + scores, pass 2 as three: one-call prefill of 1072 tokens, 28 heads, 75.6 / 64.9 us.
+template <typename T>
+bool probe_short(const Layer& L, int pb) {
+  if (sizeof(T) != 2) return false;
+  const int nblk = cdiv(L.N, pb), nchunk = cdiv(L.N, probe_keys_per_wg<T>());
+  return nchunk <= kShortChunks && L.G * nblk <= kShortRows && nblk <= 32 &&
+         (long long)L.Hkv * score_mean_chunks(L) * L.D <= (long long)L.Hq * L.ld;
+}
+
 template <typename T, int D>
 int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* key_scores, void* ws, hipStream_t st,
-                 const float* probe_keys, float* scores, const Ragged& rg) {
+                 float* probe_keys, float* scores, const Ragged& rg) {
   Arena a(ws);
   ProbeWs w = carve_probe<T>(a, L, pb);
   const int nblk = cdiv(L.N, pb);
   constexpr int KPG = probe_keys_per_wg<T>();
   const int nchunk = cdiv(L.N, KPG);
   const int BH = L.B * L.Hq;
-  {
+  ShortRoles roles{}, late{};
+  const int pooled_rows = sizeof(T) == 2 ? cdiv(nblk, 32) * 32 : nblk;
+  if (scores && probe_short<T>(L, pb)) {
+    roles.Q = static_cast<const u16*>(Q);
+    roles.partial = key_scores;
+    roles.mean_chunks = score_mean_chunks(L);
+    roles.score_blocks = cdiv(L.N, kScoreRows);
+    roles.probe = probe_keys;
+    roles.scores = scores;
+    late.part_m = w.part_m;
+    late.part_l = w.part_l;
     ProfScope prof__(kProfPool, st);
-    const int pooled_rows = sizeof(T) == 2 ? cdiv(nblk, 32) * 32 : nblk;
+    if constexpr (sizeof(T) == 2)
+      hipLaunchKernelGGL((pool_and_mean_kernel<D>), dim3(pooled_rows * BH + roles.mean_chunks * L.B * L.Hkv), dim3(kThreads), 0, st,
+                         static_cast<const u16*>(Q), static_cast<const u16*>(K), L, rg, pb, nblk, pooled_rows, roles.mean_chunks,
+                         w.qsplit, key_scores);
+    OMNI_LAUNCH_CHECK();
+  } else {
+    if (scores) {
+      const int rc = run_probe_keys(L, sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32, K, probe_keys, ws, st, rg);
+      if (rc != OMNI_OK) return rc;
+    }
+    ProfScope prof__(kProfPool, st);
     if (scores) {
       hipLaunchKernelGGL((pool_queries_kernel<T, D, true>), dim3(pooled_rows, BH), dim3(kThreads), 0, st,
                          static_cast<const T*>(Q), L, rg, pb, nblk, w.qbar, w.qsplit, probe_keys, scores);
@@ -626,20 +744,22 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
     // four sequences, 512 workgroups: 47 us undivided, 49 and 54 in two and three pieces).
     const int nwg = nchunk * L.B * L.Hkv;
     const int per_piece = cdiv(L.G, std::max(1, std::min(L.G, kProbeWgs / nwg)));
-    const dim3 grid(nwg, cdiv(L.G, per_piece));
+    const unsigned grid = (unsigned)nwg * (unsigned)cdiv(L.G, per_piece);
     {
       ProfScope prof__(kProfProbeLse, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), grid, dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
-                         w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr, per_piece);
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 1>), dim3(grid + (unsigned)(roles.score_blocks * BH)), dim3(kThreads), 0, st, Kp, L, rg,
+                         pb, nblk, nchunk, w.qsplit, w.part_m, w.part_l, (const float*)nullptr, (float*)nullptr, per_piece, roles);
       OMNI_LAUNCH_CHECK();
     }
+    if (!late.part_m) {
     hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
                        w.part_m, w.part_l, w.lse2w);
     OMNI_LAUNCH_CHECK();
+    }
     {
       ProfScope prof__(kProfProbeSum, st);
-      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), grid, dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
-                         (float*)nullptr, (float*)nullptr, w.lse2w, key_scores, per_piece);
+      hipLaunchKernelGGL((probe_bf16_kernel<D, 2>), dim3(grid), dim3(kThreads), 0, st, Kp, L, rg, pb, nblk, nchunk, w.qsplit,
+                         (float*)nullptr, (float*)nullptr, w.lse2w, key_scores, per_piece, late);
       OMNI_LAUNCH_CHECK();
     }
     return OMNI_OK;
@@ -672,7 +792,7 @@ size_t probe_ws(const Layer& L, int dtype, int pb) {
 }
 
 int run_probe(const Layer& L, int dtype, const void* Q, const void* K, int pb, float* key_scores, void* ws,
-              hipStream_t st, const float* probe_keys, float* scores, const Ragged& rg) {
+              hipStream_t st, float* probe_keys, float* scores, const Ragged& rg) {
   if (dtype == OMNI_BF16) {
     if (L.D == 128) return launch_probe<u16, 128>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);
     return launch_probe<u16, 64>(L, Q, K, pb, key_scores, ws, st, probe_keys, scores, rg);

@@ -7,62 +7,20 @@
 // whole contiguous rows.
 #include "common.h"
 #include "kernels.h"
+#include "score_dev.h"
 
 namespace omni {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kMeanRowsPerChunk = 256;     // ~1000 workgroups at 64k: enough to fill the memory system
+constexpr int kThreads = kScoreThreads;
 
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void mean_key_partial_kernel(const T* __restrict__ K, Layer L, Ragged rg, int nchunk,
                                                                    float* __restrict__ partial) {
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int LPR = D / E;              // lanes per row
-  constexpr int RPP = kThreads / LPR;     // rows per pass
-  __shared__ float red[RPP][D];
-  const int chunk = blockIdx.x;
-  const int bg = blockIdx.y;
-  const int b = bg / L.Hkv, g = bg % L.Hkv;
-  const T* base = K + b * L.ks[0] + g * L.ks[1];
-  const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
-  const int v1 = rg.on ? rg.v1[b] : L.v1;
-  const int row_begin = (rg.on ? rg.v0[b] : L.v0) + chunk * kMeanRowsPerChunk;
-  const int row_end = min(v1, row_begin + kMeanRowsPerChunk);
-  if (row_begin >= v1) return;             // a shorter sequence of a padded batch
-  float acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.f;
-  constexpr int kRowsInFlight = 8;         // loads issued together; added in ascending order of the rows
-  for (int rb = row_begin + r0; rb < row_end; rb += RPP * kRowsInFlight) {
-    u32x4 raw[kRowsInFlight];
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; ++u) {
-      const int r = rb + u * RPP;
-      if (r < row_end) raw[u] = *reinterpret_cast<const u32x4*>(base + (long long)r * L.ks[2] + c * E);
-    }
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; ++u) {
-      if (rb + u * RPP >= row_end) break;
-      float v[E];
-      unpack16(raw[u], v, (const T*)nullptr);
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += v[e];
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < E; ++e) red[r0][c * E + e] = acc[e];
-  __syncthreads();
-  if (threadIdx.x < D) {
-    float s = 0.f;
-#pragma unroll 4
-    for (int r = 0; r < RPP; ++r) s += red[r][threadIdx.x];
-    partial[((long long)bg * nchunk + chunk) * D + threadIdx.x] = s;
-  }
+  __shared__ float red[kThreads / (D / Elem<T>::kPer16B) * D];
+  mean_key_block<T, D>(K, L, rg, nchunk, blockIdx.x, blockIdx.y, partial, red);
 }
-
-constexpr int kFinalSplit = 8;
 
 template <typename T, int D>
 __global__ void probe_keys_finalize_kernel(const T* __restrict__ K, Layer L, Ragged rg, int nchunk,

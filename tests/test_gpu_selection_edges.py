@@ -257,3 +257,23 @@ def test_padded_batch_with_scratch_for_one_sequence_gives_the_same():
     for u, v in ((x.q_cnt, y.q_cnt), (x.budget.budget, y.budget.budget), (x.budget.recall, y.budget.recall),
                  (x.budget.kurtosis, y.budget.kurtosis), (x.probe_keys, y.probe_keys)):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [(14, 2), (2, 2)])
+@pytest.mark.parametrize("N,block", [(1, 256), (40, 256), (300, 16), (300, 256), (4096, 128), (4096, 256), (4097, 256), (9000, 256)])
+def test_selection_of_short_and_long_sequences_gives_what_the_separate_calls_give(N, block, heads, d, causal):
+    """The launches that a short selection shares (rows and key chunks few enough; block 128 at 4096 tokens and seven heads a
+    group is past the line) against the passes one by one, which keep launches of their own: bit for bit."""
+    H, Hkv = heads
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    Q, K = (torch.randn(2, h, N, d, generator=g, device="cuda").bfloat16() for h in (H, Hkv))
+    v0, v1 = (0, N) if N < 3 else (1, N - 1)
+    desc = ob.make_layer_desc(Q, K, v0, v1, 0, causal)
+    out = ob.omni_prefill_select(desc, Q, K, 0, 0.3, 0.9, block, 0)
+    probe, scores = ob.omni_score_queries(desc, Q, K)
+    b = ob.omni_kv_budget(desc, Q, K, 0.9, block, 0)
+    for x, y in ((out.probe_keys, probe), (out.scores, scores), (out.budget.key_scores, b.key_scores),
+                 (out.budget.budget, b.budget), (out.budget.kurtosis, b.kurtosis), (out.budget.recall, b.recall)):
+        assert torch.equal(x, y)
