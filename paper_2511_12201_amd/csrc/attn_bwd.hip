@@ -5,16 +5,15 @@
 //   P = exp(S - lse), dV = P^T dO, dP = dO V^T, dS = P (dP - delta),
 //   delta = rowsum(dO O), dQ = scale dS K, dK = scale dS^T Q.
 //
-// Deterministic, no floating-point atomics.  bf16 (the measured path), three kernels in the forward's style
+// Deterministic, no floating-point atomics.  bf16 (the measured path), two kernels in the forward's style
 // (8 wavefronts, LDS-DMA ring, position masks from the visible-prefix counts):
-//  * attn_bwd_dq_bf16_kernel: a work item is 256 kept queries of a head (32 per wavefront) from the forward's
-//    longest-first list; it streams 64-key tiles of K, V (fragment order) and K^T (k-packed): S^T = K Q^T,
-//    dP^T = V dO^T, dQ^T += K^T dS^T.  Short sequences: attn_bwd_dq_split_kernel, 32 queries an item, no list.
-//  * attn_bwd_key_bf16_kernel: a workgroup owns 256 packed keys of a query head (32 per wavefront, K and V fragments
-//    resident) and streams 32-query tiles (d = 64: 64) of the packed kept rows (Q, dO in fragment order and k-packed, lse and
-//    delta by 4-byte LDS-DMA): S = Q K^T, dP = dO V^T, dV' += P^T dO, dK' += dS^T Q.  Items (head, key tile, split)
-//    come from a list a small kernel compacts; a key tile seen by many query tiles is shared by up to four workgroups,
+//  * attn_bwd_bf16_kernel, persistent, goes through two lists one after the other.
+//    Key items: 256 packed keys of a query head (32 per wavefront, K and V fragments resident); 32-query tiles (d = 64: 64) of
+//    the packed kept rows (Q, dO in fragment order and k-packed, lse and delta by 4-byte LDS-DMA) are streamed: S = Q K^T,
+//    dP = dO V^T, dV' += P^T dO, dK' += dS^T Q.  A key tile seen by many query tiles is shared by up to four workgroups,
 //    each with a partial plane of its own.
+//    dQ items: 256 kept queries of a head (32 per wavefront) from the forward's longest-first list; 64-key tiles of K, V
+//    (fragment order) and K^T (k-packed): S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
 // fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_f32_kernel (blocks for dK' and dV' of 32 keys, and for dQ);
@@ -54,7 +53,7 @@ struct BwdParams {
   float* dKp;           // [B*Hq, npad, D] fp32 per-query-head partial gradients
   float* dVp;
   void* dQ;
-  int* sched;           // work list of the dQ kernel (sched.h)
+  int* sched;           // work list of the dQ items (sched.h)
   size_t order_off;     // where its hand-out order starts
   const int* list;      // [B*Hq, list_stride] the heads' key lists
   int list_stride;
@@ -515,8 +514,10 @@ constexpr int kDqStages = 3;
 
 constexpr int kBwdMaxMapTiles = 2048;               // key tiles of one head in the in-place variant (128k tokens)
 
+template <int D>
+constexpr int kDqLds = kDqStages * 3 * kTileN * D * 2;
 template <int D, bool TILEMAP>
-__global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdParams p) {
+__device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem, int* sBound, int& sItem, int* sTileMap) {
   typedef u16 T;
   constexpr int kOpBytes = kTileN * D * 2;           // one operand tile
   constexpr int kStageBytes = 3 * kOpBytes;          // K, V, K k-packed
@@ -524,10 +525,7 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
   constexpr int LPT = 3 * LPH;
   constexpr int NB = D / 32;
   static_assert(LPH >= 1, "tile too small for the copy scheme");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kDqStages * kStageBytes];
-  __shared__ int sBound[2];
-  __shared__ int sItem;
-  __shared__ int sTileMap[TILEMAP ? kBwdMaxMapTiles : 1];
+  static_assert(kDqLds<D> == kDqStages * kStageBytes, "");
 
   const Layer& L = p.L;
   const int lane = lane_id();
@@ -705,133 +703,9 @@ __global__ __launch_bounds__(kDqThreads, 2) void attn_bwd_dq_bf16_kernel(BwdPara
   }  // work-item loop
 }
 
-// ------------------------------------------------------------------ dQ, bf16, short sequences
-//
-// As the forward on short sequences (attn_fwd.hip): an item is 32 kept queries, its four wavefronts share the 32-key
-// blocks, operands straight from memory in fragment order, partial sums added in wavefront order; no work list.  A 256-row
-// item walks its tiles one after the other at 1.5 to 2 us each, and short sequences have a few dozen of them.  At d = 128
-// one workgroup fits a CU (304 registers); a layout for two (K^T in halves, the sums over the Q and dO rows) measured the
-// same within 4 % either way.
-constexpr int kSplitWaves = 4;
-constexpr int kSplitThreads = kSplitWaves * 64;
-// Which of the two dQ kernels, by the shape only (the gathered and the in-place lists of a layer take the same one).  Forward
-// and backward of a layer in us, (heads, d) N: split / the other, a third of the queries and half of the keys kept:
-// (28, 128) 1072: 149 / 170, 2048: 203 / 224, 4096 (6.0e10): 346 / 347, (56, 64) 3101 (3.4e10): 203 / 220, (28, 64) 6000
-// (6.5e10): 363 / 375, (8, 128) 4096 (1.7e10): 227 / 259, 7500 (5.8e10): 457 / 442.  On lists of everything (both rules' split
-// kernels / the others / the 256-row items that all shapes had before): (28, 128) 2048: 364 / 392 / 434, 3300 (3.9e10): 724 /
-// 661 / 735, (28, 64) 4600 (3.8e10): 697 / 688 / 747, (8, 128) 6000 (3.7e10): 627 / 711 / 831.
-constexpr double kSplitWork = 4.0e10;
-
-// grid: cdiv(N, 32) * B*Hq, heads fastest; a head's last rows, which see the most keys, first
-template <int D, bool TILEMAP>
-__global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_split_kernel(BwdParams p) {
-  typedef u16 T;
-  constexpr int CH = D / 8, KS = D / 16, NB = D / 32;
-  __shared__ __attribute__((aligned(16))) unsigned char sQ[32 * D * 2], sG[32 * D * 2];
-  __shared__ __attribute__((aligned(16))) float sO[kSplitWaves][32][D + 4];
-  const Layer& L = p.L;
-  const int BH = L.B * L.Hq, bh = blockIdx.x % BH, b = bh / L.Hq, i = bh % L.Hq;
-  const int nq = p.q_cnt[bh];
-  const int tq = cdiv(nq, 32) - 1 - (int)(blockIdx.x / BH);
-  if (tq < 0) return;
-  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int ln = lane & 31, h = lane >> 5;
-  const float c2 = L.scale * kLog2e;
-  const int* qlist = p.q_idx + (long long)bh * L.N;
-  const int* qvis = p.qvis + (long long)bh * L.N;
-  const long long qo = (long long)bh * p.nqpad + tq * 32;
-  const int qvisible = qvis[min(tq * 32 + ln, nq - 1)] - 4 * h;
-  const int n_full = qvis[tq * 32] / 32, nblocks = cdiv(qvis[min(tq * 32 + 31, nq - 1)], 32);
-  const float lse = p.lse2c[qo + ln], delta = p.deltac[qo + ln];
-#pragma unroll
-  for (int c = threadIdx.x; c < 32 * CH; c += kSplitThreads) {
-    *reinterpret_cast<u32x4*>(sQ + c * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.Qn) + qo * D + c * 8);
-    *reinterpret_cast<u32x4*>(sG + c * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.dOn) + qo * D + c * 8);
-  }
-  const int bhx = TILEMAP ? b * L.Hkv + i / L.G : bh;
-  const long long head = (long long)bhx * p.npad_kv * D;
-  const T *kn = static_cast<const T*>(p.Kn) + head + lane * 8, *vn = static_cast<const T*>(p.Vn) + head + lane * 8;
-  const T* kt = static_cast<const T*>(p.Kt) + head + lane * 8;
-  auto block_off = [&](int t) {
-    if (!TILEMAP) return (long long)t * 32 * D;
-    return (long long)(__builtin_amdgcn_readfirstlane(p.tile_map[(long long)bh * p.tile_stride + t / 2]) * 2 + t % 2) * 32 * D;
-  };
-  bf16x8 kf[KS], vf[KS];
-  auto load_kv = [&](int t) {
-    const long long o = block_off(t);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kf[ks] = *reinterpret_cast<const bf16x8*>(kn + o + ks * 512);
-      vf[ks] = *reinterpret_cast<const bf16x8*>(vn + o + ks * 512);
-    }
-  };
-  f32x16 dq[NB];
-#pragma unroll
-  for (int db = 0; db < NB; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
-  if (wave < nblocks) load_kv(wave);
-  __syncthreads();
-  for (int t = wave; t < nblocks; t += kSplitWaves) {
-    bf16x8 ktf[2][NB];
-    const T* ktb = kt + block_off(t);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int db = 0; db < NB; ++db) ktf[u][db] = *reinterpret_cast<const bf16x8*>(ktb + (u * NB + db) * 512);
-    f32x16 s, dp;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f, dp[r] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int at = (ks * 64 + lane) * 16;
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], *reinterpret_cast<const bf16x8*>(sQ + at), s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], *reinterpret_cast<const bf16x8*>(sG + at), dp, 0, 0, 0);
-    }
-    if (t + kSplitWaves < nblocks) load_kv(t + kSplitWaves);
-    const bool masked = t >= n_full;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float pv = fast_exp2(fmaf(s[r], c2, -lse));
-      if (masked && t * 32 + 8 * (r >> 2) + (r & 3) >= qvisible) pv = 0.f;
-      dp[r] = pv * (dp[r] - delta);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const bf16x8 ds = pack8(dp, u * 8);
-#pragma unroll
-      for (int db = 0; db < NB; ++db) dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[u][db], ds, dq[db], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int db = 0; db < NB; ++db)
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const f32x4 v = {dq[db][q4 * 4], dq[db][q4 * 4 + 1], dq[db][q4 * 4 + 2], dq[db][q4 * 4 + 3]};
-      *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
-    }
-  __syncthreads();
-  T* out = static_cast<T*>(p.dQ) + b * L.qs[0] + i * L.qs[1];
-#pragma unroll
-  for (int c = threadIdx.x; c < 32 * CH; c += kSplitThreads) {
-    const int row = c / CH, d = c % CH * 8;
-    if (tq * 32 + row >= nq) continue;
-    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
-#pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) {
-      x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
-      y += *reinterpret_cast<const f32x4*>(&sO[w][row][d + 4]);
-    }
-    x *= L.scale;
-    y *= L.scale;
-    const u32x4 o = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
-    *reinterpret_cast<u32x4*>(out + (long long)qlist[tq * 32 + row] * L.qs[2] + d) = o;
-  }
-}
-
 // ------------------------------------------------------------------ dK' and dV', bf16 fast path
 //
-// The dQ kernel with the roles of keys and queries swapped: a workgroup of 8 wavefronts owns 256 packed keys of one
+// The dQ items with the roles of keys and queries swapped: a workgroup of 8 wavefronts owns 256 packed keys of one
 // query head (32 per wavefront, K and V fragments resident in registers) and streams tiles of the packed kept rows
 // memory -> LDS with LDS-DMA loads into a ring of four: Q and dO in fragment order (operands of S and dP) and k-packed (of the
 // updates), 8 KB each, so that a wavefront issues one load per operand and tile, three tiles ahead.  Per 32 queries and
@@ -849,8 +723,10 @@ __global__ __launch_bounds__(kSplitThreads, D == 64 ? 2 : 1) void attn_bwd_dq_sp
 // lse * log2e and delta of the tile's queries come with the tile (LDS-DMA of 4 bytes per lane); the causal
 // mask is a comparison of the query position with the first position that sees the lane's key.
 
+template <int D>
+constexpr int kKeyLds = 4 * (4 * 8192 + 4096 / D / 32 * 256);
 template <int D, bool TILEMAP>
-__global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdParams p) {
+__device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* smem, int* sBound, int& sItem, int* sFirst) {
   typedef u16 T;
   constexpr int CH = D / 8;
   constexpr int NB = D / 32;
@@ -864,9 +740,7 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
   constexpr int kStageBytes = kSmallOff + NSMALL * 256;
   constexpr int LPT = 4;                             // loads of a wavefront per tile
   static_assert(kOpBytes == kKeyWaves * 1024 && kKeyQ % kRows == 0, "one 1 KB load per wavefront and operand");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * kStageBytes];
-  __shared__ int sBound[2];
-  __shared__ int sItem;
+  static_assert(kKeyLds<D> == kStages * kStageBytes, "");
 
   const Layer& L = p.L;
   const int lane = lane_id();
@@ -928,8 +802,7 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
     asm volatile("" : "+v"(kf[ks]));
     asm volatile("" : "+v"(vf[ks]));
   }
-  asm volatile("" : "+v"(my_first));
-  const int first_h = my_first - 4 * h;
+  if (h == 0) sFirst[wave * 32 + ln] = my_first;           // of this wavefront only: read in the masked tiles
 
   f32x16 dk[NB], dv[NB];
 #pragma unroll
@@ -973,7 +846,8 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
     const int l = loop_lane();
     const unsigned char* stage = smem + (u % kStages) * kStageBytes;
     const unsigned char* st = stage + l * 16;                        // fragments: 16 bytes a lane, in lane order
-    const int rel = first_h - q_begin * kKeyQ - u * kRows;           // query positions below rel do not see this key
+    int rel = 0;                                     // query positions below rel do not see this lane's key
+    if (decltype(with_mask)::value) rel = sFirst[wave * 32 + (l & 31)] - (l >> 5) * 4 - q_begin * kKeyQ - u * kRows;
 #pragma unroll
     for (int qb = 0; qb < kRows / 32; ++qb) {
       // S^T and dP^T of the block's 32 queries: chunk c = operand (0: Q, 1: dO), k step
@@ -1074,6 +948,24 @@ __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_key_bf16_kernel(BwdPa
       *reinterpret_cast<f32x4*>(p.dVp + out + d) = y;
     }
   }   // items
+}
+
+// Key items, then dQ items: a workgroup that finds no key item left goes on with the other list, so that a launch has one tail
+// instead of two, filled with the shortest dQ items.  Forward and backward in us, as two launches / one: 28 heads, d = 128, 6000
+// tokens 495 / 426 (a budget per head: 398 / 310), 12000 (a budget per head) 887 / 730, 8 heads, 8000 406 / 315, d = 64, 20000
+// 1521 / 1479, 32768 6473 / 6460; blocks at d = 64, 8192 663 / 604.  On short sequences the dQ items used to be 32 rows, in a kernel
+// of their own whose wavefronts shared the keys, because 256-row items left most CUs idle; beside the key items they do not:
+// two clips of 3101, d = 64, 165 / 145, 28 heads, d = 128, 500 tokens 88 / 79, 1072 107 / 87, 3000 212 / 179, d = 64, 2000 98 / 98.
+template <int D, bool TILEMAP>
+__global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_bf16_kernel(BwdParams p) {
+  static_assert(kKeyThreads == kDqThreads, "one workgroup does both");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kDqLds<D> > kKeyLds<D> ? kDqLds<D> : kKeyLds<D>];
+  __shared__ int sBound[2];
+  __shared__ int sItem;
+  __shared__ int sFirst[kKeyTile];
+  __shared__ int sTileMap[TILEMAP ? kBwdMaxMapTiles : 1];
+  key_items<D, TILEMAP>(p, smem, sBound, sItem, sFirst);
+  dq_items<D, TILEMAP>(p, smem, sBound, sItem, sTileMap);
 }
 
 // ------------------------------------------------------------------ dK, dV = sum over the heads of a KV group
@@ -1208,7 +1100,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   BwdWs w = carve_bwd(a, L, dt, npad, nqpad, npad_kv, cap_keys / kTileN);
   constexpr bool kFast = sizeof(T) == 2;
   constexpr int tile_m = kFast ? kDqTileM : kTileM;
-  const bool split = kFast ? short_route(attention_work(L) <= kSplitWork) : f32_short(L);      // short sequences: no work list
+  const bool split = !kFast && f32_short(L);           // fp32 on short sequences: no work list
   const bool copies = kFast || split;                  // fp32 on long sequences: only K and V, row by row
   int rc = check_work_list(L, tile_m);
   if (rc != OMNI_OK) return rc;
@@ -1293,7 +1185,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   p.tile_map = w.tile_map;
   p.tile_stride = cap_keys / kTileN;
   p.npad_kv = BLOCKS ? npad_kv : npad;
-  Bounds bn{};                                 // masks by position, slot map, cleared rows, the bf16 dQ kernel's work items
+  Bounds bn{};                                 // masks by position, slot map, cleared rows, the dQ work items
   bn.q_idx = q_idx;
   bn.q_cnt = q_cnt;
   bn.klist = kv_idx;
@@ -1309,7 +1201,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   bn.tile_m = tile_m;
   bn.sched = split ? nullptr : w.sched;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
-  if (!kFast && split) {                       // no list at all: one launch
+  if (split) {                                 // no list at all: one launch
     rc = run_prepare(L, dt, true, &kv, &pq, &bn, nullptr, nullptr, st);
   } else {                                     // the lists, a few serial workgroups, hide under the packs
     // Dispatch order of the key kernel: heads in groups of 7, key tile by key tile inside a group.  Head after head leaves the
@@ -1332,13 +1224,13 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     const Order order = make_order(L, q_cnt, tile_m, w.sched);
     rc = run_prepare(L, dt, true, nullptr, nullptr, &bn, nullptr, nullptr, st);
     if (rc != OMNI_OK) return rc;
-    rc = run_prepare(L, dt, true, &kv, &pq, nullptr, split ? nullptr : &order, kFast ? &kl : nullptr, st);
+    rc = run_prepare(L, dt, true, &kv, &pq, nullptr, &order, kFast ? &kl : nullptr, st);
   }
   if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfBwdDkDv, st);
     if constexpr (sizeof(T) == 2) {
-      hipLaunchKernelGGL((attn_bwd_key_bf16_kernel<D, BLOCKS>), dim3((unsigned)persistent_grid() / 2), dim3(kKeyThreads), 0, st, p);
+      hipLaunchKernelGGL((attn_bwd_bf16_kernel<D, BLOCKS>), dim3((unsigned)persistent_grid() / 2), dim3(kKeyThreads), 0, st, p);
     } else {
       const unsigned heads = (unsigned)(L.B * L.Hq), key_blocks = heads * (unsigned)(npad / 32) * kKeyMaxSplits;
       if (split)
@@ -1349,18 +1241,12 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     }
     OMNI_LAUNCH_CHECK();
   }
-  {
-    ProfScope prof__(kProfBwdDq, st);
-    if constexpr (kFast) {
-      if (split)
-        hipLaunchKernelGGL((attn_bwd_dq_split_kernel<D, BLOCKS>), dim3((unsigned)(L.B * L.Hq) * (unsigned)cdiv(L.N, 32)),
-                           dim3(kSplitThreads), 0, st, p);
-      else
-        hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, BLOCKS>), dim3(persistent_grid() / 2), dim3(kDqThreads), 0, st, p);
-    } else if (!split) {
+  if constexpr (!kFast) {
+    if (!split) {
+      ProfScope prof__(kProfBwdDq, st);
       hipLaunchKernelGGL((attn_bwd_dq_f32_long_kernel<D>), dim3(persistent_grid() / 2), dim3(kThreads), 0, st, p);
+      OMNI_LAUNCH_CHECK();
     }
-    OMNI_LAUNCH_CHECK();
   }
   {
     ProfScope prof__(kProfBwdReduce, st);

@@ -290,7 +290,8 @@ __device__ __forceinline__ int key_slot(const Layer& L, const KeyList& p, int i,
 }
 
 // One workgroup: the list, and the length of a split: a workgroup's share of all query tiles (a longer
-// chain would outlast the others), between 8 and p.split_len.  At 3k tokens, two sequences of 28 heads, the longest chain
+// chain would outlast the others), between 5 and p.split_len (1072 tokens, 28 heads, d = 128, forward and backward at least 8 / 5
+// tiles: 108 / 98 us; elsewhere level).  At 3k tokens, two sequences of 28 heads, the longest chain
 // is head 0's 49 query tiles while a share is 9: dK' 87 -> 44 us, dV' 63 -> 34 us.
 template <int NT>
 __device__ __forceinline__ void key_list_block(const Layer& L, const KeyList& p, int (&wave_cnt)[NT / 64]) {
@@ -304,7 +305,7 @@ __device__ __forceinline__ void key_list_block(const Layer& L, const KeyList& p,
   tiles = 0;
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w) tiles += wave_cnt[w];
-  const int split_len = min(p.split_len, max(8, cdiv(tiles, p.key_wgs)));
+  const int split_len = min(p.split_len, max(5, cdiv(tiles, p.key_wgs)));
   int base = 0;
   for (int i0 = 0; i0 < n_slots; i0 += NT) {
     const int i = i0 + (int)threadIdx.x;
