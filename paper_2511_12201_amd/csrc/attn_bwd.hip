@@ -60,10 +60,9 @@ struct BwdParams {
   const int* qvis;      // [B*Hq, N] visible packed keys per kept-query position
   const int* kfirst;    // [B*Hq, npad] first kept-query position that sees a packed key
   int nsplit;           // most workgroups that share the query tiles of one key tile (bf16 key kernel)
-  int split_len;        // query tiles per split, at least (bf16: at most, see key_list_kernel)
+  int split_len;        // query tiles per split, at least (bf16: at most, see key_list_block)
   long long plane;      // floats between the partial-gradient planes of two splits
-  int* klist;           // work list of the key kernel: [0] counter, [1] number of items, [2] split length, [4..] items;
-                        // null: fp32
+  int* klist;           // work list of the key items (sched.h); null: fp32
   // In-place block lists (TILEMAP kernels): Kn, Vn, Kt hold every KV head once, in token order ([B*Hkv, npad_kv, D]),
   // and tile t of a head's key list is tile tile_map[bh * tile_stride + t] of its KV head's copy.
   const int* tile_map;
@@ -517,7 +516,7 @@ constexpr int kBwdMaxMapTiles = 2048;               // key tiles of one head in 
 template <int D>
 constexpr int kDqLds = kDqStages * 3 * kTileN * D * 2;
 template <int D, bool TILEMAP>
-__device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem, int* sBound, int& sItem, int* sTileMap) {
+__device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem, int4& sItem, int* sTileMap) {
   typedef u16 T;
   constexpr int kOpBytes = kTileN * D * 2;           // one operand tile
   constexpr int kStageBytes = 3 * kOpBytes;          // K, V, K k-packed
@@ -536,26 +535,31 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem
 
   const int lane_b = lane * 16;                      // copies and fragment reads: 16 bytes a lane, in lane order
 
+  const int n_items = p.sched[kSchedTotal];          // one queue, longest item first
   for (;;) {
   __syncthreads();
-  if (threadIdx.x == 0) sItem = sched_next(p.sched);
+  if (threadIdx.x == 0) {
+    int bh = -1, tq = 0, full = 0, all = 0;
+    const int k = atomicAdd(p.sched + kSchedCursor, 1);
+    if (k < n_items) {
+      sched_decode(p.sched, p.order_off, k, bh, tq);
+      const int* qvis = p.qvis + (long long)bh * L.N;
+      full = qvis[tq * kDqTileM];
+      all = qvis[min((tq + 1) * kDqTileM, p.q_cnt[bh]) - 1];
+    }
+    sItem = make_int4(bh, tq, full, all);
+  }
   __syncthreads();
-  const int item = __builtin_amdgcn_readfirstlane(sItem);   // wave-uniform, and known to be: tile bases stay in SGPRs
-  if (item < 0) break;
-  int bh, tq;
-  sched_decode(p.sched, p.order_off, item, bh, tq);
-  bh = __builtin_amdgcn_readfirstlane(bh);
-  tq = __builtin_amdgcn_readfirstlane(tq);
+  const int bh = __builtin_amdgcn_readfirstlane(sItem.x);   // wave-uniform, and known to be: tile bases stay in SGPRs
+  const int tq = __builtin_amdgcn_readfirstlane(sItem.y);
+  if (bh < 0) break;
   const int b = bh / L.Hq, i = bh % L.Hq;
   const int nq = p.q_cnt[bh];
   const int* qlist = p.q_idx + (long long)bh * L.N;
   const int* qvis = p.qvis + (long long)bh * L.N;
-
-  const int pos_first = tq * kDqTileM, pos_last = min(pos_first + kDqTileM, nq) - 1;
-  if (threadIdx.x == 0 || threadIdx.x == 64) sBound[threadIdx.x ? 1 : 0] = qvis[threadIdx.x ? pos_last : pos_first];
-  __syncthreads();
-  const int n_full_tiles = sBound[0] / kTileN;
-  const int ntiles = cdiv(sBound[1], kTileN);
+  const int pos_first = tq * kDqTileM;
+  const int n_full_tiles = __builtin_amdgcn_readfirstlane(sItem.z) / kTileN;
+  const int ntiles = cdiv(__builtin_amdgcn_readfirstlane(sItem.w), kTileN);
   if constexpr (TILEMAP) {                                   // this item's share of the head's tile map
     const int* tm = p.tile_map + (long long)bh * p.tile_stride;
     for (int t = threadIdx.x; t < ntiles; t += kDqThreads) sTileMap[t] = tm[t];
@@ -567,15 +571,17 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem
   const int qpos_c = min(qpos, nq - 1);
   const int qrow = qlist[qpos_c];
   const int qvisible = qvis[qpos_c] - 4 * h;
+  // the packed rows: no list entry between the item and the loads (rows past the last are garbage that nobody stores)
+  const long long packed = (long long)bh * p.nqpad + min(pos_first + wave * 32, (nq - 1) & ~31);
   const float lse2 = p.lse2c[(long long)bh * p.nqpad + qpos_c];
   const float delta = p.deltac[(long long)bh * p.nqpad + qpos_c];
-  const T* qptr = static_cast<const T*>(p.Q) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
-  const T* gptr = static_cast<const T*>(p.dO) + b * L.qs[0] + i * L.qs[1] + (long long)qrow * L.qs[2];
+  const T* qptr = static_cast<const T*>(p.Qn) + packed * D + lane * 8;
+  const T* gptr = static_cast<const T*>(p.dOn) + packed * D + lane * 8;
   bf16x8 qf[D / 16], gf[D / 16];
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) {
-    qf[ks] = *reinterpret_cast<const bf16x8*>(qptr + ks * 16 + h * 8);
-    gf[ks] = *reinterpret_cast<const bf16x8*>(gptr + ks * 16 + h * 8);
+    qf[ks] = *reinterpret_cast<const bf16x8*>(qptr + ks * 512);
+    gf[ks] = *reinterpret_cast<const bf16x8*>(gptr + ks * 512);
   }
   float lse2r = lse2, deltar = delta;
   // finish every ordinary load here: a compiler-placed wait inside the tile loop would drain the ring
@@ -726,7 +732,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem
 template <int D>
 constexpr int kKeyLds = 4 * (4 * 8192 + 4096 / D / 32 * 256);
 template <int D, bool TILEMAP>
-__device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* smem, int* sBound, int& sItem, int* sFirst) {
+__device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* smem, int4& sItem, int* sFirst) {
   typedef u16 T;
   constexpr int CH = D / 8;
   constexpr int NB = D / 32;
@@ -749,36 +755,24 @@ __device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* sme
   const float c2 = L.scale * kLog2e;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  for (;;) {                                   // persistent: one item of the work list per iteration
+  // Persistent: one item of the work list per iteration.  (Claimed while the one before is worked on, a workgroup with a long item
+  // keeps another from those that are free: 3000 tokens, 28 heads 183 -> 215 us.)
+  const int n_items = p.klist[1];
+  for (;;) {
   __syncthreads();                             // LDS of the previous item is no longer read
   if (threadIdx.x == 0) {
     const int k = atomicAdd(&p.klist[0], 1);
-    sItem = k < p.klist[1] ? p.klist[kKeyListHeader + k] : -1;
+    sItem = k < n_items ? reinterpret_cast<const int4*>(p.klist + kKeyListHeader)[k] : make_int4(-1, 0, 0, 0);
   }
   __syncthreads();
-  const int item = __builtin_amdgcn_readfirstlane(sItem);
+  const int item = __builtin_amdgcn_readfirstlane(sItem.x);
   if (item < 0) break;
   const int bh = item >> 16, ktile = (item >> 3) & 0x1fff, sp = item & 7;
   const int b = bh / L.Hq;
-  const int nkeys = min(p.budget[budget_slot(L.bph, b, bh)], p.b_cap);
-  const int nq = p.q_cnt[bh];
-  const int slot0 = ktile * kKeyTile;
-  const int slot = slot0 + wave * 32 + ln;                  // this lane's key slot (< npad by construction)
-  const int* kfirst = p.kfirst + (long long)bh * p.npad;
-  if (threadIdx.x == 0 || threadIdx.x == 64) {
-    const int last_slot = min(slot0 + kKeyTile, nkeys) - 1;
-    sBound[threadIdx.x ? 1 : 0] = kfirst[threadIdx.x ? last_slot : slot0];
-  }
-  int my_first = kfirst[slot];
-  __syncthreads();
-  const bool has_pad = slot0 + kKeyTile > nkeys;
-  const int q_full_pos = has_pad ? 0x7fffffff : sBound[1];  // tiles starting at or after this position need no mask
-  const int n_qtiles = cdiv(nq, kKeyQ);
-  const int q_first = sBound[0] / kKeyQ;                    // first query tile with an admissible pair
-  const int n_all = n_qtiles - q_first;
-  const int n_sp = key_tile_splits(n_all, p.nsplit, p.klist[2]);
-  const int per_split = cdiv(n_all, n_sp);
-  const int q_begin = q_first + sp * per_split;             // this workgroup's query tiles: [q_begin, q_begin + per_split)
+  const int q_begin = __builtin_amdgcn_readfirstlane(sItem.y), n_q = __builtin_amdgcn_readfirstlane(sItem.z);
+  const int q_full_pos = __builtin_amdgcn_readfirstlane(sItem.w);   // tiles starting at or after this position need no mask
+  const int slot = ktile * kKeyTile + wave * 32 + ln;       // this lane's key slot (< npad by construction)
+  int my_first = p.kfirst[(long long)bh * p.npad + slot];
 
   // resident K and V fragments: B operands, lane = key column
   long long kv_row = (long long)bh * p.npad + slot;
@@ -819,7 +813,7 @@ __device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* sme
   const float* small = p.lse2c + q_row + wave % NSMALL * 32;       // every wavefront brings one: the same count of loads for all
   const unsigned delta_off = (unsigned)((p.deltac - p.lse2c) * 4);     // delta lies behind lse (carve_bwd)
 
-  const int n = min(per_split, n_qtiles - q_begin) * (kKeyQ / kRows);
+  const int n = n_q * (kKeyQ / kRows);
   // u = tile index relative to the workgroup's first (ring position); past the end the last tile comes again, into a stage
   // that nobody reads any more, so that the loads in flight are the same number in every step
   auto issue_part = [&](int u, int op) {
@@ -960,12 +954,11 @@ template <int D, bool TILEMAP>
 __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_bf16_kernel(BwdParams p) {
   static_assert(kKeyThreads == kDqThreads, "one workgroup does both");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kDqLds<D> > kKeyLds<D> ? kDqLds<D> : kKeyLds<D>];
-  __shared__ int sBound[2];
-  __shared__ int sItem;
+  __shared__ int4 sItem;
   __shared__ int sFirst[kKeyTile];
   __shared__ int sTileMap[TILEMAP ? kBwdMaxMapTiles : 1];
-  key_items<D, TILEMAP>(p, smem, sBound, sItem, sFirst);
-  dq_items<D, TILEMAP>(p, smem, sBound, sItem, sTileMap);
+  key_items<D, TILEMAP>(p, smem, sItem, sFirst);
+  dq_items<D, TILEMAP>(p, smem, sItem, sTileMap);
 }
 
 // ------------------------------------------------------------------ dK, dV = sum over the heads of a KV group
@@ -1064,7 +1057,7 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.qvis = a.take<int>(BH * L.N);
   w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
-  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * kKeyMaxSplits);
+  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * kKeyMaxSplits * kKeyItemInts);
   w.vbudget = a.take<int>(L.B);
   w.tile_map = a.take<int>(npad_kv > 0 ? BH * cap_tiles : 4);
   return w;

@@ -75,6 +75,9 @@ Order make_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, int q
 constexpr int kKeyTile = 256;                // packed keys per workgroup
 constexpr int kKeyQ = 64;                    // queries per tile, as the splits count them
 constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, -
+// An item is four ints, all that a workgroup has to know before its first load: head << 16 | key tile << 3 | split, first query
+// tile, number of query tiles, first query position from which on nothing is masked.
+constexpr int kKeyItemInts = 4;
 struct KeyList {
   const int *q_cnt, *budget;
   int b_cap, npad;

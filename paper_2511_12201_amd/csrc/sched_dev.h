@@ -321,7 +321,15 @@ __device__ __forceinline__ void key_list_block(const Layer& L, const KeyList& p,
       at += w < wave ? wave_cnt[w] : 0;
       base += wave_cnt[w];
     }
-    for (int sp = 0; sp < n_sp; ++sp) p.klist[kKeyListHeader + at + sp] = (bh << 16) | (ktile << 3) | sp;
+    if (n_sp) {
+      const int* kfirst = p.kfirst + (long long)bh * p.npad + ktile * kKeyTile;
+      const int nkeys = min(p.budget[budget_slot(L.bph, bh / L.Hq, bh)], p.b_cap) - ktile * kKeyTile;
+      const int q_tiles = cdiv(p.q_cnt[bh], kKeyQ), first = kfirst[0] / kKeyQ, each = cdiv(q_tiles - first, n_sp);
+      const int unmasked = nkeys < kKeyTile ? 0x7fffffff : kfirst[kKeyTile - 1];
+      int4* items = reinterpret_cast<int4*>(p.klist + kKeyListHeader) + at;
+      for (int sp = 0; sp < n_sp; ++sp)
+        items[sp] = make_int4((bh << 16) | (ktile << 3) | sp, first + sp * each, min(each, q_tiles - first - sp * each), unmasked);
+    }
   }
   if (threadIdx.x == 0) {
     p.klist[0] = 0;
