@@ -530,12 +530,12 @@ __device__ __forceinline__ void decode_head_rows(const DecodeParams& p, int slic
 // before), p.active where `store`.  A wavefront takes every fourth head, with the loads of all of them in flight together
 // and the sums in the order of one head after the other.
 template <typename T, int D, int GT>
-__device__ __forceinline__ void classify_heads(const DecodeParams& p, int b, int g, int head0, bool store,
-                                               unsigned& active_bits) {
-  constexpr int kWaves = kThreads / 64, kMine = (GT + kWaves - 1) / kWaves, kPer = D / 64;
+struct HeadClasses {
+  static constexpr int kWaves = kThreads / 64, kMine = (GT + kWaves - 1) / kWaves, kPer = D / 64;
+  float diff[kPer], qv[kMine][kPer];
+  __device__ __forceinline__ void load(const DecodeParams& p, int b, int g, int head0) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float* pk = p.probe + ((long long)(b * p.Hkv + g) * 2) * D;
-  float diff[kPer], qv[kMine][kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) diff[k] = pk[D + lane + 64 * k] - pk[lane + 64 * k];
 #pragma unroll
@@ -545,6 +545,9 @@ __device__ __forceinline__ void classify_heads(const DecodeParams& p, int b, int
     for (int k = 0; k < kPer; ++k)
       qv[u][k] = Elem<T>::load(static_cast<const T*>(p.q) + (long long)(b * p.Hq + head0 + h) * D + lane + 64 * k);
   }
+  }
+  __device__ __forceinline__ void finish(const DecodeParams& p, int b, int head0, bool store, unsigned& active_bits) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
   for (int u = 0; u < kMine; ++u) {
     const int h = wave + u * kWaves, i = head0 + h;
@@ -559,6 +562,14 @@ __device__ __forceinline__ void classify_heads(const DecodeParams& p, int b, int
       if (store && p.active) p.active[b * p.Hq + i] = (unsigned char)act;
     }
   }
+  }
+};
+template <typename T, int D, int GT>
+__device__ __forceinline__ void classify_heads(const DecodeParams& p, int b, int g, int head0, bool store,
+                                               unsigned& active_bits) {
+  HeadClasses<T, D, GT> c;
+  c.load(p, b, g, head0);
+  c.finish(p, b, head0, store, active_bits);
 }
 
 // The union list of a KV group, GT heads per workgroup: slice `slice` of unit `unit`.  Classifies the
@@ -632,20 +643,28 @@ __device__ __forceinline__ void decode_group_rows(const DecodeParams& p, int sli
 // token t), the marked tokens are compacted, in ascending order, into an LDS list with their member words, and the
 // rows are streamed exactly as from a stored group list -- a row is loaded once, whichever of the heads store it.
 // Reading the lists costs 4 bytes per stored entry and active head, against 4 D bytes per row.
-constexpr int kMergeSpan = 1024;            // tokens of a span
-constexpr int kMergeWindow = kMergeSpan;    // list entries read per head and span: no more can fall into it
+// SPAN: tokens of a span, and list entries read per head and span (no more can fall into it).  Slices of at most kShortSpan tokens
+// (short caches: the row slices are as many as there is work for) take spans of that length: a window of 1024 entries for 64
+// tokens was most of the kernel's loads, registers and code.  They also search the lists of all heads under the classification
+// instead of those of the active heads after it; with long slices the searches of lazy heads' lists would cost cache lines.
+// Decode step in us, spans of 1024 / 128: 28 heads, 1000 tokens 14.3 / 12.7, 4108 (slices of 64) 17.5 / 14.3, 16000 (84) 28.8 /
+// 26.5; and two or more spans of 128 where a slice is longer: 30000 (154) 29.7 / 33.7, four sequences of 8000 (165) 28.2 / 32.0.
+// (A short span of 64: slices of 84 tokens 22.8 / 24.9; of 256: 4108 15.0.)
+constexpr int kMergeSpan = 1024, kShortSpan = 128;
 
 // First positions of two ascending lists a0[0, n0), a1[0, n1) whose values are >= v, found together by one
 // wavefront (all lanes take part and get both results): 64 probes per list and round, the loads of both lists in
 // flight at once.  Three rounds for lists of up to 2^18 entries.  (More probes per round would save a round but
 // every probe is a cache line of its own: with a thousand workgroups searching seven lists each, 256 probes per
 // round move more bytes than the rows of the step.)
+// under: work that does not need the answers, done while the first probes are on their way.
+template <typename Under>
 __device__ __forceinline__ void wave_lower_bound2(const int* __restrict__ a0, int n0, const int* __restrict__ a1, int n1,
-                                                  int v, int& r0, int& r1) {
+                                                  int v, int& r0, int& r1, Under under) {
   const int lane = threadIdx.x & 63;
   const int* a[2] = {a0, a1};
   int lo[2] = {0, 0}, hi[2] = {n0, n1};                 // the answers lie in [lo, hi]
-  for (;;) {
+  for (bool first = true;; first = false) {
     const bool last = hi[0] - lo[0] <= 64 && hi[1] - lo[1] <= 64;        // wave-uniform
     int val[2], step[2];
 #pragma unroll
@@ -654,6 +673,7 @@ __device__ __forceinline__ void wave_lower_bound2(const int* __restrict__ a0, in
       const int idx = lo[w] + lane * step[w];
       val[w] = idx < hi[w] ? a[w][idx] : 0x7fffffff;
     }
+    if (first) under();
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
       const int below = __popcll(__ballot(val[w] < v));  // probes ascend with the lane: those below v are a prefix
@@ -671,14 +691,14 @@ __device__ __forceinline__ void wave_lower_bound2(const int* __restrict__ a0, in
   r1 = lo[1];
 }
 
-template <typename T, int D, int GT>
+template <typename T, int D, int GT, int SPAN>
 __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int slice, int unit) {
   __shared__ unsigned sBits;
   __shared__ int sCur[GT];                              // per head: first list entry not yet consumed
   __shared__ int sCount;
   __shared__ int sWaveSum[kThreads / 64];
-  __shared__ unsigned sWord[kMergeSpan];                // bitmap of a span, then the member words of its list
-  __shared__ int sTok[kMergeSpan];
+  __shared__ unsigned sWord[SPAN];                // bitmap of a span, then the member words of its list
+  __shared__ int sTok[SPAN];
   const int chunks = p.G / GT;
   const int chunk = unit % chunks, bg = unit / chunks;
   const int b = bg / p.Hkv, g = bg % p.Hkv;
@@ -689,7 +709,7 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
   const int span_tokens = max(0, vis_hi - p.v0);
   const int per = cdiv(max(1, p.v1 - p.v0), p.n_head);   // tokens per slice
   const int t_begin = p.v0 + min(span_tokens, slice * per), t_end = p.v0 + min(span_tokens, (slice + 1) * per);
-  const int nsub_all = cdiv(t_end - t_begin, kMergeSpan);
+  const int nsub_all = cdiv(t_end - t_begin, SPAN);
   if (threadIdx.x == 0) sBits = 0u;
   __syncthreads();
   int cnt_all[2];                                       // asked for early: one latency less in the chain below
@@ -698,10 +718,15 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
     const int h = wave + w * (kThreads / 64);
     cnt_all[w] = p.vis_cnt[b * p.Hq + head0 + (h < GT ? h : 0)];
   }
-  classify_heads<T, D, GT>(p, b, g, head0, slice == 0, sBits);
-  __syncthreads();
-  const unsigned bits = sBits;
-  const int nsub = bits ? nsub_all : 0;
+  constexpr bool kShort = SPAN == kShortSpan;
+  HeadClasses<T, D, GT> classes;
+  classes.load(p, b, g, head0);
+  if constexpr (!kShort) {
+    classes.finish(p, b, head0, slice == 0, sBits);
+    __syncthreads();
+  }
+  unsigned bits = kShort ? (1u << GT) - 1u : sBits;
+  int nsub = bits ? nsub_all : 0;
   // A wavefront looks after heads `wave` and `wave + 4` of the tile (GT <= 8), both at once; a head that is lazy,
   // or beyond GT, is an empty list.
   static_assert(GT <= 2 * (kThreads / 64), "two heads per wavefront");
@@ -715,24 +740,32 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
     hlist[w] = p.vis_idx + (long long)bh * p.b_cap;
     hcnt[w] = on ? max(0, min(cnt_all[w], p.b_cap)) : 0;
   }
-  if (nsub > 0) {                                       // where the lists enter the slice
+  if (nsub > 0 || kShort) {                             // where the lists enter the slice
     int c0, c1;
-    wave_lower_bound2(hlist[0], hcnt[0], hlist[1], hcnt[1], t_begin, c0, c1);
+    wave_lower_bound2(hlist[0], hcnt[0], hlist[1], hcnt[1], t_begin, c0, c1, [&]() {
+      if constexpr (kShort) classes.finish(p, b, head0, slice == 0, sBits);
+    });
     if (lane == 0) {
       if (wave < GT) sCur[wave] = c0;
       if (wave + kThreads / 64 < GT) sCur[wave + kThreads / 64] = c1;
     }
   }
   __syncthreads();
+  if constexpr (kShort) {
+    bits = sBits;
+    nsub = bits ? nsub_all : 0;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) hcnt[w] = (bits >> (wave + w * (kThreads / 64))) & 1u ? hcnt[w] : 0;
+  }
   auto prep = [&](int sub, int& begin, int& end) {
-    const int t_lo = t_begin + sub * kMergeSpan, t_hi = min(t_end, t_lo + kMergeSpan);
+    const int t_lo = t_begin + sub * SPAN, t_hi = min(t_end, t_lo + SPAN);
     __syncthreads();                                    // the previous span's list is no longer read
-    for (int t = threadIdx.x; t < kMergeSpan; t += kThreads) sWord[t] = 0u;
+    for (int t = threadIdx.x; t < SPAN; t += kThreads) sWord[t] = 0u;
     __syncthreads();
     {
-      // ascending entries: those of this span are among the next kMergeWindow entries of a list.  The loads of both
+      // ascending entries: those of this span are among the next SPAN entries of a list.  The loads of both
       // lists of the wavefront are issued before any is used.
-      constexpr int NK = kMergeWindow / 64;
+      constexpr int NK = SPAN / 64;
       int tok[2][NK], cur[2];
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
@@ -759,13 +792,13 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
       }
     }
     __syncthreads();
-    // compaction in token order: every thread owns kMergeSpan / kThreads consecutive words
-    constexpr int PER = kMergeSpan / kThreads;
+    // compaction in token order: every thread owns SPAN / kThreads consecutive words
+    constexpr int PER = SPAN > kThreads ? SPAN / kThreads : 1;
     unsigned w[PER];
     int mine = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      w[j] = sWord[threadIdx.x * PER + j];
+      w[j] = SPAN >= kThreads || (int)threadIdx.x < SPAN ? sWord[threadIdx.x * PER + j] : 0u;
       mine += w[j] != 0u;
     }
     int incl = mine;
@@ -884,7 +917,7 @@ int group_tile(int G) {
   return 1;
 }
 
-constexpr int kNoLists = 0, kStoredGroupLists = 1, kMergedHeadLists = 2;
+constexpr int kNoLists = 0, kStoredGroupLists = 1, kMergedHeadLists = 2, kMergedShort = 3;
 
 // One launch for the row streams of a step that share a register footprint.  With lists (the stored group lists, or
 // the per-head lists of a group merged on the fly -- a kernel of its own, so that its bookkeeping does not cost the
@@ -904,9 +937,9 @@ __global__ __launch_bounds__(kThreads, 3) void decode_rows_kernel(DecodeParams p
       return;
     }
   }
-  if constexpr (LISTS == kMergedHeadLists) {
+  if constexpr (LISTS == kMergedHeadLists || LISTS == kMergedShort) {
     if (i < n_list) {
-      decode_merged_rows<T, D, GT>(p, i % p.n_head, i / p.n_head);
+      decode_merged_rows<T, D, GT, LISTS == kMergedShort ? kShortSpan : kMergeSpan>(p, i % p.n_head, i / p.n_head);
       return;
     }
   }
@@ -931,8 +964,11 @@ void launch_rows(const DecodeParams& p, hipStream_t st) {
     return;
   }
   if (p.n_head > 0 && GT >= 2) {
-    hipLaunchKernelGGL((decode_rows_kernel<T, D, GT, kMergedHeadLists>), dim3(n_shared + p.n_head * units_s),
-                       dim3(kThreads), 0, st, p);
+    const dim3 grid(n_shared + p.n_head * units_s);
+    if (cdiv(p.v1 - p.v0, p.n_head) <= kShortSpan)
+      hipLaunchKernelGGL((decode_rows_kernel<T, D, GT, kMergedShort>), grid, dim3(kThreads), 0, st, p);
+    else
+      hipLaunchKernelGGL((decode_rows_kernel<T, D, GT, kMergedHeadLists>), grid, dim3(kThreads), 0, st, p);
     return;
   }
   if (p.n_head > 0)      // per-head lists: the long kernel first

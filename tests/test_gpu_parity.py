@@ -1759,3 +1759,34 @@ def test_selection_and_attention_on_odd_layouts(layout, dtype):
         fin = np.isfinite(Lo)
         assert np.array_equal(np.isfinite(to_host(lse)), fin)
         assert np.max(np.abs(to_host(lse)[fin] - Lo[fin])) <= (1e-4 if dtype == "f32" else 2e-3)
+
+
+@pytest.mark.parametrize("nv", [1, 64, 65, 8191, 32768, 32769])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_on_lists_as_they_are_around_the_short_slices(nv, d):
+    """One KV group of seven heads, 256 slices at most: slices of 1 to 128 tokens take spans of 128 and search all lists, those of
+    129 spans of 1024; a head that stores everything, one that stores nothing, stored rows beyond the context."""
+    H, cap, rng = 7, nv + 40, np.random.default_rng(nv)
+    g = torch.Generator(device="cuda").manual_seed(nv)
+    K, V = (torch.randn(1, 1, cap, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(1, H, d, generator=g, device="cuda").bfloat16()
+    probe = torch.randn(1, 1, 2, d, generator=g, device="cuda")
+    keep = rng.random((H, nv)) < rng.random((H, 1))
+    keep[0], keep[1] = True, False
+    lists = [[np.flatnonzero(keep[h]).astype(np.int32) for h in range(H)]]
+    vis_idx, vis_cnt = lists_to_padded(lists, H, nv)
+    for ctx in (nv + 33, max(1, nv - 5)):
+        desc = ob.make_decode_desc(q, K, 0, nv, 0.2)
+        O, active = ob.omni_slim_decode(desc, q, K, V, torch.tensor([ctx], dtype=torch.int32, device="cuda"), probe, vis_idx,
+                                        vis_cnt, nv)
+        for h in range(H):
+            z = probe[0, 0].double() @ q[0, h].double() * d ** -0.5
+            act = h == 0 or float(torch.sigmoid(z[1] - z[0])) > 0.2
+            assert bool(active[0, h]) == act
+            seen = np.ones(ctx, dtype=bool)
+            seen[:min(nv, ctx)] = keep[h, :ctx] if act else False
+            rows = torch.from_numpy(np.flatnonzero(seen)).cuda()
+            want = torch.zeros(d, dtype=torch.float64, device="cuda")
+            if len(rows):
+                want = torch.softmax(K[0, 0, rows].double() @ q[0, h].double() * d ** -0.5, -1) @ V[0, 0, rows].double()
+            assert float((O[0, h].double() - want).abs().max()) <= 2e-2
