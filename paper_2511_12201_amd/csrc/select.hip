@@ -42,12 +42,15 @@ __device__ __forceinline__ float key_value(unsigned key) {         // inverse of
 // vector; the elements of the bin it picks are copied to LDS, and once no more than kFew are left they are ranked against
 // each other.  28 heads, kurtosis + budget + cuts of both lists, as four passes of 8 bits over the whole vector and
 // kernels of their own for arg-min, counts, scans and lists (nine launches) / digits of 11, 11 and 10 bits and a kernel for
-// the lists / now: 1k scores 53 / 28 / 21 us, 64k 150 / 95 / 77 us; the three calls on scores in hand at 32k 79 -> 59 us.
+// the lists / now: 1k scores 53 / 28 / 21 us, 64k 150 / 95 / 77 us; the three calls on scores in hand at 32k 79 -> 60 us.
+// What a pass costs beside its sweep is barriers and latencies, 1 to 2 us: hence 256 elements that are ranked against each other
+// (64 left one pass more to most vectors beyond 8192) and the first loads of a sweep under the clearing and the picking before it.
+// The three calls, before / now: 10451 tokens 55.6 / 51.7 us, 23036 69.5 / 65.3, 48349 96.5 / 91.1.
 constexpr int kBins = 2048;
 constexpr int kPitch = kBins + 8;       // words between two replicas of the count histogram: other banks for a bin's replicas
 constexpr int kReps = 4;                // replicas of a bin, so that lanes on one bin rarely meet on an address
 constexpr int kCand = 8192;
-constexpr int kFew = 64;                // elements that are ranked against each other instead of histogrammed
+constexpr int kFew = 256;               // elements that are ranked against each other, by four threads each, instead of histogrammed
 struct __attribute__((aligned(16))) RadixShared {
   union {
     unsigned cnt[kReps * kPitch];
@@ -110,35 +113,45 @@ __device__ __forceinline__ void sweep(const float* x, int n, F f) {
     f(v, some);
   }
 }
-// In memory: four neighbours per load, the next sixteen elements of a thread in flight under those in hand, nothing checked but in
-// the last stretch.  Bound by the vector ALU of the one CU (a few dozen instructions per 64 elements).
-template <typename F>
-__device__ __forceinline__ void sweep_memory(const float* __restrict__ x, int n, F f) {
-  constexpr int kLoads = 4, kStep = 4 * kLoads * kSelThreads;
-  f32x4_any next[kLoads];
-  auto load = [&](int at) {
+// In memory, at least four elements: four neighbours per load, the next sixteen elements of a thread in flight under those in hand, and
+// the first ones under whatever comes before the sweep (the caller starts them).  Nothing is checked but in the last stretch: a load
+// that would pass the end is moved back to it, and of its elements those count that an earlier load does not have.  Bound by the
+// vector ALU of the one CU (a few dozen instructions per 64 elements).
+constexpr int kLoads = 4, kStep = 4 * kLoads * kSelThreads;
+struct Ahead {
+  f32x4_any quad[kLoads];
+  __device__ __forceinline__ void load(const float* __restrict__ x, int n, int at) {
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u)
-      next[u] = element<f32x4_any>(x, at + 4 * (u * kSelThreads + (int)threadIdx.x));
-  };
-  const int whole = n / kStep * kStep;
-  if (whole) load(0);
+    for (int u = 0; u < kLoads; ++u) quad[u] = element<f32x4_any>(x, min(at + 4 * (u * kSelThreads + (int)threadIdx.x), n - 4));
+  }
+};
+template <typename F>
+__device__ __forceinline__ void sweep_memory(const float* __restrict__ x, int n, Ahead& next, F f) {
 #pragma unroll 1
-  for (int at = 0; at < whole; at += kStep) {
+  for (int at = 0; at < n; at += kStep) {
     Batch v[2];
 #pragma unroll
-    for (int e = 0; e < 2 * kBatch; ++e) v[e / kBatch][e % kBatch] = next[e / 4][e % 4];
-    if (at + kStep < whole) load(at + kStep);
+    for (int e = 0; e < 2 * kBatch; ++e) v[e / kBatch][e % kBatch] = next.quad[e / 4][e % 4];
+    if (at + kStep < n) {
+      next.load(x, n, at + kStep);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2 * kBatch; ++e) {
+        const int i = at + 4 * (e / 4 * kSelThreads + (int)threadIdx.x);
+        if (min(i, n - 4) + e % 4 < i) v[e / kBatch][e % kBatch] = __uint_as_float(0xffffffffu);
+      }
+    }
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
+      const int some = min(kBatch, 4 * cdiv(n - at - half * kStep / 2, 4 * kSelThreads));
+      if (some <= 0) break;
       if (half) {
 #pragma unroll
         for (int e = 0; e < kBatch; ++e) v[0][e] = v[1][e];
       }
-      f(v[0], kBatch);
+      f(v[0], some);
     }
   }
-  if (whole < n) sweep(x + whole, n - whole, f);
 }
 
 // Every element in memory, nothing in the place of those past the end.
@@ -234,6 +247,8 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
   } else {
     sample[0] = x[(long long)n * threadIdx.x / kSelThreads];
   }
+  Ahead ahead;
+  if (!staged) ahead.load(x, n, 0);
   __syncthreads();
   if (threadIdx.x == 0) {
     sh.rem = target;
@@ -277,7 +292,7 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
     const int rep = ((int)threadIdx.x & (reps - 1)) * kPitch;
     const bool first = pass == 0 && !staged;       // the whole vector, in memory
     if (first) {
-      sweep_memory(x, n, [&](const Batch& v, int some) {
+      sweep_memory(x, n, ahead, [&](const Batch& v, int some) {
 #pragma unroll
         for (int e = 0; e < kBatch; ++e) {
           if (e >= some) break;
@@ -296,6 +311,7 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
         }
       });
     }
+    if (first) ahead.load(x, n, 0);
     // infinite and huge elements: the sums may have left 64 bits
     if (MASS && (top >= 16777216.f || to_fixed(top) >= target)) sh.alone = 1;
     const bool found = histogram_pick<MASS>(sh, reps);
@@ -335,7 +351,7 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
         }
       }
     };
-    if (first) sweep_memory(x, n, part);
+    if (first) sweep_memory(x, n, ahead, part);
     else sweep(src, m, part);
     __syncthreads();
     left = sh.count;
@@ -349,38 +365,44 @@ __device__ RadixCut radix_cut(const float* x, int n, unsigned long long target, 
   }
   if (threadIdx.x == 0) sh.key = lo;
   if (left <= kFew && lo != hi) {
-    // Every element left against every other: the one whose own share crosses sh.rem is the cut (equal elements all
-    // write the same values).
+    // Every element left against every other, by four lanes: the one whose own share crosses sh.rem is the cut (equal elements
+    // all write the same values).
     const float* few = src;                        // the short list, or the long one where that was enough
     const unsigned long long rem = sh.rem;
     __syncthreads();
     if ((int)threadIdx.x < left) {
       const float own = few[threadIdx.x];
-      const unsigned mine = float_key(own);
-      sh.few_key[threadIdx.x] = mine;
+      sh.few_key[threadIdx.x] = float_key(own);
       sh.few_mass[threadIdx.x] = to_fixed(own);
     }
     __syncthreads();
+    const int who = (int)threadIdx.x >> 2;
     unsigned mine = 0;
-    if ((int)threadIdx.x < left) {
-      mine = sh.few_key[threadIdx.x];
+    if (who < left) {
+      mine = sh.few_key[who];
       unsigned more = 0, same = 0;
       unsigned long long mass = 0;
 #pragma unroll 8
-      for (int t = 0; t < left; ++t) {
+      for (int t = (int)threadIdx.x & 3; t < left; t += 4) {
         const unsigned k = sh.few_key[t];
         more += k > mine;
         same += k == mine;
         if (MASS) mass += k > mine ? sh.few_mass[t] : 0ull;
       }
-      const unsigned long long excl = MASS ? mass : more, own = MASS ? same * sh.few_mass[threadIdx.x] : same;
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) {
+        more += __shfl_xor(more, o, 4);
+        same += __shfl_xor(same, o, 4);
+        if (MASS) mass += __shfl_xor(mass, o, 4);
+      }
+      const unsigned long long excl = MASS ? mass : more, own = MASS ? same * sh.few_mass[who] : same;
       if (excl < rem && rem <= excl + own) {
         sh.key = mine;
         sh.rem = rem - excl;
       }
     }
     __syncthreads();
-    if ((int)threadIdx.x < left && mine > sh.key) other += MASS ? 1ull : sh.few_mass[threadIdx.x];
+    if (who < left && ((int)threadIdx.x & 3) == 0 && mine > sh.key) other += MASS ? 1ull : sh.few_mass[who];
   }
   other = block_sum(other, sh);
   const RadixCut cut{true, false, sh.key, sh.rem, other};

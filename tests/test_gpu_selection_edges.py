@@ -79,6 +79,31 @@ def test_cuts_among_scores_that_no_sample_shows(N):
             assert abs(float(r.recall[0, h]) - np.sort(c[0, h].astype(np.float64))[::-1][:b].sum() / N) <= 2.0 ** -23
 
 
+@pytest.mark.parametrize("m", [1, 64, 65, 255, 256, 257, 1025])
+@pytest.mark.parametrize("N", [2000, 8192, 8193, 8194, 8195, 16385, 24579])
+def test_cuts_in_a_bin_that_holds_a_given_number_of_scores(N, m):
+    """m neighbouring scores, some of them equal, far from all others: as many as are ranked against each other in one go, fewer and
+    more, in vectors whose last load is whole, moved back by one, two or three elements, or not there."""
+    H, rng = 2, np.random.default_rng(N + m)
+    a = np.exp(2 * rng.standard_normal((1, H, N)))
+    a[(a > 1.0) & (a < 4.0)] *= 4.0
+    at = np.stack([rng.choice(N, m, replace=False) for _ in range(H)])
+    for h in range(H):
+        a[0, h, at[h]] = 2.0 + 2.0 ** -18 * (rng.integers(0, 2 * m, m) // 2)
+    a = a.astype(np.float32)
+    d = _desc(H, N, 0, N)
+    for h in range(H):
+        above = int((a[0, h] >= 2.5).sum())
+        for b in sorted({above + 1, above + (m + 1) // 2, above + m, min(N, above + m + 1)}):
+            kv = ob.omni_select_kv(d, torch.from_numpy(a).cuda(), torch.tensor([b], dtype=torch.int32, device="cuda"), N)
+            np.testing.assert_array_equal(kv[0, h, :b].cpu().numpy(), np.sort(np.lexsort((np.arange(N), -a[0, h]))[:b]))
+        c = np.ascontiguousarray(a * (N / a.sum(-1, keepdims=True, dtype=np.float64)), dtype=np.float32)
+        top = np.sort(c[0, h].astype(np.float64))[::-1][: above + (m + 1) // 2]
+        p = float((top.sum() - 0.5 * top[-1]) / N)      # a cut amid the group, half an element away from the next
+        r = ob.omni_budget_from_scores(d, torch.from_numpy(c).cuda(), p, 2)
+        assert int(r.budget[0, h]) == oc.budget_of(c[0, h], p, N)
+
+
 def test_lists_with_infinite_negative_and_nan_scores():
     """The order of the keys is that of the floats, NaN above infinity; counts and ties follow it."""
     N, H = 3000, 2
