@@ -26,8 +26,8 @@
 //    memory straight into a ring of four LDS stages (global_load_lds, hand-placed
 //    s_waitcnt), one barrier per tile; inside a wavefront the softmax of tile t
 //    runs under the MFMAs of tile t+1.  Work items come from a persistent,
-//    longest-first work list with one queue per XCD (sched.hip); causal masks are
-//    position compares against per-query visible-prefix counts (bounds_kernel, sched.hip).
+//    longest-first work list with one queue per XCD (sched_dev.h); causal masks are
+//    position compares against per-query visible-prefix counts (bounds_block, sched_dev.h).
 //    Short sequences go through attn_fwd_split_kernel: 32-row items, key tiles dealt to the wavefronts.
 //  * fp32 inputs (the accuracy path of the 1e-4 parity cases): the fp32 32x32x2 MFMA.  Short sequences
 //    (attn_fwd_f32_kernel) have the division of labour of the split kernel, long ones (attn_fwd_f32_long_kernel) 128-row
@@ -78,10 +78,9 @@ struct FwdParams {
 // single barrier per tile is enough.  The loads are inline assembly with hand-placed
 // s_waitcnt vmcnt(n): the compiler would wait for *every* outstanding LDS-DMA load before the
 // first LDS read, which collapses the ring to one tile of prefetch.
-// A wavefront's LDS-DMA instruction writes 64 x 16 contiguous bytes, so the K tile cannot be
-// row-padded; it is stored unpadded with an XOR swizzle of the 16-byte chunk index
-// (chunk ^ row % chunks_per_row), applied on the global-address side of the copy, which keeps
-// the 16 rows a ds_read_b128 touches on distinct banks.  V is already in operand order.
+// A wavefront's LDS-DMA instruction writes 64 x 16 contiguous bytes, and a fragment is 64 x 16 bytes lane by lane: the
+// packs lay K out in fragment order and V k-packed, a fragment a contiguous kilobyte, so the tile needs no swizzle, its
+// reads meet no bank twice and one address register serves it all.
 
 constexpr int kFastWaves = 8;
 constexpr int kFastThreads = kFastWaves * 64;
