@@ -1057,7 +1057,8 @@ BwdWs carve_bwd(Arena& a, const Layer& L, int dtype, int npad, int nqpad, int np
   w.qvis = a.take<int>(BH * L.N);
   w.kfirst = a.take<int>(krows);
   w.inv = a.take<int>(BH * L.N);
-  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * kKeyMaxSplits * kKeyItemInts);
+  // a tile's splits are no more than its query tiles
+  w.klist = a.take<int>(kKeyListHeader + key_list_slots(L, npad) * std::min(kKeyMaxSplits, cdiv(L.N, kKeyQ)) * kKeyItemInts);
   w.vbudget = a.take<int>(L.B);
   w.tile_map = a.take<int>(npad_kv > 0 ? BH * cap_tiles : 4);
   return w;

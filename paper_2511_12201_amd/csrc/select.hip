@@ -434,8 +434,8 @@ struct ListJob {
 // Cut of a head's own budget, as the budget search leaves it: elements above `key` and `need` of those at it.
 // need < 0: not known (the whole vector, or one element that is infinite or beyond the fixed point).
 struct OwnCut {
-  unsigned key;
-  int need;
+  unsigned* key;         // [B*H]
+  int* need;             // [B*H]
 };
 __device__ __forceinline__ float recall_of(unsigned long long mass, int N) {
   return (float)((double)mass / kFixScale / (double)(float)N);
@@ -446,7 +446,7 @@ struct KeySource {
   int mode;              // 0: budget of the flattest head, 1: largest budget of the heads, 2: the head's own (all from
                          // own[B*H] and kurt), 3: given counts (budget array), 4: top fraction of the visual range
   const int* own;        // [B*H] budget of every head's own scores
-  const OwnCut* cut;     // [B*H] and the cut that this budget makes, or null
+  OwnCut cut;            // and the cut that this budget makes, or null; for long vectors this is the job's own thr and need
   const double* kurt;    // [B*H]
   int* flattest;         // [B] out (modes 0..2)
   int* budget;           // [B] or [B*H] out (modes 0..2), in (mode 3)
@@ -493,7 +493,7 @@ __device__ __forceinline__ int flattest_head(const double* __restrict__ kurt, in
 __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* __restrict__ a, Layer L, Ragged rg,
                                                                  double recall_p, int only_flattest,
                                                                  double* __restrict__ kurt, int* __restrict__ own,
-                                                                 OwnCut* __restrict__ own_cut, float* __restrict__ recall) {
+                                                                 OwnCut own_cut, float* __restrict__ recall) {
   __shared__ RadixShared sh;
   __shared__ double red[2][kSelWaves];
   const int b = blockIdx.y, head = only_flattest ? flattest_head(kurt + (long long)b * L.Hq, L.Hq) : (int)blockIdx.x;
@@ -506,19 +506,22 @@ __global__ __launch_bounds__(kSelThreads) void score_stats_kernel(const float* _
     const RadixCut cut = radix_cut<true>(x, N, target, true, sh);
     if (threadIdx.x == 0) {
       int r = N;                                // even the whole vector falls short: take everything
-      OwnCut oc = {0u, -1};
+      unsigned at = 0u;
+      int need = -1;
       if (cut.alone) {
         r = 1;
       } else if (cut.found) {
         const unsigned long long v = to_fixed(key_value(cut.key)), q = (cut.rem + v - 1) / v;   // v > 0: its bin crossed the target
         r = max(1, (int)min((unsigned long long)N, cut.other + q));
         if (cut.other + q == (unsigned long long)r && r < N) {
-          oc = OwnCut{cut.key, (int)q};
+          at = cut.key;
+          need = (int)q;
           if (recall) recall[bh] = recall_of(target - cut.rem + q * v, N);
         }
       }
       own[bh] = r;
-      own_cut[bh] = oc;
+      own_cut.key[bh] = at;
+      own_cut.need[bh] = need;
     }
     return;
   }
@@ -745,10 +748,10 @@ __global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged r
     }
     const int n = hi - lo;
     unsigned long long mass = 0;
-    const bool known = src.mode <= 2 && src.cut && k == src.own[bh] && src.cut[bh].need >= 0;     // found by the search for the budget, with
-    if (known) {                                                                        // its recall
-      thr = src.cut[bh].key;
-      need = src.cut[bh].need;
+    const bool known = src.mode <= 2 && src.cut.need && k == src.own[bh] && src.cut.need[bh] >= 0;     // found by the search for the
+    if (known) {                                                                                  // budget, with its recall
+      thr = src.cut.key[bh];
+      need = src.cut.need[bh];
     } else if ((job.rule.keep_all_head0 && h == 0) || k >= n) {
       thr = 0u;
       if (src.recall) {
@@ -771,6 +774,7 @@ __global__ __launch_bounds__(kSelThreads) void list_cut_kernel(Layer L, Ragged r
     short_list(job, row, h, bh, N, v0, v1, thr, need, lsh);
     return;
   }
+  __syncthreads();                      // the cut of the head's own budget, read above, lies where this one goes
   if (threadIdx.x == 0) {
     job.thr[bh] = thr;
     job.need[bh] = need;
@@ -926,12 +930,13 @@ constexpr int kBudgetHeads = 256;
 
 struct StatsWs {
   int* own;
-  OwnCut* cut;
+  OwnCut cut;
 };
 StatsWs carve_stats(Arena& a, const Layer& L) {
   StatsWs w;
   w.own = a.take<int>((size_t)L.B * L.Hq);
-  w.cut = a.take<OwnCut>((size_t)L.B * L.Hq);
+  w.cut.key = a.take<unsigned>((size_t)L.B * L.Hq);
+  w.cut.need = a.take<int>((size_t)L.B * L.Hq);
   return w;
 }
 
@@ -950,7 +955,7 @@ int launch_stats(const Layer& L, const Ragged& rg, const float* key_scores, floa
   *src = KeySource{};
   src->mode = budget_mode;
   src->own = w.own;
-  src->cut = after ? nullptr : w.cut;              // known for every head only where all were searched
+  src->cut = after ? OwnCut{} : w.cut;             // known for every head only where all were searched
   src->kurt = kurt;
   src->flattest = flattest;
   src->budget = budget;
@@ -1006,9 +1011,9 @@ int run_budget_stats(const Layer& L, const float* key_scores, float recall_p, in
 
 size_t select_lists_ws(const Layer& L) {
   Arena a(nullptr);
-  carve_stats(a, L);
   carve_cut(a, L);
   carve_cut(a, L);
+  a.take<int>((size_t)L.B * L.Hq);
   return a.used();
 }
 
@@ -1017,11 +1022,12 @@ int run_select_lists(const Layer& L, const Ragged& rg, const float* scores, int 
                      int* budget, float* recall, int* kv_idx, int b_cap, void* ws, hipStream_t st) {
   Arena a(ws);
   KeySource ks, qs;
-  const int rc = launch_stats(L, rg, key_scores, recall_p, budget_mode, kurt, carve_stats(a, L), flattest, budget, recall, b_cap,
-                              &ks, st);
+  const CutWs kw = carve_cut(a, L), qw = carve_cut(a, L);
+  const StatsWs stats = {a.take<int>((size_t)L.B * L.Hq), {kw.thr, kw.need}};
+  const int rc = launch_stats(L, rg, key_scores, recall_p, budget_mode, kurt, stats, flattest, budget, recall, b_cap, &ks, st);
   if (rc != OMNI_OK) return rc;
-  const ListJob kj = list_job(carve_cut(a, L), key_scores, key_rule(), kv_idx, b_cap, nullptr);
-  const ListJob qj = query_job(L, carve_cut(a, L), scores, q_mode, q_param, q_idx, q_cnt, &qs);
+  const ListJob kj = list_job(kw, key_scores, key_rule(), kv_idx, b_cap, nullptr);
+  const ListJob qj = query_job(L, qw, scores, q_mode, q_param, q_idx, q_cnt, &qs);
   return launch_lists(L, rg, 2, qj, qs, kj, ks, st);
 }
 
