@@ -121,10 +121,16 @@ __device__ __forceinline__ void bounds_block(const Layer& L, const Bounds& p, in
 // Block bx of cdiv(cap, NT / kRankLanes) blocks.  The hand-out order of the items: an item's rank among the keys (all distinct) is its
 // place.  Every workgroup places the heads on the queues for itself (a few hundred instructions: less than a launch),
 // the first one writes the header.  One launch where there were three (prefix, placement, rank): 31 -> 18 us at 64k, 29 -> 11 at 32k.
+// The serial placement takes a head's number of items from LDS: as a load for each head it was 56 us for 224 heads and 80 beside
+// the packs, which it then did not hide under.  Forward call, 28 heads a sequence, d = 128, before / now in us: 8 sequences of
+// 3000 334 / 280, 32 of 2000 982 / 800, one of 16384 420 / 413.
 constexpr int kRankLanes = 16;
 constexpr int kRankTile = 1024;                             // keys staged per pass
+// 16.5 KB with 256 threads, 16.6 with 384 or 512.  The packs of the same launches need 16.6 KB (bf16, d = 128; 33 where Q and dO
+// are packed too), 8.4 KB (bf16 forward, d = 64) or 256 bytes (fp32); the wavefronts of eight workgroups of 256 threads fill a CU
+// in any case, with 133 of its 160 KB.
 template <int NT>
-struct OrderShared {                                        // 16 KB: no more than the packs that run beside it need
+struct OrderShared {
   unsigned long long tile[kRankTile];
   int cost[kSchedMaxQueuedHeads];
   u16 place[kSchedMaxQueuedHeads], order[kSchedMaxQueuedHeads];        // place = queue << 13 | position in it
@@ -209,6 +215,7 @@ __device__ __forceinline__ void order_block(const Order& od, int bx, OrderShared
         int r = 0;
         for (int j = 0; j < BH; ++j) r += (sh.cost[j] > mine || (sh.cost[j] == mine && j < bh)) ? 1 : 0;
         sh.order[r] = (u16)bh;
+        sh.place[bh] = (u16)tiles_of(q_cnt, bh, N, tile_m);       // until the head is placed
       }
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -223,7 +230,7 @@ __device__ __forceinline__ void order_block(const Order& od, int bx, OrderShared
           for (int r = 1; r < kSchedQueues; ++r) m = min(m, load[r]);
           const int q = (int)(m & 7u);
           const unsigned c = (unsigned)(sh.cost[bh] >> shift) << 3;
-          const int ni = tiles_of(q_cnt, bh, N, tile_m);
+          const int ni = sh.place[bh];
 #pragma unroll
           for (int r = 0; r < kSchedQueues; ++r)               // compile-time indices keep the arrays in registers
             if (r == q) {

@@ -150,11 +150,14 @@ def _work_list_lists(kind, rng):
     if kind == "long":                                       # the work of a CU is several longest items: head after head
         N = 65536
         return N, [np.arange(N, dtype=np.int32)] + [pick(N, 21000 + 11 * h) for h in range(27)], [pick(N, 35000)] * 28
+    if kind == "hundreds":                                   # as many heads as a large batch has, of very different lengths
+        N = 2100
+        return N, [pick(N, int(n)) for n in rng.integers(0, N + 1, 900)], [pick(N, 1 + 2 * h) for h in range(900)]
     N = 300                                                  # "many": more heads than queues place
     return N, [pick(N, int(n)) for n in rng.integers(0, N + 1, 1100)], [pick(N, 200)] * 1100
 
 
-@pytest.mark.parametrize("kind", ["edges", "even", "long", "many"])
+@pytest.mark.parametrize("kind", ["edges", "even", "long", "hundreds", "many"])
 @pytest.mark.parametrize("queues", [1, 8])
 @pytest.mark.parametrize("tile_rows", [128, 256])
 @pytest.mark.parametrize("causal", [True, False])
@@ -218,59 +221,74 @@ def test_forward_on_both_sides_of_the_short_sequence_rule(d, causal, full):
             assert float((lse[b, h, q][fin] - m[fin]).abs().max()) <= 2e-3
 
 
+def _check_block_and_list_gradients(B, H, N, d, causal, full, block=64):
+    """Block lists in place give the bits of their token lists, and the gradients of the first and the last sequence are those
+    of 64-bit sums over the listed pairs."""
+    rng = np.random.default_rng(N + d)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    rand = lambda h, s=1.0: (s * torch.randn(B, h, N, d, generator=g, device="cuda")).bfloat16()  # noqa: E731
+    Q, K, V, dO = rand(H), rand(1), rand(1), rand(H, d ** -0.5)
+    desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
+    nb = N // block
+    nsel = nb if full else nb // 3
+    blocks = [[np.sort(rng.choice(nb, nsel, replace=False)) for _ in range(H)] for _ in range(B)]
+    kept = (N, N, N, N) if full else (N, N // 5, 33, 31)
+    rows = [[np.sort(rng.choice(N, kept[h % 4], replace=False)) for h in range(H)] for _ in range(B)]
+    q_idx, q_cnt = lists_to_padded(rows, H, N)
+    blk_idx, _ = lists_to_padded(blocks, H, nb)
+    blk_budget = torch.full((B,), nsel, dtype=torch.int32, device="cuda")
+    kv_idx, budget = ob.omni_expand_blocks(desc, blk_idx, blk_budget, block)
+    O, lse = ob.omni_block_attn_fwd(desc, Q, K, V, q_idx, q_cnt, blk_idx, blk_budget, block)
+    O2, lse2 = ob.omni_sparse_attn_fwd(desc, Q, K, V, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
+    assert torch.equal(O, O2) and torch.equal(lse, lse2)
+    got = ob.omni_block_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, blk_idx, blk_budget, block)
+    got2 = ob.omni_sparse_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
+    for x, y in zip(got, got2):
+        assert torch.equal(x, y)
+    for b in {0, B - 1}:
+        k64, v64 = K[b, 0].double(), V[b, 0].double()
+        want = [torch.zeros(H, N, d, dtype=torch.float64, device="cuda")] + [torch.zeros_like(k64) for _ in range(2)]
+        rss = [torch.zeros_like(x) for x in want]
+        for h in range(H):
+            q = torch.from_numpy(rows[b][h]).cuda()
+            k = (torch.from_numpy(blocks[b][h]).cuda()[:, None] * block + torch.arange(block, device="cuda")).flatten()
+            z = Q[b, h, q].double() @ k64[k].T * d ** -0.5
+            if causal:
+                z = z.masked_fill(k[None] > q[:, None], -float("inf"))
+            P = torch.nan_to_num(torch.softmax(z, -1))
+            go = dO[b, h, q].double()
+            dS = P * (go @ v64[k].T - (go * O[b, h, q].double()).sum(-1, keepdim=True)) * d ** -0.5
+            for out, f in ((want, lambda x: x), (rss, torch.square)):
+                out[0][h, q] = f(dS) @ f(k64[k])
+                out[1][k] += f(dS).T @ f(Q[b, h, q].double())
+                out[2][k] += f(P).T @ f(go)
+        for x, w, r in zip((got[0][b], got[1][b, 0], got[2][b, 0]), want, rss):
+            ulp = torch.from_numpy(bf16_ulp(w.cpu().numpy())).cuda()
+            bar = torch.clamp(GRAD_RSS * r.sqrt() + 0.5 * ulp, min=2e-2)      # grad_bar
+            assert bool(((x.double() - w).abs() <= bar).all())
+
+
 @pytest.mark.parametrize("full", [False, True])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
 def test_gradients_on_both_sides_of_the_short_sequence_rules(d, causal, full):
-    """Shapes just below and just above the lines between the dQ kernels (4.0e10) and the forward kernels (6.5e10; the
-    backward takes each forward's output): block lists in place give the bits of their token lists, and the gradients of
-    the first and the last sequence are those of 64-bit sums over the listed pairs."""
-    H, Hkv, B, block = 16, 1, 4, 64
+    """The backward on either forward's output: shapes just below and just above the line between the forward kernels
+    (6.5e10), and at sizes below it (4.0e10)."""
+    H, B, block = 16, 4, 64
     for line in (4.0e10, 6.5e10):
         N0 = int((line / (B * H * d * (1 if causal else 2))) ** 0.5) // block * block
         for N in (N0, N0 + block):
-            rng = np.random.default_rng(N + d)
-            g = torch.Generator(device="cuda").manual_seed(N)
-            rand = lambda h, s=1.0: (s * torch.randn(B, h, N, d, generator=g, device="cuda")).bfloat16()  # noqa: E731
-            Q, K, V, dO = rand(H), rand(Hkv), rand(Hkv), rand(H, d ** -0.5)
-            desc = ob.make_layer_desc(Q, K, 0, N, 0, causal)
-            nb = N // block
-            nsel = nb if full else nb // 3
-            blocks = [[np.sort(rng.choice(nb, nsel, replace=False)) for _ in range(H)] for _ in range(B)]
-            kept = (N, N, N, N) if full else (N, N // 5, 33, 31)
-            rows = [[np.sort(rng.choice(N, kept[h % 4], replace=False)) for h in range(H)] for _ in range(B)]
-            q_idx, q_cnt = lists_to_padded(rows, H, N)
-            blk_idx, _ = lists_to_padded(blocks, H, nb)
-            blk_budget = torch.full((B,), nsel, dtype=torch.int32, device="cuda")
-            kv_idx, budget = ob.omni_expand_blocks(desc, blk_idx, blk_budget, block)
-            O, lse = ob.omni_block_attn_fwd(desc, Q, K, V, q_idx, q_cnt, blk_idx, blk_budget, block)
-            O2, lse2 = ob.omni_sparse_attn_fwd(desc, Q, K, V, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
-            assert torch.equal(O, O2) and torch.equal(lse, lse2)
-            got = ob.omni_block_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, blk_idx, blk_budget, block)
-            got2 = ob.omni_sparse_attn_bwd(desc, Q, K, V, O, dO, lse, q_idx, q_cnt, kv_idx, budget, kv_idx.shape[-1])
-            for x, y in zip(got, got2):
-                assert torch.equal(x, y)
-            for b in (0, B - 1):
-                k64, v64 = K[b, 0].double(), V[b, 0].double()
-                want = [torch.zeros(H, N, d, dtype=torch.float64, device="cuda")] + [torch.zeros_like(k64) for _ in range(2)]
-                rss = [torch.zeros_like(x) for x in want]
-                for h in range(H):
-                    q = torch.from_numpy(rows[b][h]).cuda()
-                    k = (torch.from_numpy(blocks[b][h]).cuda()[:, None] * block + torch.arange(block, device="cuda")).flatten()
-                    z = Q[b, h, q].double() @ k64[k].T * d ** -0.5
-                    if causal:
-                        z = z.masked_fill(k[None] > q[:, None], -float("inf"))
-                    P = torch.nan_to_num(torch.softmax(z, -1))
-                    go = dO[b, h, q].double()
-                    dS = P * (go @ v64[k].T - (go * O[b, h, q].double()).sum(-1, keepdim=True)) * d ** -0.5
-                    for out, f in ((want, lambda x: x), (rss, torch.square)):
-                        out[0][h, q] = f(dS) @ f(k64[k])
-                        out[1][k] += f(dS).T @ f(Q[b, h, q].double())
-                        out[2][k] += f(P).T @ f(go)
-                for x, w, r in zip((got[0][b], got[1][b, 0], got[2][b, 0]), want, rss):
-                    ulp = torch.from_numpy(bf16_ulp(w.cpu().numpy())).cuda()
-                    bar = torch.clamp(GRAD_RSS * r.sqrt() + 0.5 * ulp, min=2e-2)      # grad_bar
-                    assert bool(((x.double() - w).abs() <= bar).all())
+            _check_block_and_list_gradients(B, H, N, d, causal, full)
+
+
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,H,N,d", [(1, 8, 3200, 128), (1, 8, 3264, 128), (2, 4, 4992, 64), (2, 4, 5056, 64), (1, 9, 64, 128),
+                                     (3, 3, 64, 64), (1, 1, 64, 64), (1, 2, 8256, 128)])
+def test_gradients_on_both_sides_of_the_few_row_rule(B, H, N, d, causal, full):
+    """Eight heads and 26000 rows of d = 128, 40000 of d = 64: below, the dQ items are 32 rows whose wavefronts share the keys,
+    above (more rows, or more heads) 256 rows."""
+    _check_block_and_list_gradients(B, H, N, d, causal, full)
 
 
 @pytest.mark.usefixtures("attention_route")
