@@ -139,8 +139,8 @@ __device__ __forceinline__ void stream_rows_mma(const DecodeParams& p, int b, in
   unsigned char* tile = sV + wave * 32 * PITCH;
   // Transposing reads: a lane supplies four neighbours of one row and gets four rows of one column; rows 4 h + .. (and 8 further
   // down) are the order that the accumulators hold the weights in.  16 instructions a trip in the place of 64 reads of two
-  // bytes and 32 packs.  Decode step in us, before / now: 131072 tokens on group lists 36.1 / 35.2, lists as they are 49.3 / 48.0, 4108 tokens
-  // 17.8 / 17.4, d = 64, 8 heads 13.2 / 12.2.
+  // bytes and 32 packs.  Captured decode steps over 131072 tokens in us, before / now: 28 heads on group lists 36.8 / 36.2, plain
+  // read of the cache 49.9 / 48.9, 8 heads 24.5 / 23.7 and 29.9 / 28.6.
   typedef __attribute__((address_space(3))) s16x4* lds_quads;
   const lds_quads vcol = (lds_quads)(tile + (4 * h + (n & 15) / 4) * PITCH + (n & 16) * 2 + (n & 3) * 8);
 
@@ -703,7 +703,11 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
   const int chunk = unit % chunks, bg = unit / chunks;
   const int b = bg / p.Hkv, g = bg % p.Hkv;
   const int head0 = g * p.G + chunk * GT;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // What belongs to the wavefront is scalar, and known to be: the lists' bases, lengths and positions in vector registers were
+  // spilled, and in some instances the compiler then let each of the window's loads wait for the one before.
+  // Decode step in us on lists as they are, before / now: 65536 tokens, 28 / 4 heads 40.3 / 34.8, 16 / 2 36.8 / 26.9, 8 / 2
+  // 28.7 / 25.1, sixteen sequences of 9000, 28 / 4 54.5 / 48.3.
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int ctx = min(p.ctx_len[b], p.cap);
   const int vis_hi = min(p.v1, ctx);                    // stored rows beyond the context are ignored
   const int span_tokens = max(0, vis_hi - p.v0);
@@ -725,7 +729,7 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
     classes.finish(p, b, head0, slice == 0, sBits);
     __syncthreads();
   }
-  unsigned bits = kShort ? (1u << GT) - 1u : sBits;
+  unsigned bits = kShort ? (1u << GT) - 1u : (unsigned)__builtin_amdgcn_readfirstlane((int)sBits);
   int nsub = bits ? nsub_all : 0;
   // A wavefront looks after heads `wave` and `wave + 4` of the tile (GT <= 8), both at once; a head that is lazy,
   // or beyond GT, is an empty list.
@@ -752,7 +756,7 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
   }
   __syncthreads();
   if constexpr (kShort) {
-    bits = sBits;
+    bits = (unsigned)__builtin_amdgcn_readfirstlane((int)sBits);
     nsub = bits ? nsub_all : 0;
 #pragma unroll
     for (int w = 0; w < 2; ++w) hcnt[w] = (bits >> (wave + w * (kThreads / 64))) & 1u ? hcnt[w] : 0;
@@ -770,7 +774,7 @@ __device__ __forceinline__ void decode_merged_rows(const DecodeParams& p, int sl
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
         const int h = wave + w * (kThreads / 64);
-        cur[w] = h < GT ? sCur[h] : 0;
+        cur[w] = h < GT ? __builtin_amdgcn_readfirstlane(sCur[h]) : 0;
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
           const int e = cur[w] + k * 64 + lane;
