@@ -367,7 +367,13 @@ __device__ __forceinline__ float half_wave_reduce_scatter(float (&v)[32], int ln
 
 // What a short selection has the two passes do besides (all zero: nothing): the scores of the rows in pass 1, each pooled row's
 // log-sum-exp from the chunks' partials in pass 2.
-constexpr int kShortChunks = 16, kShortRows = 256;     // key chunks; (head, pooled row) pairs of a workgroup
+// Key chunks, which a thread holds in registers, and (head, pooled row) pairs of a workgroup, a thread each; at the edge of both,
+// 28 heads, d = 128, 4096 tokens 52 / 57 us.
+constexpr int kShortChunks = 16, kShortRows = 256;
+// Elements of Q: the scores read it again, from the caches while it is small.  Whole selection in us, in three launches / one by
+// one: 28 heads, d = 128, 4 sequences of 2048 tokens (59 MB of Q) 67.0 / 68.9, 8 of 1000 (57 MB) 89.4 / 89.1, 4 of 3000 (86 MB)
+// 86.1 / 78.5, 8 of 2048 (117 MB) 115 / 103, 32 of 4096 (940 MB) 664 / 503; 8 heads, d = 64, 32 of 3000 (98 MB) 106.5 / 107.9.
+constexpr long long kShortQueries = 1 << 25;
 struct ShortRoles {
   const u16* Q;
   const float* partial;                       // sums of the visual keys
@@ -683,14 +689,15 @@ ProbeWs carve_probe(Arena& a, const Layer& L, int pb) {
   return w;
 }
 
-// Short selections: key chunks and pooled rows few enough for pass 2 to form the rows' log-sum-exp by itself, and the mean's
-// partial sums fit where the key scores will be.  mean, pool + scores, pass 1, log-sum-exp, pass 2 as five launches (and one for
+// Short selections: key chunks and pooled rows few enough for pass 2 to form the rows' log-sum-exp by itself, Q small enough to
+// be read twice, and the mean's partial sums fit where the key scores will be.  mean, pool + scores, pass 1, log-sum-exp, pass 2 as five launches (and one for
 // the probe keys) / pool + mean, pass 1 + scores, pass 2 as three: one-call prefill of 1072 tokens, 28 heads, 75.6 / 64.9 us.
 template <typename T>
 bool probe_short(const Layer& L, int pb) {
   if (sizeof(T) != 2) return false;
   const int nblk = cdiv(L.N, pb), nchunk = cdiv(L.N, probe_keys_per_wg<T>());
   return nchunk <= kShortChunks && L.G * nblk <= kShortRows && nblk <= 32 &&
+         (long long)L.B * L.Hq * L.N * L.D <= kShortQueries &&
          (long long)L.Hkv * score_mean_chunks(L) * L.D <= (long long)L.Hq * L.ld;
 }
 

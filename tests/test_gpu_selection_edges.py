@@ -302,3 +302,57 @@ def test_selection_of_short_and_long_sequences_gives_what_the_separate_calls_giv
     for x, y in ((out.probe_keys, probe), (out.scores, scores), (out.budget.key_scores, b.key_scores),
                  (out.budget.budget, b.budget), (out.budget.kurtosis, b.kurtosis), (out.budget.recall, b.recall)):
         assert torch.equal(x, y)
+
+
+def _same_selection_as_the_separate_calls(desc, Q, K, q_mode, q_param, recall_p, block, mode, b_cap):
+    """Every output of the fused call, the lists up to their counts, against the four calls one after the other: bit for bit (the
+    recall counts the keys taken, so it is compared where the capacity takes them all)."""
+    H, N = desc.n_q_heads, desc.n_tokens
+    out = ob.omni_prefill_select(desc, Q, K, q_mode, q_param, recall_p, block, mode, b_cap)
+    probe, scores = ob.omni_score_queries(desc, Q, K)
+    q_idx, q_cnt = ob.omni_select_queries(desc, scores, q_mode, q_param)
+    b = ob.omni_kv_budget(desc, Q, K, recall_p, block, mode)
+    kv_idx = (ob.omni_select_kv_per_head if mode == 2 else ob.omni_select_kv)(desc, b.key_scores, b.budget, b_cap)
+    got = out.budget
+    for x, y in ((out.probe_keys, probe), (out.scores, scores), (out.q_cnt, q_cnt), (got.key_scores, b.key_scores),
+                 (got.budget, b.budget), (got.flattest, b.flattest), (got.kurtosis, b.kurtosis)):
+        assert torch.equal(x, y)
+    per_head = b.budget if mode == 2 else b.budget[:, None].expand(-1, H)
+    assert torch.equal(got.recall[per_head <= b_cap], b.recall[per_head <= b_cap])
+    at = torch.arange(N, device="cuda")
+    assert torch.equal(torch.where(at < q_cnt[..., None], out.q_idx, -1), torch.where(at < q_cnt[..., None], q_idx, -1))
+    listed = at[:b_cap] < per_head[..., None]
+    assert torch.equal(torch.where(listed, out.kv_idx, -1), torch.where(listed, kv_idx, -1))
+    return out
+
+
+@pytest.mark.parametrize("cap", ["all", "few"])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("N", [300, 4096, 8192, 8193, 9000])
+def test_selection_in_one_call_forms_the_lists_of_the_separate_calls(N, mode, cap):
+    """The fused call takes a head's list from the cut that its own budget's search left (budgets of one head in modes 0 and 1,
+    of all in mode 2; past 8192 tokens that cut lies where the list's own goes), the separate calls search it again.  Every
+    key stands four times in a row, so that ties straddle the cuts, and a capacity below the budgets moves them."""
+    H, Hkv, D = 6, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(N)
+    Q = torch.randn(2, H, N, D, generator=g, device="cuda").bfloat16()
+    K = torch.randn(2, Hkv, N // 4 + 1, D, generator=g, device="cuda").bfloat16().repeat_interleave(4, 2)[:, :, :N].contiguous()
+    desc = ob.make_layer_desc(Q, K, 1, N - 9, 0, False)
+    out = _same_selection_as_the_separate_calls(desc, Q, K, 1, 0.31, 0.83, 256, mode, N if cap == "all" else N // 3)
+    if cap == "few":
+        assert int(out.budget.budget.max()) > N // 3
+    else:                                       # the cut stands among equal scores
+        n = int(out.budget.budget.flatten()[0])
+        a = out.budget.key_scores[0, 0].sort(descending=True).values
+        assert n % 4 == 0 or float(a[n - 1]) == float(a[n])
+
+
+@pytest.mark.parametrize("batch", [4, 5])
+def test_selection_of_a_short_batch_on_both_sides_of_the_size_of_its_queries(batch):
+    """Up to 2^25 elements of Q a short selection reads them twice and shares its launches (4 sequences of 14 heads, 4096
+    tokens, d = 128), beyond they are read once."""
+    H, Hkv, N, D = 14, 2, 4096, 128
+    assert (batch * H * N * D <= 1 << 25) == (batch == 4)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    Q, K = (torch.randn(batch, h, N, D, generator=g, device="cuda").bfloat16() for h in (H, Hkv))
+    _same_selection_as_the_separate_calls(ob.make_layer_desc(Q, K, 1, N - 1, 0, True), Q, K, 0, 0.3, 0.9, 256, 0, N)
