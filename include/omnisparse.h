@@ -684,7 +684,7 @@ int omni_debug_key_split_len(int tiles);
  * Diagnostic: the attention calls take one of two sets of kernels by a rule on the shape; 1 takes
  * the one for short sequences on every shape, 2 the one for long sequences (so that a test
  * reaches both on small inputs), 0 restores the rule.  Holds for the calling host thread, its
- * workspace queries included.  omni_dense_attn_fwd and the backward in bf16 have one set.
+ * workspace queries included.  omni_dense_attn_fwd in bf16 has one set.
  */
 int omni_debug_attention_route(int route);
 

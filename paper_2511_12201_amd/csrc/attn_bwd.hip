@@ -13,7 +13,8 @@
 //    dP = dO V^T, dV' += P^T dO, dK' += dS^T Q.  A key tile seen by many query tiles is shared by up to four workgroups,
 //    each with a partial plane of its own.
 //    dQ items: 256 kept queries of a head (32 per wavefront) from the forward's longest-first list; 64-key tiles of K, V
-//    (fragment order) and K^T (k-packed): S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
+//    (fragment order) and K^T (k-packed): S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.  Where the rows are few, 32 kept queries
+//    whose keys the eight wavefronts share.
 //  * attn_bwd_reduce_kernel adds the per-query-head dK', dV' rows (and split planes) of a KV group in a fixed order
 //    into dK, dV -- a head's row is found through an inverse slot map -- and writes zeros for unselected tokens.
 // fp32 inputs, on the fp32 32x32x2 MFMA: attn_bwd_f32_kernel (blocks for dK' and dV' of 32 keys, and for dQ);
@@ -709,6 +710,131 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, unsigned char* smem
   }  // work-item loop
 }
 
+// ------------------------------------------------------------------ dQ, bf16, few rows
+//
+// Items of 32 kept queries whose eight wavefronts share the 32-key blocks of the head's list, operands straight from memory in
+// fragment order, partial sums added in wavefront order; no work list.  A 256-row item walks its tiles one after the other at 1.5
+// to 2 us each, and where the heads are few there is nothing else to do meanwhile (one head of 8192 tokens: 32 items of up to 128
+// tiles on 256 CUs).  Bound by the loads: every item fetches its head's K, V and K^T, eight times what a 256-row item does, from
+// the caches; hence the line (bwd_few_rows).
+template <int D>
+constexpr int kDqRowsLds = 2 * 32 * D * 2 + kKeyWaves * 32 * (D + 4) * 4;
+template <int D, bool TILEMAP>
+__device__ __forceinline__ void dq_row_items(const BwdParams& p, unsigned char* smem, int4& sItem) {
+  typedef u16 T;
+  constexpr int KS = D / 16, NB = D / 32, kOp = 32 * D * 2;
+  unsigned char *sQ = smem, *sG = smem + kOp;
+  float (*sO)[32][D + 4] = reinterpret_cast<float (*)[32][D + 4]>(smem + 2 * kOp);
+  const Layer& L = p.L;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ln = lane & 31, h = lane >> 5;
+  const float c2 = L.scale * kLog2e;
+  const int BH = L.B * L.Hq, n_slots = cdiv(L.N, 32) * BH;         // heads fastest; a head's last rows, which see the most keys, first
+  for (;;) {
+    __syncthreads();                           // LDS of the item before is no longer read
+    if (threadIdx.x == 0) {
+      int bh = -1, tq = -1;
+      for (int k = atomicAdd(&p.klist[kKeyListRows], 1); k < n_slots; k = atomicAdd(&p.klist[kKeyListRows], 1)) {
+        tq = cdiv(p.q_cnt[k % BH], 32) - 1 - k / BH;
+        if (tq >= 0) {
+          bh = k % BH;
+          break;
+        }
+      }
+      sItem = make_int4(bh, tq, 0, 0);
+    }
+    __syncthreads();
+    const int bh = __builtin_amdgcn_readfirstlane(sItem.x), tq = __builtin_amdgcn_readfirstlane(sItem.y);
+    if (bh < 0) break;
+    const int b = bh / L.Hq, i = bh % L.Hq, nq = p.q_cnt[bh];
+    const int* qlist = p.q_idx + (long long)bh * L.N;
+    const int* qvis = p.qvis + (long long)bh * L.N;
+    const long long qo = (long long)bh * p.nqpad + tq * 32;
+    const int qvisible = qvis[min(tq * 32 + ln, nq - 1)] - 4 * h;
+    const int n_full = qvis[tq * 32] / 32, nblocks = cdiv(qvis[min(tq * 32 + 31, nq - 1)], 32);
+    const float lse = p.lse2c[qo + ln], delta = p.deltac[qo + ln];
+    if (threadIdx.x < kOp / 16) {
+      *reinterpret_cast<u32x4*>(sQ + threadIdx.x * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.Qn) + qo * D + threadIdx.x * 8);
+      *reinterpret_cast<u32x4*>(sG + threadIdx.x * 16) = *reinterpret_cast<const u32x4*>(static_cast<const T*>(p.dOn) + qo * D + threadIdx.x * 8);
+    }
+    const int bhx = TILEMAP ? b * L.Hkv + i / L.G : bh;
+    const long long head = (long long)bhx * p.npad_kv * D + lane * 8;
+    const T *kn = static_cast<const T*>(p.Kn) + head, *vn = static_cast<const T*>(p.Vn) + head, *kt = static_cast<const T*>(p.Kt) + head;
+    auto block_off = [&](int t) {
+      if (!TILEMAP) return (long long)t * 32 * D;
+      return (long long)(__builtin_amdgcn_readfirstlane(p.tile_map[(long long)bh * p.tile_stride + t / 2]) * 2 + t % 2) * 32 * D;
+    };
+    bf16x8 kf[KS], vf[KS];
+    auto load_kv = [&](int t) {
+      const long long o = block_off(t);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        kf[ks] = *reinterpret_cast<const bf16x8*>(kn + o + ks * 512);
+        vf[ks] = *reinterpret_cast<const bf16x8*>(vn + o + ks * 512);
+      }
+    };
+    f32x16 dq[NB];
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+    if (wave < nblocks) load_kv(wave);
+    __syncthreads();
+    for (int t = wave; t < nblocks; t += kKeyWaves) {
+      bf16x8 ktf[2][NB];
+      const T* ktb = kt + block_off(t);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int db = 0; db < NB; ++db) ktf[u][db] = *reinterpret_cast<const bf16x8*>(ktb + (u * NB + db) * 512);
+      const unsigned char* frag = sQ + loop_lane() * 16;          // anew: resident, the fragments would take 64 registers
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f, dp[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], *reinterpret_cast<const bf16x8*>(frag + ks * 1024), s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], *reinterpret_cast<const bf16x8*>(frag + kOp + ks * 1024), dp, 0, 0, 0);
+      }
+      if (t + kKeyWaves < nblocks) load_kv(t + kKeyWaves);
+      const bool masked = t >= n_full;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float pv = fast_exp2(fmaf(s[r], c2, -lse));
+        if (masked && t * 32 + 8 * (r >> 2) + (r & 3) >= qvisible) pv = 0.f;
+        dp[r] = pv * (dp[r] - delta);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const bf16x8 ds = pack8(dp, u * 8);
+#pragma unroll
+        for (int db = 0; db < NB; ++db) dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[u][db], ds, dq[db], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 v = {dq[db][q4 * 4], dq[db][q4 * 4 + 1], dq[db][q4 * 4 + 2], dq[db][q4 * 4 + 3]};
+        *reinterpret_cast<f32x4*>(&sO[wave][ln][db * 32 + 8 * q4 + 4 * h]) = v;
+      }
+    __syncthreads();
+    const int row = threadIdx.x / (D / 8), d = threadIdx.x % (D / 8) * 8;      // a thread adds eight of d
+    if (row < 32 && tq * 32 + row < nq) {
+      f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+#pragma unroll
+      for (int w = 0; w < kKeyWaves; ++w) {
+        x += *reinterpret_cast<const f32x4*>(&sO[w][row][d]);
+        y += *reinterpret_cast<const f32x4*>(&sO[w][row][d + 4]);
+      }
+      x *= L.scale;
+      y *= L.scale;
+      T* out = static_cast<T*>(p.dQ) + b * L.qs[0] + i * L.qs[1] + (long long)qlist[tq * 32 + row] * L.qs[2] + d;
+      *reinterpret_cast<u32x4*>(out) = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    }
+  }
+}
+
 // ------------------------------------------------------------------ dK' and dV', bf16 fast path
 //
 // The dQ items with the roles of keys and queries swapped: a workgroup of 8 wavefronts owns 256 packed keys of one
@@ -947,18 +1073,20 @@ __device__ __forceinline__ void key_items(const BwdParams& p, unsigned char* sme
 // Key items, then dQ items: a workgroup that finds no key item left goes on with the other list, so that a launch has one tail
 // instead of two, filled with the shortest dQ items.  Forward and backward in us, as two launches / one: 28 heads, d = 128, 6000
 // tokens 495 / 426 (a budget per head: 398 / 310), 12000 (a budget per head) 887 / 730, 8 heads, 8000 406 / 315, d = 64, 20000
-// 1521 / 1479, 32768 6473 / 6460; blocks at d = 64, 8192 663 / 604.  On short sequences the dQ items used to be 32 rows, in a kernel
-// of their own whose wavefronts shared the keys, because 256-row items left most CUs idle; beside the key items they do not:
-// two clips of 3101, d = 64, 165 / 145, 28 heads, d = 128, 500 tokens 88 / 79, 1072 107 / 87, 3000 212 / 179, d = 64, 2000 98 / 98.
-template <int D, bool TILEMAP>
+// 1521 / 1479, 32768 6473 / 6460; blocks at d = 64, 8192 663 / 604.  Beside the key items of many heads 256-row dQ items leave no
+// CUs idle on short sequences either (two launches, with 32-row dQ items / one): two clips of 3101, d = 64, 165 / 145, 28 heads, d =
+// 128, 500 tokens 88 / 79, 1072 107 / 87, 3000 212 / 179, d = 64, 2000 98 / 98.
+template <int D, bool TILEMAP, bool FEW_ROWS>
 __global__ __launch_bounds__(kKeyThreads, 2) void attn_bwd_bf16_kernel(BwdParams p) {
   static_assert(kKeyThreads == kDqThreads, "one workgroup does both");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kDqLds<D> > kKeyLds<D> ? kDqLds<D> : kKeyLds<D>];
+  constexpr int kDq = FEW_ROWS ? kDqRowsLds<D> : kDqLds<D>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kDq > kKeyLds<D> ? kDq : kKeyLds<D>];
   __shared__ int4 sItem;
   __shared__ int sFirst[kKeyTile];
-  __shared__ int sTileMap[TILEMAP ? kBwdMaxMapTiles : 1];
+  __shared__ int sTileMap[TILEMAP && !FEW_ROWS ? kBwdMaxMapTiles : 1];
   key_items<D, TILEMAP>(p, smem, sItem, sFirst);
-  dq_items<D, TILEMAP>(p, smem, sItem, sTileMap);
+  if constexpr (FEW_ROWS) dq_row_items<D, TILEMAP>(p, smem, sItem);
+  else dq_items<D, TILEMAP>(p, smem, sItem, sTileMap);
 }
 
 // ------------------------------------------------------------------ dK, dV = sum over the heads of a KV group
@@ -1023,6 +1151,19 @@ struct BlockLists {
   const int* blk_budget;
   int blk_cap, block;
 };
+
+// Which dQ items, by the shape only (the gathered and the in-place lists of a layer take the same ones).  Backward call in us,
+// 256-row items / 32-row ones; a third of the queries and half of the keys kept, or all (full).  d = 128: 1 head 8192 156 / 123,
+// 24000 453 / 351 and (full) 8192 259 / 129, 24000 848 / 604; 2 heads (full) 12000 429 / 336; 4 heads 6000 134 / 109 and (full)
+// 230 / 200; 8 heads 3100 88 / 80 and (full) 144 / 148; above the line 8 heads 4096 110 / 92 but (full) 186 / 223, 4 heads 12000
+// 252 / 214 but (full) 526 / 766, 14 heads 2048 76 / 73 but (full) 135 / 150, 28 heads 1072 65 / 65 and (full) 108 / 121.  d = 64: 1
+// head 32768 410 / 328 and (full) 725 / 582, 4 heads 8192 120 / 88 and (full) 207 / 178, 8 heads 4096 80 / 62 and (full) 122 /
+// 118; above the line 4 heads 12000 165 / 120 but (full) 321 / 361, 8 heads 6000 102 / 86 but (full) 182 / 223, 14 heads 3100 76 /
+// 73 but (full) 122 / 142.
+inline bool bwd_few_rows(const Layer& L) {
+  const long long heads = (long long)L.B * L.Hq;
+  return heads <= 8 && heads * L.N <= (L.D == 128 ? 26000 : 40000);
+}
 
 constexpr int kKeyHeadGroup = 7;
 int g_key_split_len = kKeySplitLen;          // omni_debug_key_split_len: tests split short key tiles too
@@ -1096,6 +1237,7 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   constexpr int tile_m = kFast ? kDqTileM : kTileM;
   const bool split = !kFast && f32_short(L);           // fp32 on short sequences: no work list
   const bool copies = kFast || split;                  // fp32 on long sequences: only K and V, row by row
+  const bool few_rows = kFast && short_route(bwd_few_rows(L));       // dQ items of 32 rows: no work list either
   int rc = check_work_list(L, tile_m);
   if (rc != OMNI_OK) return rc;
   // the bf16 key kernel's list: heads and key tiles in 16 and 13 bits of an item
@@ -1193,15 +1335,15 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
   bn.X = dQ;
   bn.elem_bytes = sizeof(T);
   bn.tile_m = tile_m;
-  bn.sched = split ? nullptr : w.sched;
+  bn.sched = split || few_rows ? nullptr : w.sched;
   p.order_off = sched_order_off(L.B * L.Hq, L.N, tile_m);
   if (split) {                                 // no list at all: one launch
     rc = run_prepare(L, dt, true, &kv, &pq, &bn, nullptr, nullptr, st);
   } else {                                     // the lists, a few serial workgroups, hide under the packs
-    // Dispatch order of the key kernel: heads in groups of 7, key tile by key tile inside a group.  Head after head leaves the
-    // long first key tiles of the last heads for the end (measured 3.9 ms at 32k), all heads at once spreads 28
-    // query streams over the caches (4.4 ms); groups of 7 take 3.4 ms.  Group sizes that share a factor with
-    // the 8 XCDs (workgroup i runs on XCD i mod 8) pin heads to XCDs and unbalance them: 8 takes 5.6 ms.
+    // Dispatch order of the key items: heads in groups of 7, key tile by key tile inside a group.  Head after head leaves the
+    // long first key tiles of the last heads for the end, all heads at once spreads 28 query streams over the caches, and group
+    // sizes that share a factor with the 8 XCDs (workgroup i runs on XCD i mod 8) pin heads to XCDs and unbalance them.  At 32k, when
+    // dK' and dV' were kernels of their own (the two together): 3.9 ms, 4.4 ms, groups of 8 5.6 ms, groups of 7 3.4 ms.
     KeyList kl{};
     kl.q_cnt = q_cnt;
     kl.budget = budget;
@@ -1218,13 +1360,15 @@ int launch_bwd(const Layer& L, const void* Q, const void* K, const void* V, cons
     const Order order = make_order(L, q_cnt, tile_m, w.sched);
     rc = run_prepare(L, dt, true, nullptr, nullptr, &bn, nullptr, nullptr, st);
     if (rc != OMNI_OK) return rc;
-    rc = run_prepare(L, dt, true, &kv, &pq, nullptr, &order, kFast ? &kl : nullptr, st);
+    rc = run_prepare(L, dt, true, &kv, &pq, nullptr, few_rows ? nullptr : &order, kFast ? &kl : nullptr, st);
   }
   if (rc != OMNI_OK) return rc;
   {
     ProfScope prof__(kProfBwdDkDv, st);
     if constexpr (sizeof(T) == 2) {
-      hipLaunchKernelGGL((attn_bwd_bf16_kernel<D, BLOCKS>), dim3((unsigned)persistent_grid() / 2), dim3(kKeyThreads), 0, st, p);
+      const dim3 grid((unsigned)persistent_grid() / 2);
+      if (few_rows) hipLaunchKernelGGL((attn_bwd_bf16_kernel<D, BLOCKS, true>), grid, dim3(kKeyThreads), 0, st, p);
+      else hipLaunchKernelGGL((attn_bwd_bf16_kernel<D, BLOCKS, false>), grid, dim3(kKeyThreads), 0, st, p);
     } else {
       const unsigned heads = (unsigned)(L.B * L.Hq), key_blocks = heads * (unsigned)(npad / 32) * kKeyMaxSplits;
       if (split)

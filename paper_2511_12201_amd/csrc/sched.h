@@ -74,7 +74,8 @@ Order make_order(const Layer& L, const int* q_cnt, int tile_m, int* sched, int q
 // The work list of the bf16 key kernel of the backward (attn_bwd.hip): (head, key tile, split) in dispatch order.
 constexpr int kKeyTile = 256;                // packed keys per workgroup
 constexpr int kKeyQ = 64;                    // queries per tile, as the splits count them
-constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, -
+constexpr int kKeyListHeader = 4;            // counter, number of items, query tiles per split, counter of the 32-row dQ items
+constexpr int kKeyListRows = 3;
 // An item is four ints, all that a workgroup has to know before its first load: head << 16 | key tile << 3 | split, first query
 // tile, number of query tiles, first query position from which on nothing is masked.
 constexpr int kKeyItemInts = 4;

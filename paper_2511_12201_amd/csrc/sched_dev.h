@@ -342,6 +342,7 @@ __device__ __forceinline__ void key_list_block(const Layer& L, const KeyList& p,
     p.klist[0] = 0;
     p.klist[1] = base;
     p.klist[2] = split_len;
+    p.klist[kKeyListRows] = 0;
   }
 }
 
