@@ -650,9 +650,17 @@ __device__ __forceinline__ void chunk_counts(const ListJob& job, const float* __
                                              int v0, int v1, unsigned thr, int need) {
   const int lane = lane_id(), nchunk = cdiv(N, kChunk);
   const bool all = job.rule.keep_all_head0 && h == 0;
-  const int lo = all ? N : job.rule.visual_only ? v0 : 0, hi = all ? N : job.rule.visual_only ? v1 : N;
+  const int lo = job.rule.visual_only ? v0 : 0, hi = job.rule.visual_only ? v1 : N;
   int* ck = job.off_keep + (long long)bh * stride;
   int* ce = job.off_eq + (long long)bh * stride;
+  if (all) {                               // nothing to look at
+    for (int c = threadIdx.x; c < nchunk; c += kSelThreads) {
+      ck[c] = c * kChunk;
+      ce[c] = 0;
+    }
+    if (threadIdx.x == 0 && job.total) job.total[bh] = min(job.out_stride, N);
+    return;
+  }
 #pragma unroll 1
   for (int c = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); c < nchunk; c += kSelWaves) {
     float v[kChunk / 64];
