@@ -8,7 +8,7 @@ import torch
 from oracle import omni_oracle as oc
 from paper_2511_12201_amd import binding as ob
 from paper_2511_12201_amd import synth
-from tests.helpers import (check_selection_on_gpu_scores, grad_bar, lists_to_padded, oracle_train, padded_to_lists,
+from tests.helpers import (GRAD_RSS, bf16_ulp, check_selection_on_gpu_scores, grad_bar, lists_to_padded, oracle_train, padded_to_lists,
                            to_device, to_host)
 
 pytestmark = pytest.mark.gpu
@@ -1765,16 +1765,33 @@ def test_selection_and_attention_on_odd_layouts(layout, dtype):
 @pytest.mark.parametrize("d", [64, 128])
 def test_decode_on_lists_as_they_are_around_the_short_slices(nv, d):
     """One KV group of seven heads, 256 slices at most: slices of 1 to 128 tokens take spans of 128 and search all lists, those of
-    129 spans of 1024; a head that stores everything, one that stores nothing, stored rows beyond the context."""
+    129 spans of 1024; a head that stores everything, one that stores nothing, stored rows beyond the context.  The rows at
+    the edges of slices, spans and context weigh so much that one of them missing or too many is seen, and so is a slice: the
+    reference without it is outside the bar."""
     H, cap, rng = 7, nv + 40, np.random.default_rng(nv)
     g = torch.Generator(device="cuda").manual_seed(nv)
-    K, V = (torch.randn(1, 1, cap, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, V = (torch.randn(1, 1, cap, d, generator=g, device="cuda") for _ in range(2))
     q = torch.randn(1, H, d, generator=g, device="cuda").bfloat16()
     probe = torch.randn(1, 1, 2, d, generator=g, device="cuda")
+    per = -(-nv // 256)
+    edges = sorted(t for t in {0, 1, 63, 64, 127, 128, per - 1, per, 2 * per - 1, 2 * per, 1023, 1024, nv // 2, nv - 6, nv - 5, nv - 1}
+                   if 0 <= t < nv)
+    # the same logit for every head, log(rows / 64 + 1): a weight of about a hundredth each
+    dual = torch.linalg.pinv(q[0].double()).sum(1) * np.log(cap / 64 + 1) * d ** 0.5
+    K[0, 0, edges] = dual.float()
+    K, V = K.bfloat16(), V.bfloat16()
     keep = rng.random((H, nv)) < rng.random((H, 1))
     keep[0], keep[1] = True, False
     lists = [[np.flatnonzero(keep[h]).astype(np.int32) for h in range(H)]]
     vis_idx, vis_cnt = lists_to_padded(lists, H, nv)
+
+    def reference(h, rows):
+        if not len(rows):
+            return torch.zeros(2, d, dtype=torch.float64, device="cuda")
+        v = V[0, 0, rows].double()
+        w = torch.softmax(K[0, 0, rows].double() @ q[0, h].double() * d ** -0.5, -1)
+        return torch.stack([w @ v, (w.square() @ v.square()).sqrt()])
+
     for ctx in (nv + 33, max(1, nv - 5)):
         desc = ob.make_decode_desc(q, K, 0, nv, 0.2)
         O, active = ob.omni_slim_decode(desc, q, K, V, torch.tensor([ctx], dtype=torch.int32, device="cuda"), probe, vis_idx,
@@ -1785,8 +1802,13 @@ def test_decode_on_lists_as_they_are_around_the_short_slices(nv, d):
             assert bool(active[0, h]) == act
             seen = np.ones(ctx, dtype=bool)
             seen[:min(nv, ctx)] = keep[h, :ctx] if act else False
-            rows = torch.from_numpy(np.flatnonzero(seen)).cuda()
-            want = torch.zeros(d, dtype=torch.float64, device="cuda")
-            if len(rows):
-                want = torch.softmax(K[0, 0, rows].double() @ q[0, h].double() * d ** -0.5, -1) @ V[0, 0, rows].double()
-            assert float((O[0, h].double() - want).abs().max()) <= 2e-2
+            want, rss = reference(h, np.flatnonzero(seen))
+            # weights rounded to 8 bits, as in grad_bar, and the result stored in 8 bits
+            bar = GRAD_RSS * rss + 0.5 * torch.from_numpy(bf16_ulp(want.cpu().numpy())).cuda()
+            assert bool(((O[0, h].double() - want).abs() <= bar).all())
+            for t in edges:                                # the bar tells a row from no row
+                rows = np.flatnonzero(seen ^ (np.arange(ctx) == t)) if t < ctx else np.append(np.flatnonzero(seen), t)
+                assert not bool(((reference(h, rows)[0] - want).abs() <= bar).all())
+            for first in (0, nv // 2 // per * per, (nv - 1) // per * per) if h == 0 else ():      # and a slice from none
+                rows = np.flatnonzero(seen & ((np.arange(ctx) < first) | (np.arange(ctx) >= min(nv, first + per))))
+                assert first >= ctx or not bool(((reference(h, rows)[0] - want).abs() <= bar).all())
