@@ -584,8 +584,8 @@ def bench_train(torch, ob, synth, steps: int = 5, per_head: bool = False):
     kern = {}
     for name in ("attn_fwd", "bwd_dkdv", "bwd_dq", "bwd_reduce", "pack_kv"):
         t, n = ob.profile_read(name)
-        if n:
-            kern[name] = round(t / n, 4)
+        if n:                      # bf16: dK, dV and dQ are one kernel, timed under the first name
+            kern[{"bwd_dkdv": "bwd_main"}.get(name, name)] = round(t / n, 4)
     ob.profile_enable(False)
     bud, q_idx, q_cnt, kv_idx = sel.budget, sel.q_idx, sel.q_cnt, sel.kv_idx
     cnt = q_cnt.cpu().numpy()[0]
@@ -594,13 +594,13 @@ def bench_train(torch, ob, synth, steps: int = 5, per_head: bool = False):
     b = float(bh.mean())
     qi, ki = q_idx.cpu().numpy()[0], kv_idx.cpu().numpy()[0]
     valid, _ = pair_counts([qi[h, : cnt[h]] for h in range(Hq)], [ki[h, : bh[h]] for h in range(Hq)], cfg.causal)
-    bwd_ms = kern.get("bwd_dkdv", 0) + kern.get("bwd_dq", 0)
+    bwd_ms = kern.get("bwd_main", 0) + kern.get("bwd_dq", 0)
     res = {"workload": f"{cfg.name}: N={N}, bf16, selection + sparse fwd + sparse bwd"
                        + (", one budget per head" if per_head else ""), "ms_per_step": round(ms, 4),
            "kernel_ms": kern, "kept_query_fraction": round(float(cnt.sum()) / (Hq * N), 4),
            "budget_fraction": round(b / N, 4),
            "bwd_algorithmic_tflops": round(10.0 * D * valid / (bwd_ms * 1e-3) / 1e12, 2) if bwd_ms else None,
-           # 7 GEMMs per pair are issued (S and dP by both the dK/dV and the dQ kernel), 5 are the algorithm's
+           # 7 GEMMs per pair are issued (S and dP for both the dK/dV and the dQ items), 5 are the algorithm's
            "bwd_issued_gemm_tflops": round(14.0 * D * valid / (bwd_ms * 1e-3) / 1e12, 2) if bwd_ms else None,
            "fwd_algorithmic_tflops": round(4.0 * D * valid / (kern["attn_fwd"] * 1e-3) / 1e12, 2)}
     return res

@@ -609,17 +609,25 @@ size_t omni_workspace_bytes(int call_id, const void* desc, int32_t param);
  * inside a region whose wall clock matters).  It also resets the records; omni_profile_read()
  * waits for the recorded launches and returns their summed duration in
  * milliseconds and their number.  Not thread safe.  kernel_id: 0 attention
- * forward main kernel, 1 K/V pack (gather), 2 output clear, 3 query pooling,
- * 4 probe pass 1 (row log-sum-exp), 5 probe pass 2 (column sums), 6 query
- * scoring, 7 backward dK/dV kernel, 8 backward dQ kernel, 9 backward
- * scatter-reduce, 10 decode partial kernel, 11 selection kernels.
+ * forward main kernel; 1 packs (gather) of K and V, in the backward of Q and dO too,
+ * with the passes over the lists that share their launch; 2 passes over the lists
+ * (what every position sees, cleared output rows) in a launch of their own (sequences
+ * that have a work list, and every bf16 backward); 3 query pooling, in a selection by
+ * one call with the query scores or, if it is short, with the sums of the visual
+ * keys; 4 probe pass 1 (row log-sum-exp), in a short selection with the query scores;
+ * 5 probe pass 2 (column sums); 6 query scoring in a launch of its own
+ * (omni_score_queries); 7 backward main kernel: dK, dV and dQ, but dK and dV only in
+ * fp32 on long sequences; 8 backward dQ kernel of fp32 on long sequences (no other
+ * launch has one of its own); 9 backward scatter-reduce; 10 decode partial kernels;
+ * 11 none.
  */
 int omni_profile_enable(int mask);
 int omni_profile_read(int kernel_id, float* total_ms /* host */, int* launches /* host */);
 
 /*
  * Diagnostic, host only: the work list the query-tile kernels (attention forward,
- * backward dQ; short sequences run without one) build on the device, computed by the same rule on the host.  Work item
+ * backward dQ; forwards and fp32 backwards of short sequences and bf16 backwards of few rows run without one) build on
+ * the device, computed by the same rule on the host.  Work item
  * = one tile of tile_rows (128 or 256) kept queries of a head, its cost the number of
  * 64-key tiles it streams (estimated here from the position of the tile; the device
  * uses exact counts where it has them).  queues = 1: one list, longest item first,
@@ -674,7 +682,7 @@ int omni_debug_mfma_rate(int random_operands, int iters, double* tflops /* host 
 /*
  * Diagnostic: the backward pass shares a key tile that is seen by very many query tiles (a head
  * that keeps every query) between several workgroups.  A share is as many 64-query tiles as a
- * workgroup's part of all of them, between 8 and `tiles` (default 128): a value below 8 makes short test inputs
+ * workgroup's part of all of them, between 5 and `tiles` (default 128): a value below 5 makes short test inputs
  * take that path.
  * tiles <= 0 restores the default.  Process-wide; not for use while a backward call is running.
  */

@@ -1812,3 +1812,36 @@ def test_decode_on_lists_as_they_are_around_the_short_slices(nv, d):
             for first in (0, nv // 2 // per * per, (nv - 1) // per * per) if h == 0 else ():      # and a slice from none
                 rows = np.flatnonzero(seen & ((np.arange(ctx) < first) | (np.arange(ctx) >= min(nv, first + per))))
                 assert first >= ctx or not bool(((reference(h, rows)[0] - want).abs() <= bar).all())
+
+
+@pytest.mark.usefixtures("attention_route")
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_kernel_timing_records_the_launches_that_the_header_names(dtype, attention_route):
+    """Which ids a call records, and how often: a program that times one id must not get another kernel, or nothing."""
+    long, N, H, Hkv, d = attention_route == "long", 300, 4, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rand = lambda h: torch.randn(1, h, N, d, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)  # noqa: E731
+    Q, K, V, dO = rand(H), rand(Hkv), rand(Hkv), rand(H)
+    desc = ob.make_layer_desc(Q, K, 0, N - 9, 0, True)
+
+    def launches(call):
+        call()
+        ob.profile_enable(True)
+        out = call()
+        got = {name: ob.profile_read(name)[1] for name in ob.PROF_KERNELS}
+        ob.profile_enable(False)
+        return out, {name: n for name, n in got.items() if n}
+
+    try:
+        _, n = launches(lambda: ob.omni_score_queries(desc, Q, K))
+        assert n == {"score": 1}
+        sel, n = launches(lambda: ob.omni_prefill_select(desc, Q, K, 0, 0.3, 0.9, 64, 0))
+        assert n == {"pool_q": 1, "probe_lse": 1, "probe_sum": 1}
+        lists = (sel.q_idx, sel.q_cnt, sel.kv_idx, sel.budget.budget, N)
+        (O, lse), n = launches(lambda: ob.omni_sparse_attn_fwd(desc, Q, K, V, *lists))
+        assert n == {"attn_fwd": 1, "pack_kv": 1, **({"clear_out": 1} if long else {})}
+        _, n = launches(lambda: ob.omni_sparse_attn_bwd(desc, Q, K, V, O, dO, lse, *lists))
+        assert n == {"bwd_dkdv": 1, "bwd_reduce": 1, "pack_kv": 1, **({"clear_out": 1} if long or dtype == "bf16" else {}),
+                     **({"bwd_dq": 1} if long and dtype == "f32" else {})}
+    finally:
+        ob.profile_enable(False)
