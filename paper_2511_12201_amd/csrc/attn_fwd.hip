@@ -6,7 +6,7 @@
 //  * A pack pass (pack.hip) gathers each head's selected K rows into a dense
 //    buffer in fragment order (the long fp32 kernel: rows as they are) and its V rows into the exact operand order the matrix cores need
 //    (below; rows as they are for the long fp32 kernel), zero-padding to whole
-//    64-key tiles and recording the original token index of every slot.  The dense baseline runs the same pack
+//    64-key tiles.  The dense baseline runs the same pack
 //    with identity indices per KV head.  The main loop is then free of gathers.
 //  * Both GEMMs are computed transposed, S^T = K Q^T and O^T = V^T P^T, with
 //    32x32 MFMA tiles.  Each lane then owns one query column: the softmax row

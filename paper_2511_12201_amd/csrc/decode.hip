@@ -534,34 +534,34 @@ struct HeadClasses {
   static constexpr int kWaves = kThreads / 64, kMine = (GT + kWaves - 1) / kWaves, kPer = D / 64;
   float diff[kPer], qv[kMine][kPer];
   __device__ __forceinline__ void load(const DecodeParams& p, int b, int g, int head0) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const float* pk = p.probe + ((long long)(b * p.Hkv + g) * 2) * D;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const float* pk = p.probe + ((long long)(b * p.Hkv + g) * 2) * D;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) diff[k] = pk[D + lane + 64 * k] - pk[lane + 64 * k];
+    for (int k = 0; k < kPer; ++k) diff[k] = pk[D + lane + 64 * k] - pk[lane + 64 * k];
 #pragma unroll
-  for (int u = 0; u < kMine; ++u) {
-    const int h = min(wave + u * kWaves, GT - 1);
+    for (int u = 0; u < kMine; ++u) {
+      const int h = min(wave + u * kWaves, GT - 1);
 #pragma unroll
-    for (int k = 0; k < kPer; ++k)
-      qv[u][k] = Elem<T>::load(static_cast<const T*>(p.q) + (long long)(b * p.Hq + head0 + h) * D + lane + 64 * k);
-  }
-  }
-  __device__ __forceinline__ void finish(const DecodeParams& p, int b, int head0, bool store, unsigned& active_bits) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-  for (int u = 0; u < kMine; ++u) {
-    const int h = wave + u * kWaves, i = head0 + h;
-    float dot = 0.f;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) dot = fmaf(qv[u][k], diff[k], dot);
-    dot = wave_sum(dot);
-    if (lane == 0 && h < GT) {
-      const float score = 1.0f / (1.0f + expf(-dot * p.scale));
-      const int act = (i == 0 || score > p.tau) ? 1 : 0;
-      if (act) atomicOr(&active_bits, 1u << h);
-      if (store && p.active) p.active[b * p.Hq + i] = (unsigned char)act;
+      for (int k = 0; k < kPer; ++k)
+        qv[u][k] = Elem<T>::load(static_cast<const T*>(p.q) + (long long)(b * p.Hq + head0 + h) * D + lane + 64 * k);
     }
   }
+  __device__ __forceinline__ void finish(const DecodeParams& p, int b, int head0, bool store, unsigned& active_bits) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+      const int h = wave + u * kWaves, i = head0 + h;
+      float dot = 0.f;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) dot = fmaf(qv[u][k], diff[k], dot);
+      dot = wave_sum(dot);
+      if (lane == 0 && h < GT) {
+        const float score = 1.0f / (1.0f + expf(-dot * p.scale));
+        const int act = (i == 0 || score > p.tau) ? 1 : 0;
+        if (act) atomicOr(&active_bits, 1u << h);
+        if (store && p.active) p.active[b * p.Hq + i] = (unsigned char)act;
+      }
+    }
   }
 };
 template <typename T, int D, int GT>

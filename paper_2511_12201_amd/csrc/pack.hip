@@ -1,8 +1,8 @@
 // Gather / re-layout passes that feed the attention kernels (HBM-bound copies).
 //
-// pack_kv: per head, the selected K/V rows are gathered into dense buffers,
-// padded with zero rows to whole 64-key tiles, and the original token index of
-// every slot is recorded (pad slots: kPadKeyIndex).  Layouts: "fragment order"
+// pack_kv: per head, the selected K/V rows are gathered into dense buffers and
+// padded with zero rows to whole 64-key tiles (who sees a slot is read from the
+// key lists themselves: bounds_block, sched_dev.h).  Layouts: "fragment order"
 // [32-row block][k step][lane] of 16 bytes, lane = 32 h + row (a k step is 16 elements of
 // bf16, 8 of fp32): the A or B operand of a 32x32 MFMA that contracts over d, a kilobyte
 // per operand with the lanes side by side, in memory and in LDS alike (no swizzle, one
@@ -22,7 +22,7 @@
 //
 // Both, and the passes over the lists (sched_dev.h), are roles of one kernel: on short sequences a launch that does nothing
 // takes 4 us, as long as most of these passes, and on long ones the serial work-list blocks hide under the packs.  Launches
-// before -> now and the whole call in us: one-call prefill of 1072 tokens 12 -> 11, 87.5 -> 84.4; fp32 forward and backward,
+// one by one -> as roles and the whole call in us, when that was done: one-call prefill of 1072 tokens 12 -> 11, 87.5 -> 84.4; fp32 forward and backward,
 // 1024 tokens, 9 -> 6, 87 -> 75; two clips of 3101 at d = 64, 10 -> 7, 178 -> 168; forward of 16391 tokens 4 -> 3, 430 ->
 // 427; blocks at 16k, forward and backward, 24 -> 18, 3044 -> 3001.
 #include "common.h"
@@ -241,39 +241,39 @@ __device__ __forceinline__ void pack_q_block(const Layer& L, const PackQ& p, int
   const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
   if (!kBf16 || threadIdx.x < kThreads) {
 #pragma unroll                                      // all loads of a thread in flight together
-  for (int rb = 0; rb < 64; rb += RPP) {
-    const int r = rb + r0;
-    const int row = sIdx[r];
-    float dot = 0.f;
-    u32x4 g = {0u, 0u, 0u, 0u}, qc = {0u, 0u, 0u, 0u};
-    if (row >= 0) {
-      const u32x4 a = *reinterpret_cast<const u32x4*>(O + head_off + (long long)row * L.qs[2] + c * E);
-      g = *reinterpret_cast<const u32x4*>(dO + head_off + (long long)row * L.qs[2] + c * E);
-      if (Qn) qc = *reinterpret_cast<const u32x4*>(Q + head_off + (long long)row * L.qs[2] + c * E);
-      float av[E], gv[E];
-      unpack16(a, av, (const T*)nullptr);
-      unpack16(g, gv, (const T*)nullptr);
-#pragma unroll
-      for (int e = 0; e < E; ++e) dot = fmaf(av[e], gv[e], dot);
-    }
-    if (Qn) {                                   // packed copies in fragment order (pad rows zero)
-      const long long o = ((long long)bh * nqpad + tile * 64 + r / 32 * 32) * D + (c * 32 + r % 32) * E;
-      *reinterpret_cast<u32x4*>(Qn + o) = qc;
-      *reinterpret_cast<u32x4*>(dOn + o) = g;
-    }
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
-    if (c == 0) {
-      const long long o = (long long)bh * nqpad + tile * 64 + r;
-      float l2 = INFINITY;
+    for (int rb = 0; rb < 64; rb += RPP) {
+      const int r = rb + r0;
+      const int row = sIdx[r];
+      float dot = 0.f;
+      u32x4 g = {0u, 0u, 0u, 0u}, qc = {0u, 0u, 0u, 0u};
       if (row >= 0) {
-        const float lv = p.lse[(long long)bh * L.N + row];
-        l2 = lv == -INFINITY ? INFINITY : lv * kLog2e;
+        const u32x4 a = *reinterpret_cast<const u32x4*>(O + head_off + (long long)row * L.qs[2] + c * E);
+        g = *reinterpret_cast<const u32x4*>(dO + head_off + (long long)row * L.qs[2] + c * E);
+        if (Qn) qc = *reinterpret_cast<const u32x4*>(Q + head_off + (long long)row * L.qs[2] + c * E);
+        float av[E], gv[E];
+        unpack16(a, av, (const T*)nullptr);
+        unpack16(g, gv, (const T*)nullptr);
+#pragma unroll
+        for (int e = 0; e < E; ++e) dot = fmaf(av[e], gv[e], dot);
       }
-      p.lse2c[o] = l2;
-      p.deltac[o] = row >= 0 ? dot : 0.f;
+      if (Qn) {                                   // packed copies in fragment order (pad rows zero)
+        const long long o = ((long long)bh * nqpad + tile * 64 + r / 32 * 32) * D + (c * 32 + r % 32) * E;
+        *reinterpret_cast<u32x4*>(Qn + o) = qc;
+        *reinterpret_cast<u32x4*>(dOn + o) = g;
+      }
+#pragma unroll
+      for (int o = LPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
+      if (c == 0) {
+        const long long o = (long long)bh * nqpad + tile * 64 + r;
+        float l2 = INFINITY;
+        if (row >= 0) {
+          const float lv = p.lse[(long long)bh * L.N + row];
+          l2 = lv == -INFINITY ? INFINITY : lv * kLog2e;
+        }
+        p.lse2c[o] = l2;
+        p.deltac[o] = row >= 0 ? dot : 0.f;
+      }
     }
-  }
   }
   if constexpr (kBf16) {
     constexpr int kItems = (64 / 16) * 2 * (D / 8);

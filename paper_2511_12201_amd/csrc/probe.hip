@@ -759,9 +759,9 @@ int launch_probe(const Layer& L, const void* Q, const void* K, int pb, float* ke
       OMNI_LAUNCH_CHECK();
     }
     if (!late.part_m) {
-    hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
-                       w.part_m, w.part_l, w.lse2w);
-    OMNI_LAUNCH_CHECK();
+      hipLaunchKernelGGL(probe_lse_kernel, dim3(cdiv(nblk, 4), BH), dim3(kThreads), 0, st, L, rg, pb, nblk, nchunk, KPG,
+                         w.part_m, w.part_l, w.lse2w);
+      OMNI_LAUNCH_CHECK();
     }
     {
       ProfScope prof__(kProfProbeSum, st);

@@ -41,7 +41,7 @@ inline size_t sched_cap(int BH, int N, int tile_m) { return (size_t)BH * ((N + t
 inline size_t sched_order_off(int BH, int N, int tile_m) { return (size_t)kSchedItems + 2 * sched_cap(BH, N, tile_m); }
 inline size_t sched_ints(int BH, int N, int tile_m) { return sched_order_off(BH, N, tile_m) + sched_cap(BH, N, tile_m); }
 
-// What the kept-query and key lists say about every position and token, in one launch (run_bounds); null: not wanted.
+// What the kept-query and key lists say about every position and token, by bounds_block (sched_dev.h); null: not wanted.
 struct Bounds {
   const int *q_idx, *q_cnt;      // [B*Hq, N], [B*Hq]
   const int* klist;              // [B*Hq, klist_stride] token indices, the first min(budget, b_cap) of a head

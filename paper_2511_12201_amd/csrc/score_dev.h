@@ -57,11 +57,10 @@ __device__ __forceinline__ void mean_key_block(const T* __restrict__ K, const La
   }
 }
 
-
 // score = softmax([q.k_lazy, q.k_act] * scale)[1] = 1 / (1 + exp(-(q.(k_act - k_lazy)) * scale)) of kScoreRows rows of head bh, with
 // the mean of the visual keys from its chunks' sums; the first block of a KV group's first head writes the probe keys.  The rows'
 // scores end up one in every lane of the row's lane group, so that the exponential is evaluated (and its code fetched) once.
-// sums: kFinalSplit * D floats.
+// diffs: D floats of LDS.
 constexpr int kScoreRows = 128;
 template <typename T, int D>
 __device__ __forceinline__ void score_rows_block(const T* __restrict__ Q, const T* __restrict__ K, const Layer& L, const Ragged& rg,
