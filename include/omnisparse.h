@@ -203,9 +203,10 @@ int omni_budget_from_scores(const omni_layer_desc* desc, const float* key_scores
  * (probe-softmax and query-mask equations) followed by Sec. "KV Selection"
  * (accumulated key score, kurtosis, budget and key-mask equations).  Every
  * output is bit-identical to what the separate calls write on the same inputs;
- * the fused call reads Q once for both the query scores and the pooled queries,
- * and compacts the key lists from the per-head cut that the recall computation
- * already finds, instead of searching it again.
+ * the fused call reads Q from memory once for both the query scores and the pooled
+ * queries (in bf16, where Q is small: twice, the second time from the caches, in
+ * fewer launches), and compacts the key lists from the per-head cut that the recall
+ * computation already finds, instead of searching it again.
  * Arguments and outputs as in the separate calls (q_mode, q_param: mode and
  * param of omni_select_queries), with one difference: recall[i] is the mass of
  * the min(budget, b_cap) keys that are actually selected, which is the recall

@@ -690,8 +690,9 @@ ProbeWs carve_probe(Arena& a, const Layer& L, int pb) {
 }
 
 // Short selections: key chunks and pooled rows few enough for pass 2 to form the rows' log-sum-exp by itself, Q small enough to
-// be read twice, and the mean's partial sums fit where the key scores will be.  mean, pool + scores, pass 1, log-sum-exp, pass 2 as five launches (and one for
-// the probe keys) / pool + mean, pass 1 + scores, pass 2 as three: one-call prefill of 1072 tokens, 28 heads, 75.6 / 64.9 us.
+// be read twice, and the mean's partial sums fit where the key scores will be.  mean, pool + scores, pass 1, log-sum-exp, pass 2 as
+// five launches (and one for the probe keys) / pool + mean, pass 1 + scores, pass 2 as three: one-call prefill of 1072 tokens, 28
+// heads, 75.6 / 64.9 us.
 template <typename T>
 bool probe_short(const Layer& L, int pb) {
   if (sizeof(T) != 2) return false;

@@ -918,7 +918,9 @@ ListJob query_job(const Layer& L, const CutWs& w, const float* scores, int mode,
 KeepRule key_rule() { return KeepRule{0, 0, 1, 0u}; }
 
 // The cuts and the lists of one or two jobs: in one launch where a vector is short, else the lists in a launch of their own with a
-// workgroup per kChunk elements.  28 heads, both lists, one launch / two: 1072 scores 12.7 us / 16.3, 65536: 64 / 48.
+// workgroup per kChunk elements.  28 heads, both lists, one launch / two: 1072 scores 12.7 us / 16.3, 65536: 64 / 48.  At the line, a
+// workgroup a CU, the cuts of many heads run in rounds and the lists with them; omni_select_queries, one launch / two: 8192 scores, 28
+// heads 17.5 us / 20.2, 252 21.3 / 25.8, 280 31.0 / 34.0, 448 31.7 / 36.7, 896 58.4 / 66.9; 4096 scores, 896 heads 45.9 / 52.0.
 int launch_lists(const Layer& L, const Ragged& rg, int jobs, const ListJob& j0, const KeySource& s0, const ListJob& j1,
                  const KeySource& s1, hipStream_t st) {
   hipLaunchKernelGGL(list_cut_kernel, dim3(L.Hq, L.B, jobs), dim3(kSelThreads), 0, st, L, rg, j0, s0, j1, s1);
