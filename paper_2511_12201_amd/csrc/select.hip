@@ -90,7 +90,8 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, Ra
 constexpr int kBatch = 8;               // loads in flight per thread
 typedef float Batch[kBatch];
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));      // rows start at any multiple of four bytes
-// Element i of a head's vector: one 32-bit offset to a base in scalar registers (a vector is shorter than 2^29 elements).
+// Element i of a stretch of a head's vector: one 32-bit offset to a base in scalar registers.  Where the stretch begins belongs to the
+// base: a vector may be longer than the 2^30 elements that the offset reaches.
 template <typename V = float>
 __device__ __forceinline__ V element(const float* __restrict__ row, int i) {
   return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(row) + (unsigned)i * 4u);
@@ -122,17 +123,18 @@ struct Ahead {
   f32x4_any quad[kLoads];
   __device__ __forceinline__ void load(const float* __restrict__ x, int n, int at) {
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) quad[u] = element<f32x4_any>(x, min(at + 4 * (u * kSelThreads + (int)threadIdx.x), n - 4));
+    for (int u = 0; u < kLoads; ++u) quad[u] = element<f32x4_any>(x + min(at, n - 4), min(4 * (u * kSelThreads + (int)threadIdx.x), max(0, n - 4 - at)));
   }
 };
 template <typename F>
 __device__ __forceinline__ void sweep_memory(const float* __restrict__ x, int n, Ahead& next, F f) {
 #pragma unroll 1
-  for (int at = 0; at < n; at += kStep) {
+  for (int at = 0;; at += kStep) {
+    const bool more = n - at > kStep;
     Batch v[2];
 #pragma unroll
     for (int e = 0; e < 2 * kBatch; ++e) v[e / kBatch][e % kBatch] = next.quad[e / 4][e % 4];
-    if (at + kStep < n) {
+    if (more) {
       next.load(x, n, at + kStep);
     } else {
 #pragma unroll
@@ -151,6 +153,7 @@ __device__ __forceinline__ void sweep_memory(const float* __restrict__ x, int n,
       }
       f(v[0], some);
     }
+    if (!more) return;
   }
 }
 
@@ -164,7 +167,7 @@ __device__ __forceinline__ void sweep_real(const float* __restrict__ x, int n, F
 #pragma unroll
     for (int e = 0; e < kBatch; ++e) {
       if (e >= some) break;
-      v[e] = element(x, min(at + e * kSelThreads + (int)threadIdx.x, n - 1));
+      v[e] = element(x + at, min(e * kSelThreads + (int)threadIdx.x, n - 1 - at));
     }
 #pragma unroll
     for (int e = 0; e < kBatch; ++e) {
@@ -665,7 +668,7 @@ __device__ __forceinline__ void chunk_counts(const ListJob& job, const float* __
   for (int c = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); c < nchunk; c += kSelWaves) {
     float v[kChunk / 64];
 #pragma unroll
-    for (int e = 0; e < kChunk / 64; ++e) v[e] = element(row, min(c * kChunk + e * 64 + lane, N - 1));
+    for (int e = 0; e < kChunk / 64; ++e) v[e] = element(row + c * kChunk, min(e * 64 + lane, N - 1 - c * kChunk));
     unsigned above = 0, at_cut = 0;
     if (c * kChunk >= lo && (c + 1) * kChunk <= hi) {
 #pragma unroll

@@ -356,3 +356,23 @@ def test_selection_of_a_short_batch_on_both_sides_of_the_size_of_its_queries(bat
     g = torch.Generator(device="cuda").manual_seed(batch)
     Q, K = (torch.randn(batch, h, N, D, generator=g, device="cuda").bfloat16() for h in (H, Hkv))
     _same_selection_as_the_separate_calls(ob.make_layer_desc(Q, K, 1, N - 1, 0, True), Q, K, 0, 0.3, 0.9, 256, 0, N)
+
+
+def test_keys_of_a_vector_beyond_two_to_the_thirty_scores():
+    """One head's scores are 4 bytes each: byte offsets past element 2^30 do not fit 32 bits.  Peaks and ties at the cut lie on
+    both sides of it, in the last elements too."""
+    N = (1 << 30) + 5001
+    g = torch.Generator(device="cuda").manual_seed(0)
+    a = torch.rand(1, 1, N, generator=g, device="cuda")
+    at = torch.cat([torch.tensor([0, 5, (1 << 30) - 1, 1 << 30, N - 1]), torch.randint(6, N - 1, (995,)),
+                    torch.randint((1 << 30) + 1, N - 1, (400,))]).unique().cuda()
+    peak, tie = at[::2], at[1::2]
+    a[0, 0, peak] = 2 + torch.rand(len(peak), generator=g, device="cuda")
+    a[0, 0, tie] = 1.5
+    n_tie = len(tie) // 2 + 1
+    budget = len(peak) + n_tie
+    d = _desc(1, 64, 0, 64)
+    d.n_tokens = d.vis_end = N
+    kv = ob.omni_select_kv(d, a, torch.tensor([budget], dtype=torch.int32, device="cuda"), budget)
+    want = torch.cat([peak, tie[:n_tie]]).sort().values
+    assert torch.equal(kv[0, 0].long(), want)
